@@ -199,7 +199,7 @@ int abft_gemm_bias(abft_ctx *ctx, const void *A, const void *B, const void *bias
 /* abft_gemm for callers that cannot allocate device memory: code under HIP graph capture, tight
  * serving loops, harnesses that forbid hipMalloc.  Same arguments (without a context), same
  * kernels, same results as abft_gemm; the workspace (checksum vectors, partial sums, tickets) is
- * a fixed array of about 3 MB inside the library's device image instead of the pools of a
+ * a fixed array of about 4 MB inside the library's device image instead of the pools of a
  * context, so the call allocates nothing, on the device or through any library.  Each GPU holds
  * its own copy of that array from the moment the library is loaded until the process ends; the
  * call uses the copy of the current device.  Limits (ABFT_EWORKSPACE beyond them):

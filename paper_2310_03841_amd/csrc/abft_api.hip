@@ -20,7 +20,7 @@ struct abft_ctx {
     bool bclean[2];         // slot is all zero
     uint32_t *pool_batch;   // per-batch scalars
     uint32_t *pool_cols;    // cc_pred
-    uint32_t *pool_obs;     // two regions of cc_obs | rc_obs | rc_pred | a_sum | a_max | cc_sto | rc_sto:
+    uint32_t *pool_obs;     // two regions of cc_obs | rc_obs | rc_pred | a_sum | a_max | cc_sto | rc_sto | cc_acc | rc_acc:
                             // protected GEMMs alternate between them; each must be clean before use
     size_t region_words;    // words per region
     int cur;                // region of the last protected GEMM
@@ -30,7 +30,7 @@ struct abft_ctx {
     int vcur;
     size_t vdirty[2];
     int32_t  *fix_tiles;
-    uint32_t *small;        // fix_count[4], cmp_ticket[4], group tickets of the finish kernel [64]
+    uint32_t *small;        // fix_count[4], cmp_ticket[4], group tickets of the item kernel [64], bias sum
     InjectArm arm;
     int last_hip;
     // what the context currently holds
@@ -82,10 +82,16 @@ extern "C" int abft_last_hip_error(const abft_ctx *ctx) { return ctx ? ctx->last
 // The device pools of a context, in 32-bit words, for a context that serves max_rows / max_cols /
 // max_depth (already rounded, see abft_create) / max_batch.
 constexpr int N_POOLS = 7;
+constexpr int SMALL_WORDS = 8 + 64 + 1;
+// one region of pool_obs; even, so that the doubles at its end stay aligned in both regions
+static constexpr size_t obs_region_words(size_t R, size_t Cn, size_t D, size_t Bt)
+{
+    return (2 * Cn + 3 * R + D + 2 * Bt + 1 + 2 * (Cn + R) + 1) / 2 * 2;
+}
 static constexpr size_t pool_total_words(size_t R, size_t Cn, size_t D, size_t Bt)
 {
-    return 2 * (D + Bt) + Bt * BATCH_WORDS + Cn + 2 * (2 * Cn + 3 * R + D + 2 * Bt) + 2 * (R + Cn) +
-           (size_t)MAX_FIX_TILES * 3 + (8 + 64);
+    return 2 * (D + Bt) + Bt * BATCH_WORDS + Cn + 2 * obs_region_words(R, Cn, D, Bt) + 2 * (R + Cn) +
+           (size_t)MAX_FIX_TILES * 3 + SMALL_WORDS;
 }
 static void pool_words(int64_t max_rows, int64_t max_cols, int64_t max_depth, int64_t max_batch, size_t words[N_POOLS])
 {
@@ -93,10 +99,10 @@ static void pool_words(int64_t max_rows, int64_t max_cols, int64_t max_depth, in
     words[0] = 2 * (D + Bt);                       // pool_depth
     words[1] = Bt * BATCH_WORDS;                   // pool_batch
     words[2] = Cn;                                 // pool_cols
-    words[3] = 2 * (2 * Cn + 3 * R + D + 2 * Bt);  // pool_obs
+    words[3] = 2 * obs_region_words(R, Cn, D, Bt); // pool_obs
     words[4] = 2 * (R + Cn);                       // pool_vobs
     words[5] = (size_t)MAX_FIX_TILES * 3;          // fix_tiles
-    words[6] = 8 + 64;                             // small
+    words[6] = SMALL_WORDS;                        // small
 }
 static void pool_slots(abft_ctx *c, void **slot[N_POOLS])
 {
@@ -109,7 +115,7 @@ static void start_clean(abft_ctx *c)
 {
     const size_t D = (size_t)c->cfg.max_depth, R = (size_t)c->cfg.max_rows, Cn = (size_t)c->cfg.max_cols,
                  Bt = (size_t)c->cfg.max_batch;
-    c->region_words = 2 * Cn + 3 * R + D + 2 * Bt;
+    c->region_words = obs_region_words(R, Cn, D, Bt);
     c->cur = 0;
     c->dirty[0] = c->dirty[1] = 0;
     c->vregion_words = R + Cn;
@@ -225,14 +231,19 @@ static void carve(const abft_ctx *c, int dt, const Shape &s, Workspace *w)
     w->rc_sto = w->cc_sto + bN;
     w->c_max = w->rc_sto + bM;
     w->zero_words = 2 * bN + 3 * bM + bK + 2 * (size_t)s.batch;
+    const size_t acc0 = (w->zero_words + 1) / 2 * 2;
+    w->cc_acc = reinterpret_cast<double *>(w->cc_obs + acc0);
+    w->rc_acc = w->cc_acc + bN;
+    // the general kernel adds up floating-point row and column sums of its tiles in doubles
+    if (dt != DT_I8 && !gemm_takes_fast(dt, s)) w->zero_words = acc0 + 2 * (bN + bM);
     w->cc_vobs = c->pool_vobs + (size_t)c->vcur * c->vregion_words;
     w->rc_vobs = w->cc_vobs + bN;
     w->fix_tiles = c->fix_tiles;
     w->fix_count = c->small;
     w->cmp_ticket = c->small + 4;
+    w->bias_sum = c->small + 8 + 64;
     w->bias = nullptr;
     w->a_given = w->amax_given = nullptr;
-    (void)dt;
 }
 
 static bool same_b(const abft_shape &x, const abft_shape &y)
@@ -354,8 +365,8 @@ extern "C" int abft_encode_b(abft_ctx *ctx, const void *B, abft_dtype dtype, con
     return ABFT_OK;
 }
 
-// The kernels of a protected GEMM, tiled path: pass over B (unless its encoding is cached), GEMM,
-// finish.  The call accumulates into the region the previous protected call did not use.  It is
+// The kernels of a protected GEMM, tiled path: pass over B (unless its encoding is cached; the general
+// kernel does it beside its tiles), GEMM, finish or check.  The call accumulates into the region the previous protected call did not use.  It is
 // clean unless a call failed half way; the region of the previous call is cleared by this
 // call's finish kernel.  So a call with a cached B checksum is two kernels: GEMM, finish.
 static int enqueue_tiled(abft_ctx *ctx, int dtype, bool cached, bool stored, const void *A, const void *B, void *C,
@@ -376,15 +387,20 @@ static int enqueue_tiled(abft_ctx *ctx, int dtype, bool cached, bool stored, con
     size_t stale = ctx->dirty[ctx->cur];
     if (gm && stale < w->zero_words) stale = w->zero_words;
     ctx->dirty[ctx->cur] = ctx->region_words;            // until everything below is enqueued
-    if (!cached) HIP_TRY(launch_encode_b(dtype, B, sh, *w, w->cc_obs, stale, st));
+    const bool fast = gemm_takes_fast(dtype, sh);
+    if (!cached && fast) HIP_TRY(launch_encode_b(dtype, B, sh, *w, w->cc_obs, stale, st));
     else if (stale) HIP_TRY(launch_zero(w->cc_obs, stale, st));
     if (ev) HIP_TRY(hipEventRecord(ev[1], st));
     ctx->sto_valid = false;
-    HIP_TRY(launch_gemm(dtype, true, stored, A, B, C, sh, *w, arm, st));
+    HIP_TRY(launch_gemm(dtype, true, stored, !cached, A, B, C, sh, *w, arm, v.counts, st));
     if (ctx->done_event && !gm) HIP_TRY(hipEventRecord(ctx->done_event, st));
     if (ev) HIP_TRY(hipEventRecord(ev[2], st));
+    auto finish = [&](uint32_t *z, size_t zw, uint32_t *z2, size_t z2w) {
+        return fast ? launch_finish(dtype, B, sh, *w, v, z, zw, z2, z2w, st)
+                    : launch_check(dtype, A, B, sh, *w, v, z, zw, z2, z2w, st);
+    };
     if (gm) {
-        HIP_TRY(launch_finish(dtype, B, sh, *w, v, nullptr, 0, nullptr, 0, st));
+        HIP_TRY(finish(nullptr, 0, nullptr, 0));
         ctx->dirty[ctx->cur] = w->zero_words;
     } else {
         const size_t prev_dirty = ctx->dirty[prev];
@@ -392,8 +408,7 @@ static int enqueue_tiled(abft_ctx *ctx, int dtype, bool cached, bool stored, con
         // the finish kernel also cleans the b slot that is not in use (for the next pass over B)
         const int other = ctx->bslot ^ 1;
         uint32_t *other_base = ctx->pool_depth + (size_t)other * ctx->bslot_words;
-        HIP_TRY(launch_finish(dtype, B, sh, *w, v, prev_base, prev_dirty, ctx->bclean[other] ? nullptr : other_base,
-                              ctx->bslot_words, st));
+        HIP_TRY(finish(prev_base, prev_dirty, ctx->bclean[other] ? nullptr : other_base, ctx->bslot_words));
         ctx->bclean[other] = true;
         ctx->dirty[prev] = 0;
         ctx->dirty[ctx->cur] = w->zero_words;
@@ -487,7 +502,7 @@ static int gemm_impl(abft_ctx *ctx, const void *A, const void *B, const void *bi
         ctx->arm.batch = -1;
         hipEvent_t *ev = (ctx->prof_ev && ctx->prof_n < ctx->prof_cap) ? ctx->prof_ev + 4 * ctx->prof_n : nullptr;
         if (ev) { HIP_TRY(hipEventRecord(ev[0], st)); HIP_TRY(hipEventRecord(ev[1], st)); }
-        HIP_TRY(launch_gemm(dtype, false, false, A, B, C, sh, w, arm, st));
+        HIP_TRY(launch_gemm(dtype, false, false, false, A, B, C, sh, w, arm, nullptr, st));
         if (ctx->done_event && !capturing(st)) HIP_TRY(hipEventRecord(ctx->done_event, st));
         if (ev) { HIP_TRY(hipEventRecord(ev[2], st)); HIP_TRY(hipEventRecord(ev[3], st)); ctx->prof_n++; }
         return ABFT_OK;

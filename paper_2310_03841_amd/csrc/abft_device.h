@@ -244,6 +244,19 @@ __device__ __forceinline__ float wave_max(float v)
     return v;
 }
 
+// Sum of the layer bias over its N entries, by the whole block (every thread gets the total).
+template <typename acc_t>
+__device__ __forceinline__ acc_t block_bias_sum(const uint32_t *bias, int N, acc_t *red4)
+{
+    acc_t v = acc_t(0);
+    for (int n = threadIdx.x; n < N; n += 256) v = add_t(v, from_word<acc_t>(bias[n]));
+    v = wave_sum(v);
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) red4[threadIdx.x >> 6] = v;
+    __syncthreads();
+    return add_t(add_t(red4[0], red4[1]), add_t(red4[2], red4[3]));
+}
+
 // Products of checksum values (integer: in Z/2^32).
 __device__ __forceinline__ int mul_t(int x, int y) { return (int)((uint32_t)x * (uint32_t)y); }
 __device__ __forceinline__ float mul_t(float x, float y) { return x * y; }

@@ -39,18 +39,22 @@ struct Workspace {
     // one region that must be zero before the protected GEMM, filled by its atomics:
     //   cc_obs [batch][N] | rc_obs [batch][M] | rc_pred [batch][M] | a_sum [batch][K] | a_max [batch]
     //   | cc_sto [batch][N] | rc_sto [batch][M] | c_max [batch]
+    //   | cc_acc [batch][N] | rc_acc [batch][M] (doubles; general kernel, floating point)
     uint32_t *cc_obs, *rc_obs;      // observed sums of C (epilogue)
     uint32_t *rc_pred;              // A (B e), from the operand slabs of A in LDS
     uint32_t *a_sum;                // a = e^T A, from the same slabs
     uint32_t *a_max;                // max|A| (float bits)
     uint32_t *cc_sto, *rc_sto;      // sums of C as stored (floating point, on request)
     uint32_t *c_max;                // max|C as stored| (float bits) [batch], formed with them
+    double *cc_acc, *rc_acc;        // observed sums of C while the tiles add to them; the check kernel
+                                    // rounds them into cc_obs, rc_obs
     size_t zero_words;              // words from cc_obs on
     uint32_t *cc_vobs, *rc_vobs;    // re-summed from stored C
     // correction
     int32_t  *fix_tiles;            // [MAX_FIX_TILES][3] (batch, tile row, tile col)
     uint32_t *fix_count;            // [4]: 0 tiles, 1 overflow flag, 2 ticket, 3 spare
-    uint32_t *cmp_ticket;           // [4] ticket and counts, then [64] first-level tickets of the finish kernel
+    uint32_t *cmp_ticket;           // [4] ticket and counts, then [64] first-level tickets of the item kernel
+    uint32_t *bias_sum;             // sum of the layer bias (general kernel, protected)
     // not workspace, but travels with it: the layer bias of the current call (device, [N], float or
     // int32 words; null = none).  Added to every row of the product before rounding and sums.
     const uint32_t *bias;
@@ -87,15 +91,22 @@ hipError_t launch_encode_b(int dt, const void *B, const Shape &s, const Workspac
                            size_t zero_words, hipStream_t st);
 // Largest K the protected path handles (the column sums of A's slabs are kept in LDS).
 int protect_max_k(int dt);
+// Whether the problem takes the fast kernel (a pass over B ahead of it, launch_finish behind it) or the
+// general one (launch_check behind it; the passes over A and B ride in its launch).
+bool gemm_takes_fast(int dt, const Shape &s);
 // protect: A-side checksums and observed sums are produced by the kernel (atomics into the
-// zeroed region of the workspace); launch_finish turns them into flags.
+// zeroed region of the workspace); launch_finish / launch_check turn them into flags.
 // stored_sums: also accumulate the row / column sums of the rounded values that are stored
-hipError_t launch_gemm(int dt, bool protect, bool stored_sums, const void *A, const void *B, void *C,
-                       const Shape &s, const Workspace &w, const InjectArm &arm, hipStream_t st);
+// encode_b, counts: general kernel, protected: form b and max|B| too; the counts it clears for launch_check
+hipError_t launch_gemm(int dt, bool protect, bool stored_sums, bool encode_b, const void *A, const void *B, void *C,
+                       const Shape &s, const Workspace &w, const InjectArm &arm, uint32_t *counts, hipStream_t st);
 // zero_ptr / zero_words: a region every block of the kernel helps to clear (may be null / 0)
 hipError_t launch_finish(int dt, const void *B, const Shape &s, const Workspace &w, const Verdict &v,
                          uint32_t *zero_ptr, size_t zero_words, uint32_t *zero2_ptr, size_t zero2_words,
                          hipStream_t st);
+// the same after the general kernel: both predictions, comparisons, flags and counts
+hipError_t launch_check(int dt, const void *A, const void *B, const Shape &s, const Workspace &w, const Verdict &v,
+                        uint32_t *zero_ptr, size_t zero_words, uint32_t *zero2_ptr, size_t zero2_words, hipStream_t st);
 // with_sto: a row / column also flags when the re-summed stored C differs from the stored-side
 // sums of the GEMM by more than STO_TOL_FACTOR * tau
 // zero_ptr / zero_words: a region every block of the kernel helps to clear (may be null / 0)

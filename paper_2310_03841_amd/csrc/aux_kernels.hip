@@ -10,6 +10,7 @@
 #include <mutex>
 
 #include "abft_device.h"
+#include "encode_pass.h"
 
 namespace abft {
 
@@ -75,153 +76,43 @@ hipError_t launch_zero(uint32_t *p, size_t nwords, hipStream_t st)
 // that reads A is done by the GEMM kernel on the slabs it holds in LDS (gemm_apass.h); what is
 // left here is the pass over B, which must be complete before that (A b needs all of b).  For a
 // weight it is done once, offline (remark (2) of the same paragraph).
-#ifndef ENC_UNROLL_N
-#define ENC_UNROLL_N 8
-#endif
-constexpr int ENC_UNROLL = ENC_UNROLL_N;     // independent 16-byte loads in flight per thread (B pass)
-#ifndef ENC_BATCHES
-#define ENC_BATCHES 2
-#endif
-// ---------------------------------------------------------------- B pass: b = B e, max|B|
-// The stored array has `rows` rows of `cols` elements.  reduce_rows = 1 (B stored N x K):
-// b[col] = sum over rows.  reduce_rows = 0 (B stored K x N): b[row] = sum over cols.
+// Pass over B as a kernel of its own (the general GEMM kernel runs the same pass beside its tiles).
 struct EncBArgs {
-    const uint8_t *X;
-    long ld, stride;      // elements
-    int rows, cols, K;
-    int reduce_rows;
-    int cw_log2;          // 16-byte chunk columns per block window (power of two <= 64)
-    int rpb;              // rows per block
-    int nwin, nrb;
-    uint32_t *sum;        // [batch][K]  accumulated with atomics: zero before the launch
-    uint32_t *max_acc;    // [batch]     max|B| as float bits, atomic max: zero before the launch
+    EncArgs e;
     uint32_t *zero_ptr;   // region every block helps to clear (the next kernel's atomics start at zero)
     size_t zero_words;
 };
 
 template <int DT>
-__global__ __launch_bounds__(256) void encode_b_kernel(EncBArgs e)
+__global__ __launch_bounds__(256) void encode_b_kernel(EncBArgs a)
 {
-    using T = Traits<DT>;
-    typedef typename T::acc_t acc_t;
-    constexpr int ES = T::ES, CE = 16 / ES;
-    __shared__ acc_t red[256 * CE];
-
+    __shared__ uint32_t red[256 * (16 / Traits<DT>::ES)];
     const int tid = threadIdx.x, bz = blockIdx.z;
     {
         const size_t nb = (size_t)gridDim.x * gridDim.z;
         const size_t bid = blockIdx.x + (size_t)gridDim.x * blockIdx.z;
-        for (size_t i = bid * 256 + tid; i < e.zero_words; i += nb * 256) e.zero_ptr[i] = 0u;
+        for (size_t i = bid * 256 + tid; i < a.zero_words; i += nb * 256) a.zero_ptr[i] = 0u;
     }
-    const int win = blockIdx.x % e.nwin, rb = blockIdx.x / e.nwin;
-    const int CW = 1 << e.cw_log2, RL = 256 >> e.cw_log2;
-    const int cx = tid & (CW - 1), ry = tid >> e.cw_log2;
-    const int col0 = (win * CW + cx) * CE;
-    const bool colok = col0 < e.cols;
-    const int nvalid = e.cols - col0;                        // elements of this chunk inside the row
-    const uint8_t *Xb = e.X + (long)bz * e.stride * ES;
-    const int rbeg = rb * e.rpb;
-    const int rend = min(rbeg + e.rpb, e.rows);
-    const int iters = (e.rpb + RL * ENC_UNROLL - 1) / (RL * ENC_UNROLL);
-
-    acc_t colacc[CE];
-#pragma unroll
-    for (int q = 0; q < CE; ++q) colacc[q] = T::zero();
-    float mx = 0.f;
-
-    for (int it = 0; it < iters; ++it) {
-        // a batch of independent loads first: the pass is bound by memory latency otherwise
-        i32x4 v[ENC_UNROLL];
-#pragma unroll
-        for (int u = 0; u < ENC_UNROLL; ++u) {
-            const int r = rbeg + ry + (it * ENC_UNROLL + u) * RL;
-            v[u] = i32x4{0, 0, 0, 0};
-            if (colok && r < rend) v[u] = *reinterpret_cast<const i32x4 *>(Xb + ((long)r * e.ld + col0) * ES);
-        }
-#pragma unroll
-        for (int u = 0; u < ENC_UNROLL; ++u) {
-            const int r = rbeg + ry + (it * ENC_UNROLL + u) * RL;
-            i32x4 w = v[u];
-            if (nvalid < CE) w = mask_chunk(w, nvalid > 0 ? nvalid * ES : 0);
-            acc_t s = T::zero();
-#pragma unroll
-            for (int q = 0; q < CE; ++q) {
-                acc_t x = T::elem(w, q);
-                if (!T::IS_INT) mx = fmaxf(mx, fabsf((float)x));
-                colacc[q] = add_t(colacc[q], x);
-                s = add_t(s, x);
-            }
-            if (!e.reduce_rows) {
-                s = seg_sum(s, CW);
-                if (cx == 0 && r < rend) atomic_add_word(e.sum + (long)bz * e.K + r, s);
-            }
-        }
-    }
-    if (e.reduce_rows) {
-#pragma unroll
-        for (int q = 0; q < CE; ++q) red[(ry * CW + cx) * CE + q] = colacc[q];
-        __syncthreads();
-        // one atomic per column, consecutive lanes on consecutive addresses
-        for (int c = tid; c < CW * CE; c += 256) {
-            const int col = win * CW * CE + c;
-            if (col < e.cols) {
-                acc_t t = red[c];
-                for (int y = 1; y < RL; ++y) t = add_t(t, red[y * CW * CE + c]);
-                atomic_add_word(e.sum + (long)bz * e.K + col, t);
-            }
-        }
-    }
-    if (!T::IS_INT) {
-        mx = wave_max(mx);
-        if ((tid & 63) == 0 && mx > 0.f) atomicMax(e.max_acc + bz, __float_as_uint(mx));
-    }
-}
-
-
-struct EncPlan { int cw_log2, nwin, rpb, nrb; };
-
-// windowed streaming pass over a rows x cols array (B pass, verify)
-static EncPlan plan_window(int rows, int cols, int chunk_elems)
-{
-    EncPlan p;
-    const int chunks = (cols + chunk_elems - 1) / chunk_elems;
-    // window width (power of two, 8..64 chunk columns): least padding, then widest
-    int best_lg = 3;
-    long best_waste = -1;
-    for (int lg = 3; lg <= 6; ++lg) {
-        const int CW = 1 << lg;
-        const long waste = (long)((chunks + CW - 1) / CW) * CW - chunks;
-        if (best_waste < 0 || waste <= best_waste) { best_waste = waste; best_lg = lg; }
-    }
-    p.cw_log2 = best_lg;
-    const int CW = 1 << best_lg, RL = 256 / CW;
-    p.nwin = (chunks + CW - 1) / CW;
-    // rows per block: ENC_BATCHES batches of ENC_UNROLL loads per thread, more when the matrix is
-    // tall: atomics that hit one cache line are served one after the other (tens of nanoseconds
-    // each), so fewer row blocks mean less waiting at the end of the pass
-    int rpb = RL * ENC_UNROLL * ENC_BATCHES;
-    while ((long)p.nwin * ((rows + rpb - 1) / rpb) > 640) rpb *= 2;
-    p.rpb = rpb;
-    p.nrb = (rows + rpb - 1) / rpb;
-    return p;
+    encode_block<DT>(a.e, blockIdx.x, bz, red);
 }
 
 hipError_t launch_encode_b(int dt, const void *B, const Shape &s, const Workspace &w, uint32_t *zero_ptr,
                            size_t zero_words, hipStream_t st)
 {
-    EncBArgs e;
+    EncBArgs a;
+    EncArgs &e = a.e;
     e.X = (const uint8_t *)B; e.ld = s.ldb; e.stride = s.sB; e.K = s.K;
     if (s.transB) { e.rows = s.N; e.cols = s.K; e.reduce_rows = 1; }
     else          { e.rows = s.K; e.cols = s.N; e.reduce_rows = 0; }
-    EncPlan p = plan_window(e.rows, e.cols, 16 / elem_size(dt));
+    const EncPlan p = plan_alone(e.rows, e.cols, 16 / elem_size(dt));
     e.cw_log2 = p.cw_log2; e.nwin = p.nwin; e.rpb = p.rpb; e.nrb = p.nrb;
     e.sum = w.b_sum; e.max_acc = w.b_max;
-    e.zero_ptr = zero_ptr; e.zero_words = zero_ptr ? zero_words : 0;
+    a.zero_ptr = zero_ptr; a.zero_words = zero_ptr ? zero_words : 0;
     dim3 grid((unsigned)(e.nwin * e.nrb), 1, (unsigned)s.batch);
     switch (dt) {
-    case DT_I8:   hipLaunchKernelGGL(encode_b_kernel<DT_I8>, grid, dim3(256), 0, st, e); break;
-    case DT_BF16: hipLaunchKernelGGL(encode_b_kernel<DT_BF16>, grid, dim3(256), 0, st, e); break;
-    case DT_F16:  hipLaunchKernelGGL(encode_b_kernel<DT_F16>, grid, dim3(256), 0, st, e); break;
+    case DT_I8:   hipLaunchKernelGGL(encode_b_kernel<DT_I8>, grid, dim3(256), 0, st, a); break;
+    case DT_BF16: hipLaunchKernelGGL(encode_b_kernel<DT_BF16>, grid, dim3(256), 0, st, a); break;
+    case DT_F16:  hipLaunchKernelGGL(encode_b_kernel<DT_F16>, grid, dim3(256), 0, st, a); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -357,15 +248,13 @@ hipError_t launch_compare(int dt, const Shape &s, const Workspace &w, const Verd
 }
 
 // ====================================================================== finish
-// Runs after the protected GEMM, when its atomics have completed a = e^T A, rc_pred = A b,
-// max|A| and the observed sums.  Column blocks form the column checksum prediction
-// cc_pred = a B (Sec. III-B.1: the product of the input-side checksum with the weight), a
-// matrix-vector product bound by one read of B, and compare it with cc_obs; row blocks compare
-// rc_pred with rc_obs; the last block to finish writes the counts and the status.
+// Runs after the fast GEMM kernel, when its atomics have completed a = e^T A, rc_pred = A b,
+// max|A| and the observed sums: forms the column checksum prediction cc_pred = a B (Sec. III-B.1: the
+// product of the input-side checksum with the weight) and compares both pairs; the last block to
+// finish writes the counts and the status.
 struct FinArgs {
     const uint8_t *B;
     long ldb, sB;
-    int transB;
     int M, N, K;
     const uint32_t *a_sum, *b_sum, *cc_obs, *rc_obs, *a_max;
     uint32_t *rc_pred;    // A b from the GEMM; with a bias the finish kernel adds sum(bias) in place
@@ -376,11 +265,9 @@ struct FinArgs {
     uint8_t *row_flag, *col_flag;
     uint32_t *counts;
     uint32_t *ticket;     // [3]: ticket, flagged rows, flagged cols (self-cleaning)
-    uint32_t *group_ticket;   // [FIN_MAX_BLOCKS / FIN_GROUP] first-level tickets (self-cleaning)
     int batch;
-    int lpr;              // B stored N x K: lanes along one row of B (8, 16, 32 or 64)
-    int ksplit;           // 1, or 4 (deep K, lpr = 64): the four waves share four rows of B, a quarter of K each
-    int col_blocks;       // units [0, col_blocks) of a batch item take columns, the rest rows
+    int ksplit;           // 1, or 4 (deep K): the four waves share FN_RW rows of B, a quarter of K each
+    int col_blocks;       // units per batch item
     uint32_t *zero_ptr;   // region every block helps to clear: what the previous protected GEMM of this
     size_t zero_words;    // context accumulated into, so that the next one finds it clean
     const uint32_t *b_max;   // max|B| of the b in use, float bits [batch]
@@ -388,256 +275,10 @@ struct FinArgs {
     size_t zero2_words;
 };
 
-// Sum of the layer bias over its N entries, by the whole block (every thread gets the total).
-template <typename acc_t>
-__device__ __forceinline__ acc_t block_bias_sum(const uint32_t *bias, int N, acc_t *red4)
-{
-    acc_t v = acc_t(0);
-    for (int n = threadIdx.x; n < N; n += 256) v = add_t(v, from_word<acc_t>(bias[n]));
-    v = wave_sum(v);
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) red4[threadIdx.x >> 6] = v;
-    __syncthreads();
-    return add_t(add_t(red4[0], red4[1]), add_t(red4[2], red4[3]));
-}
-
-constexpr int FIN_KY = 8;          // k lanes of a column block over a B stored K x N
-constexpr int FIN_MAX_BLOCKS = 1024;
-constexpr int FIN_GROUP = 16;          // blocks per first-level ticket
-
-// Work is cut into units: (batch item, block of columns) and (batch item, block of 256 rows).
-// A block takes units blockIdx.x, blockIdx.x + gridDim.x, ...: many small batch items (attention
-// heads) then cost few blocks, and few blocks matter because each ends on the same ticket.
-template <int DT>
-__global__ __launch_bounds__(256) void finish_kernel(FinArgs f)
-{
-    using T = Traits<DT>;
-    typedef typename T::acc_t acc_t;
-    constexpr int ES = T::ES, CE = 16 / ES;
-    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
-    __shared__ acc_t wred[4];
-    __shared__ acc_t kpart[4][4];
-    __shared__ unsigned wcnt[4][2];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int M = f.M, N = f.N, K = f.K;
-    {
-        const size_t nb = gridDim.x;
-        for (size_t i = (size_t)blockIdx.x * 256 + tid; i < f.zero_words; i += nb * 256) f.zero_ptr[i] = 0u;
-        for (size_t i = (size_t)blockIdx.x * 256 + tid; i < f.zero2_words; i += nb * 256) f.zero2_ptr[i] = 0u;
-    }
-    const int row_blocks = (M + 255) / 256;
-    const int upi = f.col_blocks + row_blocks;                 // units per batch item
-    const int units = upi * f.batch;                           // fits: checked by the launcher
-    unsigned nr_w = 0, nc_w = 0;                               // flagged rows / columns seen by this wave
-    acc_t sb = T::zero();                                      // sum of the bias
-    if (f.bias) sb = block_bias_sum<acc_t>(f.bias, N, wred);
-
-    for (int u = blockIdx.x; u < units; u += gridDim.x) {
-        const int bz = u / upi, blk = u - bz * upi;
-        const uint8_t *Bb = f.B + (long)bz * f.sB * ES;
-        const uint32_t *asum = f.a_sum + (long)bz * K;
-        float tol = 0.f;
-        if (!T::IS_INT) {
-            const float ma = __uint_as_float(f.a_max[bz]), mb = __uint_as_float(f.b_max[bz]);
-            tol = f.tau_override > 0.f ? f.tau_override : (1e-3f * (float)K) * ma * mb;
-            if (blk == 0 && tid == 0) {
-                f.maxabs[(long)bz * 2] = ma;
-                f.maxabs[(long)bz * 2 + 1] = mb;
-                f.tau[bz] = tol;
-            }
-        }
-        if (blk < f.col_blocks) {
-            if (f.transB) {
-                // B stored N x K: lpr lanes run along a row of B (K), a wave takes 64 / lpr rows at
-                // a time, four times.  The matching values of a come straight from memory, in
-                // flight together with B.
-                const int nch = (K + CE - 1) / CE;
-                const int lpr = f.lpr, rpw = 64 / lpr;
-                const int sub = lane / lpr, lc = lane % lpr;
-                const bool split = f.ksplit == 4;
-                // row of pass 0; pass j: + j * rpw.  Deep K: every wave takes the block's four rows
-                // and every fourth run of 64 chunks.
-                const int nb = split ? blk * 4 : blk * (16 * rpw) + wave * 4 * rpw + sub;
-                acc_t dot[4] = {T::zero(), T::zero(), T::zero(), T::zero()};
-                for (int ch = split ? lane + 64 * wave : lc; ch < nch; ch += split ? 256 : lpr) {
-                    i32x4 v[4], aw[CE / 4];
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const int n = nb + j * rpw;
-                        v[j] = i32x4{0, 0, 0, 0};
-                        if (n < N) v[j] = *reinterpret_cast<const i32x4 *>(Bb + ((long)n * f.ldb + ch * CE) * ES);
-                    }
-                    const int left = K - ch * CE;                       // >= 1
-                    if (left >= CE) {
-#pragma unroll
-                        for (int q4 = 0; q4 < CE / 4; ++q4) {
-                            // dword-aligned reads (the batch offset need not be a multiple of four words)
-                            const uint32_t *ap = asum + ch * CE + 4 * q4;
-                            aw[q4] = i32x4{(int)ap[0], (int)ap[1], (int)ap[2], (int)ap[3]};
-                        }
-                    } else {
-#pragma unroll
-                        for (int q4 = 0; q4 < CE / 4; ++q4)
-#pragma unroll
-                            for (int e = 0; e < 4; ++e)
-                                aw[q4][e] = (4 * q4 + e < left) ? (int)asum[ch * CE + 4 * q4 + e] : 0;
-                    }
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        i32x4 w = v[j];
-                        if (left < CE) w = mask_chunk(w, left * ES);
-#pragma unroll
-                        for (int q = 0; q < CE; ++q)
-                            dot[j] = add_t(dot[j], mul_t(T::elem(w, q), from_word<acc_t>((uint32_t)aw[q >> 2][q & 3])));
-                    }
-                }
-                if (lpr == 64) {
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) dot[j] = wave_sum(dot[j]);
-                } else {
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) dot[j] = seg_sum(dot[j], lpr);
-                }
-                if (split) {
-                    __syncthreads();                                    // previous unit done with kpart
-                    if (lane == 0) {
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) kpart[wave][j] = dot[j];
-                    }
-                    __syncthreads();
-#pragma unroll
-                    for (int j = 0; j < 4; ++j)
-                        dot[j] = add_t(add_t(kpart[0][j], kpart[1][j]), add_t(kpart[2][j], kpart[3][j]));
-                }
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    acc_t t = dot[j];
-                    const int n = nb + j * rpw;
-                    bool fl = false;
-                    if (lc == 0 && n < N && (!split || wave == 0)) {
-                        const long o = (long)bz * N + n;
-                        if (f.bias) t = add_t(t, mul_t((acc_t)M, from_word<acc_t>(f.bias[n])));
-                        f.cc_pred[o] = as_word(t);
-                        fl = mismatch<T::IS_INT>(f.cc_obs[o], as_word(t), f.tau_override_cols > 0.f ? f.tau_override_cols : tol);
-                        f.col_flag[o] = fl ? 1 : 0;
-                    }
-                    nc_w += __popcll(__ballot(fl));
-                }
-            } else {
-                // B stored K x N: a staged in LDS; 32 chunk columns per unit, FIN_KY lanes run along K
-                acc_t *al = reinterpret_cast<acc_t *>(lds);
-                __syncthreads();                                        // previous unit done with al / red
-                for (int k = tid; k < K; k += 256) al[k] = from_word<acc_t>(asum[k]);
-                __syncthreads();
-                acc_t *red = al + (K + 3) / 4 * 4;                      // [FIN_KY][32 * CE]
-                const int cx = tid & 31, ky = tid >> 5;
-                const int nst = (blk * 32 + cx) * CE;
-                const int left = N - nst;
-                acc_t colp[CE];
-#pragma unroll
-                for (int q = 0; q < CE; ++q) colp[q] = T::zero();
-                for (int k0 = ky; k0 < K; k0 += 4 * FIN_KY) {
-                    i32x4 v[4];
-#pragma unroll
-                    for (int uu = 0; uu < 4; ++uu) {
-                        const int k = k0 + uu * FIN_KY;
-                        v[uu] = i32x4{0, 0, 0, 0};
-                        if (k < K && left > 0) v[uu] = *reinterpret_cast<const i32x4 *>(Bb + ((long)k * f.ldb + nst) * ES);
-                    }
-#pragma unroll
-                    for (int uu = 0; uu < 4; ++uu) {
-                        const int k = k0 + uu * FIN_KY;
-                        if (k < K) {
-                            const acc_t ak = al[k];
-#pragma unroll
-                            for (int q = 0; q < CE; ++q) colp[q] = add_t(colp[q], mul_t(T::elem(v[uu], q), ak));
-                        }
-                    }
-                }
-#pragma unroll
-                for (int q = 0; q < CE; ++q) red[ky * 32 * CE + cx * CE + q] = colp[q];
-                __syncthreads();
-                // at most two columns per thread (int8: 512 columns per unit)
-                for (int c = tid; c < 32 * CE; c += 256) {
-                    const int n = blk * 32 * CE + c;
-                    bool fl = false;
-                    if (n < N) {
-                        acc_t t = red[c];
-#pragma unroll
-                        for (int y = 1; y < FIN_KY; ++y) t = add_t(t, red[y * 32 * CE + c]);
-                        if (f.bias) t = add_t(t, mul_t((acc_t)M, from_word<acc_t>(f.bias[n])));
-                        const long o = (long)bz * N + n;
-                        f.cc_pred[o] = as_word(t);
-                        fl = mismatch<T::IS_INT>(f.cc_obs[o], as_word(t), f.tau_override_cols > 0.f ? f.tau_override_cols : tol);
-                        f.col_flag[o] = fl ? 1 : 0;
-                    }
-                    nc_w += __popcll(__ballot(fl));
-                }
-            }
-        } else {
-            const int r = (blk - f.col_blocks) * 256 + tid;
-            bool fl = false;
-            if (r < M) {
-                const long o = (long)bz * M + r;
-                uint32_t rpw = f.rc_pred[o];
-                if (f.bias) { rpw = as_word(add_t(from_word<acc_t>(rpw), sb)); f.rc_pred[o] = rpw; }
-                fl = mismatch<T::IS_INT>(f.rc_obs[o], rpw, tol);
-                f.row_flag[o] = fl ? 1 : 0;
-            }
-            nr_w += __popcll(__ballot(fl));
-            if (blk == f.col_blocks) {
-                // scalar a . b (the single-number check value of Sec. III-B.1), by the first row unit
-                acc_t v = T::zero();
-                for (int k = tid; k < K; k += 256)
-                    v = add_t(v, mul_t(from_word<acc_t>(asum[k]), from_word<acc_t>(f.b_sum[(long)bz * K + k])));
-                v = wave_sum(v);
-                __syncthreads();                                        // wred free again
-                if (lane == 0) wred[wave] = v;
-                __syncthreads();
-                if (tid == 0)
-                    f.s_pred[bz] = as_word(add_t(add_t(add_t(wred[0], wred[1]), add_t(wred[2], wred[3])), mul_t((acc_t)M, sb)));
-            }
-        }
-    }
-    // flagged rows / columns of this block, then its ticket
-    if (lane == 0) { wcnt[wave][0] = nr_w; wcnt[wave][1] = nc_w; }
-    __syncthreads();
-    if (tid == 0) {
-        const unsigned nr = wcnt[0][0] + wcnt[1][0] + wcnt[2][0] + wcnt[3][0];
-        const unsigned nc = wcnt[0][1] + wcnt[1][1] + wcnt[2][1] + wcnt[3][1];
-        if (nr | nc) {
-            // rare: the counts must be at the coherence point before this block's ticket is, so
-            // fetch their old values and wait for them
-            unsigned o1 = 0, o2 = 0;
-            if (nr) o1 = atomicAdd(f.ticket + 1, nr);
-            if (nc) o2 = atomicAdd(f.ticket + 2, nc);
-            asm volatile("s_waitcnt vmcnt(0)" :: "v"(o1), "v"(o2) : "memory");
-        }
-        // Tickets in two levels (atomics on one word are served one after the other, ~12 ns each):
-        // the last block of a group of FIN_GROUP takes a ticket for the group.
-        const unsigned grp = blockIdx.x / FIN_GROUP, ngrp = (gridDim.x + FIN_GROUP - 1) / FIN_GROUP;
-        const unsigned gsize = min((unsigned)FIN_GROUP, gridDim.x - grp * FIN_GROUP);
-        bool last = false;
-        if (atomicAdd(f.group_ticket + grp, 1u) == gsize - 1) {
-            atomicExch(f.group_ticket + grp, 0u);
-            last = atomicAdd(f.ticket, 1u) == ngrp - 1;
-        }
-        if (last) {
-            const uint32_t r = atomicExch(f.ticket + 1, 0u), c = atomicExch(f.ticket + 2, 0u);
-            atomicExch(f.ticket, 0u);
-            f.counts[0] = r;
-            f.counts[1] = c;
-            f.counts[2] = status_of(r, c);
-            f.counts[3] = 0u;
-            f.counts[4] = status_of(r, c);
-        }
-    }
-}
-
-// The same step for a B stored N x K (a Linear layer's weight: the common case), arranged so that
-// a block's critical path is one round of loads, one reduction and one ticket: the kernel is bound
-// by latency, not by the 2 K N bytes it reads, so everything a block needs is requested before
-// anything is used.  A unit is (batch item, block of rows of B): each wave takes FN_RW rows of B
+// Runs after the fast GEMM kernel (B stored N x K), arranged so that a block's critical path is one
+// round of loads, one reduction and one ticket: the kernel is bound by latency, not by the 2 K N
+// bytes it reads, so everything a block needs is requested before anything is used.  A unit is
+// (batch item, block of rows of B): each wave takes FN_RW rows of B
 // with its lanes along K (deep K: the four waves share FN_RW rows, a quarter of K each), and the
 // unit also compares its share of the M rows.  One ticket per block; the last block writes counts.
 constexpr int FN_RW = 8;
@@ -819,7 +460,7 @@ hipError_t launch_finish(int dt, const void *B, const Shape &s, const Workspace 
     FinArgs f;
     f.b_max = w.b_max; f.zero2_ptr = zero2_ptr; f.zero2_words = zero2_ptr ? zero2_words : 0;
     f.zero_ptr = zero_ptr; f.zero_words = zero_ptr ? zero_words : 0;
-    f.B = (const uint8_t *)B; f.ldb = s.ldb; f.sB = s.sB; f.transB = s.transB;
+    f.B = (const uint8_t *)B; f.ldb = s.ldb; f.sB = s.sB;
     f.M = s.M; f.N = s.N; f.K = s.K;
     f.a_sum = w.a_given ? w.a_given : w.a_sum;
     f.b_sum = w.b_sum; f.rc_pred = w.rc_pred; f.cc_obs = w.cc_obs; f.rc_obs = w.rc_obs;
@@ -827,39 +468,309 @@ hipError_t launch_finish(int dt, const void *B, const Shape &s, const Workspace 
     f.a_max = (w.a_given && w.amax_given) ? w.amax_given : w.a_max; f.cc_pred = w.cc_pred; f.s_pred = w.s_pred; f.maxabs = w.maxabs; f.tau = w.tau;
     f.tau_override = v.tau_override; f.tau_override_cols = v.tau_override_cols;
     f.row_flag = v.row_flag; f.col_flag = v.col_flag; f.counts = v.counts; f.ticket = w.cmp_ticket;
-    f.group_ticket = w.cmp_ticket + 4;
     const int ce = 16 / elem_size(dt);
     const int nch = (s.K + ce - 1) / ce;
     f.batch = s.batch;
-    if (s.transB) {
-        // deep K (more than one trip of 128 chunks per row): the waves of a block share its rows
-        f.ksplit = nch > 128 ? 4 : 1;
-        f.lpr = 64;
-        const int rpb = f.ksplit == 4 ? FN_RW : 4 * FN_RW;
-        f.col_blocks = (s.N + rpb - 1) / rpb;
-        const long units = (long)f.col_blocks * s.batch;
-        if (units > 0x7FFFFFFFL) return hipErrorInvalidValue;
-        dim3 grid((unsigned)(units < 512 ? units : 512), 1, 1);
-        switch (dt) {
-        case DT_I8:   hipLaunchKernelGGL(finish_nk_kernel<DT_I8>, grid, dim3(256), 0, st, f); break;
-        case DT_BF16: hipLaunchKernelGGL(finish_nk_kernel<DT_BF16>, grid, dim3(256), 0, st, f); break;
-        case DT_F16:  hipLaunchKernelGGL(finish_nk_kernel<DT_F16>, grid, dim3(256), 0, st, f); break;
-        default: return hipErrorInvalidValue;
-        }
-        return hipGetLastError();
-    }
-    f.lpr = nch <= 8 ? 8 : (nch <= 16 ? 16 : (nch <= 32 ? 32 : 64));
-    f.ksplit = 1;
-    f.col_blocks = (s.N + 32 * ce - 1) / (32 * ce);
-    const int row_blocks = (s.M + 255) / 256;
-    const size_t smem = ((size_t)(s.K + 3) / 4 * 4 + (size_t)FIN_KY * 32 * ce) * 4;
-    const long units = (long)(f.col_blocks + row_blocks) * s.batch;
+    // deep K (more than one trip of 128 chunks per row): the waves of a block share its rows
+    f.ksplit = nch > 128 ? 4 : 1;
+    const int rpb = f.ksplit == 4 ? FN_RW : 4 * FN_RW;
+    f.col_blocks = (s.N + rpb - 1) / rpb;
+    const long units = (long)f.col_blocks * s.batch;
     if (units > 0x7FFFFFFFL) return hipErrorInvalidValue;
-    dim3 grid((unsigned)(units < FIN_MAX_BLOCKS ? units : FIN_MAX_BLOCKS), 1, 1);
+    dim3 grid((unsigned)(units < 512 ? units : 512), 1, 1);
     switch (dt) {
-    case DT_I8:   hipLaunchKernelGGL(finish_kernel<DT_I8>, grid, dim3(256), smem, st, f); break;
-    case DT_BF16: hipLaunchKernelGGL(finish_kernel<DT_BF16>, grid, dim3(256), smem, st, f); break;
-    case DT_F16:  hipLaunchKernelGGL(finish_kernel<DT_F16>, grid, dim3(256), smem, st, f); break;
+    case DT_I8:   hipLaunchKernelGGL(finish_nk_kernel<DT_I8>, grid, dim3(256), 0, st, f); break;
+    case DT_BF16: hipLaunchKernelGGL(finish_nk_kernel<DT_BF16>, grid, dim3(256), 0, st, f); break;
+    case DT_F16:  hipLaunchKernelGGL(finish_nk_kernel<DT_F16>, grid, dim3(256), 0, st, f); break;
+    default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+// ======================================================================= check
+// Runs after the general GEMM kernel (gemm_tile.hip), whose launch has completed a = e^T A, b = B e,
+// the two maxima and the observed sums.  Forms both predictions of Sec. III-B.1, cc_pred = a B and
+// rc_pred = A b, each a matrix-vector product over one read of its operand, compares and flags.
+//
+// Bound by latency: a workgroup's critical path is one round of loads and one reduction.  Units of a
+// batch item: row units of A, column units of B (a B stored N x K is the same product as A b), one
+// unit for the scalar a.b.  There is no last block: the GEMM launch has cleared the counts, and only
+// waves that saw a mismatch touch them (report_flags).
+struct ChkArgs {
+    const uint8_t *A, *B;
+    long lda, sA, ldb, sB;
+    int transB;
+    int M, N, K, batch;
+    const uint32_t *a_sum, *b_sum, *a_max, *b_max;
+    uint32_t *cc_obs, *rc_obs;       // integers: complete; floating point: written here from
+    const double *cc_acc, *rc_acc;   // what the tiles added up
+    const uint32_t *bias; // layer bias [N] or null: cc_pred gains M bias[n], rc_pred sum(bias), a.b M sum(bias)
+    const uint32_t *bias_sum;   // its sum, formed by the GEMM launch
+    uint32_t *cc_pred, *rc_pred, *s_pred;
+    float *maxabs, *tau;
+    float tau_override, tau_override_cols;
+    uint8_t *row_flag, *col_flag;
+    uint32_t *counts;
+    int row_units, col_units;
+    int ksplit;           // 1, or 4 (deep K): the four waves of a unit share its rows, a quarter of K each
+    uint32_t *zero_ptr;   // regions every block helps to clear (see FinArgs)
+    size_t zero_words;
+    uint32_t *zero2_ptr;
+    size_t zero2_words;
+};
+
+// A wave found nr rows and nc columns that disagree.  counts[0], counts[1] gain them, counts[2] and
+// counts[4] become the status: localised once both sides have flags, suspect while one has.  A wave
+// adds first and looks second, so of the waves that flag different sides at least one sees both;
+// it sets "localised" whatever is there, while "suspect" only replaces "clean".
+__device__ __forceinline__ void report_flags(uint32_t *counts, unsigned nr, unsigned nc)
+{
+    unsigned o1 = 0, o2 = 0;
+    if (nr) o1 = atomicAdd(counts, nr);
+    if (nc) o2 = atomicAdd(counts + 1, nc);
+    asm volatile("s_waitcnt vmcnt(0)" :: "v"(o1), "v"(o2) : "memory");
+    const unsigned r = atomicAdd(counts, 0u), c = atomicAdd(counts + 1, 0u);
+    const uint32_t st = status_of(r, c);
+    for (int q = 2; q <= 4; q += 2) {
+        if (st == 1u) atomicExch(counts + q, 1u);
+        else atomicCAS(counts + q, 0u, st);
+    }
+}
+
+// Dots of RW rows of a K-contiguous operand with a vector of K words: lanes along K, two chunks per
+// lane and trip, everything of a trip in flight.  split: this wave takes every fourth run of 128
+// chunks.  Every lane returns the wave's share of all RW dots.
+template <int DT, int RW>
+__device__ __forceinline__ void row_dots(const uint8_t *X, long ld, int row0, int rows, int K, const uint32_t *vec,
+                                         bool split, typename Traits<DT>::acc_t (&dot)[RW])
+{
+    using T = Traits<DT>;
+    typedef typename T::acc_t acc_t;
+    constexpr int ES = T::ES, CE = 16 / ES;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int nch = (K + CE - 1) / CE;
+    const bool vec16 = ((uintptr_t)vec & 15u) == 0;              // 16-byte loads of the vector are aligned
+#pragma unroll
+    for (int j = 0; j < RW; ++j) dot[j] = T::zero();
+    for (int ch0 = split ? wave * 128 : 0; ch0 < nch; ch0 += split ? 512 : 128) {
+        i32x4 v[RW][2], aw[2][CE / 4];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int ch = ch0 + 64 * h + lane;
+            const bool in = ch < nch;
+#pragma unroll
+            for (int j = 0; j < RW; ++j) {
+                v[j][h] = i32x4{0, 0, 0, 0};
+                if (in && row0 + j < rows) v[j][h] = *reinterpret_cast<const i32x4 *>(X + ((long)(row0 + j) * ld + (long)ch * CE) * ES);
+            }
+            const int left = K - ch * CE;
+#pragma unroll
+            for (int q4 = 0; q4 < CE / 4; ++q4) {
+                aw[h][q4] = i32x4{0, 0, 0, 0};
+                if (in) {
+                    const uint32_t *ap = vec + ch * CE + 4 * q4;
+                    if (vec16 && left >= CE) aw[h][q4] = *reinterpret_cast<const i32x4 *>(ap);
+                    else {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) aw[h][q4][e] = (4 * q4 + e < left) ? (int)ap[e] : 0;
+                    }
+                }
+            }
+        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int left = K - (ch0 + 64 * h + lane) * CE;
+#pragma unroll
+            for (int j = 0; j < RW; ++j) {
+                i32x4 w = v[j][h];
+                if (left < CE) w = mask_chunk(w, left > 0 ? left * ES : 0);
+#pragma unroll
+                for (int q = 0; q < CE; ++q)
+                    dot[j] = add_t(dot[j], mul_t(T::elem(w, q), from_word<acc_t>((uint32_t)aw[h][q >> 2][q & 3])));
+            }
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < RW; ++j) dot[j] = wave_sum(dot[j]);
+}
+
+constexpr int CHK_KN_LANES = 4;        // chunk columns of a unit over a B stored K x N (64 lanes run along k)
+
+template <int DT, int RW>
+__global__ __launch_bounds__(256) void check_kernel(ChkArgs f)
+{
+    using T = Traits<DT>;
+    typedef typename T::acc_t acc_t;
+    constexpr int ES = T::ES, CE = 16 / ES;
+    __shared__ acc_t wred[4];
+    __shared__ acc_t part[4][CHK_KN_LANES * CE > RW ? CHK_KN_LANES * CE : RW];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int M = f.M, N = f.N, K = f.K;
+    const int upi = f.row_units + f.col_units + 1;              // units per batch item
+    const int bz = blockIdx.x / upi, u = blockIdx.x - bz * upi;
+    const uint32_t *asum = f.a_sum + (long)bz * K, *bsum = f.b_sum + (long)bz * K;
+    {
+        const size_t nb = gridDim.x;
+        for (size_t i = (size_t)blockIdx.x * 256 + tid; i < f.zero_words; i += nb * 256) f.zero_ptr[i] = 0u;
+        for (size_t i = (size_t)blockIdx.x * 256 + tid; i < f.zero2_words; i += nb * 256) f.zero2_ptr[i] = 0u;
+    }
+    float tol = 0.f;
+    if (!T::IS_INT) {
+        const float ma = __uint_as_float(f.a_max[bz]), mb = __uint_as_float(f.b_max[bz]);
+        tol = f.tau_override > 0.f ? f.tau_override : (1e-3f * (float)K) * ma * mb;
+        if (u == upi - 1 && tid == 0) {
+            f.maxabs[(long)bz * 2] = ma;
+            f.maxabs[(long)bz * 2 + 1] = mb;
+            f.tau[bz] = tol;
+        }
+    }
+    const float tol_c = f.tau_override_cols > 0.f ? f.tau_override_cols : tol;
+    if (u == upi - 1) {
+        // scalar a . b (the single-number check value of Sec. III-B.1)
+        acc_t v = T::zero();
+        for (int k = tid; k < K; k += 256) v = add_t(v, mul_t(from_word<acc_t>(asum[k]), from_word<acc_t>(bsum[k])));
+        const acc_t sb = f.bias ? from_word<acc_t>(*f.bias_sum) : T::zero();
+        v = wave_sum(v);
+        if (lane == 0) wred[wave] = v;
+        __syncthreads();
+        if (tid == 0)
+            f.s_pred[bz] = as_word(add_t(add_t(add_t(wred[0], wred[1]), add_t(wred[2], wred[3])), mul_t((acc_t)M, sb)));
+        return;
+    }
+    const bool is_row = u < f.row_units;
+    if (is_row || f.transB) {
+        // A b against the row sums of C, or a B (rows of B are columns of C) against the column sums
+        const int unit = is_row ? u : u - f.row_units;
+        const bool split = f.ksplit == 4;
+        const int rows = is_row ? M : N;
+        const int row0 = split ? unit * RW : (unit * 4 + wave) * RW;
+        const bool mine_ok = lane < RW && row0 + lane < rows && (!split || wave == 0);
+        const long o = (long)bz * rows + row0 + lane;
+        // what the dots are compared with, requested first
+        uint32_t obs = 0;
+        acc_t add = T::zero();
+        if (mine_ok) obs = T::IS_INT ? (is_row ? f.rc_obs : f.cc_obs)[o] : __float_as_uint((float)(is_row ? f.rc_acc : f.cc_acc)[o]);
+        if (f.bias && mine_ok)
+            add = is_row ? from_word<acc_t>(*f.bias_sum) : mul_t((acc_t)M, from_word<acc_t>(f.bias[row0 + lane]));
+        acc_t dot[RW];
+        row_dots<DT, RW>(is_row ? f.A + (long)bz * f.sA * ES : f.B + (long)bz * f.sB * ES, is_row ? f.lda : f.ldb, row0, rows, K,
+                         is_row ? bsum : asum, split, dot);
+        if (split) {
+            if (lane == 0) {
+#pragma unroll
+                for (int j = 0; j < RW; ++j) part[wave][j] = dot[j];
+            }
+            __syncthreads();
+#pragma unroll
+            for (int j = 0; j < RW; ++j) dot[j] = add_t(add_t(part[0][j], part[1][j]), add_t(part[2][j], part[3][j]));
+        }
+        acc_t mine = dot[0];
+#pragma unroll
+        for (int j = 1; j < RW; ++j) mine = lane == j ? dot[j] : mine;
+        mine = add_t(mine, add);
+        bool fl = false;
+        if (mine_ok) {
+            (is_row ? f.rc_pred : f.cc_pred)[o] = as_word(mine);
+            if (!T::IS_INT) (is_row ? f.rc_obs : f.cc_obs)[o] = obs;
+            fl = mismatch<T::IS_INT>(obs, as_word(mine), is_row ? tol : tol_c);
+            (is_row ? f.row_flag : f.col_flag)[o] = fl ? 1 : 0;
+        }
+        const unsigned nf = __popcll(__ballot(fl));
+        if (nf && lane == 0) report_flags(f.counts, is_row ? nf : 0u, is_row ? 0u : nf);
+    } else {
+        // a B over a B stored K x N: CHK_KN_LANES chunk columns, 64 lanes along k
+        const int cx = tid % CHK_KN_LANES, ky = tid / CHK_KN_LANES;
+        const uint8_t *Bb = f.B + (long)bz * f.sB * ES;
+        const int col0 = (u - f.row_units) * CHK_KN_LANES * CE, nst = col0 + cx * CE;
+        const bool in = nst < N;
+        const int n = col0 + tid;                               // this thread's column in the end
+        const bool mine_ok = tid < CHK_KN_LANES * CE && n < N;
+        uint32_t obs = 0;
+        acc_t add = T::zero();
+        if (mine_ok) {
+            obs = T::IS_INT ? f.cc_obs[(long)bz * N + n] : __float_as_uint((float)f.cc_acc[(long)bz * N + n]);
+            if (f.bias) add = mul_t((acc_t)M, from_word<acc_t>(f.bias[n]));
+        }
+        acc_t colp[CE];
+#pragma unroll
+        for (int q = 0; q < CE; ++q) colp[q] = T::zero();
+        constexpr int U = 8;
+        for (int k0 = ky; k0 < K; k0 += 64 * U) {
+            i32x4 v[U];
+            acc_t ak[U];
+#pragma unroll
+            for (int uu = 0; uu < U; ++uu) {
+                const int k = k0 + 64 * uu;
+                v[uu] = i32x4{0, 0, 0, 0};
+                ak[uu] = T::zero();
+                if (k < K && in) {
+                    v[uu] = *reinterpret_cast<const i32x4 *>(Bb + ((long)k * f.ldb + nst) * ES);
+                    ak[uu] = from_word<acc_t>(asum[k]);
+                }
+            }
+#pragma unroll
+            for (int uu = 0; uu < U; ++uu) {
+                if (k0 + 64 * uu < K) {
+#pragma unroll
+                    for (int q = 0; q < CE; ++q) colp[q] = add_t(colp[q], mul_t(T::elem(v[uu], q), ak[uu]));
+                }
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < CE; ++q) {
+            acc_t t = colp[q];
+            t = add_t(t, dpp_get<0x124>(t));                    // row_ror:4 inside 16 lanes
+            t = add_t(t, dpp_get<0x128>(t));                    // row_ror:8
+            t = add_xor16(t);
+            t = add_xor32(t);
+            if (lane < CHK_KN_LANES) part[wave][cx * CE + q] = t;
+        }
+        __syncthreads();
+        bool fl = false;
+        if (mine_ok) {
+            const acc_t t = add_t(add_t(add_t(part[0][tid], part[1][tid]), add_t(part[2][tid], part[3][tid])), add);
+            const long o = (long)bz * N + n;
+            f.cc_pred[o] = as_word(t);
+            if (!T::IS_INT) f.cc_obs[o] = obs;
+            fl = mismatch<T::IS_INT>(obs, as_word(t), tol_c);
+            f.col_flag[o] = fl ? 1 : 0;
+        }
+        const unsigned nf = __popcll(__ballot(fl));
+        if (nf && lane == 0) report_flags(f.counts, 0u, nf);
+    }
+}
+
+hipError_t launch_check(int dt, const void *A, const void *B, const Shape &s, const Workspace &w, const Verdict &v,
+                        uint32_t *zero_ptr, size_t zero_words, uint32_t *zero2_ptr, size_t zero2_words, hipStream_t st)
+{
+    constexpr int RW = 4;                                       // rows per wave
+    ChkArgs f;
+    f.A = (const uint8_t *)A; f.B = (const uint8_t *)B;
+    f.lda = s.lda; f.sA = s.sA; f.ldb = s.ldb; f.sB = s.sB; f.transB = s.transB;
+    f.M = s.M; f.N = s.N; f.K = s.K; f.batch = s.batch;
+    f.a_sum = w.a_given ? w.a_given : w.a_sum;
+    f.a_max = (w.a_given && w.amax_given) ? w.amax_given : w.a_max;
+    f.b_sum = w.b_sum; f.b_max = w.b_max; f.cc_obs = w.cc_obs; f.rc_obs = w.rc_obs;
+    f.cc_acc = w.cc_acc; f.rc_acc = w.rc_acc;
+    f.bias = w.bias; f.bias_sum = w.bias_sum;
+    f.cc_pred = w.cc_pred; f.rc_pred = w.rc_pred; f.s_pred = w.s_pred; f.maxabs = w.maxabs; f.tau = w.tau;
+    f.tau_override = v.tau_override; f.tau_override_cols = v.tau_override_cols;
+    f.row_flag = v.row_flag; f.col_flag = v.col_flag; f.counts = v.counts;
+    f.zero_ptr = zero_ptr; f.zero_words = zero_ptr ? zero_words : 0;
+    f.zero2_ptr = zero2_ptr; f.zero2_words = zero2_ptr ? zero2_words : 0;
+    const int ce = 16 / elem_size(dt);
+    const int nch = (s.K + ce - 1) / ce;
+    f.ksplit = nch > 128 ? 4 : 1;                               // more than one trip of 128 chunks per row
+    const int rpb = f.ksplit == 4 ? RW : 4 * RW;
+    f.row_units = (s.M + rpb - 1) / rpb;
+    f.col_units = s.transB ? (s.N + rpb - 1) / rpb : (s.N + CHK_KN_LANES * ce - 1) / (CHK_KN_LANES * ce);
+    const long units = ((long)f.row_units + f.col_units + 1) * s.batch;
+    if (units > 0x7FFFFFFFL) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)units, 1, 1);
+    switch (dt) {
+    case DT_I8:   hipLaunchKernelGGL((check_kernel<DT_I8, RW>), grid, dim3(256), 0, st, f); break;
+    case DT_BF16: hipLaunchKernelGGL((check_kernel<DT_BF16, RW>), grid, dim3(256), 0, st, f); break;
+    case DT_F16:  hipLaunchKernelGGL((check_kernel<DT_F16, RW>), grid, dim3(256), 0, st, f); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -1004,7 +915,7 @@ hipError_t launch_verify_sums(int dt, const void *C, const Shape &s, const Works
     a.gate = gated ? w.fix_count : nullptr;
     a.C = (const uint8_t *)C; a.ldc = s.ldc; a.sC = s.sC; a.M = s.M; a.N = s.N;
     a.cc_vobs = w.cc_vobs; a.rc_vobs = w.rc_vobs;
-    EncPlan plan = plan_window(s.M, s.N, 16 / out_size(dt));
+    const EncPlan plan = plan_alone(s.M, s.N, 16 / out_size(dt));
     a.cw_log2 = plan.cw_log2; a.nwin = plan.nwin; a.rpb = plan.rpb; a.nrb = plan.nrb;
     dim3 grid((unsigned)(a.nwin * a.nrb), 1, (unsigned)s.batch);
     switch (dt) {

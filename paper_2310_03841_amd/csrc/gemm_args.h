@@ -1,5 +1,6 @@
 // Kernel arguments shared by the GEMM kernels of libabft.
 #pragma once
+#include <hip/hip_runtime.h>
 #include <stdint.h>
 
 namespace abft {
@@ -15,6 +16,7 @@ struct GemmArgs {
     int inj_b, inj_row, inj_col, inj_bit;         // armed accumulator flip (inj_b < 0: none)
     // protected launches: all of these are accumulated with atomics and start at zero
     uint32_t *cc_obs, *rc_obs;                    // observed sums of C        [batch][N], [batch][M]
+    double *cc_acc, *rc_acc;                      // general kernel, floating point: what its tiles add to instead
     uint32_t *rc_pred;                            // A (B e)                    [batch][M]
     uint32_t *a_sum;                              // e^T A                      [batch][K]
     uint32_t *a_max;                              // max|A| as float bits       [batch]
@@ -26,6 +28,22 @@ struct GemmArgs {
     const uint32_t *b_sum;                        // B e, complete before the launch [batch][K]
     int mul24_ok;                                 // int8: |b| < 2^23, 24-bit multiplies are exact
 };
+
+// Workgroup -> tile inside a region of tiles_m x tiles_n tiles: consecutive ids of one XCD
+// (workgroups are dealt to the 8 XCDs round-robin) walk GROUP_M tile rows, then the next column,
+// so the workgroups that share an L2 work on a compact group of tiles.
+__device__ __forceinline__ void map_tile(int bid, int nb, int tiles_m, int tiles_n, int *tm, int *tn)
+{
+    constexpr int GROUP_M = 4;          // measured against 2, 3, 6, 8, 16: best or equal on every Linear shape
+    const int q = nb >> 3, r = nb & 7, xcd = bid & 7;
+    const int L = xcd * q + (xcd < r ? xcd : r) + (bid >> 3);
+    const int per_group = GROUP_M * tiles_n;
+    const int grp = L / per_group, in_grp = L % per_group;
+    const int first_m = grp * GROUP_M;
+    const int gsz = (tiles_m - first_m) < GROUP_M ? (tiles_m - first_m) : GROUP_M;
+    *tm = first_m + in_grp % gsz;
+    *tn = in_grp / gsz;
+}
 
 // Fast path (gemm_fast.hip): B stored N x K, K a whole number of 128-byte slabs.
 bool gemm_fast_eligible(int dt, int M, int N, int K, bool transB, long lda, long ldb);

@@ -311,22 +311,6 @@ __device__ __forceinline__ void fast_tile(const GemmArgs &g, uint8_t *smem, int 
     gemm_epilogue<DT, BM, BN, PROT>(g, acc, smem, m0, n0, bz, ep);
 }
 
-// Workgroup -> tile inside a region of tiles_m x tiles_n tiles: consecutive ids of one XCD
-// (workgroups are dealt to the 8 XCDs round-robin) walk GROUP_M tile rows, then the next column,
-// so the workgroups that share an L2 work on a compact group of tiles.
-__device__ __forceinline__ void map_tile(int bid, int nb, int tiles_m, int tiles_n, int *tm, int *tn)
-{
-    constexpr int GROUP_M = 4;          // measured against 2, 3, 6, 8, 16: best or equal on every Linear shape
-    const int q = nb >> 3, r = nb & 7, xcd = bid & 7;
-    const int L = xcd * q + (xcd < r ? xcd : r) + (bid >> 3);
-    const int per_group = GROUP_M * tiles_n;
-    const int grp = L / per_group, in_grp = L % per_group;
-    const int first_m = grp * GROUP_M;
-    const int gsz = (tiles_m - first_m) < GROUP_M ? (tiles_m - first_m) : GROUP_M;
-    *tm = first_m + in_grp % gsz;
-    *tn = in_grp / gsz;
-}
-
 // The grid mixes two tile shapes against wave quantisation: 256 x 256 tiles cover the first
 // big_rows rows, 128 x 256 tiles the rest; how many of each is chosen by playing the dispatch
 // through (choose_big_rows).  (600 big tiles on 256 CUs would be three rounds for 2.34 rounds

@@ -1,0 +1,611 @@
+// Protected GEMM for gfx950, every shape the other two GEMM kernels do not take: problems of a few
+// tiles, ragged K, B stored K x N.  C = A B with the observed row and column sums of C taken from
+// the accumulators on their way out (epilogue fusion: Sec. IV-C memory paragraph, Sec. V
+// "Optimizations" (2)).
+//
+// What bounds these problems is not arithmetic or bandwidth but the chain of latencies of a call.
+// So the input-side vectors a = e^T A and b = B e, which depend on nothing, are formed by extra
+// workgroups of the same launch, beside the tiles, instead of by a kernel of their own ahead of it;
+// both predictions wait for the check kernel behind the launch (check_kernel, aux_kernels.hip).  A
+// call is two launches whatever is cached.  (Before: pass over B, GEMM with the pass over A inside
+// its main loop, finish; 197 x 768 x 768 int8 25.4 us, of which 5.2 + 14.0 + 7.8 in the kernels.)
+//
+// Tile: BM x BN by four waves of (BM/2) x (BN/2), 32 x 32 MFMA blocks.  K advances in slabs of 128
+// bytes per row of A.  Slabs go from global memory straight into LDS (global_load_lds_dwordx4),
+// NS buffers deep, so NS - 1 slabs are in flight while one is multiplied; one barrier per slab.
+// The fragments of slab s are read while the MFMAs of slab s - 1 run (two register sets).
+//
+// LDS: rows of 128 bytes as eight 16-byte chunks, chunk c of row r in slot c ^ ((r >> 1) & 7)
+// (sixteen consecutive rows of a fragment read then fall on sixteen different 16-byte bank groups).
+// B stored K x N keeps its own orientation in LDS and is transposed on the way to the matrix cores by
+// the LDS transpose reads of gfx950 (ds_read_b64_tr_b16 / _b8: sixteen lanes fetch 4 x 16 (8 x 16)
+// elements as rows of k and receive columns); its swizzle puts the rows of one such read on
+// different banks.  Direct loads land where the lane order says, so every swizzle is applied by
+// choosing which global chunk a lane fetches.
+//
+// Edges: rows and columns past the problem fetch the last valid ones; what they produce is never
+// stored or summed.  Past the end of K the fragments of the last slab are cleared in registers.
+#include "abft_device.h"
+#include "encode_pass.h"
+#include "gemm_args.h"
+#include "gemm_epilogue.h"
+
+namespace abft {
+
+typedef const __attribute__((address_space(1))) void *tile_gas_ptr;
+typedef __attribute__((address_space(3))) void *tile_las_ptr;
+
+struct TileArgs {
+    GemmArgs g;
+    int n_extra;                  // workgroups [0, n_extra) of a batch item: n_enc_a of the pass over A, n_enc_b of the
+    int n_enc_a, n_enc_b;         // pass over B, and with a bias one for its sum
+    int n_tiles;                  // the workgroups behind them take tiles
+    EncArgs ea, eb;
+    uint32_t *counts;             // protected: cleared here, completed by the check kernel
+    uint32_t *bias_sum;           // protected, with a bias: its sum, formed by one more workgroup
+};
+
+constexpr int TILE_STAGE_ROW = 36;                               // words per staged row of a 32 x 32 block (32 + pad)
+constexpr int TILE_STAGE_WAVE = 32 * TILE_STAGE_ROW * 4;
+
+// ns: buffers in use, min(NS, slabs of the problem)
+__host__ __device__ constexpr int tile_lds_bytes(int BM, int BN, int ns)
+{
+    const int loop = ns * (BM + BN) * SLAB_BYTES, epi = 4 * TILE_STAGE_WAVE + 4 * (BM + BN) * 4;
+    return loop > epi ? loop : epi;
+}
+
+// Swizzle of B stored K x N: 16-byte slot of a row of k <-> chunk of columns.  ROWB: bytes per row.
+template <int ES, int ROWB> __device__ __forceinline__ int kn_swizzle(int k)
+{
+    if constexpr (ES == 2) return ROWB == 128 ? ((k >> 1) & 1) << 2 : (k & 3) << 2;      // 32-byte pieces of 4 rows
+    else return ROWB == 64 ? ((k >> 2) & 1) << 1 : ((k >> 1) & 3) << 1;                  // 16-byte pieces of 8 rows
+}
+
+template <int DT, int BM, int BN, int NS, bool PROT, bool TRANSB>
+__global__ __launch_bounds__(256) void gemm_tile_kernel(TileArgs a)
+{
+    using T = Traits<DT>;
+    typedef typename T::acc_t acc_t;
+    typedef typename T::accv_t accv_t;
+    constexpr int ES = T::ES, OS = T::OS;
+    constexpr int KE = SLAB_BYTES / ES;                          // elements of K per slab
+    constexpr int TM = BM / 2, TN = BN / 2, MI = TM / 32, NI = TN / 32;
+    constexpr int BUF = (BM + BN) * SLAB_BYTES;
+    constexpr int GA = BM / 32, GB = BN / 32;                    // load instructions per wave and slab (8 LDS rows of 128 bytes each)
+    constexpr int BROWB = BN * ES;                               // bytes of a row of k (B stored K x N)
+    static_assert((NS - 2) * (GA + GB) < 64, "the wait count is an immediate");
+
+    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+    const GemmArgs &g = a.g;
+    const int bz = blockIdx.y;
+    if (PROT) {
+        if (blockIdx.x == 0 && bz == 0 && threadIdx.x < 5) a.counts[threadIdx.x] = 0u;
+        const int e = blockIdx.x;
+        if (e < a.n_extra) {
+            if (e == a.n_enc_a + a.n_enc_b) {
+                const acc_t t = block_bias_sum<acc_t>(g.bias, g.N, reinterpret_cast<acc_t *>(smem));
+                if (threadIdx.x == 0 && bz == 0) *a.bias_sum = as_word(t);
+            } else if (e < a.n_enc_a) encode_block<DT>(a.ea, e, bz, reinterpret_cast<uint32_t *>(smem));
+            else encode_block<DT>(a.eb, e - a.n_enc_a, bz, reinterpret_cast<uint32_t *>(smem));
+            return;
+        }
+    }
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave >> 1, wn = wave & 1;
+    const int l32 = lane & 31, lh = lane >> 5;
+    int tm, tn;
+    map_tile(PROT ? blockIdx.x - a.n_extra : blockIdx.x, a.n_tiles, g.tiles_m, g.tiles_n, &tm, &tn);
+    const int m0 = tm * BM, n0 = tn * BN;
+    const int M = g.M, N = g.N, K = g.K;
+    const int nslab = (K + KE - 1) / KE;
+    const int nch = (K * ES + 15) / 16;                          // 16-byte chunks of a row along K that hold data
+
+    const uint8_t *Ab = g.A + (long)bz * g.sA * ES;
+    const uint8_t *Bb = g.B + (long)bz * g.sB * ES;
+
+    // the bias of this lane's four columns of every block column, requested before everything else
+    acc_t bias4[NI][4];
+#pragma unroll
+    for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int gc = n0 + wn * TN + ni * 32 + 4 * (lane & 7) + e;
+            bias4[ni][e] = (g.bias && gc < N) ? from_word<acc_t>(g.bias[gc]) : T::zero();
+        }
+
+    // ---- sources of the direct loads.  K-contiguous operand: group p of this wave fills LDS rows
+    // (4 p + wave) * 8 .. + 8, lane l row l >> 3, slot l & 7.
+    const int lrow = lane >> 3;
+    const int lchunk = (lane & 7) ^ (((wave & 1) << 2) + (lrow >> 1));
+    const uint8_t *arow[GA], *brow[GB];
+    int bk[GB], bcb[GB];                                         // B stored K x N: row of k inside the slab, byte offset of the chunk
+#pragma unroll
+    for (int p = 0; p < GA; ++p) {
+        int r = m0 + (4 * p + wave) * 8 + lrow;
+        r = r < M ? r : M - 1;
+        arow[p] = Ab + (long)r * g.lda * ES;
+    }
+#pragma unroll
+    for (int p = 0; p < GB; ++p) {
+        if (TRANSB) {
+            int r = n0 + (4 * p + wave) * 8 + lrow;
+            r = r < N ? r : N - 1;
+            brow[p] = Bb + (long)r * g.ldb * ES;
+            bk[p] = bcb[p] = 0;
+        } else {
+            constexpr int LPR = BROWB / 16, RPG = 64 / LPR;      // lanes per row of k, rows per load instruction
+            bk[p] = (4 * p + wave) * RPG + lane / LPR;
+            int cb = n0 * ES + (((lane % LPR) ^ kn_swizzle<ES, BROWB>(bk[p])) * 16);
+            const int last = ((N - 1) * ES) / 16 * 16;           // last chunk that holds a column
+            bcb[p] = cb < last ? cb : last;
+            brow[p] = Bb;
+        }
+    }
+    auto issue = [&](int s) __attribute__((always_inline)) {
+        uint8_t *dA = smem + (s % NS) * BUF;
+        uint8_t *dB = dA + BM * SLAB_BYTES;
+        int ch = s * 8 + lchunk;
+        ch = ch < nch ? ch : nch - 1;                            // past the end of K: any valid chunk (cleared in registers)
+#pragma unroll
+        for (int p = 0; p < GA; ++p)
+            __builtin_amdgcn_global_load_lds((tile_gas_ptr)(arow[p] + (long)ch * 16),
+                                             (tile_las_ptr)(dA + (4 * p + wave) * 8 * SLAB_BYTES), 16, 0, 0);
+#pragma unroll
+        for (int p = 0; p < GB; ++p) {
+            const uint8_t *src;
+            if (TRANSB) {
+                src = brow[p] + (long)ch * 16;
+            } else {
+                int k = s * KE + bk[p];
+                k = k < K ? k : K - 1;
+                src = brow[p] + (long)k * g.ldb * ES + bcb[p];
+            }
+            __builtin_amdgcn_global_load_lds((tile_gas_ptr)src, (tile_las_ptr)(dB + (4 * p + wave) * 8 * SLAB_BYTES), 16, 0, 0);
+        }
+    };
+
+    typedef int i32x2 __attribute__((ext_vector_type(2)));
+    i32x4 fa[2][4][MI], fb[2][4][NI];
+    auto read_frags = [&](int s, auto set_c) __attribute__((always_inline)) {
+        constexpr int set = decltype(set_c)::value;
+        const uint8_t *sA = smem + (s % NS) * BUF;
+        const uint8_t *sB = sA + BM * SLAB_BYTES;
+#pragma unroll
+        for (int s4 = 0; s4 < 4; ++s4) {
+            const int sw = ((2 * s4 + lh) ^ ((lane >> 1) & 7)) * 16;
+#pragma unroll
+            for (int mi = 0; mi < MI; ++mi)
+                fa[set][s4][mi] = *reinterpret_cast<const i32x4 *>(sA + (wm * TM + mi * 32 + l32) * SLAB_BYTES + sw);
+            if constexpr (TRANSB) {
+#pragma unroll
+                for (int ni = 0; ni < NI; ++ni)
+                    fb[set][s4][ni] = *reinterpret_cast<const i32x4 *>(sB + (wn * TN + ni * 32 + l32) * SLAB_BYTES + sw);
+            }
+        }
+        if constexpr (!TRANSB) {
+            // Sixteen lanes read 4 (8) rows of k of sixteen columns; each gets one column.  A step of
+            // 32 bytes of k per lane is two such reads; the four steps of a slab and the halves of a
+            // step lie at fixed distances (the swizzle does not change over them).  Written as
+            // instructions: in front of the built-in the compiler waits for every outstanding load
+            // (800 x 700 x 4096: bf16 36.9 us with the built-in, 19.5 us so).
+            constexpr int HALF = (ES == 2 ? 4 : 8) * BROWB, STEP = (ES == 2 ? 16 : 32) * BROWB;
+            const int i16 = lane & 15;
+            const int kk = ES == 2 ? 8 * lh + (i16 >> 2) : 16 * lh + (i16 >> 1);
+#pragma unroll
+            for (int ni = 0; ni < NI; ++ni) {
+                const int cb = (wn * TN + ni * 32 + 16 * ((lane >> 4) & 1)) * ES + (ES == 2 ? (i16 & 3) : (i16 & 1)) * 8;
+                const uint32_t at = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const uint8_t *)(
+                    sB + kk * BROWB + (((cb >> 4) ^ kn_swizzle<ES, BROWB>(kk)) * 16) + (cb & 15));
+                i32x2 h[8];
+#define TILE_TR(T) \
+                asm volatile(T " %0, %8\n\t" T " %1, %8 offset:%9\n\t" T " %2, %8 offset:%10\n\t" T " %3, %8 offset:%11\n\t" \
+                             T " %4, %8 offset:%12\n\t" T " %5, %8 offset:%13\n\t" T " %6, %8 offset:%14\n\t" T " %7, %8 offset:%15\n\t" \
+                             "s_waitcnt lgkmcnt(0)" \
+                             : "=&v"(h[0]), "=&v"(h[1]), "=&v"(h[2]), "=&v"(h[3]), "=&v"(h[4]), "=&v"(h[5]), "=&v"(h[6]), "=&v"(h[7]) \
+                             : "v"(at), "n"(HALF), "n"(STEP), "n"(STEP + HALF), "n"(2 * STEP), "n"(2 * STEP + HALF), "n"(3 * STEP), \
+                               "n"(3 * STEP + HALF) : "memory")
+                if constexpr (ES == 2) TILE_TR("ds_read_b64_tr_b16");
+                else TILE_TR("ds_read_b64_tr_b8");
+#undef TILE_TR
+#pragma unroll
+                for (int s4 = 0; s4 < 4; ++s4)
+                    fb[set][s4][ni] = i32x4{h[2 * s4][0], h[2 * s4][1], h[2 * s4 + 1][0], h[2 * s4 + 1][1]};
+            }
+        }
+    };
+    auto clear_tail = [&](auto set_c) __attribute__((always_inline)) {
+        constexpr int set = decltype(set_c)::value;
+        const int base = K * ES - (nslab - 1) * SLAB_BYTES;      // bytes of K in the last slab
+#pragma unroll
+        for (int s4 = 0; s4 < 4; ++s4) {
+            const int keep = base - (2 * s4 + lh) * 16;
+#pragma unroll
+            for (int mi = 0; mi < MI; ++mi) fa[set][s4][mi] = mask_chunk(fa[set][s4][mi], keep);
+#pragma unroll
+            for (int ni = 0; ni < NI; ++ni) fb[set][s4][ni] = mask_chunk(fb[set][s4][ni], keep);
+        }
+    };
+    accv_t acc[MI][NI];
+#pragma unroll
+    for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+        for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[mi][ni][i] = T::zero();
+    auto mfmas = [&](auto set_c) __attribute__((always_inline)) {
+        constexpr int set = decltype(set_c)::value;
+#pragma unroll
+        for (int s4 = 0; s4 < 4; ++s4)
+#pragma unroll
+            for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+                for (int ni = 0; ni < NI; ++ni)
+                    acc[mi][ni] = T::mfma(fb[set][s4][ni], fa[set][s4][mi], acc[mi][ni]);
+    };
+    typedef std::integral_constant<int, 0> set0;
+    typedef std::integral_constant<int, 1> set1;
+
+    // ---- main loop.  Slab s is in place behind "at most the slabs issued after it outstanding"
+    // (a wave's loads complete in order) and the barrier; the same barrier says that every wave has
+    // its fragments of slab s - 1 in registers, so that buffer takes slab s + NS - 1.
+    for (int s = 0; s < NS - 1; ++s)
+        if (s < nslab) issue(s);
+    auto arrive = [&](int s) __attribute__((always_inline)) {
+        const int ahead = nslab - 1 - s;                         // slabs issued after s: min(ahead, NS - 2)
+        constexpr int L = GA + GB;
+        if (ahead >= NS - 2) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"((NS - 2) * L) : "memory");
+        else if (NS > 3 && ahead == 1) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(L) : "memory");
+        else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        if (s + NS - 1 < nslab) issue(s + NS - 1);
+    };
+    const bool ragged = (K * ES) % SLAB_BYTES != 0;
+    arrive(0);
+    read_frags(0, set0{});
+    int s = 1;
+    for (; s + 1 < nslab; s += 2) {
+        arrive(s);
+        read_frags(s, set1{});
+        mfmas(set0{});
+        arrive(s + 1);
+        read_frags(s + 1, set0{});
+        mfmas(set1{});
+    }
+    if (s < nslab) {
+        arrive(s);
+        read_frags(s, set1{});
+        mfmas(set0{});
+        if (ragged) clear_tail(set1{});
+        mfmas(set1{});
+    } else {
+        if (ragged) clear_tail(set0{});
+        mfmas(set0{});
+    }
+
+    // ---- epilogue: block by block through a stage of the wave's own.  Lane l holds row l & 31 of a
+    // block and in register i column 8 (i >> 2) + 4 (l >> 5) + (i & 3); read back, lane l has four
+    // consecutive columns 4 (l & 7) .. of rows 8 p + (l >> 3).
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");       // every wave is done with the operand buffers
+    uint8_t *stage = smem + wave * TILE_STAGE_WAVE;
+    acc_t *rs_part = reinterpret_cast<acc_t *>(smem + 4 * TILE_STAGE_WAVE);          // [2][BM] by wave column
+    acc_t *cs_part = rs_part + 2 * BM;                                               // [2][BN] by wave row
+    float *rs_sto = reinterpret_cast<float *>(cs_part + 2 * BN);                     // the same of the values as stored
+    float *cs_sto = rs_sto + 2 * BM;
+    uint8_t *Cb = g.C + (long)bz * g.sC * OS;
+    const bool sto = PROT && !T::IS_INT && g.cc_sto != nullptr;
+    const bool inj_here = g.inj_b == bz && g.inj_row >= m0 && g.inj_row < m0 + BM && g.inj_col >= n0 && g.inj_col < n0 + BN;
+    float cmax_s = 0.f;
+    acc_t cs[NI][4];
+    float cs_s[NI][4];
+#pragma unroll
+    for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { cs[ni][e] = T::zero(); cs_s[ni][e] = 0.f; }
+    auto wave_sync = [&]() __attribute__((always_inline)) {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+    static_for<0, MI>([&](auto mi_c) {
+        constexpr int mi = decltype(mi_c)::value;
+        const int row0 = m0 + wm * TM + mi * 32 + (lane >> 3);           // this lane's row of pass 0; pass p: + 8 p
+        acc_t rsum[4] = {T::zero(), T::zero(), T::zero(), T::zero()};
+        float rsum_s[4] = {0.f, 0.f, 0.f, 0.f};
+        static_for<0, NI>([&](auto ni_c) {
+            constexpr int ni = decltype(ni_c)::value;
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                *reinterpret_cast<i32x4 *>(stage + (l32 * TILE_STAGE_ROW + 8 * q + 4 * lh) * 4) =
+                    i32x4{(int)as_word(acc[mi][ni][4 * q]), (int)as_word(acc[mi][ni][4 * q + 1]),
+                          (int)as_word(acc[mi][ni][4 * q + 2]), (int)as_word(acc[mi][ni][4 * q + 3])};
+            wave_sync();
+            i32x4 w4[4];
+#pragma unroll
+            for (int p = 0; p < 4; ++p)
+                w4[p] = *reinterpret_cast<const i32x4 *>(stage + ((8 * p + (lane >> 3)) * TILE_STAGE_ROW + 4 * (lane & 7)) * 4);
+            wave_sync();                                                 // the stage is free for the next block
+            const int gc = n0 + wn * TN + ni * 32 + 4 * (lane & 7);
+            const bool cfull = gc + 4 <= N;
+            if (inj_here) {
+                // the armed flip: one bit of one accumulator, before rounding and before the sums
+#pragma unroll
+                for (int p = 0; p < 4; ++p)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (row0 + 8 * p == g.inj_row && g.inj_col == gc + e) w4[p][e] ^= (int)(1u << g.inj_bit);
+            }
+#pragma unroll
+            for (int p = 0; p < 4; ++p) {
+                const bool rv = row0 + 8 * p < M;
+                acc_t v[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] = add_t(from_word<acc_t>((uint32_t)w4[p][e]), bias4[ni][e]);
+                if (PROT) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const acc_t x = (rv && gc + e < N) ? v[e] : T::zero();
+                        cs[ni][e] = add_t(cs[ni][e], x);
+                        rsum[p] = add_t(rsum[p], x);
+                    }
+                }
+                uint8_t *dst = Cb + ((long)(row0 + 8 * p) * g.ldc + gc) * OS;
+                if constexpr (T::IS_INT) {
+                    if (rv && cfull) {
+                        *reinterpret_cast<i32x4 *>(dst) = i32x4{v[0], v[1], v[2], v[3]};
+                    } else if (rv) {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            if (gc + e < N) reinterpret_cast<int *>(dst)[e] = v[e];
+                    }
+                } else {
+                    const uint32_t lo = pack2<DT>(v[0], v[1]), hi = pack2<DT>(v[2], v[3]);
+                    if (sto) {
+                        float sv[4];
+                        if constexpr (DT == DT_BF16) {
+                            sv[0] = __uint_as_float(lo << 16); sv[1] = __uint_as_float(lo & 0xFFFF0000u);
+                            sv[2] = __uint_as_float(hi << 16); sv[3] = __uint_as_float(hi & 0xFFFF0000u);
+                        } else {
+                            sv[0] = f16_bits_to_f32(lo & 0xFFFFu); sv[1] = f16_bits_to_f32(lo >> 16);
+                            sv[2] = f16_bits_to_f32(hi & 0xFFFFu); sv[3] = f16_bits_to_f32(hi >> 16);
+                        }
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            const float x = (rv && gc + e < N) ? sv[e] : 0.f;
+                            cs_s[ni][e] += x;
+                            rsum_s[p] += x;
+                            cmax_s = fmaxf(cmax_s, fabsf(x));
+                        }
+                    }
+                    if (rv && cfull) {
+                        typedef __attribute__((ext_vector_type(2))) unsigned int u32x2;
+                        *reinterpret_cast<u32x2 *>(dst) = u32x2{lo, hi};
+                    } else if (rv) {
+                        uint16_t *d16 = reinterpret_cast<uint16_t *>(dst);
+                        if (gc + 0 < N) d16[0] = (uint16_t)(lo & 0xFFFFu);
+                        if (gc + 1 < N) d16[1] = (uint16_t)(lo >> 16);
+                        if (gc + 2 < N) d16[2] = (uint16_t)(hi & 0xFFFFu);
+                        if (gc + 3 < N) d16[3] = (uint16_t)(hi >> 16);
+                    }
+                }
+            }
+        });
+        if (PROT) {
+#pragma unroll
+            for (int p = 0; p < 4; ++p) {
+                const acc_t r = row8_sum(rsum[p]);
+                if ((lane & 7) == 0) rs_part[wn * BM + wm * TM + mi * 32 + 8 * p + (lane >> 3)] = r;
+                if constexpr (!T::IS_INT) {
+                    if (sto) {
+                        const float rs = row8_sum(rsum_s[p]);
+                        if ((lane & 7) == 0) rs_sto[wn * BM + wm * TM + mi * 32 + 8 * p + (lane >> 3)] = rs;
+                    }
+                }
+            }
+        }
+    });
+    if (PROT) {
+        auto over_rows = [&](auto v) __attribute__((always_inline)) {
+            v = add_t(v, dpp_get<0x128>(v));                              // lane ^ 8
+            v = add_xor16(v);
+            return add_xor32(v);
+        };
+#pragma unroll
+        for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const acc_t t = over_rows(cs[ni][e]);
+                if (lane < 8) cs_part[wm * BN + wn * TN + ni * 32 + 4 * lane + e] = t;
+                if constexpr (!T::IS_INT) {
+                    if (sto) {
+                        const float ts = over_rows(cs_s[ni][e]);
+                        if (lane < 8) cs_sto[wm * BN + wn * TN + ni * 32 + 4 * lane + e] = ts;
+                    }
+                }
+            }
+        // over LDS traffic only: a full barrier would also wait for every store of C
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        for (int t = tid; t < BM + BN; t += 256) {
+            const bool isrow = t < BM;
+            const int q = isrow ? t : t - BM, gi = (isrow ? m0 : n0) + q, len = isrow ? M : N;
+            if (gi < len) {
+                const acc_t *src = isrow ? rs_part + q : cs_part + q;
+                const long o = (long)bz * len + gi;
+                const acc_t sum = add_t(src[0], src[isrow ? BM : BN]);
+                if constexpr (T::IS_INT) {
+                    atomic_add_word((isrow ? g.rc_obs : g.cc_obs) + o, sum);
+                } else {
+                    // in doubles: small tiles are many, and the order of their additions must not show
+                    unsafeAtomicAdd((isrow ? g.rc_acc : g.cc_acc) + o, (double)sum);
+                    if (sto) {
+                        const float *ss = isrow ? rs_sto + q : cs_sto + q;
+                        unsafeAtomicAdd(reinterpret_cast<float *>(isrow ? g.rc_sto : g.cc_sto) + o, ss[0] + ss[isrow ? BM : BN]);
+                    }
+                }
+            }
+        }
+        if constexpr (!T::IS_INT) {
+            if (sto) {
+                // the largest stored magnitude: what a consumer of this C needs as its max|A|
+                cmax_s = wave_max(cmax_s);
+                if (lane == 0 && cmax_s > 0.f && cmax_s == cmax_s) atomicMax(g.c_max + bz, __float_as_uint(cmax_s));
+            }
+        }
+    }
+}
+
+// ------------------------------------------------------------------------------------------
+static int slabs_of(int dt, int K) { return (int)(((long)K * elem_size(dt) + SLAB_BYTES - 1) / SLAB_BYTES); }
+
+template <int DT, int BM, int BN, int NS, bool PROT, bool TRANSB>
+static hipError_t launch_one(const TileArgs &a, int batch, hipStream_t st)
+{
+    constexpr int smem_max = tile_lds_bytes(BM, BN, NS);
+    static_assert(tile_lds_bytes(BM, BN, 1) >= 256 * 16 * 4, "the passes over A and B use 16 KB");
+    auto kern = gemm_tile_kernel<DT, BM, BN, NS, PROT, TRANSB>;
+    if (smem_max > 48 * 1024) {
+        hipError_t e = ensure_max_lds(reinterpret_cast<const void *>(kern), smem_max);
+        if (e != hipSuccess) return e;
+    }
+    // a problem of fewer slabs than buffers leaves the rest of the LDS to further workgroups
+    const int nslab = slabs_of(DT, a.g.K);
+    const int smem = tile_lds_bytes(BM, BN, nslab < NS ? nslab : NS);
+    dim3 grid((unsigned)(a.n_extra + a.n_tiles), (unsigned)batch, 1);
+    hipLaunchKernelGGL(kern, grid, dim3(256), smem, st, a);
+    return hipGetLastError();
+}
+
+// 64 x 64, 64 x 128 or 128 x 128 tiles.  What a compute unit spends on a slab is its LDS traffic (per
+// wave a read of its rows of A and of B, once a write of the tile's): measured 0.19, 0.28 and 0.46 us
+// for the three shapes, so wider tiles cost less per product, but a problem of few tiles ends sooner
+// the smaller its tiles are: 197 x 768 x 3072 (48 / 24 / 12 tiles) 12.7 / 17.8 / 27.4 us; 1000 x 1000
+// x 1024 (256 / 128 / 64) 8.2 / 9.5 / 13.1; 2048 x 1024 x 1024 (512 / 256 / 128) 10.6 / 10.5 / 13.7;
+// 6304 x 768 x 3080 with B stored K x N (1188 / 594 / 300) 64.9 / 59.0 / 64.3; 12608 x 1000 x 200
+// (3152 / 1576 / 792) 26.3 / 25.0 / 29.5; 6304 x 3072 x 776 (4752 / 2376 / 1200) 74.3 / 69.5 / 62.9.
+// Up to two slabs there is no main loop to speak of, and the smallest tile, of which most fit on a
+// compute unit, hides the start and the end of its neighbours: 58 x (526 x 526 x 64) 23.4 / 30.8 /
+// 49.4 us, 12608 x 1000 x 128 24.0 / 26.1 / 31.4.
+static void tile_size(int M, int N, int nslab, int batch, int *bm, int *bn)
+{
+    auto tiles = [&](int tm, int tn) { return (long)((M + tm - 1) / tm) * ((N + tn - 1) / tn) * batch; };
+    *bm = *bn = 64;
+    if (nslab <= 2 || N <= 64) return;
+    if (tiles(64, 64) > 256) *bn = 128;
+    if (nslab >= 8 && tiles(128, 128) >= 1024) *bm = 128;
+}
+
+template <int DT, int BM, int BN, int NS>
+static hipError_t launch_cfg(bool protect, bool transB, TileArgs &a, int batch, hipStream_t st)
+{
+    a.g.tiles_m = (a.g.M + BM - 1) / BM;
+    a.g.tiles_n = (a.g.N + BN - 1) / BN;
+    const long tiles = (long)a.g.tiles_m * a.g.tiles_n;
+    if (tiles + a.n_extra > 0x7FFFFFFFL) return hipErrorInvalidValue;
+    a.n_tiles = (int)tiles;
+    if (protect) return transB ? launch_one<DT, BM, BN, NS, true, true>(a, batch, st)
+                               : launch_one<DT, BM, BN, NS, true, false>(a, batch, st);
+    return transB ? launch_one<DT, BM, BN, NS, false, true>(a, batch, st)
+                  : launch_one<DT, BM, BN, NS, false, false>(a, batch, st);
+}
+
+// Buffers: where every compute unit has a workgroup at most, four (197 x 768 x 3072: 12.7 us against
+// 14.5 with three); otherwise three, for more workgroups on a compute unit (6304 x 768 x 768 on 64 x 64
+// tiles: 17.3 us against 20.2 with four).
+template <int DT>
+static hipError_t launch_tile(bool protect, bool transB, TileArgs &a, int batch, hipStream_t st)
+{
+    int bm, bn;
+    tile_size(a.g.M, a.g.N, slabs_of(DT, a.g.K), batch, &bm, &bn);
+    if (bm == 128) return launch_cfg<DT, 128, 128, 3>(protect, transB, a, batch, st);
+    if (bn == 128) return launch_cfg<DT, 64, 128, 3>(protect, transB, a, batch, st);
+    if ((long)((a.g.M + 63) / 64) * ((a.g.N + 63) / 64) * batch > 256) return launch_cfg<DT, 64, 64, 3>(protect, transB, a, batch, st);
+    return launch_cfg<DT, 64, 64, 4>(protect, transB, a, batch, st);
+}
+
+void gemm_tile_shape(int dt, const Shape &s, int *tm, int *tn)
+{
+    if (gemm_item_eligible(dt, s, false)) {          // one workgroup per batch item
+        *tm = s.M;
+        *tn = s.N;
+        return;
+    }
+    if (gemm_takes_fast(dt, s)) {
+        gemm_fast_tile(tm, tn);
+        return;
+    }
+    tile_size(s.M, s.N, slabs_of(dt, s.K), s.batch, tm, tn);
+}
+
+// The fast kernel's 256 x 256 tiles use the matrix cores best and fill the chip worst.  Measured
+// (unprotected, fast / general): 32 of its tiles (2048 x 1024 x 1024) 16.0 / 10.5 us, 39 (3152 x 768 x
+// 768) 14.8 / 11.8 and at K = 3072 40.7 / 30.4, 81 (2304 x 2304 x 768) 14.8 / 18.3, 96 (2048 x 3072 x
+// 3072) 46.6 / 58.6; int8 96 tiles, K = 4096: 35.8 / 43.8.
+bool gemm_takes_fast(int dt, const Shape &s)
+{
+    const long tiles = (long)((s.M + 255) / 256) * ((s.N + 255) / 256) * s.batch;
+    return tiles >= 64 && gemm_fast_eligible(dt, s.M, s.N, s.K, s.transB != 0, s.lda, s.ldb);
+}
+
+static EncArgs enc_args(const void *X, long ld, long stride, int rows, int cols, int K, int reduce_rows, int dt,
+                        uint32_t *sum, uint32_t *max_acc)
+{
+    EncArgs e;
+    e.X = (const uint8_t *)X; e.ld = ld; e.stride = stride; e.rows = rows; e.cols = cols; e.K = K;
+    e.reduce_rows = reduce_rows;
+    // Beside the tiles: about twelve row blocks, of one to eight batches of loads per thread.  The
+    // additions of the row blocks meet in the same words, which are served one after the other, and the
+    // last of them ends the launch: 6304 x 768 x 768 with 99 / 32 / 16 / 8 row blocks of A 26.6 / 22.8 /
+    // 22.2 / 22.2 us, 1537 x 1001 x 713 with 24 / 16 / 8 of them 15.4 / 13.6 / 13.0 us.
+    EncPlan p = plan_window(rows, cols, 16 / elem_size(dt));
+    const int batch_rows = (256 >> p.cw_log2) * ENC_UNROLL;
+    int batches = (rows + 12 * batch_rows - 1) / (12 * batch_rows);
+    batches = batches > 8 ? 8 : batches;
+    e.cw_log2 = p.cw_log2; e.nwin = p.nwin;
+    e.rpb = batches * batch_rows;
+    e.nrb = (rows + e.rpb - 1) / e.rpb;
+    e.sum = sum; e.max_acc = max_acc;
+    return e;
+}
+
+hipError_t launch_gemm(int dt, bool protect, bool stored_sums, bool encode_b, const void *A, const void *B, void *C,
+                       const Shape &s, const Workspace &w, const InjectArm &arm, uint32_t *counts, hipStream_t st)
+{
+    if (!protect && !w.bias && gemm_item_eligible(dt, s, false))
+        return launch_gemm_item(dt, false, false, false, A, B, C, s, w, nullptr, arm, st);
+    TileArgs a;
+    GemmArgs &g = a.g;
+    g.A = (const uint8_t *)A;
+    g.B = (const uint8_t *)B;
+    g.C = (uint8_t *)C;
+    g.M = s.M; g.N = s.N; g.K = s.K;
+    g.lda = s.lda; g.ldb = s.ldb; g.ldc = s.ldc;
+    g.sA = s.sA; g.sB = s.sB; g.sC = s.sC;
+    g.inj_b = arm.batch; g.inj_row = arm.row; g.inj_col = arm.col; g.inj_bit = arm.bit;
+    g.cc_obs = w.cc_obs; g.rc_obs = w.rc_obs; g.rc_pred = w.rc_pred; g.cc_acc = w.cc_acc; g.rc_acc = w.rc_acc;
+    g.a_sum = w.a_sum; g.a_max = w.a_max; g.b_sum = w.b_sum;
+    g.bias = w.bias;
+    g.cc_sto = (protect && stored_sums && dt != DT_I8) ? w.cc_sto : nullptr;
+    g.rc_sto = g.cc_sto ? w.rc_sto : nullptr;
+    g.c_max = g.cc_sto ? w.c_max : nullptr;
+    g.a_given = (protect && w.a_given) ? 1 : 0;
+    g.mul24_ok = s.N < 65536 ? 1 : 0;            // |b| <= 128 N
+    g.tiles_m = g.tiles_n = g.n_big = g.tiles_m_big = g.tiles_m_small = 0;
+    g.n_small = 0; g.batch = s.batch;
+    if (gemm_takes_fast(dt, s)) return launch_gemm_fast(dt, protect, g, s.batch, st);
+    a.counts = counts;
+    a.bias_sum = w.bias_sum;
+    a.ea = enc_args(A, s.lda, s.sA, s.M, s.K, s.K, 1, dt, w.a_sum, w.a_max);
+    a.eb = s.transB ? enc_args(B, s.ldb, s.sB, s.N, s.K, s.K, 1, dt, w.b_sum, w.b_max)
+                    : enc_args(B, s.ldb, s.sB, s.K, s.N, s.K, 0, dt, w.b_sum, w.b_max);
+    a.n_enc_a = (protect && !w.a_given) ? a.ea.nwin * a.ea.nrb : 0;
+    a.n_enc_b = (protect && encode_b) ? a.eb.nwin * a.eb.nrb : 0;
+    a.n_extra = a.n_enc_a + a.n_enc_b + (protect && w.bias ? 1 : 0);
+    switch (dt) {
+    case DT_I8:   return launch_tile<DT_I8>(protect, s.transB != 0, a, s.batch, st);
+    case DT_BF16: return launch_tile<DT_BF16>(protect, s.transB != 0, a, s.batch, st);
+    case DT_F16:  return launch_tile<DT_F16>(protect, s.transB != 0, a, s.batch, st);
+    }
+    return hipErrorInvalidValue;
+}
+
+}  // namespace abft

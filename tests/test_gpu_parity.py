@@ -1506,3 +1506,29 @@ def test_detect_correct_on_clean_input_leaves_the_fused_verdict(ctx, dtype):
     run.gemm(ab.ABFT_DETECT_CORRECT)
     cnt = run.cnt()
     assert np.array_equal(run.C(), C_clean) and cnt[2] == ab.ABFT_CLEAN and cnt[3] == 0
+
+
+# (M, N, K, batch, trans_b): the general kernel's tile shapes and depths of buffering, at their edges
+TILE_SHAPES = [
+    (64, 64, 64, 1, True),          # one 64 x 64 tile, whole
+    (65, 63, 1, 1, False),          # a row too many, a column too few, one element of K
+    (129, 65, 257, 2, False),       # as many slabs as buffers and one more (bf16: five), B transposed from LDS
+    (1100, 1025, 129, 1, True),     # 64 x 64 tiles, up to two slabs, several workgroups per compute unit
+    (1100, 1030, 400, 1, True),     # 64 x 128 tiles, a ragged last column of tiles
+    (1100, 1030, 400, 1, False),
+    (1090, 60, 600, 16, True),      # N within one tile: 64 x 64 tiles on three buffers
+    (129, 130, 1030, 256, True),    # 128 x 128 tiles
+    (129, 130, 1030, 256, False),
+]
+
+
+@pytest.mark.parametrize("dtype", ["i8", "bf16", "f16"])
+@pytest.mark.parametrize("M,N,K,batch,trans_b", TILE_SHAPES)
+def test_general_kernel_tile_shapes(dtype, M, N, K, batch, trans_b):
+    """C, every checksum vector and flag of the general kernel against the oracle where its tiles,
+    slabs and buffers end."""
+    ctx = ab.abft_create(max_rows=batch * M, max_cols=batch * N, max_depth=batch * (K + 127), max_batch=batch)
+    try:
+        _clean_case(ctx, dtype, M, N, K, batch, trans_b)
+    finally:
+        ab.abft_destroy(ctx)
