@@ -10,8 +10,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libabft.so")
-SOURCES = ["gemm_tile.hip", "gemm_fast.hip", "gemm_item.hip", "aux_kernels.hip", "abft_api.hip"]
-HEADERS = ["abft_internal.h", "abft_device.h", "gemm_args.h", "gemm_epilogue.h", "gemm_apass.h", "encode_pass.h", os.path.join("..", "..", "include", "abft.h")]
+SOURCES = ["gemm_tile.hip", "gemm_fast.hip", "gemm_item_rows.hip", "gemm_item_cols.hip", "gemm_item.hip", "aux_kernels.hip", "abft_api.hip"]
+HEADERS = ["abft_internal.h", "abft_device.h", "gemm_args.h", "gemm_epilogue.h", "gemm_apass.h", "gemm_item.h", "encode_pass.h", os.path.join("..", "..", "include", "abft.h")]
 
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-fPIC", "-std=c++17", "-munsafe-fp-atomics",
@@ -66,7 +66,7 @@ def build(force: bool = True, verbose: bool = False) -> str:
             raise RuntimeError("hipcc failed: " + " ".join(cmd))
         return r.stderr
 
-    with ThreadPoolExecutor(max_workers=4) as ex:
+    with ThreadPoolExecutor(max_workers=8) as ex:
         logs = list(ex.map(run, jobs))
     for cmd, log in zip(jobs, logs):
         if "-Rpass-analysis=kernel-resource-usage" in cmd:

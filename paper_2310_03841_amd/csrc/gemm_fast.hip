@@ -1,6 +1,5 @@
 // Fast path of the protected GEMM for gfx950: B stored N x K (both operands K-contiguous) and
-// K a whole number (at least three) of 128-byte slabs.  Same mathematics, the same pass over
-// A's slabs and the same epilogue as gemm_kernel; what differs is the data movement:
+// K a whole number (at least three) of 128-byte slabs.  The data movement:
 //   * global -> LDS with direct-to-LDS loads (global_load_lds_dwordx4): no VGPR staging.  One
 //     wave instruction fills 8 LDS rows of 128 bytes; the XOR swizzle of the LDS layout is
 //     applied by choosing which global 16-byte chunk each lane fetches.

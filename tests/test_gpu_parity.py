@@ -1532,3 +1532,61 @@ def test_general_kernel_tile_shapes(dtype, M, N, K, batch, trans_b):
         _clean_case(ctx, dtype, M, N, K, batch, trans_b)
     finally:
         ab.abft_destroy(ctx)
+
+
+# (M, N, K, batch, trans_b): one workgroup per item, where its kernels' blocks, rings and chunks end
+ITEM_EDGES = [
+    (300, 128, 96, 64, True),       # the widest item whose waves own rows; two blocks of rows for some waves
+    (33, 129, 96, 64, True),        # the narrowest whose waves own columns
+    (290, 64, 577, 64, False),      # deeper than the ring of A, an odd number of steps
+    (129, 97, 801, 64, False),      # four blocks of columns, the last of one column; too deep for LDS in 16 bits
+    (65, 33, 400, 64, True),        # as deep with B stored N x K
+    (330, 260, 80, 64, True),       # rows of A in more than one chunk, two blocks of columns per wave
+    (330, 260, 80, 64, False),
+    (96, 256, 190, 64, True),       # whole blocks both ways
+]
+
+
+@pytest.mark.parametrize("dtype", ["i8", "bf16", "f16"])
+@pytest.mark.parametrize("M,N,K,batch,trans_b", ITEM_EDGES)
+def test_item_kernels_at_their_edges(dtype, M, N, K, batch, trans_b):
+    """C, every checksum vector, flags and C's padding of the item kernels against the oracle."""
+    ctx = ab.abft_create(max_rows=batch * M, max_cols=batch * N, max_depth=batch * (K + 127), max_batch=batch)
+    try:
+        _clean_case(ctx, dtype, M, N, K, batch, trans_b)
+    finally:
+        ab.abft_destroy(ctx)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("value", [np.inf, np.nan])
+@pytest.mark.parametrize("M,N,K,trans_b", [(70, 60, 100, False), (70, 200, 64, True)])
+def test_item_kernels_keep_non_finite_values_apart(ctx_items, dtype, value, M, N, K, trans_b):
+    """One Inf or NaN in A: its row and every column are flagged and no other row is; the sums of A's other
+    columns, the other rows' predictions and max|A| (which a maximum takes without NaN) are as without it."""
+    batch, bi, row, k = 64, 3, 21, 7
+    A, B = gen.gen_operands(dtype, M, N, K, 31, 32, trans_b=trans_b, batch=batch, b_kind="act")
+    clean = Run(ctx_items, dtype, A, B, trans_b)
+    clean.gemm(ab.ABFT_DETECT)
+    a0, rcp0, mx0 = (clean.ws(w)[bi].copy() for w in (ab.ABFT_WS_A_SUM, ab.ABFT_WS_RC_PRED, ab.ABFT_WS_MAXABS))
+    run = Run(ctx_items, dtype, A, B, trans_b)
+    assert ab.abft_tile_shape(run.code, run.shape) == (M, N)
+    bits = {("bf16", False): 0x7F80, ("bf16", True): 0x7FC0, ("f16", False): 0x7C00, ("f16", True): 0x7E00}
+    run.dA[bi, row, k] = bits[dtype, bool(np.isnan(value))]
+    was = abs(orc.decode(A[bi], dtype)[row, k])
+    run.gemm(ab.ABFT_DETECT)
+    rf, cf = run.flags()
+    want_r, want_c = np.zeros((batch, M), bool), np.zeros((batch, N), bool)
+    want_r[bi, row], want_c[bi] = True, True
+    assert np.array_equal(rf, want_r) and np.array_equal(cf, want_c)
+    a1, rcp1, mx1 = (run.ws(w)[bi] for w in (ab.ABFT_WS_A_SUM, ab.ABFT_WS_RC_PRED, ab.ABFT_WS_MAXABS))
+    others = np.arange(K) != k
+    assert not np.isfinite(a1[k])
+    # the sums of the other columns were formed a second time, in another order: fp32 rounding of M terms
+    assert np.max(np.abs(a1[others] - a0[others])) <= 2.0 ** -23 * M * np.max(np.abs(mx0))
+    rows = np.arange(M) != row
+    assert np.max(np.abs(rcp1[rows] - rcp0[rows])) <= 2.0 ** -23 * K * np.max(np.abs(mx0)) * N * np.max(np.abs(mx0))
+    if np.isnan(value):
+        assert mx1[0] == mx0[0] or was == mx0[0]
+    else:
+        assert np.isinf(mx1[0])
