@@ -173,10 +173,10 @@ int abft_encode_b(abft_ctx *ctx, const void *B, abft_dtype dtype, const abft_sha
  * Enqueues: the pass over B that gives b = B e and max|B| (skipped with
  * ABFT_B_CHECKSUM_CACHED); the GEMM, which besides C produces, from the operand slabs of A it
  * holds on chip, a = e^T A, the row prediction A b and max|A|, and from its accumulators
- * (before rounding) the observed sums e^T C and C e; the finish kernel, which forms the
+ * (before rounding) the observed sums e^T C and C e; the check kernel, which forms the
  * column prediction a B from one read of B, compares both pairs (equality for ABFT_I8,
  * |difference| <= tau otherwise; NaN or Inf always flag) and writes flags, counts and status.
- * A and B must stay unchanged until the finish kernel has run.
+ * A and B must stay unchanged until the check kernel has run.
  * A batch of at least 64 small problems (per-head attention products: N <= 640, M <= 1024, a row
  * of K at most 640 bytes, operands of one item fitting the local memory of a compute unit; with
  * ABFT_STORED_SUMS only up to N = 256) is one kernel instead: one workgroup per batch item forms b, a, both
@@ -229,12 +229,12 @@ int abft_supply_a(abft_ctx *ctx, const void *a, const void *amax);
 
 /* Pipelining several independent GEMMs (Sec. IV-C: the check must stay a small fraction of the
  * layer's time).  A protected call is a chain of dependent kernels of which only the GEMM fills
- * the chip; the pass over B and the finish kernel are bound by latency.  Two or three streams,
+ * the chip; the pass over B and the check kernel are bound by latency.  Two or three streams,
  * each with a context of its own, hide them: while one stream's GEMM runs, the other streams' small
  * kernels run beside it.  For that the GEMMs must not start together (they would share the chip, end
- * together and leave it idle during both finish kernels, and that state persists).  `event` is a
+ * together and leave it idle during both check kernels, and that state persists).  `event` is a
  * caller-owned hipEvent_t that every following abft_gemm / abft_gemm_bias of this context (any
- * mode, also ABFT_OFF) records on its stream right behind its GEMM kernel, before the finish
+ * mode, also ABFT_OFF) records on its stream right behind its GEMM kernel, before the check
  * kernel; the caller lets the other stream wait for it (hipStreamWaitEvent) before that stream's
  * first call, after which the streams stay half a step apart by themselves.  NULL stops the
  * recording.  Nothing is recorded while a call is being captured into a graph, nor by protected
@@ -313,7 +313,7 @@ int abft_tile_shape(abft_dtype dtype, const abft_shape *s, int *tile_m, int *til
 /* Kernel timing for reports (not a hot call: creates HIP events).  Between begin and end every
  * abft_gemm records events on the caller's stream around its kernels; up to max_calls calls are
  * kept.  abft_profile_end waits for the recorded events and returns average milliseconds per call:
- * ms[0] pass over B (or the clearing kernel that replaces it), ms[1] GEMM kernel, ms[2] finish
+ * ms[0] pass over B (or the clearing kernel that replaces it), ms[1] GEMM kernel, ms[2] check
  * kernel, ms[3] first event to last.  (Calls that are a single kernel report it as ms[1].) */
 int abft_profile_begin(abft_ctx *ctx, int max_calls);
 int abft_profile_end(abft_ctx *ctx, double ms[4], int *calls);

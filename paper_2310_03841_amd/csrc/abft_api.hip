@@ -334,7 +334,7 @@ static void end_resum(abft_ctx *ctx, size_t words)
 }
 
 // A pass over B accumulates into the slot that is not in use; that slot is clean unless two
-// passes follow each other without a protected GEMM in between (whose finish kernel cleans it).
+// passes follow each other without a protected GEMM in between (whose check kernel cleans it).
 static int begin_b_pass(abft_ctx *ctx, hipStream_t st)
 {
     const bool gm = in_graph_mode(ctx, st);
@@ -366,9 +366,9 @@ extern "C" int abft_encode_b(abft_ctx *ctx, const void *B, abft_dtype dtype, con
 }
 
 // The kernels of a protected GEMM, tiled path: pass over B (unless its encoding is cached; the general
-// kernel does it beside its tiles), GEMM, finish or check.  The call accumulates into the region the previous protected call did not use.  It is
+// kernel does it beside its tiles), GEMM, check.  The call accumulates into the region the previous protected call did not use.  It is
 // clean unless a call failed half way; the region of the previous call is cleared by this
-// call's finish kernel.  So a call with a cached B checksum is two kernels: GEMM, finish.
+// call's check kernel.  So a call with a cached B checksum is two kernels: GEMM, check.
 static int enqueue_tiled(abft_ctx *ctx, int dtype, bool cached, bool stored, const void *A, const void *B, void *C,
                          const Shape &sh, Workspace *w, const Verdict &v, const InjectArm &arm, hipEvent_t *ev,
                          hipStream_t st)
@@ -395,20 +395,19 @@ static int enqueue_tiled(abft_ctx *ctx, int dtype, bool cached, bool stored, con
     HIP_TRY(launch_gemm(dtype, true, stored, !cached, A, B, C, sh, *w, arm, v.counts, st));
     if (ctx->done_event && !gm) HIP_TRY(hipEventRecord(ctx->done_event, st));
     if (ev) HIP_TRY(hipEventRecord(ev[2], st));
-    auto finish = [&](uint32_t *z, size_t zw, uint32_t *z2, size_t z2w) {
-        return fast ? launch_finish(dtype, B, sh, *w, v, z, zw, z2, z2w, st)
-                    : launch_check(dtype, A, B, sh, *w, v, z, zw, z2, z2w, st);
+    auto check = [&](uint32_t *z, size_t zw, uint32_t *z2, size_t z2w) {
+        return launch_check(dtype, fast, A, B, sh, *w, v, z, zw, z2, z2w, st);
     };
     if (gm) {
-        HIP_TRY(finish(nullptr, 0, nullptr, 0));
+        HIP_TRY(check(nullptr, 0, nullptr, 0));
         ctx->dirty[ctx->cur] = w->zero_words;
     } else {
         const size_t prev_dirty = ctx->dirty[prev];
         ctx->dirty[prev] = ctx->region_words;
-        // the finish kernel also cleans the b slot that is not in use (for the next pass over B)
+        // the check kernel also cleans the b slot that is not in use (for the next pass over B)
         const int other = ctx->bslot ^ 1;
         uint32_t *other_base = ctx->pool_depth + (size_t)other * ctx->bslot_words;
-        HIP_TRY(finish(prev_base, prev_dirty, ctx->bclean[other] ? nullptr : other_base, ctx->bslot_words));
+        HIP_TRY(check(prev_base, prev_dirty, ctx->bclean[other] ? nullptr : other_base, ctx->bslot_words));
         ctx->bclean[other] = true;
         ctx->dirty[prev] = 0;
         ctx->dirty[ctx->cur] = w->zero_words;

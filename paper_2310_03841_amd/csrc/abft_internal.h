@@ -28,13 +28,13 @@ __host__ __device__ inline int out_size(int dt) { return dt == DT_I8 ? 4 : 2; }
 // DT_I8 and float otherwise, so every element is one 32-bit word.
 struct Workspace {
     // B pass: b = B e and max|B| are accumulated with atomics into one of two slots (the
-    // context alternates; the finish kernel of a protected GEMM clears the slot not in use)
+    // context alternates; the check kernel of a protected GEMM clears the slot not in use)
     uint32_t *b_sum;                // [batch][K]   slot in use
     uint32_t *b_max;                // [batch]      max|B| as float bits, same slot
     float    *maxabs;               // [batch][2]   max|A|, max|B|
     float    *tau;                  // [batch]
     // predicted
-    uint32_t *cc_pred;              // [batch][N]   (e^T A) B, written by the finish kernel
+    uint32_t *cc_pred;              // [batch][N]   (e^T A) B, written by the check kernel
     uint32_t *s_pred;               // [batch]
     // one region that must be zero before the protected GEMM, filled by its atomics:
     //   cc_obs [batch][N] | rc_obs [batch][M] | rc_pred [batch][M] | a_sum [batch][K] | a_max [batch]
@@ -91,21 +91,18 @@ hipError_t launch_encode_b(int dt, const void *B, const Shape &s, const Workspac
                            size_t zero_words, hipStream_t st);
 // Largest K the protected path handles (the column sums of A's slabs are kept in LDS).
 int protect_max_k(int dt);
-// Whether the problem takes the fast kernel (a pass over B ahead of it, launch_finish behind it) or the
-// general one (launch_check behind it; the passes over A and B ride in its launch).
+// Whether the problem takes the fast kernel (a pass over B ahead of it) or the general one (the passes
+// over A and B ride in its launch).
 bool gemm_takes_fast(int dt, const Shape &s);
 // protect: A-side checksums and observed sums are produced by the kernel (atomics into the
-// zeroed region of the workspace); launch_finish / launch_check turn them into flags.
+// zeroed region of the workspace); launch_check turns them into flags.
 // stored_sums: also accumulate the row / column sums of the rounded values that are stored
-// encode_b, counts: general kernel, protected: form b and max|B| too; the counts it clears for launch_check
+// encode_b: general kernel, protected: form b and max|B| too; counts: protected: cleared for launch_check
 hipError_t launch_gemm(int dt, bool protect, bool stored_sums, bool encode_b, const void *A, const void *B, void *C,
                        const Shape &s, const Workspace &w, const InjectArm &arm, uint32_t *counts, hipStream_t st);
-// zero_ptr / zero_words: a region every block of the kernel helps to clear (may be null / 0)
-hipError_t launch_finish(int dt, const void *B, const Shape &s, const Workspace &w, const Verdict &v,
-                         uint32_t *zero_ptr, size_t zero_words, uint32_t *zero2_ptr, size_t zero2_words,
-                         hipStream_t st);
-// the same after the general kernel: both predictions, comparisons, flags and counts
-hipError_t launch_check(int dt, const void *A, const void *B, const Shape &s, const Workspace &w, const Verdict &v,
+// behind the GEMM kernel (after_fast: the fast one): the predictions that are missing, comparisons, flags
+// and counts.  zero_ptr / zero_words: regions every block of the kernel helps to clear (may be null / 0)
+hipError_t launch_check(int dt, bool after_fast, const void *A, const void *B, const Shape &s, const Workspace &w, const Verdict &v,
                         uint32_t *zero_ptr, size_t zero_words, uint32_t *zero2_ptr, size_t zero2_words, hipStream_t st);
 // with_sto: a row / column also flags when the re-summed stored C differs from the stored-side
 // sums of the GEMM by more than STO_TOL_FACTOR * tau

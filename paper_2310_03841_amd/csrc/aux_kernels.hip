@@ -1,5 +1,5 @@
-// Kernels around the protected GEMM: the pass over B (its checksum vector), finish (column
-// prediction from the sums the GEMM collected, compare, flags), verify (re-sum stored C),
+// Kernels around the protected GEMM: the pass over B (its checksum vector), check (the predictions
+// that are missing, compare, flags), verify (re-sum stored C),
 // correct (localise, recompute tiles, re-check) and the bit-flip test hook.
 //
 // Paper references: the two input-side vectors and the comparison with the
@@ -125,7 +125,7 @@ int protect_max_k(int dt) { (void)dt; return 4096; }
 // ===================================================================== compare
 // Flags from observed sums against the predictions the last abft_gemm left in the context
 // (Sec. III-B.1 item (2): equality for fixed point, tolerance for floating point).  Used by
-// abft_verify and abft_correct; abft_gemm compares in its finish kernel.
+// abft_verify and abft_correct; abft_gemm compares in its check kernel.
 struct CmpArgs {
     const uint32_t *cc_pred, *rc_pred;
     const uint32_t *cc_obs, *rc_obs;
@@ -247,255 +247,19 @@ hipError_t launch_compare(int dt, const Shape &s, const Workspace &w, const Verd
     return hipGetLastError();
 }
 
-// ====================================================================== finish
-// Runs after the fast GEMM kernel, when its atomics have completed a = e^T A, rc_pred = A b,
-// max|A| and the observed sums: forms the column checksum prediction cc_pred = a B (Sec. III-B.1: the
-// product of the input-side checksum with the weight) and compares both pairs; the last block to
-// finish writes the counts and the status.
-struct FinArgs {
-    const uint8_t *B;
-    long ldb, sB;
-    int M, N, K;
-    const uint32_t *a_sum, *b_sum, *cc_obs, *rc_obs, *a_max;
-    uint32_t *rc_pred;    // A b from the GEMM; with a bias the finish kernel adds sum(bias) in place
-    const uint32_t *bias; // layer bias [N] or null: cc_pred gains M bias[n], rc_pred sum(bias), a.b M sum(bias)
-    uint32_t *cc_pred, *s_pred;
-    float *maxabs, *tau;
-    float tau_override, tau_override_cols;
-    uint8_t *row_flag, *col_flag;
-    uint32_t *counts;
-    uint32_t *ticket;     // [3]: ticket, flagged rows, flagged cols (self-cleaning)
-    int batch;
-    int ksplit;           // 1, or 4 (deep K): the four waves share FN_RW rows of B, a quarter of K each
-    int col_blocks;       // units per batch item
-    uint32_t *zero_ptr;   // region every block helps to clear: what the previous protected GEMM of this
-    size_t zero_words;    // context accumulated into, so that the next one finds it clean
-    const uint32_t *b_max;   // max|B| of the b in use, float bits [batch]
-    uint32_t *zero2_ptr;  // second region to clear: the b slot the next pass over B will accumulate into
-    size_t zero2_words;
-};
-
-// Runs after the fast GEMM kernel (B stored N x K), arranged so that a block's critical path is one
-// round of loads, one reduction and one ticket: the kernel is bound by latency, not by the 2 K N
-// bytes it reads, so everything a block needs is requested before anything is used.  A unit is
-// (batch item, block of rows of B): each wave takes FN_RW rows of B
-// with its lanes along K (deep K: the four waves share FN_RW rows, a quarter of K each), and the
-// unit also compares its share of the M rows.  One ticket per block; the last block writes counts.
-constexpr int FN_RW = 8;
-
-template <int DT>
-__global__ __launch_bounds__(256) void finish_nk_kernel(FinArgs f)
-{
-    using T = Traits<DT>;
-    typedef typename T::acc_t acc_t;
-    constexpr int ES = T::ES, CE = 16 / ES;
-    __shared__ acc_t wred[4];
-    __shared__ acc_t kpart[4][FN_RW];
-    __shared__ unsigned wcnt[4][2];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int M = f.M, N = f.N, K = f.K;
-    {
-        const size_t nb = gridDim.x;
-        for (size_t i = (size_t)blockIdx.x * 256 + tid; i < f.zero_words; i += nb * 256) f.zero_ptr[i] = 0u;
-        for (size_t i = (size_t)blockIdx.x * 256 + tid; i < f.zero2_words; i += nb * 256) f.zero2_ptr[i] = 0u;
-    }
-    const int nch = (K + CE - 1) / CE;
-    const bool split = f.ksplit == 4;
-    const int rpb = split ? FN_RW : 4 * FN_RW;                  // rows of B per unit
-    const int units = f.col_blocks * f.batch;
-    const int rshare = (M + f.col_blocks - 1) / f.col_blocks;   // rows of C a unit compares
-    const bool vec_a = (K & 3) == 0 && ((uintptr_t)f.a_sum & 15u) == 0;     // 16-byte loads of a are aligned
-    unsigned nr_w = 0, nc_w = 0;
-    acc_t sb = T::zero();                                       // sum of the bias
-    if (f.bias) sb = block_bias_sum<acc_t>(f.bias, N, wred);
-
-    for (int u = blockIdx.x; u < units; u += gridDim.x) {
-        const int bz = u / f.col_blocks, cb = u - bz * f.col_blocks;
-        const uint8_t *Bb = f.B + (long)bz * f.sB * ES;
-        const uint32_t *asum = f.a_sum + (long)bz * K;
-        // ---- everything the unit will compare against, requested first
-        const int nrow0 = cb * rpb + (split ? 0 : wave * FN_RW);
-        uint32_t my_obs = 0;
-        acc_t my_bias = T::zero();
-        if (lane < FN_RW && nrow0 + lane < N) {
-            my_obs = f.cc_obs[(long)bz * N + nrow0 + lane];
-            if (f.bias) my_bias = mul_t((acc_t)M, from_word<acc_t>(f.bias[nrow0 + lane]));
-        }
-        const int rbeg = cb * rshare, rend = min(rbeg + rshare, M);
-        uint32_t ro = 0, rp = 0;
-        if (rbeg + tid < rend) { ro = f.rc_obs[(long)bz * M + rbeg + tid]; rp = f.rc_pred[(long)bz * M + rbeg + tid]; }
-        float tol = 0.f;
-        if (!T::IS_INT) {
-            const float ma = __uint_as_float(f.a_max[bz]), mb = __uint_as_float(f.b_max[bz]);
-            tol = f.tau_override > 0.f ? f.tau_override : (1e-3f * (float)K) * ma * mb;
-            if (cb == 0 && tid == 0) {
-                f.maxabs[(long)bz * 2] = ma;
-                f.maxabs[(long)bz * 2 + 1] = mb;
-                f.tau[bz] = tol;
-            }
-        }
-        // ---- a B over this wave's rows: two chunks per lane and trip, all loads of a trip in flight
-        acc_t dot[FN_RW];
-#pragma unroll
-        for (int j = 0; j < FN_RW; ++j) dot[j] = T::zero();
-        const int cstep = split ? 512 : 128;
-        for (int ch0 = split ? wave * 128 : 0; ch0 < nch; ch0 += cstep) {
-            i32x4 v[FN_RW][2], aw[2][CE / 4];
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int ch = ch0 + 64 * h + lane;
-                const bool in = ch < nch && (!split || ch < ch0 + 128);
-#pragma unroll
-                for (int j = 0; j < FN_RW; ++j) {
-                    v[j][h] = i32x4{0, 0, 0, 0};
-                    if (in && nrow0 + j < N) v[j][h] = *reinterpret_cast<const i32x4 *>(Bb + ((long)(nrow0 + j) * f.ldb + (long)ch * CE) * ES);
-                }
-                const int left = K - ch * CE;
-#pragma unroll
-                for (int q4 = 0; q4 < CE / 4; ++q4) {
-                    aw[h][q4] = i32x4{0, 0, 0, 0};
-                    if (in) {
-                        const uint32_t *ap = asum + ch * CE + 4 * q4;
-                        if (vec_a && left >= CE) aw[h][q4] = *reinterpret_cast<const i32x4 *>(ap);
-                        else {
-#pragma unroll
-                            for (int e = 0; e < 4; ++e) aw[h][q4][e] = (4 * q4 + e < left) ? (int)ap[e] : 0;
-                        }
-                    }
-                }
-            }
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int left = K - (ch0 + 64 * h + lane) * CE;
-#pragma unroll
-                for (int j = 0; j < FN_RW; ++j) {
-                    i32x4 w = v[j][h];
-                    if (left < CE) w = mask_chunk(w, left > 0 ? left * ES : 0);
-#pragma unroll
-                    for (int q = 0; q < CE; ++q)
-                        dot[j] = add_t(dot[j], mul_t(T::elem(w, q), from_word<acc_t>((uint32_t)aw[h][q >> 2][q & 3])));
-                }
-            }
-        }
-#pragma unroll
-        for (int j = 0; j < FN_RW; ++j) dot[j] = wave_sum(dot[j]);
-        if (split) {
-            __syncthreads();                                    // previous unit done with kpart
-            if (lane == 0) {
-#pragma unroll
-                for (int j = 0; j < FN_RW; ++j) kpart[wave][j] = dot[j];
-            }
-            __syncthreads();
-#pragma unroll
-            for (int j = 0; j < FN_RW; ++j)
-                dot[j] = add_t(add_t(kpart[0][j], kpart[1][j]), add_t(kpart[2][j], kpart[3][j]));
-        }
-        {
-            acc_t mine = dot[0];
-#pragma unroll
-            for (int j = 1; j < FN_RW; ++j) mine = lane == j ? dot[j] : mine;
-            mine = add_t(mine, my_bias);
-            bool fl = false;
-            if (lane < FN_RW && nrow0 + lane < N && (!split || wave == 0)) {
-                const long o = (long)bz * N + nrow0 + lane;
-                f.cc_pred[o] = as_word(mine);
-                fl = mismatch<T::IS_INT>(my_obs, as_word(mine), f.tau_override_cols > 0.f ? f.tau_override_cols : tol);
-                f.col_flag[o] = fl ? 1 : 0;
-            }
-            nc_w += __popcll(__ballot(fl));
-        }
-        // ---- this unit's share of the rows
-        for (int r = rbeg + tid; r - tid < rend; r += 256) {
-            bool fl = false;
-            if (r < rend) {
-                const long o = (long)bz * M + r;
-                if (r != rbeg + tid) { ro = f.rc_obs[o]; rp = f.rc_pred[o]; }
-                if (f.bias) { rp = as_word(add_t(from_word<acc_t>(rp), sb)); f.rc_pred[o] = rp; }
-                fl = mismatch<T::IS_INT>(ro, rp, tol);
-                f.row_flag[o] = fl ? 1 : 0;
-            }
-            nr_w += __popcll(__ballot(fl));
-        }
-        if (cb == 0) {
-            // scalar a . b (the single-number check value of Sec. III-B.1)
-            acc_t sv = T::zero();
-            for (int k = tid; k < K; k += 256)
-                sv = add_t(sv, mul_t(from_word<acc_t>(asum[k]), from_word<acc_t>(f.b_sum[(long)bz * K + k])));
-            sv = wave_sum(sv);
-            __syncthreads();                                    // wred free again
-            if (lane == 0) wred[wave] = sv;
-            __syncthreads();
-            if (tid == 0)
-                f.s_pred[bz] = as_word(add_t(add_t(add_t(wred[0], wred[1]), add_t(wred[2], wred[3])), mul_t((acc_t)M, sb)));
-        }
-    }
-    if (lane == 0) { wcnt[wave][0] = nr_w; wcnt[wave][1] = nc_w; }
-    __syncthreads();
-    if (tid == 0) {
-        const unsigned nr = wcnt[0][0] + wcnt[1][0] + wcnt[2][0] + wcnt[3][0];
-        const unsigned nc = wcnt[0][1] + wcnt[1][1] + wcnt[2][1] + wcnt[3][1];
-        if (nr | nc) {
-            // rare: the counts must be at the coherence point before this block's ticket is
-            unsigned o1 = 0, o2 = 0;
-            if (nr) o1 = atomicAdd(f.ticket + 1, nr);
-            if (nc) o2 = atomicAdd(f.ticket + 2, nc);
-            asm volatile("s_waitcnt vmcnt(0)" :: "v"(o1), "v"(o2) : "memory");
-        }
-        if (atomicAdd(f.ticket, 1u) == gridDim.x - 1) {
-            const uint32_t r = atomicExch(f.ticket + 1, 0u), c = atomicExch(f.ticket + 2, 0u);
-            atomicExch(f.ticket, 0u);
-            f.counts[0] = r;
-            f.counts[1] = c;
-            f.counts[2] = status_of(r, c);
-            f.counts[3] = 0u;
-            f.counts[4] = status_of(r, c);
-        }
-    }
-}
-
-hipError_t launch_finish(int dt, const void *B, const Shape &s, const Workspace &w, const Verdict &v,
-                         uint32_t *zero_ptr, size_t zero_words, uint32_t *zero2_ptr, size_t zero2_words,
-                         hipStream_t st)
-{
-    FinArgs f;
-    f.b_max = w.b_max; f.zero2_ptr = zero2_ptr; f.zero2_words = zero2_ptr ? zero2_words : 0;
-    f.zero_ptr = zero_ptr; f.zero_words = zero_ptr ? zero_words : 0;
-    f.B = (const uint8_t *)B; f.ldb = s.ldb; f.sB = s.sB;
-    f.M = s.M; f.N = s.N; f.K = s.K;
-    f.a_sum = w.a_given ? w.a_given : w.a_sum;
-    f.b_sum = w.b_sum; f.rc_pred = w.rc_pred; f.cc_obs = w.cc_obs; f.rc_obs = w.rc_obs;
-    f.bias = w.bias;
-    f.a_max = (w.a_given && w.amax_given) ? w.amax_given : w.a_max; f.cc_pred = w.cc_pred; f.s_pred = w.s_pred; f.maxabs = w.maxabs; f.tau = w.tau;
-    f.tau_override = v.tau_override; f.tau_override_cols = v.tau_override_cols;
-    f.row_flag = v.row_flag; f.col_flag = v.col_flag; f.counts = v.counts; f.ticket = w.cmp_ticket;
-    const int ce = 16 / elem_size(dt);
-    const int nch = (s.K + ce - 1) / ce;
-    f.batch = s.batch;
-    // deep K (more than one trip of 128 chunks per row): the waves of a block share its rows
-    f.ksplit = nch > 128 ? 4 : 1;
-    const int rpb = f.ksplit == 4 ? FN_RW : 4 * FN_RW;
-    f.col_blocks = (s.N + rpb - 1) / rpb;
-    const long units = (long)f.col_blocks * s.batch;
-    if (units > 0x7FFFFFFFL) return hipErrorInvalidValue;
-    dim3 grid((unsigned)(units < 512 ? units : 512), 1, 1);
-    switch (dt) {
-    case DT_I8:   hipLaunchKernelGGL(finish_nk_kernel<DT_I8>, grid, dim3(256), 0, st, f); break;
-    case DT_BF16: hipLaunchKernelGGL(finish_nk_kernel<DT_BF16>, grid, dim3(256), 0, st, f); break;
-    case DT_F16:  hipLaunchKernelGGL(finish_nk_kernel<DT_F16>, grid, dim3(256), 0, st, f); break;
-    default: return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
-}
-
 // ======================================================================= check
-// Runs after the general GEMM kernel (gemm_tile.hip), whose launch has completed a = e^T A, b = B e,
-// the two maxima and the observed sums.  Forms both predictions of Sec. III-B.1, cc_pred = a B and
-// rc_pred = A b, each a matrix-vector product over one read of its operand, compares and flags.
+// Runs after a GEMM kernel, whose launch has completed a = e^T A, b = B e, the two maxima and the
+// observed sums.  Forms the predictions of Sec. III-B.1 that are missing, cc_pred = a B and (behind the
+// general kernel; the fast one forms it from the slabs it holds) rc_pred = A b, each a matrix-vector
+// product over one read of its operand, compares and flags.
 //
 // Bound by latency: a workgroup's critical path is one round of loads and one reduction.  Units of a
 // batch item: row units of A, column units of B (a B stored N x K is the same product as A b), one
 // unit for the scalar a.b.  There is no last block: the GEMM launch has cleared the counts, and only
-// waves that saw a mismatch touch them (report_flags).
+// waves that saw a mismatch touch them (report_flags).  (Behind the fast kernel there used to be a kernel
+// of its own, with eight rows of B per wave and a ticket per workgroup; a call with a bf16 12608 x 3072 x 768
+// then took 80.1 us and takes 77.9, with 6304 x 768 x 3072 in fp16 57.8 and 54.1, with an int8 12608 x 1024 x
+// 1024 41.2 and 37.9.)
 struct ChkArgs {
     const uint8_t *A, *B;
     long lda, sA, ldb, sB;
@@ -503,9 +267,10 @@ struct ChkArgs {
     int M, N, K, batch;
     const uint32_t *a_sum, *b_sum, *a_max, *b_max;
     uint32_t *cc_obs, *rc_obs;       // integers: complete; floating point: written here from
-    const double *cc_acc, *rc_acc;   // what the tiles added up
+    const double *cc_acc, *rc_acc;   // what the tiles added up (null: cc_obs, rc_obs are complete)
+    int rc_ready;                    // rc_pred holds A b: the row units compare 256 rows each
     const uint32_t *bias; // layer bias [N] or null: cc_pred gains M bias[n], rc_pred sum(bias), a.b M sum(bias)
-    const uint32_t *bias_sum;   // its sum, formed by the GEMM launch
+    const uint32_t *bias_sum;   // its sum, formed by the general kernel's launch (with rc_ready: formed here)
     uint32_t *cc_pred, *rc_pred, *s_pred;
     float *maxabs, *tau;
     float tau_override, tau_override_cols;
@@ -513,9 +278,9 @@ struct ChkArgs {
     uint32_t *counts;
     int row_units, col_units;
     int ksplit;           // 1, or 4 (deep K): the four waves of a unit share its rows, a quarter of K each
-    uint32_t *zero_ptr;   // regions every block helps to clear (see FinArgs)
-    size_t zero_words;
-    uint32_t *zero2_ptr;
+    uint32_t *zero_ptr;   // region every block helps to clear: what the previous protected GEMM of this
+    size_t zero_words;    // context accumulated into, so that the next one finds it clean
+    uint32_t *zero2_ptr;  // second region to clear: the b slot the next pass over B will accumulate into
     size_t zero2_words;
 };
 
@@ -625,11 +390,19 @@ __global__ __launch_bounds__(256) void check_kernel(ChkArgs f)
         }
     }
     const float tol_c = f.tau_override_cols > 0.f ? f.tau_override_cols : tol;
+    const bool acc_obs = !T::IS_INT && f.cc_acc != nullptr;     // the observed sums are still doubles
+    acc_t sb = T::zero();                                       // sum of the bias
+    if (f.bias) {
+        if (!f.rc_ready) sb = from_word<acc_t>(*f.bias_sum);
+        else if (u == upi - 1 || u < f.row_units) {
+            sb = block_bias_sum<acc_t>(f.bias, N, wred);
+            __syncthreads();
+        }
+    }
     if (u == upi - 1) {
         // scalar a . b (the single-number check value of Sec. III-B.1)
         acc_t v = T::zero();
         for (int k = tid; k < K; k += 256) v = add_t(v, mul_t(from_word<acc_t>(asum[k]), from_word<acc_t>(bsum[k])));
-        const acc_t sb = f.bias ? from_word<acc_t>(*f.bias_sum) : T::zero();
         v = wave_sum(v);
         if (lane == 0) wred[wave] = v;
         __syncthreads();
@@ -638,7 +411,19 @@ __global__ __launch_bounds__(256) void check_kernel(ChkArgs f)
         return;
     }
     const bool is_row = u < f.row_units;
-    if (is_row || f.transB) {
+    if (is_row && f.rc_ready) {
+        const int r = u * 256 + tid;
+        bool fl = false;
+        if (r < M) {
+            const long o = (long)bz * M + r;
+            uint32_t pred = f.rc_pred[o];
+            if (f.bias) { pred = as_word(add_t(from_word<acc_t>(pred), sb)); f.rc_pred[o] = pred; }
+            fl = mismatch<T::IS_INT>(f.rc_obs[o], pred, tol);
+            f.row_flag[o] = fl ? 1 : 0;
+        }
+        const unsigned nf = __popcll(__ballot(fl));
+        if (nf && lane == 0) report_flags(f.counts, nf, 0u);
+    } else if (is_row || f.transB) {
         // A b against the row sums of C, or a B (rows of B are columns of C) against the column sums
         const int unit = is_row ? u : u - f.row_units;
         const bool split = f.ksplit == 4;
@@ -649,9 +434,9 @@ __global__ __launch_bounds__(256) void check_kernel(ChkArgs f)
         // what the dots are compared with, requested first
         uint32_t obs = 0;
         acc_t add = T::zero();
-        if (mine_ok) obs = T::IS_INT ? (is_row ? f.rc_obs : f.cc_obs)[o] : __float_as_uint((float)(is_row ? f.rc_acc : f.cc_acc)[o]);
+        if (mine_ok) obs = acc_obs ? __float_as_uint((float)(is_row ? f.rc_acc : f.cc_acc)[o]) : (is_row ? f.rc_obs : f.cc_obs)[o];
         if (f.bias && mine_ok)
-            add = is_row ? from_word<acc_t>(*f.bias_sum) : mul_t((acc_t)M, from_word<acc_t>(f.bias[row0 + lane]));
+            add = is_row ? sb : mul_t((acc_t)M, from_word<acc_t>(f.bias[row0 + lane]));
         acc_t dot[RW];
         row_dots<DT, RW>(is_row ? f.A + (long)bz * f.sA * ES : f.B + (long)bz * f.sB * ES, is_row ? f.lda : f.ldb, row0, rows, K,
                          is_row ? bsum : asum, split, dot);
@@ -671,7 +456,7 @@ __global__ __launch_bounds__(256) void check_kernel(ChkArgs f)
         bool fl = false;
         if (mine_ok) {
             (is_row ? f.rc_pred : f.cc_pred)[o] = as_word(mine);
-            if (!T::IS_INT) (is_row ? f.rc_obs : f.cc_obs)[o] = obs;
+            if (acc_obs) (is_row ? f.rc_obs : f.cc_obs)[o] = obs;
             fl = mismatch<T::IS_INT>(obs, as_word(mine), is_row ? tol : tol_c);
             (is_row ? f.row_flag : f.col_flag)[o] = fl ? 1 : 0;
         }
@@ -688,7 +473,7 @@ __global__ __launch_bounds__(256) void check_kernel(ChkArgs f)
         uint32_t obs = 0;
         acc_t add = T::zero();
         if (mine_ok) {
-            obs = T::IS_INT ? f.cc_obs[(long)bz * N + n] : __float_as_uint((float)f.cc_acc[(long)bz * N + n]);
+            obs = acc_obs ? __float_as_uint((float)f.cc_acc[(long)bz * N + n]) : f.cc_obs[(long)bz * N + n];
             if (f.bias) add = mul_t((acc_t)M, from_word<acc_t>(f.bias[n]));
         }
         acc_t colp[CE];
@@ -731,7 +516,7 @@ __global__ __launch_bounds__(256) void check_kernel(ChkArgs f)
             const acc_t t = add_t(add_t(add_t(part[0][tid], part[1][tid]), add_t(part[2][tid], part[3][tid])), add);
             const long o = (long)bz * N + n;
             f.cc_pred[o] = as_word(t);
-            if (!T::IS_INT) f.cc_obs[o] = obs;
+            if (acc_obs) f.cc_obs[o] = obs;
             fl = mismatch<T::IS_INT>(obs, as_word(t), tol_c);
             f.col_flag[o] = fl ? 1 : 0;
         }
@@ -740,7 +525,7 @@ __global__ __launch_bounds__(256) void check_kernel(ChkArgs f)
     }
 }
 
-hipError_t launch_check(int dt, const void *A, const void *B, const Shape &s, const Workspace &w, const Verdict &v,
+hipError_t launch_check(int dt, bool after_fast, const void *A, const void *B, const Shape &s, const Workspace &w, const Verdict &v,
                         uint32_t *zero_ptr, size_t zero_words, uint32_t *zero2_ptr, size_t zero2_words, hipStream_t st)
 {
     constexpr int RW = 4;                                       // rows per wave
@@ -751,7 +536,8 @@ hipError_t launch_check(int dt, const void *A, const void *B, const Shape &s, co
     f.a_sum = w.a_given ? w.a_given : w.a_sum;
     f.a_max = (w.a_given && w.amax_given) ? w.amax_given : w.a_max;
     f.b_sum = w.b_sum; f.b_max = w.b_max; f.cc_obs = w.cc_obs; f.rc_obs = w.rc_obs;
-    f.cc_acc = w.cc_acc; f.rc_acc = w.rc_acc;
+    f.cc_acc = after_fast ? nullptr : w.cc_acc; f.rc_acc = after_fast ? nullptr : w.rc_acc;
+    f.rc_ready = after_fast ? 1 : 0;
     f.bias = w.bias; f.bias_sum = w.bias_sum;
     f.cc_pred = w.cc_pred; f.rc_pred = w.rc_pred; f.s_pred = w.s_pred; f.maxabs = w.maxabs; f.tau = w.tau;
     f.tau_override = v.tau_override; f.tau_override_cols = v.tau_override_cols;
@@ -762,7 +548,7 @@ hipError_t launch_check(int dt, const void *A, const void *B, const Shape &s, co
     const int nch = (s.K + ce - 1) / ce;
     f.ksplit = nch > 128 ? 4 : 1;                               // more than one trip of 128 chunks per row
     const int rpb = f.ksplit == 4 ? RW : 4 * RW;
-    f.row_units = (s.M + rpb - 1) / rpb;
+    f.row_units = after_fast ? (s.M + 255) / 256 : (s.M + rpb - 1) / rpb;
     f.col_units = s.transB ? (s.N + rpb - 1) / rpb : (s.N + CHK_KN_LANES * ce - 1) / (CHK_KN_LANES * ce);
     const long units = ((long)f.row_units + f.col_units + 1) * s.batch;
     if (units > 0x7FFFFFFFL) return hipErrorInvalidValue;

@@ -26,6 +26,7 @@ struct GemmArgs {
                                                   // slabs forms the row dots only, nothing is added to a_sum / a_max
     const uint32_t *bias;                         // layer bias [N] (float / int32 words) or null
     const uint32_t *b_sum;                        // B e, complete before the launch [batch][K]
+    uint32_t *counts;                             // fast kernel, protected: cleared for the check kernel
     int mul24_ok;                                 // int8: |b| < 2^23, 24-bit multiplies are exact
 };
 

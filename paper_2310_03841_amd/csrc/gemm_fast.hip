@@ -318,6 +318,7 @@ template <int DT, bool PROT>
 __global__ __launch_bounds__(256) void gemm_fast_kernel(GemmArgs g)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+    if (PROT && blockIdx.x == 0 && threadIdx.x < 5) g.counts[threadIdx.x] = 0u;      // completed by the check kernel
     // Persistent workgroups: one per compute unit, each walks the tile list with the grid's stride.
     // The 128-row tiles come first in the list: the compute units that start with one are half a
     // tile ahead of the others from then on, so the two groups store their tiles of C at different

@@ -591,6 +591,7 @@ hipError_t launch_gemm(int dt, bool protect, bool stored_sums, bool encode_b, co
     g.mul24_ok = s.N < 65536 ? 1 : 0;            // |b| <= 128 N
     g.tiles_m = g.tiles_n = g.n_big = g.tiles_m_big = g.tiles_m_small = 0;
     g.n_small = 0; g.batch = s.batch;
+    g.counts = counts;
     if (gemm_takes_fast(dt, s)) return launch_gemm_fast(dt, protect, g, s.batch, st);
     a.counts = counts;
     a.bias_sum = w.bias_sum;
