@@ -125,6 +125,25 @@ template <> struct Traits<DT_F16> {
     __device__ static __forceinline__ acc_t zero() { return 0.f; }
 };
 
+// ---------------------------------------------------------------- 16 x 16 MFMA: 64 bytes of K per row, four registers
+// Lane l of an operand holds row l & 15 and the 16-byte piece l >> 4 along K; of the result, column l & 15
+// (row of b) and rows 4 (l >> 4) + register.
+template <int DT> struct Acc4 { typedef __attribute__((ext_vector_type(4))) float type; };
+template <> struct Acc4<DT_I8> { typedef i32x4 type; };
+template <int DT>
+__device__ __forceinline__ typename Acc4<DT>::type mfma16(const i32x4 &a, const i32x4 &b, const typename Acc4<DT>::type &c)
+{
+    if constexpr (DT == DT_I8)
+        return __builtin_amdgcn_mfma_i32_16x16x64_i8(a, b, c, 0, 0, 0);
+    else if constexpr (DT == DT_BF16)
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+    else
+        return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
+}
+template <int DT> __device__ __forceinline__ typename Acc4<DT>::type acc4_zero()
+{
+    return typename Acc4<DT>::type{0, 0, 0, 0};
+}
 // ---------------------------------------------------------------- 32-bit word views of checksum values
 __device__ __forceinline__ uint32_t as_word(int v) { return (uint32_t)v; }
 __device__ __forceinline__ uint32_t as_word(float v) { return __float_as_uint(v); }

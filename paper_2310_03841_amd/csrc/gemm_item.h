@@ -275,22 +275,6 @@ __device__ __forceinline__ typename Traits<DT>::acc_t finite_or_again(typename T
 // Products with one are exact, and an accumulator adds in 32 bits as the vector unit does.  But Inf and NaN
 // reach through products with zeros what they have no part in: sums and dots that are not
 // finite are formed again, element by element (finite_or_again, dot_or_again).
-template <int DT> struct Acc4 { typedef __attribute__((ext_vector_type(4))) float type; };
-template <> struct Acc4<DT_I8> { typedef i32x4 type; };
-template <int DT>
-__device__ __forceinline__ typename Acc4<DT>::type mfma16(const i32x4 &a, const i32x4 &b, const typename Acc4<DT>::type &c)
-{
-    if constexpr (DT == DT_I8)
-        return __builtin_amdgcn_mfma_i32_16x16x64_i8(a, b, c, 0, 0, 0);
-    else if constexpr (DT == DT_BF16)
-        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
-    else
-        return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
-}
-template <int DT> __device__ __forceinline__ typename Acc4<DT>::type acc4_zero()
-{
-    return typename Acc4<DT>::type{0, 0, 0, 0};
-}
 template <int DT> __device__ __forceinline__ typename Traits<DT>::accv_t item_zero()
 {
     typename Traits<DT>::accv_t z;

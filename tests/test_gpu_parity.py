@@ -1590,3 +1590,24 @@ def test_item_kernels_keep_non_finite_values_apart(ctx_items, dtype, value, M, N
         assert mx1[0] == mx0[0] or was == mx0[0]
     else:
         assert np.isinf(mx1[0])
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("value", [np.inf, np.nan])
+def test_stored_sums_keep_non_finite_values_apart(ctx, dtype, value):
+    """One Inf or NaN in A on the 256 x 256-tile path: the stored-side sums of the other rows, which are formed
+    together with it, stay finite and its own row alone is flagged by the fused check."""
+    M, N, K, row, k = 600, 520, 256, 21, 7
+    A, B = gen.gen_operands(dtype, M, N, K, 41, 42, trans_b=True, batch=1)
+    run = Run(ctx, dtype, A, B, True)
+    bits = {("bf16", False): 0x7F80, ("bf16", True): 0x7FC0, ("f16", False): 0x7C00, ("f16", True): 0x7E00}
+    run.dA[0, row, k] = bits[dtype, bool(np.isnan(value))]
+    run.gemm(ab.ABFT_DETECT | ab.ABFT_STORED_SUMS)
+    rf, _ = run.flags()
+    others = np.arange(M) != row
+    assert rf[0, row] and not rf[0, others].any()
+    sto = run.ws(ab.ABFT_WS_RC_STO)[0]
+    C = orc.decode(run.C()[0], dtype).astype(np.float64)
+    assert not np.isfinite(sto[row]) and np.isfinite(sto[others]).all()
+    # fp32 sums of N stored values
+    assert np.max(np.abs(sto[others] - C[others].sum(1))) <= 2.0 ** -23 * N * np.max(np.abs(C[others])) * 4
