@@ -224,7 +224,9 @@ int abft_gemm_static(const void *A, const void *B, void *C, abft_dtype dtype, in
  * abft_result.tau; ignored for ABFT_I8).  Both must stay valid until that call's kernels have run;
  * the pointers are consumed by that call.  Where A is the stored output of a protected GEMM run
  * with ABFT_STORED_SUMS on the same shape family (consumer M, K = producer M, N), a and amax are
- * that call's ABFT_WS_CC_STO and ABFT_WS_C_MAX.  ABFT_WS_A_SUM is not filled by such a call. */
+ * that call's ABFT_WS_CC_STO and ABFT_WS_C_MAX.  They may be vectors of this same context, as its last
+ * call left them: such a vector is copied (one more small kernel) before the call clears anything.
+ * ABFT_WS_A_SUM is not filled by such a call. */
 int abft_supply_a(abft_ctx *ctx, const void *a, const void *amax);
 
 /* Pipelining several independent GEMMs (Sec. IV-C: the check must stay a small fraction of the

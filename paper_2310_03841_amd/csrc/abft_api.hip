@@ -31,6 +31,7 @@ struct abft_ctx {
     size_t vdirty[2];
     int32_t  *fix_tiles;
     uint32_t *small;        // fix_count[4], cmp_ticket[4], group tickets of the item kernel [64], bias sum
+    uint32_t *pool_given;   // copy of a supplied e^T A, then of max|A| per batch item: see own_given
     InjectArm arm;
     int last_hip;
     // what the context currently holds
@@ -81,7 +82,7 @@ extern "C" int abft_last_hip_error(const abft_ctx *ctx) { return ctx ? ctx->last
 
 // The device pools of a context, in 32-bit words, for a context that serves max_rows / max_cols /
 // max_depth (already rounded, see abft_create) / max_batch.
-constexpr int N_POOLS = 7;
+constexpr int N_POOLS = 8;
 constexpr int SMALL_WORDS = 8 + 64 + 1;
 // one region of pool_obs; even, so that the doubles at its end stay aligned in both regions
 static constexpr size_t obs_region_words(size_t R, size_t Cn, size_t D, size_t Bt)
@@ -91,7 +92,7 @@ static constexpr size_t obs_region_words(size_t R, size_t Cn, size_t D, size_t B
 static constexpr size_t pool_total_words(size_t R, size_t Cn, size_t D, size_t Bt)
 {
     return 2 * (D + Bt) + Bt * BATCH_WORDS + Cn + 2 * obs_region_words(R, Cn, D, Bt) + 2 * (R + Cn) +
-           (size_t)MAX_FIX_TILES * 3 + SMALL_WORDS;
+           (size_t)MAX_FIX_TILES * 3 + SMALL_WORDS + D + Bt;
 }
 static void pool_words(int64_t max_rows, int64_t max_cols, int64_t max_depth, int64_t max_batch, size_t words[N_POOLS])
 {
@@ -103,12 +104,13 @@ static void pool_words(int64_t max_rows, int64_t max_cols, int64_t max_depth, in
     words[4] = 2 * (R + Cn);                       // pool_vobs
     words[5] = (size_t)MAX_FIX_TILES * 3;          // fix_tiles
     words[6] = SMALL_WORDS;                        // small
+    words[7] = D + Bt;                             // pool_given
 }
 static void pool_slots(abft_ctx *c, void **slot[N_POOLS])
 {
     slot[0] = (void **)&c->pool_depth; slot[1] = (void **)&c->pool_batch; slot[2] = (void **)&c->pool_cols;
     slot[3] = (void **)&c->pool_obs;   slot[4] = (void **)&c->pool_vobs;  slot[5] = (void **)&c->fix_tiles;
-    slot[6] = (void **)&c->small;
+    slot[6] = (void **)&c->small;      slot[7] = (void **)&c->pool_given;
 }
 // Host-side bookkeeping of a context whose pools are all zero.
 static void start_clean(abft_ctx *c)
@@ -165,9 +167,10 @@ extern "C" int abft_destroy(abft_ctx *c)
 {
     if (!c || c->is_static) return ABFT_EINVAL;
     prof_free(c);
-    void *ptrs[] = {c->pool_depth, c->pool_batch, c->pool_cols, c->pool_obs, c->pool_vobs, c->fix_tiles, c->small};
-    for (void *p : ptrs)
-        if (p) (void)hipFree(p);
+    void **slot[N_POOLS];
+    pool_slots(c, slot);
+    for (void **p : slot)
+        if (*p) (void)hipFree(*p);
     delete c;
     return ABFT_OK;
 }
@@ -365,6 +368,38 @@ extern "C" int abft_encode_b(abft_ctx *ctx, const void *B, abft_dtype dtype, con
     return ABFT_OK;
 }
 
+// A supplied e^T A or max|A| may be a vector of this very context (abft_workspace of the call that produced
+// A).  The call that uses it clears and rewrites those vectors while it still reads them -- the check
+// kernel clears the region of the call before it, a call of a context with captured calls its own region
+// first of all -- so it works on a copy, taken ahead of everything else.
+static bool in_pools(abft_ctx *ctx, const void *p)
+{
+    size_t words[N_POOLS];
+    pool_words(ctx->cfg.max_rows, ctx->cfg.max_cols, ctx->cfg.max_depth, ctx->cfg.max_batch, words);
+    void **slot[N_POOLS];
+    pool_slots(ctx, slot);
+    for (int i = 0; i < N_POOLS; ++i) {
+        const uintptr_t base = (uintptr_t)*slot[i];
+        if ((uintptr_t)p >= base && (uintptr_t)p < base + words[i] * 4) return true;
+    }
+    return false;
+}
+static int own_given(abft_ctx *ctx, int dtype, const Shape &sh, Workspace *w, hipStream_t st)
+{
+    const size_t na = (size_t)sh.batch * sh.K, nm = (size_t)sh.batch;
+    if (in_pools(ctx, w->a_given)) {
+        HIP_TRY(launch_copy(ctx->pool_given, w->a_given, na, st));
+        w->a_given = ctx->pool_given;
+    }
+    // (integers have no use for max|A|: that pointer is not looked at)
+    if (dtype != DT_I8 && w->amax_given && in_pools(ctx, w->amax_given)) {
+        uint32_t *m = ctx->pool_given + ctx->cfg.max_depth;
+        HIP_TRY(launch_copy(m, w->amax_given, nm, st));
+        w->amax_given = m;
+    }
+    return ABFT_OK;
+}
+
 // The kernels of a protected GEMM, tiled path: pass over B (unless its encoding is cached; the general
 // kernel does it beside its tiles), GEMM, check.  The call accumulates into the region the previous protected call did not use.  It is
 // clean unless a call failed half way; the region of the previous call is cleared by this
@@ -373,6 +408,10 @@ static int enqueue_tiled(abft_ctx *ctx, int dtype, bool cached, bool stored, con
                          const Shape &sh, Workspace *w, const Verdict &v, const InjectArm &arm, hipEvent_t *ev,
                          hipStream_t st)
 {
+    if (w->a_given) {
+        int rc = own_given(ctx, dtype, sh, w, st);
+        if (rc) return rc;
+    }
     const bool gm = in_graph_mode(ctx, st);
     const int prev = ctx->cur;
     if (!gm) ctx->cur ^= 1;

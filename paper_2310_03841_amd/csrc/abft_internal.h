@@ -86,6 +86,7 @@ int device_cu_count(hipError_t *err);
 
 // ---- launchers (each enqueues on `st`, returns the hipError_t of the launch) ----
 hipError_t launch_zero(uint32_t *p, size_t nwords, hipStream_t st);
+hipError_t launch_copy(uint32_t *dst, const uint32_t *src, size_t nwords, hipStream_t st);
 // zero_ptr / zero_words: a region every block of the pass helps to clear (may be null / 0)
 hipError_t launch_encode_b(int dt, const void *B, const Shape &s, const Workspace &w, uint32_t *zero_ptr,
                            size_t zero_words, hipStream_t st);

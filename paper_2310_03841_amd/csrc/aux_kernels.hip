@@ -69,6 +69,21 @@ hipError_t launch_zero(uint32_t *p, size_t nwords, hipStream_t st)
     return hipGetLastError();
 }
 
+__global__ void copy_kernel(uint32_t *dst, const uint32_t *src, size_t n)
+{
+    size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    size_t step = (size_t)gridDim.x * blockDim.x;
+    for (; i < n; i += step) dst[i] = src[i];
+}
+
+hipError_t launch_copy(uint32_t *dst, const uint32_t *src, size_t nwords, hipStream_t st)
+{
+    size_t blocks = (nwords + 255) / 256;
+    if (blocks > 1024) blocks = 1024;
+    hipLaunchKernelGGL(copy_kernel, dim3((unsigned)blocks), dim3(256), 0, st, dst, src, nwords);
+    return hipGetLastError();
+}
+
 // ====================================================================== encode
 // Input-side checksum vectors (Sec. III-B.1 "Checksums"): a = e^T A (the input summed over its
 // rows) and b = B e (the weight reduced over its output dimension), both of length K, plus

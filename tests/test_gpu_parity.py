@@ -1153,6 +1153,63 @@ def test_input_checksum_carried_over_from_the_producer(ctx, dtype, M, N1, N2, K1
     assert not rf.any() and cons.cnt()[2] == ab.ABFT_CHECKSUM_SUSPECT
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("M,N1,N2,K1", [(197, 768, 264, 128), (2100, 1856, 2056, 192)])
+def test_input_checksum_carried_over_inside_one_context(dtype, M, N1, N2, K1):
+    """As above with producer and consumer on one context, the producer's vectors handed over as they
+    are (abft_workspace): first eagerly, then both calls captured and replayed.  The consumer clears
+    what the producer accumulated into, so it has to take the vectors in safety first."""
+    ctx = ab.abft_create(max_rows=M, max_cols=max(N1, N2), max_depth=max(N1, 256), max_batch=1)
+    try:
+        A1, W1 = gen.gen_operands(dtype, M, N1, K1, 721, 722, trans_b=True)
+        _, W2 = gen.gen_operands(dtype, M, N2, N1, 723, 724, trans_b=True)
+        prod = Run(ctx, dtype, A1, W1, True)
+        prod.gemm(ab.ABFT_DETECT | ab.ABFT_STORED_SUMS)
+        C1 = prod.C()
+        P2 = orc.protected_gemm(C1[0], W2[0], dtype, True)
+        cons = Run(ctx, dtype, C1, W2, True)                     # (its operand: the producer's C, bit for bit)
+
+        def pair():
+            assert ab.abft_gemm(ctx, prod.dA, prod.dB, prod.dC, prod.code, ab.ABFT_DETECT | ab.ABFT_STORED_SUMS,
+                                prod.shape, prod.result()) == ab.ABFT_OK
+            a_ptr, _ = ab.abft_workspace(ctx, ab.ABFT_WS_CC_STO, prod.shape)
+            m_ptr, _ = ab.abft_workspace(ctx, ab.ABFT_WS_C_MAX, prod.shape)
+            assert ab.abft_supply_a(ctx, a_ptr, m_ptr) == ab.ABFT_OK
+            assert ab.abft_gemm(ctx, cons.dA, cons.dB, cons.dC, cons.code, ab.ABFT_DETECT | ab.ABFT_A_CHECKSUM_GIVEN,
+                                cons.shape, cons.result()) == ab.ABFT_OK
+
+        def check(tag):
+            torch.cuda.synchronize()
+            rf, cf = cons.flags()
+            assert not rf.any() and not cf.any() and cons.cnt()[2] == ab.ABFT_CLEAN, tag
+            assert cons.ws(ab.ABFT_WS_TAU)[0, 0] == pytest.approx(P2.tau, rel=1e-5), tag
+            tol = 1e-2 * P2.tau
+            assert np.max(np.abs(cons.ws(ab.ABFT_WS_CC_PRED)[0] - P2.cc_pred)) <= tol * np.sqrt(M), tag
+            # a.b in fp32 over K terms of |a| <= M max|A|, |b| <= N max|B|
+            assert abs(cons.ws(ab.ABFT_WS_S_PRED)[0, 0] - P2.s_pred) <= 1e-4 * N1 * M * N2 * P2.max_a * P2.max_b, tag
+        for rep in range(4):
+            pair()
+            check(("eager", rep))
+        graph = torch.cuda.CUDAGraph()
+        side = torch.cuda.Stream()
+        side.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(side):
+            with torch.cuda.graph(graph, stream=side):
+                pair()
+        torch.cuda.current_stream().wait_stream(side)
+        for rep in range(3):
+            cons.counts.fill_(99)
+            cons.col_flag.fill_(7)
+            torch.cuda.synchronize()
+            graph.replay()
+            check(("replay", rep))
+            pair()
+            check(("eager between", rep))
+        del graph
+    finally:
+        ab.abft_destroy(ctx)
+
+
 def test_input_checksum_given_int8(ctx):
     """The same mode on the integer path: the caller's a = e^T A (here the oracle's, in Z/2^32);
     an input flipped after its checksum was taken flags exactly the columns j with B[k,j] != 0."""
