@@ -44,6 +44,7 @@ struct ItemArgs {
     // protected launches: everything below is written with plain stores, item by item
     uint32_t *cc_obs, *rc_obs, *rc_pred, *a_sum, *a_max, *b_sum, *b_max, *cc_pred, *s_pred;
     uint32_t *cc_sto, *rc_sto;                    // sums of C as stored (after rounding), on request (floating point)
+    uint32_t *c_max;                              // max|C as stored| as float bits, with them
     float *maxabs, *tau;
     float tau_override, tau_override_cols;
     uint8_t *row_flag, *col_flag;
@@ -661,12 +662,18 @@ __device__ __forceinline__ unsigned item_rows_out(const ItemArgs &g, int bz, int
     if ((tid & 63) == 0) *dot_out = as_word(sp);
     return nr;
 }
-template <int DT>
-__device__ __forceinline__ void item_scalars_out(const ItemArgs &g, int bz, const uint32_t *dots, int nw, const ItemTol &t)
+// misc: from word 16 a.b of the waves, with STO from word 40 their max|C as stored|
+template <int DT, bool STO>
+__device__ __forceinline__ void item_scalars_out(const ItemArgs &g, int bz, const uint32_t *misc, int nw, const ItemTol &t)
 {
     using T = Traits<DT>;
     typedef typename T::acc_t acc_t;
-    g.s_pred[bz] = as_word(sum_copies<acc_t>(dots, 1, nw));
+    g.s_pred[bz] = as_word(sum_copies<acc_t>(misc + 16, 1, nw));
+    if (STO) {
+        float m = 0.f;
+        for (int w = 0; w < nw; ++w) m = fmaxf(m, __uint_as_float(misc[40 + w]));
+        g.c_max[bz] = __float_as_uint(m);
+    }
     if (!T::IS_INT) {
         g.maxabs[(long)bz * 2] = t.ma;
         g.maxabs[(long)bz * 2 + 1] = t.mb;

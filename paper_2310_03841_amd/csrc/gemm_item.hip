@@ -63,6 +63,7 @@ hipError_t launch_gemm_item(int dt, bool protect, bool cached_b, bool stored_sum
     g.cc_obs = w.cc_obs; g.rc_obs = w.rc_obs; g.rc_pred = w.rc_pred; g.a_sum = w.a_sum; g.a_max = w.a_max;
     g.b_sum = w.b_sum; g.b_max = w.b_max; g.cc_pred = w.cc_pred; g.s_pred = w.s_pred;
     g.cc_sto = sto ? w.cc_sto : nullptr; g.rc_sto = sto ? w.rc_sto : nullptr;
+    g.c_max = w.c_max;
     g.maxabs = w.maxabs; g.tau = w.tau;
     g.tau_override = v ? v->tau_override : 0.f;
     g.tau_override_cols = v ? v->tau_override_cols : 0.f;

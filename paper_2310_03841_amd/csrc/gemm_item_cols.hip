@@ -34,7 +34,7 @@ struct ColsLds {
         rcpred = o; o += Mr;
         rspart = o; o += COLS_NW * RC;
         ccobs = o; o += Nr;
-        misc = o; o += 48;                       // 0..7 max|A|, 8..15 max|B|, 16..23 a.b per wave; 24..39 flag counts
+        misc = o; o += 48;                       // 0..7 max|A|, 8..15 max|B|, 16..23 a.b per wave; 24..39 flag counts; 40..47 max|C as stored|
         rcsto = o; o += sto ? Mr : 0;
         rsspart = o; o += sto ? COLS_NW * RC : 0;
         ccsto = o; o += sto ? Nr : 0;
@@ -98,7 +98,7 @@ __global__ __launch_bounds__(COLS_NT, TPW == 1 && !STO ? 4 : 2) void item_cols_k
 
         uint32_t amax = 0;
         acc_t cs[TPW][16];                       // column sums: register i of the blocks this wave owns, by lane's row
-        float cs_s[STO ? TPW : 1][16];
+        float cs_s[STO ? TPW : 1][16], cmax = 0.f;
 #pragma unroll
         for (int t = 0; t < TPW; ++t)
 #pragma unroll
@@ -210,6 +210,7 @@ __global__ __launch_bounds__(COLS_NT, TPW == 1 && !STO ? 4 : 2) void item_cols_k
                                             rs_s[r] += y0 + y1;
                                             cs_s[t][2 * j] += y0;
                                             cs_s[t][2 * j + 1] += y1;
+                                            cmax = fmaxf(cmax, fmaxf(fabsf(y0), fabsf(y1)));
                                         }
                                     }
                                     store_block<DT>(g, Cb, w, m0, n0, lane);
@@ -248,6 +249,10 @@ __global__ __launch_bounds__(COLS_NT, TPW == 1 && !STO ? 4 : 2) void item_cols_k
                 if (k < K) v = finite_or_again<DT>(v, as.src + (long)k * ES, g.lda * ES, M);
                 a_lds[k] = as_word(v);
             }
+            if (STO) {
+                const float m = wave_max(cmax);
+                if (lane == 0) misc[40 + wave] = __float_as_uint(m);
+            }
             // column sums of C over the lanes
             static_for<0, TPW>([&](auto t_c) {
                 constexpr int t = decltype(t_c)::value;
@@ -285,7 +290,7 @@ __global__ __launch_bounds__(COLS_NT, TPW == 1 && !STO ? 4 : 2) void item_cols_k
             nr_w += item_rows_out<DT>(g, bz, COLS_NT, tid, rcobs, rcpred, STO ? vec + L.rcsto : nullptr, a_lds, b_lds, tt.tol,
                                       misc + 16 + wave);
             item_barrier();
-            if (tid == 0) item_scalars_out<DT>(g, bz, misc + 16, COLS_NW, tt);
+            if (tid == 0) item_scalars_out<DT, STO>(g, bz, misc, COLS_NW, tt);
         }
         item_barrier();                          // LDS is reused by the next item
     }

@@ -39,7 +39,7 @@ struct RowsLds {
         rcpred = o; o += Mr;
         cspart = o; o += nw * Nr;
         ccpred = o; o += Nr;
-        misc = o; o += 48;                       // 0..7 max|A|, 8..15 max|B|, 16..23 a.b per wave; 24..39 flag counts
+        misc = o; o += 48;                       // 0..7 max|A|, 8..15 max|B|, 16..23 a.b per wave; 24..39 flag counts; 40..47 max|C as stored|
         rcsto = o; o += sto ? Mr : 0;
         csspart = o; o += sto ? nw * Nr : 0;
         total = o;
@@ -121,7 +121,7 @@ __global__ __launch_bounds__(512, TPW == 2 && !STO ? 4 : 2) void item_rows_kerne
 
         uint32_t amax = 0;
         acc_t csum[TPW];                         // column sums, folded: column fold16_column(lane) of each block
-        float csum_s[STO ? TPW : 1];
+        float csum_s[STO ? TPW : 1], cmax = 0.f;
 #pragma unroll
         for (int t = 0; t < TPW; ++t) { csum[t] = T::zero(); csum_s[STO ? t : 0] = 0.f; }
         for (int rb = wave; rb < MB; rb += nw) {
@@ -219,6 +219,8 @@ __global__ __launch_bounds__(512, TPW == 2 && !STO ? 4 : 2) void item_rows_kerne
                             float sv[16];
 #pragma unroll
                             for (int j = 0; j < 8; ++j) { sv[2 * j] = unpack_lo<DT>(w[j]); sv[2 * j + 1] = unpack_hi<DT>(w[j]); }
+#pragma unroll
+                            for (int j = 0; j < 8; ++j) cmax = fmaxf(cmax, fmaxf(fabsf(sv[2 * j]), fabsf(sv[2 * j + 1])));
                             rs_s += sum16<float>(sv);
                             csum_s[t] += fold16<float>(sv, lane);
                         }
@@ -250,6 +252,10 @@ __global__ __launch_bounds__(512, TPW == 2 && !STO ? 4 : 2) void item_rows_kerne
                     }
             }
             item_max_out<DT>(amax, Ab, g.lda * ES, M, K, lane, misc + wave);
+            if (STO) {
+                const float m = wave_max(cmax);
+                if (lane == 0) misc[40 + wave] = __float_as_uint(m);
+            }
             item_barrier();
             for (int k = tid; k < L.KP; k += nt) {
                 acc_t v = sum_copies<acc_t>(vec + L.apart + k, L.KP, wact);
@@ -291,7 +297,7 @@ __global__ __launch_bounds__(512, TPW == 2 && !STO ? 4 : 2) void item_rows_kerne
                 }
                 nc_w += __popcll(__ballot(fl));
             }
-            if (tid == 0) item_scalars_out<DT>(g, bz, misc + 16, nw, tt);
+            if (tid == 0) item_scalars_out<DT, STO>(g, bz, misc, nw, tt);
         }
         item_barrier();                          // LDS is reused by the next item
     }

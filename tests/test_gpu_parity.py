@@ -1668,3 +1668,27 @@ def test_stored_sums_keep_non_finite_values_apart(ctx, dtype, value):
     assert not np.isfinite(sto[row]) and np.isfinite(sto[others]).all()
     # fp32 sums of N stored values
     assert np.max(np.abs(sto[others] - C[others].sum(1))) <= 2.0 ** -23 * N * np.max(np.abs(C[others])) * 4
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("M,N,K,trans_b", [(300, 50, 90, False), (40, 128, 96, True), (197, 64, 577, False), (70, 200, 64, True)])
+def test_item_kernels_form_the_largest_stored_magnitude(dtype, M, N, K, trans_b):
+    """With the stored-side sums comes max|C as stored| of every item, the max|A| of a consumer of this C:
+    the exact maximum of the stored values, without NaN, and again without what an earlier call left."""
+    batch = 64
+    A, B = gen.gen_operands(dtype, M, N, K, 43, 44, trans_b=trans_b, batch=batch, b_kind="act")
+    ctx = ab.abft_create(max_rows=batch * M, max_cols=batch * N, max_depth=batch * (K + 127), max_batch=batch)
+    try:
+        run = Run(ctx, dtype, A, B, trans_b)
+        assert ab.abft_tile_shape(run.code, run.shape) == (M, N)
+        for rep in range(2):
+            if rep == 1:                                         # smaller values, and a NaN in one item
+                run.dA[:, :, :K].copy_((run.dA[:, :, :K].view(torch.bfloat16 if dtype == "bf16" else torch.float16) * 0.25)
+                                       .view(torch.int16))
+                run.dA[3, M // 2, K // 2] = 0x7FC0 if dtype == "bf16" else 0x7E00
+            run.gemm(ab.ABFT_DETECT | ab.ABFT_STORED_SUMS)
+            C = np.abs(orc.decode(run.C(), dtype)).reshape(batch, -1)
+            assert rep == 0 or np.isnan(C[3]).sum() == N
+            assert np.array_equal(run.ws(ab.ABFT_WS_C_MAX)[:, 0], np.nanmax(C, axis=1).astype(np.float32)), rep
+    finally:
+        ab.abft_destroy(ctx)
