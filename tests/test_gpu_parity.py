@@ -1692,3 +1692,26 @@ def test_item_kernels_form_the_largest_stored_magnitude(dtype, M, N, K, trans_b)
             assert np.array_equal(run.ws(ab.ABFT_WS_C_MAX)[:, 0], np.nanmax(C, axis=1).astype(np.float32)), rep
     finally:
         ab.abft_destroy(ctx)
+
+
+
+@pytest.mark.parametrize("dtype", ["i8", "bf16", "f16"])
+@pytest.mark.parametrize("M,N,K,trans_b", [(300, 50, 90, False), (40, 128, 96, True), (70, 200, 64, True), (64, 300, 64, False)])
+def test_item_kernels_flip_an_accumulator_unprotected(ctx_items, dtype, M, N, K, trans_b):
+    """ABFT_INJECT_ACCUMULATOR is applied in every mode: a campaign on an unprotected layer sees the flip
+    in C, at the element alone, and once."""
+    batch = 64
+    A, B = gen.gen_operands(dtype, M, N, K, 47, 48, trans_b=trans_b, batch=batch, b_kind="act")
+    run = Run(ctx_items, dtype, A, B, trans_b)
+    assert ab.abft_tile_shape(run.code, run.shape) == (M, N)
+    run.gemm(ab.ABFT_OFF)
+    C0 = run.C().copy()
+    for (bi, i, j) in [(0, 0, 0), (batch - 1, M - 1, N - 1), (7, M // 2, N // 2)]:
+        run.inject(bi, i, j, 30, ab.ABFT_INJECT_ACCUMULATOR)
+        run.gemm(ab.ABFT_OFF)
+        moved = np.argwhere(run.C() != C0)
+        assert moved.tolist() == [[bi, i, j]]
+        if dtype == "i8":
+            assert run.C()[bi, i, j] == C0[bi, i, j] ^ (1 << 30)
+        run.gemm(ab.ABFT_OFF)
+        assert np.array_equal(run.C(), C0)
