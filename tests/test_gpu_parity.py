@@ -94,19 +94,42 @@ SHAPES = [
     (197, 197, 64, 3, True),       # per-head Q K^T
     (197, 64, 197, 3, False),      # per-head attn V (B stored K x N)
     (150, 200, 136, 2, False),
-    (777, 600, 192, 1, True),      # 256x256-tile path for 16-bit types (K a multiple of 64)
-    (520, 1030, 256, 2, True),     # 256x256-tile path for all types, ragged both ways, batched
-    (512, 512, 128, 1, True),      # tile-exact on the 256x256 path
-    (520, 600, 4096, 1, True),     # deepest K of a protected GEMM: 16 / 32 slabs per workgroup to reduce
-    (600, 512, 640, 1, True),      # two tile columns: a workgroup reduces every other slab of its tile row
-    (520, 1300, 1152, 1, True),    # six tile columns, a ragged last one: owned slabs three (int8: one or two) apart
-    (140, 90, 4096, 1, False),     # the same on the general kernel
+    (777, 600, 192, 1, True),      # whole slabs for 16-bit types, half a slab too many for int8
+    (520, 1030, 256, 2, True),     # ragged both ways, batched
+    (512, 512, 128, 1, True),      # tile-exact on tiles of every size
+    (520, 600, 4096, 1, True),     # deepest K of a protected GEMM
+    (600, 512, 640, 1, True),
+    (520, 1300, 1152, 1, True),
+    (140, 90, 4096, 1, False),     # the deepest with B stored K x N
 ]
+
+# The fast kernel takes problems of 64 of its 256 x 256 tiles and more.
+FAST_SHAPES = [
+    (2050, 2060, 384, 1, True),    # 9 x 9 tiles, ragged both ways; int8: three slabs, the fewest it takes
+    (520, 1030, 384, 6, True),     # 3 x 5 tiles an item, ragged both ways, batched
+    (2048, 2048, 384, 1, True),    # tile-exact
+    (2049, 2049, 4096, 1, True),   # deepest K of a protected GEMM, a row and a column in the last tiles
+    (8200, 512, 640, 1, True),     # two tile columns: a workgroup reduces every other slab of its tile row
+    (2900, 1300, 1152, 1, True),   # six tile columns, a ragged last one: owned slabs three (int8: one or two) apart
+]
+
+
+def assert_fast(dtype, M, N, K, batch=1):
+    """The problem is one of the fast kernel's."""
+    s = ab.make_shape(M, N, K, batch=batch, transB=True)
+    assert ab.abft_tile_shape(ab.DTYPE_CODE[dtype], s) == (256, 256), (dtype, M, N, K, batch)
 
 
 @pytest.mark.parametrize("dtype", ["i8", "bf16", "f16"])
 @pytest.mark.parametrize("M,N,K,batch,trans_b", SHAPES)
 def test_clean_gemm_matches_oracle(ctx, dtype, M, N, K, batch, trans_b):
+    _clean_case(ctx, dtype, M, N, K, batch, trans_b)
+
+
+@pytest.mark.parametrize("dtype", ["i8", "bf16", "f16"])
+@pytest.mark.parametrize("M,N,K,batch,trans_b", FAST_SHAPES)
+def test_fast_kernel_clean_matches_oracle(ctx, dtype, M, N, K, batch, trans_b):
+    assert_fast(dtype, M, N, K, batch)
     _clean_case(ctx, dtype, M, N, K, batch, trans_b)
 
 
@@ -133,8 +156,10 @@ def _clean_case(ctx, dtype, M, N, K, batch, trans_b):
 
 
 @pytest.mark.parametrize("dtype", ["i8", "bf16", "f16"])
-def test_cached_b_checksum(ctx, dtype):
-    M, N, K = 200, 136, 320
+@pytest.mark.parametrize("M,N,K", [(200, 136, 320), (2050, 2060, 384)])
+def test_cached_b_checksum(ctx, dtype, M, N, K):
+    if M >= 2048:
+        assert_fast(dtype, M, N, K)
     A, B = gen.gen_operands(dtype, M, N, K, 7, 8, trans_b=True)
     A2, _ = gen.gen_operands(dtype, M, N, K, 9, 8, trans_b=True)
     run = Run(ctx, dtype, A, B, True)
@@ -148,8 +173,10 @@ def test_cached_b_checksum(ctx, dtype):
 
 @pytest.mark.parametrize("dtype", ["i8", "bf16", "f16"])
 @pytest.mark.parametrize("M,N,K,batch,trans_b", [(197, 768, 768, 1, True), (130, 70, 100, 2, False),
-                                                  (600, 520, 256, 1, True)])
+                                                  (600, 520, 256, 1, True), (2050, 2060, 384, 1, True)])
 def test_stored_flip_verify_correct(ctx, dtype, M, N, K, batch, trans_b):
+    if M >= 2048:
+        assert_fast(dtype, M, N, K)
     A, B = gen.gen_operands(dtype, M, N, K, 31, 32, trans_b=trans_b, batch=batch)
     run = Run(ctx, dtype, A, B, trans_b)
     P = oracle_items(dtype, A, B, trans_b)
@@ -201,8 +228,11 @@ def test_stored_flip_verify_correct(ctx, dtype, M, N, K, batch, trans_b):
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 @pytest.mark.parametrize("M,N,K,batch,trans_b", [(600, 520, 256, 1, True), (197, 768, 768, 1, True),
-                                                  (130, 70, 100, 2, False)])
+                                                  (130, 70, 100, 2, False), (2050, 2060, 384, 1, True),
+                                                  (520, 1030, 384, 6, True)])
 def test_tightened_storage_check(ctx, dtype, M, N, K, batch, trans_b):
+    if K == 384:
+        assert_fast(dtype, M, N, K, batch)
     _tightened_storage_case(ctx, dtype, M, N, K, batch, trans_b)
 
 
@@ -401,8 +431,10 @@ def _with_ld(C, run):
 
 
 @pytest.mark.parametrize("dtype", ["i8", "bf16", "f16"])
-def test_accumulator_flip_is_caught_by_the_fused_check(ctx, dtype):
-    M, N, K = 197, 200, 256
+@pytest.mark.parametrize("M,N,K", [(197, 200, 256), (2050, 2060, 384)])
+def test_accumulator_flip_is_caught_by_the_fused_check(ctx, dtype, M, N, K):
+    if M >= 2048:
+        assert_fast(dtype, M, N, K)
     A, B = gen.gen_operands(dtype, M, N, K, 41, 42, trans_b=True)
     run = Run(ctx, dtype, A, B, True)
     run.gemm(ab.ABFT_DETECT)
@@ -410,7 +442,7 @@ def test_accumulator_flip_is_caught_by_the_fused_check(ctx, dtype):
     # fp32 accumulators: only the top exponent bit turns a value of order one into a delta
     # above tau for certain; integers: any bit does
     fp = dtype != "i8"
-    for (i, j, bit) in [(0, 0, 30), (196, 199, 30 if fp else 27), (130, 129, 30 if fp else 0)]:
+    for (i, j, bit) in [(0, 0, 30), (M - 1, N - 1, 30 if fp else 27), (130, 129, 30 if fp else 0)]:
         print(f"acc flip dtype={dtype} i={i} j={j} bit={bit}", flush=True)
         run.inject(0, i, j, bit, ab.ABFT_INJECT_ACCUMULATOR)
         run.gemm(ab.ABFT_DETECT)
@@ -454,11 +486,11 @@ def test_corrupted_checksum_is_one_sided(ctx):
 
 @pytest.mark.gpu
 def test_context_reuse_across_shapes_and_modes(ctx):
-    """Protected calls alternate between two accumulate regions and each call's finish kernel
+    """Protected calls alternate between two accumulate regions and each call's check kernel
     clears the other one: whatever the order of shapes, dtypes and cached / uncached calls, a
     clean GEMM must come out clean, with exact integer checksums."""
     cases = [("i8", 300, 520, 256, True), ("bf16", 600, 640, 192, True), ("i8", 130, 70, 100, False),
-             ("i8", 640, 520, 384, True)]
+             ("i8", 640, 520, 384, True), ("bf16", 2050, 2060, 384, True)]
     runs = []
     for k, (dtype, M, N, K, tb) in enumerate(cases):
         A, B = gen.gen_operands(dtype, M, N, K, 71 + k, 81 + k, trans_b=tb)
@@ -917,13 +949,16 @@ def test_item_kernel_flips_cached_b_and_correction(ctx_items, dtype, M, N, K, ba
 
 @pytest.mark.parametrize("dtype", ["i8", "bf16"])
 @pytest.mark.parametrize("M,N,K,batch,trans_b", [(197, 130, 72, 3, True), (150, 70, 100, 2, False),
-                                                 (600, 520, 256, 2, True),       # 256-row tiles
+                                                 (600, 520, 256, 2, True),
+                                                 (520, 1030, 384, 6, True),      # the fast kernel's
                                                  (70, 50, 40, 64, False), (100, 130, 72, 65, True)])
 def test_leading_dimensions_and_batch_strides(ctx_items, dtype, M, N, K, batch, trans_b):
     """Operands and C embedded in larger allocations: leading dimensions wider than the rows,
     batch strides longer than an item.  Everything outside the M x N items of C must stay as it
     was; everything outside the operands is filled with a pattern that must never be used."""
     ctx = ctx_items
+    if batch == 6:
+        assert_fast(dtype, M, N, K, batch)
     es, osz = (1, 4) if dtype == "i8" else (2, 2)
     A, B = gen.gen_operands(dtype, M, N, K, 71, 72, trans_b=trans_b, batch=batch)
     P = oracle_items(dtype, A, B, trans_b)
@@ -1035,14 +1070,17 @@ def test_faults_in_the_operands(ctx, M, N, K):
 
 @pytest.mark.parametrize("dtype", ["i8", "bf16", "f16"])
 @pytest.mark.parametrize("M,N,K,batch,trans_b", [(777, 600, 192, 1, True), (300, 200, 264, 2, True), (150, 200, 136, 2, False),
-                                                 (197, 64, 197, 3, False), (100, 130, 72, 65, True), (520, 1030, 256, 1, True)])
+                                                 (197, 64, 197, 3, False), (100, 130, 72, 65, True), (520, 1030, 256, 1, True),
+                                                 (2050, 2060, 384, 1, True), (520, 1030, 384, 6, True)])
 def test_gemm_with_layer_bias(ctx_items, dtype, M, N, K, batch, trans_b):
     """C = A B + bias (Sec. III-B.1 "Checksums": the checked product is adjusted by the layer
     bias): C, both predictions, both observed sums, the scalar, clean flags, the unprotected mode,
     and a stored flip localised and repaired by a tile recompute that adds the bias again -- on the
-    256-wide tiles, the general kernel, both layouts of B, batches, and a batch the bias-free call
+    fast and on the general kernel, both layouts of B, batches, and a batch the bias-free call
     would hand to the one-workgroup-per-item kernel."""
     ctx = ctx_items
+    if K == 384:
+        assert_fast(dtype, M, N, K, batch)
     A, B = gen.gen_operands(dtype, M, N, K, 301 + M, 302 + N, trans_b=trans_b, batch=batch,
                             b_kind="weight" if batch == 1 else "act")
     rng = np.random.default_rng(77 + N)
@@ -1091,7 +1129,7 @@ def test_gemm_with_layer_bias(ctx_items, dtype, M, N, K, batch, trans_b):
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
-@pytest.mark.parametrize("M,N1,N2,K1", [(600, 512, 520, 256), (197, 768, 264, 128)])
+@pytest.mark.parametrize("M,N1,N2,K1", [(600, 512, 520, 256), (197, 768, 264, 128), (2100, 1856, 2056, 192)])
 def test_input_checksum_carried_over_from_the_producer(ctx, dtype, M, N1, N2, K1):
     """Sec. V "Optimizations" (2): the checksum of a tensor is generated while it is produced.
     Producer C1 = A1 W1^T with the stored-side sums; consumer C2 = C1 W2^T takes e^T C1 and
@@ -1100,6 +1138,9 @@ def test_input_checksum_carried_over_from_the_producer(ctx, dtype, M, N1, N2, K1
     the two calls is outside the consumer's own view of its input (its row prediction is formed from
     the flipped tensor) but disagrees with the carried checksum: the column check flags exactly the
     columns the oracle names, the row check stays silent."""
+    if M >= 2048:
+        assert_fast(dtype, M, N1, K1)
+        assert_fast(dtype, M, N2, N1)
     A1, W1 = gen.gen_operands(dtype, M, N1, K1, 701, 702, trans_b=True)
     _, W2 = gen.gen_operands(dtype, M, N2, N1, 703, 704, trans_b=True)
     prod = Run(ctx, dtype, A1, W1, True)
@@ -1150,7 +1191,14 @@ def test_input_checksum_carried_over_from_the_producer(ctx, dtype, M, N1, N2, K1
         shift = np.abs(delta * orc.decode(W2[0], dtype)[:, k])                 # what column j of C2 moved by
     sure, quiet = ~(shift <= 2 * P2.tau), shift < P2.tau / 2
     assert cf[0][sure].all() and not cf[0][quiet].any() and sure.any()
-    assert not rf.any() and cons.cnt()[2] == ab.ABFT_CHECKSUM_SUSPECT
+    # The flipped row's own prediction and sum are of the flip's size.  The fast kernel adds both up in fp32,
+    # so they differ by up to 2^-24 N2 |delta| max|W2|, which for bf16 (delta about 1e37) is far above tau;
+    # the general kernel's sums, in doubles, agree here.
+    rounding = 2.0 ** -24 * N2 * abs(delta) * P2.max_b
+    may = np.zeros((1, M), bool)
+    may[0, i] = M >= 2048 and rounding > P2.tau
+    assert not (rf & ~may).any()
+    assert cons.cnt()[2] == (ab.ABFT_LOCALISED if rf.any() else ab.ABFT_CHECKSUM_SUSPECT)
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
@@ -1210,10 +1258,12 @@ def test_input_checksum_carried_over_inside_one_context(dtype, M, N1, N2, K1):
         ab.abft_destroy(ctx)
 
 
-def test_input_checksum_given_int8(ctx):
+@pytest.mark.parametrize("M,N,K", [(300, 264, 256), (2050, 2060, 384)])
+def test_input_checksum_given_int8(ctx, M, N, K):
     """The same mode on the integer path: the caller's a = e^T A (here the oracle's, in Z/2^32);
     an input flipped after its checksum was taken flags exactly the columns j with B[k,j] != 0."""
-    M, N, K = 300, 264, 256
+    if M >= 2048:
+        assert_fast("i8", M, N, K)
     A, B = gen.gen_operands("i8", M, N, K, 711, 712, trans_b=True)
     P = orc.protected_gemm(A[0], B[0], "i8", True)
     a_dev = torch.from_numpy(ring(P.a).view(np.int32)).to("cuda")
@@ -1317,7 +1367,8 @@ def test_item_kernel_more_items_than_workgroups(dtype, M, N, K, batch, trans_b):
 
 
 @pytest.mark.parametrize("dtype,M,N,K,batch,trans_b", [("i8", 197, 768, 768, 1, True), ("bf16", 600, 520, 256, 2, True),
-                                                       ("bf16", 100, 130, 72, 65, True), ("i8", 70, 50, 40, 64, False)])
+                                                       ("bf16", 100, 130, 72, 65, True), ("i8", 70, 50, 40, 64, False),
+                                                       ("bf16", 520, 1030, 384, 6, True), ("i8", 2050, 2060, 384, 1, True)])
 def test_calls_can_be_captured_in_a_graph(dtype, M, N, K, batch, trans_b):
     """The hot calls only enqueue kernels (no allocation, no copy, no synchronisation, no memset
     node): a protected GEMM followed by a verify is captured once and replayed several times, with
@@ -1383,7 +1434,7 @@ def test_calls_can_be_captured_in_a_graph(dtype, M, N, K, batch, trans_b):
                 run.correct()
                 assert run.cnt()[2] == ab.ABFT_CLEAN and torch.equal(run.dC[:, :, :N], C_eager[:, :, :N]), rep
             run.dC.fill_(0)
-            run.gemm(ab.ABFT_DETECT)                 # nothing cached: pass over B, GEMM, finish
+            run.gemm(ab.ABFT_DETECT)                 # nothing cached
             assert torch.equal(run.dC[:, :, :N], C_eager[:, :, :N]), rep
             rf, cf = run.flags()
             assert not rf.any() and not cf.any() and run.cnt()[2] == ab.ABFT_CLEAN, rep
@@ -1393,7 +1444,8 @@ def test_calls_can_be_captured_in_a_graph(dtype, M, N, K, batch, trans_b):
         ab.abft_destroy(ctx)
 
 
-@pytest.mark.parametrize("dtype,M,N,K", [("bf16", 600, 520, 256), ("f16", 197, 768, 768)])
+@pytest.mark.parametrize("dtype,M,N,K", [("bf16", 600, 520, 256), ("f16", 197, 768, 768), ("bf16", 2050, 2060, 384),
+                                           ("f16", 2050, 2060, 384)])
 def test_fault_before_the_stored_sums_is_corrected_to_clean(ctx, dtype, M, N, K):
     """A fault that is in the accumulators when the epilogue sums the values it stores is part of
     those sums.  After abft_correct has recomputed the tile, the sums of its rows and columns are
@@ -1531,11 +1583,13 @@ def test_two_streams_half_a_step_apart():
 
 
 @pytest.mark.parametrize("dtype", ["i8", "bf16"])
-def test_detect_correct_on_clean_input_leaves_the_fused_verdict(ctx, dtype):
+@pytest.mark.parametrize("M,N,K", [(700, 520, 192), (2050, 2060, 384)])
+def test_detect_correct_on_clean_input_leaves_the_fused_verdict(ctx, dtype, M, N, K):
     """A clean DETECT_CORRECT call recomputes nothing and does not re-sum the stored C: flags,
     counts and C are those of a DETECT call; a stored flip afterwards is still found and repaired
     (the correction then sums the stored C itself)."""
-    M, N, K = 700, 520, 192
+    if M >= 2048:
+        assert_fast(dtype, M, N, K)
     A, B = gen.gen_operands(dtype, M, N, K, 311, 312, trans_b=True)
     run = Run(ctx, dtype, A, B, True)
     P = oracle_items(dtype, A, B, True)
@@ -1651,10 +1705,15 @@ def test_item_kernels_keep_non_finite_values_apart(ctx_items, dtype, value, M, N
 
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 @pytest.mark.parametrize("value", [np.inf, np.nan])
-def test_stored_sums_keep_non_finite_values_apart(ctx, dtype, value):
-    """One Inf or NaN in A on the 256 x 256-tile path: the stored-side sums of the other rows, which are formed
-    together with it, stay finite and its own row alone is flagged by the fused check."""
-    M, N, K, row, k = 600, 520, 256, 21, 7
+@pytest.mark.parametrize("M,N,K", [(600, 520, 256), (2100, 2090, 256)])
+@pytest.mark.parametrize("row", [21, -3])
+def test_stored_sums_keep_non_finite_values_apart(ctx, dtype, value, M, N, K, row):
+    """One Inf or NaN in A, on the general and on the fast kernel, in a whole and in the ragged last group of
+    rows: the stored-side sums of the other rows, which are formed together with it, stay finite and right,
+    its own row alone is flagged by the fused check, and max|C as stored| takes Inf but not NaN."""
+    if M >= 2048:
+        assert_fast(dtype, M, N, K)
+    row, k = row % M, 7
     A, B = gen.gen_operands(dtype, M, N, K, 41, 42, trans_b=True, batch=1)
     run = Run(ctx, dtype, A, B, True)
     bits = {("bf16", False): 0x7F80, ("bf16", True): 0x7FC0, ("f16", False): 0x7C00, ("f16", True): 0x7E00}
@@ -1663,11 +1722,41 @@ def test_stored_sums_keep_non_finite_values_apart(ctx, dtype, value):
     rf, _ = run.flags()
     others = np.arange(M) != row
     assert rf[0, row] and not rf[0, others].any()
-    sto = run.ws(ab.ABFT_WS_RC_STO)[0]
+    sto, cst = run.ws(ab.ABFT_WS_RC_STO)[0], run.ws(ab.ABFT_WS_CC_STO)[0]
     C = orc.decode(run.C()[0], dtype).astype(np.float64)
     assert not np.isfinite(sto[row]) and np.isfinite(sto[others]).all()
     # fp32 sums of N stored values
     assert np.max(np.abs(sto[others] - C[others].sum(1))) <= 2.0 ** -23 * N * np.max(np.abs(C[others])) * 4
+    # every column holds the value's row
+    assert not np.isfinite(cst).any()
+    cmax = run.ws(ab.ABFT_WS_C_MAX)[0, 0]
+    assert np.isinf(cmax) if np.isinf(C[row]).any() else cmax == np.float32(np.max(np.abs(C[others])))
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("value", [np.inf, np.nan])
+@pytest.mark.parametrize("M,N,K", [(600, 520, 256), (2100, 2090, 256)])
+@pytest.mark.parametrize("col", [150, -3])
+def test_stored_sums_of_other_columns_keep_a_column_apart(ctx, dtype, value, M, N, K, col):
+    """The same with the value in B, in one column of C, in a whole and in the ragged last group of columns."""
+    if M >= 2048:
+        assert_fast(dtype, M, N, K)
+    col, k = col % N, 7
+    A, B = gen.gen_operands(dtype, M, N, K, 45, 46, trans_b=True, batch=1)
+    run = Run(ctx, dtype, A, B, True)
+    bits = {("bf16", False): 0x7F80, ("bf16", True): 0x7FC0, ("f16", False): 0x7C00, ("f16", True): 0x7E00}
+    run.dB[0, col, k] = bits[dtype, bool(np.isnan(value))]
+    run.gemm(ab.ABFT_DETECT | ab.ABFT_STORED_SUMS)
+    _, cf = run.flags()
+    others = np.arange(N) != col
+    assert cf[0, col]
+    sto, cst = run.ws(ab.ABFT_WS_RC_STO)[0], run.ws(ab.ABFT_WS_CC_STO)[0]
+    C = orc.decode(run.C()[0], dtype).astype(np.float64)
+    assert not np.isfinite(cst[col]) and np.isfinite(cst[others]).all() and not np.isfinite(sto).any()
+    # fp32 sums of M stored values
+    assert np.max(np.abs(cst[others] - C[:, others].sum(0))) <= 2.0 ** -23 * M * np.max(np.abs(C[:, others])) * 4
+    cmax = run.ws(ab.ABFT_WS_C_MAX)[0, 0]
+    assert np.isinf(cmax) if np.isinf(C[:, col]).any() else cmax == np.float32(np.max(np.abs(C[:, others])))
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
