@@ -386,19 +386,21 @@ __global__ __launch_bounds__(256) void check_kernel(ChkArgs f)
     __shared__ acc_t part[4][CHK_KN_LANES * CE > RW ? CHK_KN_LANES * CE : RW];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int M = f.M, N = f.N, K = f.K;
-    const int upi = f.row_units + f.col_units + 1;              // units per batch item
-    const int bz = blockIdx.x / upi, u = blockIdx.x - bz * upi;
+    const unsigned upi = (unsigned)f.row_units + f.col_units + 1;      // units per batch item
+    const unsigned id = blockIdx.y * gridDim.x + blockIdx.x;
+    if (id >= upi * f.batch) return;
+    const int bz = id / upi, u = id - bz * upi;
     const uint32_t *asum = f.a_sum + (long)bz * K, *bsum = f.b_sum + (long)bz * K;
     {
-        const size_t nb = gridDim.x;
-        for (size_t i = (size_t)blockIdx.x * 256 + tid; i < f.zero_words; i += nb * 256) f.zero_ptr[i] = 0u;
-        for (size_t i = (size_t)blockIdx.x * 256 + tid; i < f.zero2_words; i += nb * 256) f.zero2_ptr[i] = 0u;
+        const size_t nb = (size_t)upi * f.batch;
+        for (size_t i = (size_t)id * 256 + tid; i < f.zero_words; i += nb * 256) f.zero_ptr[i] = 0u;
+        for (size_t i = (size_t)id * 256 + tid; i < f.zero2_words; i += nb * 256) f.zero2_ptr[i] = 0u;
     }
     float tol = 0.f;
     if (!T::IS_INT) {
         const float ma = __uint_as_float(f.a_max[bz]), mb = __uint_as_float(f.b_max[bz]);
         tol = f.tau_override > 0.f ? f.tau_override : (1e-3f * (float)K) * ma * mb;
-        if (u == upi - 1 && tid == 0) {
+        if (u == (int)upi - 1 && tid == 0) {
             f.maxabs[(long)bz * 2] = ma;
             f.maxabs[(long)bz * 2 + 1] = mb;
             f.tau[bz] = tol;
@@ -409,12 +411,12 @@ __global__ __launch_bounds__(256) void check_kernel(ChkArgs f)
     acc_t sb = T::zero();                                       // sum of the bias
     if (f.bias) {
         if (!f.rc_ready) sb = from_word<acc_t>(*f.bias_sum);
-        else if (u == upi - 1 || u < f.row_units) {
+        else if (u == (int)upi - 1 || u < f.row_units) {
             sb = block_bias_sum<acc_t>(f.bias, N, wred);
             __syncthreads();
         }
     }
-    if (u == upi - 1) {
+    if (u == (int)upi - 1) {
         // scalar a . b (the single-number check value of Sec. III-B.1)
         acc_t v = T::zero();
         for (int k = tid; k < K; k += 256) v = add_t(v, mul_t(from_word<acc_t>(asum[k]), from_word<acc_t>(bsum[k])));
@@ -567,7 +569,8 @@ hipError_t launch_check(int dt, bool after_fast, const void *A, const void *B, c
     f.col_units = s.transB ? (s.N + rpb - 1) / rpb : (s.N + CHK_KN_LANES * ce - 1) / (CHK_KN_LANES * ce);
     const long units = ((long)f.row_units + f.col_units + 1) * s.batch;
     if (units > 0x7FFFFFFFL) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)units, 1, 1);
+    const unsigned gx = (unsigned)(units < MAX_GRID_X ? units : MAX_GRID_X);
+    const dim3 grid(gx, (unsigned)((units + gx - 1) / gx), 1);
     switch (dt) {
     case DT_I8:   hipLaunchKernelGGL((check_kernel<DT_I8, RW>), grid, dim3(256), 0, st, f); break;
     case DT_BF16: hipLaunchKernelGGL((check_kernel<DT_BF16, RW>), grid, dim3(256), 0, st, f); break;

@@ -495,7 +495,7 @@ def test_context_reuse_across_shapes_and_modes(ctx):
     for k, (dtype, M, N, K, tb) in enumerate(cases):
         A, B = gen.gen_operands(dtype, M, N, K, 71 + k, 81 + k, trans_b=tb)
         runs.append((Run(ctx, dtype, A, B, tb), oracle_items(dtype, A, B, tb)[0], dtype))
-    order = [0, 1, 0, 0, 2, 3, 1, 3, 3, 2, 0]
+    order = [0, 1, 0, 0, 2, 3, 1, 3, 3, 2, 0, 4, 0, 4, 4, 1, 4, 3, 0]
     last = None
     for step_no, idx in enumerate(order):
         run, P, dtype = runs[idx]
@@ -1804,3 +1804,34 @@ def test_item_kernels_flip_an_accumulator_unprotected(ctx_items, dtype, M, N, K,
             assert run.C()[bi, i, j] == C0[bi, i, j] ^ (1 << 30)
         run.gemm(ab.ABFT_OFF)
         assert np.array_equal(run.C(), C0)
+
+
+def test_more_rows_than_one_grid_direction_holds():
+    """A protected int8 product of a few columns and more rows than 2^32 threads of a launch's x direction
+    cover at the check kernel's sixteen rows a workgroup: sampled rows of C and of the row checks, exact
+    column checks, clean flags, and a flip in the last row that flags it alone."""
+    M, N, K = (1 << 28) + 1234, 3, 16
+    ctx = ab.abft_create(max_rows=M, max_cols=16, max_depth=128, max_batch=1)
+    try:
+        g = torch.Generator(device="cuda").manual_seed(9)
+        A = torch.randint(-128, 128, (M, K), generator=g, device="cuda", dtype=torch.int8)
+        B = torch.randint(-128, 128, (N, K), generator=g, device="cuda", dtype=torch.int8)
+        C = torch.zeros((M, 4), dtype=torch.int32, device="cuda")
+        rf, cf = torch.full((M,), 7, dtype=torch.uint8, device="cuda"), torch.full((N,), 7, dtype=torch.uint8, device="cuda")
+        counts = torch.full((8,), 99, dtype=torch.int32, device="cuda")
+        s, r = ab.make_shape(M, N, K, ldc=4, transB=True), ab.make_result(rf, cf, counts)
+        assert ab.abft_gemm(ctx, A, B, C, ab.ABFT_I8, ab.ABFT_DETECT, s, r) == ab.ABFT_OK
+        torch.cuda.synchronize()
+        assert not rf.any() and not cf.any() and counts[:3].tolist() == [0, 0, ab.ABFT_CLEAN]
+        rows = torch.cat([torch.arange(0, M, 1000003), torch.arange(M - 40, M)]).cuda()
+        want = A[rows].double() @ B.double().T
+        assert torch.equal(C[rows, :N].double(), want)
+        assert ab.abft_inject(ctx, A, ab.ABFT_I8, s, 0, M - 1, 5, 6, ab.ABFT_INJECT_OPERAND_A) == ab.ABFT_OK
+        assert ab.abft_inject(ctx, None, ab.ABFT_I8, s, 0, M - 1, 2, 3, ab.ABFT_INJECT_ACCUMULATOR) == ab.ABFT_OK
+        assert ab.abft_gemm(ctx, A, B, C, ab.ABFT_I8, ab.ABFT_DETECT, s, r) == ab.ABFT_OK
+        torch.cuda.synchronize()
+        assert int(rf.sum()) == 1 and bool(rf[M - 1]) and cf.tolist() == [0, 0, 1]
+        assert counts[:3].tolist() == [1, 1, ab.ABFT_LOCALISED]
+    finally:
+        ab.abft_destroy(ctx)
+        torch.cuda.empty_cache()
