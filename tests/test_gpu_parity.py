@@ -1835,3 +1835,28 @@ def test_more_rows_than_one_grid_direction_holds():
     finally:
         ab.abft_destroy(ctx)
         torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("M,N,K", [(300, 260, 100), (2050, 2060, 384)])
+def test_counts_when_everything_is_flagged(ctx, M, N, K):
+    """Every wave of the check reports: the counts are all rows and all columns, the status localised; with the
+    rows' tolerance out of reach (a finite shift of every column's prediction) suspect, columns alone."""
+    A, B = gen.gen_operands("bf16", M, N, K, 51, 52, trans_b=True)
+    run = Run(ctx, "bf16", A, B, True)
+    run.gemm(ab.ABFT_DETECT)
+    for rep in range(3):
+        run.dA[0, :, 0] = 0x7FC0
+        run.gemm(ab.ABFT_DETECT)
+        assert run.cnt()[:5].tolist() == [M, N, ab.ABFT_LOCALISED, 0, ab.ABFT_LOCALISED]
+        run.dA[:, :, :K] = torch.from_numpy(A.view(np.int16)).to("cuda")
+        # a = e^T A as it is, but for one entry that shifts every column
+        a = torch.from_numpy(orc.decode(A[0], "bf16").sum(axis=0).astype(np.float32)).to("cuda")
+        a[3] += 1e12
+        run.tau = 1e4
+        assert ab.abft_supply_a(ctx, a, None) == ab.ABFT_OK
+        run.gemm(ab.ABFT_DETECT | ab.ABFT_A_CHECKSUM_GIVEN)
+        run.tau = 0.0
+        n = int(np.count_nonzero(orc.decode(B[0], "bf16")[:, 3]))     # smallest weight: 1e12 of it is far above 1e4
+        assert run.cnt()[:5].tolist() == [0, n, ab.ABFT_CHECKSUM_SUSPECT, 0, ab.ABFT_CHECKSUM_SUSPECT]
+        run.gemm(ab.ABFT_DETECT)
+        assert run.cnt()[2] == ab.ABFT_CLEAN
