@@ -15,8 +15,9 @@ constexpr int MAX_FIX_TILES = 256;
 // Tolerance of the stored-side comparison relative to tau: both sides are fp32 sums of the same
 // rounded values, so only the order of summation separates them.
 constexpr float STO_TOL_FACTOR = 1e-2f;
-// Most workgroups of 256 threads along x: a launch of 2^32 threads in one direction is refused.
-constexpr long MAX_GRID_X = 1L << 23;
+// Most workgroups of 256 threads along x: the runtime cuts off a launch of 2^32 threads in one direction, without
+// an error.
+constexpr long MAX_GRID_X = (1L << 24) - 1;
 // Most flagged rows (columns) per batch item that localisation lists.
 constexpr int MAX_LIST = 64;
 

@@ -292,6 +292,7 @@ struct ChkArgs {
     uint8_t *row_flag, *col_flag;
     uint32_t *counts;
     int row_units, col_units;
+    unsigned grid_x;      // workgroups along x
     int ksplit;           // 1, or 4 (deep K): the four waves of a unit share its rows, a quarter of K each
     uint32_t *zero_ptr;   // region every block helps to clear: what the previous protected GEMM of this
     size_t zero_words;    // context accumulated into, so that the next one finds it clean
@@ -387,7 +388,7 @@ __global__ __launch_bounds__(256) void check_kernel(ChkArgs f)
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int M = f.M, N = f.N, K = f.K;
     const unsigned upi = (unsigned)f.row_units + f.col_units + 1;      // units per batch item
-    const unsigned id = blockIdx.y * gridDim.x + blockIdx.x;
+    const unsigned id = blockIdx.y * f.grid_x + blockIdx.x;
     if (id >= upi * f.batch) return;
     const int bz = id / upi, u = id - bz * upi;
     const uint32_t *asum = f.a_sum + (long)bz * K, *bsum = f.b_sum + (long)bz * K;
@@ -570,6 +571,7 @@ hipError_t launch_check(int dt, bool after_fast, const void *A, const void *B, c
     const long units = ((long)f.row_units + f.col_units + 1) * s.batch;
     if (units > 0x7FFFFFFFL) return hipErrorInvalidValue;
     const unsigned gx = (unsigned)(units < MAX_GRID_X ? units : MAX_GRID_X);
+    f.grid_x = gx;
     const dim3 grid(gx, (unsigned)((units + gx - 1) / gx), 1);
     switch (dt) {
     case DT_I8:   hipLaunchKernelGGL((check_kernel<DT_I8, RW>), grid, dim3(256), 0, st, f); break;

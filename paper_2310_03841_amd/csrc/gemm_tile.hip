@@ -79,11 +79,9 @@ __global__ __launch_bounds__(256) void gemm_tile_kernel(TileArgs a)
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
     const GemmArgs &g = a.g;
     const int bz = blockIdx.y;
-    const int bid = blockIdx.z * gridDim.x + blockIdx.x;
-    if (bid >= a.n_extra + a.n_tiles) return;
     if (PROT) {
-        if (bid == 0 && bz == 0 && threadIdx.x < 5) a.counts[threadIdx.x] = 0u;
-        const int e = bid;
+        if (blockIdx.x == 0 && bz == 0 && threadIdx.x < 5) a.counts[threadIdx.x] = 0u;
+        const int e = blockIdx.x;
         if (e < a.n_extra) {
             if (e == a.n_enc_a + a.n_enc_b) {
                 const acc_t t = block_bias_sum<acc_t>(g.bias, g.N, reinterpret_cast<acc_t *>(smem));
@@ -98,7 +96,7 @@ __global__ __launch_bounds__(256) void gemm_tile_kernel(TileArgs a)
     const int wm = wave >> 1, wn = wave & 1;
     const int l32 = lane & 31, lh = lane >> 5;
     int tm, tn;
-    map_tile(PROT ? bid - a.n_extra : bid, a.n_tiles, g.tiles_m, g.tiles_n, &tm, &tn);
+    map_tile(PROT ? blockIdx.x - a.n_extra : blockIdx.x, a.n_tiles, g.tiles_m, g.tiles_n, &tm, &tn);
     const int m0 = tm * BM, n0 = tn * BN;
     const int M = g.M, N = g.N, K = g.K;
     const int nslab = (K + KE - 1) / KE;
@@ -472,8 +470,7 @@ static hipError_t launch_one(const TileArgs &a, int batch, hipStream_t st)
     // a problem of fewer slabs than buffers leaves the rest of the LDS to further workgroups
     const int nslab = slabs_of(DT, a.g.K);
     const int smem = tile_lds_bytes(BM, BN, nslab < NS ? nslab : NS);
-    const long blocks = (long)a.n_extra + a.n_tiles, gx = blocks < MAX_GRID_X ? blocks : MAX_GRID_X;
-    dim3 grid((unsigned)gx, (unsigned)batch, (unsigned)((blocks + gx - 1) / gx));
+    dim3 grid((unsigned)(a.n_extra + a.n_tiles), (unsigned)batch, 1);
     hipLaunchKernelGGL(kern, grid, dim3(256), smem, st, a);
     return hipGetLastError();
 }
@@ -491,6 +488,8 @@ static hipError_t launch_one(const TileArgs &a, int batch, hipStream_t st)
 static void tile_size(int M, int N, int nslab, int batch, int *bm, int *bn)
 {
     auto tiles = [&](int tm, int tn) { return (long)((M + tm - 1) / tm) * ((N + tn - 1) / tn) * batch; };
+    *bm = *bn = 128;
+    if (tiles(64, 64) / batch > MAX_GRID_X / 2) return;          // more than a launch holds
     *bm = *bn = 64;
     if (nslab <= 2 || N <= 64) return;
     if (tiles(64, 64) > 256) *bn = 128;
@@ -503,7 +502,7 @@ static hipError_t launch_cfg(bool protect, bool transB, TileArgs &a, int batch, 
     a.g.tiles_m = (a.g.M + BM - 1) / BM;
     a.g.tiles_n = (a.g.N + BN - 1) / BN;
     const long tiles = (long)a.g.tiles_m * a.g.tiles_n;
-    if (tiles + a.n_extra > 0x7FFFFFFFL - MAX_GRID_X) return hipErrorInvalidValue;
+    if (tiles + a.n_extra > MAX_GRID_X) return hipErrorInvalidValue;
     a.n_tiles = (int)tiles;
     if (protect) return transB ? launch_one<DT, BM, BN, NS, true, true>(a, batch, st)
                                : launch_one<DT, BM, BN, NS, true, false>(a, batch, st);
