@@ -39,12 +39,22 @@ static size_t item_plan(int dt, const Shape &s, bool protect, bool sto, ItemArgs
     return s.N <= 128 ? item_rows_lds(dt, s, protect, sto, g) : item_cols_lds(dt, s, protect, sto, g);
 }
 
-bool gemm_item_eligible(int dt, const Shape &s, bool stored_sums)
+// Where B leaves room for one block of rows of A at a time only, an item has a barrier per block and the
+// compute unit to itself: it takes more items before that is the faster way.  Measured, item kernel / tiles,
+// int8 Q K^T of 478 keys, K = 256: 64 queries, 104 items 20.1 / 31.1 us; 256 queries, 64 items 41.3 / 33.6, 104 items
+// 42.0 / 49.1, 256 items 46.4 / 106; 1024 queries, 104 items 125 / 113, 120 items 132 / 132; unprotected 128
+// queries, 150 items 18.4 / 16.3; 33 queries, 150 items 9.9 / 7.8; 256 queries, 256 items 32.1 / 44.8.
+constexpr int ONE_BLOCK_MIN_BATCH = 104, ONE_BLOCK_MIN_BATCH_TALL = 120, ONE_BLOCK_MIN_BATCH_PLAIN = 256;
+
+// protect: of two problems of one shape the unprotected one may be tiled
+bool gemm_item_eligible(int dt, const Shape &s, bool stored_sums, bool protect)
 {
     if (s.batch < ITEM_MIN_BATCH) return false;
     ItemArgs g;
-    // the tile shape of a problem does not depend on whether it is protected
-    return item_plan(dt, s, true, stored_sums && dt != DT_I8, &g) > 0;
+    if (item_plan(dt, s, true, stored_sums && dt != DT_I8, &g) == 0) return false;
+    if (s.N <= 128 || g.rch > 1 || g.MB == 1) return true;
+    return protect ? s.batch >= (g.MB <= 8 ? ONE_BLOCK_MIN_BATCH : ONE_BLOCK_MIN_BATCH_TALL)
+                   : s.batch >= ONE_BLOCK_MIN_BATCH_PLAIN && g.MB >= 4;
 }
 
 hipError_t launch_gemm_item(int dt, bool protect, bool cached_b, bool stored_sums, const void *A, const void *B, void *C,

@@ -315,7 +315,8 @@ size_t item_cols_lds(int dt, const Shape &s, bool protect, bool sto, ItemArgs *g
             const ColsLds L(*g, es, sto);
             const size_t bytes = (size_t)g->lds_vec + (protect ? (size_t)L.total * 4 : 0);
             if (bytes <= budget) return bytes;
-            if (g->rch <= 2) break;              // smaller chunks cost more in barriers than a second workgroup gives
+            // smaller chunks cost more in barriers than a second workgroup gives (one block: see gemm_item_eligible)
+            if (g->rch <= (budget < (size_t)ITEM_LDS_LIMIT ? 2 : 1)) break;
         }
     return 0;
 }

@@ -574,7 +574,7 @@ hipError_t launch_gemm(int dt, bool protect, bool stored_sums, bool encode_b, co
 {
     // The unprotected item kernels do not look for an armed flip (in them the look cost bf16 400 x 400 x 80,
     // 256 items 24.4 -> 25.0 us): such a call is tiled, C comes out bit for bit the same.
-    if (!protect && !w.bias && arm.batch < 0 && gemm_item_eligible(dt, s, false))
+    if (!protect && !w.bias && arm.batch < 0 && gemm_item_eligible(dt, s, false, false))
         return launch_gemm_item(dt, false, false, false, A, B, C, s, w, nullptr, arm, st);
     TileArgs a;
     GemmArgs &g = a.g;

@@ -1860,3 +1860,19 @@ def test_counts_when_everything_is_flagged(ctx, M, N, K):
         assert run.cnt()[:5].tolist() == [0, n, ab.ABFT_CHECKSUM_SUSPECT, 0, ab.ABFT_CHECKSUM_SUSPECT]
         run.gemm(ab.ABFT_DETECT)
         assert run.cnt()[2] == ab.ABFT_CLEAN
+
+
+@pytest.mark.parametrize("dtype,M,N,K,batch,trans_b", [("i8", 197, 478, 208, 104, True), ("i8", 65, 451, 256, 104, True),
+                                                       ("bf16", 197, 500, 128, 104, False), ("bf16", 130, 500, 104, 256, True),
+                                                       ("f16", 290, 500, 128, 120, False)])
+def test_item_kernel_one_block_of_rows_at_a_time(dtype, M, N, K, batch, trans_b):
+    """Items whose B leaves room for a single block of rows of A: from as many items on as are worth it, and
+    the tiles one item below."""
+    shape = lambda b: ab.make_shape(M, N, K, batch=b, transB=trans_b)
+    assert ab.abft_tile_shape(ab.DTYPE_CODE[dtype], shape(batch)) == (M, N)
+    assert ab.abft_tile_shape(ab.DTYPE_CODE[dtype], shape((120 if M > 256 else 104) - 1)) != (M, N)
+    ctx = ab.abft_create(max_rows=batch * M, max_cols=batch * N, max_depth=batch * (K + 127), max_batch=batch)
+    try:
+        _clean_case(ctx, dtype, M, N, K, batch, trans_b)
+    finally:
+        ab.abft_destroy(ctx)
