@@ -426,8 +426,8 @@ static int enqueue_tiled(abft_ctx *ctx, int dtype, bool cached, bool stored, con
     size_t stale = ctx->dirty[ctx->cur];
     if (gm && stale < w->zero_words) stale = w->zero_words;
     ctx->dirty[ctx->cur] = ctx->region_words;            // until everything below is enqueued
-    const bool fast = gemm_takes_fast(dtype, sh);
-    if (!cached && fast) HIP_TRY(launch_encode_b(dtype, B, sh, *w, w->cc_obs, stale, st));
+    const bool fast = gemm_takes_fast(dtype, sh), rc_ready = fast || gemm_fuses_a(dtype, sh);
+    if (!cached && rc_ready) HIP_TRY(launch_encode_b(dtype, B, sh, *w, w->cc_obs, stale, st));
     else if (stale) HIP_TRY(launch_zero(w->cc_obs, stale, st));
     if (ev) HIP_TRY(hipEventRecord(ev[1], st));
     ctx->sto_valid = false;
@@ -435,7 +435,7 @@ static int enqueue_tiled(abft_ctx *ctx, int dtype, bool cached, bool stored, con
     if (ctx->done_event && !gm) HIP_TRY(hipEventRecord(ctx->done_event, st));
     if (ev) HIP_TRY(hipEventRecord(ev[2], st));
     auto check = [&](uint32_t *z, size_t zw, uint32_t *z2, size_t z2w) {
-        return launch_check(dtype, fast, A, B, sh, *w, v, z, zw, z2, z2w, st);
+        return launch_check(dtype, fast, rc_ready, A, B, sh, *w, v, z, zw, z2, z2w, st);
     };
     if (gm) {
         HIP_TRY(check(nullptr, 0, nullptr, 0));

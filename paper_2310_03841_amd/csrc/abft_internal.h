@@ -98,6 +98,8 @@ int protect_max_k(int dt);
 // Whether the problem takes the fast kernel (a pass over B ahead of it) or the general one (the passes
 // over A and B ride in its launch).
 bool gemm_takes_fast(int dt, const Shape &s);
+// Whether the general kernel, protected, reduces A from the slabs it holds (a pass over B ahead of it, A b with it).
+bool gemm_fuses_a(int dt, const Shape &s);
 // protect: A-side checksums and observed sums are produced by the kernel (atomics into the
 // zeroed region of the workspace); launch_check turns them into flags.
 // stored_sums: also accumulate the row / column sums of the rounded values that are stored
@@ -106,7 +108,7 @@ hipError_t launch_gemm(int dt, bool protect, bool stored_sums, bool encode_b, co
                        const Shape &s, const Workspace &w, const InjectArm &arm, uint32_t *counts, hipStream_t st);
 // behind the GEMM kernel (after_fast: the fast one): the predictions that are missing, comparisons, flags
 // and counts.  zero_ptr / zero_words: regions every block of the kernel helps to clear (may be null / 0)
-hipError_t launch_check(int dt, bool after_fast, const void *A, const void *B, const Shape &s, const Workspace &w, const Verdict &v,
+hipError_t launch_check(int dt, bool after_fast, bool rc_ready, const void *A, const void *B, const Shape &s, const Workspace &w, const Verdict &v,
                         uint32_t *zero_ptr, size_t zero_words, uint32_t *zero2_ptr, size_t zero2_words, hipStream_t st);
 // with_sto: a row / column also flags when the re-summed stored C differs from the stored-side
 // sums of the GEMM by more than STO_TOL_FACTOR * tau

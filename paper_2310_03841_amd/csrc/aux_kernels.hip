@@ -436,7 +436,10 @@ __global__ __launch_bounds__(256) void check_kernel(ChkArgs f)
             const long o = (long)bz * M + r;
             uint32_t pred = f.rc_pred[o];
             if (f.bias) { pred = as_word(add_t(from_word<acc_t>(pred), sb)); f.rc_pred[o] = pred; }
-            fl = mismatch<T::IS_INT>(f.rc_obs[o], pred, tol);
+            uint32_t obs;
+            if (acc_obs) f.rc_obs[o] = obs = __float_as_uint((float)f.rc_acc[o]);
+            else obs = f.rc_obs[o];
+            fl = mismatch<T::IS_INT>(obs, pred, tol);
             f.row_flag[o] = fl ? 1 : 0;
         }
         const unsigned nf = __popcll(__ballot(fl));
@@ -543,7 +546,7 @@ __global__ __launch_bounds__(256) void check_kernel(ChkArgs f)
     }
 }
 
-hipError_t launch_check(int dt, bool after_fast, const void *A, const void *B, const Shape &s, const Workspace &w, const Verdict &v,
+hipError_t launch_check(int dt, bool after_fast, bool rc_ready, const void *A, const void *B, const Shape &s, const Workspace &w, const Verdict &v,
                         uint32_t *zero_ptr, size_t zero_words, uint32_t *zero2_ptr, size_t zero2_words, hipStream_t st)
 {
     constexpr int RW = 4;                                       // rows per wave
@@ -555,7 +558,7 @@ hipError_t launch_check(int dt, bool after_fast, const void *A, const void *B, c
     f.a_max = (w.a_given && w.amax_given) ? w.amax_given : w.a_max;
     f.b_sum = w.b_sum; f.b_max = w.b_max; f.cc_obs = w.cc_obs; f.rc_obs = w.rc_obs;
     f.cc_acc = after_fast ? nullptr : w.cc_acc; f.rc_acc = after_fast ? nullptr : w.rc_acc;
-    f.rc_ready = after_fast ? 1 : 0;
+    f.rc_ready = rc_ready ? 1 : 0;
     f.bias = w.bias; f.bias_sum = w.bias_sum;
     f.cc_pred = w.cc_pred; f.rc_pred = w.rc_pred; f.s_pred = w.s_pred; f.maxabs = w.maxabs; f.tau = w.tau;
     f.tau_override = v.tau_override; f.tau_override_cols = v.tau_override_cols;
@@ -566,7 +569,7 @@ hipError_t launch_check(int dt, bool after_fast, const void *A, const void *B, c
     const int nch = (s.K + ce - 1) / ce;
     f.ksplit = nch > 128 ? 4 : 1;                               // more than one trip of 128 chunks per row
     const int rpb = f.ksplit == 4 ? RW : 4 * RW;
-    f.row_units = after_fast ? (s.M + 255) / 256 : (s.M + rpb - 1) / rpb;
+    f.row_units = rc_ready ? (s.M + 255) / 256 : (s.M + rpb - 1) / rpb;
     f.col_units = s.transB ? (s.N + rpb - 1) / rpb : (s.N + CHK_KN_LANES * ce - 1) / (CHK_KN_LANES * ce);
     const long units = ((long)f.row_units + f.col_units + 1) * s.batch;
     if (units > 0x7FFFFFFFL) return hipErrorInvalidValue;

@@ -74,7 +74,7 @@ __host__ __device__ inline size_t apass_lds_bytes_per_wave(int dt, int nslab, in
 // atomic adds per wave and slab held the wave's next LDS reads back by some 800 clocks.
 template <int DT, int BM, bool GIVEN = false, bool SW16 = false, bool SPLIT_ONLY = false, bool PER_WAVE = false>
 __device__ __forceinline__ void a_pass(const uint8_t *sA, const uint32_t *b_lds, int rows_valid,
-                                       uint32_t *col_lds, APassState<DT> &st, bool mul24_ok)
+                                       uint32_t *col_lds, APassState<DT> &st, bool mul24_ok, int keep = SLAB_BYTES)
 {
     using T = Traits<DT>;
     typedef typename T::acc_t acc_t;
@@ -96,6 +96,10 @@ __device__ __forceinline__ void a_pass(const uint8_t *sA, const uint32_t *b_lds,
     i32x4 v[P];
 #pragma unroll
     for (int p = 0; p < P; ++p) v[p] = *reinterpret_cast<const i32x4 *>(src + p * 32 * SLAB_BYTES);
+    if (keep < SLAB_BYTES) {
+#pragma unroll
+        for (int p = 0; p < P; ++p) v[p] = mask_chunk(v[p], keep - c * 16);
+    }
     acc_t mine = T::zero();
     bool done = false;
     if constexpr (T::IS_INT) {

@@ -27,6 +27,7 @@
 // stored or summed.  Past the end of K the fragments of the last slab are cleared in registers.
 #include "abft_device.h"
 #include "encode_pass.h"
+#include "gemm_apass.h"
 #include "gemm_args.h"
 #include "gemm_epilogue.h"
 
@@ -43,6 +44,8 @@ struct TileArgs {
     EncArgs ea, eb;
     uint32_t *counts;             // protected: cleared here, completed by the check kernel
     uint32_t *bias_sum;           // protected, with a bias: its sum, formed by one more workgroup
+    int fuse_bm;                  // host: rows of a tile of the instantiations with APASS, 0: the others
+    int aux_off;                  // APASS: where the words of b and of a begin in LDS
 };
 
 constexpr int TILE_STAGE_ROW = 36;                               // words per staged row of a 32 x 32 block (32 + pad)
@@ -62,7 +65,7 @@ template <int ES, int ROWB> __device__ __forceinline__ int kn_swizzle(int k)
     else return ROWB == 64 ? ((k >> 2) & 1) << 1 : ((k >> 1) & 3) << 1;                  // 16-byte pieces of 8 rows
 }
 
-template <int DT, int BM, int BN, int NS, bool PROT, bool TRANSB>
+template <int DT, int BM, int BN, int NS, bool PROT, bool TRANSB, bool APASS>
 __global__ __launch_bounds__(256) void gemm_tile_kernel(TileArgs a)
 {
     using T = Traits<DT>;
@@ -250,6 +253,24 @@ __global__ __launch_bounds__(256) void gemm_tile_kernel(TileArgs a)
     // ---- main loop.  Slab s is in place behind "at most the slabs issued after it outstanding"
     // (a wave's loads complete in order) and the barrier; the same barrier says that every wave has
     // its fragments of slab s - 1 in registers, so that buffer takes slab s + NS - 1.
+    // APASS: of the tiles that share rows of A, the one in column s mod tiles_n reduces slab s while it is resident
+    // (gemm_apass.h).  Its words of b go straight into LDS ahead of the slabs.
+    const int owned = (APASS && tn < nslab) ? (nslab - tn + g.tiles_n - 1) / g.tiles_n : 0;
+    uint32_t *b_lds = reinterpret_cast<uint32_t *>(smem + a.aux_off), *col_lds = b_lds + owned * KE;
+    APassState<DT> ast;
+    ast.rdot = T::zero(); ast.amax = 0.f;
+    int next_own = tn, own_at = 0;
+    if constexpr (APASS) {
+        for (int j = wave; j < owned; j += 4)
+#pragma unroll
+            for (int h = 0; h < KE / 64; ++h) {
+                int k = (tn + j * g.tiles_n) * KE + 64 * h + lane;
+                k = k < K ? k : K - 1;                           // past the end of K: times zero
+                __builtin_amdgcn_global_load_lds((tile_gas_ptr)(g.b_sum + (long)bz * K + k),
+                                                 (tile_las_ptr)(b_lds + j * KE + 64 * h), 4, 0, 0);
+            }
+        for (int i = tid; i < owned * KE; i += 256) col_lds[i] = 0u;
+    }
     for (int s = 0; s < NS - 1; ++s)
         if (s < nslab) issue(s);
     auto arrive = [&](int s) __attribute__((always_inline)) {
@@ -260,22 +281,38 @@ __global__ __launch_bounds__(256) void gemm_tile_kernel(TileArgs a)
         else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
         if (s + NS - 1 < nslab) issue(s + NS - 1);
     };
+    auto reduce = [&](int s) __attribute__((always_inline)) {
+        if constexpr (APASS) {
+            if (s != next_own) return;
+            const uint8_t *sA = smem + (s % NS) * BUF;
+            if (g.a_given)
+                a_pass<DT, BM, true, true, true, false>(sA, b_lds + own_at, M - m0, col_lds + own_at, ast, true, K * ES - s * SLAB_BYTES);
+            else
+                a_pass<DT, BM, false, true, true, false>(sA, b_lds + own_at, M - m0, col_lds + own_at, ast, true, K * ES - s * SLAB_BYTES);
+            next_own += g.tiles_n;
+            own_at += KE;
+        }
+    };
     const bool ragged = (K * ES) % SLAB_BYTES != 0;
     arrive(0);
     read_frags(0, set0{});
+    reduce(0);
     int s = 1;
     for (; s + 1 < nslab; s += 2) {
         arrive(s);
         read_frags(s, set1{});
         mfmas(set0{});
+        reduce(s);
         arrive(s + 1);
         read_frags(s + 1, set0{});
         mfmas(set1{});
+        reduce(s + 1);
     }
     if (s < nslab) {
         arrive(s);
         read_frags(s, set1{});
         mfmas(set0{});
+        reduce(s);
         if (ragged) clear_tail(set1{});
         mfmas(set1{});
     } else {
@@ -287,6 +324,20 @@ __global__ __launch_bounds__(256) void gemm_tile_kernel(TileArgs a)
     // block and in register i column 8 (i >> 2) + 4 (l >> 5) + (i & 3); read back, lane l has four
     // consecutive columns 4 (l & 7) .. of rows 8 p + (l >> 3).
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");       // every wave is done with the operand buffers
+    if constexpr (APASS) {
+        if (!g.a_given) {
+            for (int i = tid; i < owned * KE; i += 256) {
+                const int k = (tn + i / KE * g.tiles_n) * KE + i % KE;
+                if (k < K) atomic_add_word(g.a_sum + (long)bz * K + k, from_word<acc_t>(col_lds[i]));
+            }
+            if constexpr (!T::IS_INT) {
+                const float m = wave_max(ast.amax);
+                if (lane == 0 && m > 0.f) atomicMax(g.a_max + bz, __float_as_uint(m));
+            }
+        }
+        const int r = m0 + (tid >> 3) + 32 * (tid & 7);
+        if (owned && (tid & 7) < BM / 32 && r < M) atomic_add_word(g.rc_pred + (long)bz * M + r, ast.rdot);
+    }
     uint8_t *stage = smem + wave * TILE_STAGE_WAVE;
     acc_t *rs_part = reinterpret_cast<acc_t *>(smem + 4 * TILE_STAGE_WAVE);          // [2][BM] by wave column
     acc_t *cs_part = rs_part + 2 * BM;                                               // [2][BN] by wave row
@@ -457,28 +508,64 @@ __global__ __launch_bounds__(256) void gemm_tile_kernel(TileArgs a)
 // ------------------------------------------------------------------------------------------
 static int slabs_of(int dt, int K) { return (int)(((long)K * elem_size(dt) + SLAB_BYTES - 1) / SLAB_BYTES); }
 
-template <int DT, int BM, int BN, int NS, bool PROT, bool TRANSB>
-static hipError_t launch_one(const TileArgs &a, int batch, hipStream_t st)
+template <int DT, int BM, int BN, int NS, bool PROT, bool TRANSB, bool APASS = false>
+static hipError_t launch_one(TileArgs &a, int batch, hipStream_t st)
 {
-    constexpr int smem_max = tile_lds_bytes(BM, BN, NS);
+    constexpr int smem_max = APASS ? 160 * 1024 : tile_lds_bytes(BM, BN, NS);
     static_assert(tile_lds_bytes(BM, BN, 1) >= 256 * 16 * 4, "the passes over A and B use 16 KB");
-    auto kern = gemm_tile_kernel<DT, BM, BN, NS, PROT, TRANSB>;
+    auto kern = gemm_tile_kernel<DT, BM, BN, NS, PROT, TRANSB, APASS>;
     if (smem_max > 48 * 1024) {
         hipError_t e = ensure_max_lds(reinterpret_cast<const void *>(kern), smem_max);
         if (e != hipSuccess) return e;
     }
     // a problem of fewer slabs than buffers leaves the rest of the LDS to further workgroups
     const int nslab = slabs_of(DT, a.g.K);
-    const int smem = tile_lds_bytes(BM, BN, nslab < NS ? nslab : NS);
+    int smem = tile_lds_bytes(BM, BN, nslab < NS ? nslab : NS);
+    a.aux_off = smem;
+    if (APASS) smem += (int)apass_lds_bytes(DT, nslab, a.g.tiles_n);
     dim3 grid((unsigned)(a.n_extra + a.n_tiles), (unsigned)batch, 1);
     hipLaunchKernelGGL(kern, grid, dim3(256), smem, st, a);
     return hipGetLastError();
 }
 
-// 64 x 64, 64 x 128 or 128 x 128 tiles.  What a compute unit spends on a slab is its LDS traffic (per
-// wave a read of its rows of A and of B, once a write of the tile's): measured 0.19, 0.28 and 0.46 us
-// for the three shapes, so wider tiles cost less per product, but a problem of few tiles ends sooner
-// the smaller its tiles are: 197 x 768 x 3072 (48 / 24 / 12 tiles) 12.7 / 17.8 / 27.4 us; 1000 x 1000
+static long tiles_of(int M, int N, int batch, int tm, int tn)
+{
+    return (long)((M + tm - 1) / tm) * ((N + tn - 1) / tn) * batch;
+}
+
+// What a launch of such tiles takes, in us: rounds of 256 compute units, each a slab at a time (what a compute
+// unit spends on a slab is its LDS traffic; alone on it, a tile waits for its loads instead) and an end.
+// Fitted to 1967 shapes timed with all three (M to 12608, N to 4096, K to 8192 bytes, up to 700 items, three
+// types, both layouts of B).
+static double tile_cost(int M, int N, int nslab, int batch, int shape)
+{
+    static const int tm[3] = {64, 64, 128}, tn[3] = {64, 128, 128};
+    static const double slab[3] = {0.22, 0.30, 0.45}, slab_alone[3] = {0.25, 0.39, 0.40}, end[3] = {0.25, 0.8, 2.8};
+    const long n = (tiles_of(M, N, batch, tm[shape], tn[shape]) + 255) / 256;
+    return nslab * (n > 1 ? slab[shape] * n : slab_alone[shape]) + end[shape] * n;
+}
+
+// Whether the tiles reduce A from the slabs they hold, behind a pass over B and with A b (APASS), instead of
+// extra workgroups that read A and B again and a check that reads A a third time.  Those run in the LDS
+// of a tile, one to three to a compute unit, and are for problems that leave the chip room.  From about
+// 50 MB of A and B on the tiles' own reduction is the faster way, so / with the extra
+// workgroups: f16 999 x 128 x 516, 596 items 518 / 913 / 456 us; bf16
+// 10496 x 768 x 2819, B cached 103 / 140 / 103; f16 12241 x 361 x 4045 127 / 130 / 140; below, bf16 8409 x 1717 x
+// 1300 (26 MB) 108 / 107 / 115.  Batches need more (64 MB): their items' slabs are few.  B stored K x N: the tiles wait
+// for LDS more than for memory, and the reduction does not fit beside (f16 10934 x 1864 x 2268 206 / 193).
+static bool fuses_a(int dt, const Shape &s, int nslab, int *bm)
+{
+    const double bytes = (double)s.batch * ((double)s.M + s.N) * s.K * elem_size(dt);
+    if (!s.transB || nslab < 6 || bytes < (s.batch == 1 ? 48e6 : 64e6) || (dt == DT_I8 && s.N >= 65536)) return false;
+    *bm = tile_cost(s.M, s.N, nslab, s.batch, 1) < 0.8 * tile_cost(s.M, s.N, nslab, s.batch, 2) ? 64 : 128;
+    const int tiles_n = (s.N + 127) / 128;
+    const long tiles = tiles_of(s.M, s.N, s.batch, *bm, 128);
+    return tiles >= 128 && tiles >= 4 * apass_owned_slabs(nslab, tiles_n) && tiles / s.batch <= MAX_GRID_X &&
+           tile_lds_bytes(*bm, 128, 3) + apass_lds_bytes(dt, nslab, tiles_n) <= 160 * 1024;
+}
+
+// 64 x 64, 64 x 128 or 128 x 128 tiles.  Wider tiles cost less LDS traffic per product, but a problem of few
+// tiles ends sooner the smaller its tiles are: 197 x 768 x 3072 (48 / 24 / 12 tiles) 12.7 / 17.8 / 27.4 us; 1000 x 1000
 // x 1024 (256 / 128 / 64) 8.2 / 9.5 / 13.1; 2048 x 1024 x 1024 (512 / 256 / 128) 10.6 / 10.5 / 13.7;
 // 6304 x 768 x 3080 with B stored K x N (1188 / 594 / 300) 64.9 / 59.0 / 64.3; 12608 x 1000 x 200
 // (3152 / 1576 / 792) 26.3 / 25.0 / 29.5; 6304 x 3072 x 776 (4752 / 2376 / 1200) 74.3 / 69.5 / 62.9.
@@ -487,13 +574,13 @@ static hipError_t launch_one(const TileArgs &a, int batch, hipStream_t st)
 // 49.4 us, 12608 x 1000 x 128 24.0 / 26.1 / 31.4.
 static void tile_size(int M, int N, int nslab, int batch, int *bm, int *bn)
 {
-    auto tiles = [&](int tm, int tn) { return (long)((M + tm - 1) / tm) * ((N + tn - 1) / tn) * batch; };
+    auto tiles = [&](int tm, int tn) { return tiles_of(M, N, batch, tm, tn); };
     *bm = *bn = 128;
     if (tiles(64, 64) / batch > MAX_GRID_X / 2) return;          // more than a launch holds
-    *bm = *bn = 64;
-    if (nslab <= 2 || N <= 64) return;
-    if (tiles(64, 64) > 256) *bn = 128;
-    if (nslab >= 8 && tiles(128, 128) >= 1024) *bm = 128;
+    int pick = 0;
+    if (nslab > 2 && N > 64 && tiles(64, 64) > 256) pick = nslab >= 8 && tiles(128, 128) >= 1024 ? 2 : 1;
+    if (pick < 2) *bm = 64;
+    if (pick < 1) *bn = 64;
 }
 
 template <int DT, int BM, int BN, int NS>
@@ -504,6 +591,8 @@ static hipError_t launch_cfg(bool protect, bool transB, TileArgs &a, int batch, 
     const long tiles = (long)a.g.tiles_m * a.g.tiles_n;
     if (tiles + a.n_extra > MAX_GRID_X) return hipErrorInvalidValue;
     a.n_tiles = (int)tiles;
+    if constexpr (BN == 128)
+        if (a.fuse_bm) return launch_one<DT, BM, BN, NS, true, true, true>(a, batch, st);
     if (protect) return transB ? launch_one<DT, BM, BN, NS, true, true>(a, batch, st)
                                : launch_one<DT, BM, BN, NS, true, false>(a, batch, st);
     return transB ? launch_one<DT, BM, BN, NS, false, true>(a, batch, st)
@@ -516,12 +605,18 @@ static hipError_t launch_cfg(bool protect, bool transB, TileArgs &a, int batch, 
 template <int DT>
 static hipError_t launch_tile(bool protect, bool transB, TileArgs &a, int batch, hipStream_t st)
 {
-    int bm, bn;
-    tile_size(a.g.M, a.g.N, slabs_of(DT, a.g.K), batch, &bm, &bn);
+    int bm = a.fuse_bm, bn = 128;
+    if (!bm) tile_size(a.g.M, a.g.N, slabs_of(DT, a.g.K), batch, &bm, &bn);
     if (bm == 128) return launch_cfg<DT, 128, 128, 3>(protect, transB, a, batch, st);
     if (bn == 128) return launch_cfg<DT, 64, 128, 3>(protect, transB, a, batch, st);
     if ((long)((a.g.M + 63) / 64) * ((a.g.N + 63) / 64) * batch > 256) return launch_cfg<DT, 64, 64, 3>(protect, transB, a, batch, st);
     return launch_cfg<DT, 64, 64, 4>(protect, transB, a, batch, st);
+}
+
+bool gemm_fuses_a(int dt, const Shape &s)
+{
+    int bm;
+    return !gemm_takes_fast(dt, s) && fuses_a(dt, s, slabs_of(dt, s.K), &bm);
 }
 
 void gemm_tile_shape(int dt, const Shape &s, int *tm, int *tn)
@@ -535,7 +630,8 @@ void gemm_tile_shape(int dt, const Shape &s, int *tm, int *tn)
         gemm_fast_tile(tm, tn);
         return;
     }
-    tile_size(s.M, s.N, slabs_of(dt, s.K), s.batch, tm, tn);
+    *tn = 128;
+    if (!fuses_a(dt, s, slabs_of(dt, s.K), tm)) tile_size(s.M, s.N, slabs_of(dt, s.K), s.batch, tm, tn);
 }
 
 // The fast kernel's 256 x 256 tiles use the matrix cores best and fill the chip worst.  Measured
@@ -602,9 +698,11 @@ hipError_t launch_gemm(int dt, bool protect, bool stored_sums, bool encode_b, co
     a.ea = enc_args(A, s.lda, s.sA, s.M, s.K, s.K, 1, dt, w.a_sum, w.a_max);
     a.eb = s.transB ? enc_args(B, s.ldb, s.sB, s.N, s.K, s.K, 1, dt, w.b_sum, w.b_max)
                     : enc_args(B, s.ldb, s.sB, s.K, s.N, s.K, 0, dt, w.b_sum, w.b_max);
-    a.n_enc_a = (protect && !w.a_given) ? a.ea.nwin * a.ea.nrb : 0;
-    a.n_enc_b = (protect && encode_b) ? a.eb.nwin * a.eb.nrb : 0;
-    a.n_extra = a.n_enc_a + a.n_enc_b + (protect && w.bias ? 1 : 0);
+    a.fuse_bm = 0;
+    if (protect && !fuses_a(dt, s, slabs_of(dt, s.K), &a.fuse_bm)) a.fuse_bm = 0;
+    a.n_enc_a = (protect && !w.a_given && !a.fuse_bm) ? a.ea.nwin * a.ea.nrb : 0;
+    a.n_enc_b = (protect && encode_b && !a.fuse_bm) ? a.eb.nwin * a.eb.nrb : 0;
+    a.n_extra = a.n_enc_a + a.n_enc_b + (protect && w.bias && !a.fuse_bm ? 1 : 0);
     switch (dt) {
     case DT_I8:   return launch_tile<DT_I8>(protect, s.transB != 0, a, s.batch, st);
     case DT_BF16: return launch_tile<DT_BF16>(protect, s.transB != 0, a, s.batch, st);

@@ -1368,7 +1368,8 @@ def test_item_kernel_more_items_than_workgroups(dtype, M, N, K, batch, trans_b):
 
 @pytest.mark.parametrize("dtype,M,N,K,batch,trans_b", [("i8", 197, 768, 768, 1, True), ("bf16", 600, 520, 256, 2, True),
                                                        ("bf16", 100, 130, 72, 65, True), ("i8", 70, 50, 40, 64, False),
-                                                       ("bf16", 520, 1030, 384, 6, True), ("i8", 2050, 2060, 384, 1, True)])
+                                                       ("bf16", 520, 1030, 384, 6, True), ("i8", 2050, 2060, 384, 1, True),
+                                                       ("bf16", 6400, 700, 3900, 1, True)])
 def test_calls_can_be_captured_in_a_graph(dtype, M, N, K, batch, trans_b):
     """The hot calls only enqueue kernels (no allocation, no copy, no synchronisation, no memset
     node): a protected GEMM followed by a verify is captured once and replayed several times, with
@@ -1876,3 +1877,97 @@ def test_item_kernel_one_block_of_rows_at_a_time(dtype, M, N, K, batch, trans_b)
         _clean_case(ctx, dtype, M, N, K, batch, trans_b)
     finally:
         ab.abft_destroy(ctx)
+
+
+# Problems of the general kernel large enough that its tiles reduce A themselves (48 MB of A and B, batches 64 MB):
+# 128 x 128 tiles, where the extra workgroups of a smaller problem would be beside 64 x 128 ones.
+REDUCING = {"one": {"i8": (12100, 300, 4090, 1), "bf16": (6401, 700, 3900, 1), "f16": (6400, 700, 3903, 1)},
+            "batch": {d: (300, 130, 1000, 160) for d in ("i8", "bf16", "f16")}}
+
+
+@pytest.fixture(scope="module")
+def ctx_large():
+    c = ab.abft_create(max_rows=160 * 300, max_cols=400 * 250, max_depth=400 * 1024, max_batch=400)
+    yield c
+    ab.abft_destroy(c)
+
+
+@pytest.mark.parametrize("dtype", ["i8", "bf16", "f16"])
+@pytest.mark.parametrize("which", ["one", "batch"])
+def test_tiles_that_reduce_a_clean(ctx_large, dtype, which):
+    M, N, K, batch = REDUCING[which][dtype]
+    assert ab.abft_tile_shape(ab.DTYPE_CODE[dtype], ab.make_shape(M, N, K, batch=batch, transB=True)) == (128, 128)
+    _clean_case(ctx_large, dtype, M, N, K, batch, True)
+
+
+@pytest.mark.parametrize("dtype", ["i8", "f16"])
+def test_tiles_of_64_rows_that_reduce_a_clean(ctx_large, dtype):
+    M, N, K, batch = 60, 250, 1000, 400
+    assert ab.abft_tile_shape(ab.DTYPE_CODE[dtype], ab.make_shape(M, N, K, batch=batch, transB=True)) == (64, 128)
+    _clean_case(ctx_large, dtype, M, N, K, batch, True)
+
+
+@pytest.mark.parametrize("dtype", ["i8", "bf16", "f16"])
+def test_tiles_that_reduce_a_with_every_option(ctx_large, dtype):
+    """Layer bias, cached B, a supplied checksum of A, stored-side sums beside an Inf and a NaN, armed flips."""
+    ctx, (M, N, K, batch) = ctx_large, REDUCING["batch"][dtype]
+    A, B = gen.gen_operands(dtype, M, N, K, 81, 82, trans_b=True, batch=batch)
+    run = Run(ctx, dtype, A, B, True)
+    rng = np.random.default_rng(5)
+    bias = rng.integers(-1000, 1000, N).astype(np.int32) if dtype == "i8" else (0.1 * rng.standard_normal(N)).astype(np.float32)
+    d_bias = torch.from_numpy(bias).to("cuda")
+    run.gemm_bias(d_bias, ab.ABFT_DETECT)
+    check_clean(run, [orc.protected_gemm(A[b], B[b], dtype, True, bias=bias) for b in range(batch)])
+    P = oracle_items(dtype, A, B, True)
+    run.gemm(ab.ABFT_DETECT)
+    check_clean(run, P)
+    C0 = run.C().copy()
+    run.gemm(ab.ABFT_DETECT | ab.ABFT_B_CHECKSUM_CACHED)
+    check_clean(run, P)
+    # a from the caller
+    a = np.stack([p.a for p in P])
+    d_a = torch.from_numpy(ring(a).view(np.int32) if dtype == "i8" else a.astype(np.float32)).to("cuda")
+    d_m = torch.tensor([p.max_a for p in P], dtype=torch.float32, device="cuda") if dtype != "i8" else None
+    assert ab.abft_supply_a(ctx, d_a, d_m) == ab.ABFT_OK
+    run.gemm(ab.ABFT_DETECT | ab.ABFT_A_CHECKSUM_GIVEN)
+    assert run.cnt()[2] == ab.ABFT_CLEAN and np.array_equal(run.C(), C0)
+    rcp, ccp = run.ws(ab.ABFT_WS_RC_PRED), run.ws(ab.ABFT_WS_CC_PRED)
+    for bi, p in enumerate(P):
+        if dtype == "i8":
+            assert np.array_equal(rcp[bi].view(np.uint32), ring(p.rc_pred)) and np.array_equal(ccp[bi].view(np.uint32), ring(p.cc_pred))
+        else:
+            assert np.max(np.abs(rcp[bi] - p.rc_pred)) <= 1e-2 * p.tau * np.sqrt(N)
+            assert np.max(np.abs(ccp[bi] - p.cc_pred)) <= 1e-2 * p.tau * np.sqrt(M)
+    # flips in the accumulators: found, repaired
+    for (bi, i, j) in [(0, 0, 0), (batch - 1, M - 1, N - 1), (7, 128, 64)]:
+        run.inject(bi, i, j, 30, ab.ABFT_INJECT_ACCUMULATOR)
+        run.gemm(ab.ABFT_DETECT)
+        rf, cf = run.flags()
+        assert rf.sum() == 1 and cf.sum() == 1 and rf[bi, i] and cf[bi, j]
+        run.correct()
+        assert np.array_equal(run.C(), C0) and run.cnt()[2] == ab.ABFT_CLEAN
+    run.inject(9, 5, 7, 30, ab.ABFT_INJECT_ACCUMULATOR)
+    run.gemm(ab.ABFT_DETECT_CORRECT)
+    assert np.array_equal(run.C(), C0) and run.cnt()[2:5].tolist() == [ab.ABFT_CLEAN, 1, ab.ABFT_LOCALISED]
+    if dtype == "i8":
+        return
+    # an Inf and a NaN: their rows, their items' columns, nothing else; the other sums stay what they are
+    inf, nan = (0x7F80, 0x7FC0) if dtype == "bf16" else (0x7C00, 0x7E00)
+    run.gemm(ab.ABFT_DETECT | ab.ABFT_STORED_SUMS)
+    a0, r0, s0 = run.ws(ab.ABFT_WS_A_SUM).copy(), run.ws(ab.ABFT_WS_RC_PRED).copy(), run.ws(ab.ABFT_WS_RC_STO).copy()
+    run.dA[3, 130, 999], run.dA[5, 299, 64] = inf, nan
+    run.gemm(ab.ABFT_DETECT | ab.ABFT_STORED_SUMS)
+    rf, cf = run.flags()
+    want_r, want_c = np.zeros((batch, M), bool), np.zeros((batch, N), bool)
+    want_r[3, 130] = want_r[5, 299] = True
+    want_c[3] = want_c[5] = True
+    assert np.array_equal(rf, want_r) and np.array_equal(cf, want_c)
+    a1, r1, s1 = run.ws(ab.ABFT_WS_A_SUM), run.ws(ab.ABFT_WS_RC_PRED), run.ws(ab.ABFT_WS_RC_STO)
+    hit_a = np.zeros((batch, K), bool)
+    hit_a[3, 999] = hit_a[5, 64] = True
+    assert not np.isfinite(a1[hit_a]).any() and not np.isfinite(r1[want_r]).any() and not np.isfinite(s1[want_r]).any()
+    # the same fp32 sums, their atomics in another order
+    big = max(p.max_a for p in P)
+    assert np.max(np.abs(a1[~hit_a] - a0[~hit_a])) <= 2.0 ** -23 * M * big
+    assert np.max(np.abs(r1[~want_r] - r0[~want_r])) <= 2.0 ** -23 * K * big * N * max(p.max_b for p in P)
+    assert np.max(np.abs(s1[~want_r] - s0[~want_r])) <= 2.0 ** -23 * N * np.max(np.abs(s0))
