@@ -330,10 +330,6 @@ __global__ __launch_bounds__(256) void gemm_tile_kernel(TileArgs a)
                 const int k = (tn + i / KE * g.tiles_n) * KE + i % KE;
                 if (k < K) atomic_add_word(g.a_sum + (long)bz * K + k, from_word<acc_t>(col_lds[i]));
             }
-            if constexpr (!T::IS_INT) {
-                const float m = wave_max(ast.amax);
-                if (lane == 0 && m > 0.f) atomicMax(g.a_max + bz, __float_as_uint(m));
-            }
         }
         const int r = m0 + (tid >> 3) + 32 * (tid & 7);
         if (owned && (tid & 7) < BM / 32 && r < M) atomic_add_word(g.rc_pred + (long)bz * M + r, ast.rdot);
@@ -479,6 +475,10 @@ __global__ __launch_bounds__(256) void gemm_tile_kernel(TileArgs a)
                 cmax_s = wave_max(cmax_s);
                 if (lane == 0) *reinterpret_cast<float *>(stage) = cmax_s;       // (the wave is done with its stage)
             }
+            if (APASS && !g.a_given) {
+                const float m = wave_max(ast.amax);
+                if (lane == 0) *reinterpret_cast<float *>(stage + 4) = m;
+            }
         }
         // over LDS traffic only: a full barrier would also wait for every store of C
         asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
@@ -502,15 +502,17 @@ __global__ __launch_bounds__(256) void gemm_tile_kernel(TileArgs a)
             }
         }
         if constexpr (!T::IS_INT) {
-            if (sto && tid == 0) {
-                // the largest stored magnitude: what a consumer of this C needs as its max|A|.  One atomic per
-                // workgroup: on one word they are served one after the other (bf16 3819 x 1465 x 1161 with the
-                // stored sums, one per wave: 55.7 us, 37.0 without the sums)
+            // The largest magnitudes: of C as stored (what a consumer of this C needs as its max|A|), of A.  One
+            // atomic per workgroup: on one word they are served one after the other (bf16 3819 x 1465 x 1161 with the
+            // stored sums, one per wave: 55.7 us, 38.0 so, 37.0 without the sums)
+            auto publish = [&](uint32_t *word, int at) __attribute__((always_inline)) {
                 float m = 0.f;
 #pragma unroll
-                for (int w = 0; w < 4; ++w) m = fmaxf(m, *reinterpret_cast<const float *>(smem + w * TILE_STAGE_WAVE));
-                if (m > 0.f) atomicMax(g.c_max + bz, __float_as_uint(m));
-            }
+                for (int w = 0; w < 4; ++w) m = fmaxf(m, *reinterpret_cast<const float *>(smem + w * TILE_STAGE_WAVE + at));
+                if (m > 0.f) atomicMax(word + bz, __float_as_uint(m));
+            };
+            if (sto && tid == 0) publish(g.c_max, 0);
+            if (APASS && !g.a_given && tid == 64) publish(g.a_max, 4);
         }
     }
 }
