@@ -46,13 +46,21 @@ static size_t item_plan(int dt, const Shape &s, bool protect, bool sto, ItemArgs
 // queries, 150 items 18.4 / 16.3; 33 queries, 150 items 9.9 / 7.8; 256 queries, 256 items 32.1 / 44.8.
 constexpr int ONE_BLOCK_MIN_BATCH = 104, ONE_BLOCK_MIN_BATCH_TALL = 120, ONE_BLOCK_MIN_BATCH_PLAIN = 256;
 
+// Deep items (N <= 128) hold most of a compute unit's LDS while its waves wait for the whole of B first; without
+// checksums to form the tiles are then often the faster way, unless there are rows and items enough (407
+// shapes: four are more than 5 % slower by this line than on the item kernel, 58 were slower on it than on the tiles
+// of the kernel before): bf16 9 x 128 x 380, 369 items 21.9 us / tiles 9; 577 x 64 x 577, 256 items 36.9 / 52.2.
+constexpr int DEEP_MIN_BATCH_PLAIN = 128;
+
 // protect: of two problems of one shape the unprotected one may be tiled
 bool gemm_item_eligible(int dt, const Shape &s, bool stored_sums, bool protect)
 {
     if (s.batch < ITEM_MIN_BATCH) return false;
     ItemArgs g;
     if (item_plan(dt, s, true, stored_sums && dt != DT_I8, &g) == 0) return false;
-    if (s.N <= 128 || g.rch > 1 || g.MB == 1) return true;
+    if (s.N <= 128)
+        return protect || (long)s.K * elem_size(dt) <= (s.N <= 64 ? 640 : 384) || (g.MB >= 5 && s.batch >= DEEP_MIN_BATCH_PLAIN);
+    if (g.rch > 1 || g.MB == 1) return true;
     return protect ? s.batch >= (g.MB <= 8 ? ONE_BLOCK_MIN_BATCH : ONE_BLOCK_MIN_BATCH_TALL)
                    : s.batch >= ONE_BLOCK_MIN_BATCH_PLAIN && g.MB >= 4;
 }

@@ -1653,6 +1653,8 @@ ITEM_EDGES = [
     (290, 64, 577, 64, False),      # deeper than the ring of A, an odd number of steps
     (129, 97, 801, 64, False),      # four blocks of columns, the last of one column; too deep for LDS in 16 bits
     (65, 33, 400, 64, True),        # as deep with B stored N x K
+    (150, 64, 577, 128, False),     # deep, and on this kernel without checksums too
+    (161, 100, 300, 128, True),
     (330, 260, 80, 64, True),       # rows of A in more than one chunk, two blocks of columns per wave
     (330, 260, 80, 64, False),
     (96, 256, 190, 64, True),       # whole blocks both ways
