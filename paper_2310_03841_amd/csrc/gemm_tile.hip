@@ -561,19 +561,21 @@ static double tile_cost(int M, int N, int nslab, int batch, int shape)
 // Whether the tiles reduce A from the slabs they hold, behind a pass over B and with A b (APASS), instead of
 // extra workgroups that read A and B again and a check that reads A a third time.  Those run in the LDS
 // of a tile, one to three to a compute unit, and are for problems that leave the chip room.  From about
-// 50 MB of A and B on the tiles' own reduction is the faster way, so / with the extra
-// workgroups: f16 999 x 128 x 516, 596 items 518 / 913 / 456 us; bf16
-// 10496 x 768 x 2819, B cached 103 / 140 / 103; f16 12241 x 361 x 4045 127 / 130 / 140; below, bf16 8409 x 1717 x
-// 1300 (26 MB) 108 / 107 / 115.  Batches need more (64 MB): their items' slabs are few.  B stored K x N: the tiles wait
-// for LDS more than for memory, and the reduction does not fit beside (f16 10934 x 1864 x 2268 206 / 193).
+// 50 MB of A and B on the tiles' own reduction is the faster way; so / with the extra workgroups: f16 999 x 128
+// x 516, 596 items 480 / 903 us; bf16 10496 x 768 x 2819, B cached 82 / 140; below, bf16 8409 x 1717 x 1300
+// (26 MB) 108 / 107.  Batches need more (64 MB): their items have few slabs.  B stored K x N: the tiles
+// wait for LDS more than for memory, and the reduction does not fit beside (f16 10934 x 1864 x 2268 206 / 193),
+// but for large batches of many tiles (200 MB: int8 436 x 128 x 1360, 648 items
+// 367 / 1156).
 static bool fuses_a(int dt, const Shape &s, int nslab, int *bm)
 {
     const double bytes = (double)s.batch * ((double)s.M + s.N) * s.K * elem_size(dt);
-    if (!s.transB || nslab < 6 || bytes < (s.batch == 1 ? 48e6 : 64e6) || (dt == DT_I8 && s.N >= 65536)) return false;
+    if (nslab < 6 || (dt == DT_I8 && s.N >= 65536)) return false;
+    if (s.transB ? bytes < (s.batch == 1 ? 48e6 : 64e6) : s.batch == 1 || bytes < 200e6) return false;
     *bm = tile_cost(s.M, s.N, nslab, s.batch, 1) < 0.8 * tile_cost(s.M, s.N, nslab, s.batch, 2) ? 64 : 128;
     const int tiles_n = (s.N + 127) / 128;
     const long tiles = tiles_of(s.M, s.N, s.batch, *bm, 128);
-    return tiles >= 128 && tiles >= 4 * apass_owned_slabs(nslab, tiles_n) && tiles / s.batch <= MAX_GRID_X &&
+    return tiles >= 128 && tiles >= (s.transB ? 4 : 32) * apass_owned_slabs(nslab, tiles_n) && tiles / s.batch <= MAX_GRID_X &&
            tile_lds_bytes(*bm, 128, 3) + apass_lds_bytes(dt, nslab, tiles_n) <= 160 * 1024;
 }
 
@@ -614,7 +616,8 @@ static hipError_t launch_cfg(bool protect, bool transB, TileArgs &a, int batch, 
     if (tiles + a.n_extra > MAX_GRID_X) return hipErrorInvalidValue;
     a.n_tiles = (int)tiles;
     if constexpr (BN == 128)
-        if (a.fuse_bm) return launch_one<DT, BM, BN, NS, true, true, true>(a, batch, st);
+        if (a.fuse_bm) return transB ? launch_one<DT, BM, BN, NS, true, true, true>(a, batch, st)
+                                     : launch_one<DT, BM, BN, NS, true, false, true>(a, batch, st);
     if (protect) return transB ? launch_one<DT, BM, BN, NS, true, true>(a, batch, st)
                                : launch_one<DT, BM, BN, NS, true, false>(a, batch, st);
     return transB ? launch_one<DT, BM, BN, NS, false, true>(a, batch, st)

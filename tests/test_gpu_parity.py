@@ -1902,6 +1902,18 @@ def test_tiles_that_reduce_a_clean(ctx_large, dtype, which):
     _clean_case(ctx_large, dtype, M, N, K, batch, True)
 
 
+@pytest.mark.parametrize("dtype,M,batch,rows", [("i8", 300, 480, 64), ("bf16", 289, 256, 128), ("f16", 61, 1700, 64)])
+def test_tiles_that_reduce_a_clean_b_stored_kn(dtype, M, batch, rows):
+    """Batches of 200 MB, 128- and 64-row tiles."""
+    N, K = min(130, M), 1000
+    assert ab.abft_tile_shape(ab.DTYPE_CODE[dtype], ab.make_shape(M, N, K, batch=batch)) == (rows, 128)
+    ctx = ab.abft_create(max_rows=batch * M, max_cols=batch * N, max_depth=batch * 1024, max_batch=batch)
+    try:
+        _clean_case(ctx, dtype, M, N, K, batch, False)
+    finally:
+        ab.abft_destroy(ctx)
+
+
 @pytest.mark.parametrize("dtype", ["i8", "f16"])
 def test_tiles_of_64_rows_that_reduce_a_clean(ctx_large, dtype):
     M, N, K, batch = 60, 250, 1000, 400
