@@ -170,17 +170,20 @@ int abft_destroy(abft_ctx *ctx);
 int abft_encode_b(abft_ctx *ctx, const void *B, abft_dtype dtype, const abft_shape *s, void *stream);
 
 /* The protected GEMM (Sec. III-B.1 "Checksums"; epilogue fusion of Sec. V "Optimizations" (2)).
- * Enqueues: the pass over B that gives b = B e and max|B| (skipped with
+ * Enqueues, for large problems: the pass over B that gives b = B e and max|B| (skipped with
  * ABFT_B_CHECKSUM_CACHED); the GEMM, which besides C produces, from the operand slabs of A it
  * holds on chip, a = e^T A, the row prediction A b and max|A|, and from its accumulators
  * (before rounding) the observed sums e^T C and C e; the check kernel, which forms the
  * column prediction a B from one read of B, compares both pairs (equality for ABFT_I8,
  * |difference| <= tau otherwise; NaN or Inf always flag) and writes flags, counts and status.
+ * Other problems are two kernels: the GEMM, whose launch also holds workgroups that form a, b and
+ * the two maxima, and the check kernel, which forms A b from another read of A as well.
  * A and B must stay unchanged until the check kernel has run.
- * A batch of at least 64 small problems (per-head attention products: N <= 640, M <= 1024, a row
- * of K at most 640 bytes, operands of one item fitting the local memory of a compute unit; with
- * ABFT_STORED_SUMS only up to N = 256) is one kernel instead: one workgroup per batch item forms b, a, both
- * predictions and both observed sums from on-chip operands and compares them itself.
+ * A batch of at least 64 small problems (per-head attention products: N <= 640, M <= 1024; a row
+ * of K at most 1600 bytes for N <= 128, 384 for N <= 256, 256 beyond; operands and vectors of one item
+ * fitting the local memory of a compute unit; with ABFT_STORED_SUMS only up to N = 256) is one kernel
+ * instead: one workgroup per batch item forms b, a, both predictions and both observed sums from on-chip
+ * operands and compares them itself.  (Wide items that fill that memory need 104 and more of them.)
  * mode ABFT_OFF ignores `r` (may be NULL).  Flags and counts are overwritten. */
 int abft_gemm(abft_ctx *ctx, const void *A, const void *B, void *C, abft_dtype dtype, int mode,
               const abft_shape *s, const abft_result *r, void *stream);
@@ -199,7 +202,7 @@ int abft_gemm_bias(abft_ctx *ctx, const void *A, const void *B, const void *bias
 /* abft_gemm for callers that cannot allocate device memory: code under HIP graph capture, tight
  * serving loops, harnesses that forbid hipMalloc.  Same arguments (without a context), same
  * kernels, same results as abft_gemm; the workspace (checksum vectors, partial sums, tickets) is
- * a fixed array of about 4 MB inside the library's device image instead of the pools of a
+ * a fixed array of about 4.4 MB inside the library's device image instead of the pools of a
  * context, so the call allocates nothing, on the device or through any library.  Each GPU holds
  * its own copy of that array from the moment the library is loaded until the process ends; the
  * call uses the copy of the current device.  Limits (ABFT_EWORKSPACE beyond them):
@@ -308,8 +311,8 @@ int abft_inject(abft_ctx *ctx, void *C, abft_dtype dtype, const abft_shape *s, i
 /* Device pointer and element count of a workspace vector for the given shape (layout [batch][len]). */
 int abft_workspace(abft_ctx *ctx, int which, const abft_shape *s, void **ptr, int64_t *count);
 
-/* Tile the GEMM kernel uses for this problem (rows, cols of C per workgroup; M, N where a
- * workgroup takes a whole batch item). */
+/* Tile the GEMM kernel uses for a protected call of this problem (rows, cols of C per workgroup; M, N where
+ * a workgroup takes a whole batch item). */
 int abft_tile_shape(abft_dtype dtype, const abft_shape *s, int *tile_m, int *tile_n);
 
 /* Kernel timing for reports (not a hot call: creates HIP events).  Between begin and end every

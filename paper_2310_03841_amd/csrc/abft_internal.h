@@ -44,8 +44,8 @@ struct Workspace {
     //   | cc_sto [batch][N] | rc_sto [batch][M] | c_max [batch]
     //   | cc_acc [batch][N] | rc_acc [batch][M] (doubles; general kernel, floating point)
     uint32_t *cc_obs, *rc_obs;      // observed sums of C (epilogue)
-    uint32_t *rc_pred;              // A (B e), from the operand slabs of A in LDS
-    uint32_t *a_sum;                // a = e^T A, from the same slabs
+    uint32_t *rc_pred;              // A (B e), from the operand slabs of A in LDS or by the check kernel
+    uint32_t *a_sum;                // a = e^T A, from the same slabs or by workgroups beside the tiles
     uint32_t *a_max;                // max|A| (float bits)
     uint32_t *cc_sto, *rc_sto;      // sums of C as stored (floating point, on request)
     uint32_t *c_max;                // max|C as stored| (float bits) [batch], formed with them

@@ -87,11 +87,11 @@ hipError_t launch_copy(uint32_t *dst, const uint32_t *src, size_t nwords, hipStr
 // ====================================================================== encode
 // Input-side checksum vectors (Sec. III-B.1 "Checksums"): a = e^T A (the input summed over its
 // rows) and b = B e (the weight reduced over its output dimension), both of length K, plus
-// max|A|, max|B| for the tolerance and the row checksum prediction rc_pred = A b.  Everything
-// that reads A is done by the GEMM kernel on the slabs it holds in LDS (gemm_apass.h); what is
-// left here is the pass over B, which must be complete before that (A b needs all of b).  For a
-// weight it is done once, offline (remark (2) of the same paragraph).
-// Pass over B as a kernel of its own (the general GEMM kernel runs the same pass beside its tiles).
+// max|A|, max|B| for the tolerance and the row checksum prediction rc_pred = A b.  Where the GEMM
+// kernel reduces A from the slabs it holds in LDS (gemm_apass.h: the fast kernel, the general one for
+// large problems), b must be complete before it (A b needs all of b): the pass over B as a kernel of its own.
+// For a weight it is done once, offline (remark (2) of the same paragraph).  Otherwise the general kernel
+// runs the passes over A and B beside its tiles, and A b is formed by the check kernel.
 struct EncBArgs {
     EncArgs e;
     uint32_t *zero_ptr;   // region every block helps to clear (the next kernel's atomics start at zero)
@@ -264,9 +264,9 @@ hipError_t launch_compare(int dt, const Shape &s, const Workspace &w, const Verd
 
 // ======================================================================= check
 // Runs after a GEMM kernel, whose launch has completed a = e^T A, b = B e, the two maxima and the
-// observed sums.  Forms the predictions of Sec. III-B.1 that are missing, cc_pred = a B and (behind the
-// general kernel; the fast one forms it from the slabs it holds) rc_pred = A b, each a matrix-vector
-// product over one read of its operand, compares and flags.
+// observed sums.  Forms the predictions of Sec. III-B.1 that are missing, cc_pred = a B and (unless the GEMM
+// kernel formed it from the slabs it holds: rc_ready) rc_pred = A b, each a matrix-vector product over
+// one read of its operand, compares and flags.
 //
 // Bound by latency: a workgroup's critical path is one round of loads and one reduction.  Units of a
 // batch item: row units of A, column units of B (a B stored N x K is the same product as A b), one

@@ -5,10 +5,11 @@
 // A (B e) (the row checksum prediction).  Both read every element of A exactly once, and every
 // element of A passes through LDS on its way to the matrix cores anyway: of the workgroups that
 // share a tile row, the one in tile column (s mod tiles_n) reduces slab s while it is resident.
-// So A is read from memory once, by the GEMM, and the separate encode pass over A disappears.
+// So A is read from memory once, by the GEMM.  The fast kernel does it always, the general one for large
+// problems (small ones form the checksums beside their tiles: encode_pass.h).
 //
 // LDS slab layout (both GEMM kernels): row r is 128 bytes = eight 16-byte chunks, chunk c stored
-// in slot c ^ (r & 7).  Thread t reduces chunk c = t & 7 of rows (t >> 3) + 32 p.
+// in slot c ^ ((r >> 1) & 7).  Thread t reduces chunk c = t & 7 of rows (t >> 3) + 32 p.
 #pragma once
 #include "abft_device.h"
 #include "gemm_args.h"
@@ -62,19 +63,18 @@ __host__ __device__ inline size_t apass_lds_bytes_per_wave(int dt, int nslab, in
 
 // Reduce one resident slab of A.  sA: the slab in LDS (BM rows).  b_lds: the KE values of b
 // that belong to the slab (LDS).  rows_valid: rows of the tile inside M (rows beyond may hold
-// anything, finite or not: they are ignored).  col_lds: KE words of this slab's column sums
-// (LDS atomics: the four waves add to the same words).
+// anything, finite or not: they are ignored).  col_lds: KE words of this slab's column sums.
+// keep: bytes of a row of the slab that are inside K.
 // GIVEN: the caller supplied a = e^T A and max|A| (a checksum carried over from the kernel that
 // produced A): only the row dots are formed.
-// SW16: the slab's swizzle is slot = chunk ^ ((row >> 1) & 7) (gemm_fast) instead of chunk ^ (row & 7).
-// SPLIT_ONLY: int8 with |b| < 2^23 guaranteed by the caller (mul24_ok is not consulted): the
-// element-wise integer form is left out, which is what keeps the fast kernel's registers free of spills.
+// int8: |b| < 2^23 (the callers' N is below 65536).
 // PER_WAVE: col_lds is this wave's own KE words for the slab, written with plain stores (the caller
-// adds the waves' words up when it hands the sums on).  Measured on the fast kernel: the eight LDS
-// atomic adds per wave and slab held the wave's next LDS reads back by some 800 clocks.
-template <int DT, int BM, bool GIVEN = false, bool SW16 = false, bool SPLIT_ONLY = false, bool PER_WAVE = false>
+// adds the waves' words up when it hands the sums on); otherwise the four waves add to the same words.
+// Measured on the fast kernel: the eight LDS atomic adds per wave and slab held the wave's next LDS
+// reads back by some 800 clocks.  The general kernel has no LDS to spare for four sets.
+template <int DT, int BM, bool GIVEN, bool PER_WAVE>
 __device__ __forceinline__ void a_pass(const uint8_t *sA, const uint32_t *b_lds, int rows_valid,
-                                       uint32_t *col_lds, APassState<DT> &st, bool mul24_ok, int keep = SLAB_BYTES)
+                                       uint32_t *col_lds, APassState<DT> &st, int keep = SLAB_BYTES)
 {
     using T = Traits<DT>;
     typedef typename T::acc_t acc_t;
@@ -82,7 +82,7 @@ __device__ __forceinline__ void a_pass(const uint8_t *sA, const uint32_t *b_lds,
     constexpr int P = BM / 32;
     const int tid = tile_thread_index();
     const int c = tid & 7, rg = tid >> 3;
-    const uint8_t *src = sA + rg * SLAB_BYTES + ((c ^ (SW16 ? (rg >> 1) & 7 : rg & 7)) * 16);
+    const uint8_t *src = sA + rg * SLAB_BYTES + ((c ^ ((rg >> 1) & 7)) * 16);
 
     acc_t bv[CE], cs[CE];
 #pragma unroll
@@ -101,54 +101,49 @@ __device__ __forceinline__ void a_pass(const uint8_t *sA, const uint32_t *b_lds,
         for (int p = 0; p < P; ++p) v[p] = mask_chunk(v[p], keep - c * 16);
     }
     acc_t mine = T::zero();
-    bool done = false;
     if constexpr (T::IS_INT) {
-        if (mul24_ok || SPLIT_ONLY) {
-            // |b| <= 128 N < 2^23: b = 256 hi + lo with 0 <= lo < 256 and |hi| < 2^15.  The bytes of a
-            // word of A as two pairs of 16-bit integers (bytes 0, 2 and bytes 1, 3): the column sums
-            // add pair-wise (at most 8 rows per thread), the row product takes two products per
-            // instruction against the pairs of hi and of lo.
-            typedef short s16x2 __attribute__((ext_vector_type(2)));
-            s16x2 bhi[8], blo[8], csp[8];
+        // |b| <= 128 N < 2^23: b = 256 hi + lo with 0 <= lo < 256 and |hi| < 2^15.  The bytes of a
+        // word of A as two pairs of 16-bit integers (bytes 0, 2 and bytes 1, 3): the column sums
+        // add pair-wise (at most 8 rows per thread), the row product takes two products per
+        // instruction against the pairs of hi and of lo.
+        typedef short s16x2 __attribute__((ext_vector_type(2)));
+        s16x2 bhi[8], blo[8], csp[8];
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+            const int b0 = (int)bv[4 * d], b1 = (int)bv[4 * d + 1], b2 = (int)bv[4 * d + 2], b3 = (int)bv[4 * d + 3];
+            bhi[2 * d] = s16x2{(short)(b0 >> 8), (short)(b2 >> 8)};
+            bhi[2 * d + 1] = s16x2{(short)(b1 >> 8), (short)(b3 >> 8)};
+            blo[2 * d] = s16x2{(short)(b0 & 255), (short)(b2 & 255)};
+            blo[2 * d + 1] = s16x2{(short)(b1 & 255), (short)(b3 & 255)};
+        }
+#pragma unroll
+        for (int j = 0; j < 8; ++j) csp[j] = s16x2{0, 0};
+#pragma unroll
+        for (int p = 0; p < P; ++p) {
+            i32x4 x4 = v[p];
+            if (rg + 32 * p >= rows_valid) x4 = i32x4{0, 0, 0, 0};
+            int dhi = 0, dlo = 0;
 #pragma unroll
             for (int d = 0; d < 4; ++d) {
-                const int b0 = (int)bv[4 * d], b1 = (int)bv[4 * d + 1], b2 = (int)bv[4 * d + 2], b3 = (int)bv[4 * d + 3];
-                bhi[2 * d] = s16x2{(short)(b0 >> 8), (short)(b2 >> 8)};
-                bhi[2 * d + 1] = s16x2{(short)(b1 >> 8), (short)(b3 >> 8)};
-                blo[2 * d] = s16x2{(short)(b0 & 255), (short)(b2 & 255)};
-                blo[2 * d + 1] = s16x2{(short)(b1 & 255), (short)(b3 & 255)};
-            }
-#pragma unroll
-            for (int j = 0; j < 8; ++j) csp[j] = s16x2{0, 0};
-#pragma unroll
-            for (int p = 0; p < P; ++p) {
-                i32x4 x4 = v[p];
-                if (rg + 32 * p >= rows_valid) x4 = i32x4{0, 0, 0, 0};
-                int dhi = 0, dlo = 0;
-#pragma unroll
-                for (int d = 0; d < 4; ++d) {
-                    const int wd = x4[d];
-                    const s16x2 w = s16x2{(short)(wd & 0xFFFF), (short)(wd >> 16)};
-                    const s16x2 ev = (w << 8) >> 8, od = w >> 8;       // bytes 0, 2 and 1, 3, sign-extended
-                    if (!GIVEN) {
-                        csp[2 * d] += ev;
-                        csp[2 * d + 1] += od;
-                    }
-                    dhi = __builtin_amdgcn_sdot2(ev, bhi[2 * d], dhi, false);
-                    dhi = __builtin_amdgcn_sdot2(od, bhi[2 * d + 1], dhi, false);
-                    dlo = __builtin_amdgcn_sdot2(ev, blo[2 * d], dlo, false);
-                    dlo = __builtin_amdgcn_sdot2(od, blo[2 * d + 1], dlo, false);
+                const int wd = x4[d];
+                const s16x2 w = s16x2{(short)(wd & 0xFFFF), (short)(wd >> 16)};
+                const s16x2 ev = (w << 8) >> 8, od = w >> 8;       // bytes 0, 2 and 1, 3, sign-extended
+                if (!GIVEN) {
+                    csp[2 * d] += ev;
+                    csp[2 * d + 1] += od;
                 }
-                acc_t dot = (acc_t)(int)((uint32_t)dhi * 256u + (uint32_t)dlo);
-                dot = row8_sum(dot);
-                if (c == p) mine = dot;
+                dhi = __builtin_amdgcn_sdot2(ev, bhi[2 * d], dhi, false);
+                dhi = __builtin_amdgcn_sdot2(od, bhi[2 * d + 1], dhi, false);
+                dlo = __builtin_amdgcn_sdot2(ev, blo[2 * d], dlo, false);
+                dlo = __builtin_amdgcn_sdot2(od, blo[2 * d + 1], dlo, false);
             }
-#pragma unroll
-            for (int q = 0; q < CE; ++q) cs[q] = (acc_t)csp[2 * (q >> 2) + (q & 1)][(q >> 1) & 1];
-            done = true;
+            acc_t dot = (acc_t)(int)((uint32_t)dhi * 256u + (uint32_t)dlo);
+            dot = row8_sum(dot);
+            if (c == p) mine = dot;
         }
-    }
-    if (!(T::IS_INT && SPLIT_ONLY) && !done) {
+#pragma unroll
+        for (int q = 0; q < CE; ++q) cs[q] = (acc_t)csp[2 * (q >> 2) + (q & 1)][(q >> 1) & 1];
+    } else {
 #pragma unroll
         for (int p = 0; p < P; ++p) {
             i32x4 x4 = v[p];
@@ -158,12 +153,8 @@ __device__ __forceinline__ void a_pass(const uint8_t *sA, const uint32_t *b_lds,
             for (int q = 0; q < CE; ++q) {
                 const acc_t x = T::elem(x4, q);
                 if (!GIVEN) cs[q] = add_t(cs[q], x);
-                if constexpr (T::IS_INT) {
-                    dot = (acc_t)((uint32_t)x * (uint32_t)bv[q] + (uint32_t)dot);
-                } else {
-                    dot = __builtin_fmaf((float)x, (float)bv[q], (float)dot);
-                    if (!GIVEN) st.amax = fmaxf(st.amax, fabsf((float)x));
-                }
+                dot = __builtin_fmaf((float)x, (float)bv[q], (float)dot);
+                if (!GIVEN) st.amax = fmaxf(st.amax, fabsf((float)x));
             }
             dot = row8_sum(dot);
             if (c == p) mine = dot;
@@ -196,7 +187,7 @@ __device__ __forceinline__ void a_pass(const uint8_t *sA, const uint32_t *b_lds,
 // piece are issued in its shadow).  begin() requests the thread's chunks of the slab and its values
 // of b, piece<k>() takes element (or, int8, half a word) k % 8 of row group k / 8, end() reduces the
 // column sums over the wave and writes them to the wave's own words for the slab in LDS.  Same
-// arithmetic, in the same order, as a_pass above with SW16, PER_WAVE and (int8) SPLIT_ONLY.
+// arithmetic, in the same order, as a_pass above with PER_WAVE.
 template <int DT, int BM, bool GIVEN> struct APassSteps {
     using T = Traits<DT>;
     typedef typename T::acc_t acc_t;

@@ -27,7 +27,6 @@ struct GemmArgs {
     const uint32_t *bias;                         // layer bias [N] (float / int32 words) or null
     const uint32_t *b_sum;                        // B e, complete before the launch [batch][K]
     uint32_t *counts;                             // fast kernel, protected: cleared for the check kernel
-    int mul24_ok;                                 // int8: |b| < 2^23, 24-bit multiplies are exact
 };
 
 // Workgroup -> tile inside a region of tiles_m x tiles_n tiles: consecutive ids of one XCD

@@ -1,4 +1,4 @@
-// Epilogue shared by the GEMM kernels: store C, take the observed row / column sums of the
+// Epilogue of the fast GEMM kernel: store C, take the observed row / column sums of the
 // M x N block from the accumulators (before rounding) and add them to cc_obs / rc_obs, and
 // hand over what the pass over A's slabs collected (gemm_apass.h).  Paper: output checksum
 // fused with the GEMM epilogue (Sec. IV-C memory paragraph, Sec. V "Optimizations" (2)).
@@ -96,8 +96,7 @@ template <int DT> struct EpiProt {
     const uint32_t *col_lds;  // column sums of the owned slabs, KE words each (LDS)
     int owned;                // number of owned slabs reduced: the j-th is slab slab0 + j * slab_step of K
     int slab0, slab_step;
-    int col_copies;           // 1, or 4: one set of column sums per wave, col_stride words apart, to be added up
-    int col_stride;
+    int col_stride;           // words from one wave's set of column sums to the next; the four are added up
 };
 
 template <int DT, int BM, int BN, bool PROT, bool BIAS>
@@ -455,7 +454,7 @@ __device__ __forceinline__ void gemm_epilogue_impl(const GemmArgs &g,
             const int k = (ep.slab0 + (t / KE) * ep.slab_step) * KE + (t % KE);
             if (k < g.K) {
                 acc_t v = from_word<acc_t>(ep.col_lds[t]);
-                for (int w = 1; w < ep.col_copies; ++w) v = add_t(v, from_word<acc_t>(ep.col_lds[w * ep.col_stride + t]));
+                for (int w = 1; w < 4; ++w) v = add_t(v, from_word<acc_t>(ep.col_lds[w * ep.col_stride + t]));
                 atomic_add_word(g.a_sum + (long)bz * g.K + k, v);
             }
         }

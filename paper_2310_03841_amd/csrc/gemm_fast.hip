@@ -174,7 +174,7 @@ __device__ __forceinline__ void fast_tile(const GemmArgs &g, uint8_t *smem, int 
     EpiProt<DT> ep;
     ep.st.rdot = T::zero(); ep.st.amax = 0.f;
     ep.col_lds = col_lds; ep.slab0 = tn; ep.slab_step = g.tiles_n; ep.owned = 0;
-    ep.col_copies = 4; ep.col_stride = 0;
+    ep.col_stride = 0;
     {
         const int nslab = K / KE;                      // at least 3 (gemm_fast_eligible)
         int next_own = tn;
@@ -209,11 +209,9 @@ __device__ __forceinline__ void fast_tile(const GemmArgs &g, uint8_t *smem, int 
             const int buf = s & 1;
             if (PROT && decltype(own_c)::value && s == next_own) {
                 if (g.a_given)
-                    a_pass<DT, BM, true, true, true, true>(smem + buf * BUF, b_lds + ep.owned * KE, a_rows, col_mine + ep.owned * KE, ep.st,
-                                         g.mul24_ok != 0);
+                    a_pass<DT, BM, true, true>(smem + buf * BUF, b_lds + ep.owned * KE, a_rows, col_mine + ep.owned * KE, ep.st);
                 else
-                    a_pass<DT, BM, false, true, true, true>(smem + buf * BUF, b_lds + ep.owned * KE, a_rows, col_mine + ep.owned * KE, ep.st,
-                                   g.mul24_ok != 0);
+                    a_pass<DT, BM, false, true>(smem + buf * BUF, b_lds + ep.owned * KE, a_rows, col_mine + ep.owned * KE, ep.st);
                 next_own += g.tiles_n;
                 ep.owned += 1;
             }

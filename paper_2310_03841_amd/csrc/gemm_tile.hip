@@ -7,7 +7,8 @@
 // So the input-side vectors a = e^T A and b = B e, which depend on nothing, are formed by extra
 // workgroups of the same launch, beside the tiles, instead of by a kernel of their own ahead of it;
 // both predictions wait for the check kernel behind the launch (check_kernel, aux_kernels.hip).  A
-// call is two launches whatever is cached.  (Before: pass over B, GEMM with the pass over A inside
+// call is two launches whatever is cached.  Large protected problems keep the older way, a pass over B
+// first and A reduced from the slabs in LDS (fuses_a below).  (Before: pass over B, GEMM with the pass over A inside
 // its main loop, finish; 197 x 768 x 768 int8 25.4 us, of which 5.2 + 14.0 + 7.8 in the kernels.)
 //
 // Tile: BM x BN by four waves of (BM/2) x (BN/2), 32 x 32 MFMA blocks.  K advances in slabs of 128
@@ -286,9 +287,9 @@ __global__ __launch_bounds__(256) void gemm_tile_kernel(TileArgs a)
             if (s != next_own) return;
             const uint8_t *sA = smem + (s % NS) * BUF;
             if (g.a_given)
-                a_pass<DT, BM, true, true, true, false>(sA, b_lds + own_at, M - m0, col_lds + own_at, ast, true, K * ES - s * SLAB_BYTES);
+                a_pass<DT, BM, true, false>(sA, b_lds + own_at, M - m0, col_lds + own_at, ast, K * ES - s * SLAB_BYTES);
             else
-                a_pass<DT, BM, false, true, true, false>(sA, b_lds + own_at, M - m0, col_lds + own_at, ast, true, K * ES - s * SLAB_BYTES);
+                a_pass<DT, BM, false, false>(sA, b_lds + own_at, M - m0, col_lds + own_at, ast, K * ES - s * SLAB_BYTES);
             next_own += g.tiles_n;
             own_at += KE;
         }
@@ -713,7 +714,6 @@ hipError_t launch_gemm(int dt, bool protect, bool stored_sums, bool encode_b, co
     g.rc_sto = g.cc_sto ? w.rc_sto : nullptr;
     g.c_max = g.cc_sto ? w.c_max : nullptr;
     g.a_given = (protect && w.a_given) ? 1 : 0;
-    g.mul24_ok = s.N < 65536 ? 1 : 0;            // |b| <= 128 N
     g.tiles_m = g.tiles_n = g.n_big = g.tiles_m_big = g.tiles_m_small = 0;
     g.n_small = 0; g.batch = s.batch;
     g.counts = counts;
