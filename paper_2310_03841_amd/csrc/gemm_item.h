@@ -44,13 +44,13 @@ struct ItemArgs {
     // protected launches: everything below is written with plain stores, item by item
     uint32_t *cc_obs, *rc_obs, *rc_pred, *a_sum, *a_max, *b_sum, *b_max, *cc_pred, *s_pred;
     uint32_t *cc_sto, *rc_sto;                    // sums of C as stored (after rounding), on request (floating point)
-    uint32_t *c_max;                              // max|C as stored| as float bits, with them
     float *maxabs, *tau;
     float tau_override, tau_override_cols;
     uint8_t *row_flag, *col_flag;
     uint32_t *counts;
     uint32_t *ticket;                             // [3]: ticket, flagged rows, flagged cols (self-cleaning)
     uint32_t *group_ticket;                       // [ITEM_MAX_BLOCKS / ITEM_GROUP] (self-cleaning)
+    uint32_t *c_max;                              // max|C as stored| as float bits, with the stored-side sums
 };
 
 // Workgroup barrier over LDS traffic only: a full barrier would also wait until every store of C
