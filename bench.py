@@ -4,7 +4,7 @@
 Workload: the bf16 ViT-B MLP fc1 GEMM at batch 64 (A 12608 x 768 ~ N(0,1), weight 3072 x 768
 ~ N(0,0.02), fp32 accumulate, fp32 checksums, no injected errors).  A step is one call of
 abft_gemm in DETECT mode: the pass over B (its checksum vector), the GEMM that also reduces A's
-slabs and its own accumulators, and the finish kernel (column prediction, compare, flags) --
+slabs and its own accumulators, and the check kernel (column prediction, compare, flags) --
 every ABFT-side kernel is inside the timed region, nothing is cached.
 Useful work counted: 2*M*N*K only.
 
@@ -41,7 +41,7 @@ HBM_PEAK_GBS = 8000.0
 MEASURED_TRAFFIC_BYTES = int((59654.2 / 0.5 + 77839.6) * 1024)   # profiles/gemm_fast_bf16_fc1_b64_hbm_traffic.txt
 # average duration of the same kernel under rocprofv3 --kernel-trace --stats (dispatch to completion, without
 # the launch latency that HIP events around a kernel include); profiles/gemm_fast_bf16_fc1_b64_kernel_stats.txt
-PROFILED_KERNEL_US = 65.57
+PROFILED_KERNEL_US = 66.55
 
 
 def log(*a):
@@ -120,7 +120,7 @@ def main():
     # Every context records an event behind each of its GEMM kernels; after a synchronisation the
     # first call of lane i waits for the first GEMM of lane i - 1, so that the lanes' GEMMs do not
     # start together (they would share the chip, end together and leave it idle during both
-    # finish kernels; from an offset start the lanes stay apart by themselves).
+    # check kernels; from an offset start the lanes stay apart by themselves).
     lane_events = []
     for c, r, rs, st in lanes:
         ev = torch.cuda.Event()
@@ -676,7 +676,7 @@ def main():
         "data": "synthetic",
         "config": {"workload": "ViT-B MLP fc1, batch 64, bf16: A 12608x768 N(0,1), W 3072x768 N(0,0.02), "
                                "C bf16, fp32 accumulate + fp32 checksums", "M": M, "N": N, "K": K,
-                   "mode": "DETECT (pass over B, GEMM with A-slab and accumulator sums, finish: predict + compare)",
+                   "mode": "DETECT (pass over B, GEMM with A-slab and accumulator sums, check: predict + compare)",
                    "streams": n_lanes,
                    "pipelining": "steps dealt round-robin to the streams; a context, a batch of activations and an "
                                  "output per stream, the weight shared; after each synchronisation every further stream's "
