@@ -566,17 +566,17 @@ static double tile_cost(int M, int N, int nslab, int batch, int shape)
 // x 516, 596 items 480 / 903 us; bf16 10496 x 768 x 2819, B cached 82 / 140; below, bf16 8409 x 1717 x 1300
 // (26 MB) 108 / 107.  Batches need more (64 MB): their items have few slabs.  B stored K x N: the tiles
 // wait for LDS more than for memory, and the reduction does not fit beside (f16 10934 x 1864 x 2268 206 / 193),
-// but for large batches of many tiles (200 MB: int8 436 x 128 x 1360, 648 items
+// but for large batches of many tiles, unless A is the far smaller operand (200 MB: int8 436 x 128 x 1360, 648 items
 // 367 / 1156).
 static bool fuses_a(int dt, const Shape &s, int nslab, int *bm)
 {
     const double bytes = (double)s.batch * ((double)s.M + s.N) * s.K * elem_size(dt);
     if (nslab < 6 || (dt == DT_I8 && s.N >= 65536)) return false;
-    if (s.transB ? bytes < (s.batch == 1 ? 48e6 : 64e6) : s.batch == 1 || bytes < 200e6) return false;
+    if (s.transB ? bytes < (s.batch == 1 ? 48e6 : 64e6) : s.batch == 1 || bytes < 200e6 || s.M < s.N / 4) return false;
     *bm = tile_cost(s.M, s.N, nslab, s.batch, 1) < 0.8 * tile_cost(s.M, s.N, nslab, s.batch, 2) ? 64 : 128;
     const int tiles_n = (s.N + 127) / 128;
     const long tiles = tiles_of(s.M, s.N, s.batch, *bm, 128);
-    return tiles >= 128 && tiles >= (s.transB ? 4 : 32) * apass_owned_slabs(nslab, tiles_n) && tiles / s.batch <= MAX_GRID_X &&
+    return tiles >= 128 && tiles >= (s.transB ? 4 : 24) * apass_owned_slabs(nslab, tiles_n) && tiles / s.batch <= MAX_GRID_X &&
            tile_lds_bytes(*bm, 128, 3) + apass_lds_bytes(dt, nslab, tiles_n) <= 160 * 1024;
 }
 
