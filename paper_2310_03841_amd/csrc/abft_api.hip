@@ -20,7 +20,7 @@ struct abft_ctx {
     bool bclean[2];         // slot is all zero
     uint32_t *pool_batch;   // per-batch scalars
     uint32_t *pool_cols;    // cc_pred
-    uint32_t *pool_obs;     // two regions of cc_obs | rc_obs | rc_pred | a_sum | a_max | cc_sto | rc_sto | cc_acc | rc_acc:
+    uint32_t *pool_obs;     // two regions (Workspace says what is in one):
                             // protected GEMMs alternate between them; each must be clean before use
     size_t region_words;    // words per region
     int cur;                // region of the last protected GEMM
@@ -87,7 +87,8 @@ constexpr int SMALL_WORDS = 8 + 64 + 1;
 // one region of pool_obs; even, so that the doubles at its end stay aligned in both regions
 static constexpr size_t obs_region_words(size_t R, size_t Cn, size_t D, size_t Bt)
 {
-    return (2 * Cn + 3 * R + D + 2 * Bt + 1 + 2 * (Cn + R) + 1) / 2 * 2;
+    const size_t most = (size_t)ONE_LAUNCH_MAX_LEN, one = 2 * ((Cn < most ? Cn : most) + (R < most ? R : most) + Bt);
+    return (2 * Cn + 3 * R + D + 2 * Bt + 1 + 2 * (Cn + R) + 1 + one + ONE_LAUNCH_TICKET_WORDS) / 2 * 2;
 }
 static constexpr size_t pool_total_words(size_t R, size_t Cn, size_t D, size_t Bt)
 {
@@ -239,6 +240,11 @@ static void carve(const abft_ctx *c, int dt, const Shape &s, Workspace *w)
     w->rc_acc = w->cc_acc + bN;
     // the general kernel adds up floating-point row and column sums of its tiles in doubles
     if (dt != DT_I8 && !gemm_takes_fast(dt, s)) w->zero_words = acc0 + 2 * (bN + bM);
+    w->cc_pacc = dt == DT_I8 ? w->cc_acc : w->rc_acc + bM;
+    w->rc_pacc = w->cc_pacc + bN;
+    w->s_pacc = w->rc_pacc + bM;
+    w->tickets = reinterpret_cast<uint32_t *>(w->s_pacc + s.batch);
+    if (const size_t tickets = gemm_one_launch(dt, s)) w->zero_words = (size_t)(w->tickets - w->cc_obs) + tickets;
     w->cc_vobs = c->pool_vobs + (size_t)c->vcur * c->vregion_words;
     w->rc_vobs = w->cc_vobs + bN;
     w->fix_tiles = c->fix_tiles;
@@ -403,7 +409,8 @@ static int own_given(abft_ctx *ctx, int dtype, const Shape &sh, Workspace *w, hi
 // The kernels of a protected GEMM, tiled path: pass over B (unless its encoding is cached; the general
 // kernel does it beside its tiles), GEMM, check.  The call accumulates into the region the previous protected call did not use.  It is
 // clean unless a call failed half way; the region of the previous call is cleared by this
-// call's check kernel.  So a call with a cached B checksum is two kernels: GEMM, check.
+// call's check kernel.  So a call with a cached B checksum is two kernels: GEMM, check.  A problem of a few tiles
+// (gemm_one_launch) is one: the general kernel, which then does all of it.
 static int enqueue_tiled(abft_ctx *ctx, int dtype, bool cached, bool stored, const void *A, const void *B, void *C,
                          const Shape &sh, Workspace *w, const Verdict &v, const InjectArm &arm, hipEvent_t *ev,
                          hipStream_t st)
@@ -427,30 +434,34 @@ static int enqueue_tiled(abft_ctx *ctx, int dtype, bool cached, bool stored, con
     if (gm && stale < w->zero_words) stale = w->zero_words;
     ctx->dirty[ctx->cur] = ctx->region_words;            // until everything below is enqueued
     const bool fast = gemm_takes_fast(dtype, sh), rc_ready = fast || gemm_fuses_a(dtype, sh);
+    const bool one = gemm_one_launch(dtype, sh) != 0;
+    // the kernel that ends the call also cleans, for calls to come, the region of the previous call and the b slot that is
+    // not in use
+    OneLaunch end = {v, nullptr, nullptr, 0, 0};
+    if (!gm) {
+        const int other = ctx->bslot ^ 1;
+        end.zero_ptr = prev_base;
+        end.zero_words = ctx->dirty[prev];
+        ctx->dirty[prev] = ctx->region_words;
+        if (!ctx->bclean[other]) {
+            end.zero2_ptr = ctx->pool_depth + (size_t)other * ctx->bslot_words;
+            end.zero2_words = ctx->bslot_words;
+        }
+    }
     if (!cached && rc_ready) HIP_TRY(launch_encode_b(dtype, B, sh, *w, w->cc_obs, stale, st));
     else if (stale) HIP_TRY(launch_zero(w->cc_obs, stale, st));
     if (ev) HIP_TRY(hipEventRecord(ev[1], st));
     ctx->sto_valid = false;
-    HIP_TRY(launch_gemm(dtype, true, stored, !cached, A, B, C, sh, *w, arm, v.counts, st));
+    HIP_TRY(launch_gemm(dtype, true, stored, !cached, A, B, C, sh, *w, arm, v.counts, one ? &end : nullptr, st));
     if (ctx->done_event && !gm) HIP_TRY(hipEventRecord(ctx->done_event, st));
     if (ev) HIP_TRY(hipEventRecord(ev[2], st));
-    auto check = [&](uint32_t *z, size_t zw, uint32_t *z2, size_t z2w) {
-        return launch_check(dtype, fast, rc_ready, A, B, sh, *w, v, z, zw, z2, z2w, st);
-    };
-    if (gm) {
-        HIP_TRY(check(nullptr, 0, nullptr, 0));
-        ctx->dirty[ctx->cur] = w->zero_words;
-    } else {
-        const size_t prev_dirty = ctx->dirty[prev];
-        ctx->dirty[prev] = ctx->region_words;
-        // the check kernel also cleans the b slot that is not in use (for the next pass over B)
-        const int other = ctx->bslot ^ 1;
-        uint32_t *other_base = ctx->pool_depth + (size_t)other * ctx->bslot_words;
-        HIP_TRY(check(prev_base, prev_dirty, ctx->bclean[other] ? nullptr : other_base, ctx->bslot_words));
-        ctx->bclean[other] = true;
+    if (!one)
+        HIP_TRY(launch_check(dtype, fast, rc_ready, A, B, sh, *w, v, end.zero_ptr, end.zero_words, end.zero2_ptr, end.zero2_words, st));
+    if (!gm) {
+        ctx->bclean[ctx->bslot ^ 1] = true;
         ctx->dirty[prev] = 0;
-        ctx->dirty[ctx->cur] = w->zero_words;
     }
+    ctx->dirty[ctx->cur] = w->zero_words;
     if (ev) HIP_TRY(hipEventRecord(ev[3], st));
     return ABFT_OK;
 }
@@ -540,7 +551,7 @@ static int gemm_impl(abft_ctx *ctx, const void *A, const void *B, const void *bi
         ctx->arm.batch = -1;
         hipEvent_t *ev = (ctx->prof_ev && ctx->prof_n < ctx->prof_cap) ? ctx->prof_ev + 4 * ctx->prof_n : nullptr;
         if (ev) { HIP_TRY(hipEventRecord(ev[0], st)); HIP_TRY(hipEventRecord(ev[1], st)); }
-        HIP_TRY(launch_gemm(dtype, false, false, false, A, B, C, sh, w, arm, nullptr, st));
+        HIP_TRY(launch_gemm(dtype, false, false, false, A, B, C, sh, w, arm, nullptr, nullptr, st));
         if (ctx->done_event && !capturing(st)) HIP_TRY(hipEventRecord(ctx->done_event, st));
         if (ev) { HIP_TRY(hipEventRecord(ev[2], st)); HIP_TRY(hipEventRecord(ev[3], st)); ctx->prof_n++; }
         return ABFT_OK;

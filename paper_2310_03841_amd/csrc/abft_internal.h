@@ -43,6 +43,7 @@ struct Workspace {
     //   cc_obs [batch][N] | rc_obs [batch][M] | rc_pred [batch][M] | a_sum [batch][K] | a_max [batch]
     //   | cc_sto [batch][N] | rc_sto [batch][M] | c_max [batch]
     //   | cc_acc [batch][N] | rc_acc [batch][M] (doubles; general kernel, floating point)
+    //   | cc_pacc [batch][N] | rc_pacc [batch][M] | s_pacc [batch] (doubles) | tickets (problems of one launch)
     uint32_t *cc_obs, *rc_obs;      // observed sums of C (epilogue)
     uint32_t *rc_pred;              // A (B e), from the operand slabs of A in LDS or by the check kernel
     uint32_t *a_sum;                // a = e^T A, from the same slabs or by workgroups beside the tiles
@@ -51,6 +52,10 @@ struct Workspace {
     uint32_t *c_max;                // max|C as stored| (float bits) [batch], formed with them
     double *cc_acc, *rc_acc;        // observed sums of C while the tiles add to them; the check kernel
                                     // rounds them into cc_obs, rc_obs
+    // problems of one launch (gemm_one_launch), behind cc_acc, rc_acc (integers: in their place):
+    double *cc_pacc, *rc_pacc;      // the predictions while workgroups add their shares (integers: words)
+    double *s_pacc;                 // the same of the scalar a.b
+    uint32_t *tickets;
     size_t zero_words;              // words from cc_obs on
     uint32_t *cc_vobs, *rc_vobs;    // re-summed from stored C
     // correction
@@ -100,12 +105,29 @@ int protect_max_k(int dt);
 bool gemm_takes_fast(int dt, const Shape &s);
 // Whether the general kernel, protected, reduces A from the slabs it holds (a pass over B ahead of it, A b with it).
 bool gemm_fuses_a(int dt, const Shape &s);
+// Whether a protected call of the problem is one launch of the general kernel: both predictions and the
+// comparison inside it (predict_pass.h).
+// Returns the words of its tickets, 0: it is not.
+size_t gemm_one_launch(int dt, const Shape &s);
+// Most rows of C, and most columns, over all batch items, and most batch items of such a problem.
+constexpr int64_t ONE_LAUNCH_MAX_LEN = 16384, ONE_LAUNCH_MAX_BATCH = 64;
+// Most tile rows and tile columns over all batch items, and most words of tickets.
+constexpr int ONE_LAUNCH_MAX_UNITS = 320;
+constexpr size_t ONE_LAUNCH_TICKET_WORDS = (1 + (size_t)ONE_LAUNCH_MAX_BATCH + ONE_LAUNCH_MAX_UNITS) * 16;
+// What such a launch takes besides: where the verdict goes, and regions its workgroups help to clear.
+struct OneLaunch {
+    Verdict v;
+    uint32_t *zero_ptr, *zero2_ptr;
+    size_t zero_words, zero2_words;
+};
 // protect: A-side checksums and observed sums are produced by the kernel (atomics into the
 // zeroed region of the workspace); launch_check turns them into flags.
 // stored_sums: also accumulate the row / column sums of the rounded values that are stored
 // encode_b: general kernel, protected: form b and max|B| too; counts: protected: cleared for launch_check
+// one: gemm_one_launch problems, protected; then no launch_check
 hipError_t launch_gemm(int dt, bool protect, bool stored_sums, bool encode_b, const void *A, const void *B, void *C,
-                       const Shape &s, const Workspace &w, const InjectArm &arm, uint32_t *counts, hipStream_t st);
+                       const Shape &s, const Workspace &w, const InjectArm &arm, uint32_t *counts, const OneLaunch *one,
+                       hipStream_t st);
 // behind the GEMM kernel (after_fast: the fast one): the predictions that are missing, comparisons, flags
 // and counts.  zero_ptr / zero_words: regions every block of the kernel helps to clear (may be null / 0)
 hipError_t launch_check(int dt, bool after_fast, bool rc_ready, const void *A, const void *B, const Shape &s, const Workspace &w, const Verdict &v,

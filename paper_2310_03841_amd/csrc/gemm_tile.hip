@@ -4,12 +4,14 @@
 // "Optimizations" (2)).
 //
 // What bounds these problems is not arithmetic or bandwidth but the chain of latencies of a call.
-// So the input-side vectors a = e^T A and b = B e, which depend on nothing, are formed by extra
-// workgroups of the same launch, beside the tiles, instead of by a kernel of their own ahead of it;
-// both predictions wait for the check kernel behind the launch (check_kernel, aux_kernels.hip).  A
-// call is two launches whatever is cached.  Large protected problems keep the older way, a pass over B
-// first and A reduced from the slabs in LDS (fuses_a below).  (Before: pass over B, GEMM with the pass over A inside
-// its main loop, finish; 197 x 768 x 768 int8 25.4 us, of which 5.2 + 14.0 + 7.8 in the kernels.)
+// A call of few tiles is therefore one launch (predict_pass.h): workgroups beside the tiles form both predictions, and who
+// is last compares.  Call after call, in us, two launches / one: int8 197 x 768 x 768 10.1 / 7.7, bf16 197 x 3072 x 768 13.1 /
+// 10.6, 197 x 768 x 3072 18.0 / 15.3, int8 3000 x 128 x 1024 15.2 / 9.2.  (A call takes 3 us before its first and after its
+// last workgroup; a second kernel adds that gap, a trip to memory and a reduction.)
+// More tiles, or predictions that would take longer than they: the input-side vectors a = e^T A and b = B e, which depend
+// on nothing, are formed by extra workgroups of the same launch, beside the tiles; both predictions wait for the check
+// kernel behind it (check_kernel, aux_kernels.hip).  Large protected problems: a pass over B
+// first and A reduced from the slabs in LDS (fuses_a below).
 //
 // Tile: BM x BN by four waves of (BM/2) x (BN/2), 32 x 32 MFMA blocks.  K advances in slabs of 128
 // bytes per row of A.  Slabs go from global memory straight into LDS (global_load_lds_dwordx4),
@@ -26,11 +28,14 @@
 //
 // Edges: rows and columns past the problem fetch the last valid ones; what they produce is never
 // stored or summed.  Past the end of K the fragments of the last slab are cleared in registers.
+#include <algorithm>
+
 #include "abft_device.h"
 #include "encode_pass.h"
 #include "gemm_apass.h"
 #include "gemm_args.h"
 #include "gemm_epilogue.h"
+#include "predict_pass.h"
 
 namespace abft {
 
@@ -46,7 +51,8 @@ struct TileArgs {
     uint32_t *counts;             // protected: cleared here, completed by the check kernel
     uint32_t *bias_sum;           // protected, with a bias: its sum, formed by one more workgroup
     int fuse_bm;                  // host: rows of a tile of the instantiations with APASS, 0: the others
-    int aux_off;                  // APASS: where the words of b and of a begin in LDS
+    int aux_off;                  // APASS: where the words of b and of a begin in LDS; ONE: the words of the predictions
+    PredArgs p;                   // ONE
 };
 
 constexpr int TILE_STAGE_ROW = 36;                               // words per staged row of a 32 x 32 block (32 + pad)
@@ -66,7 +72,8 @@ template <int ES, int ROWB> __device__ __forceinline__ int kn_swizzle(int k)
     else return ROWB == 64 ? ((k >> 2) & 1) << 1 : ((k >> 1) & 3) << 1;                  // 16-byte pieces of 8 rows
 }
 
-template <int DT, int BM, int BN, int NS, bool PROT, bool TRANSB, bool APASS>
+// ONE: the whole protected call (predict_pass.h)
+template <int DT, int BM, int BN, int NS, bool PROT, bool TRANSB, bool APASS, bool ONE>
 __global__ __launch_bounds__(256) void gemm_tile_kernel(TileArgs a)
 {
     using T = Traits<DT>;
@@ -83,7 +90,19 @@ __global__ __launch_bounds__(256) void gemm_tile_kernel(TileArgs a)
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
     const GemmArgs &g = a.g;
     const int bz = blockIdx.y;
-    if (PROT) {
+    if constexpr (ONE) {
+        // The arguments that the end of the call needs, a few lines of them, are asked for here: a scalar load that
+        // misses in the middle of the chain at the end costs half a microsecond.
+        asm volatile("" :: "s"(a.g.cc_acc), "s"(a.g.bias), "s"(a.p.rc_pacc), "s"(a.p.tickets), "s"(a.p.cc_acc), "s"(a.p.tau), "s"(a.p.counts));
+        const size_t first = (size_t)bz * a.p.wgs + blockIdx.x, nw = (size_t)a.p.wgs * a.p.batch;
+        for (size_t i = first * 256 + threadIdx.x; i < a.p.zero_words; i += nw * 256) a.p.zero_ptr[i] = 0u;
+        for (size_t i = first * 256 + threadIdx.x; i < a.p.zero2_words; i += nw * 256) a.p.zero2_ptr[i] = 0u;
+        if ((int)blockIdx.x < a.n_extra) {
+            predict_block<DT, TRANSB>(a.p, blockIdx.x, bz, smem, a.aux_off);
+            end_predict<DT>(a.p, blockIdx.x, a.n_extra, bz, reinterpret_cast<uint32_t *>(smem));
+            return;
+        }
+    } else if (PROT) {
         if (blockIdx.x == 0 && bz == 0 && threadIdx.x < 5) a.counts[threadIdx.x] = 0u;
         const int e = blockIdx.x;
         if (e < a.n_extra) {
@@ -516,17 +535,18 @@ __global__ __launch_bounds__(256) void gemm_tile_kernel(TileArgs a)
             if (APASS && !g.a_given && tid == 64) publish(g.a_max, 4);
         }
     }
+    if constexpr (ONE) end_tile<DT, BM, BN>(a.p, tm, tn, bz, reinterpret_cast<uint32_t *>(smem));
 }
 
 // ------------------------------------------------------------------------------------------
 static int slabs_of(int dt, int K) { return (int)(((long)K * elem_size(dt) + SLAB_BYTES - 1) / SLAB_BYTES); }
 
-template <int DT, int BM, int BN, int NS, bool PROT, bool TRANSB, bool APASS = false>
+template <int DT, int BM, int BN, int NS, bool PROT, bool TRANSB, bool APASS = false, bool ONE = false>
 static hipError_t launch_one(TileArgs &a, int batch, hipStream_t st)
 {
-    constexpr int smem_max = APASS ? 160 * 1024 : tile_lds_bytes(BM, BN, NS);
+    constexpr int smem_max = APASS || ONE ? 160 * 1024 : tile_lds_bytes(BM, BN, NS);
     static_assert(tile_lds_bytes(BM, BN, 1) >= 256 * 16 * 4, "the passes over A and B use 16 KB");
-    auto kern = gemm_tile_kernel<DT, BM, BN, NS, PROT, TRANSB, APASS>;
+    auto kern = gemm_tile_kernel<DT, BM, BN, NS, PROT, TRANSB, APASS, ONE>;
     if (smem_max > 48 * 1024) {
         hipError_t e = ensure_max_lds(reinterpret_cast<const void *>(kern), smem_max);
         if (e != hipSuccess) return e;
@@ -536,6 +556,13 @@ static hipError_t launch_one(TileArgs &a, int batch, hipStream_t st)
     int smem = tile_lds_bytes(BM, BN, nslab < NS ? nslab : NS);
     a.aux_off = smem;
     if (APASS) smem += (int)apass_lds_bytes(DT, nslab, a.g.tiles_n);
+    if (ONE) {
+        const int pieces = (a.p.a_steps + a.p.b_steps) * PRED_STEP_BYTES;
+        a.aux_off = pieces > 256 * 16 * 4 ? pieces : 256 * 16 * 4;
+        smem = std::max(smem, a.aux_off + PRED_VEC_WORDS * 4);
+        a.p.wgs = a.n_extra + a.n_tiles;
+        a.p.tiles_m = a.g.tiles_m; a.p.tiles_n = a.g.tiles_n; a.p.bm = BM; a.p.bn = BN;
+    }
     dim3 grid((unsigned)(a.n_extra + a.n_tiles), (unsigned)batch, 1);
     hipLaunchKernelGGL(kern, grid, dim3(256), smem, st, a);
     return hipGetLastError();
@@ -619,6 +646,9 @@ static hipError_t launch_cfg(bool protect, bool transB, TileArgs &a, int batch, 
     if constexpr (BN == 128)
         if (a.fuse_bm) return transB ? launch_one<DT, BM, BN, NS, true, true, true>(a, batch, st)
                                      : launch_one<DT, BM, BN, NS, true, false, true>(a, batch, st);
+    if constexpr (BM == 64)
+        if (a.p.one_launch) return transB ? launch_one<DT, BM, BN, NS, true, true, false, true>(a, batch, st)
+                                          : launch_one<DT, BM, BN, NS, true, false, false, true>(a, batch, st);
     if (protect) return transB ? launch_one<DT, BM, BN, NS, true, true>(a, batch, st)
                                : launch_one<DT, BM, BN, NS, true, false>(a, batch, st);
     return transB ? launch_one<DT, BM, BN, NS, false, true>(a, batch, st)
@@ -691,8 +721,101 @@ static EncArgs enc_args(const void *X, long ld, long stride, int rows, int cols,
     return e;
 }
 
+// How a problem's predictions are dealt to workgroups (predict_pass.h): the operand that is split and its blocks, so that
+// the estimate is least.  Returns that, in us; negative: it does not fit max_steps steps of LDS.  A step of a wave is an LDS
+// read, MFMAs and their sums, twice; of a B stored K x N, vector instructions; and the shares of all workgroups
+// meet in the same lines, where they queue (f16 4640 x 105 x 320 with 280 workgroups 22.1 us, 11.9 in two launches;
+// int8 237 x 2112 x 2112 with 264 / 99 workgroups 23.0 / 10.7).
+constexpr double PRED_STEP_US = 0.6, PRED_KN_STEP_US = 0.9, PRED_QUEUE_US = 0.02;
+constexpr int PRED_MAX_WGS = 512;
+// Additions of a launch, in doubles or words: with more, the tiles' own wait behind them (bf16 704 x 640 x 1709, 142 k:
+// 17.6 us, 14.8 in two launches; 197 x 768 x 3072, 111 k: 15.3 / 18.0).
+constexpr double PRED_MAX_ADDS = 115e3, PRED_MAX_ADDS_INT = 200e3;
+static double pred_plan(int dt, const Shape &s, int max_steps, PredArgs *p)
+{
+    const int ce = 16 / elem_size(dt), kr = PRED_CHUNKS * ce;
+    auto steps = [](int n, int per) { return (n + per - 1) / per; };
+    const int nkr = steps(s.K, kr), pieces = steps(s.N, ce);
+    double best = -1.0;
+    auto offer = [&](int split_b, int units, int nblk, int whole, int split, int wa, int w_log2, double chain) {
+        const int len = steps(units, nblk);
+        nblk = steps(units, len);
+        if (whole + split > max_steps || nkr * nblk > PRED_MAX_WGS) return;
+        const double adds = (double)s.batch * nkr * (split_b ? (double)nblk * s.M + s.N : (double)nblk * s.N + s.M);
+        const double cost = chain + PRED_QUEUE_US * nkr * nblk;
+        if (adds > (dt == DT_I8 ? PRED_MAX_ADDS_INT : PRED_MAX_ADDS) || (best >= 0.0 && cost >= best)) return;
+        best = cost;
+        p->nkr = nkr; p->nblk = nblk; p->split_b = split_b; p->blk_len = len;
+        p->a_steps = split_b ? whole : split;
+        p->b_steps = split_b ? split : whole;
+        p->waves_a = wa; p->w_log2 = w_log2;
+    };
+    // steps of a K x N operand over c pieces of columns: a power of two of pieces of kr rows
+    auto kn_log2 = [](int c) {
+        int lg = 3;
+        while ((1 << lg) < c) ++lg;
+        return lg;
+    };
+    const int a_all = steps(s.M, 64);
+    for (int nblk = 1; nblk <= 64; nblk += nblk < 8 ? 1 : 4) {
+        if (s.transB) {
+            const int split_b = s.N >= s.M, big = std::max(s.M, s.N);
+            if (nblk > steps(big, 64)) break;
+            const int whole = steps(std::min(s.M, s.N), 64), split = steps(steps(big, nblk), 64);
+            for (int w = 1; w <= 3; ++w)                     // waves on the whole operand
+                offer(split_b, big, nblk, whole, split, split_b ? w : 4 - w, 3,
+                      PRED_STEP_US * std::max(steps(whole, w), steps(split, 4 - w)));
+        } else {
+            if (nblk <= steps(pieces, 8) && steps(pieces, nblk) <= 256) {
+                const int lg = kn_log2(steps(pieces, nblk)), b = std::max(1, (kr << lg) / 256);
+                offer(1, pieces, nblk, a_all, b, 4, lg, PRED_STEP_US * steps(a_all, 4) + PRED_KN_STEP_US * b);
+            }
+            if (nblk <= a_all && pieces <= 256) {
+                const int lg = kn_log2(pieces), b = std::max(1, (kr << lg) / 256), a = steps(steps(s.M, nblk), 64);
+                offer(0, s.M, nblk, b, a, 4, lg, PRED_STEP_US * steps(a, 4) + PRED_KN_STEP_US * b);
+            }
+        }
+    }
+    return best;
+}
+
+// Steps of LDS a workgroup of the predictions takes at most: what fits the LDS of the tiles beside it.
+static int pred_max_steps(int bm, int bn, int ns) { return (tile_lds_bytes(bm, bn, ns) - PRED_VEC_WORDS * 4) / PRED_STEP_BYTES; }
+
+// One launch, unless the predictions take longer than the tiles by more than the check kernel behind two launches costs.  Of
+// 400 problems (linear layers of up to 2200 tiles, up to 63 attention items, three types, both layouts of B) it takes 196, which
+// then take 0.84 of their time (0.59 to 1.12, five of them more than 1.05).  Batches of more workgroups than are resident at once
+// lose by it (bf16 151 x 80 x 151, 41 items 11.3 -> 12.6 us).
+constexpr int ONE_LAUNCH_MAX_TILES = 512, ONE_LAUNCH_MAX_BATCH_WGS = 440;
+static bool one_launch_plan(int dt, const Shape &s, PredArgs *p, int *units)
+{
+    if (gemm_takes_fast(dt, s) || s.batch > ONE_LAUNCH_MAX_BATCH || (long)s.batch * s.M > ONE_LAUNCH_MAX_LEN ||
+        (long)s.batch * s.N > ONE_LAUNCH_MAX_LEN)
+        return false;
+    int bm, bn;
+    const int nslab = slabs_of(dt, s.K);
+    if (fuses_a(dt, s, nslab, &bm)) return false;
+    tile_size(s.M, s.N, nslab, s.batch, true, &bm, &bn);
+    if (bm != 64) return false;
+    const long tiles = tiles_of(s.M, s.N, s.batch, bm, bn);
+    *units = ((s.M + bm - 1) / bm + (s.N + bn - 1) / bn) * s.batch;
+    if (tiles > ONE_LAUNCH_MAX_TILES || *units > ONE_LAUNCH_MAX_UNITS) return false;
+    p->nkr = p->nblk = 0;
+    const double pred = pred_plan(dt, s, pred_max_steps(bm, bn, bn == 64 && tiles <= 256 ? 4 : 3), p);
+    if (s.batch > 1 && tiles + (long)s.batch * p->nkr * p->nblk > ONE_LAUNCH_MAX_BATCH_WGS) return false;
+    return pred >= 0.0 && pred <= 0.28 * nslab + (s.transB ? 2.0 : 1.2);
+}
+
+size_t gemm_one_launch(int dt, const Shape &s)
+{
+    PredArgs p;
+    int units;
+    return one_launch_plan(dt, s, &p, &units) ? (size_t)(unit_line0(s.batch) + units) * TICKET_LINE : 0;
+}
+
 hipError_t launch_gemm(int dt, bool protect, bool stored_sums, bool encode_b, const void *A, const void *B, void *C,
-                       const Shape &s, const Workspace &w, const InjectArm &arm, uint32_t *counts, hipStream_t st)
+                       const Shape &s, const Workspace &w, const InjectArm &arm, uint32_t *counts, const OneLaunch *one,
+                       hipStream_t st)
 {
     // The unprotected item kernels do not look for an armed flip (in them the look cost bf16 400 x 400 x 80,
     // 256 items 24.4 -> 25.0 us): such a call is tiled, C comes out bit for bit the same.
@@ -728,6 +851,28 @@ hipError_t launch_gemm(int dt, bool protect, bool stored_sums, bool encode_b, co
     a.n_enc_a = (protect && !w.a_given && !a.fuse_bm) ? a.ea.nwin * a.ea.nrb : 0;
     a.n_enc_b = (protect && encode_b && !a.fuse_bm) ? a.eb.nwin * a.eb.nrb : 0;
     a.n_extra = a.n_enc_a + a.n_enc_b + (protect && w.bias && !a.fuse_bm ? 1 : 0);
+    PredArgs &p = a.p;
+    int units = 0;
+    p.one_launch = protect && one && one_launch_plan(dt, s, &p, &units) ? 1 : 0;
+    if (p.one_launch) {
+        p.A = g.A; p.B = g.B;
+        p.lda = s.lda; p.ldb = s.ldb; p.sA = s.sA; p.sB = s.sB;
+        p.M = s.M; p.N = s.N; p.K = s.K; p.batch = s.batch;
+        p.a_given = g.a_given; p.b_given = encode_b ? 0 : 1;
+        p.a_vec = w.a_given;
+        p.a_sum = w.a_sum; p.b_sum = w.b_sum; p.a_max = w.a_max; p.b_max = w.b_max;
+        p.cc_pacc = w.cc_pacc; p.rc_pacc = w.rc_pacc; p.s_pacc = w.s_pacc;
+        p.tickets = w.tickets;
+        p.amax_in = (w.a_given && w.amax_given) ? w.amax_given : w.a_max;
+        p.cc_obs = w.cc_obs; p.rc_obs = w.rc_obs; p.cc_acc = w.cc_acc; p.rc_acc = w.rc_acc;
+        p.bias = w.bias;
+        p.cc_pred = w.cc_pred; p.rc_pred = w.rc_pred; p.s_pred = w.s_pred; p.maxabs = w.maxabs; p.tau = w.tau;
+        p.tau_override = one->v.tau_override; p.tau_override_cols = one->v.tau_override_cols;
+        p.row_flag = one->v.row_flag; p.col_flag = one->v.col_flag; p.counts = one->v.counts;
+        p.zero_ptr = one->zero_ptr; p.zero_words = one->zero_words;
+        p.zero2_ptr = one->zero2_ptr; p.zero2_words = one->zero2_words;
+        a.n_extra = p.nkr * p.nblk + (p.bias ? 1 : 0);
+    }
     switch (dt) {
     case DT_I8:   return launch_tile<DT_I8>(protect, s.transB != 0, a, s.batch, st);
     case DT_BF16: return launch_tile<DT_BF16>(protect, s.transB != 0, a, s.batch, st);

@@ -1646,6 +1646,69 @@ def test_general_kernel_tile_shapes(dtype, M, N, K, batch, trans_b):
         ab.abft_destroy(ctx)
 
 
+# (M, N, K, batch, trans_b): calls of one launch, where the workgroups that form the predictions end: their 64 rows,
+# 64 bytes of K, waves, blocks of the operand that is split, and steps over a B stored K x N
+ONE_LAUNCH_EDGES = [
+    (1, 64, 16, 1, True),
+    (65, 129, 130, 1, True),
+    (64, 2049, 97, 1, True),        # B in blocks
+    (1300, 70, 700, 1, True),       # A in blocks
+    (197, 768, 1540, 1, True),      # many ranges of K, the last of a few bytes
+    (33, 65, 100, 17, True),        # more items than first-level tickets
+    (64, 200, 1100, 1, False),
+    (300, 40, 1500, 1, False),      # narrow, A in blocks
+    (64, 1030, 900, 1, False),      # wide
+    (50, 48, 390, 18, False),
+]
+
+
+@pytest.mark.parametrize("dtype", ["i8", "bf16", "f16"])
+@pytest.mark.parametrize("M,N,K,batch,trans_b", ONE_LAUNCH_EDGES)
+def test_one_launch_edges(dtype, M, N, K, batch, trans_b):
+    """C, every checksum vector, flags and counts against the oracle, twice in a row (the second call finds what the
+    first has cleared)."""
+    ctx = ab.abft_create(max_rows=batch * M, max_cols=batch * N, max_depth=batch * (K + 127), max_batch=batch)
+    try:
+        _clean_case(ctx, dtype, M, N, K, batch, trans_b)
+        _clean_case(ctx, dtype, M, N, K, batch, trans_b)
+    finally:
+        ab.abft_destroy(ctx)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("value", [np.inf, np.nan])
+@pytest.mark.parametrize("where", ["A", "B"])
+@pytest.mark.parametrize("M,N,K,trans_b", [(70, 200, 300, True), (150, 72, 300, False)])
+def test_one_launch_keeps_non_finite_values_apart(ctx, dtype, value, where, M, N, K, trans_b):
+    """One Inf or NaN in an operand: its own row (column) of C is flagged and no other is, and the operand's sums over its
+    other columns are those of the run without it (A's whole predictions of other rows too)."""
+    A, B = gen.gen_operands(dtype, M, N, K, 51, 52, trans_b=trans_b, batch=1)
+    run = Run(ctx, dtype, A, B, trans_b)
+    run.gemm()
+    assert run.cnt()[2] == ab.ABFT_CLEAN
+    sums = ab.ABFT_WS_A_SUM if where == "A" else ab.ABFT_WS_B_SUM
+    before, rc = run.ws(sums)[0].copy(), run.ws(ab.ABFT_WS_RC_PRED)[0].copy()
+    i, k = 37, 131
+    bits = {("bf16", False): 0x7F80, ("bf16", True): 0x7FC0, ("f16", False): 0x7C00, ("f16", True): 0x7E00}
+    d = run.dA if where == "A" else run.dB
+    d[(0, i, k) if where == "A" or trans_b else (0, k, i)] = bits[dtype, bool(np.isnan(value))]
+    run.gemm()
+    rf, cf = run.flags()
+    own, other = (rf[0], cf[0]) if where == "A" else (cf[0], rf[0])
+    rest = np.arange(len(own)) != i
+    assert own[i] and not own[rest].any() and other.all()
+    after = run.ws(sums)[0]
+    keep = np.arange(K) != k
+    # the same fp32 values in another order
+    assert not np.isfinite(after[k])
+    assert np.max(np.abs(after[keep] - before[keep])) <= 1e-5 * np.max(np.abs(before)) + 1e-5
+    if where == "A":
+        assert np.max(np.abs(run.ws(ab.ABFT_WS_RC_PRED)[0][rest] - rc[rest])) <= 1e-5 * K
+    # max|.| takes Inf and passes over NaN
+    top = run.ws(ab.ABFT_WS_MAXABS)[0][0 if where == "A" else 1]
+    assert np.isinf(top) if np.isinf(value) else np.isfinite(top)
+
+
 # (M, N, K, batch, trans_b): one workgroup per item, where its kernels' blocks, rings and chunks end
 ITEM_EDGES = [
     (300, 128, 96, 64, True),       # the widest item whose waves own rows; two blocks of rows for some waves
