@@ -5,8 +5,9 @@
 // A (B e) (the row checksum prediction).  Both read every element of A exactly once, and every
 // element of A passes through LDS on its way to the matrix cores anyway: of the workgroups that
 // share a tile row, the one in tile column (s mod tiles_n) reduces slab s while it is resident.
-// So A is read from memory once, by the GEMM.  The fast kernel does it always, the general one for large
-// problems (small ones form the checksums beside their tiles: encode_pass.h).
+// So A is read from memory once, by the GEMM.  The fast kernel does it unless its tiles leave compute units
+// idle (those then run a_beside below), the general one for large problems (small ones form the
+// checksums beside their tiles: encode_pass.h).
 //
 // LDS slab layout (both GEMM kernels): row r is 128 bytes = eight 16-byte chunks, chunk c stored
 // in slot c ^ ((r >> 1) & 7).  Thread t reduces chunk c = t & 7 of rows (t >> 3) + 32 p.
@@ -291,5 +292,92 @@ template <int DT, int BM, bool GIVEN> struct APassSteps {
         }
     }
 };
+
+// The same reductions by a workgroup of its own, for a launch whose tiles leave compute units idle: rows
+// rb * rpb .. of A, a window of 2^cw_log2 16-byte chunks along K.  A thread keeps one chunk column (its values of b
+// and its column sums stay in registers) and takes UN consecutive rows at a time, all UN loads in flight:
+// 64 KB per compute unit, bound by the latency of memory and not by the 40-odd vector instructions per
+// chunk.  smem: 256 * (16 / element size) words.  K is a whole number of slabs: no chunk is cut.
+template <int DT>
+__device__ __forceinline__ void a_beside(const GemmArgs &g, int blk, uint8_t *smem)
+{
+    using T = Traits<DT>;
+    typedef typename T::acc_t acc_t;
+    constexpr int CE = 16 / T::ES, UN = 16;
+    const int per_item = g.beside.nwin * g.beside.nrb;
+    const int bz = blk / per_item, in_item = blk - bz * per_item;
+    const int rb = in_item / g.beside.nwin, win = in_item - rb * g.beside.nwin;
+    const int tid = threadIdx.x;
+    const int CW = 1 << g.beside.cw_log2, RL = 256 >> g.beside.cw_log2;
+    const int cx = tid & (CW - 1), ry = tid >> g.beside.cw_log2;
+    const int col0 = (win * CW + cx) * CE;
+    const bool colok = col0 < g.K;
+    const uint8_t *src = g.A + ((long)bz * g.sA + (colok ? col0 : 0)) * T::ES;
+    const int rbeg = rb * g.beside.rpb, rend = min(rbeg + g.beside.rpb, g.M);
+    const long ldb = g.lda * T::ES;
+
+    acc_t bv[CE], cs[CE];
+#pragma unroll
+    for (int e = 0; e < CE; ++e) {
+        bv[e] = colok ? from_word<acc_t>(g.b_sum[(long)bz * g.K + col0 + e]) : T::zero();
+        cs[e] = T::zero();
+    }
+    float amax = 0.f;
+    for (int r0 = rbeg; r0 < rend; r0 += RL * UN) {
+        const int rt = r0 + ry * UN;                            // this thread's rows: rt .. rt + UN
+        i32x4 v[UN];
+#pragma unroll
+        for (int u = 0; u < UN; ++u) {
+            const int r = min(rt + u, g.M - 1);                 // loads without a branch: rows past the end are cleared below
+            v[u] = *reinterpret_cast<const i32x4 *>(src + (long)r * ldb);
+        }
+        acc_t part[CE], m0 = T::zero(), m1 = T::zero();         // the batch's column sums; dots of rows cx and cx + 8
+#pragma unroll
+        for (int e = 0; e < CE; ++e) part[e] = T::zero();
+#pragma unroll
+        for (int u = 0; u < UN; ++u) {
+            i32x4 x4 = v[u];
+            if (!colok || rt + u >= rend) x4 = i32x4{0, 0, 0, 0};
+            acc_t dot = T::zero();
+#pragma unroll
+            for (int e = 0; e < CE; ++e) {
+                const acc_t x = T::elem(x4, e);
+                part[e] = add_t(part[e], x);
+                if constexpr (T::IS_INT) {
+                    dot += __mul24((int)x, (int)bv[e]);         // |b| < 2^23 (gemm_fast_eligible)
+                } else {
+                    dot = __builtin_fmaf((float)x, (float)bv[e], (float)dot);
+                    amax = fmaxf(amax, fabsf((float)x));
+                }
+            }
+            dot = seg_sum(dot, CW);
+            if (cx == (u & 7)) { if (u < 8) m0 = dot; else m1 = dot; }
+        }
+#pragma unroll
+        for (int e = 0; e < CE; ++e) cs[e] = add_t(cs[e], part[e]);
+        if (cx < 8) {
+            uint32_t *d = g.rc_pred + (long)bz * g.M + rt + cx;
+            if (rt + cx < rend) atomic_add_word(d, m0);
+            if (rt + cx + 8 < rend) atomic_add_word(d + 8, m1);
+        }
+    }
+    if (g.a_given) return;
+    acc_t *red = reinterpret_cast<acc_t *>(smem);
+#pragma unroll
+    for (int e = 0; e < CE; ++e) red[(ry * CW + cx) * CE + e] = cs[e];
+    __syncthreads();
+    for (int c = tid; c < CW * CE; c += 256) {
+        const int k = win * CW * CE + c;
+        if (k < g.K) {
+            acc_t t = red[c];
+            for (int y = 1; y < RL; ++y) t = add_t(t, red[y * CW * CE + c]);
+            atomic_add_word(g.a_sum + (long)bz * g.K + k, t);
+        }
+    }
+    if constexpr (!T::IS_INT) {
+        amax = wave_max(amax);
+        if ((tid & 63) == 0 && amax > 0.f) atomicMax(g.a_max + bz, __float_as_uint(amax));
+    }
+}
 
 }  // namespace abft

@@ -5,6 +5,9 @@
 
 namespace abft {
 
+// Fast path: workgroups behind the tiles that reduce A (n = nwin * nrb * batch; 0: the tiles do it).
+struct BesideArgs { int n, cw_log2, nwin, nrb, rpb; };
+
 struct GemmArgs {
     const uint8_t *A, *B;
     uint8_t *C;
@@ -27,6 +30,7 @@ struct GemmArgs {
     const uint32_t *bias;                         // layer bias [N] (float / int32 words) or null
     const uint32_t *b_sum;                        // B e, complete before the launch [batch][K]
     uint32_t *counts;                             // fast kernel, protected: cleared for the check kernel
+    BesideArgs beside;
 };
 
 // Workgroup -> tile inside a region of tiles_m x tiles_n tiles: consecutive ids of one XCD

@@ -18,6 +18,7 @@
 #include <vector>
 
 #include "abft_device.h"
+#include "encode_pass.h"
 #include "gemm_args.h"
 #include "gemm_epilogue.h"
 
@@ -177,8 +178,9 @@ __device__ __forceinline__ void fast_tile(const GemmArgs &g, uint8_t *smem, int 
     ep.col_stride = 0;
     {
         const int nslab = K / KE;                      // at least 3 (gemm_fast_eligible)
-        int next_own = tn;
-        const int owned = (PROT && tn < nslab) ? (nslab - tn + g.tiles_n - 1) / g.tiles_n : 0;
+        // (workgroups beside the tiles reduce A: none of the slabs is this tile's)
+        int next_own = PROT && g.beside.n ? nslab : tn;
+        const int owned = (PROT && next_own < nslab) ? (nslab - tn + g.tiles_n - 1) / g.tiles_n : 0;
         // column sums: one set of owned * KE words per wave (plain stores, added up by the epilogue)
         ep.col_stride = owned * KE;
         uint32_t *col_mine = col_lds + wave * owned * KE;
@@ -324,7 +326,12 @@ __global__ __launch_bounds__(256) void gemm_fast_kernel(GemmArgs g)
     // the matrix pipes at different times.  Measured on 12608 x 3072 x 768: 63 -> 60.5 us.
     const int per_item = g.n_small + g.n_big;
     const int total = per_item * g.batch;
-    for (int t = blockIdx.x; t < total; t += gridDim.x) {
+    const int n_tile = PROT ? (int)gridDim.x - g.beside.n : (int)gridDim.x;
+    if (PROT && (int)blockIdx.x >= n_tile) {
+        a_beside<DT>(g, (int)blockIdx.x - n_tile, smem);
+        return;
+    }
+    for (int t = blockIdx.x; t < total; t += n_tile) {
         const int bz = t / per_item, bid = t - bz * per_item;
         int tm, tn;
         if (bid >= g.n_small) {
@@ -394,11 +401,41 @@ static int choose_big_rows(int M, int tiles_n, int batch, int ncu)
     return best;
 }
 
+// Workgroups that reduce A on the `idle` compute units the tiles of a single round leave (a_beside).  Windows of 8
+// to 64 chunks along K (least padding, then widest), the rows dealt to as many row blocks as fit.  The tiles
+// are then free of their owned slabs, but their first slabs queue behind this pass's loads: about 1 us lost, against 0.5 us
+// (int8 1 us) for each owned slab.  Measured against tiles that reduce A, us: f16 6304 x 768 x 3072 (16 owned of 48 slabs)
+// 54.4 -> 52.0, 10870 x 896 x 2688 bf16 81.9 -> 75.2, int8 5099 x 896 x 2176 37.1 -> 32.7, 6422 x 1536 x 2688 47.5 -> 42.6; where K is
+// short or shared by many tile columns it lost: f16 6783 x 704 x 832 37.8 -> 38.4, 2788 x 3648 x 2240 (2.3 owned) 87.0 ->
+// 88.4, int8 10144 x 1408 x 1024 32.2 -> 33.3.  A workgroup reads 64 KB at a time, some 20 GB/s; the pass must end before
+// the tiles do (0.75 us per slab and 128 rows).
+constexpr double BESIDE_FIXED_US = 4.0, BESIDE_BYTES_PER_US = 20e3, TILE_SLAB_US = 0.75;
+static BesideArgs plan_beside(int dt, int M, int K, int batch, int slabs, int tiles_n, int idle, double tiles_us)
+{
+    const BesideArgs none = {0, 0, 0, 0, 0};
+    if (dt == DT_I8 ? slabs < 9 || slabs < tiles_n : slabs < 20 || slabs < 3 * tiles_n) return none;
+    const EncPlan w = plan_window(M, K, 16 / elem_size(dt));
+    const long per_row_block = (long)w.nwin * batch;
+    if (per_row_block > idle) return none;
+    BesideArgs b;
+    b.cw_log2 = w.cw_log2; b.nwin = w.nwin;
+    const int rl = (256 >> w.cw_log2) * 16;                      // rows a workgroup takes at a time
+    b.nrb = (int)(idle / per_row_block);
+    b.rpb = (M + b.nrb - 1) / b.nrb;
+    b.rpb = (b.rpb + 15) / 16 * 16;
+    if (b.rpb < rl) b.rpb = rl;
+    b.nrb = (M + b.rpb - 1) / b.rpb;
+    b.n = (int)(b.nrb * per_row_block);
+    const double us = BESIDE_FIXED_US + (double)b.rpb * (16 << w.cw_log2) / BESIDE_BYTES_PER_US;
+    return us <= tiles_us ? b : none;
+}
+
 template <int DT, bool PROT>
 static hipError_t launch_fast_one(GemmArgs &g, int batch, hipStream_t st)
 {
     constexpr int smem_main = 2 * (256 + 256) * SLAB_BYTES;
     constexpr int smem_max = 160 * 1024;
+    const int slabs = g.K / (SLAB_BYTES / Traits<DT>::ES);
     auto kern = gemm_fast_kernel<DT, PROT>;
     hipError_t e = ensure_max_lds(reinterpret_cast<const void *>(kern), smem_max);
     if (e != hipSuccess) return e;
@@ -417,9 +454,13 @@ static hipError_t launch_fast_one(GemmArgs &g, int batch, hipStream_t st)
     if (total > 0x7FFFFFFFL) return hipErrorInvalidValue;
     dim3 grid((unsigned)(total < num_cu ? total : num_cu), 1, 1);
     size_t smem = smem_main;
-    if (PROT) {
-        const int ke = SLAB_BYTES / Traits<DT>::ES;
-        smem += apass_lds_bytes_per_wave(DT, g.K / ke, g.tiles_n);
+    g.beside.n = 0;
+    if (PROT && total < num_cu) {
+        g.beside = plan_beside(DT, g.M, g.K, batch, slabs, g.tiles_n, num_cu - (int)total, TILE_SLAB_US * (g.n_big ? 2 : 1) * slabs);
+        grid.x += g.beside.n;
+    }
+    if (PROT && !g.beside.n) {
+        smem += apass_lds_bytes_per_wave(DT, slabs, g.tiles_n);
         if (smem > (size_t)smem_max) return hipErrorInvalidValue;
     }
     hipLaunchKernelGGL(kern, grid, dim3(256), smem, st, g);

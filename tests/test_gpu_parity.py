@@ -155,6 +155,42 @@ def _clean_case(ctx, dtype, M, N, K, batch, trans_b):
         assert np.all(pad == 0x1111)
 
 
+# Tiles in one round that leaves compute units idle and K deep enough: workgroups beside the tiles reduce A
+BESIDE_SHAPES = [
+    (4100, 1030, 1408, 1, True),   # windows of 16 chunks along K (int8: 8), the last row block of a few rows
+    (1030, 700, 2560, 6, True),    # six items; windows of 64 chunks (int8: 32)
+    (8201, 512, 1536, 1, True),    # many row blocks
+    (2600, 1800, 2624, 1, True),   # 328 chunks in windows of 8 (int8: K is no whole slab, the general kernel)
+]
+
+
+@pytest.mark.parametrize("dtype", ["i8", "bf16", "f16"])
+@pytest.mark.parametrize("M,N,K,batch,trans_b", BESIDE_SHAPES)
+def test_a_reduced_beside_the_tiles(ctx, dtype, M, N, K, batch, trans_b):
+    """Every checksum vector against the oracle; then the same call with a = e^T A supplied: the row dots, which are
+    all that is left of the pass, the column predictions and the verdict once more."""
+    if dtype != "i8" or K % 128 == 0:
+        assert_fast(dtype, M, N, K, batch)
+    _clean_case(ctx, dtype, M, N, K, batch, trans_b)
+    A, B = gen.gen_operands(dtype, M, N, K, 61, 62, trans_b=trans_b, batch=batch)
+    run = Run(ctx, dtype, A, B, trans_b)
+    P = oracle_items(dtype, A, B, trans_b)
+    run.gemm()
+    a_dev = torch.from_numpy(run.ws(ab.ABFT_WS_A_SUM).view(np.int32).copy()).to("cuda")
+    m_dev = torch.from_numpy(run.ws(ab.ABFT_WS_MAXABS)[:, 0].astype(np.float32).view(np.int32).copy()).to("cuda")
+    rc = run.ws(ab.ABFT_WS_RC_PRED).copy()
+    assert ab.abft_supply_a(ctx, a_dev, m_dev) == ab.ABFT_OK
+    run.gemm(ab.ABFT_DETECT | ab.ABFT_A_CHECKSUM_GIVEN)
+    assert run.cnt()[2] == ab.ABFT_CLEAN
+    after = run.ws(ab.ABFT_WS_RC_PRED)
+    if dtype == "i8":
+        assert np.array_equal(after, rc)
+        assert all(np.array_equal(run.C()[z], P[z].C_stored) for z in range(batch))
+    else:
+        # the same terms in another order: well inside the bound that predictions are held to
+        assert np.max(np.abs(after - rc)) <= 1e-2 * np.min(run.ws(ab.ABFT_WS_TAU))
+
+
 @pytest.mark.parametrize("dtype", ["i8", "bf16", "f16"])
 @pytest.mark.parametrize("M,N,K", [(200, 136, 320), (2050, 2060, 384)])
 def test_cached_b_checksum(ctx, dtype, M, N, K):
