@@ -24,11 +24,21 @@
 
 namespace abft {
 
+constexpr int BIG_LDS = 2 * (256 + 256) * SLAB_BYTES, BESIDE_BUFS = 3, BESIDE_LDS = BESIDE_BUFS * (128 + 256) * SLAB_BYTES;
+
 typedef const __attribute__((address_space(1))) void *gas_ptr;
 typedef __attribute__((address_space(3))) void *las_ptr;
 
+// Unprotected; protected, the tiles reduce A; protected, workgroups beside the tiles do.  A kernel for each: the last
+// has no code for owned slabs, the others none for the pass beside them, and its 128-row tiles keep
+// three operand buffers: the pass beside them makes their loads wait longer (f16 6304 x 768 x 3072 52.1 -> 50.7 us, 4363 x
+// 1024 x 3264 57.3 -> 54.2; int8 of a dozen slabs 1-2 % slower).  Without that pass the third buffer only adds its
+// loads to the start of a tile: unprotected 3834 x 1216 x 768 18.0 -> 19.1, 1984 x 2303 x 4032 55.7 -> 58.
+enum { FAST_PLAIN, FAST_OWN, FAST_BESIDE };
+
 // One BM x BN tile with origin (m0, n0) of batch item bz.
-template <int DT, int BM, int BN, bool PROT>
+// NB: operand buffers, one slab each; what the pass over A keeps lies behind them.
+template <int DT, int BM, int BN, int NB, int MODE>
 __device__ __forceinline__ void fast_tile(const GemmArgs &g, uint8_t *smem, int m0, int n0, int bz, int tn)
 {
     using T = Traits<DT>;
@@ -39,6 +49,7 @@ __device__ __forceinline__ void fast_tile(const GemmArgs &g, uint8_t *smem, int 
     constexpr int MI = TM / 32, NI = TN / 32;
     constexpr int GA = BM / 32, GB = BN / 32;     // 8-row load groups per wave per slab
     constexpr int BUF = (BM + BN) * SLAB_BYTES;
+    constexpr bool PROT = MODE != FAST_PLAIN, OWN = MODE == FAST_OWN;
 
     const int tid = tile_thread_index(), lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);      // wave-uniform by construction
@@ -102,9 +113,9 @@ __device__ __forceinline__ void fast_tile(const GemmArgs &g, uint8_t *smem, int 
     // The fragments of step t+1 are read from LDS while the MFMAs of step t run (two register
     // sets); the reads are issued in the first half of a step so that the second half covers
     // their latency.  The barrier sits between steps 2 and 3: by then every wave has read its
-    // step-3 fragments, so nobody reads this slab's buffer any more and the loads of slab s+2
+    // step-3 fragments, so nobody reads this slab's buffer any more and the loads of slab s+NB
     // are issued into it at once, spread between the MFMAs of step 3, which also prefetches
-    // step 0 of slab s+1.  The loop is peeled (first slab: literal-zero addend; last two slabs:
+    // step 0 of slab s+1.  The loop is peeled (first slab: literal-zero addend; last NB slabs:
     // nothing left to load) so that no branch separates loads and MFMAs.
     i32x4 fa[2][MI], fb[2][NI];
     auto ldfr = [&](int buf, int s4, int set) __attribute__((always_inline)) {
@@ -137,16 +148,16 @@ __device__ __forceinline__ void fast_tile(const GemmArgs &g, uint8_t *smem, int 
     };
     // Step 3 of a slab that still has loads to issue, in explicit program order: after every
     // MFMA (register set 1) one fragment read of the next slab's step 0 (into set 0) while
-    // there are any, and this MFMA's share of the GA + GB direct-to-LDS loads of slab s + 2.
+    // there are any, and this MFMA's share of the GA + GB direct-to-LDS loads of slab s + NB.
     // The scheduling fences keep that order; left alone, the compiler issues all loads in one
     // burst behind the barrier and the matrix pipe waits for them.
-    auto step3_loads = [&](int s2, int buf) __attribute__((always_inline)) {
+    auto step3_loads = [&](int s2, int buf, int nbuf) __attribute__((always_inline)) {
         constexpr int NMF = MI * NI, NLD = GA + GB;
         const uint8_t *ak = a_base + (long)s2 * SLAB_BYTES;
         const uint8_t *bk = b_base + (long)s2 * SLAB_BYTES;
         uint8_t *dA = smem + buf * BUF;
         uint8_t *dB = dA + BM * SLAB_BYTES;
-        const uint8_t *sA = smem + (buf ^ 1) * BUF;
+        const uint8_t *sA = smem + nbuf * BUF;
         const uint8_t *sB = sA + BM * SLAB_BYTES;
         const int sw = (lh ^ ((lane >> 1) & 7)) * 16;
         static_for<0, NMF>([&](auto j_c) {
@@ -170,7 +181,7 @@ __device__ __forceinline__ void fast_tile(const GemmArgs &g, uint8_t *smem, int 
     };
     // Protected tiles reduce the slabs of A they own (slab s belongs to tile column s mod
     // tiles_n) while those are resident: see gemm_apass.h.
-    constexpr int AUX_OFF = 2 * (256 + 256) * SLAB_BYTES;           // behind the buffers of the largest tile
+    constexpr int AUX_OFF = BIG_LDS;                   // behind the buffers of the largest tile
     uint32_t *col_lds = reinterpret_cast<uint32_t *>(smem + AUX_OFF);
     EpiProt<DT> ep;
     ep.st.rdot = T::zero(); ep.st.amax = 0.f;
@@ -178,14 +189,13 @@ __device__ __forceinline__ void fast_tile(const GemmArgs &g, uint8_t *smem, int 
     ep.col_stride = 0;
     {
         const int nslab = K / KE;                      // at least 3 (gemm_fast_eligible)
-        // (workgroups beside the tiles reduce A: none of the slabs is this tile's)
-        int next_own = PROT && g.beside.n ? nslab : tn;
-        const int owned = (PROT && next_own < nslab) ? (nslab - tn + g.tiles_n - 1) / g.tiles_n : 0;
+        int next_own = tn;
+        const int owned = (OWN && tn < nslab) ? (nslab - tn + g.tiles_n - 1) / g.tiles_n : 0;
         // column sums: one set of owned * KE words per wave (plain stores, added up by the epilogue)
         ep.col_stride = owned * KE;
         uint32_t *col_mine = col_lds + wave * owned * KE;
         uint32_t *b_lds = col_lds + 4 * owned * KE;
-        if (PROT) {
+        if (OWN) {
             // the values of b the owned slabs need, straight into LDS (one slab per wave and turn):
             // in place behind the first barrier
             for (int j = wave; j < owned; j += 4) {
@@ -195,21 +205,25 @@ __device__ __forceinline__ void fast_tile(const GemmArgs &g, uint8_t *smem, int 
                     __builtin_amdgcn_global_load_lds((gas_ptr)(src + 64 * h), (las_ptr)(b_lds + j * KE + 64 * h), 4, 0, 0);
             }
         }
-        issue_loads(0, 0);
-        issue_loads(1, 1);
+#pragma unroll
+        for (int p = 0; p < NB; ++p) issue_loads(p, p);
         // Start as soon as slab 0 is in place: loads complete in order, so "at most the GA + GB
-        // loads of slab 1 outstanding" means everything issued before them has landed.  (The
-        // barrier inside slab 0 waits for the rest.)
-        if constexpr (GA + GB == 16) asm volatile("s_waitcnt vmcnt(16) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-        else if constexpr (GA + GB == 12) asm volatile("s_waitcnt vmcnt(12) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-        else __syncthreads();
+        // loads of each slab behind it outstanding" means everything issued before them has landed.
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"((NB - 1) * (GA + GB)) : "memory");
         ldfr(0, 0, 0);
         // own_c: whether the slab can be one that this workgroup reduces (the first slab and the last
         // two: the pass then runs ahead of the slab's MFMAs; the middle slabs have own_slab below)
+        // the barrier of slab s: slab s + 1 is in place, the loads of `behind` slabs after it may be under way
+        auto slab_barrier = [&](auto behind_c) __attribute__((always_inline)) {
+            if constexpr (NB == 2) __syncthreads();
+            else asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(decltype(behind_c)::value * (GA + GB)) : "memory");
+        };
+        typedef std::integral_constant<int, NB - 2> all_behind;
+        typedef std::integral_constant<int, 0> none_behind;
         auto slab = [&](auto first_c, auto loads_c, auto own_c, int s) __attribute__((always_inline)) {
             constexpr bool LOADS = decltype(loads_c)::value;
-            const int buf = s & 1;
-            if (PROT && decltype(own_c)::value && s == next_own) {
+            const int buf = s % NB, nbuf = (s + 1) % NB;
+            if (OWN && decltype(own_c)::value && s == next_own) {
                 if (g.a_given)
                     a_pass<DT, BM, true, true>(smem + buf * BUF, b_lds + ep.owned * KE, a_rows, col_mine + ep.owned * KE, ep.st);
                 else
@@ -223,11 +237,13 @@ __device__ __forceinline__ void fast_tile(const GemmArgs &g, uint8_t *smem, int 
             ldfr(buf, 2, 0); mfmas(std::false_type{}, 1); interleave();
             __builtin_amdgcn_sched_barrier(0);
             ldfr(buf, 3, 1); mfmas(std::false_type{}, 0); interleave();
-            __syncthreads();
             if constexpr (LOADS) {
-                step3_loads(s + 2, buf);
+                slab_barrier(all_behind{});
+                step3_loads(s + NB, buf, nbuf);
             } else {
-                ldfr(buf ^ 1, 0, 0);                   // after the last slab: read and never used
+                if (NB > 2 && s + NB == nslab) slab_barrier(all_behind{});
+                else slab_barrier(none_behind{});
+                ldfr(nbuf, 0, 0);                      // after the last slab: read and never used
                 mfmas(std::false_type{}, 1); interleave();
                 __builtin_amdgcn_sched_barrier(0);
             }
@@ -244,19 +260,19 @@ __device__ __forceinline__ void fast_tile(const GemmArgs &g, uint8_t *smem, int 
         auto own_slab = [&](int s) __attribute__((always_inline)) {
             constexpr bool GIVEN = false;
             constexpr int NMF = MI * NI, NLD = GA + GB, LAG = NMF / 2;
-            const int buf = s & 1;
+            const int buf = s % NB, nbuf = (s + 1) % NB;
             APassSteps<DT, BM, GIVEN> ap;
             __builtin_amdgcn_sched_barrier(0);
             ap.begin(smem + buf * BUF, b_lds + ep.owned * KE, a_rows);
-            const uint8_t *ak = a_base + (long)(s + 2) * SLAB_BYTES;
-            const uint8_t *bk = b_base + (long)(s + 2) * SLAB_BYTES;
+            const uint8_t *ak = a_base + (long)(s + NB) * SLAB_BYTES;
+            const uint8_t *bk = b_base + (long)(s + NB) * SLAB_BYTES;
             uint8_t *dA = smem + buf * BUF;
             uint8_t *dB = dA + BM * SLAB_BYTES;
             static_for<0, 4>([&](auto t_c) {
                 constexpr int t = decltype(t_c)::value;
                 constexpr int set = t & 1, nset = set ^ 1;
                 // fragments of the next step: step t + 1 of this slab, or step 0 of the next slab
-                const uint8_t *sA = smem + (t < 3 ? buf : buf ^ 1) * BUF;
+                const uint8_t *sA = smem + (t < 3 ? buf : nbuf) * BUF;
                 const uint8_t *sB = sA + BM * SLAB_BYTES;
                 const int sw = ((2 * ((t + 1) & 3) + lh) ^ ((lane >> 1) & 7)) * 16;
                 static_for<0, NMF>([&](auto j_c) {
@@ -280,7 +296,7 @@ __device__ __forceinline__ void fast_tile(const GemmArgs &g, uint8_t *smem, int 
                     ap.template piece<t * NMF + j - LAG>();
                     __builtin_amdgcn_sched_barrier(0);
                 });
-                if constexpr (t == 2) __syncthreads();
+                if constexpr (t == 2) slab_barrier(all_behind{});
             });
             static_for<4 * NMF - LAG, 4 * NMF>([&](auto k_c) { ap.template piece<decltype(k_c)::value>(); });
             ap.end(col_mine + ep.owned * KE, ep.st);
@@ -293,10 +309,10 @@ __device__ __forceinline__ void fast_tile(const GemmArgs &g, uint8_t *smem, int 
         slab(std::true_type{}, std::true_type{}, maybe_own{}, 0);
         // the middle slabs: runs of slabs that are not this workgroup's, each followed by one that is
         int s = 1;
-        const int mid_end = nslab - 2;
+        const int mid_end = nslab - NB;
         // (loops and straight-line code only: an if / else with MFMAs in both arms would move the
         // accumulators out of the accumulation registers)
-        if constexpr (PROT) {
+        if constexpr (OWN) {
             while (next_own < mid_end) {                   // next_own >= s here
                 for (; s < next_own; ++s) slab(std::false_type{}, std::true_type{}, never_own{}, s);
                 own_slab(s);
@@ -314,10 +330,11 @@ __device__ __forceinline__ void fast_tile(const GemmArgs &g, uint8_t *smem, int 
 // big_rows rows, 128 x 256 tiles the rest; how many of each is chosen by playing the dispatch
 // through (choose_big_rows).  (600 big tiles on 256 CUs would be three rounds for 2.34 rounds
 // of work.)
-template <int DT, bool PROT>
+template <int DT, int MODE>
 __global__ __launch_bounds__(256) void gemm_fast_kernel(GemmArgs g)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+    constexpr bool PROT = MODE != FAST_PLAIN;
     if (PROT && blockIdx.x == 0 && threadIdx.x < 5) g.counts[threadIdx.x] = 0u;      // completed by the check kernel
     // Persistent workgroups: one per compute unit, each walks the tile list with the grid's stride.
     // The 128-row tiles come first in the list: the compute units that start with one are half a
@@ -326,20 +343,22 @@ __global__ __launch_bounds__(256) void gemm_fast_kernel(GemmArgs g)
     // the matrix pipes at different times.  Measured on 12608 x 3072 x 768: 63 -> 60.5 us.
     const int per_item = g.n_small + g.n_big;
     const int total = per_item * g.batch;
-    const int n_tile = PROT ? (int)gridDim.x - g.beside.n : (int)gridDim.x;
-    if (PROT && (int)blockIdx.x >= n_tile) {
-        a_beside<DT>(g, (int)blockIdx.x - n_tile, smem);
-        return;
+    const int n_tile = MODE == FAST_BESIDE ? (int)gridDim.x - g.beside.n : (int)gridDim.x;
+    if constexpr (MODE == FAST_BESIDE) {
+        if ((int)blockIdx.x >= n_tile) {
+            a_beside<DT>(g, (int)blockIdx.x - n_tile, smem);
+            return;
+        }
     }
     for (int t = blockIdx.x; t < total; t += n_tile) {
         const int bz = t / per_item, bid = t - bz * per_item;
         int tm, tn;
         if (bid >= g.n_small) {
             map_tile(bid - g.n_small, g.n_big, g.tiles_m_big, g.tiles_n, &tm, &tn);
-            fast_tile<DT, 256, 256, PROT>(g, smem, tm * 256, tn * 256, bz, tn);
+            fast_tile<DT, 256, 256, 2, MODE>(g, smem, tm * 256, tn * 256, bz, tn);
         } else {
             map_tile(bid, g.n_small, g.tiles_m_small, g.tiles_n, &tm, &tn);
-            fast_tile<DT, 128, 256, PROT>(g, smem, g.tiles_m_big * 256 + tm * 128, tn * 256, bz, tn);
+            fast_tile<DT, 128, 256, MODE == FAST_BESIDE ? BESIDE_BUFS : 2, MODE>(g, smem, g.tiles_m_big * 256 + tm * 128, tn * 256, bz, tn);
         }
         // the epilogue's last reads of LDS precede the next tile's first writes
         asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
@@ -405,7 +424,7 @@ static int choose_big_rows(int M, int tiles_n, int batch, int ncu)
 // to 64 chunks along K (least padding, then widest), the rows dealt to as many row blocks as fit.  The tiles
 // are then free of their owned slabs, but their first slabs queue behind this pass's loads: about 1 us lost, against 0.5 us
 // (int8 1 us) for each owned slab.  Measured against tiles that reduce A, us: f16 6304 x 768 x 3072 (16 owned of 48 slabs)
-// 54.4 -> 52.0, 10870 x 896 x 2688 bf16 81.9 -> 75.2, int8 5099 x 896 x 2176 37.1 -> 32.7, 6422 x 1536 x 2688 47.5 -> 42.6; where K is
+// 54.4 -> 52.1, 10870 x 896 x 2688 bf16 81.9 -> 75.2, int8 5099 x 896 x 2176 37.1 -> 32.7, 6422 x 1536 x 2688 47.5 -> 42.6; where K is
 // short or shared by many tile columns it lost: f16 6783 x 704 x 832 37.8 -> 38.4, 2788 x 3648 x 2240 (2.3 owned) 87.0 ->
 // 88.4, int8 10144 x 1408 x 1024 32.2 -> 33.3.  A workgroup reads 64 KB at a time, some 20 GB/s; the pass must end before
 // the tiles do (0.75 us per slab and 128 rows).
@@ -433,12 +452,9 @@ static BesideArgs plan_beside(int dt, int M, int K, int batch, int slabs, int ti
 template <int DT, bool PROT>
 static hipError_t launch_fast_one(GemmArgs &g, int batch, hipStream_t st)
 {
-    constexpr int smem_main = 2 * (256 + 256) * SLAB_BYTES;
     constexpr int smem_max = 160 * 1024;
     const int slabs = g.K / (SLAB_BYTES / Traits<DT>::ES);
-    auto kern = gemm_fast_kernel<DT, PROT>;
-    hipError_t e = ensure_max_lds(reinterpret_cast<const void *>(kern), smem_max);
-    if (e != hipSuccess) return e;
+    hipError_t e;
     const int num_cu = device_cu_count(&e);
     if (e != hipSuccess) return e;
     g.tiles_n = (g.N + 255) / 256;
@@ -453,16 +469,20 @@ static hipError_t launch_fast_one(GemmArgs &g, int batch, hipStream_t st)
     const long total = (long)(g.n_big + g.n_small) * batch;
     if (total > 0x7FFFFFFFL) return hipErrorInvalidValue;
     dim3 grid((unsigned)(total < num_cu ? total : num_cu), 1, 1);
-    size_t smem = smem_main;
     g.beside.n = 0;
     if (PROT && total < num_cu) {
         g.beside = plan_beside(DT, g.M, g.K, batch, slabs, g.tiles_n, num_cu - (int)total, TILE_SLAB_US * (g.n_big ? 2 : 1) * slabs);
         grid.x += g.beside.n;
     }
-    if (PROT && !g.beside.n) {
-        smem += apass_lds_bytes_per_wave(DT, slabs, g.tiles_n);
-        if (smem > (size_t)smem_max) return hipErrorInvalidValue;
-    }
+    size_t smem = BIG_LDS;
+    if (g.beside.n) smem = BIG_LDS > BESIDE_LDS ? BIG_LDS : BESIDE_LDS;
+    else if (PROT) smem += apass_lds_bytes_per_wave(DT, slabs, g.tiles_n);
+    if (smem > (size_t)smem_max) return hipErrorInvalidValue;
+    auto kern = gemm_fast_kernel<DT, PROT ? FAST_OWN : FAST_PLAIN>;
+    if constexpr (PROT)
+        if (g.beside.n) kern = gemm_fast_kernel<DT, FAST_BESIDE>;
+    e = ensure_max_lds(reinterpret_cast<const void *>(kern), smem_max);
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, grid, dim3(256), smem, st, g);
     return hipGetLastError();
 }
@@ -477,7 +497,7 @@ bool gemm_fast_eligible(int dt, int M, int N, int K, bool transB, long lda, long
            lda * elem_size(dt) < (1L << 23) && ldb * elem_size(dt) < (1L << 23) &&
            // what the pass over A's slabs keeps per tile fits behind the operand buffers (protected or
            // not: the tile shape of a problem does not depend on the mode)
-           2 * (256 + 256) * SLAB_BYTES + apass_lds_bytes_per_wave(dt, K / ke, (N + 255) / 256) <= 160 * 1024;
+           BIG_LDS + apass_lds_bytes_per_wave(dt, K / ke, (N + 255) / 256) <= 160 * 1024;
 }
 
 void gemm_fast_tile(int *tm, int *tn) { *tm = 256; *tn = 256; }
