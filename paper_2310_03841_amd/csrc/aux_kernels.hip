@@ -101,14 +101,14 @@ struct EncBArgs {
 template <int DT>
 __global__ __launch_bounds__(256) void encode_b_kernel(EncBArgs a)
 {
-    __shared__ uint32_t red[256 * (16 / Traits<DT>::ES)];
+    __shared__ uint32_t red[256 * (16 / Traits<DT>::ES) + 4];
     const int tid = threadIdx.x, bz = blockIdx.z;
     {
         const size_t nb = (size_t)gridDim.x * gridDim.z;
         const size_t bid = blockIdx.x + (size_t)gridDim.x * blockIdx.z;
         for (size_t i = bid * 256 + tid; i < a.zero_words; i += nb * 256) a.zero_ptr[i] = 0u;
     }
-    encode_block<DT>(a.e, blockIdx.x, bz, red);
+    encode_block<DT, ENC_UNROLL_ALONE>(a.e, blockIdx.x, bz, red);
 }
 
 hipError_t launch_encode_b(int dt, const void *B, const Shape &s, const Workspace &w, uint32_t *zero_ptr,

@@ -8,7 +8,8 @@
 
 namespace abft {
 
-constexpr int ENC_UNROLL = 8;         // independent 16-byte loads in flight per thread
+constexpr int ENC_UNROLL = 8;         // independent 16-byte loads in flight per thread, beside the tiles of a GEMM
+constexpr int ENC_UNROLL_ALONE = 16;  // the same for a kernel that does nothing else
 
 struct EncPlan { int cw_log2, nwin, rpb, nrb; };
 
@@ -46,21 +47,22 @@ inline EncPlan plan_window(int rows, int cols, int chunk_elems)
     return p;
 }
 
-// For a kernel that does nothing else: two batches of ENC_UNROLL loads per thread, more when the
+// For a kernel that does nothing else: one batch of ENC_UNROLL_ALONE loads per thread, more when the
 // matrix is tall (more than 640 blocks): atomics that hit one cache line are served one after the
 // other, so fewer row blocks mean less waiting at the end of the pass.
 inline EncPlan plan_alone(int rows, int cols, int chunk_elems)
 {
     EncPlan p = plan_window(rows, cols, chunk_elems);
-    long rpb = (256L >> p.cw_log2) * ENC_UNROLL * 2;
+    long rpb = (256L >> p.cw_log2) * ENC_UNROLL_ALONE;
     while (rpb < rows && (long)p.nwin * ((rows + rpb - 1) / rpb) > 640) rpb *= 2;
     p.rpb = (int)rpb;
     p.nrb = (int)((rows + rpb - 1) / rpb);
     return p;
 }
 
-// Block `blk` (of nwin * nrb) of batch item bz.  red: 256 * (16 / element size) words of LDS.
-template <int DT, bool REDUCE_ROWS>
+// Block `blk` (of nwin * nrb) of batch item bz.  red: 256 * (16 / element size) + 4 words of LDS.
+// UNROLL: independent 16-byte loads in flight per thread.
+template <int DT, int UNROLL, bool REDUCE_ROWS>
 __device__ __forceinline__ void encode_block_dir(const EncArgs &e, int blk, int bz, uint32_t *red_words)
 {
     using T = Traits<DT>;
@@ -77,7 +79,7 @@ __device__ __forceinline__ void encode_block_dir(const EncArgs &e, int blk, int 
     const uint8_t *Xb = e.X + (long)bz * e.stride * ES;
     const int rbeg = rb * e.rpb;
     const int rend = min(rbeg + e.rpb, e.rows);
-    const int iters = (rend - rbeg + RL * ENC_UNROLL - 1) / (RL * ENC_UNROLL);
+    const int iters = (rend - rbeg + RL * UNROLL - 1) / (RL * UNROLL);
 
     acc_t colacc[CE];
 #pragma unroll
@@ -86,16 +88,16 @@ __device__ __forceinline__ void encode_block_dir(const EncArgs &e, int blk, int 
 
     for (int it = 0; it < iters; ++it) {
         // a batch of independent loads first: the pass is bound by memory latency otherwise
-        i32x4 v[ENC_UNROLL];
+        i32x4 v[UNROLL];
 #pragma unroll
-        for (int u = 0; u < ENC_UNROLL; ++u) {
-            const int r = rbeg + ry + (it * ENC_UNROLL + u) * RL;
+        for (int u = 0; u < UNROLL; ++u) {
+            const int r = rbeg + ry + (it * UNROLL + u) * RL;
             v[u] = i32x4{0, 0, 0, 0};
             if (colok && r < rend) v[u] = *reinterpret_cast<const i32x4 *>(Xb + ((long)r * e.ld + col0) * ES);
         }
 #pragma unroll
-        for (int u = 0; u < ENC_UNROLL; ++u) {
-            const int r = rbeg + ry + (it * ENC_UNROLL + u) * RL;
+        for (int u = 0; u < UNROLL; ++u) {
+            const int r = rbeg + ry + (it * UNROLL + u) * RL;
             i32x4 w = v[u];
             if (nvalid < CE) w = mask_chunk(w, nvalid > 0 ? nvalid * ES : 0);
             acc_t s = T::zero();
@@ -112,6 +114,13 @@ __device__ __forceinline__ void encode_block_dir(const EncArgs &e, int blk, int 
             }
         }
     }
+    // One atomic on max|X| per block, not per wave: they all hit one word, which serves them one after the other.
+    float *mx4 = reinterpret_cast<float *>(red_words + 256 * CE);
+    if (!T::IS_INT) {
+        mx = wave_max(mx);
+        if ((tid & 63) == 0) mx4[tid >> 6] = mx;
+        if constexpr (!REDUCE_ROWS) __syncthreads();
+    }
     if constexpr (REDUCE_ROWS) {
 #pragma unroll
         for (int q = 0; q < CE; ++q) red[(ry * CW + cx) * CE + q] = colacc[q];
@@ -126,17 +135,17 @@ __device__ __forceinline__ void encode_block_dir(const EncArgs &e, int blk, int 
             }
         }
     }
-    if (!T::IS_INT) {
-        mx = wave_max(mx);
-        if ((tid & 63) == 0 && mx > 0.f) atomicMax(e.max_acc + bz, __float_as_uint(mx));
+    if (!T::IS_INT && tid == 0) {
+        mx = fmaxf(fmaxf(mx4[0], mx4[1]), fmaxf(mx4[2], mx4[3]));
+        if (mx > 0.f) atomicMax(e.max_acc + bz, __float_as_uint(mx));
     }
 }
 
-template <int DT>
+template <int DT, int UNROLL>
 __device__ __forceinline__ void encode_block(const EncArgs &e, int blk, int bz, uint32_t *red_words)
 {
-    if (e.reduce_rows) encode_block_dir<DT, true>(e, blk, bz, red_words);
-    else encode_block_dir<DT, false>(e, blk, bz, red_words);
+    if (e.reduce_rows) encode_block_dir<DT, UNROLL, true>(e, blk, bz, red_words);
+    else encode_block_dir<DT, UNROLL, false>(e, blk, bz, red_words);
 }
 
 }  // namespace abft

@@ -109,8 +109,8 @@ __global__ __launch_bounds__(256) void gemm_tile_kernel(TileArgs a)
             if (e == a.n_enc_a + a.n_enc_b) {
                 const acc_t t = block_bias_sum<acc_t>(g.bias, g.N, reinterpret_cast<acc_t *>(smem));
                 if (threadIdx.x == 0 && bz == 0) *a.bias_sum = as_word(t);
-            } else if (e < a.n_enc_a) encode_block<DT>(a.ea, e, bz, reinterpret_cast<uint32_t *>(smem));
-            else encode_block<DT>(a.eb, e - a.n_enc_a, bz, reinterpret_cast<uint32_t *>(smem));
+            } else if (e < a.n_enc_a) encode_block<DT, ENC_UNROLL>(a.ea, e, bz, reinterpret_cast<uint32_t *>(smem));
+            else encode_block<DT, ENC_UNROLL>(a.eb, e - a.n_enc_a, bz, reinterpret_cast<uint32_t *>(smem));
             return;
         }
     }
