@@ -675,34 +675,43 @@ __global__ __launch_bounds__(256) void verify_kernel(VerArgs a)
     const int nvalid = a.N - col0;
     const uint8_t *Cb = a.C + (long)bz * a.sC * OS;
     const int rbeg = rb * a.rpb, rend = min(rbeg + a.rpb, a.M);
-    const int iters = (a.rpb + RL * ENC_UNROLL - 1) / (RL * ENC_UNROLL);
     acc_t colacc[CE];
 #pragma unroll
     for (int q = 0; q < CE; ++q) colacc[q] = T::zero();
-    for (int it = 0; it < iters; ++it) {
-        i32x4 v[ENC_UNROLL];
+    // A thread takes UN consecutive rows at a time: their sums meet in eight lanes, which add sixteen neighbouring
+    // words in two atomics (a row at a time, one lane each, the row sums were most of the pass).
+    constexpr int UN = ENC_UNROLL_ALONE;
+    const uint8_t *src = Cb + (colok ? (long)col0 * OS : 0);
+    for (int r0 = rbeg; r0 < rend; r0 += RL * UN) {
+        const int rt = r0 + ry * UN;
+        i32x4 v[UN];
 #pragma unroll
-        for (int u = 0; u < ENC_UNROLL; ++u) {
-            const int r = rbeg + ry + (it * ENC_UNROLL + u) * RL;
-            v[u] = i32x4{0, 0, 0, 0};
-            if (colok && r < rend) v[u] = *reinterpret_cast<const i32x4 *>(Cb + ((long)r * a.ldc + col0) * OS);
-        }
+        for (int u = 0; u < UN; ++u)                             // past the end: the last row, cleared below
+            v[u] = *reinterpret_cast<const i32x4 *>(src + (long)min(rt + u, a.M - 1) * a.ldc * OS);
+        acc_t part[CE], m0 = T::zero(), m1 = T::zero();
 #pragma unroll
-        for (int u = 0; u < ENC_UNROLL; ++u) {
-            const int r = rbeg + ry + (it * ENC_UNROLL + u) * RL;
+        for (int q = 0; q < CE; ++q) part[q] = T::zero();
+#pragma unroll
+        for (int u = 0; u < UN; ++u) {
+            i32x4 w = v[u];
+            if (!colok || rt + u >= rend) w = i32x4{0, 0, 0, 0};
+            else if (nvalid < CE) w = mask_chunk(w, nvalid * OS);
             acc_t s = T::zero();
-            if (colok && r < rend) {
 #pragma unroll
-                for (int q = 0; q < CE; ++q) {
-                    if (q < nvalid) {
-                        acc_t x = out_elem<DT>(v[u], q);
-                        colacc[q] = add_t(colacc[q], x);
-                        s = add_t(s, x);
-                    }
-                }
+            for (int q = 0; q < CE; ++q) {
+                const acc_t x = out_elem<DT>(w, q);
+                part[q] = add_t(part[q], x);
+                s = add_t(s, x);
             }
             s = seg_sum(s, CW);
-            if (cx == 0 && r < rend) atomic_add_word(a.rc_vobs + (long)bz * a.M + r, s);
+            if (cx == (u & 7)) { if (u < 8) m0 = s; else m1 = s; }
+        }
+#pragma unroll
+        for (int q = 0; q < CE; ++q) colacc[q] = add_t(colacc[q], part[q]);
+        if (cx < 8) {
+            uint32_t *d = a.rc_vobs + (long)bz * a.M + rt + cx;
+            if (rt + cx < rend) atomic_add_word(d, m0);
+            if (rt + cx + 8 < rend) atomic_add_word(d + 8, m1);
         }
     }
 #pragma unroll
