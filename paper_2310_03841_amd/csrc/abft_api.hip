@@ -84,11 +84,11 @@ extern "C" int abft_last_hip_error(const abft_ctx *ctx) { return ctx ? ctx->last
 // max_depth (already rounded, see abft_create) / max_batch.
 constexpr int N_POOLS = 8;
 constexpr int SMALL_WORDS = 8 + 64 + 1;
-// one region of pool_obs; even, so that the doubles at its end stay aligned in both regions
+// one region of pool_obs; whole 16 bytes, so that the doubles at its end, and 16-byte loads of a sum, are aligned alike in both regions
 static constexpr size_t obs_region_words(size_t R, size_t Cn, size_t D, size_t Bt)
 {
     const size_t most = (size_t)ONE_LAUNCH_MAX_LEN, one = 2 * ((Cn < most ? Cn : most) + (R < most ? R : most) + Bt);
-    return (2 * Cn + 3 * R + D + 2 * Bt + 1 + 2 * (Cn + R) + 1 + one + ONE_LAUNCH_TICKET_WORDS) / 2 * 2;
+    return (2 * Cn + 3 * R + D + 2 * Bt + 1 + 2 * (Cn + R) + 1 + one + ONE_LAUNCH_TICKET_WORDS + 3) / 4 * 4;
 }
 static constexpr size_t pool_total_words(size_t R, size_t Cn, size_t D, size_t Bt)
 {
@@ -698,7 +698,7 @@ extern "C" int abft_verify(abft_ctx *ctx, const void *C, abft_dtype dtype, const
     Workspace w;
     carve(ctx, dtype, sh, &w);
     if (rp.stale) HIP_TRY(launch_zero(w.cc_vobs, rp.stale, st));
-    HIP_TRY(launch_verify_sums(dtype, C, sh, w, st));
+    HIP_TRY(launch_verify_sums(dtype, C, sh, w, v.counts, st));
     HIP_TRY(launch_compare(dtype, sh, w, v, false, ctx->sto_valid, rp.other, rp.other_words, st));
     end_resum(ctx, words);
     note_vobs(ctx, C, s, st);

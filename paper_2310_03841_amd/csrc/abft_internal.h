@@ -138,7 +138,8 @@ hipError_t launch_check(int dt, bool after_fast, bool rc_ready, const void *A, c
 // gated: the kernel does nothing when the tile list of the correction before it is empty
 hipError_t launch_compare(int dt, const Shape &s, const Workspace &w, const Verdict &v, bool after_fix,
                           bool with_sto, uint32_t *zero_ptr, size_t zero_words, hipStream_t st, bool gated = false);
-hipError_t launch_verify_sums(int dt, const void *C, const Shape &s, const Workspace &w, hipStream_t st,
+// counts: cleared for the compare that follows (null: that of a correction, which writes them all itself)
+hipError_t launch_verify_sums(int dt, const void *C, const Shape &s, const Workspace &w, uint32_t *counts, hipStream_t st,
                               bool gated = false);
 // stale_words: leading words of the re-summing region in use that must be cleared first;
 // zero_ptr / zero_words: the other re-summing region, cleared by the final compare

@@ -137,6 +137,24 @@ hipError_t launch_encode_b(int dt, const void *B, const Shape &s, const Workspac
 // of K) next to the operand buffers until the epilogue.
 int protect_max_k(int dt) { (void)dt; return 4096; }
 
+// A wave found n rows (side 0) or n columns (side 1) that disagree.  counts[side] gains them; counts[2] and
+// counts[4] become the status: localised once both sides have flags, suspect while one has.  Only the
+// first wave of a side writes it.  It adds first and looks at the other side second, so of the two first
+// waves at least one sees both; "localised" goes in whatever is there, "suspect" only replaces "clean".
+// (With every wave looking and writing, a bf16 12608 x 3072 x 768 whose every row and column flags took 137 us;
+// so 84, and 78 clean: atomics on one line are served one after the other.)
+__device__ __forceinline__ void report_flags(uint32_t *counts, int side, unsigned n)
+{
+    if (atomicAdd(counts + side, n) != 0u) return;
+    if (atomicAdd(counts + (side ^ 1), 0u) != 0u) {
+        atomicExch(counts + 2, 1u);
+        atomicExch(counts + 4, 1u);
+    } else {
+        atomicCAS(counts + 2, 0u, 2u);
+        atomicCAS(counts + 4, 0u, 2u);
+    }
+}
+
 // ===================================================================== compare
 // Flags from observed sums against the predictions the last abft_gemm left in the context
 // (Sec. III-B.1 item (2): equality for fixed point, tolerance for floating point).  Used by
@@ -149,7 +167,7 @@ struct CmpArgs {
     float tau_override_cols;   // > 0: tolerance of the column check
     uint8_t *row_flag, *col_flag;
     uint32_t *counts;
-    uint32_t *ticket;     // [3]: ticket, flagged rows, flagged cols (self-cleaning)
+    uint32_t *ticket;     // after a correction: [3]: ticket, flagged rows, flagged cols (self-cleaning)
     uint32_t *fix_count;  // non-null after a correction: [0] tiles listed, [1] overflow (cleared after use)
     const int32_t *fix_tiles;          // after a correction: the tiles it recomputed
     uint32_t *cc_sto, *rc_sto;         // non-null: stored-side sums of the GEMM (floating point)
@@ -204,6 +222,17 @@ __global__ __launch_bounds__(256) void compare_kernel(CmpArgs a)
             fcol = fcol || mismatch<false>(a.cc_obs[(long)bz * N + j], a.cc_sto[(long)bz * N + j], STO_TOL_FACTOR * tol_c);
         a.col_flag[(long)bz * N + j] = fcol ? 1 : 0;
     }
+    if (!a.fix_count) {
+        // the pass over stored C has cleared the counts: only waves that saw a mismatch touch them.  (A ticket per block and
+        // a last block that publishes are two trips to memory more: int8 6304 x 768 x 3072, flip, verify and repair
+        // 33.7 -> 32.8 us; bf16 6304 x 3072 x 768 with stored sums and verify 80.0 -> 77.1.)
+        const unsigned wr = __popcll(__ballot(frow)), wc = __popcll(__ballot(fcol));
+        if ((tid & 63) == 0) {
+            if (wr) report_flags(a.counts, 0, wr);
+            if (wc) report_flags(a.counts, 1, wc);
+        }
+        return;
+    }
     const unsigned nr = __syncthreads_count(frow);
     const unsigned nc = __syncthreads_count(fcol);
     if (tid == 0) {
@@ -226,17 +255,11 @@ __global__ __launch_bounds__(256) void compare_kernel(CmpArgs a)
         const uint32_t before = a.counts[2];
         a.counts[0] = r;
         a.counts[1] = c;
-        if (a.fix_count) {
-            // the list is consumed: the next correction starts from an empty one
-            const uint32_t tiles = atomicExch(a.fix_count, 0u);
-            a.counts[2] = atomicExch(a.fix_count + 1, 0u) ? 3u : status_of(r, c);
-            a.counts[3] = tiles > (uint32_t)MAX_FIX_TILES ? (uint32_t)MAX_FIX_TILES : tiles;
-            a.counts[4] = before;
-        } else {
-            a.counts[2] = status_of(r, c);
-            a.counts[3] = 0u;
-            a.counts[4] = status_of(r, c);
-        }
+        // the list is consumed: the next correction starts from an empty one
+        const uint32_t tiles = atomicExch(a.fix_count, 0u);
+        a.counts[2] = atomicExch(a.fix_count + 1, 0u) ? 3u : status_of(r, c);
+        a.counts[3] = tiles > (uint32_t)MAX_FIX_TILES ? (uint32_t)MAX_FIX_TILES : tiles;
+        a.counts[4] = before;
     }
 }
 
@@ -300,24 +323,6 @@ struct ChkArgs {
     size_t zero2_words;
 };
 
-// A wave found n rows (side 0) or n columns (side 1) that disagree.  counts[side] gains them; counts[2] and
-// counts[4] become the status: localised once both sides have flags, suspect while one has.  Only the
-// first wave of a side writes it.  It adds first and looks at the other side second, so of the two first
-// waves at least one sees both; "localised" goes in whatever is there, "suspect" only replaces "clean".
-// (With every wave looking and writing, a bf16 12608 x 3072 x 768 whose every row and column flags took 137 us;
-// so 84, and 78 clean: atomics on one line are served one after the other.)
-__device__ __forceinline__ void report_flags(uint32_t *counts, int side, unsigned n)
-{
-    if (atomicAdd(counts + side, n) != 0u) return;
-    if (atomicAdd(counts + (side ^ 1), 0u) != 0u) {
-        atomicExch(counts + 2, 1u);
-        atomicExch(counts + 4, 1u);
-    } else {
-        atomicCAS(counts + 2, 0u, 2u);
-        atomicCAS(counts + 4, 0u, 2u);
-    }
-}
-
 // Dots of RW rows of a K-contiguous operand with a vector of K words: lanes along K, two chunks per
 // lane and trip, everything of a trip in flight.  split: this wave takes every fourth run of 128
 // chunks.  Every lane returns the wave's share of all RW dots.
@@ -330,28 +335,46 @@ __device__ __forceinline__ void row_dots(const uint8_t *X, long ld, int row0, in
     constexpr int ES = T::ES, CE = 16 / ES;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int nch = (K + CE - 1) / CE;
-    const bool vec16 = ((uintptr_t)vec & 15u) == 0;              // 16-byte loads of the vector are aligned
+    // 16-byte loads of the vector are aligned and no chunk is cut: then every load is issued, lanes and rows past the end
+    // ask for the last one (around a load under a branch the compiler waits for those before it)
+    const bool whole = ((uintptr_t)vec & 15u) == 0 && K % CE == 0;
 #pragma unroll
     for (int j = 0; j < RW; ++j) dot[j] = T::zero();
     for (int ch0 = split ? wave * 128 : 0; ch0 < nch; ch0 += split ? 512 : 128) {
         i32x4 v[RW][2], aw[2][CE / 4];
+        if (whole) {
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int ch = ch0 + 64 * h + lane;
-            const bool in = ch < nch;
+            for (int h = 0; h < 2; ++h) {
+                const int ch = min(ch0 + 64 * h + lane, nch - 1);
 #pragma unroll
-            for (int j = 0; j < RW; ++j) {
-                v[j][h] = i32x4{0, 0, 0, 0};
-                if (in && row0 + j < rows) v[j][h] = *reinterpret_cast<const i32x4 *>(X + ((long)(row0 + j) * ld + (long)ch * CE) * ES);
+                for (int j = 0; j < RW; ++j)
+                    v[j][h] = *reinterpret_cast<const i32x4 *>(X + ((long)min(row0 + j, rows - 1) * ld + (long)ch * CE) * ES);
+#pragma unroll
+                for (int q4 = 0; q4 < CE / 4; ++q4) aw[h][q4] = *reinterpret_cast<const i32x4 *>(vec + ch * CE + 4 * q4);
             }
-            const int left = K - ch * CE;
 #pragma unroll
-            for (int q4 = 0; q4 < CE / 4; ++q4) {
-                aw[h][q4] = i32x4{0, 0, 0, 0};
-                if (in) {
-                    const uint32_t *ap = vec + ch * CE + 4 * q4;
-                    if (vec16 && left >= CE) aw[h][q4] = *reinterpret_cast<const i32x4 *>(ap);
-                    else {
+            for (int h = 0; h < 2; ++h) {
+                if (ch0 + 64 * h + lane >= nch) {
+#pragma unroll
+                    for (int q4 = 0; q4 < CE / 4; ++q4) aw[h][q4] = i32x4{0, 0, 0, 0};
+                }
+            }
+        } else {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int ch = ch0 + 64 * h + lane;
+                const bool in = ch < nch;
+#pragma unroll
+                for (int j = 0; j < RW; ++j) {
+                    v[j][h] = i32x4{0, 0, 0, 0};
+                    if (in && row0 + j < rows) v[j][h] = *reinterpret_cast<const i32x4 *>(X + ((long)(row0 + j) * ld + (long)ch * CE) * ES);
+                }
+                const int left = K - ch * CE;
+#pragma unroll
+                for (int q4 = 0; q4 < CE / 4; ++q4) {
+                    aw[h][q4] = i32x4{0, 0, 0, 0};
+                    if (in) {
+                        const uint32_t *ap = vec + ch * CE + 4 * q4;
 #pragma unroll
                         for (int e = 0; e < 4; ++e) aw[h][q4][e] = (4 * q4 + e < left) ? (int)ap[e] : 0;
                     }
@@ -387,6 +410,8 @@ __global__ __launch_bounds__(256) void check_kernel(ChkArgs f)
     __shared__ acc_t part[4][CHK_KN_LANES * CE > RW ? CHK_KN_LANES * CE : RW];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int M = f.M, N = f.N, K = f.K;
+    // every cache line of the arguments is asked for at once: left alone, the loads wait for the branch below
+    asm volatile("" :: "s"(f.A), "s"(f.K), "s"(f.cc_acc), "s"(f.maxabs), "s"(f.zero2_words));
     const unsigned upi = (unsigned)f.row_units + f.col_units + 1;      // units per batch item
     const unsigned id = blockIdx.y * f.grid_x + blockIdx.x;
     if (id >= upi * f.batch) return;
@@ -397,26 +422,36 @@ __global__ __launch_bounds__(256) void check_kernel(ChkArgs f)
         for (size_t i = (size_t)id * 256 + tid; i < f.zero_words; i += nb * 256) f.zero_ptr[i] = 0u;
         for (size_t i = (size_t)id * 256 + tid; i < f.zero2_words; i += nb * 256) f.zero2_ptr[i] = 0u;
     }
-    float tol = 0.f;
-    if (!T::IS_INT) {
-        const float ma = __uint_as_float(f.a_max[bz]), mb = __uint_as_float(f.b_max[bz]);
-        tol = f.tau_override > 0.f ? f.tau_override : (1e-3f * (float)K) * ma * mb;
-        if (u == (int)upi - 1 && tid == 0) {
-            f.maxabs[(long)bz * 2] = ma;
-            f.maxabs[(long)bz * 2 + 1] = mb;
-            f.tau[bz] = tol;
-        }
-    }
-    const float tol_c = f.tau_override_cols > 0.f ? f.tau_override_cols : tol;
+    // What the comparison needs is requested here and first used behind the dots: a use in between (the
+    // tolerance, the conversion of an observed sum) is a wait for memory ahead of the loads of the dots.  (bf16 12608 x 3072 x
+    // 768, nothing cached: 76.1 -> 75.7 us; 1537 x 1001 x 713 with B stored K x N: 16.3 -> 15.9; 6304 x 3072 x 768: 81.6 -> 80.0 with sums and verify.)
+    uint32_t ma = 0, mb = 0;
+    if (!T::IS_INT) { ma = f.a_max[bz]; mb = f.b_max[bz]; }
+    auto tolerance = [&]() __attribute__((always_inline)) {
+        return T::IS_INT ? 0.f : f.tau_override > 0.f ? f.tau_override : (1e-3f * (float)K) * __uint_as_float(ma) * __uint_as_float(mb);
+    };
+    auto tolerance_cols = [&]() __attribute__((always_inline)) { return f.tau_override_cols > 0.f ? f.tau_override_cols : tolerance(); };
     const bool acc_obs = !T::IS_INT && f.cc_acc != nullptr;     // the observed sums are still doubles
-    acc_t sb = T::zero();                                       // sum of the bias
-    if (f.bias) {
-        if (!f.rc_ready) sb = from_word<acc_t>(*f.bias_sum);
-        else if (u == (int)upi - 1 || u < f.row_units) {
-            sb = block_bias_sum<acc_t>(f.bias, N, wred);
-            __syncthreads();
-        }
+    // An observed sum as two words (the second one is only looked at if it is a double): loads without a branch, into
+    // registers nothing else is written to.
+    struct Obs { uint32_t lo, hi; };
+    auto request = [&](const double *acc, const uint32_t *sum, long o) __attribute__((always_inline)) {
+        const uint32_t *at = acc_obs ? reinterpret_cast<const uint32_t *>(acc + o) : sum + o;
+        return Obs{at[0], at[acc_obs ? 1 : 0]};
+    };
+    auto observed = [&](const Obs &x) __attribute__((always_inline)) {
+        return acc_obs ? __float_as_uint((float)__hiloint2double((int)x.hi, (int)x.lo)) : x.lo;
+    };
+    // sum of the bias
+    const uint32_t sb_word = *(f.bias && !f.rc_ready ? f.bias_sum : bsum);
+    acc_t sb_block = T::zero();
+    if (f.bias && f.rc_ready && (u == (int)upi - 1 || u < f.row_units)) {
+        sb_block = block_bias_sum<acc_t>(f.bias, N, wred);
+        __syncthreads();
     }
+    auto bias_sum = [&]() __attribute__((always_inline)) {
+        return !f.bias ? T::zero() : f.rc_ready ? sb_block : from_word<acc_t>(sb_word);
+    };
     if (u == (int)upi - 1) {
         // scalar a . b (the single-number check value of Sec. III-B.1)
         acc_t v = T::zero();
@@ -424,8 +459,14 @@ __global__ __launch_bounds__(256) void check_kernel(ChkArgs f)
         v = wave_sum(v);
         if (lane == 0) wred[wave] = v;
         __syncthreads();
-        if (tid == 0)
-            f.s_pred[bz] = as_word(add_t(add_t(add_t(wred[0], wred[1]), add_t(wred[2], wred[3])), mul_t((acc_t)M, sb)));
+        if (tid == 0) {
+            f.s_pred[bz] = as_word(add_t(add_t(add_t(wred[0], wred[1]), add_t(wred[2], wred[3])), mul_t((acc_t)M, bias_sum())));
+            if (!T::IS_INT) {
+                f.maxabs[(long)bz * 2] = __uint_as_float(ma);
+                f.maxabs[(long)bz * 2 + 1] = __uint_as_float(mb);
+                f.tau[bz] = tolerance();
+            }
+        }
         return;
     }
     const bool is_row = u < f.row_units;
@@ -435,11 +476,11 @@ __global__ __launch_bounds__(256) void check_kernel(ChkArgs f)
         if (r < M) {
             const long o = (long)bz * M + r;
             uint32_t pred = f.rc_pred[o];
-            if (f.bias) { pred = as_word(add_t(from_word<acc_t>(pred), sb)); f.rc_pred[o] = pred; }
-            uint32_t obs;
-            if (acc_obs) f.rc_obs[o] = obs = __float_as_uint((float)f.rc_acc[o]);
-            else obs = f.rc_obs[o];
-            fl = mismatch<T::IS_INT>(obs, pred, tol);
+            const Obs x = request(f.rc_acc, f.rc_obs, o);
+            const uint32_t obs = observed(x);
+            if (acc_obs) f.rc_obs[o] = obs;
+            if (f.bias) { pred = as_word(add_t(from_word<acc_t>(pred), sb_block)); f.rc_pred[o] = pred; }
+            fl = mismatch<T::IS_INT>(obs, pred, tolerance());
             f.row_flag[o] = fl ? 1 : 0;
         }
         const unsigned nf = __popcll(__ballot(fl));
@@ -453,11 +494,9 @@ __global__ __launch_bounds__(256) void check_kernel(ChkArgs f)
         const bool mine_ok = lane < RW && row0 + lane < rows && (!split || wave == 0);
         const long o = (long)bz * rows + row0 + lane;
         // what the dots are compared with, requested first
-        uint32_t obs = 0;
-        acc_t add = T::zero();
-        if (mine_ok) obs = acc_obs ? __float_as_uint((float)(is_row ? f.rc_acc : f.cc_acc)[o]) : (is_row ? f.rc_obs : f.cc_obs)[o];
-        if (f.bias && mine_ok)
-            add = is_row ? sb : mul_t((acc_t)M, from_word<acc_t>(f.bias[row0 + lane]));
+        const int at = min(row0 + (lane & (RW - 1)), rows - 1);
+        const Obs x = request(is_row ? f.rc_acc : f.cc_acc, is_row ? f.rc_obs : f.cc_obs, (long)bz * rows + at);
+        const uint32_t bias = *(f.bias && !is_row ? f.bias + at : bsum);
         acc_t dot[RW];
         row_dots<DT, RW>(is_row ? f.A + (long)bz * f.sA * ES : f.B + (long)bz * f.sB * ES, is_row ? f.lda : f.ldb, row0, rows, K,
                          is_row ? bsum : asum, split, dot);
@@ -473,12 +512,13 @@ __global__ __launch_bounds__(256) void check_kernel(ChkArgs f)
         acc_t mine = dot[0];
 #pragma unroll
         for (int j = 1; j < RW; ++j) mine = lane == j ? dot[j] : mine;
-        mine = add_t(mine, add);
+        if (f.bias) mine = add_t(mine, is_row ? bias_sum() : mul_t((acc_t)M, from_word<acc_t>(bias)));
+        const uint32_t obs = observed(x);
         bool fl = false;
         if (mine_ok) {
             (is_row ? f.rc_pred : f.cc_pred)[o] = as_word(mine);
             if (acc_obs) (is_row ? f.rc_obs : f.cc_obs)[o] = obs;
-            fl = mismatch<T::IS_INT>(obs, as_word(mine), is_row ? tol : tol_c);
+            fl = mismatch<T::IS_INT>(obs, as_word(mine), is_row ? tolerance() : tolerance_cols());
             (is_row ? f.row_flag : f.col_flag)[o] = fl ? 1 : 0;
         }
         const unsigned nf = __popcll(__ballot(fl));
@@ -491,12 +531,9 @@ __global__ __launch_bounds__(256) void check_kernel(ChkArgs f)
         const bool in = nst < N;
         const int n = col0 + tid;                               // this thread's column in the end
         const bool mine_ok = tid < CHK_KN_LANES * CE && n < N;
-        uint32_t obs = 0;
-        acc_t add = T::zero();
-        if (mine_ok) {
-            obs = acc_obs ? __float_as_uint((float)f.cc_acc[(long)bz * N + n]) : f.cc_obs[(long)bz * N + n];
-            if (f.bias) add = mul_t((acc_t)M, from_word<acc_t>(f.bias[n]));
-        }
+        const int at = min(n, N - 1);
+        const Obs x = request(f.cc_acc, f.cc_obs, (long)bz * N + at);
+        const uint32_t bias = *(f.bias ? f.bias + at : bsum);
         acc_t colp[CE];
 #pragma unroll
         for (int q = 0; q < CE; ++q) colp[q] = T::zero();
@@ -534,11 +571,13 @@ __global__ __launch_bounds__(256) void check_kernel(ChkArgs f)
         __syncthreads();
         bool fl = false;
         if (mine_ok) {
-            const acc_t t = add_t(add_t(add_t(part[0][tid], part[1][tid]), add_t(part[2][tid], part[3][tid])), add);
+            acc_t t = add_t(add_t(part[0][tid], part[1][tid]), add_t(part[2][tid], part[3][tid]));
+            if (f.bias) t = add_t(t, mul_t((acc_t)M, from_word<acc_t>(bias)));
+            const uint32_t obs = observed(x);
             const long o = (long)bz * N + n;
             f.cc_pred[o] = as_word(t);
             if (acc_obs) f.cc_obs[o] = obs;
-            fl = mismatch<T::IS_INT>(obs, as_word(t), tol_c);
+            fl = mismatch<T::IS_INT>(obs, as_word(t), tolerance_cols());
             f.col_flag[o] = fl ? 1 : 0;
         }
         const unsigned nf = __popcll(__ballot(fl));
@@ -646,6 +685,7 @@ struct VerArgs {
     int cw_log2, rpb, nwin, nrb;
     uint32_t *cc_vobs, *rc_vobs;
     const uint32_t *gate; // non-null: nothing to do if *gate == 0 (no tile was recomputed: C is as it was checked)
+    uint32_t *counts;     // non-null: cleared for the compare kernel
 };
 
 // value q of a 16-byte chunk of stored C
@@ -667,6 +707,7 @@ __global__ __launch_bounds__(256) void verify_kernel(VerArgs a)
     __shared__ acc_t red[256 * CE];
     const int tid = threadIdx.x, bz = blockIdx.z;
     if (a.gate && *a.gate == 0u) return;
+    if (a.counts && blockIdx.x == 0 && bz == 0 && tid < 5) a.counts[tid] = 0u;
     const int win = blockIdx.x % a.nwin, rb = blockIdx.x / a.nwin;
     const int CW = 1 << a.cw_log2, RL = 256 >> a.cw_log2;
     const int cx = tid & (CW - 1), ry = tid >> a.cw_log2;
@@ -727,9 +768,10 @@ __global__ __launch_bounds__(256) void verify_kernel(VerArgs a)
     }
 }
 
-hipError_t launch_verify_sums(int dt, const void *C, const Shape &s, const Workspace &w, hipStream_t st, bool gated)
+hipError_t launch_verify_sums(int dt, const void *C, const Shape &s, const Workspace &w, uint32_t *counts, hipStream_t st, bool gated)
 {
     VerArgs a;
+    a.counts = counts;
     a.gate = gated ? w.fix_count : nullptr;
     a.C = (const uint8_t *)C; a.ldc = s.ldc; a.sC = s.sC; a.M = s.M; a.N = s.N;
     a.cc_vobs = w.cc_vobs; a.rc_vobs = w.rc_vobs;
@@ -1120,7 +1162,7 @@ hipError_t launch_correct(int dt, const void *A, const void *B, void *C, const S
     // re-check without earlier sums of this C: the stored C is re-summed as a whole (a streaming
     // pass at HBM speed) and compared with the predictions
     if (stale_words && (e = launch_zero(w.cc_vobs, stale_words, st)) != hipSuccess) return e;
-    if ((e = launch_verify_sums(dt, C, s, w, st, skip_if_clean)) != hipSuccess) return e;
+    if ((e = launch_verify_sums(dt, C, s, w, nullptr, st, skip_if_clean)) != hipSuccess) return e;
     return launch_compare(dt, s, w, v, true, with_sto, zero_ptr, zero_words, st, skip_if_clean);
 }
 
