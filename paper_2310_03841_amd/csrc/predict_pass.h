@@ -106,14 +106,15 @@ struct PredRows {
     int w0, nw;                      // wave w0 + i of nw takes steps i, i + nw, ...
 };
 
-// What lies past the operand (rows, and bytes of K) is cleared in LDS, by the wave that requested it: rare, and both
-// passes then read pieces as they are.
+// What lies past the operand (every row of every step from cnt on, and bytes of K) is cleared in LDS, by the wave that
+// requested it: rare, and both passes then read pieces as they are.  The last block of a split operand can end steps
+// before the others do (385 rows: 129, 129, 127, in three steps each).
 __device__ __forceinline__ void pred_clear(const PredRows &x, int wave, int lane)
 {
     const bool ragged = x.left < PRED_CHUNKS * 16;
     if (!ragged && x.steps * 64 == x.cnt) return;
     for (int t = wave - x.w0; t < x.steps; t += x.nw) {
-        if (!ragged && t != x.steps - 1) continue;
+        if (!ragged && (t + 1) * 64 <= x.cnt) continue;
         const int row = t * 64 + lane;
         for (int c = 0; c < PRED_CHUNKS; ++c) {
             i32x4 *at = reinterpret_cast<i32x4 *>(x.lds + pred_at(row, c));

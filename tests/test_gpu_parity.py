@@ -1711,6 +1711,24 @@ def test_one_launch_edges(dtype, M, N, K, batch, trans_b):
         ab.abft_destroy(ctx)
 
 
+# The same, with a last block of the operand that is split whose rows leave more than the last step of 64 unfilled
+# (385 rows in three blocks: 129, 129 and 127, three steps each)
+ONE_LAUNCH_SHORT_BLOCKS = [
+    (64, 385, 256, 1, True),
+    (385, 64, 256, 1, True),
+    (197, 577, 768, 1, True),
+    (160, 577, 335, 1, True),       # the last range of K cut as well
+    (577, 64, 577, 4, False),       # attn V of one image
+]
+
+
+@pytest.mark.parametrize("dtype", ["i8", "bf16", "f16"])
+@pytest.mark.parametrize("M,N,K,batch,trans_b", ONE_LAUNCH_SHORT_BLOCKS)
+def test_one_launch_short_last_block(ctx, dtype, M, N, K, batch, trans_b):
+    """Every checksum vector and a clean verdict: no row of an operand is summed twice."""
+    _clean_case(ctx, dtype, M, N, K, batch, trans_b)
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 @pytest.mark.parametrize("value", [np.inf, np.nan])
 @pytest.mark.parametrize("where", ["A", "B"])
