@@ -231,8 +231,13 @@ template <int DT> __device__ __forceinline__ uint32_t pred_term(typename Traits<
         v = (int)((uint32_t)v - (uint32_t)d) >> 8;
         return (uint32_t)d & 0xFFu;
     } else {
-        const uint32_t h = DT == DT_BF16 ? f32_to_bf16_bits(v) : f32_to_f16_bits(v);
-        v -= DT == DT_BF16 ? bf16_bits_to_f32(h) : f16_bits_to_f32(h);
+        // A finite value that the type would round to infinity starts with the type's largest; infinities and NaN are one
+        // term (what is left of them would be NaN).
+        uint32_t h = DT == DT_BF16 ? f32_to_bf16_bits(v) : f32_to_f16_bits(v);
+        const bool finite = (__float_as_uint(v) & 0x7F800000u) != 0x7F800000u;
+        if (finite && (h & pred_inf<DT>()) == pred_inf<DT>()) h = (h & 0x8000u) | (pred_inf<DT>() - 1u);
+        const float left = v - (DT == DT_BF16 ? bf16_bits_to_f32(h) : f16_bits_to_f32(h));
+        v = finite ? left : 0.f;
         return h;
     }
 }
@@ -478,7 +483,7 @@ __device__ __forceinline__ void predict_block(const PredArgs &p, int e, int bz, 
             m = fmaxf(m, dpp_get<0x140>(m));
             m = max_xor16(m);                                // over the 32 lanes of a vector
             int ex = (int)(__float_as_uint(m) >> 23) - 127;
-            ex = ex < -100 ? -100 : ex > 120 ? 120 : ex;
+            ex = ex < -100 ? -100 : ex;                      // at most 128 (infinity): both scales are normal numbers
             if (i == 0) misc[8 + (is_b ? 1 : 0)] = (uint32_t)(127 + ex - 14) << 23;
             v *= __uint_as_float((uint32_t)(127 - ex + 14) << 23);
         }

@@ -1763,6 +1763,48 @@ def test_one_launch_keeps_non_finite_values_apart(ctx, dtype, value, where, M, N
     assert np.isinf(top) if np.isinf(value) else np.isfinite(top)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("value", [np.inf, 3.3995e38])
+@pytest.mark.parametrize("M,N,K,trans_b", [(70, 200, 300, True), (150, 72, 300, False)])
+def test_one_launch_vectors_at_the_end_of_fp32(ctx, dtype, value, M, N, K, trans_b):
+    """a (supplied) and b (the encoding of another B) with an Inf, or with a finite value that the operand type rounds
+    to Inf: the predictions are what fp32 products and sums give, infinities with their signs."""
+    A, B = gen.gen_operands(dtype, M, N, K, 53, 54, trans_b=trans_b, batch=1, a_kind="weight")
+    run = Run(ctx, dtype, A, B, trans_b)
+    Ad, Bd = orc.decode(A[0], dtype).astype(np.float64), orc.decode(B[0], dtype).astype(np.float64)
+    Bd = Bd.T if trans_b else Bd                                          # K x N
+    k = 131
+    a = np.random.default_rng(55).standard_normal(K).astype(np.float32)
+    a[k] = value
+    other = B.copy()
+    column = other[0, :, k] if trans_b else other[0, k]
+    if np.isinf(value):
+        column[7] = 0x7F80 if dtype == "bf16" else 0x7C00
+    elif dtype == "bf16":
+        column[:] = 0
+        column[7], column[9] = 0x7F7F, 0x7B40                             # 3.3895e38 + 1.0e36
+    dec = orc.decode(other[0], dtype).astype(np.float64)
+    b = dec.sum(axis=0 if trans_b else 1)
+    # an encoding of `other`, then a call with B that takes it
+    full = run.dB.clone()
+    full[:, :, :other.shape[2]] = torch.from_numpy(other.view(np.int16)).to("cuda")
+    assert ab.abft_encode_b(ctx, full, run.code, run.shape) == ab.ABFT_OK
+    a_dev = torch.from_numpy(a).to("cuda")
+    assert ab.abft_supply_a(ctx, a_dev, None) == ab.ABFT_OK
+    run.tau = 1.0
+    run.gemm(ab.ABFT_DETECT | ab.ABFT_A_CHECKSUM_GIVEN | ab.ABFT_B_CHECKSUM_CACHED)
+    a = a.astype(np.float64)
+    for which, X, v in ((ab.ABFT_WS_CC_PRED, Bd.T, a), (ab.ABFT_WS_RC_PRED, Ad, b)):
+        with np.errstate(invalid="ignore"):
+            want = X @ v
+            # K products, rounded when they are added in fp32; b itself is a sum of N (here M, N <= K)
+            bound = 2 * K * 2.0 ** -24 * (np.abs(X) @ np.abs(v))
+        got = run.ws(which)[0]
+        fin = np.isfinite(want)
+        assert np.array_equal(got[~fin], want[~fin], equal_nan=True)
+        assert np.all(np.abs(got[fin] - want[fin]) <= bound[fin])
+
+
 # (M, N, K, batch, trans_b): one workgroup per item, where its kernels' blocks, rings and chunks end
 ITEM_EDGES = [
     (300, 128, 96, 64, True),       # the widest item whose waves own rows; two blocks of rows for some waves
