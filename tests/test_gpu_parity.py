@@ -5,6 +5,8 @@ Bars: integer C, checksums (in Z/2^32), flags and counts bit-exact; bf16/fp16 C 
 max|C_ref| (and within one rounding of the storage type element-wise); fp32 checksums within a
 small fraction of the tolerance tau = 1e-3 K max|A| max|B|; flags equal except for flips whose
 |delta| lies within a factor two of tau."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -12,7 +14,7 @@ import torch
 import abft_inputs as gen
 import oracle as orc
 import paper_2310_03841_amd as ab
-from abft_harness import Run
+from abft_harness import Run, _DevView
 
 pytestmark = pytest.mark.gpu
 
@@ -1692,8 +1694,9 @@ ONE_LAUNCH_EDGES = [
     (197, 768, 1540, 1, True),      # many ranges of K, the last of a few bytes
     (33, 65, 100, 17, True),        # more items than first-level tickets
     (64, 200, 1100, 1, False),
-    (300, 40, 1500, 1, False),      # narrow, A in blocks
-    (64, 1030, 900, 1, False),      # wide
+    (300, 40, 1500, 1, False),      # narrow; int8: A in blocks
+    (64, 500, 768, 1, False),       # wide (int8: two launches)
+    (64, 1030, 900, 1, False),      # too wide: two launches
     (50, 48, 390, 18, False),
 ]
 
@@ -1718,7 +1721,7 @@ ONE_LAUNCH_SHORT_BLOCKS = [
     (385, 64, 256, 1, True),
     (197, 577, 768, 1, True),
     (160, 577, 335, 1, True),       # the last range of K cut as well
-    (577, 64, 577, 4, False),       # attn V of one image
+    (577, 64, 577, 4, False),       # attn V of one image (int8: two launches)
 ]
 
 
@@ -1727,6 +1730,67 @@ ONE_LAUNCH_SHORT_BLOCKS = [
 def test_one_launch_short_last_block(ctx, dtype, M, N, K, batch, trans_b):
     """Every checksum vector and a clean verdict: no row of an operand is summed twice."""
     _clean_case(ctx, dtype, M, N, K, batch, trans_b)
+
+
+def _unit_tickets(run):
+    """The ticket words of a one-launch call's rows and columns of tiles, as it has left them in the context: behind the
+    sums that floating-point tiles add up in doubles, the predictions' doubles, and the lines of the other tickets."""
+    b, M, N, K = run.batch, run.M, run.N, run.K
+    words = (2 * b * N + 3 * b * M + b * K + 2 * b + 1) // 2 * 2
+    words += (0 if run.dtype == "i8" else 2 * b * (N + M)) + 2 * b * (N + M + 1)
+    tm, tn = ab.abft_tile_shape(run.code, run.shape)
+    tiles_m, tiles_n = -(-M // tm), -(-N // tn)
+    first = words + 16 * (1 + max(b, 17))
+    ptr, _ = ab.abft_workspace(run.ctx, ab.ABFT_WS_CC_OBS, run.shape)
+    n = first + 16 * b * (tiles_m + tiles_n)
+    torch.cuda.synchronize()
+    t = torch.as_tensor(_DevView(ptr, n, "<u4"), device="cuda").clone().cpu().numpy().view(np.uint32)
+    return t[first::16].reshape(b, tiles_m + tiles_n), tiles_m, tiles_n
+
+
+# late: the predictions take longer than the tiles, whatever the type
+@pytest.mark.parametrize("dtype,M,N,K,batch,trans_b,late", [(d, *s) for s, types in [
+    ((64, 2049, 97, 1, True, True), "i8 bf16 f16"),
+    ((33, 65, 100, 17, True, True), "i8 bf16 f16"),
+    ((1300, 70, 700, 1, True, False), "i8 bf16 f16"),       # A in blocks
+    ((64, 200, 1100, 1, False, False), "i8 bf16 f16"),
+    ((300, 40, 1500, 1, False, False), "i8"),               # A in blocks
+    ((64, 500, 3072, 1, False, False), "bf16 f16"),         # wide; tickets of two levels
+    ((197, 768, 3072, 1, True, False), "bf16 f16"),
+    ((50, 48, 390, 18, False, False), "bf16 f16"),
+] for d in types.split()])
+def test_one_launch_units_left_to_the_predictions(dtype, M, N, K, batch, trans_b, late):
+    """Tiles that do not wait for the predictions leave their rows and columns to the last workgroup that forms them:
+    clean calls, and an accumulator flip, whoever compares.  The tickets also show that the call is one launch."""
+    ctx = ab.abft_create(max_rows=batch * M, max_cols=batch * N, max_depth=batch * (K + 127), max_batch=batch)
+    try:
+        L = ab.lib()
+        L.abft_test_polls.argtypes = [ctypes.c_void_p, ctypes.c_int]
+        assert L.abft_test_polls(ctx, -1) == ab.ABFT_EINVAL
+        assert L.abft_test_polls(ctx, 0) == ab.ABFT_OK
+        _clean_case(ctx, dtype, M, N, K, batch, trans_b)
+        A, B = gen.gen_operands(dtype, M, N, K, 61, 62, trans_b=trans_b, batch=batch)
+        run = Run(ctx, dtype, A, B, trans_b)
+        left = 0
+        for n in range(6):
+            z, i, j = (batch - 1) * n // 5, (M - 1) * n // 5, (N - 1) * n // 5
+            if n % 2:
+                run.inject(z, i, j, 30, ab.ABFT_INJECT_ACCUMULATOR)
+            run.gemm()
+            t, tiles_m, tiles_n = _unit_tickets(run)
+            assert np.all(t[:, :tiles_m] & 0x1FFFF == 0x10000 | tiles_n)
+            assert np.all(t[:, tiles_m:] & 0x1FFFF == 0x10000 | tiles_m)
+            left += np.count_nonzero(t & 0x20000)
+            rf, cf = run.flags()
+            if n % 2 == 0:
+                assert not rf.any() and not cf.any() and list(run.cnt()[:5]) == [0] * 5
+            else:
+                assert np.argwhere(rf).tolist() == [[z, i]] and np.argwhere(cf).tolist() == [[z, j]]
+                assert list(run.cnt()[:5]) == [1, 1, ab.ABFT_LOCALISED, 0, ab.ABFT_LOCALISED]
+        print("units left:", left, flush=True)
+        assert left > 0 or not late
+    finally:
+        ab.abft_destroy(ctx)
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
