@@ -41,7 +41,6 @@ struct abft_ctx {
     bool vobs_captured;     // ... and they were formed by a call enqueued under capture
     const void *vobs_C;     // the stored C the re-summed vectors belong to (with its ldc and batch stride)
     int64_t vobs_ldc, vobs_strideC;
-    int polls;              // ONE_LAUNCH_POLLS, or what a test has set
     bool list_dirty;        // the tile list's counters may be non-zero (a correction failed half way)
     int b_dt, pred_dt;
     const void *given_a, *given_amax;   // abft_supply_a: a = e^T A and max|A| for the next call with ABFT_A_CHECKSUM_GIVEN
@@ -128,7 +127,6 @@ static void start_clean(abft_ctx *c)
     c->bslot_words = D + Bt;
     c->bslot = 0;
     c->bclean[0] = c->bclean[1] = true;
-    c->polls = ONE_LAUNCH_POLLS;
 }
 
 extern "C" int abft_create(abft_ctx **out, const abft_config *cfg)
@@ -439,7 +437,7 @@ static int enqueue_tiled(abft_ctx *ctx, int dtype, bool cached, bool stored, con
     const bool one = gemm_one_launch(dtype, sh) != 0;
     // the kernel that ends the call also cleans, for calls to come, the region of the previous call and the b slot that is
     // not in use
-    OneLaunch end = {v, ctx->polls, nullptr, nullptr, 0, 0};
+    OneLaunch end = {v, nullptr, nullptr, 0, 0};
     if (!gm) {
         const int other = ctx->bslot ^ 1;
         end.zero_ptr = prev_base;
@@ -669,15 +667,6 @@ extern "C" int abft_gemm_done_event(abft_ctx *ctx, void *event)
 {
     if (!ctx) return ABFT_EINVAL;
     ctx->done_event = (hipEvent_t)event;
-    return ABFT_OK;
-}
-
-// Not part of the interface: with 0, tests of one-launch calls see units left to the workgroups of the predictions, which
-// otherwise happens on a busy chip only.
-extern "C" int abft_test_polls(abft_ctx *ctx, int polls)
-{
-    if (!ctx || polls < 0 || polls > ONE_LAUNCH_POLLS) return ABFT_EINVAL;
-    ctx->polls = polls;
     return ABFT_OK;
 }
 

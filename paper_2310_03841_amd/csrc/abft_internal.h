@@ -114,13 +114,9 @@ constexpr int64_t ONE_LAUNCH_MAX_LEN = 16384, ONE_LAUNCH_MAX_BATCH = 64;
 // Most tile rows and tile columns over all batch items, and most words of tickets.
 constexpr int ONE_LAUNCH_MAX_UNITS = 320;
 constexpr size_t ONE_LAUNCH_TICKET_WORDS = (1 + (size_t)ONE_LAUNCH_MAX_BATCH + ONE_LAUNCH_MAX_UNITS) * 16;
-// How often the last tile of a row or column of tiles looks for the predictions, about half a microsecond each, before it
-// leaves the comparison to the workgroups that form them.
-constexpr int ONE_LAUNCH_POLLS = 64;
-// What such a launch takes besides: where the verdict goes, how often its tiles look, and regions its workgroups help to clear.
+// What such a launch takes besides: where the verdict goes, and regions its workgroups help to clear.
 struct OneLaunch {
     Verdict v;
-    int polls;
     uint32_t *zero_ptr, *zero2_ptr;
     size_t zero_words, zero2_words;
 };

@@ -863,7 +863,6 @@ hipError_t launch_gemm(int dt, bool protect, bool stored_sums, bool encode_b, co
         p.a_sum = w.a_sum; p.b_sum = w.b_sum; p.a_max = w.a_max; p.b_max = w.b_max;
         p.cc_pacc = w.cc_pacc; p.rc_pacc = w.rc_pacc; p.s_pacc = w.s_pacc;
         p.tickets = w.tickets;
-        p.polls = one->polls;
         p.amax_in = (w.a_given && w.amax_given) ? w.amax_given : w.a_max;
         p.cc_obs = w.cc_obs; p.rc_obs = w.rc_obs; p.cc_acc = w.cc_acc; p.rc_acc = w.rc_acc;
         p.bias = w.bias;

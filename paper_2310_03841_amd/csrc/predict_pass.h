@@ -24,7 +24,7 @@
 // The comparison: a tile row of C is a unit, and so is a tile column.  Every workgroup waits for its additions to arrive
 // and then draws tickets: a tile those of its two units, the workgroups of the predictions one of their own, whose last
 // holder tells every unit that they are complete.  A unit is compared by its last tile.  If the predictions are not complete by
-// then it looks for them again for a while (ONE_LAUNCH_POLLS); if they still are not, it leaves the unit to the last of their
+// then it looks for them again for a while (POLLS); if they still are not, it leaves the unit to the last of their
 // workgroups.  So nobody has to wait, and the order in which workgroups run does not matter.  (One last workgroup for
 // everything reads what others have added at 7 KB per us: 7.7 us of a bf16 197 x 3072 x 768.  Tickets on one word are served
 // one after the other: 256 workgroups, launch and end 6.6 us, with sixteen words in front 4.5; a second kernel instead
@@ -58,7 +58,6 @@ struct PredArgs {
     int wgs;                         // workgroups of a batch item
     int batch;
     int tiles_m, tiles_n, bm, bn;    // units: tile rows, then tile columns
-    int polls;                       // ONE_LAUNCH_POLLS
     uint32_t *tickets;               // lines of TICKET_LINE words: [0] units done and what they flagged; [1 ..] of the
                                      // predictions: one for each batch item, of a single problem PRED_GROUPS + 1; then the units'
     const uint32_t *amax_in;         // max|A| (a_max, or the caller's)
@@ -79,6 +78,8 @@ constexpr int PRED_TWO_LEVELS = 160;         // from this many of them on
 constexpr int TICKET_LINE = 16;              // words
 // a unit's ticket word: its tiles that have ended, and
 constexpr uint32_t UNIT_TILES = 0xFFFFu, UNIT_PREDICTED = 0x10000u, UNIT_LEFT = 0x20000u;
+constexpr uint32_t UNIT_NO_WAIT = 0x40000u;  // in the word before the call (tests put it there): the last tile does not look again
+constexpr int POLLS = 64;                    // about half a microsecond each
 __host__ __device__ constexpr int unit_line0(int batch) { return 1 + (batch > PRED_GROUPS + 1 ? batch : PRED_GROUPS + 1); }
 constexpr int PRED_STEP_BYTES = 256 * 16;
 constexpr int PRED_CHUNKS = 4;               // 16-byte pieces of a row in a range of K
@@ -643,7 +644,7 @@ __device__ __forceinline__ void end_tile(const PredArgs &p, int tm, int tn, int 
         uint32_t *t = p.tickets + (unit_line0(p.batch) + (long)bz * (p.tiles_m + p.tiles_n) + unit) * TICKET_LINE;
         uint32_t mine = 0u, w = draw_ticket(t);
         if ((w & UNIT_TILES) == (unsigned)(tid == 0 ? p.tiles_n : p.tiles_m) - 1) {      // the last tile
-            for (int i = 0; i < p.polls && !(w & UNIT_PREDICTED); ++i) w = shared_word(t);
+            for (int i = 0; i < POLLS && !(w & (UNIT_PREDICTED | UNIT_NO_WAIT)); ++i) w = shared_word(t);
             if (!(w & UNIT_PREDICTED)) w = draw_ticket(t, UNIT_LEFT);
             mine = w & UNIT_PREDICTED ? 1u : 0u;
         }

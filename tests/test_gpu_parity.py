@@ -5,8 +5,6 @@ Bars: integer C, checksums (in Z/2^32), flags and counts bit-exact; bf16/fp16 C 
 max|C_ref| (and within one rounding of the storage type element-wise); fp32 checksums within a
 small fraction of the tolerance tau = 1e-3 K max|A| max|B|; flags equal except for flips whose
 |delta| lies within a factor two of tau."""
-import ctypes
-
 import numpy as np
 import pytest
 import torch
@@ -1733,8 +1731,9 @@ def test_one_launch_short_last_block(ctx, dtype, M, N, K, batch, trans_b):
 
 
 def _unit_tickets(run):
-    """The ticket words of a one-launch call's rows and columns of tiles, as it has left them in the context: behind the
-    sums that floating-point tiles add up in doubles, the predictions' doubles, and the lines of the other tickets."""
+    """The ticket words of the rows and columns of tiles, [batch][tile rows, then tile columns], in the region that the
+    last one-launch call used: behind the sums that floating-point tiles add up in doubles, the predictions' doubles, and
+    the lines of the other tickets."""
     b, M, N, K = run.batch, run.M, run.N, run.K
     words = (2 * b * N + 3 * b * M + b * K + 2 * b + 1) // 2 * 2
     words += (0 if run.dtype == "i8" else 2 * b * (N + M)) + 2 * b * (N + M + 1)
@@ -1743,9 +1742,8 @@ def _unit_tickets(run):
     first = words + 16 * (1 + max(b, 17))
     ptr, _ = ab.abft_workspace(run.ctx, ab.ABFT_WS_CC_OBS, run.shape)
     n = first + 16 * b * (tiles_m + tiles_n)
-    torch.cuda.synchronize()
-    t = torch.as_tensor(_DevView(ptr, n, "<u4"), device="cuda").clone().cpu().numpy().view(np.uint32)
-    return t[first::16].reshape(b, tiles_m + tiles_n), tiles_m, tiles_n
+    t = torch.as_tensor(_DevView(ptr, n, "<i4"), device="cuda")
+    return t[first::16].view(b, tiles_m + tiles_n), tiles_m, tiles_n
 
 
 # late: the predictions take longer than the tiles, whatever the type
@@ -1760,24 +1758,27 @@ def _unit_tickets(run):
     ((50, 48, 390, 18, False, False), "bf16 f16"),
 ] for d in types.split()])
 def test_one_launch_units_left_to_the_predictions(dtype, M, N, K, batch, trans_b, late):
-    """Tiles that do not wait for the predictions leave their rows and columns to the last workgroup that forms them:
-    clean calls, and an accumulator flip, whoever compares.  The tickets also show that the call is one launch."""
+    """Tiles that do not wait for the predictions (a mark in their tickets, which no call leaves there) leave their rows
+    and columns to the last workgroup that forms those: clean calls, and an accumulator flip, whoever compares.  The
+    tickets also show that the call is one launch."""
     ctx = ab.abft_create(max_rows=batch * M, max_cols=batch * N, max_depth=batch * (K + 127), max_batch=batch)
     try:
-        L = ab.lib()
-        L.abft_test_polls.argtypes = [ctypes.c_void_p, ctypes.c_int]
-        assert L.abft_test_polls(ctx, -1) == ab.ABFT_EINVAL
-        assert L.abft_test_polls(ctx, 0) == ab.ABFT_OK
-        _clean_case(ctx, dtype, M, N, K, batch, trans_b)
         A, B = gen.gen_operands(dtype, M, N, K, 61, 62, trans_b=trans_b, batch=batch)
         run = Run(ctx, dtype, A, B, trans_b)
+        run.gemm()
+        before, _, _ = _unit_tickets(run)
+        run.gemm()
         left = 0
         for n in range(6):
+            # the calls alternate between two regions; the one the next call takes has been cleared
+            mark, (before, tiles_m, tiles_n) = before, _unit_tickets(run)
+            assert not mark.any()
+            mark.fill_(0x40000)                             # the last tile does not look again
             z, i, j = (batch - 1) * n // 5, (M - 1) * n // 5, (N - 1) * n // 5
             if n % 2:
                 run.inject(z, i, j, 30, ab.ABFT_INJECT_ACCUMULATOR)
             run.gemm()
-            t, tiles_m, tiles_n = _unit_tickets(run)
+            t = mark.cpu().numpy()
             assert np.all(t[:, :tiles_m] & 0x1FFFF == 0x10000 | tiles_n)
             assert np.all(t[:, tiles_m:] & 0x1FFFF == 0x10000 | tiles_m)
             left += np.count_nonzero(t & 0x20000)
