@@ -1682,6 +1682,51 @@ def test_general_kernel_tile_shapes(dtype, M, N, K, batch, trans_b):
         ab.abft_destroy(ctx)
 
 
+@pytest.mark.parametrize("dtype", ["i8", "bf16", "f16"])
+@pytest.mark.parametrize("M,N,K,batch", [
+    (1101, 1030, 13, 1),            # less than one chunk of int8
+    (1101, 1030, 403, 1),
+    (1101, 1030, 2069, 1),          # waves share a row
+    (1101, 1030, 403, 3),           # vectors of the items on any word
+])
+def test_check_kernel_ragged_depth(dtype, M, N, K, batch):
+    """Behind the general kernel, K no whole number of chunks: every vector; the same predictions from a supplied a that
+    lies on no 16 bytes; and an infinity in the last row and column of A, which reaches its own row and no other."""
+    ctx = ab.abft_create(max_rows=batch * M, max_cols=batch * N, max_depth=batch * (K + 127), max_batch=batch)
+    try:
+        _clean_case(ctx, dtype, M, N, K, batch, True)
+        A, B = gen.gen_operands(dtype, M, N, K, 71, 72, trans_b=True, batch=batch)
+        run = Run(ctx, dtype, A, B, True)
+        run.gemm()
+        cc, rc, a = (run.ws(w).copy() for w in (ab.ABFT_WS_CC_PRED, ab.ABFT_WS_RC_PRED, ab.ABFT_WS_A_SUM))
+        buf = torch.zeros(a.size + 1, dtype=torch.int32, device="cuda")
+        buf[1:] = torch.from_numpy(a.view(np.int32).reshape(-1)).to("cuda")
+        run.tau = 0.0 if dtype == "i8" else float(run.ws(ab.ABFT_WS_TAU).min())
+        assert ab.abft_supply_a(ctx, buf[1:], None) == ab.ABFT_OK
+        run.gemm(ab.ABFT_DETECT | ab.ABFT_A_CHECKSUM_GIVEN)
+        assert run.cnt()[2] == ab.ABFT_CLEAN
+        # bit for bit: the same sums in the same order
+        assert np.array_equal(run.ws(ab.ABFT_WS_CC_PRED), cc)
+        if dtype == "i8":
+            return
+        run.dA[batch - 1, M - 1, K - 1] = 0x7F80 if dtype == "bf16" else 0x7C00
+        run.gemm()
+        rf, cf = run.flags()
+        assert np.argwhere(rf).tolist() == [[batch - 1, M - 1]] and cf[batch - 1].all() and not cf[:-1].any()
+        got = run.ws(ab.ABFT_WS_RC_PRED)
+        last = np.zeros(got.shape, dtype=bool)
+        last[batch - 1, M - 1] = True
+        b_last = run.ws(ab.ABFT_WS_B_SUM)[batch - 1, K - 1]
+        assert got[last][0] == np.copysign(np.inf, b_last)
+        # b is added up by atomics, in another order each time
+        assert np.max(np.abs(got[~last] - rc[~last])) <= 1e-2 * run.tau * np.sqrt(N)
+        cols = orc.decode(B[batch - 1], dtype)[:, K - 1]
+        want = np.where(cols == 0, np.nan, np.copysign(np.inf, cols)).astype(np.float32)
+        assert np.array_equal(run.ws(ab.ABFT_WS_CC_PRED)[batch - 1], want, equal_nan=True)
+    finally:
+        ab.abft_destroy(ctx)
+
+
 # (M, N, K, batch, trans_b): calls of one launch, where the workgroups that form the predictions end: their 64 rows,
 # 64 bytes of K, waves, blocks of the operand that is split, and steps over a B stored K x N
 ONE_LAUNCH_EDGES = [
