@@ -244,7 +244,6 @@ static void carve(const abft_ctx *c, int dt, const Shape &s, Workspace *w)
     w->rc_pacc = w->cc_pacc + bN;
     w->s_pacc = w->rc_pacc + bM;
     w->tickets = reinterpret_cast<uint32_t *>(w->s_pacc + s.batch);
-    if (const size_t tickets = gemm_one_launch(dt, s)) w->zero_words = (size_t)(w->tickets - w->cc_obs) + tickets;
     w->cc_vobs = c->pool_vobs + (size_t)c->vcur * c->vregion_words;
     w->rc_vobs = w->cc_vobs + bN;
     w->fix_tiles = c->fix_tiles;
@@ -429,12 +428,14 @@ static int enqueue_tiled(abft_ctx *ctx, int dtype, bool cached, bool stored, con
     const uint32_t *bias = w->bias, *a_given = w->a_given, *amax_given = w->amax_given;
     carve(ctx, dtype, sh, w);
     w->bias = bias; w->a_given = a_given; w->amax_given = amax_given;
+    const size_t tickets = gemm_one_launch(dtype, sh);   // asked here only: it costs the host 0.1 to 0.2 us
+    const bool one = tickets != 0;
+    if (one) w->zero_words = (size_t)(w->tickets - w->cc_obs) + tickets;
     uint32_t *prev_base = ctx->pool_obs + (size_t)prev * ctx->region_words;
     size_t stale = ctx->dirty[ctx->cur];
     if (gm && stale < w->zero_words) stale = w->zero_words;
     ctx->dirty[ctx->cur] = ctx->region_words;            // until everything below is enqueued
     const bool fast = gemm_takes_fast(dtype, sh), rc_ready = fast || gemm_fuses_a(dtype, sh);
-    const bool one = gemm_one_launch(dtype, sh) != 0;
     // the kernel that ends the call also cleans, for calls to come, the region of the previous call and the b slot that is
     // not in use
     OneLaunch end = {v, nullptr, nullptr, 0, 0};

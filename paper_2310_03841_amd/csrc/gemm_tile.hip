@@ -52,8 +52,11 @@ struct TileArgs {
     uint32_t *bias_sum;           // protected, with a bias: its sum, formed by one more workgroup
     int fuse_bm;                  // host: rows of a tile of the instantiations with APASS, 0: the others
     int aux_off;                  // APASS: where the words of b and of a begin in LDS; ONE: the words of the predictions
-    PredArgs p;                   // ONE
 };
+// ONE alone takes the arguments of the predictions: what a launch copies, every call pays for.
+struct OneArgs : TileArgs { PredArgs p; };
+template <bool ONE> struct KernelArgs { typedef TileArgs type; };
+template <> struct KernelArgs<true> { typedef OneArgs type; };
 
 constexpr int TILE_STAGE_ROW = 36;                               // words per staged row of a 32 x 32 block (32 + pad)
 constexpr int TILE_STAGE_WAVE = 32 * TILE_STAGE_ROW * 4;
@@ -74,7 +77,7 @@ template <int ES, int ROWB> __device__ __forceinline__ int kn_swizzle(int k)
 
 // ONE: the whole protected call (predict_pass.h)
 template <int DT, int BM, int BN, int NS, bool PROT, bool TRANSB, bool APASS, bool ONE>
-__global__ __launch_bounds__(256) void gemm_tile_kernel(TileArgs a)
+__global__ __launch_bounds__(256) void gemm_tile_kernel(typename KernelArgs<ONE>::type a)
 {
     using T = Traits<DT>;
     typedef typename T::acc_t acc_t;
@@ -542,7 +545,7 @@ __global__ __launch_bounds__(256) void gemm_tile_kernel(TileArgs a)
 static int slabs_of(int dt, int K) { return (int)(((long)K * elem_size(dt) + SLAB_BYTES - 1) / SLAB_BYTES); }
 
 template <int DT, int BM, int BN, int NS, bool PROT, bool TRANSB, bool APASS = false, bool ONE = false>
-static hipError_t launch_one(TileArgs &a, int batch, hipStream_t st)
+static hipError_t launch_one(OneArgs &a, int batch, hipStream_t st)
 {
     constexpr int smem_max = APASS || ONE ? 160 * 1024 : tile_lds_bytes(BM, BN, NS);
     static_assert(tile_lds_bytes(BM, BN, 1) >= 256 * 16 * 4, "the passes over A and B use 16 KB");
@@ -636,7 +639,7 @@ static void tile_size(int M, int N, int nslab, int batch, bool beside, int *bm, 
 }
 
 template <int DT, int BM, int BN, int NS>
-static hipError_t launch_cfg(bool protect, bool transB, TileArgs &a, int batch, hipStream_t st)
+static hipError_t launch_cfg(bool protect, bool transB, OneArgs &a, int batch, hipStream_t st)
 {
     a.g.tiles_m = (a.g.M + BM - 1) / BM;
     a.g.tiles_n = (a.g.N + BN - 1) / BN;
@@ -659,7 +662,7 @@ static hipError_t launch_cfg(bool protect, bool transB, TileArgs &a, int batch, 
 // 14.5 with three); otherwise three, for more workgroups on a compute unit (6304 x 768 x 768 on 64 x 64
 // tiles: 17.3 us against 20.2 with four).
 template <int DT>
-static hipError_t launch_tile(bool protect, bool transB, TileArgs &a, int batch, hipStream_t st)
+static hipError_t launch_tile(bool protect, bool transB, OneArgs &a, int batch, hipStream_t st)
 {
     int bm = a.fuse_bm, bn = 128;
     if (!bm) tile_size(a.g.M, a.g.N, slabs_of(DT, a.g.K), batch, protect, &bm, &bn);
@@ -821,7 +824,7 @@ hipError_t launch_gemm(int dt, bool protect, bool stored_sums, bool encode_b, co
     // 256 items 24.4 -> 25.0 us): such a call is tiled, C comes out bit for bit the same.
     if (!protect && !w.bias && arm.batch < 0 && gemm_item_eligible(dt, s, false, false))
         return launch_gemm_item(dt, false, false, false, A, B, C, s, w, nullptr, arm, st);
-    TileArgs a;
+    OneArgs a;
     GemmArgs &g = a.g;
     g.A = (const uint8_t *)A;
     g.B = (const uint8_t *)B;
