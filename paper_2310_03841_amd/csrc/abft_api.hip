@@ -428,7 +428,7 @@ static int enqueue_tiled(abft_ctx *ctx, int dtype, bool cached, bool stored, con
     const uint32_t *bias = w->bias, *a_given = w->a_given, *amax_given = w->amax_given;
     carve(ctx, dtype, sh, w);
     w->bias = bias; w->a_given = a_given; w->amax_given = amax_given;
-    const size_t tickets = gemm_one_launch(dtype, sh);   // asked here only: it costs the host 0.1 to 0.2 us
+    const size_t tickets = gemm_one_launch(dtype, sh, cached);   // asked here only: it costs the host 0.1 to 0.2 us
     const bool one = tickets != 0;
     if (one) w->zero_words = (size_t)(w->tickets - w->cc_obs) + tickets;
     uint32_t *prev_base = ctx->pool_obs + (size_t)prev * ctx->region_words;

@@ -107,8 +107,8 @@ bool gemm_takes_fast(int dt, const Shape &s);
 bool gemm_fuses_a(int dt, const Shape &s);
 // Whether a protected call of the problem is one launch of the general kernel: both predictions and the
 // comparison inside it (predict_pass.h).
-// Returns the words of its tickets, 0: it is not.
-size_t gemm_one_launch(int dt, const Shape &s);
+// Returns the words of its tickets, 0: it is not.  b_given: B e is there already.
+size_t gemm_one_launch(int dt, const Shape &s, bool b_given);
 // Most rows of C, and most columns, over all batch items, and most batch items of such a problem.
 constexpr int64_t ONE_LAUNCH_MAX_LEN = 16384, ONE_LAUNCH_MAX_BATCH = 64;
 // Most tile rows and tile columns over all batch items, and most words of tickets.

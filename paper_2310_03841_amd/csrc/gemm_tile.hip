@@ -5,8 +5,8 @@
 //
 // What bounds these problems is not arithmetic or bandwidth but the chain of latencies of a call.
 // A call of few tiles is therefore one launch (predict_pass.h): workgroups beside the tiles form both predictions, and who
-// is last compares.  Call after call, in us, two launches / one: int8 197 x 768 x 768 10.1 / 7.7, bf16 197 x 3072 x 768 13.1 /
-// 10.6, 197 x 768 x 3072 18.0 / 15.3, int8 3000 x 128 x 1024 15.2 / 9.2.  (A call takes 3 us before its first and after its
+// is last compares.  Call after call, in us, two launches / one: int8 197 x 768 x 768 8.7 / 7.5, 3000 x 128 x 1024 14.2 / 9.3, bf16
+// 197 x 768 x 3072 16.4 / 15.4, 64 x 500 x 3072 with B stored K x N 25.1 / 18.9.  (A call takes 3 us before its first and after its
 // last workgroup; a second kernel adds that gap, a trip to memory and a reduction.)
 // More tiles, or predictions that would take longer than they: the input-side vectors a = e^T A and b = B e, which depend
 // on nothing, are formed by extra workgroups of the same launch, beside the tiles; both predictions wait for the check
@@ -703,22 +703,25 @@ bool gemm_takes_fast(int dt, const Shape &s)
     return tiles >= 64 && gemm_fast_eligible(dt, s.M, s.N, s.K, s.transB != 0, s.lda, s.ldb);
 }
 
+// Beside the tiles: about twelve row blocks, of one to eight batches of loads per thread.  The
+// additions of the row blocks meet in the same words, which are served one after the other, and the
+// last of them ends the launch: 6304 x 768 x 768 with 99 / 32 / 16 / 8 row blocks of A 26.6 / 22.8 /
+// 22.2 / 22.2 us, 1537 x 1001 x 713 with 24 / 16 / 8 of them 15.4 / 13.6 / 13.0 us.
+static int beside_batches(const EncPlan &p, int rows)
+{
+    const int per = 12 * (256 >> p.cw_log2) * ENC_UNROLL;
+    return std::min((rows + per - 1) / per, 8);
+}
+
 static EncArgs enc_args(const void *X, long ld, long stride, int rows, int cols, int K, int reduce_rows, int dt,
                         uint32_t *sum, uint32_t *max_acc)
 {
     EncArgs e;
     e.X = (const uint8_t *)X; e.ld = ld; e.stride = stride; e.rows = rows; e.cols = cols; e.K = K;
     e.reduce_rows = reduce_rows;
-    // Beside the tiles: about twelve row blocks, of one to eight batches of loads per thread.  The
-    // additions of the row blocks meet in the same words, which are served one after the other, and the
-    // last of them ends the launch: 6304 x 768 x 768 with 99 / 32 / 16 / 8 row blocks of A 26.6 / 22.8 /
-    // 22.2 / 22.2 us, 1537 x 1001 x 713 with 24 / 16 / 8 of them 15.4 / 13.6 / 13.0 us.
-    EncPlan p = plan_window(rows, cols, 16 / elem_size(dt));
-    const int batch_rows = (256 >> p.cw_log2) * ENC_UNROLL;
-    int batches = (rows + 12 * batch_rows - 1) / (12 * batch_rows);
-    batches = batches > 8 ? 8 : batches;
+    const EncPlan p = plan_window(rows, cols, 16 / elem_size(dt));
     e.cw_log2 = p.cw_log2; e.nwin = p.nwin;
-    e.rpb = batches * batch_rows;
+    e.rpb = beside_batches(p, rows) * (256 >> p.cw_log2) * ENC_UNROLL;
     e.nrb = (rows + e.rpb - 1) / e.rpb;
     e.sum = sum; e.max_acc = max_acc;
     return e;
@@ -731,10 +734,13 @@ static EncArgs enc_args(const void *X, long ld, long stride, int rows, int cols,
 // int8 237 x 2112 x 2112 with 264 / 99 workgroups 23.0 / 10.7).
 constexpr double PRED_STEP_US = 0.6, PRED_KN_STEP_US = 0.9, PRED_QUEUE_US = 0.02;
 constexpr int PRED_MAX_WGS = 512;
-// Additions of a launch, in doubles or words: with more, the tiles' own wait behind them (bf16 704 x 640 x 1709, 142 k:
-// 17.6 us, 14.8 in two launches; 197 x 768 x 3072, 111 k: 15.3 / 18.0).
-constexpr double PRED_MAX_ADDS = 115e3, PRED_MAX_ADDS_INT = 200e3;
-static double pred_plan(int dt, const Shape &s, int max_steps, PredArgs *p)
+// Workgroups of a launch, tiles and all: with more than one to a compute unit the tiles and the predictions wait for each other.
+// One launch / two: 16-bit 1.03 to 1.27 on average, however long the predictions take (up to 256: 0.90 to 0.98); int8 0.88 to 0.94 up
+// to 80 k additions, 1.0 to 1.1 beyond, but 0.95 where B is split and b given, so that one block alone forms A b.  16-bit shares
+// are added in doubles: the tiles' own wait behind them (up to 120 k 0.92 to 0.97, to 160 k 0.96 to 1.02; 64 x 1536 x 3697, 193 k, 1.35).
+constexpr int ONE_LAUNCH_CUS = 256;
+constexpr double PRED_MAX_ADDS = 120e3, PRED_MAX_ADDS_SHARED = 80e3;
+static double pred_plan(int dt, const Shape &s, bool b_given, int max_steps, long tiles, PredArgs *p)
 {
     const int ce = 16 / elem_size(dt), kr = PRED_CHUNKS * ce;
     auto steps = [](int n, int per) { return (n + per - 1) / per; };
@@ -746,7 +752,9 @@ static double pred_plan(int dt, const Shape &s, int max_steps, PredArgs *p)
         if (whole + split > max_steps || nkr * nblk > PRED_MAX_WGS) return;
         const double adds = (double)s.batch * nkr * (split_b ? (double)nblk * s.M + s.N : (double)nblk * s.N + s.M);
         const double cost = chain + PRED_QUEUE_US * nkr * nblk;
-        if (adds > (dt == DT_I8 ? PRED_MAX_ADDS_INT : PRED_MAX_ADDS) || (best >= 0.0 && cost >= best)) return;
+        const bool shares = tiles + (long)s.batch * nkr * nblk > ONE_LAUNCH_CUS;
+        if (dt != DT_I8 ? shares || adds > PRED_MAX_ADDS : shares && adds > PRED_MAX_ADDS_SHARED && !(split_b && b_given)) return;
+        if (best >= 0.0 && cost >= best) return;
         best = cost;
         p->nkr = nkr; p->nblk = nblk; p->split_b = split_b; p->blk_len = len;
         p->a_steps = split_b ? whole : split;
@@ -785,13 +793,17 @@ static double pred_plan(int dt, const Shape &s, int max_steps, PredArgs *p)
 // Steps of LDS a workgroup of the predictions takes at most: what fits the LDS of the tiles beside it.
 static int pred_max_steps(int bm, int bn, int ns) { return (tile_lds_bytes(bm, bn, ns) - PRED_VEC_WORDS * 4) / PRED_STEP_BYTES; }
 
-// One launch, unless the predictions take longer than the tiles by more than the check kernel behind two launches costs.  Of
-// 400 problems (linear layers of up to 2200 tiles, up to 63 attention items, three types, both layouts of B) it takes 196, which
-// then take 0.84 of their time (0.59 to 1.12, five of them more than 1.05).  Batches of more workgroups than are resident at once
-// lose by it (bf16 151 x 80 x 151, 41 items 11.3 -> 12.6 us).
+// One launch, unless the predictions take longer than the tiles by more than the check kernel behind two launches costs: by the
+// estimate, `longer` us.  One launch / two, averages over 8000 problems (linear layers, up to 63 attention items, three types, both
+// layouts of B, cached or not), on this side of the line and half a us or 64 of K on the other:
+//   B stored N x K  int8 0.86 | 0.93 (and up to 1.09); 16-bit 0.93 | 1.01, of a given b with B split, where one block alone forms
+//                   A b, 0.93 | 1.02; where a pass over A or B beside the tiles of two launches would outlast them 0.90 | 0.95
+//   B stored K x N  by its depth, which the check kernel goes through 512 at a time: 0.66 int8, 0.87 16-bit | 1.04, 1.01; batches
+//                   0.95 | 1.0
 constexpr int ONE_LAUNCH_MAX_TILES = 512, ONE_LAUNCH_MAX_BATCH_WGS = 440;
-static bool one_launch_plan(int dt, const Shape &s, PredArgs *p, int *units)
+static bool one_launch_plan(int dt, const Shape &s, bool b_given, PredArgs *p, int *units)
 {
+    if (!s.transB && s.K <= (s.batch > 1 ? 512 : 384)) return false;
     if (gemm_takes_fast(dt, s) || s.batch > ONE_LAUNCH_MAX_BATCH || (long)s.batch * s.M > ONE_LAUNCH_MAX_LEN ||
         (long)s.batch * s.N > ONE_LAUNCH_MAX_LEN)
         return false;
@@ -804,16 +816,22 @@ static bool one_launch_plan(int dt, const Shape &s, PredArgs *p, int *units)
     *units = ((s.M + bm - 1) / bm + (s.N + bn - 1) / bn) * s.batch;
     if (tiles > ONE_LAUNCH_MAX_TILES || *units > ONE_LAUNCH_MAX_UNITS) return false;
     p->nkr = p->nblk = 0;
-    const double pred = pred_plan(dt, s, pred_max_steps(bm, bn, bn == 64 && tiles <= 256 ? 4 : 3), p);
+    const double pred = pred_plan(dt, s, b_given, pred_max_steps(bm, bn, bn == 64 && tiles <= 256 ? 4 : 3), tiles, p);
     if (s.batch > 1 && tiles + (long)s.batch * p->nkr * p->nblk > ONE_LAUNCH_MAX_BATCH_WGS) return false;
-    return pred >= 0.0 && pred <= 0.28 * nslab + (s.transB ? 2.0 : 1.2);
+    auto pass = [&](int rows) { return 0.9 * beside_batches(plan_window(rows, s.K, 16 / elem_size(dt)), rows); };
+    double longer = 1.75;
+    if (s.transB) {
+        const double passes = std::max(pass(s.M), b_given ? 0.0 : pass(s.N));
+        longer = dt == DT_I8 || (s.batch == 1 && passes > 0.28 * nslab + 3.0) ? 2.0 : b_given && p->split_b && s.batch == 1 ? 1.0 : 0.5;
+    }
+    return pred >= 0.0 && pred <= 0.28 * nslab + longer;
 }
 
-size_t gemm_one_launch(int dt, const Shape &s)
+size_t gemm_one_launch(int dt, const Shape &s, bool b_given)
 {
     PredArgs p;
     int units;
-    return one_launch_plan(dt, s, &p, &units) ? (size_t)(unit_line0(s.batch) + units) * TICKET_LINE : 0;
+    return one_launch_plan(dt, s, b_given, &p, &units) ? (size_t)(unit_line0(s.batch) + units) * TICKET_LINE : 0;
 }
 
 hipError_t launch_gemm(int dt, bool protect, bool stored_sums, bool encode_b, const void *A, const void *B, void *C,
@@ -856,7 +874,7 @@ hipError_t launch_gemm(int dt, bool protect, bool stored_sums, bool encode_b, co
     a.n_extra = a.n_enc_a + a.n_enc_b + (protect && w.bias && !a.fuse_bm ? 1 : 0);
     PredArgs &p = a.p;
     int units = 0;
-    p.one_launch = protect && one && one_launch_plan(dt, s, &p, &units) ? 1 : 0;
+    p.one_launch = protect && one && one_launch_plan(dt, s, !encode_b, &p, &units) ? 1 : 0;
     if (p.one_launch) {
         p.A = g.A; p.B = g.B;
         p.lda = s.lda; p.ldb = s.ldb; p.sA = s.sA; p.sB = s.sB;

@@ -1732,15 +1732,16 @@ def test_check_kernel_ragged_depth(dtype, M, N, K, batch):
 ONE_LAUNCH_EDGES = [
     (1, 64, 16, 1, True),
     (65, 129, 130, 1, True),
-    (64, 2049, 97, 1, True),        # B in blocks
+    (64, 2049, 97, 1, True),        # B in blocks (16-bit: two launches)
     (1300, 70, 700, 1, True),       # A in blocks
     (197, 768, 1540, 1, True),      # many ranges of K, the last of a few bytes
     (33, 65, 100, 17, True),        # more items than first-level tickets
     (64, 200, 1100, 1, False),
     (300, 40, 1500, 1, False),      # narrow; int8: A in blocks
-    (64, 500, 768, 1, False),       # wide (int8: two launches)
+    (64, 500, 768, 1, False),       # wide
     (64, 1030, 900, 1, False),      # too wide: two launches
-    (50, 48, 390, 18, False),
+    (50, 48, 390, 18, False),       # too shallow: two launches
+    (50, 48, 600, 6, False),
 ]
 
 
@@ -1764,7 +1765,8 @@ ONE_LAUNCH_SHORT_BLOCKS = [
     (385, 64, 256, 1, True),
     (197, 577, 768, 1, True),
     (160, 577, 335, 1, True),       # the last range of K cut as well
-    (577, 64, 577, 4, False),       # attn V of one image (int8: two launches)
+    (577, 64, 577, 4, False),       # attn V of one image (16-bit: two blocks)
+    (577, 48, 577, 3, False),
 ]
 
 
@@ -1793,14 +1795,16 @@ def _unit_tickets(run):
 
 # late: the predictions take longer than the tiles, whatever the type
 @pytest.mark.parametrize("dtype,M,N,K,batch,trans_b,late", [(d, *s) for s, types in [
-    ((64, 2049, 97, 1, True, True), "i8 bf16 f16"),
+    ((64, 2049, 97, 1, True, True), "i8"),
     ((33, 65, 100, 17, True, True), "i8 bf16 f16"),
     ((1300, 70, 700, 1, True, False), "i8 bf16 f16"),       # A in blocks
     ((64, 200, 1100, 1, False, False), "i8 bf16 f16"),
     ((300, 40, 1500, 1, False, False), "i8"),               # A in blocks
     ((64, 500, 3072, 1, False, False), "bf16 f16"),         # wide; tickets of two levels
     ((197, 768, 3072, 1, True, False), "bf16 f16"),
-    ((50, 48, 390, 18, False, False), "bf16 f16"),
+    ((64, 500, 768, 1, False, False), "i8 bf16 f16"),
+    ((50, 48, 600, 6, False, False), "i8 bf16 f16"),
+    ((577, 48, 577, 3, False, False), "i8 bf16 f16"),
 ] for d in types.split()])
 def test_one_launch_units_left_to_the_predictions(dtype, M, N, K, batch, trans_b, late):
     """Tiles that do not wait for the predictions (a mark in their tickets, which no call leaves there) leave their rows
@@ -1842,7 +1846,7 @@ def test_one_launch_units_left_to_the_predictions(dtype, M, N, K, batch, trans_b
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 @pytest.mark.parametrize("value", [np.inf, np.nan])
 @pytest.mark.parametrize("where", ["A", "B"])
-@pytest.mark.parametrize("M,N,K,trans_b", [(70, 200, 300, True), (150, 72, 300, False)])
+@pytest.mark.parametrize("M,N,K,trans_b", [(70, 200, 300, True), (150, 72, 300, False), (150, 72, 450, False)])
 def test_one_launch_keeps_non_finite_values_apart(ctx, dtype, value, where, M, N, K, trans_b):
     """One Inf or NaN in an operand: its own row (column) of C is flagged and no other is, and the operand's sums over its
     other columns are those of the run without it (A's whole predictions of other rows too)."""
@@ -1875,7 +1879,7 @@ def test_one_launch_keeps_non_finite_values_apart(ctx, dtype, value, where, M, N
 
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 @pytest.mark.parametrize("value", [np.inf, 3.3995e38])
-@pytest.mark.parametrize("M,N,K,trans_b", [(70, 200, 300, True), (150, 72, 300, False)])
+@pytest.mark.parametrize("M,N,K,trans_b", [(70, 200, 300, True), (150, 72, 450, False)])
 def test_one_launch_vectors_at_the_end_of_fp32(ctx, dtype, value, M, N, K, trans_b):
     """a (supplied) and b (the encoding of another B) with an Inf, or with a finite value that the operand type rounds
     to Inf: the predictions are what fp32 products and sums give, infinities with their signs."""
