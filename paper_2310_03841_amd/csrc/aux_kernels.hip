@@ -907,13 +907,15 @@ __global__ __launch_bounds__(64 * (FIX_WAVES + 1)) void recompute_kernel(FixArgs
 #pragma unroll
     for (int i = 0; i < 16; ++i) acc[i] = T::zero();
     const int steps = (K + 2 * CE - 1) / (2 * CE);
-    // Loads without a branch: what lies past the end asks for the last row, column or chunk and is cleared once
-    // all are under way.  (Under a branch each, or masked at once, every load is waited for before the next.)  Runs
-    // inside both operands have a path of their own without the masks: this code runs once per call, so its
-    // instructions come from memory and a long straight path costs what it saves (int8, K = 3072, flip, verify and repair:
-    // 32.8 us with a branch per load, 35.2 with masks for all, 31.9 so, on a card 3 % slower).
+    // Loads without a branch: what lies past the end asks for the last row, column or chunk.  (Under a branch each, or masked at
+    // once, every load is waited for before the next.)  Rows and columns past the end need no more: what they give is not
+    // stored.  Past the end of K a run is cleared once all of it is under way, by masks that both operands share: this code runs
+    // once per call, so its instructions come from memory and a long straight path costs what it saves.  (Flip, verify and
+    // repair, with a branch per load / with masks for rows, columns and K of every tile at an edge / so: f16 318 x 41 x 3456 36.0 /
+    // 37.7 / 33.3 us; bf16 231 x 310 x 3305 34.2 / 36.1 / 32.8.)
     const long rowc = min(row, a.M - 1), colc = min(col, a.N - 1);
     const int last_kb = (K - 1) / CE * CE;
+    const i32x4 last_mask = mask_chunk(i32x4{-1, -1, -1, -1}, (K - last_kb) * ES);
     auto load_run = [&](int ks0, i32x4 (&av)[UB], i32x4 (&bv)[UB]) __attribute__((always_inline)) {
 #pragma unroll
         for (int u = 0; u < UB; ++u) {
@@ -951,9 +953,6 @@ __global__ __launch_bounds__(64 * (FIX_WAVES + 1)) void recompute_kernel(FixArgs
             }
         }
     };
-    auto inside = [&](int ks, bool ok) __attribute__((always_inline)) {      // bytes of a chunk inside the operand
-        return ok ? (K - (ks * 2 * CE + lh * CE)) * ES : 0;
-    };
     // every wave takes the same number of trips: the barriers are reached by all
     for (int g0 = 0; g0 < steps; g0 += FIX_WAVES * UB) {
         const int lw = wave - 1;                            // loading wave 0 .. FIX_WAVES - 1
@@ -961,9 +960,10 @@ __global__ __launch_bounds__(64 * (FIX_WAVES + 1)) void recompute_kernel(FixArgs
         i32x4 av[UB], bv[UB];
         const bool loads = wave != 0 && ks0 < steps;
         if (loads) {
-            if (a.transB && (ks0 + UB) * 2 * CE <= K && (tr + 1) * CT <= a.M && (tc + 1) * CT <= a.N) {
-                const uint8_t *pa = Ab + ((long)row * a.lda + ks0 * 2 * CE + lh * CE) * ES;
-                const uint8_t *pb = Bb + ((long)col * a.ldb + ks0 * 2 * CE + lh * CE) * ES;
+            const bool whole = (ks0 + UB) * 2 * CE <= K;
+            if (a.transB && whole) {
+                const uint8_t *pa = Ab + (rowc * a.lda + ks0 * 2 * CE + lh * CE) * ES;
+                const uint8_t *pb = Bb + (colc * a.ldb + ks0 * 2 * CE + lh * CE) * ES;
 #pragma unroll
                 for (int u = 0; u < UB; ++u) {
                     av[u] = *reinterpret_cast<const i32x4 *>(pa + 32 * u);
@@ -971,10 +971,17 @@ __global__ __launch_bounds__(64 * (FIX_WAVES + 1)) void recompute_kernel(FixArgs
                 }
             } else {
                 load_run(ks0, av, bv);
+                if (!whole) {
 #pragma unroll
-                for (int u = 0; u < UB; ++u) {
-                    av[u] = mask_chunk(av[u], inside(ks0 + u, row < a.M));
-                    bv[u] = mask_chunk(bv[u], inside(ks0 + u, col < a.N));
+                    for (int u = 0; u < UB; ++u) {
+                        const int kb = (ks0 + u) * 2 * CE + lh * CE;
+#pragma unroll
+                        for (int w = 0; w < 4; ++w) {
+                            const int keep = kb < last_kb ? -1 : kb == last_kb ? last_mask[w] : 0;
+                            av[u][w] &= keep;
+                            bv[u][w] &= keep;
+                        }
+                    }
                 }
             }
         }

@@ -1683,6 +1683,36 @@ def test_general_kernel_tile_shapes(dtype, M, N, K, batch, trans_b):
 
 
 @pytest.mark.parametrize("dtype", ["i8", "bf16", "f16"])
+@pytest.mark.parametrize("M,N,K,trans_b", [(33, 65, 1004, True), (70, 90, 200, True), (63, 33, 45, True), (70, 90, 1001, False)])
+def test_repair_in_the_last_tile(ctx, dtype, M, N, K, trans_b):
+    """The last element of C flips, in a tile that the problem fills in part: found, and restored bit for bit, with an
+    infinity in the row and the column of the operands that the tile's loads stop at."""
+    A, B = gen.gen_operands(dtype, M, N, K, 81, 82, trans_b=trans_b, batch=1)
+    run = Run(ctx, dtype, A, B, trans_b)
+    run.gemm()
+    C = run.C().copy()
+    run.inject(0, M - 1, N - 1, 30 if dtype == "i8" else 14)
+    run.verify()
+    rf, cf = run.flags()
+    assert np.argwhere(rf).tolist() == [[0, M - 1]] and np.argwhere(cf).tolist() == [[0, N - 1]]
+    run.correct()
+    assert np.array_equal(run.C(), C) and list(run.cnt()[:5]) == [0, 0, ab.ABFT_CLEAN, 1, ab.ABFT_LOCALISED]
+    if dtype == "i8":
+        return
+    # the rows and columns past the end are copies of the last: what they hold must reach no element of C
+    inf = 0x7F80 if dtype == "bf16" else 0x7C00
+    run.dA[0, M - 1, K - 1] = inf
+    run.dB[(0, N - 1, K - 1) if trans_b else (0, K - 1, N - 1)] = inf
+    run.gemm()
+    C = run.C().copy()
+    run.inject(0, M - 1, N - 2, 9)
+    run.verify()
+    run.correct()
+    got, want = orc.decode(run.C()[0], dtype), orc.decode(C[0], dtype)
+    assert np.array_equal(got, want, equal_nan=True)
+
+
+@pytest.mark.parametrize("dtype", ["i8", "bf16", "f16"])
 @pytest.mark.parametrize("M,N,K,batch", [
     (1101, 1030, 13, 1),            # less than one chunk of int8
     (1101, 1030, 403, 1),
