@@ -29,6 +29,13 @@
 // everything reads what others have added at 7 KB per us: 7.7 us of a bf16 197 x 3072 x 768.  Tickets on one word are served
 // one after the other: 256 workgroups, launch and end 6.6 us, with sixteen words in front 4.5; a second kernel instead
 // 7.1.)  The tickets lie in the region that the call accumulates into and are cleared with it.
+//
+// What orders all this: everything others read here, shares, sums and maxima, moves through atomics of device scope, which are
+// performed where all dies see them, and is read by atomic loads there.  A wave waits for its own with s_waitcnt vmcnt(0), which
+// on gfx9 counts atomics without a result too and falls when they have been performed; the barrier collects the waves; then the
+// ticket is drawn.  It is the sequence of the memory model for a release at device scope, without the write back of the L2 that
+// comes first for plain stores: none of those is handed over.  Whoever draws the last ticket so finds what was added
+// before the others were drawn, and asks for it behind the wait for the ticket and a barrier.
 #pragma once
 #include <type_traits>
 
