@@ -211,8 +211,6 @@ __device__ __forceinline__ void fast_tile(const GemmArgs &g, uint8_t *smem, int 
         // loads of each slab behind it outstanding" means everything issued before them has landed.
         asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"((NB - 1) * (GA + GB)) : "memory");
         ldfr(0, 0, 0);
-        // own_c: whether the slab can be one that this workgroup reduces (the first slab and the last
-        // two: the pass then runs ahead of the slab's MFMAs; the middle slabs have own_slab below)
         // the barrier of slab s: slab s + 1 is in place, the loads of `behind` slabs after it may be under way
         auto slab_barrier = [&](auto behind_c) __attribute__((always_inline)) {
             if constexpr (NB == 2) __syncthreads();
@@ -220,6 +218,8 @@ __device__ __forceinline__ void fast_tile(const GemmArgs &g, uint8_t *smem, int 
         };
         typedef std::integral_constant<int, NB - 2> all_behind;
         typedef std::integral_constant<int, 0> none_behind;
+        // own_c: whether the slab can be one that this workgroup reduces (the first slab and the last NB:
+        // the pass then runs ahead of the slab's MFMAs; the middle slabs have own_slab below)
         auto slab = [&](auto first_c, auto loads_c, auto own_c, int s) __attribute__((always_inline)) {
             constexpr bool LOADS = decltype(loads_c)::value;
             const int buf = s % NB, nbuf = (s + 1) % NB;
