@@ -177,8 +177,10 @@ int abft_encode_b(abft_ctx *ctx, const void *B, abft_dtype dtype, const abft_sha
  * column prediction a B from one read of B, compares both pairs (equality for ABFT_I8,
  * |difference| <= tau otherwise; NaN or Inf always flag) and writes flags, counts and status.
  * Other problems are two kernels: the GEMM, whose launch also holds workgroups that form a, b and
- * the two maxima, and the check kernel, which forms A b from another read of A as well.
- * A and B must stay unchanged until the check kernel has run.
+ * the two maxima, and the check kernel, which forms A b from another read of A as well.  Of these,
+ * problems of a few tiles are one kernel: the GEMM, whose launch also holds workgroups that form
+ * both predictions, and which compares and writes flags, counts and status itself.
+ * A and B must stay unchanged until the last of these kernels has run.
  * A batch of at least 64 small problems (per-head attention products: N <= 640, M <= 1024; a row
  * of K at most 1600 bytes for N <= 128, 384 for N <= 256, 256 beyond; operands and vectors of one item
  * fitting the local memory of a compute unit; with ABFT_STORED_SUMS only up to N = 256) is one kernel
@@ -202,7 +204,7 @@ int abft_gemm_bias(abft_ctx *ctx, const void *A, const void *B, const void *bias
 /* abft_gemm for callers that cannot allocate device memory: code under HIP graph capture, tight
  * serving loops, harnesses that forbid hipMalloc.  Same arguments (without a context), same
  * kernels, same results as abft_gemm; the workspace (checksum vectors, partial sums, tickets) is
- * a fixed array of about 4.4 MB inside the library's device image instead of the pools of a
+ * a fixed array of about 4.9 MB inside the library's device image instead of the pools of a
  * context, so the call allocates nothing, on the device or through any library.  Each GPU holds
  * its own copy of that array from the moment the library is loaded until the process ends; the
  * call uses the copy of the current device.  Limits (ABFT_EWORKSPACE beyond them):
@@ -239,8 +241,9 @@ int abft_supply_a(abft_ctx *ctx, const void *a, const void *amax);
  * kernels run beside it.  For that the GEMMs must not start together (they would share the chip, end
  * together and leave it idle during both check kernels, and that state persists).  `event` is a
  * caller-owned hipEvent_t that every following abft_gemm / abft_gemm_bias of this context (any
- * mode, also ABFT_OFF) records on its stream right behind its GEMM kernel, before the check
- * kernel; the caller lets the other stream wait for it (hipStreamWaitEvent) before that stream's
+ * mode, also ABFT_OFF) records on its stream right behind its GEMM kernel: before the check
+ * kernel, where there is one, at the end of the call where the GEMM kernel is all of it (small
+ * problems; see abft_gemm); the caller lets the other stream wait for it (hipStreamWaitEvent) before that stream's
  * first call, after which the streams stay half a step apart by themselves.  NULL stops the
  * recording.  Nothing is recorded while a call is being captured into a graph, nor by protected
  * calls of a context once one of its calls has been captured.  The event must stay
