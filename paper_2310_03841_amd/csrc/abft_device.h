@@ -251,6 +251,19 @@ __device__ __forceinline__ float wave_max(float v)
     return v;
 }
 
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v)
+{
+    auto up = [&](uint32_t w) __attribute__((always_inline)) { v = w > v ? w : v; };
+    up((uint32_t)dpp_mov<0xB1>((int)v));       // lane ^ 1
+    up((uint32_t)dpp_mov<0x4E>((int)v));       // lane ^ 2
+    up((uint32_t)dpp_mov<0x141>((int)v));      // i <-> 7 - i inside 8 lanes
+    up((uint32_t)dpp_mov<0x140>((int)v));      // i <-> 15 - i inside 16 lanes
+    auto p = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    v = p[0] > p[1] ? p[0] : p[1];
+    auto q = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    return q[0] > q[1] ? q[0] : q[1];
+}
+
 // Sum of the layer bias over its N entries, by the whole block (every thread gets the total).
 template <typename acc_t>
 __device__ __forceinline__ acc_t block_bias_sum(const uint32_t *bias, int N, acc_t *red4)

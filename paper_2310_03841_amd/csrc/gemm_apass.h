@@ -12,10 +12,22 @@
 // LDS slab layout (both GEMM kernels): row r is 128 bytes = eight 16-byte chunks, chunk c stored
 // in slot c ^ ((r >> 1) & 7).  Thread t reduces chunk c = t & 7 of rows (t >> 3) + 32 p.
 #pragma once
+#include <type_traits>
+
 #include "abft_device.h"
 #include "gemm_args.h"
 
 namespace abft {
+
+template <int I, int N, typename F> __device__ __forceinline__ void static_for(F &&f)
+{
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>{});
+        static_for<I + 1, N>(f);
+    }
+}
+
+constexpr int FAST_WAVES = 8;                         // of a workgroup of the fast kernel
 
 // Sum over each aligned group of 8 lanes; every lane of the group ends with the total.
 template <typename T> __device__ __forceinline__ T row8_sum(T v)
@@ -56,12 +68,6 @@ __host__ __device__ inline size_t apass_lds_bytes(int dt, int nslab, int tiles_n
 {
     return (size_t)apass_owned_slabs(nslab, tiles_n) * (SLAB_BYTES / elem_size(dt)) * 8;
 }
-// the same with column sums kept per wave (four waves) instead of added up in place
-__host__ __device__ inline size_t apass_lds_bytes_per_wave(int dt, int nslab, int tiles_n)
-{
-    return (size_t)apass_owned_slabs(nslab, tiles_n) * (SLAB_BYTES / elem_size(dt)) * 20;
-}
-
 // Reduce one resident slab of A.  sA: the slab in LDS (BM rows).  b_lds: the KE values of b
 // that belong to the slab (LDS).  rows_valid: rows of the tile inside M (rows beyond may hold
 // anything, finite or not: they are ignored).  col_lds: KE words of this slab's column sums.
@@ -69,11 +75,7 @@ __host__ __device__ inline size_t apass_lds_bytes_per_wave(int dt, int nslab, in
 // GIVEN: the caller supplied a = e^T A and max|A| (a checksum carried over from the kernel that
 // produced A): only the row dots are formed.
 // int8: |b| < 2^23 (the callers' N is below 65536).
-// PER_WAVE: col_lds is this wave's own KE words for the slab, written with plain stores (the caller
-// adds the waves' words up when it hands the sums on); otherwise the four waves add to the same words.
-// Measured on the fast kernel: the eight LDS atomic adds per wave and slab held the wave's next LDS
-// reads back by some 800 clocks.  The general kernel has no LDS to spare for four sets.
-template <int DT, int BM, bool GIVEN, bool PER_WAVE>
+template <int DT, int BM, bool GIVEN>
 __device__ __forceinline__ void a_pass(const uint8_t *sA, const uint32_t *b_lds, int rows_valid,
                                        uint32_t *col_lds, APassState<DT> &st, int keep = SLAB_BYTES)
 {
@@ -177,119 +179,142 @@ __device__ __forceinline__ void a_pass(const uint8_t *sA, const uint32_t *b_lds,
     if ((tid & 63) < 8) {
 #pragma unroll
         for (int q = 0; q < CE; ++q) {
-            if constexpr (PER_WAVE) col_lds[c * CE + q] = as_word(cs[q]);
-            else lds_add_word(col_lds + c * CE + q, cs[q]);
+            lds_add_word(col_lds + c * CE + q, cs[q]);
         }
     }
 }
 
-// The same reduction cut into pieces that the fast GEMM kernel issues one by one behind the MFMAs
-// of the slab (the matrix pipe works on an MFMA for 32 clocks; the few vector instructions of a
-// piece are issued in its shadow).  begin() requests the thread's chunks of the slab and its values
-// of b, piece<k>() takes element (or, int8, half a word) k % 8 of row group k / 8, end() reduces the
-// column sums over the wave and writes them to the wave's own words for the slab in LDS.  Same
-// arithmetic, in the same order, as a_pass above with PER_WAVE.
-template <int DT, int BM, bool GIVEN> struct APassSteps {
-    using T = Traits<DT>;
-    typedef typename T::acc_t acc_t;
-    typedef short s16x2 __attribute__((ext_vector_type(2)));
-    static constexpr int CE = 16 / T::ES;
-    static constexpr int P = BM / 32;
-    static constexpr int PIECES = P * 8;
-    int c, rg, rows_valid;
-    i32x4 v[P];
-    acc_t bv[T::IS_INT ? 1 : CE], cs[T::IS_INT ? 1 : CE];
-    s16x2 bhi[T::IS_INT ? 8 : 1], blo[T::IS_INT ? 8 : 1], csp[T::IS_INT ? 8 : 1], ev, od;
-    acc_t dot, mine;
-    int dhi, dlo;
-    float amax;
+// ---- The fast kernel's form of the pass: matrix instructions on the fragments the GEMM has in registers.
+// A 16 x 16 MFMA takes lane l of a 32-row fragment for row l & 15 and piece l >> 4 along its own K, so rows r and r + 16 meet
+// in one sum.  Times the identity, positions along K come out in the lanes, to be added up over rows (four registers and two
+// exchanges per slab); times b, split into terms that the operand type holds exactly, the dots of the fragment's 32 rows do, a
+// term to a register.  (The item kernels do the same: gemm_item.h.)  The four waves that share rows of A take a step
+// of the slab each.  Per owned slab of a 256-row tile that is eight MFMAs of 16 clocks (int8 twelve) and some seventy-five
+// vector instructions of one wave in four, where element by element it was two hundred of every wave.  What an owned slab adds to
+// a tile: int8 36928 x 1024 x 4096 (eight to a tile) 3000 -> 2300 clocks, the launch 171.9 -> 161.4 us; f16 6304 x 768 x 3072 1700.
+// Products with one are exact, and so are those with b's terms before they are added.  But Inf and NaN reach through
+// products with zeros what they have no part in: sums and dots that are not finite are formed again, element by element, from
+// memory (fast_dot_again, fast_col_again).
+//
+// LDS: the column sums of every owned slab; b in three terms, of two slabs in turn; 128 bytes of zeros; words of b, of two slabs in turn.
+__host__ __device__ inline size_t fast_aux_bytes(int dt, int nslab, int tiles_n)
+{
+    return (size_t)(apass_owned_slabs(nslab, tiles_n) + 2) * (SLAB_BYTES / elem_size(dt)) * 4 + (2 * 3 + 1) * SLAB_BYTES;
+}
 
-    __device__ __forceinline__ void begin(const uint8_t *sA, const uint32_t *b_lds, int rows_valid_)
-    {
-        const int tid = tile_thread_index();
-        c = tid & 7; rg = tid >> 3; rows_valid = rows_valid_;
-        const uint8_t *src = sA + rg * SLAB_BYTES + ((c ^ ((rg >> 1) & 7)) * 16);
+// The operand of ones that turns a fragment: of positions 0..15 of a step (16-bit types), of 16 u .. + 15 (int8).
+template <int DT> __device__ __forceinline__ i32x4 turn_operand(int lane, int u)
+{
+    constexpr int ONE = DT == DT_BF16 ? 0x3F80 : 0x3C00;
+    const int j = lane & 15, lh = lane >> 5, pos = j - 8 * lh;
+    i32x4 f;
 #pragma unroll
-        for (int p = 0; p < P; ++p) v[p] = *reinterpret_cast<const i32x4 *>(src + p * 32 * SLAB_BYTES);
-        if constexpr (T::IS_INT) {
-#pragma unroll
-            for (int d = 0; d < 4; ++d) {
-                const i32x4 w = *reinterpret_cast<const i32x4 *>(b_lds + c * CE + 4 * d);
-                const int b0 = w[0], b1 = w[1], b2 = w[2], b3 = w[3];
-                bhi[2 * d] = s16x2{(short)(b0 >> 8), (short)(b2 >> 8)};
-                bhi[2 * d + 1] = s16x2{(short)(b1 >> 8), (short)(b3 >> 8)};
-                blo[2 * d] = s16x2{(short)(b0 & 255), (short)(b2 & 255)};
-                blo[2 * d + 1] = s16x2{(short)(b1 & 255), (short)(b3 & 255)};
-            }
-#pragma unroll
-            for (int j = 0; j < 8; ++j) csp[j] = s16x2{0, 0};
-        } else {
-#pragma unroll
-            for (int q4 = 0; q4 < CE / 4; ++q4) {
-                const i32x4 w = *reinterpret_cast<const i32x4 *>(b_lds + c * CE + 4 * q4);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) bv[4 * q4 + e] = from_word<acc_t>((uint32_t)w[e]);
-            }
-#pragma unroll
-            for (int q = 0; q < CE; ++q) cs[q] = T::zero();
-        }
-        mine = T::zero();
-        amax = 0.f;
+    for (int w = 0; w < 4; ++w) {
+        if constexpr (DT == DT_I8) f[w] = lh == u && (j >> 2) == w ? 1 << (8 * (j & 3)) : 0;
+        else f[w] = pos == 2 * w ? ONE : pos == 2 * w + 1 ? (int)((unsigned)ONE << 16) : 0;
     }
+    return f;
+}
 
-    template <int K> __device__ __forceinline__ void piece()
-    {
-        if constexpr (K >= 0 && K < PIECES) {
-            constexpr int p = K / 8, e = K % 8;
-            if constexpr (e == 0) {
-                if (rg + 32 * p >= rows_valid) v[p] = i32x4{0, 0, 0, 0};
-                dot = T::zero(); dhi = 0; dlo = 0;
-            }
-            if constexpr (T::IS_INT) {
-                constexpr int d = e >> 1;
-                if constexpr ((e & 1) == 0) {
-                    const int wd = v[p][d];
-                    const s16x2 w = s16x2{(short)(wd & 0xFFFF), (short)(wd >> 16)};
-                    ev = (w << 8) >> 8; od = w >> 8;                 // bytes 0, 2 and 1, 3, sign-extended
-                    if (!GIVEN) { csp[2 * d] += ev; csp[2 * d + 1] += od; }
-                } else {
-                    dhi = __builtin_amdgcn_sdot2(ev, bhi[2 * d], dhi, false);
-                    dhi = __builtin_amdgcn_sdot2(od, bhi[2 * d + 1], dhi, false);
-                    dlo = __builtin_amdgcn_sdot2(ev, blo[2 * d], dlo, false);
-                    dlo = __builtin_amdgcn_sdot2(od, blo[2 * d + 1], dlo, false);
-                }
-                if constexpr (e == 7) dot = (acc_t)(int)((uint32_t)dhi * 256u + (uint32_t)dlo);
-            } else {
-                const acc_t x = T::elem(v[p], e);
-                if (!GIVEN) cs[e] = add_t(cs[e], x);
-                dot = __builtin_fmaf((float)x, (float)bv[e], (float)dot);
-                if (!GIVEN) amax = fmaxf(amax, fabsf((float)x));
-            }
-            if constexpr (e == 7) {
-                dot = row8_sum(dot);
-                if (c == p) mine = dot;
-            }
-        }
+// Term d = 0, 1, 2 of b, as bits of the operand type; what is left of it in v.  int8: signed bytes (|b| < 2^23).  bf16: three times
+// eight bits, cut off and not rounded (a value near the largest must not become Inf).  fp16: of b times a power of two that
+// brings N max|B| below 2^15: what the last term leaves off is 2^-40 of that.
+template <int DT> __device__ __forceinline__ uint32_t b_term(typename Traits<DT>::acc_t &v)
+{
+    if constexpr (DT == DT_I8) {
+        const int lo = (int)(int8_t)(v & 0xFF);
+        v = (v - lo) >> 8;
+        return (uint32_t)lo & 0xFFu;
+    } else if constexpr (DT == DT_BF16) {
+        const uint32_t hi = __float_as_uint(v) & 0xFFFF0000u;
+        v -= __uint_as_float(hi);
+        return hi >> 16;
+    } else {
+        const uint32_t h = f32_to_f16_bits(v);
+        v -= f16_bits_to_f32(h);
+        return h;
     }
+}
+// fp16: the exponent of that power of two; N max|B| past 2^100 (or none): NaN for its inverse, and every dot is formed again
+__device__ __forceinline__ void b_scale(uint32_t bmax_bits, int N, float *scale, float *back)
+{
+    // (in scalar registers)
+    const uint32_t bits = __builtin_amdgcn_readfirstlane(__float_as_uint(__uint_as_float(bmax_bits) * (float)N));
+    const int ex = (int)(bits >> 23) - 127 + 1;                            // the bound is below 2^ex (infinity, NaN: 129)
+    const bool ok = ex <= 100;
+    const int e = ok ? (ex < -80 ? -80 : ex) : 0;
+    *scale = __uint_as_float((uint32_t)(127 + 15 - e) << 23);
+    *back = __uint_as_float(ok ? (uint32_t)(127 - 15 + e) << 23 : 0x7FC00000u);
+}
 
-    __device__ __forceinline__ void end(uint32_t *col_lds, APassState<DT> &st)
+// d[mi] += b x[mi] and c = the sum over mi of x[mi] turned; operands and results in vector registers.  As instructions: the
+// built-in's results would be given accumulation registers, which the tile fills.  The waits cover what the compiler does not
+// see in here: operands written by vector instructions just ahead, results read right behind.
+template <int DT> struct TurnSums { typename Acc4<DT>::type c[2]; };
+#define ABFT_M16(OP, D, A, B, C) OP " %" D ", %" A ", %" B ", " C "\n\t"
+template <int DT, int MI>
+__device__ __forceinline__ void pass_mfmas(typename Acc4<DT>::type (&d)[MI], TurnSums<DT> &ts, const i32x4 (&x)[MI], const i32x4 &b,
+                                           const i32x4 &id0, const i32x4 &id1)
+{
+    // operands: %0 %1 the turned sums, %2 .. the dots, then the fragments, b, id0, id1
+    if constexpr (DT == DT_I8) {
+        if constexpr (MI == 4)
+            asm volatile("s_nop 4\n\t"
+                         ABFT_M16("v_mfma_i32_16x16x64_i8", "0", "6", "11", "0") ABFT_M16("v_mfma_i32_16x16x64_i8", "1", "6", "12", "0")
+                         ABFT_M16("v_mfma_i32_16x16x64_i8", "2", "10", "6", "%2")
+                         ABFT_M16("v_mfma_i32_16x16x64_i8", "3", "10", "7", "%3") "s_nop 7\n\t"
+                         ABFT_M16("v_mfma_i32_16x16x64_i8", "0", "7", "11", "%0") ABFT_M16("v_mfma_i32_16x16x64_i8", "1", "7", "12", "%1")
+                         ABFT_M16("v_mfma_i32_16x16x64_i8", "4", "10", "8", "%4") "s_nop 7\n\t"
+                         ABFT_M16("v_mfma_i32_16x16x64_i8", "0", "8", "11", "%0") ABFT_M16("v_mfma_i32_16x16x64_i8", "1", "8", "12", "%1")
+                         ABFT_M16("v_mfma_i32_16x16x64_i8", "5", "10", "9", "%5") "s_nop 7\n\t"
+                         ABFT_M16("v_mfma_i32_16x16x64_i8", "0", "9", "11", "%0") ABFT_M16("v_mfma_i32_16x16x64_i8", "1", "9", "12", "%1")
+                         "s_nop 15\n\ts_nop 7"
+                         : "=&v"(ts.c[0]), "=&v"(ts.c[1]), "+v"(d[0]), "+v"(d[1]), "+v"(d[2]), "+v"(d[3])
+                         : "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]), "v"(b), "v"(id0), "v"(id1));
+        else
+            asm volatile("s_nop 4\n\t"
+                         ABFT_M16("v_mfma_i32_16x16x64_i8", "0", "4", "7", "0") ABFT_M16("v_mfma_i32_16x16x64_i8", "1", "4", "8", "0")
+                         ABFT_M16("v_mfma_i32_16x16x64_i8", "2", "6", "4", "%2") ABFT_M16("v_mfma_i32_16x16x64_i8", "3", "6", "5", "%3") "s_nop 7\n\t"
+                         ABFT_M16("v_mfma_i32_16x16x64_i8", "0", "5", "7", "%0") ABFT_M16("v_mfma_i32_16x16x64_i8", "1", "5", "8", "%1")
+                         "s_nop 15\n\ts_nop 7"
+                         : "=&v"(ts.c[0]), "=&v"(ts.c[1]), "+v"(d[0]), "+v"(d[1])
+                         : "v"(x[0]), "v"(x[1]), "v"(b), "v"(id0), "v"(id1));
+    } else {
+        // (the two turned sums take every other fragment each; the caller adds them)
+#define ABFT_PASS16(OP)                                                                                                             \
+        if constexpr (MI == 4)                                                                                                      \
+            asm volatile("s_nop 4\n\t"                                                                                              \
+                         ABFT_M16(OP, "0", "6", "11", "0") ABFT_M16(OP, "2", "10", "6", "%2")                                       \
+                         ABFT_M16(OP, "1", "7", "11", "0") ABFT_M16(OP, "3", "10", "7", "%3") "s_nop 3\n\t"                         \
+                         ABFT_M16(OP, "0", "8", "11", "%0") ABFT_M16(OP, "4", "10", "8", "%4") "s_nop 3\n\t"                        \
+                         ABFT_M16(OP, "1", "9", "11", "%1") ABFT_M16(OP, "5", "10", "9", "%5")                                      \
+                         "s_nop 15\n\ts_nop 7"                                                                                      \
+                         : "=&v"(ts.c[0]), "=&v"(ts.c[1]), "+v"(d[0]), "+v"(d[1]), "+v"(d[2]), "+v"(d[3])                           \
+                         : "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]), "v"(b), "v"(id0));                                           \
+        else                                                                                                                        \
+            asm volatile("s_nop 4\n\t"                                                                                              \
+                         ABFT_M16(OP, "0", "4", "7", "0") ABFT_M16(OP, "2", "6", "4", "%2")                                         \
+                         ABFT_M16(OP, "1", "5", "7", "0") ABFT_M16(OP, "3", "6", "5", "%3")                                         \
+                         "s_nop 15\n\ts_nop 7"                                                                                      \
+                         : "=&v"(ts.c[0]), "=&v"(ts.c[1]), "+v"(d[0]), "+v"(d[1])                                                   \
+                         : "v"(x[0]), "v"(x[1]), "v"(b), "v"(id0))
+        if constexpr (DT == DT_BF16) { ABFT_PASS16("v_mfma_f32_16x16x32_bf16"); }
+        else { ABFT_PASS16("v_mfma_f32_16x16x32_f16"); }
+#undef ABFT_PASS16
+    }
+}
+#undef ABFT_M16
+
+// What the pass leaves of a tile.
+template <int DT, int MI> struct FastPass {
+    typedef typename Traits<DT>::acc_t acc_t;
+    typename Acc4<DT>::type dot[MI];   // lane l < 32, registers 0, 1, 2: products of row l of block mi with the terms of b, over the owned slabs
+    uint32_t amax;                     // 16-bit types: largest |element| as bits, in either half
+    // the dot of row lane & 31 (lanes 0..31) of block mi over what this wave has taken
+    __device__ __forceinline__ acc_t total(int mi) const
     {
-        st.rdot = add_t(st.rdot, mine);
-        if constexpr (GIVEN) return;
-        if constexpr (!T::IS_INT) st.amax = fmaxf(st.amax, amax);
-        acc_t t[CE];
-#pragma unroll
-        for (int q = 0; q < CE; ++q) {
-            if constexpr (T::IS_INT) t[q] = (acc_t)csp[2 * (q >> 2) + (q & 1)][(q >> 1) & 1];
-            else t[q] = cs[q];
-            t[q] = add_t(t[q], dpp_get<0x128>(t[q]));      // row_ror:8 inside 16 lanes: lane ^ 8
-            t[q] = add_xor16(t[q]);
-            t[q] = add_xor32(t[q]);
-        }
-        if ((tile_thread_index() & 63) < 8) {
-#pragma unroll
-            for (int q = 0; q < CE; ++q) col_lds[c * CE + q] = as_word(t[q]);      // this wave's own words
-        }
+        if constexpr (DT == DT_I8) return (int)((uint32_t)dot[mi][0] + ((uint32_t)dot[mi][1] << 8) + ((uint32_t)dot[mi][2] << 16));
+        else return ((float)dot[mi][2] + (float)dot[mi][1]) + (float)dot[mi][0];
     }
 };
 
@@ -297,18 +322,18 @@ template <int DT, int BM, bool GIVEN> struct APassSteps {
 // rb * rpb .. of A, a window of 2^cw_log2 16-byte chunks along K.  A thread keeps one chunk column (its values of b
 // and its column sums stay in registers) and takes UN consecutive rows at a time, all UN loads in flight:
 // 64 KB per compute unit, bound by the latency of memory and not by the 40-odd vector instructions per
-// chunk.  smem: 256 * (16 / element size) words.  K is a whole number of slabs: no chunk is cut.
+// chunk.  smem: 64 FAST_WAVES * (16 / element size) words.  K is a whole number of slabs: no chunk is cut.
 template <int DT>
 __device__ __forceinline__ void a_beside(const GemmArgs &g, int blk, uint8_t *smem)
 {
     using T = Traits<DT>;
     typedef typename T::acc_t acc_t;
-    constexpr int CE = 16 / T::ES, UN = 16;
+    constexpr int CE = 16 / T::ES, UN = 8;
     const int per_item = g.beside.nwin * g.beside.nrb;
     const int bz = blk / per_item, in_item = blk - bz * per_item;
     const int rb = in_item / g.beside.nwin, win = in_item - rb * g.beside.nwin;
     const int tid = threadIdx.x;
-    const int CW = 1 << g.beside.cw_log2, RL = 256 >> g.beside.cw_log2;
+    const int CW = 1 << g.beside.cw_log2, RL = 64 * FAST_WAVES >> g.beside.cw_log2;
     const int cx = tid & (CW - 1), ry = tid >> g.beside.cw_log2;
     const int col0 = (win * CW + cx) * CE;
     const bool colok = col0 < g.K;
@@ -331,7 +356,7 @@ __device__ __forceinline__ void a_beside(const GemmArgs &g, int blk, uint8_t *sm
             const int r = min(rt + u, g.M - 1);                 // loads without a branch: rows past the end are cleared below
             v[u] = *reinterpret_cast<const i32x4 *>(src + (long)r * ldb);
         }
-        acc_t part[CE], m0 = T::zero(), m1 = T::zero();         // the batch's column sums; dots of rows cx and cx + 8
+        acc_t part[CE], mine = T::zero();                       // the batch's column sums; the dot of row cx
 #pragma unroll
         for (int e = 0; e < CE; ++e) part[e] = T::zero();
 #pragma unroll
@@ -351,22 +376,18 @@ __device__ __forceinline__ void a_beside(const GemmArgs &g, int blk, uint8_t *sm
                 }
             }
             dot = seg_sum(dot, CW);
-            if (cx == (u & 7)) { if (u < 8) m0 = dot; else m1 = dot; }
+            if (cx == u) mine = dot;
         }
 #pragma unroll
         for (int e = 0; e < CE; ++e) cs[e] = add_t(cs[e], part[e]);
-        if (cx < 8) {
-            uint32_t *d = g.rc_pred + (long)bz * g.M + rt + cx;
-            if (rt + cx < rend) atomic_add_word(d, m0);
-            if (rt + cx + 8 < rend) atomic_add_word(d + 8, m1);
-        }
+        if (cx < UN && rt + cx < rend) atomic_add_word(g.rc_pred + (long)bz * g.M + rt + cx, mine);
     }
     if (g.a_given) return;
     acc_t *red = reinterpret_cast<acc_t *>(smem);
 #pragma unroll
     for (int e = 0; e < CE; ++e) red[(ry * CW + cx) * CE + e] = cs[e];
     __syncthreads();
-    for (int c = tid; c < CW * CE; c += 256) {
+    for (int c = tid; c < CW * CE; c += 64 * FAST_WAVES) {
         const int k = win * CW * CE + c;
         if (k < g.K) {
             acc_t t = red[c];

@@ -8,7 +8,7 @@
 // register i, column 8*(i>>2) + 4*(l>>5) + (i&3) -- four consecutive columns per register
 // quad.  Consequences:
 //   * C goes out through LDS: each lane packs four converted values into one LDS write, the
-//     wave reads the staged rows back 16 bytes per lane and stores whole 256/512-byte row
+//     wave reads the staged rows back 16 bytes per lane and stores whole 128/256-byte row
 //     segments to global memory.
 //   * row sums are in-lane adds plus one exchange between the half-waves;
 //   * column sums need a reduction over the 32 lanes (rows): partial sums are transposed
@@ -33,19 +33,11 @@
 
 namespace abft {
 
-template <int I, int N, typename F> __device__ __forceinline__ void static_for(F &&f)
-{
-    if constexpr (I < N) {
-        f(std::integral_constant<int, I>{});
-        static_for<I + 1, N>(f);
-    }
-}
-
 // bytes of wave-private LDS the epilogue needs for a wave tile that is TN columns wide
 __host__ __device__ constexpr int epi_wave_bytes(int TN) { return 32 * (TN * 4 + 16); }
 __host__ __device__ constexpr int epi_total_bytes(int BM, int BN)
 {
-    return 4 * epi_wave_bytes(BN / 2) + (3 * BM + 2 * BN) * 4 + 16;
+    return FAST_WAVES * epi_wave_bytes(BN / 4) + (12 * BM + 5 * BN) * 4 + 8 * FAST_WAVES;
 }
 
 // Read one accumulator element where it lives (an AGPR) at the point of use.  Without this the
@@ -91,48 +83,87 @@ template <int DT> __device__ __forceinline__ float stored_value(float v)
 }
 
 // What a protected tile hands to the epilogue besides its accumulators.
-template <int DT> struct EpiProt {
-    APassState<DT> st;        // row dots and max|A| of the owned slabs
-    const uint32_t *col_lds;  // column sums of the owned slabs, KE words each (LDS)
-    int owned;                // number of owned slabs reduced: the j-th is slab slab0 + j * slab_step of K
+template <int DT, int MI> struct EpiProt {
+    FastPass<DT, MI> pass;    // what the pass over the owned slabs left in registers
+    const uint32_t *col_lds;  // column sums of the owned slabs (LDS)
+    int owned;                // number of owned slabs: the j-th is slab slab0 + j * slab_step of K
     int slab0, slab_step;
-    int col_stride;           // words from one wave's set of column sums to the next; the four are added up
+    float back;               // fp16: what undoes the scale of b's terms
 };
 
-template <int DT, int BM, int BN, bool PROT, bool BIAS>
+// A dot of row `row` of A with b over the owned slabs, and a column sum of A over rows row0 .. + rows, formed again from memory:
+// where the sums along K by matrix instructions are not finite.  amax: of the row's elements, NaN left out.
+template <int DT, int MI>
+__device__ __forceinline__ float fast_dot_again(const GemmArgs &g, const EpiProt<DT, MI> &ep, int bz, int row, float *amax)
+{
+    constexpr int KE = SLAB_BYTES / Traits<DT>::ES;
+    float v = 0.f;
+    for (int j = 0; j < ep.owned; ++j)
+        for (int e = 0; e < KE; ++e) {
+            const int k = (ep.slab0 + j * ep.slab_step) * KE + e;
+            const float x = (float)Traits<DT>::load_c(g.A, (long)bz * g.sA + (long)row * g.lda + k);
+            v = __builtin_fmaf(x, __uint_as_float(g.b_sum[(long)bz * g.K + k]), v);
+            *amax = fmaxf(*amax, fabsf(x));
+        }
+    return v;
+}
+template <int DT> __device__ __forceinline__ float fast_col_again(const GemmArgs &g, int bz, int row0, int rows, int k)
+{
+    float v = 0.f;
+    for (int r = row0; r < row0 + rows; ++r) v += (float)Traits<DT>::load_c(g.A, (long)bz * g.sA + (long)r * g.lda + k);
+    return v;
+}
+
+template <int DT, int BM, bool PROT, bool STO, bool BIAS>
 __device__ __forceinline__ void gemm_epilogue_impl(const GemmArgs &g,
-                                              typename Traits<DT>::accv_t (&acc)[BM / 64][BN / 64],
-                                              uint8_t *smem, int m0, int n0, int bz, const EpiProt<DT> &ep)
+                                              typename Traits<DT>::accv_t (&acc)[BM / 64][2],
+                                              uint8_t *smem, int m0, int n0, int bz, const EpiProt<DT, BM / 64> &ep)
 {
     using T = Traits<DT>;
     typedef typename T::acc_t acc_t;
-    constexpr int TM = BM / 2, TN = BN / 2;
+    constexpr int BN = 256, THREADS = 64 * FAST_WAVES;
+    constexpr int TM = BM / 2, TN = BN / 4;         // waves: two rows of four
     constexpr int MI = TM / 32, NI = TN / 32;
     constexpr int OS = T::OS;
     constexpr int KE = SLAB_BYTES / T::ES;
-    constexpr int CPL = TN / 64;                    // columns per lane when a wave walks a row
+    static_assert(TN == 64, "a lane to a column where a wave walks a row");
     constexpr int WAVE_BYTES = epi_wave_bytes(TN);
     constexpr int CROW = TN * OS + 16;              // staged C row (bytes), padded
     constexpr int SROW = TN * 4 + 16;               // staged 32-bit row (bytes), padded
     const int tid = tile_thread_index(), lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);      // wave-uniform by construction
-    const int wm = wave >> 1, wn = wave & 1;
+    const int wm = wave >> 2, wn = wave & 3;
     const int l32 = lane & 31, lh = lane >> 5;
     const int M = g.M, N = g.N;
 
     uint8_t *wbuf = smem + wave * WAVE_BYTES;                              // wave-private staging
-    acc_t *rs_part = reinterpret_cast<acc_t *>(smem + 4 * WAVE_BYTES);     // [2][BM] by wave column
-    acc_t *cs_part = rs_part + 2 * BM;                                     // [2][BN] by wave row
-    acc_t *rp = cs_part + 2 * BN;                                          // [BM] row dots of the A pass
-    float *amax4 = reinterpret_cast<float *>(rp + BM);                     // [4]
+    acc_t *rs_part = reinterpret_cast<acc_t *>(smem + FAST_WAVES * WAVE_BYTES);      // [4][BM] by wave column
+    acc_t *cs_part = rs_part + 4 * BM;                                     // [2][BN] by wave row: a place to a thread
+    acc_t *rp_part = cs_part + 2 * BN;                                     // [4][BM] row dots of the A pass, by wave column
+    uint32_t *amax_w = reinterpret_cast<uint32_t *>(rp_part + 4 * BM);     // largest |element| the pass saw (bits), by wave
     uint8_t *Cb = g.C + (long)bz * g.sC * OS;
     // layer bias of this tile's columns, staged once (zero beyond N); added to every accumulator
     // value on its way out, before the sums and before rounding
     constexpr bool has_bias = BIAS;
-    acc_t *bias_lds = reinterpret_cast<acc_t *>(amax4 + 4);                // [BN]
+    acc_t *bias_lds = reinterpret_cast<acc_t *>(amax_w + FAST_WAVES);      // [BN]
     if (has_bias) {
-        for (int t = tid; t < BN; t += 256) bias_lds[t] = n0 + t < N ? from_word<acc_t>(g.bias[n0 + t]) : T::zero();
+        for (int t = tid; t < BN; t += THREADS) bias_lds[t] = n0 + t < N ? from_word<acc_t>(g.bias[n0 + t]) : T::zero();
         __syncthreads();
+    }
+    if (PROT && ep.owned > 0) {
+        // what the pass over A's slabs left in registers (nothing in a tile that reduced no slab: where K has fewer slabs than the
+        // tile row has tiles, that is most tiles)
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi) {
+            acc_t v = ep.pass.total(mi);
+            if constexpr (DT == DT_F16) v *= ep.back;
+            if (lane < 32) rp_part[wn * BM + wm * TM + mi * 32 + lane] = v;
+        }
+        if constexpr (!T::IS_INT) {
+            const uint32_t m = ep.pass.amax, hi = m >> 16, lo = m & 0xFFFFu;
+            const uint32_t w = wave_max_u32(hi > lo ? hi : lo);
+            if (lane == 0) amax_w[wave] = w;
+        }
     }
     const bool inj_here = g.inj_b == bz && g.inj_row >= m0 && g.inj_row < m0 + BM &&
                           g.inj_col >= n0 && g.inj_col < n0 + BN;
@@ -146,80 +177,73 @@ __device__ __forceinline__ void gemm_epilogue_impl(const GemmArgs &g,
     };
 
     // column partials: of the groups that went the register way (block column ni, register i:
-    // this lane's rows) and of the groups that were walked row by row (columns CPL*lane ..)
+    // this lane's rows) and of the groups that were walked row by row (column `lane`)
     acc_t cp[PROT ? NI : 1][16];
-    acc_t colacc[CPL];
-    // Sums of the values as stored (after rounding), on request and for floating point only: edge groups
+    acc_t colacc = T::zero();
+    // STO: sums of the values as stored (after rounding), floating point only: edge groups
     // add to these while they walk their rows; register-path groups form them by MFMA from the row
     // pieces they store (stored_sums below).
-    const bool sto = PROT && !T::IS_INT && g.cc_sto != nullptr;
-    float colacc_s[CPL], rowsto[MI];
+    float colacc_s = 0.f;
     float cmax_s = 0.f;                 // max|value as stored| seen by this lane (with the stored-side sums)
-#pragma unroll
-    for (int j = 0; j < CPL; ++j) colacc_s[j] = 0.f;
-#pragma unroll
-    for (int mi = 0; mi < MI; ++mi) rowsto[mi] = 0.f;
-    bool reg_path[MI];
     typename Acc4<DT>::type dcol = acc4_zero<DT>();      // stored-side column sums of the register-path groups
-    // A stored row piece of a group: lane l holds 16 bytes, chunk l & 15, of row 4 it + (l >> 4).  As an
-    // operand of a 16 x 16 MFMA it has the chunks for rows and (row, element of the chunk) along K, so
-    // times "element j" it gives the columns' sums over its four rows, times "row j" each chunk's share of
-    // the rows' sums: two MFMAs for what took some nine vector instructions per value, 512 values to a
-    // lane (bf16 6304 x 3072 x 768 with a bias, then verify: 88.8 us, so 83.6).  Products with one are exact and the
+    // the sums of the wave's rows and columns, by wave column and by wave row: the tile adds each up before it hands it over
+    float *rs_sto = reinterpret_cast<float *>(bias_lds + BN);
+    float *cs_sto = rs_sto + 4 * BM, *cmax_w = cs_sto + 2 * BN;
+    if constexpr (STO) cs_sto[tid] = 0.f;                // (a place to a thread)
+    // A stored row piece of a group: lane l holds 16 bytes, chunk l & 7, of row 8 it + (l >> 3).  As an
+    // operand of a 16 x 16 MFMA it has (chunk, parity of the row) for rows and (row / 2, element of the chunk) along K, so
+    // times "element j" it gives the columns' sums over its rows of a parity, times "row pair j" each chunk's share of
+    // the rows' sums: two MFMAs for what took some nine vector instructions per value.  Products with one are exact and the
     // values themselves are the stored ones.  Inf and NaN would reach their neighbours through the
     // zeros: a group that holds one is summed element by element.
-    auto stored_sums = [&](int br) __attribute__((always_inline)) {
-        if constexpr (PROT && !T::IS_INT) {
+    auto stored_sums = [&](int mi, const i32x4 *rowv) __attribute__((always_inline)) {
+        if constexpr (STO) {
             typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
             constexpr uint32_t INF_BITS = DT == DT_BF16 ? 0x7F80u : 0x7C00u;
             constexpr uint32_t ONE = DT == DT_BF16 ? 0x3F80u : 0x3C00u;
-            static_assert(TN == 128 && OS == 2, "sixteen lanes to a row");
-            const int ln = tile_thread_index() & 63, j = ln & 15, r4 = ln >> 4;
-            const uint8_t *piece = wbuf + r4 * CROW + j * 16;           // of row r4; of row 4 it + r4: + 4 it rows
-            float *rsto = reinterpret_cast<float *>(g.rc_sto) + (long)bz * M + br;
+            static_assert(OS == 2, "eight lanes to a row");
+            const int ln = tile_thread_index() & 63, j = ln & 15, k4 = ln >> 4;
+            float *rsto = rs_sto + wn * BM + wm * TM + mi * 32;
             i32x4 elem;
 #pragma unroll
             for (int w = 0; w < 4; ++w) elem[w] = j == 2 * w ? (int)ONE : j == 2 * w + 1 ? (int)(ONE << 16) : 0;
             u16x2 mx = {0, 0};
-            auto sums = dcol;
-            float row[2];
+            auto sums = dcol, drow = acc4_zero<DT>();
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                auto drow = acc4_zero<DT>();
+            for (int it = 0; it < 4; ++it) {
+                const int w = j == 4 * it + k4 ? (int)(ONE | (ONE << 16)) : 0;
+                sums = mfma16<DT>(rowv[it], elem, sums);
+                drow = mfma16<DT>(rowv[it], i32x4{w, w, w, w}, drow);
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const i32x4 v = *reinterpret_cast<const i32x4 *>(piece + (16 * h + 4 * q) * CROW);
-                    const int w = j == 4 * q + r4 ? (int)(ONE | (ONE << 16)) : 0;
-                    sums = mfma16<DT>(v, elem, sums);
-                    drow = mfma16<DT>(v, i32x4{w, w, w, w}, drow);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) mx = __builtin_elementwise_max(mx, __builtin_bit_cast(u16x2, v[e] & 0x7FFF7FFF));
-                }
-                row[h] = add_xor32(add_xor16(((float)drow[0] + (float)drow[1]) + ((float)drow[2] + (float)drow[3])));
+                for (int e = 0; e < 4; ++e) mx = __builtin_elementwise_max(mx, __builtin_bit_cast(u16x2, rowv[it][e] & 0x7FFF7FFF));
             }
+            // lane l: column j = 4 it + row / 2 of rows 4 (l >> 4) .. + 4 of the result: chunks of parity l >> 5
+            const float row = add_xor16(((float)drow[0] + (float)drow[1]) + ((float)drow[2] + (float)drow[3]));
             const uint32_t m = mx[0] > mx[1] ? mx[0] : mx[1];
             if (!__any(m >= INF_BITS)) {
                 cmax_s = fmaxf(cmax_s, DT == DT_BF16 ? __uint_as_float(m << 16) : f16_bits_to_f32(m));
                 dcol = sums;
-                if (ln < 32) unsafeAtomicAdd(rsto + ln, ln < 16 ? row[0] : row[1]);
+                if (!(k4 & 1)) rsto[2 * j + (k4 >> 1)] = row;
             } else {
-                float cv[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-                for (int it = 0; it < 8; ++it) {
-                    const i32x4 v = *reinterpret_cast<const i32x4 *>(piece + 4 * it * CROW);
-                    float s = 0.f;
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        const float x = T::elem(v, e);
-                        cv[e] += x;
-                        s += x;
+                // column e of the lane's chunk over its rows, then its row; loops, to cost few registers and little code
+                const uint16_t *piece = reinterpret_cast<const uint16_t *>(wbuf + (ln >> 3) * CROW + (ln & 7) * 16);
+#pragma unroll 1
+                for (int e = 0; e < 8; ++e) {
+                    float c = 0.f;
+                    for (int it = 0; it < 4; ++it) {
+                        const float x = (float)T::load_c(piece, 4 * it * CROW + e);
+                        c += x;
                         cmax_s = fmaxf(cmax_s, fabsf(x));
                     }
-                    s = row16_sum(s);
-                    if (j == 0) unsafeAtomicAdd(rsto + 4 * it + r4, s);
+                    lds_add_word(reinterpret_cast<uint32_t *>(cs_sto) + wm * BN + wn * TN + 8 * (ln & 7) + e, c);
                 }
-#pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    unsafeAtomicAdd(reinterpret_cast<float *>(g.cc_sto) + (long)bz * N + wc0 + 8 * j + e, cv[e]);
+#pragma unroll 1
+                for (int it = 0; it < 4; ++it) {
+                    float s = 0.f;
+                    for (int e = 0; e < 8; ++e) s += (float)T::load_c(piece, 4 * it * CROW + e);
+                    s = row8_sum(s);
+                    if ((ln & 7) == 0) rsto[8 * it + (ln >> 3)] = s;
+                }
             }
         }
     };
@@ -228,14 +252,11 @@ __device__ __forceinline__ void gemm_epilogue_impl(const GemmArgs &g,
         for (int ni = 0; ni < NI; ++ni)
 #pragma unroll
             for (int i = 0; i < 16; ++i) cp[ni][i] = T::zero();
-#pragma unroll
-        for (int j = 0; j < CPL; ++j) colacc[j] = T::zero();
     }
 
     static_for<0, MI>([&](auto mi_c) {
         constexpr int mi = decltype(mi_c)::value;
         const int br = wr0 + mi * 32;                                      // first row of this 32-row group
-        reg_path[mi] = cols_full && br + 32 <= M;
         if (cols_full && br + 32 <= M) {
             // ---- register path: one read of every accumulator serves the sums and the store
             acc_t rowsum = T::zero();
@@ -255,6 +276,9 @@ __device__ __forceinline__ void gemm_epilogue_impl(const GemmArgs &g,
                         cp[PROT ? ni : 0][4 * q + 1] = add_t(cp[PROT ? ni : 0][4 * q + 1], v1);
                         cp[PROT ? ni : 0][4 * q + 2] = add_t(cp[PROT ? ni : 0][4 * q + 2], v2);
                         cp[PROT ? ni : 0][4 * q + 3] = add_t(cp[PROT ? ni : 0][4 * q + 3], v3);
+                        // (here and now: moved behind the branch, as the compiler would have them, the additions keep every value alive)
+                        asm volatile("" : "+v"(cp[PROT ? ni : 0][4 * q]), "+v"(cp[PROT ? ni : 0][4 * q + 1]), "+v"(cp[PROT ? ni : 0][4 * q + 2]),
+                                          "+v"(cp[PROT ? ni : 0][4 * q + 3]));
                         rowsum = add_t(rowsum, add_t(add_t(v0, v1), add_t(v2, v3)));
                     }
                     uint8_t *d = wbuf + l32 * CROW + (ni * 32 + 8 * q + 4 * lh) * OS;
@@ -279,18 +303,16 @@ __device__ __forceinline__ void gemm_epilogue_impl(const GemmArgs &g,
             constexpr int RPI = 64 / LPR;                                  // rows per instruction
             constexpr int NIT = 32 / RPI;
             const int r0 = lane / LPR, cch = lane % LPR;
+            uint8_t *crow = Cb + ((long)(br + r0) * g.ldc + wc0) * OS + cch * 16;
+            const long cstep = (long)RPI * g.ldc * OS;
             i32x4 rowv[NIT];
 #pragma unroll
             for (int it = 0; it < NIT; ++it)
                 rowv[it] = *reinterpret_cast<const i32x4 *>(wbuf + (it * RPI + r0) * CROW + cch * 16);
-            uint8_t *crow = Cb + ((long)(br + r0) * g.ldc + wc0) * OS + cch * 16;
-            const long cstep = (long)RPI * g.ldc * OS;
 #pragma unroll
             for (int it = 0; it < NIT; ++it)
                 __builtin_nontemporal_store(rowv[it], reinterpret_cast<i32x4 *>(crow + it * cstep));
-            if constexpr (PROT && !T::IS_INT) {
-                if (sto) stored_sums(br);
-            }
+            if constexpr (STO) stored_sums(mi, rowv);
             wave_sync();
         } else if (br < M && wc0 < N) {
             // ---- edge path: raw accumulators to LDS, then a plain loop over rows
@@ -312,24 +334,17 @@ __device__ __forceinline__ void gemm_epilogue_impl(const GemmArgs &g,
                 wave_sync();
             }
             const int nrow = M - br < 32 ? M - br : 32;
-            // (1) lane <-> CPL consecutive columns, walking the rows: store C, column sums
-            for (int r = 0; r < nrow; ++r) {
-#pragma unroll
-                for (int j = 0; j < CPL; ++j) {
-                    const int col = CPL * lane + j, gc = wc0 + col;
-                    if (gc < N) {
-                        acc_t v = from_word<acc_t>(*reinterpret_cast<const uint32_t *>(wbuf + r * SROW + col * 4));
-                        if (has_bias) v = add_t(v, bias_lds[wn * TN + col]);
-                        T::store_c(Cb, (long)(br + r) * g.ldc + gc, v);
-                        if (PROT) colacc[j] = add_t(colacc[j], v);
-                        if constexpr (PROT && !T::IS_INT) {
-                            if (sto) {
-                                const float sv = stored_value<DT>((float)v);
-                                colacc_s[j] += sv;
-                                cmax_s = fmaxf(cmax_s, fabsf(sv));
-                            }
-                        }
-                    }
+            // (1) lane <-> column, walking the rows: store C, column sums
+            const int gc = wc0 + lane;
+            for (int r = 0; r < nrow && gc < N; ++r) {
+                acc_t v = from_word<acc_t>(*reinterpret_cast<const uint32_t *>(wbuf + r * SROW + lane * 4));
+                if (has_bias) v = add_t(v, bias_lds[wn * TN + lane]);
+                T::store_c(Cb, (long)(br + r) * g.ldc + gc, v);
+                if (PROT) colacc = add_t(colacc, v);
+                if constexpr (STO) {
+                    const float sv = stored_value<DT>((float)v);
+                    colacc_s += sv;
+                    cmax_s = fmaxf(cmax_s, fabsf(sv));
                 }
             }
             // (2) lane <-> row, the half-waves split the columns, walking the columns (each lane
@@ -346,23 +361,22 @@ __device__ __forceinline__ void gemm_epilogue_impl(const GemmArgs &g,
                         acc_t v = from_word<acc_t>(*reinterpret_cast<const uint32_t *>(wbuf + l32 * SROW + col * 4));
                         if (has_bias) v = add_t(v, bias_lds[wn * TN + col]);
                         rs = add_t(rs, v);
-                        if constexpr (!T::IS_INT) {
-                            if (sto) rs_s += stored_value<DT>((float)v);
-                        }
+                        if constexpr (STO) rs_s += stored_value<DT>((float)v);
                     }
                 }
                 rs = add_xor32(rs);
                 if (lane < 32) rs_part[wn * BM + wm * TM + mi * 32 + lane] = rs;
-                if constexpr (!T::IS_INT) {
-                    if (sto) {
-                        rs_s = add_xor32(rs_s);
-                        rowsto[mi] = rs_s;                              // lanes 0..31: row mi * 32 + lane
-                    }
+                if constexpr (STO) {
+                    rs_s = add_xor32(rs_s);
+                    if (lane < 32) rs_sto[wn * BM + wm * TM + mi * 32 + lane] = rs_s;
                 }
             }
             wave_sync();
         } else if (PROT) {
             if (lane < 32) rs_part[wn * BM + wm * TM + mi * 32 + lane] = T::zero();
+            if constexpr (STO) {
+                if (lane < 32) rs_sto[wn * BM + wm * TM + mi * 32 + lane] = 0.f;
+            }
         }
     });
 
@@ -379,101 +393,109 @@ __device__ __forceinline__ void gemm_epilogue_impl(const GemmArgs &g,
             });
         });
         wave_sync();
+        // four columns of every fourth row to a lane
+        acc_t csum[4] = {T::zero(), T::zero(), T::zero(), T::zero()};
 #pragma unroll
-        for (int r = 0; r < 32; ++r) {
-            if constexpr (CPL == 2) {
-                const uint2 w = *reinterpret_cast<const uint2 *>(wbuf + r * SROW + lane * 8);
-                colacc[0] = add_t(colacc[0], from_word<acc_t>(w.x));
-                colacc[1] = add_t(colacc[1], from_word<acc_t>(w.y));
-            } else {
+        for (int r = 0; r < 8; ++r) {
+            const i32x4 w = *reinterpret_cast<const i32x4 *>(wbuf + (4 * r + (lane >> 4)) * SROW + (lane & 15) * 16);
 #pragma unroll
-                for (int j = 0; j < CPL; ++j)
-                    colacc[j] = add_t(colacc[j], from_word<acc_t>(*reinterpret_cast<const uint32_t *>(
-                                                     wbuf + r * SROW + (CPL * lane + j) * 4)));
-            }
+            for (int e = 0; e < 4; ++e) csum[e] = add_t(csum[e], from_word<acc_t>((uint32_t)w[e]));
         }
 #pragma unroll
-        for (int j = 0; j < CPL; ++j) cs_part[wm * BN + wn * TN + CPL * lane + j] = colacc[j];
-        if constexpr (!T::IS_INT) {
-            if (sto) {
-                // one atomic per row / column of the wave tile (two waves share each)
-                const int j16 = lane & 15;
-                if (cols_full && j16 < 8) {
+        for (int e = 0; e < 4; ++e) csum[e] = add_xor32(add_xor16(csum[e]));
+        wave_sync();
+        if (lane < 16)
+            *reinterpret_cast<i32x4 *>(wbuf + lane * 16) =
+                i32x4{(int)as_word(csum[0]), (int)as_word(csum[1]), (int)as_word(csum[2]), (int)as_word(csum[3])};
+        wave_sync();
+        cs_part[tile_thread_index()] = add_t(colacc, from_word<acc_t>(*reinterpret_cast<const uint32_t *>(wbuf + lane * 4)));
+        if constexpr (STO) {
+            const int ln = tile_thread_index() & 63, j16 = ln & 15;     // (addresses formed here, not kept across the tile)
+            wave_sync();                                             // behind the additions of groups summed element by element
+            // register-path groups: column j16 of a chunk; rows 4 (lane >> 4) + r of the product are chunk + 8 parity
 #pragma unroll
-                    for (int r = 0; r < 4; ++r)
-                        unsafeAtomicAdd(reinterpret_cast<float *>(g.cc_sto) + (long)bz * N + wc0 + (4 * (lane >> 4) + r) * 8 + j16, (float)dcol[r]);
-                }
-                if (!cols_full || wr0 + TM > M) {                       // edge groups among them
-                    if (lane < 32) {
-#pragma unroll
-                        for (int mi = 0; mi < MI; ++mi) {
-                            const int gr = wr0 + mi * 32 + lane;
-                            if (!reg_path[mi] && gr < M) unsafeAtomicAdd(reinterpret_cast<float *>(g.rc_sto) + (long)bz * M + gr, rowsto[mi]);
-                        }
-                    }
-#pragma unroll
-                    for (int j = 0; j < CPL; ++j) {
-                        const int gc = wc0 + CPL * lane + j;
-                        if (gc < N) unsafeAtomicAdd(reinterpret_cast<float *>(g.cc_sto) + (long)bz * N + gc, colacc_s[j]);
-                    }
-                }
-                // the largest stored magnitude: what a consumer of this C needs as its max|A|
-                cmax_s = wave_max(cmax_s);
-                if (lane == 0 && cmax_s > 0.f && cmax_s == cmax_s) atomicMax(g.c_max + bz, __float_as_uint(cmax_s));
+            for (int r = 0; r < 4; ++r) {
+                const float c = add_xor32((float)dcol[r]);
+                if (j16 < 8 && ln < 32) cs_sto[wm * BN + wn * TN + (4 * (ln >> 4) + r) * 8 + j16] += c;
             }
-        }
-        // ---- what the pass over A's slabs left in registers (nothing in a tile that reduced no slab:
-        // where K has fewer slabs than the tile row has tiles, that is most tiles)
-        if (ep.owned > 0) {
-            constexpr int P = BM / 32;
-            const int c = tid & 7, rg = tid >> 3;
-            if (c < P) rp[rg + 32 * c] = ep.st.rdot;
-            if (!T::IS_INT) {
-                const float m = wave_max(ep.st.amax);
-                if (lane == 0) amax4[wave] = m;
-            }
+            wave_sync();
+            cs_sto[tile_thread_index()] += colacc_s;                  // edge groups
+            // the largest stored magnitude: what a consumer of this C needs as its max|A|
+            cmax_s = wave_max(cmax_s);
+            if (lane == 0) cmax_w[wave] = cmax_s;
         }
         // Barrier over LDS traffic only: the partial sums meet in LDS, and a full barrier would
         // also wait until every store of C issued above has been acknowledged.
         asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-        for (int t = tid; t < BM + BN; t += 256) {
+        constexpr uint32_t INF_BITS = DT == DT_BF16 ? 0x7F80u : 0x7C00u;
+        uint32_t amax = 0u;
+        if (!T::IS_INT && ep.owned > 0) {
+#pragma unroll
+            for (int w = 0; w < FAST_WAVES; ++w) amax = amax_w[w] > amax ? amax_w[w] : amax;
+        }
+        const bool nan_seen = amax > INF_BITS;                  // a NaN hides the largest of the others
+        float amax_again = 0.f;
+        for (int t = tid; t < BM + BN; t += THREADS) {
             if (t < BM) {
                 const int gr = m0 + t;
                 if (gr < M) {
-                    atomic_add_word(g.rc_obs + (long)bz * M + gr, add_t(rs_part[t], rs_part[BM + t]));
-                    if (ep.owned > 0) atomic_add_word(g.rc_pred + (long)bz * M + gr, rp[t]);
+                    if constexpr (STO)
+                        unsafeAtomicAdd(reinterpret_cast<float *>(g.rc_sto) + (long)bz * M + gr, (rs_sto[t] + rs_sto[BM + t]) + (rs_sto[2 * BM + t] + rs_sto[3 * BM + t]));
+                    atomic_add_word(g.rc_obs + (long)bz * M + gr, add_t(add_t(rs_part[t], rs_part[BM + t]), add_t(rs_part[2 * BM + t], rs_part[3 * BM + t])));
+                    if (ep.owned > 0) {
+                        acc_t v = add_t(add_t(rp_part[t], rp_part[BM + t]), add_t(rp_part[2 * BM + t], rp_part[3 * BM + t]));
+                        if constexpr (!T::IS_INT) {
+                            if (nan_seen || !(fabsf(v) < __builtin_inff())) v = fast_dot_again<DT>(g, ep, bz, gr, &amax_again);
+                        }
+                        atomic_add_word(g.rc_pred + (long)bz * M + gr, v);
+                    }
                 }
             } else {
                 const int gc = n0 + (t - BM);
+                if constexpr (STO) {
+                    if (gc < N) unsafeAtomicAdd(reinterpret_cast<float *>(g.cc_sto) + (long)bz * N + gc, cs_sto[t - BM] + cs_sto[BN + t - BM]);
+                }
                 if (gc < N)
                     atomic_add_word(g.cc_obs + (long)bz * N + gc, add_t(cs_part[t - BM], cs_part[BN + t - BM]));
             }
         }
-        // column sums of A over this tile's rows, for the slabs this workgroup reduced
-        for (int t = tid; t < ep.owned * KE && !g.a_given; t += 256) {
-            const int k = (ep.slab0 + (t / KE) * ep.slab_step) * KE + (t % KE);
-            if (k < g.K) {
-                acc_t v = from_word<acc_t>(ep.col_lds[t]);
-                for (int w = 1; w < 4; ++w) v = add_t(v, from_word<acc_t>(ep.col_lds[w * ep.col_stride + t]));
-                atomic_add_word(g.a_sum + (long)bz * g.K + k, v);
+        if constexpr (STO) {
+            // One atomic per tile: on one word they are served one after the other (bf16 6304 x 3072 x 768, 600 tiles: with the
+            // verify behind it 110 us with one per wave, 74 so)
+            if (tid == 64) {
+                float m = 0.f;
+                for (int w = 0; w < FAST_WAVES; ++w) m = fmaxf(m, cmax_w[w]);
+                if (m > 0.f) atomicMax(g.c_max + bz, __float_as_uint(m));
             }
         }
-        if (!T::IS_INT && tid == 0 && !g.a_given && ep.owned > 0) {
-            const float m = fmaxf(fmaxf(amax4[0], amax4[1]), fmaxf(amax4[2], amax4[3]));
-            if (m > 0.f) atomicMax(g.a_max + bz, __float_as_uint(m));
+        // column sums of A over this tile's rows, for the slabs this workgroup reduced
+        for (int t = tid; t < ep.owned * KE && !g.a_given; t += THREADS) {
+            const int k = (ep.slab0 + (t / KE) * ep.slab_step) * KE + (t % KE);
+            acc_t v = from_word<acc_t>(ep.col_lds[t]);
+            if constexpr (!T::IS_INT) {
+                if (!(fabsf(v) < __builtin_inff())) v = fast_col_again<DT>(g, bz, m0, M - m0 < BM ? M - m0 : BM, k);
+            }
+            atomic_add_word(g.a_sum + (long)bz * g.K + k, v);
+        }
+        if (!T::IS_INT && !g.a_given && ep.owned > 0) {
+            if (nan_seen) {
+                if (amax_again > 0.f) atomicMax(g.a_max + bz, __float_as_uint(amax_again));
+            } else if (tid == 0 && amax > 0u) {
+                atomicMax(g.a_max + bz, __float_as_uint(DT == DT_BF16 ? bf16_bits_to_f32(amax) : f16_bits_to_f32(amax)));
+            }
         }
     }
 }
 
 // With and without a layer bias: two copies of the epilogue behind one uniform branch (a test per
 // group of four values inside one copy costs a branch per group).
-template <int DT, int BM, int BN, bool PROT>
+template <int DT, int BM, bool PROT, bool STO>
 __device__ __forceinline__ void gemm_epilogue(const GemmArgs &g,
-                                              typename Traits<DT>::accv_t (&acc)[BM / 64][BN / 64],
-                                              uint8_t *smem, int m0, int n0, int bz, const EpiProt<DT> &ep)
+                                              typename Traits<DT>::accv_t (&acc)[BM / 64][2],
+                                              uint8_t *smem, int m0, int n0, int bz, const EpiProt<DT, BM / 64> &ep)
 {
-    if (g.bias != nullptr) gemm_epilogue_impl<DT, BM, BN, PROT, true>(g, acc, smem, m0, n0, bz, ep);
-    else gemm_epilogue_impl<DT, BM, BN, PROT, false>(g, acc, smem, m0, n0, bz, ep);
+    if (g.bias != nullptr) gemm_epilogue_impl<DT, BM, PROT, STO, true>(g, acc, smem, m0, n0, bz, ep);
+    else gemm_epilogue_impl<DT, BM, PROT, STO, false>(g, acc, smem, m0, n0, bz, ep);
 }
 
 }  // namespace abft

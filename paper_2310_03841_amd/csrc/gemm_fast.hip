@@ -3,10 +3,18 @@
 //   * global -> LDS with direct-to-LDS loads (global_load_lds_dwordx4): no VGPR staging.  One
 //     wave instruction fills 8 LDS rows of 128 bytes; the XOR swizzle of the LDS layout is
 //     applied by choosing which global 16-byte chunk each lane fetches.
-//   * 256 x 256 tiles, 4 waves of 128 x 128 (sixteen 32x32 MFMA blocks per wave), two LDS
-//     buffers of 64 KB, one barrier per slab; 128 x 256 tiles fill the last, partial round.
-//   * the loads of the next-but-one slab are issued one by one between the MFMAs of a slab's
-//     last step, without branches.
+//   * 256 x 256 tiles by eight waves of 128 x 64 (eight 32x32 MFMA blocks per wave), 128 x 256 tiles by eight of 64 x 64;
+//     one barrier per slab, loads spread evenly between the MFMAs.
+//   * two waves per SIMD: what one wave spends on issuing loads, fragment reads and the epilogue's vector instructions, the other
+//     fills with MFMAs.  With one (four waves of 128 x 128, the LDS traffic of a slab 192 instead of 256 KB) every instruction
+//     beside an MFMA costs five clocks of the only wave there is.  What bounded that loop was not LDS bandwidth, which a
+//     micro-benchmark puts at 256 bytes per clock for 16-byte fragment reads (64 KB of them per 32 KB loaded cost nothing), but issue:
+//     the vector memory path takes a load of 1 KB every 18 clocks per compute unit, and all of a slab's loads in one of its four steps
+//     held every wave there.  Four waves / eight, clocks per slab (MFMAs alone 2048 and 1024): 256 x 256
+//     2388 / 2152, 128 x 256 1526 / 1130; epilogue of a 256 x 256 tile, unprotected 5500 / 3900, protected 12000 / 10200.
+//     bf16, unprotected: 6304 x 768 x 768 11.9 -> 10.7 us, 6304 x 768 x 3072 40.9 -> 32.6, 12608 x 3072 x 768 57.9 -> 55.0, 4096 x 4096 x 4096
+//     103 -> 100.  The large ones are power-limited: of the 11 % fewer clocks the chip takes back most by its clock (1.73 -> 1.56
+//     GHz over 4096 x 4096 x 4096).
 //   * MFMAs take the B fragment first, so a lane owns a row of C (see gemm_epilogue.h).
 //   * workgroup -> tile mapping keeps the workgroups that share an XCD (and its L2) on a
 //     compact group of tiles.
@@ -24,71 +32,96 @@
 
 namespace abft {
 
-constexpr int BIG_LDS = 2 * (256 + 256) * SLAB_BYTES, BESIDE_BUFS = 3, BESIDE_LDS = BESIDE_BUFS * (128 + 256) * SLAB_BYTES;
-
 typedef const __attribute__((address_space(1))) void *gas_ptr;
 typedef __attribute__((address_space(3))) void *las_ptr;
 
 // Unprotected; protected, the tiles reduce A; protected, workgroups beside the tiles do.  A kernel for each: the last
-// has no code for owned slabs, the others none for the pass beside them, and its 128-row tiles keep
-// three operand buffers: the pass beside them makes their loads wait longer (f16 6304 x 768 x 3072 52.1 -> 50.7 us, 4363 x
-// 1024 x 3264 57.3 -> 54.2; int8 of a dozen slabs 1-2 % slower than with two, and still 0.94 of tiles that reduce A: 15 random
-// ones 0.87 to 0.98).  Without that pass the third buffer only adds its
-// loads to the start of a tile: unprotected 3834 x 1216 x 768 18.0 -> 19.1, 1984 x 2303 x 4032 55.7 -> 58.
+// has no code for owned slabs, the others none for the pass beside them.
 enum { FAST_PLAIN, FAST_OWN, FAST_BESIDE };
 
-// One BM x BN tile with origin (m0, n0) of batch item bz.
-// NB: operand buffers, one slab each; what the pass over A keeps lies behind them.
-template <int DT, int BM, int BN, int NB, int MODE>
+// LDS of a tile: a slab is MI units of A and 2 NI of B, 64 rows of 128 bytes each: one load instruction of every wave.  Unit mi of A
+// holds the rows of block row mi of both wave rows, unit (ni, h) of B those of block column ni of wave columns 2 h and 2 h + 1.
+// The first FM units of A and the first 2 FN of B have three buffers, the others two.
+template <int BM, int FM, int FN> struct FastLds {
+    static constexpr int MI = BM / 64, NI = 2, UNIT = 64 * SLAB_BYTES;
+    static constexpr int NLD = MI + 2 * NI;                                // units
+    static constexpr int NF = FM + 2 * FN, NR = NLD - NF;                  // those with three buffers, with two
+    static constexpr int F_BYTES = NF * UNIT, R_BYTES = NR * UNIT, BYTES = 3 * F_BYTES + 2 * R_BYTES;
+    // Load q of a slab: first the units with two buffers, A then B, then those with three.
+    static constexpr bool ring3(int q) { return q >= NR; }
+    static constexpr bool is_a(int q) { return q < NR ? q < MI - FM : q < NR + FM; }
+    static constexpr int unit(int q)                                       // mi, or 2 ni + h
+    {
+        return q < NR ? (q < MI - FM ? FM + q : 2 * FN + q - (MI - FM)) : q < NR + FM ? q - NR : q - NR - FM;
+    }
+    // Loads of the four steps from a slab's barrier on: the first of them go where the next barrier needs them.
+    static constexpr int by_step(int n) { return n == 0 ? 0 : n == 1 ? (3 * NLD + 7) / 8 : n == 2 ? (5 * NLD + 7) / 8 : n == 3 ? 7 * NLD / 8 : NLD; }
+    // where it lies in its buffer
+    static constexpr int at(int q) { return (q < NR ? q : q - NR) * UNIT; }
+    static constexpr int load_of_a(int mi) { return mi < FM ? NR + mi : mi - FM; }
+    static constexpr int load_of_b(int ni) { return ni < FN ? NR + FM + 2 * ni : MI - FM + 2 * (ni - FN); }      // h = 0
+};
+template <int MODE, int BM> struct FastShape;
+template <int MODE> struct FastShape<MODE, 256> { typedef FastLds<256, MODE == FAST_OWN ? 3 : 4, 0> lds; };
+template <int MODE> struct FastShape<MODE, 128> { typedef FastLds<128, 2, 2> lds; };
+template <int MODE> constexpr int fast_lds_bytes()
+{
+    const int b = FastShape<MODE, 256>::lds::BYTES, s = FastShape<MODE, 128>::lds::BYTES;
+    return b > s ? b : s;
+}
+
+// One BM x 256 tile with origin (m0, n0) of batch item bz.
+// What the pass over A keeps lies behind the operand buffers.
+template <int DT, int BM, int MODE, bool STO>
 __device__ __forceinline__ void fast_tile(const GemmArgs &g, uint8_t *smem, int m0, int n0, int bz, int tn)
 {
     using T = Traits<DT>;
+    using L = typename FastShape<MODE, BM>::lds;
     typedef typename T::accv_t accv_t;
+    typedef __attribute__((address_space(3))) uint8_t *lds_ptr;
+    typedef __attribute__((address_space(3))) void *lds_void;
+    typedef const __attribute__((address_space(3))) i32x4 *lds_frag;
     constexpr int ES = T::ES;
     constexpr int KE = SLAB_BYTES / ES;
-    constexpr int TM = BM / 2, TN = BN / 2;
-    constexpr int MI = TM / 32, NI = TN / 32;
-    constexpr int GA = BM / 32, GB = BN / 32;     // 8-row load groups per wave per slab
-    constexpr int BUF = (BM + BN) * SLAB_BYTES;
+    constexpr int TM = BM / 2, TN = 64;
+    constexpr int MI = L::MI, NI = L::NI, NMF = MI * NI, NFR = MI + NI;
+    constexpr int NF = L::NF, NR = L::NR, NLD = L::NLD;
     constexpr bool PROT = MODE != FAST_PLAIN, OWN = MODE == FAST_OWN;
 
     const int tid = tile_thread_index(), lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);      // wave-uniform by construction
-    const int wm = wave >> 1, wn = wave & 1;
+    const int wm = wave >> 2, wn = wave & 3;
     const int l32 = lane & 31, lh = lane >> 5;
     const int M = g.M, N = g.N, K = g.K;
 
-    const uint8_t *Ab = g.A + (long)bz * g.sA * ES;
-    const uint8_t *Bb = g.B + (long)bz * g.sB * ES;
-
-    // ---- global sources.  Load group p of this wave covers tile rows (4 p + wave) * 8 .. + 8;
-    // lane l lands in LDS row + (l >> 3), slot (l & 7), and fetches the chunk for which
+    // ---- global sources.  This wave's load of a unit fills its LDS rows 8 wave .. + 8;
+    // lane l lands in row + (l >> 3), slot (l & 7), and fetches the chunk for which
     // LDS slot = chunk ^ ((row >> 1) & 7).  (A 16-byte fragment read is served sixteen lanes at a
     // time from 64 banks: sixteen consecutive rows must fall on sixteen different 16-byte bank
     // groups.  Two consecutive 128-byte rows span all 64 banks, so the eight even rows need eight
     // different slots, and so do the eight odd rows; chunk ^ (row & 7) makes rows r and r + 8
-    // collide, which the LDS bank-conflict counter showed as half of all LDS cycles.)  An address is a wave-uniform base (tile origin plus
-    // the slab's offset along K) plus a per-lane 32-bit offset that never changes, so issuing a
-    // load inside the main loop costs no vector arithmetic and no branch.  Rows of the tile past
+    // collide, which the LDS bank-conflict counter showed as half of all LDS cycles.)  Buffer loads: the tile's
+    // origin in a descriptor, a lane's offset inside the tile, which never changes, in a register, the slab's in a scalar, so
+    // that a load inside the main loop is itself and the word that says where it goes.  Rows of the tile past
     // the end of the matrix fetch the last valid row instead.
     const int lrow = lane >> 3;
     const int lchunk = (lane & 7) ^ (((wave & 1) << 2) + (lrow >> 1));
-    const uint8_t *a_base = Ab + (long)m0 * g.lda * ES;
-    const uint8_t *b_base = Bb + (long)n0 * g.ldb * ES;
-    uint32_t a_off[GA], b_off[GB];
-#pragma unroll
-    for (int p = 0; p < GA; ++p) {
-        int r = (4 * p + wave) * 8 + lrow;
-        r = r < M - m0 ? r : M - m0 - 1;
-        a_off[p] = (uint32_t)r * (uint32_t)(g.lda * ES) + lchunk * 16;
-    }
-#pragma unroll
-    for (int p = 0; p < GB; ++p) {
-        int r = (4 * p + wave) * 8 + lrow;
-        r = r < N - n0 ? r : N - n0 - 1;
-        b_off[p] = (uint32_t)r * (uint32_t)(g.ldb * ES) + lchunk * 16;
-    }
+    constexpr int RSRC_FLAGS = 0x00027000;
+    const __amdgpu_buffer_rsrc_t a_src = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<uint8_t *>(g.A + ((long)bz * g.sA + (long)m0 * g.lda) * ES), 0, 0x7FFFFFFF, RSRC_FLAGS);
+    const __amdgpu_buffer_rsrc_t b_src = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<uint8_t *>(g.B + ((long)bz * g.sB + (long)n0 * g.ldb) * ES), 0, 0x7FFFFFFF, RSRC_FLAGS);
+    int off[NLD];
+    static_for<0, NLD>([&](auto q_c) {
+        constexpr int q = decltype(q_c)::value, u = L::unit(q);
+        constexpr bool is_a = L::is_a(q);
+        const int in = (wave & 3) * 8 + lrow, last = (is_a ? M - m0 : N - n0) - 1;
+        int r = is_a ? (wave >> 2) * TM + u * 32 + in : (2 * (u & 1) + (wave >> 2)) * TN + (u >> 1) * 32 + in;
+        r = r < last ? r : last;
+        off[q] = r * (int)((is_a ? g.lda : g.ldb) * ES) + lchunk * 16;
+    });
     const int a_rows = M - m0;                        // rows of this tile inside A
+    const int nslab = K / KE;                         // at least 3 (gemm_fast_eligible)
 
     // The accumulators are never zero-filled: the first MFMA of every block takes a literal
     // zero as its addend.  Every block is always computed, also where the tile hangs over the
@@ -98,241 +131,232 @@ __device__ __forceinline__ void fast_tile(const GemmArgs &g, uint8_t *smem, int 
 #pragma unroll
     for (int i = 0; i < 16; ++i) zerov[i] = T::zero();
 
-    auto issue_loads = [&](int s, int buf) __attribute__((always_inline)) {
-        const uint8_t *ak = a_base + (long)s * SLAB_BYTES;
-        const uint8_t *bk = b_base + (long)s * SLAB_BYTES;
-        uint8_t *sA = smem + buf * BUF;
-        uint8_t *sB = sA + BM * SLAB_BYTES;
-#pragma unroll
-        for (int p = 0; p < GA; ++p)
-            __builtin_amdgcn_global_load_lds((gas_ptr)(ak + a_off[p]), (las_ptr)(sA + (4 * p + wave) * 8 * SLAB_BYTES), 16, 0, 0);
-#pragma unroll
-        for (int p = 0; p < GB; ++p)
-            __builtin_amdgcn_global_load_lds((gas_ptr)(bk + b_off[p]), (las_ptr)(sB + (4 * p + wave) * 8 * SLAB_BYTES), 16, 0, 0);
+    // The buffers of a slab: f of those in rings of three, r of two.
+    const lds_ptr lds = (lds_ptr)smem;
+    struct Buf { int f, r; };
+    auto load = [&](auto q_c, int s, Buf to) __attribute__((always_inline)) {
+        constexpr int q = decltype(q_c)::value;
+        const lds_ptr dst = lds + ((L::ring3(q) ? to.f : to.r) + wave * 8 * SLAB_BYTES) + L::at(q);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(L::is_a(q) ? a_src : b_src, (lds_void)dst, 16, off[q], s * SLAB_BYTES, 0, 0);
     };
     // ---- main loop, software-pipelined by hand.  A slab is four MFMA steps of 32 bytes of K.
     // The fragments of step t+1 are read from LDS while the MFMAs of step t run (two register
-    // sets); the reads are issued in the first half of a step so that the second half covers
-    // their latency.  The barrier sits between steps 2 and 3: by then every wave has read its
-    // step-3 fragments, so nobody reads this slab's buffer any more and the loads of slab s+NB
-    // are issued into it at once, spread between the MFMAs of step 3, which also prefetches
-    // step 0 of slab s+1.  The loop is peeled (first slab: literal-zero addend; last NB slabs:
-    // nothing left to load) so that no branch separates loads and MFMAs.
+    // sets).  The barrier sits between steps 2 and 3: by then every wave has
+    // read its step-3 fragments, so nobody reads this slab's buffers any more.  From there on, over the four steps up to the
+    // next slab's barrier, the loads into those buffers are issued: the units with two buffers of slab s + 2, then those with
+    // three of slab s + 3.
     i32x4 fa[2][MI], fb[2][NI];
-    auto ldfr = [&](int buf, int s4, int set) __attribute__((always_inline)) {
-        const uint8_t *sA = smem + buf * BUF;
-        const uint8_t *sB = sA + BM * SLAB_BYTES;
-        const int sw = ((2 * s4 + lh) ^ ((lane >> 1) & 7)) * 16;
-#pragma unroll
-        for (int mi = 0; mi < MI; ++mi)
-            fa[set][mi] = *reinterpret_cast<const i32x4 *>(sA + (wm * TM + mi * 32 + l32) * SLAB_BYTES + sw);
-#pragma unroll
-        for (int ni = 0; ni < NI; ++ni)
-            fb[set][ni] = *reinterpret_cast<const i32x4 *>(sB + (wn * TN + ni * 32 + l32) * SLAB_BYTES + sw);
+    // a lane's place in a unit of A at step 0 (row l32 of this wave's half); at step t chunk 2 t + lh, so bits 5 and 6 change
+    const int frag_at = wm * 32 * SLAB_BYTES + l32 * SLAB_BYTES + (lh ^ ((lane >> 1) & 7)) * 16;
+    const int b_from_a = (wn - wm) * 32 * SLAB_BYTES; // the same in a unit of B, from unit h = 0 on
+    // fragment j of step t: of B, then of A
+    auto fragment = [&](auto j_c, auto t_c, Buf b) __attribute__((always_inline)) {
+        constexpr int j = decltype(j_c)::value, t = decltype(t_c)::value, set = t & 1;
+        constexpr bool isb = j < NI;
+        constexpr int q = isb ? L::load_of_b(isb ? j : 0) : L::load_of_a(isb ? 0 : j - NI);
+        const int base = (L::ring3(q) ? b.f : b.r) + (isb ? b_from_a : 0);
+        const i32x4 v = *(lds_frag)(lds + ((frag_at ^ (32 * t)) + base) + L::at(q));
+        if constexpr (isb) fb[set][isb ? j : 0] = v;
+        else fa[set][isb ? 0 : j - NI] = v;
     };
-    auto mfmas = [&](auto first_c, int set) __attribute__((always_inline)) {
-        constexpr bool FIRST = decltype(first_c)::value;
-#pragma unroll
-        for (int mi = 0; mi < MI; ++mi)
-#pragma unroll
-            for (int ni = 0; ni < NI; ++ni)
-                acc[mi][ni] = T::mfma(fb[set][ni], fa[set][mi], FIRST ? zerov : acc[mi][ni]);
-    };
-    auto interleave = [&]() __attribute__((always_inline)) {
-        // scheduling directive: (MFMA, LDS read) x (MI + NI), then the remaining MFMAs
-#pragma unroll
-        for (int j = 0; j < MI + NI; ++j) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-        }
-        __builtin_amdgcn_sched_group_barrier(0x008, MI * NI - (MI + NI), 0);
-    };
-    // Step 3 of a slab that still has loads to issue, in explicit program order: after every
-    // MFMA (register set 1) one fragment read of the next slab's step 0 (into set 0) while
-    // there are any, and this MFMA's share of the GA + GB direct-to-LDS loads of slab s + NB.
-    // The scheduling fences keep that order; left alone, the compiler issues all loads in one
-    // burst behind the barrier and the matrix pipe waits for them.
-    auto step3_loads = [&](int s2, int buf, int nbuf) __attribute__((always_inline)) {
-        constexpr int NMF = MI * NI, NLD = GA + GB;
-        const uint8_t *ak = a_base + (long)s2 * SLAB_BYTES;
-        const uint8_t *bk = b_base + (long)s2 * SLAB_BYTES;
-        uint8_t *dA = smem + buf * BUF;
-        uint8_t *dB = dA + BM * SLAB_BYTES;
-        const uint8_t *sA = smem + nbuf * BUF;
-        const uint8_t *sB = sA + BM * SLAB_BYTES;
-        const int sw = (lh ^ ((lane >> 1) & 7)) * 16;
-        static_for<0, NMF>([&](auto j_c) {
-            constexpr int j = decltype(j_c)::value;
-            constexpr int mi = j / NI, ni = j % NI;
-            acc[mi][ni] = T::mfma(fb[1][ni], fa[1][mi], acc[mi][ni]);
-            if constexpr (j < MI)
-                fa[0][j] = *reinterpret_cast<const i32x4 *>(sA + (wm * TM + j * 32 + l32) * SLAB_BYTES + sw);
-            else if constexpr (j < MI + NI)
-                fb[0][j - MI] = *reinterpret_cast<const i32x4 *>(sB + (wn * TN + (j - MI) * 32 + l32) * SLAB_BYTES + sw);
-            constexpr int l0 = j * NLD / NMF, l1 = (j + 1) * NLD / NMF;
-            static_for<l0, l1>([&](auto l_c) {
-                constexpr int l = decltype(l_c)::value;
-                if constexpr (l < GA)
-                    __builtin_amdgcn_global_load_lds((gas_ptr)(ak + a_off[l]), (las_ptr)(dA + (4 * l + wave) * 8 * SLAB_BYTES), 16, 0, 0);
-                else
-                    __builtin_amdgcn_global_load_lds((gas_ptr)(bk + b_off[l - GA]), (las_ptr)(dB + (4 * (l - GA) + wave) * 8 * SLAB_BYTES), 16, 0, 0);
-            });
-            __builtin_amdgcn_sched_barrier(0);
-        });
+    // MFMA j of step t (set t & 1)
+    auto mfma = [&](auto first_c, auto t_c, auto j_c) __attribute__((always_inline)) {
+        constexpr int set = decltype(t_c)::value & 1, mi = decltype(j_c)::value / NI, ni = decltype(j_c)::value % NI;
+        acc[mi][ni] = T::mfma(fb[set][ni], fa[set][mi], decltype(first_c)::value ? zerov : acc[mi][ni]);
     };
     // Protected tiles reduce the slabs of A they own (slab s belongs to tile column s mod
     // tiles_n) while those are resident: see gemm_apass.h.
-    constexpr int AUX_OFF = BIG_LDS;                   // behind the buffers of the largest tile
-    uint32_t *col_lds = reinterpret_cast<uint32_t *>(smem + AUX_OFF);
-    EpiProt<DT> ep;
-    ep.st.rdot = T::zero(); ep.st.amax = 0.f;
-    ep.col_lds = col_lds; ep.slab0 = tn; ep.slab_step = g.tiles_n; ep.owned = 0;
-    ep.col_stride = 0;
+    constexpr int AUX_OFF = fast_lds_bytes<MODE>();    // behind the buffers of the larger tile
+    EpiProt<DT, MI> ep;
+    ep.slab0 = tn; ep.slab_step = g.tiles_n; ep.owned = (OWN && tn < nslab) ? (nslab - tn + g.tiles_n - 1) / g.tiles_n : 0;
+    ep.col_lds = reinterpret_cast<uint32_t *>(smem + AUX_OFF);
+    ep.back = 1.f;
     {
-        const int nslab = K / KE;                      // at least 3 (gemm_fast_eligible)
-        int next_own = tn;
-        const int owned = (OWN && tn < nslab) ? (nslab - tn + g.tiles_n - 1) / g.tiles_n : 0;
-        // column sums: one set of owned * KE words per wave (plain stores, added up by the epilogue)
-        ep.col_stride = owned * KE;
-        uint32_t *col_mine = col_lds + wave * owned * KE;
-        uint32_t *b_lds = col_lds + 4 * owned * KE;
-        if (OWN) {
-            // the values of b the owned slabs need, straight into LDS (one slab per wave and turn):
-            // in place behind the first barrier
-            for (int j = wave; j < owned; j += 4) {
-                const uint32_t *src = g.b_sum + (long)bz * K + (long)(tn + j * g.tiles_n) * KE + lane;
+        int next_own = tn, own_at = 0;                 // the next slab to reduce, and its place among the owned
+        // column sums, [owned][KE]; terms of b, [2][3][KE]; zeros; words of b, [2][KE]
+        constexpr int TERM = SLAB_BYTES, TERMS = 3 * TERM;
+        uint8_t *const terms = smem + AUX_OFF + ep.owned * KE * 4;
+        uint32_t *const words = reinterpret_cast<uint32_t *>(terms + 2 * TERMS + TERM);
+        // b of the j-th owned slab, straight into LDS, two owned slabs ahead.  (A register would be waited for together
+        // with every operand load behind it.)
+        auto fetch_b = [&](int j) __attribute__((always_inline)) {
+            if (wave < KE / 64 && j < ep.owned)
+                __builtin_amdgcn_global_load_lds((gas_ptr)(g.b_sum + (long)bz * K + (tn + j * g.tiles_n) * KE + 64 * wave + lane),
+                                                 (las_ptr)(words + (j & 1) * KE + 64 * wave), 4, 0, 0);
+        };
+        if constexpr (OWN) {
+            fetch_b(0);
+            fetch_b(1);
 #pragma unroll
-                for (int h = 0; h < KE / 64; ++h)
-                    __builtin_amdgcn_global_load_lds((gas_ptr)(src + 64 * h), (las_ptr)(b_lds + j * KE + 64 * h), 4, 0, 0);
-            }
+            for (int mi = 0; mi < MI; ++mi) ep.pass.dot[mi] = acc4_zero<DT>();
+            ep.pass.amax = 0u;
+            for (int i = tid; i < ep.owned * KE + SLAB_BYTES / 4; i += 64 * FAST_WAVES)
+                reinterpret_cast<uint32_t *>(smem + AUX_OFF)[i < ep.owned * KE ? i : i + 2 * TERMS / 4] = 0u;
         }
-#pragma unroll
-        for (int p = 0; p < NB; ++p) issue_loads(p, p);
-        // Start as soon as slab 0 is in place: loads complete in order, so "at most the GA + GB
-        // loads of each slab behind it outstanding" means everything issued before them has landed.
-        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"((NB - 1) * (GA + GB)) : "memory");
-        ldfr(0, 0, 0);
-        // the barrier of slab s: slab s + 1 is in place, the loads of `behind` slabs after it may be under way
+        // buffers of slabs s, s + 1, s + 2 (three-buffer units; two-buffer units of s + 2: those of s)
+        int f0 = 0, f1 = L::F_BYTES, f2 = 2 * L::F_BYTES, r0 = 3 * L::F_BYTES, r1 = r0 + L::R_BYTES;
+        auto next = [&]() __attribute__((always_inline)) {
+            const int f = f0, r = r0;
+            f0 = f1; f1 = f2; f2 = f;
+            r0 = r1; r1 = r;
+        };
+        static_for<0, NLD>([&](auto q_c) { load(q_c, 0, Buf{f0, r0}); });
+        static_for<0, NLD>([&](auto q_c) { load(q_c, 1, Buf{f1, r1}); });
+        // Start as soon as slab 0 is in place: loads complete in order, so "at most the loads of the
+        // slab behind it outstanding" means everything issued before them has landed.
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(NLD) : "memory");
+        static_for<0, NFR>([&](auto j_c) { fragment(j_c, std::integral_constant<int, 0>{}, Buf{f0, r0}); });
+        // The barrier of slab s: slab s + 1 is in place; what was requested after it are the units with three buffers of
+        // slab s + 2 (or nothing any more).
         auto slab_barrier = [&](auto behind_c) __attribute__((always_inline)) {
-            if constexpr (NB == 2) __syncthreads();
-            else asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(decltype(behind_c)::value * (GA + GB)) : "memory");
+            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(decltype(behind_c)::value ? NF : 0) : "memory");
         };
-        typedef std::integral_constant<int, NB - 2> all_behind;
-        typedef std::integral_constant<int, 0> none_behind;
-        // own_c: whether the slab can be one that this workgroup reduces (the first slab and the last NB:
-        // the pass then runs ahead of the slab's MFMAs; the middle slabs have own_slab below)
-        auto slab = [&](auto first_c, auto loads_c, auto own_c, int s) __attribute__((always_inline)) {
-            constexpr bool LOADS = decltype(loads_c)::value;
-            const int buf = s % NB, nbuf = (s + 1) % NB;
-            if (OWN && decltype(own_c)::value && s == next_own) {
-                if (g.a_given)
-                    a_pass<DT, BM, true, true>(smem + buf * BUF, b_lds + ep.owned * KE, a_rows, col_mine + ep.owned * KE, ep.st);
-                else
-                    a_pass<DT, BM, false, true>(smem + buf * BUF, b_lds + ep.owned * KE, a_rows, col_mine + ep.owned * KE, ep.st);
+        // b of the next slab to reduce in terms of the operand type, a slab ahead of it
+        float scale = 1.f;
+        if constexpr (OWN && DT == DT_F16) b_scale(g.b_max[bz], N, &scale, &ep.back);
+        auto put_terms = [&]() __attribute__((always_inline)) {
+            if (wave < KE / 64) {
+                typename T::acc_t v = from_word<typename T::acc_t>(words[(own_at & 1) * KE + 64 * wave + lane]);
+                if constexpr (DT == DT_F16) v *= scale;
+                uint8_t *d = terms + (own_at & 1) * TERMS + (64 * wave + lane) * ES;
+#pragma unroll
+                for (int e = 0; e < 3; ++e) {
+                    const uint32_t h = b_term<DT>(v);
+                    if constexpr (ES == 1) d[e * TERM] = (uint8_t)h;
+                    else *reinterpret_cast<uint16_t *>(d + e * TERM) = (uint16_t)h;
+                }
+            }
+        };
+        if (OWN && tn == 0) {
+            put_terms();
+            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        }
+        auto own_ahead = [&](int s) __attribute__((always_inline)) {
+            if (OWN && s + 1 == next_own) put_terms();
+        };
+        auto own_done = [&](int s) __attribute__((always_inline)) {
+            if (OWN && s == next_own) {
                 next_own += g.tiles_n;
-                ep.owned += 1;
-            }
-            __builtin_amdgcn_sched_barrier(0);
-            ldfr(buf, 1, 1); mfmas(first_c, 0); interleave();
-            __builtin_amdgcn_sched_barrier(0);
-            ldfr(buf, 2, 0); mfmas(std::false_type{}, 1); interleave();
-            __builtin_amdgcn_sched_barrier(0);
-            ldfr(buf, 3, 1); mfmas(std::false_type{}, 0); interleave();
-            if constexpr (LOADS) {
-                slab_barrier(all_behind{});
-                step3_loads(s + NB, buf, nbuf);
-            } else {
-                if (NB > 2 && s + NB == nslab) slab_barrier(all_behind{});
-                else slab_barrier(none_behind{});
-                ldfr(nbuf, 0, 0);                      // after the last slab: read and never used
-                mfmas(std::false_type{}, 1); interleave();
-                __builtin_amdgcn_sched_barrier(0);
+                own_at += 1;
+                fetch_b(own_at + 1);
             }
         };
-        // A middle slab that this workgroup reduces: the same MFMAs, fragment reads and loads as any
-        // other slab, in explicit program order (one group per MFMA, fenced), with one piece of the
-        // pass over the slab (gemm_apass.h) behind every MFMA.  The pieces start half a step late, so
-        // that the chunks begin() requested have arrived.  Straight-line code of its own: a branch
-        // around the pass inside the common slab code keeps it apart from the MFMAs, and the pass
-        // then runs while the matrix pipe waits.
-        // (With a checksum of A supplied by the caller the column sums and the maximum are formed all
-        // the same, under the MFMAs, and not handed on: a second copy of the slab would have to sit
-        // behind a branch.)
-        auto own_slab = [&](int s) __attribute__((always_inline)) {
-            constexpr bool GIVEN = false;
-            constexpr int NMF = MI * NI, NLD = GA + GB, LAG = NMF / 2;
-            const int buf = s % NB, nbuf = (s + 1) % NB;
-            APassSteps<DT, BM, GIVEN> ap;
-            __builtin_amdgcn_sched_barrier(0);
-            ap.begin(smem + buf * BUF, b_lds + ep.owned * KE, a_rows);
-            const uint8_t *ak = a_base + (long)(s + NB) * SLAB_BYTES;
-            const uint8_t *bk = b_base + (long)(s + NB) * SLAB_BYTES;
-            uint8_t *dA = smem + buf * BUF;
-            uint8_t *dB = dA + BM * SLAB_BYTES;
+        // The pass over step t of a slab this tile owns, on the fragments of that step: by one of the four waves that hold them, such
+        // that the two waves of a SIMD are not at it together.
+        const int my_step = (wn + 2 * wm) & 3;
+        auto reduce = [&](auto t_c) __attribute__((always_inline)) {
+            constexpr int t = decltype(t_c)::value, set = t & 1;
+            constexpr int NU = T::IS_INT ? 2 : 1;
+#pragma unroll
+            for (int mi = 0; mi < MI; ++mi)                     // rows past the end hold the last one's elements: they are done with
+                if (wm * TM + mi * 32 + l32 >= a_rows) fa[set][mi] = i32x4{0, 0, 0, 0};
+            // lane: column c = lane & 15 of the product belongs to the rows of half c >> 2, and to term c & 3
+            const int c = lane & 15, term = (c >> 2) == ((lane >> 4) & 1) ? c & 3 : 3;
+            const uint8_t *src = terms + (term < 3 ? (own_at & 1) * TERMS + term * TERM : 2 * TERMS);
+            const i32x4 b = *reinterpret_cast<const i32x4 *>(src + t * 32 + lh * 16);
+            TurnSums<DT> ts;
+            const i32x4 id0 = turn_operand<DT>(lane, 0), id1 = T::IS_INT ? turn_operand<DT>(lane, 1) : id0;
+            pass_mfmas<DT, MI>(ep.pass.dot, ts, fa[set], b, id0, id1);
+            if constexpr (!T::IS_INT) {
+                typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+                u16x2 m = __builtin_bit_cast(u16x2, ep.pass.amax);
+#pragma unroll
+                for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+                    for (int w = 0; w < 4; ++w) m = __builtin_elementwise_max(m, __builtin_bit_cast(u16x2, fa[set][mi][w] & 0x7FFF7FFF));
+                ep.pass.amax = __builtin_bit_cast(uint32_t, m);
+                ts.c[0] += ts.c[1];
+            }
+#pragma unroll
+            for (int u = 0; u < NU; ++u) {
+                typename T::acc_t v = add_t(add_t((typename T::acc_t)ts.c[u][0], (typename T::acc_t)ts.c[u][1]),
+                                            add_t((typename T::acc_t)ts.c[u][2], (typename T::acc_t)ts.c[u][3]));
+                v = add_xor32(add_xor16(v));
+                if (lane < 16) lds_add_word(const_cast<uint32_t *>(ep.col_lds) + own_at * KE + t * (KE / 4) + 16 * u + lane, v);
+            }
+        };
+        // A slab with loads between its MFMAs, in explicit program order (one group per MFMA, fenced): left
+        // alone, the compiler issues all loads in one burst and the matrix pipe waits for them.  first_c: the first slab; all
+        // of slab 1 has been requested ahead of it.  The pass over a slab sits behind the MFMAs of a step, under a test of a
+        // scalar.
+        auto slab = [&](auto first_c, int s) __attribute__((always_inline)) {
+            constexpr bool FIRST = decltype(first_c)::value;
+            own_ahead(s);
+            const int own_step = OWN && s == next_own ? my_step : -1;
             static_for<0, 4>([&](auto t_c) {
                 constexpr int t = decltype(t_c)::value;
-                constexpr int set = t & 1, nset = set ^ 1;
-                // fragments of the next step: step t + 1 of this slab, or step 0 of the next slab
-                const uint8_t *sA = smem + (t < 3 ? buf : nbuf) * BUF;
-                const uint8_t *sB = sA + BM * SLAB_BYTES;
-                const int sw = ((2 * ((t + 1) & 3) + lh) ^ ((lane >> 1) & 7)) * 16;
+                // this step's loads: step 3 begins with those into this slab's buffers, steps 0 to 2 go on with those into the last one's
+                constexpr int at = t == 3 ? 0 : t + 1;
+                constexpr int q0 = FIRST && t < 3 ? NR + NF * t / 3 : L::by_step(at), q1 = FIRST && t < 3 ? NR + NF * (t + 1) / 3 : L::by_step(at + 1);
+                constexpr int RPM = NMF >= NFR ? 1 : 2;                // fragment reads behind an MFMA
                 static_for<0, NMF>([&](auto j_c) {
                     constexpr int j = decltype(j_c)::value;
-                    constexpr int mi = j / NI, ni = j % NI;
-                    acc[mi][ni] = T::mfma(fb[set][ni], fa[set][mi], acc[mi][ni]);
-                    if constexpr (j < MI)
-                        fa[nset][j] = *reinterpret_cast<const i32x4 *>(sA + (wm * TM + j * 32 + l32) * SLAB_BYTES + sw);
-                    else if constexpr (j < MI + NI)
-                        fb[nset][j - MI] = *reinterpret_cast<const i32x4 *>(sB + (wn * TN + (j - MI) * 32 + l32) * SLAB_BYTES + sw);
-                    if constexpr (t == 3) {
-                        constexpr int l0 = j * NLD / NMF, l1 = (j + 1) * NLD / NMF;
-                        static_for<l0, l1>([&](auto l_c) {
-                            constexpr int l = decltype(l_c)::value;
-                            if constexpr (l < GA)
-                                __builtin_amdgcn_global_load_lds((gas_ptr)(ak + a_off[l]), (las_ptr)(dA + (4 * l + wave) * 8 * SLAB_BYTES), 16, 0, 0);
-                            else
-                                __builtin_amdgcn_global_load_lds((gas_ptr)(bk + b_off[l - GA]), (las_ptr)(dB + (4 * (l - GA) + wave) * 8 * SLAB_BYTES), 16, 0, 0);
-                        });
-                    }
-                    ap.template piece<t * NMF + j - LAG>();
+                    mfma(std::integral_constant<bool, FIRST && t == 0>{}, t_c, j_c);
+                    static_for<(j * RPM < NFR ? j * RPM : NFR), (j * RPM + RPM < NFR ? j * RPM + RPM : NFR)>([&](auto r_c) {
+                        fragment(r_c, std::integral_constant<int, (t + 1) & 3>{}, t < 3 ? Buf{f0, r0} : Buf{f1, r1});
+                    });
+                    static_for<q0 + (q1 - q0) * j / NMF, q0 + (q1 - q0) * (j + 1) / NMF>([&](auto q_c) {
+                        constexpr int q = decltype(q_c)::value;
+                        int to = s + (t == 3 ? 1 : 0) + (q < NR ? 1 : 2);
+                        if (FIRST && t == 3 && q >= NR) to = to < nslab ? to : nslab - 1;      // of three slabs: bytes nobody reads
+                        load(q_c, to, t == 3 ? Buf{f0, r0} : Buf{f2, r1});
+                    });
                     __builtin_amdgcn_sched_barrier(0);
                 });
-                if constexpr (t == 2) slab_barrier(all_behind{});
+                if (OWN && own_step == t) reduce(t_c);
+                __builtin_amdgcn_sched_barrier(0);
+                if constexpr (t == 2) slab_barrier(std::true_type{});
             });
-            static_for<4 * NMF - LAG, 4 * NMF>([&](auto k_c) { ap.template piece<decltype(k_c)::value>(); });
-            ap.end(col_mine + ep.owned * KE, ep.st);
-            __builtin_amdgcn_sched_barrier(0);
-            next_own += g.tiles_n;
-            ep.owned += 1;
+            own_done(s);
+            next();
         };
-        typedef std::false_type never_own;
-        typedef std::true_type maybe_own;
-        slab(std::true_type{}, std::true_type{}, maybe_own{}, 0);
-        // the middle slabs: runs of slabs that are not this workgroup's, each followed by one that is
+        // One of the last slabs: the loads that are still to come in groups ahead of a step's MFMAs.
+        auto tail_slab = [&](int s) __attribute__((always_inline)) {
+            own_ahead(s);
+            const int own_step = OWN && s == next_own ? my_step : -1;
+            static_for<0, 4>([&](auto t_c) {
+                constexpr int t = decltype(t_c)::value;
+                constexpr int at = t == 3 ? 0 : t + 1;
+                constexpr int q0 = L::by_step(at), q1 = L::by_step(at + 1), qr = q1 < NR ? q1 : NR < q0 ? q0 : NR;
+                const int ahead = s + (t == 3 ? 1 : 0);
+                if (q0 < qr && ahead + 1 < nslab) static_for<q0, qr>([&](auto q_c) { load(q_c, ahead + 1, Buf{f0, t == 3 ? r0 : r1}); });
+                if (qr < q1 && ahead + 2 < nslab) static_for<qr, q1>([&](auto q_c) { load(q_c, ahead + 2, Buf{t == 3 ? f0 : f2, r0}); });
+                __builtin_amdgcn_sched_barrier(0);
+                static_for<0, NMF>([&](auto j_c) {
+                    constexpr int j = decltype(j_c)::value;
+                    constexpr int RPM = NMF >= NFR ? 1 : 2;
+                    mfma(std::false_type{}, t_c, j_c);
+                    // after the last slab: read and never used
+                    static_for<(j * RPM < NFR ? j * RPM : NFR), (j * RPM + RPM < NFR ? j * RPM + RPM : NFR)>([&](auto r_c) {
+                        fragment(r_c, std::integral_constant<int, (t + 1) & 3>{}, t < 3 ? Buf{f0, r0} : Buf{f1, r1});
+                    });
+                    __builtin_amdgcn_sched_barrier(0);
+                });
+                if (OWN && own_step == t) reduce(t_c);
+                __builtin_amdgcn_sched_barrier(0);
+                if constexpr (t == 2) {
+                    if (s + 2 < nslab) slab_barrier(std::true_type{});
+                    else slab_barrier(std::false_type{});
+                }
+            });
+            own_done(s);
+            next();
+        };
+        slab(std::true_type{}, 0);
         int s = 1;
-        const int mid_end = nslab - NB;
-        // (loops and straight-line code only: an if / else with MFMAs in both arms would move the
-        // accumulators out of the accumulation registers)
-        if constexpr (OWN) {
-            while (next_own < mid_end) {                   // next_own >= s here
-                for (; s < next_own; ++s) slab(std::false_type{}, std::true_type{}, never_own{}, s);
-                own_slab(s);
-                ++s;
-            }
-        }
-        for (; s < mid_end; ++s) slab(std::false_type{}, std::true_type{}, never_own{}, s);
-        for (; s < nslab; ++s) slab(std::false_type{}, std::false_type{}, maybe_own{}, s);
+        for (; s < nslab - 3; ++s) slab(std::false_type{}, s);
+        for (; s < nslab; ++s) tail_slab(s);
     }
     __syncthreads();
-    gemm_epilogue<DT, BM, BN, PROT>(g, acc, smem, m0, n0, bz, ep);
+    gemm_epilogue<DT, BM, PROT, STO>(g, acc, smem, m0, n0, bz, ep);
 }
 
 // The grid mixes two tile shapes against wave quantisation: 256 x 256 tiles cover the first
 // big_rows rows, 128 x 256 tiles the rest; how many of each is chosen by playing the dispatch
 // through (choose_big_rows).  (600 big tiles on 256 CUs would be three rounds for 2.34 rounds
 // of work.)
-template <int DT, int MODE>
-__global__ __launch_bounds__(256) void gemm_fast_kernel(GemmArgs g)
+template <int DT, int MODE, bool STO>
+__global__ __launch_bounds__(64 * FAST_WAVES) void gemm_fast_kernel(GemmArgs g)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
     constexpr bool PROT = MODE != FAST_PLAIN;
@@ -341,7 +365,7 @@ __global__ __launch_bounds__(256) void gemm_fast_kernel(GemmArgs g)
     // The 128-row tiles come first in the list: the compute units that start with one are half a
     // tile ahead of the others from then on, so the two groups store their tiles of C at different
     // times (a round of the machine that stores in step asks for tens of MB at once) and draw on
-    // the matrix pipes at different times.  Measured on 12608 x 3072 x 768: 63 -> 60.5 us.
+    // the matrix pipes at different times.  Measured on 12608 x 3072 x 768 (tiles by four waves): 63 -> 60.5 us.
     const int per_item = g.n_small + g.n_big;
     const int total = per_item * g.batch;
     const int n_tile = MODE == FAST_BESIDE ? (int)gridDim.x - g.beside.n : (int)gridDim.x;
@@ -354,12 +378,12 @@ __global__ __launch_bounds__(256) void gemm_fast_kernel(GemmArgs g)
     for (int t = blockIdx.x; t < total; t += n_tile) {
         const int bz = t / per_item, bid = t - bz * per_item;
         int tm, tn;
-        if (bid >= g.n_small) {
+        if (!STO && bid >= g.n_small) {
             map_tile(bid - g.n_small, g.n_big, g.tiles_m_big, g.tiles_n, &tm, &tn);
-            fast_tile<DT, 256, 256, 2, MODE>(g, smem, tm * 256, tn * 256, bz, tn);
+            if constexpr (!STO) fast_tile<DT, 256, MODE, STO>(g, smem, tm * 256, tn * 256, bz, tn);
         } else {
             map_tile(bid, g.n_small, g.tiles_m_small, g.tiles_n, &tm, &tn);
-            fast_tile<DT, 128, 256, MODE == FAST_BESIDE ? BESIDE_BUFS : 2, MODE>(g, smem, g.tiles_m_big * 256 + tm * 128, tn * 256, bz, tn);
+            fast_tile<DT, 128, MODE, STO>(g, smem, g.tiles_m_big * 256 + tm * 128, tn * 256, bz, tn);
         }
         // the epilogue's last reads of LDS precede the next tile's first writes
         asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
@@ -368,11 +392,10 @@ __global__ __launch_bounds__(256) void gemm_fast_kernel(GemmArgs g)
 
 // ------------------------------------------------------------------------------------------
 // How many tile rows get 256-row tiles (the rest of M gets 128-row tiles).  Workgroups are
-// dispatched in index order to whichever CU is free, one per CU; a 128 x 256 tile takes about
-// 0.62 of the time of a 256 x 256 tile (measured), not half: its main loop waits on the same
-// load latency per slab.  A few candidate splits are played through with those two costs and
-// the one that finishes first wins; the result is remembered per shape.
-static double play_schedule(int big_rows, int M, int tiles_n, int batch, int ncu)
+// dispatched in index order to whichever CU is free, one per CU; a 128 x 256 tile takes 0.57 of the time of a 256 x 256 tile
+// (19.6 k of 34.6 k clocks at 12 slabs), protected 0.66 (29.7 k of 45 k): its prologue is the same.  A few candidate splits are
+// played through with those two costs and the one that finishes first wins; the result is remembered per shape.
+static double play_schedule(int big_rows, int M, int tiles_n, int batch, int ncu, double small)
 {
     const int rest = M - big_rows * 256;
     const long nb = (long)big_rows * tiles_n, ns = (long)(rest > 0 ? (rest + 127) / 128 : 0) * tiles_n;
@@ -381,7 +404,7 @@ static double play_schedule(int big_rows, int M, int tiles_n, int batch, int ncu
     double end = 0.0;
     for (int z = 0; z < batch; ++z)
         for (long t = 0; t < nb + ns; ++t) {
-            const double f = cu.top() + (t < ns ? 0.62 : 1.0);     // dispatch order: the half-height tiles first
+            const double f = cu.top() + (t < ns ? small : 1.0);     // dispatch order: the half-height tiles first
             cu.pop();
             cu.push(f);
             if (f > end) end = f;
@@ -389,16 +412,17 @@ static double play_schedule(int big_rows, int M, int tiles_n, int batch, int ncu
     return end;
 }
 
-static int choose_big_rows(int M, int tiles_n, int batch, int ncu)
+static int choose_big_rows(int M, int tiles_n, int batch, int ncu, bool protect)
 {
-    struct Memo { int M, tiles_n, batch, ncu, big_rows; };
+    struct Memo { int M, tiles_n, batch, ncu, protect, big_rows; };
     static Memo memo[16];
     static int memo_n = 0;
     static std::mutex memo_lock;                 // contexts may be driven from different host threads
     std::lock_guard<std::mutex> hold(memo_lock);
     for (int i = 0; i < memo_n; ++i)
-        if (memo[i].M == M && memo[i].tiles_n == tiles_n && memo[i].batch == batch && memo[i].ncu == ncu)
+        if (memo[i].M == M && memo[i].tiles_n == tiles_n && memo[i].batch == batch && memo[i].ncu == ncu && memo[i].protect == protect)
             return memo[i].big_rows;
+    const double small = protect ? 0.66 : 0.57;
     const int rows_all_big = (M + 255) / 256;
     const long per_row = (long)tiles_n * batch;
     const long total_big = rows_all_big * per_row;
@@ -411,12 +435,12 @@ static int choose_big_rows(int M, int tiles_n, int batch, int ncu)
     const long fewer = whole - (ncu + per_row - 1) / per_row;    // one round fewer
     if (fewer > 0) cand[nc++] = (int)fewer;
     int best = cand[0];
-    double best_t = play_schedule(cand[0], M, tiles_n, batch, ncu);
+    double best_t = play_schedule(cand[0], M, tiles_n, batch, ncu, small);
     for (int i = 1; i < nc; ++i) {
-        const double t = play_schedule(cand[i], M, tiles_n, batch, ncu);
+        const double t = play_schedule(cand[i], M, tiles_n, batch, ncu, small);
         if (t < best_t - 1e-9) { best_t = t; best = cand[i]; }
     }
-    Memo m = {M, tiles_n, batch, ncu, best};
+    Memo m = {M, tiles_n, batch, ncu, protect, best};
     memo[memo_n < 16 ? memo_n++ : (M + tiles_n) & 15] = m;
     return best;
 }
@@ -426,7 +450,7 @@ static int choose_big_rows(int M, int tiles_n, int batch, int ncu)
 // are then free of their owned slabs, but their first slabs queue behind this pass's loads: about 1 us lost, against 0.5 us
 // (int8 1 us) for each owned slab.  Measured against tiles that reduce A, us: f16 6304 x 768 x 3072 (16 owned of 48 slabs)
 // 54.4 -> 52.1, 10870 x 896 x 2688 bf16 81.9 -> 75.2, int8 5099 x 896 x 2176 37.1 -> 32.7, 6422 x 1536 x 2688 47.5 -> 42.6; where K is
-// short or shared by many tile columns it lost: f16 6783 x 704 x 832 37.8 -> 38.4, 2788 x 3648 x 2240 (2.3 owned) 87.0 ->
+// short or shared by many tile columns it lost (tiles by four waves): f16 6783 x 704 x 832 37.8 -> 38.4, 2788 x 3648 x 2240 (2.3 owned) 87.0 ->
 // 88.4, int8 10144 x 1408 x 1024 32.2 -> 33.3.  A workgroup reads 64 KB at a time, some 20 GB/s; the pass must end before
 // the tiles do (0.75 us per slab and 128 rows).
 constexpr double BESIDE_FIXED_US = 4.0, BESIDE_BYTES_PER_US = 20e3, TILE_SLAB_US = 0.75;
@@ -439,7 +463,7 @@ static BesideArgs plan_beside(int dt, int M, int K, int batch, int slabs, int ti
     if (per_row_block > idle) return none;
     BesideArgs b;
     b.cw_log2 = w.cw_log2; b.nwin = w.nwin;
-    const int rl = (256 >> w.cw_log2) * 16;                      // rows a workgroup takes at a time
+    const int rl = (64 * FAST_WAVES >> w.cw_log2) * 8;                      // rows a workgroup takes at a time
     b.nrb = (int)(idle / per_row_block);
     b.rpb = (M + b.nrb - 1) / b.nrb;
     b.rpb = (b.rpb + 15) / 16 * 16;
@@ -450,7 +474,7 @@ static BesideArgs plan_beside(int dt, int M, int K, int batch, int slabs, int ti
     return us <= tiles_us ? b : none;
 }
 
-template <int DT, bool PROT>
+template <int DT, bool PROT, bool STO>
 static hipError_t launch_fast_one(GemmArgs &g, int batch, hipStream_t st)
 {
     constexpr int smem_max = 160 * 1024;
@@ -459,7 +483,9 @@ static hipError_t launch_fast_one(GemmArgs &g, int batch, hipStream_t st)
     const int num_cu = device_cu_count(&e);
     if (e != hipSuccess) return e;
     g.tiles_n = (g.N + 255) / 256;
-    const int big_rows = choose_big_rows(g.M, g.tiles_n, batch, num_cu);
+    // (The sums of the stored values need registers that only 128-row tiles leave: in 256-row tiles blocks of accumulators go to
+    // scratch memory.)
+    const int big_rows = STO ? 0 : choose_big_rows(g.M, g.tiles_n, batch, num_cu, PROT);
     g.tiles_m_big = big_rows;
     g.n_big = big_rows * g.tiles_n;
     const int rest = g.M - big_rows * 256;
@@ -475,16 +501,22 @@ static hipError_t launch_fast_one(GemmArgs &g, int batch, hipStream_t st)
         g.beside = plan_beside(DT, g.M, g.K, batch, slabs, g.tiles_n, num_cu - (int)total, TILE_SLAB_US * (g.n_big ? 2 : 1) * slabs);
         grid.x += g.beside.n;
     }
-    size_t smem = BIG_LDS;
-    if (g.beside.n) smem = BIG_LDS > BESIDE_LDS ? BIG_LDS : BESIDE_LDS;
-    else if (PROT) smem += apass_lds_bytes_per_wave(DT, slabs, g.tiles_n);
+    size_t smem;
+    auto kern = gemm_fast_kernel<DT, PROT ? FAST_OWN : FAST_PLAIN, STO>;
+    if constexpr (PROT) {
+        const size_t aux = fast_aux_bytes(DT, slabs, g.tiles_n);
+        smem = fast_lds_bytes<FAST_OWN>() + aux;
+        if (g.beside.n) {
+            kern = gemm_fast_kernel<DT, FAST_BESIDE, STO>;
+            smem = fast_lds_bytes<FAST_BESIDE>();
+        }
+    } else {
+        smem = fast_lds_bytes<FAST_PLAIN>();
+    }
     if (smem > (size_t)smem_max) return hipErrorInvalidValue;
-    auto kern = gemm_fast_kernel<DT, PROT ? FAST_OWN : FAST_PLAIN>;
-    if constexpr (PROT)
-        if (g.beside.n) kern = gemm_fast_kernel<DT, FAST_BESIDE>;
     e = ensure_max_lds(reinterpret_cast<const void *>(kern), smem_max);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, grid, dim3(256), smem, st, g);
+    hipLaunchKernelGGL(kern, grid, dim3(64 * FAST_WAVES), smem, st, g);
     return hipGetLastError();
 }
 
@@ -498,20 +530,25 @@ bool gemm_fast_eligible(int dt, int M, int N, int K, bool transB, long lda, long
            lda * elem_size(dt) < (1L << 23) && ldb * elem_size(dt) < (1L << 23) &&
            // what the pass over A's slabs keeps per tile fits behind the operand buffers (protected or
            // not: the tile shape of a problem does not depend on the mode)
-           BIG_LDS + apass_lds_bytes_per_wave(dt, K / ke, (N + 255) / 256) <= 160 * 1024;
+           fast_lds_bytes<FAST_OWN>() + fast_aux_bytes(dt, K / ke, (N + 255) / 256) <= 160 * 1024;
 }
 
 void gemm_fast_tile(int *tm, int *tn) { *tm = 256; *tn = 256; }
 
+template <int DT> static hipError_t launch_fast_type(bool protect, GemmArgs &g, int batch, hipStream_t st)
+{
+    if (!protect) return launch_fast_one<DT, false, false>(g, batch, st);
+    if constexpr (!Traits<DT>::IS_INT)
+        if (g.cc_sto) return launch_fast_one<DT, true, true>(g, batch, st);
+    return launch_fast_one<DT, true, false>(g, batch, st);
+}
+
 hipError_t launch_gemm_fast(int dt, bool protect, GemmArgs &g, int batch, hipStream_t st)
 {
     switch (dt) {
-    case DT_I8:
-        return protect ? launch_fast_one<DT_I8, true>(g, batch, st) : launch_fast_one<DT_I8, false>(g, batch, st);
-    case DT_BF16:
-        return protect ? launch_fast_one<DT_BF16, true>(g, batch, st) : launch_fast_one<DT_BF16, false>(g, batch, st);
-    case DT_F16:
-        return protect ? launch_fast_one<DT_F16, true>(g, batch, st) : launch_fast_one<DT_F16, false>(g, batch, st);
+    case DT_I8:   return launch_fast_type<DT_I8>(protect, g, batch, st);
+    case DT_BF16: return launch_fast_type<DT_BF16>(protect, g, batch, st);
+    case DT_F16:  return launch_fast_type<DT_F16>(protect, g, batch, st);
     }
     return hipErrorInvalidValue;
 }

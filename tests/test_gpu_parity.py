@@ -1949,6 +1949,77 @@ def test_one_launch_vectors_at_the_end_of_fp32(ctx, dtype, value, M, N, K, trans
         assert np.all(np.abs(got[fin] - want[fin]) <= bound[fin])
 
 
+# The fast kernel's pass over A: its sums along K are products of matrix instructions, formed again where they are not finite
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("value", [np.inf, np.nan])
+@pytest.mark.parametrize("where", ["A", "B"])
+@pytest.mark.parametrize("M,N,K,i,k", [(2050, 2060, 384, 53, 131), (2050, 2060, 384, 2049, 383), (8200, 512, 640, 4111, 0)])
+def test_fast_kernel_keeps_non_finite_values_apart(ctx, dtype, value, where, M, N, K, i, k):
+    """One Inf or NaN in an operand: its own row (column) of C is flagged and no other is, and the operand's sums over its
+    other columns are those of the run without it (A's whole predictions of other rows too)."""
+    assert_fast(dtype, M, N, K)
+    A, B = gen.gen_operands(dtype, M, N, K, 51, 52, trans_b=True, batch=1)
+    run = Run(ctx, dtype, A, B, True)
+    run.gemm()
+    assert run.cnt()[2] == ab.ABFT_CLEAN
+    sums = ab.ABFT_WS_A_SUM if where == "A" else ab.ABFT_WS_B_SUM
+    before, rc = run.ws(sums)[0].copy(), run.ws(ab.ABFT_WS_RC_PRED)[0].copy()
+    if where == "B":
+        i %= N
+    bits = {("bf16", False): 0x7F80, ("bf16", True): 0x7FC0, ("f16", False): 0x7C00, ("f16", True): 0x7E00}
+    (run.dA if where == "A" else run.dB)[0, i, k] = bits[dtype, bool(np.isnan(value))]
+    run.gemm()
+    rf, cf = run.flags()
+    own, other = (rf[0], cf[0]) if where == "A" else (cf[0], rf[0])
+    rest = np.arange(len(own)) != i
+    assert own[i] and not own[rest].any() and other.all()
+    after = run.ws(sums)[0]
+    keep = np.arange(K) != k
+    assert not np.isfinite(after[k])
+    # the same fp32 values, added by atomics in another order: 2^-24 of the sum of magnitudes (below 4 a value) an addition
+    bound = 2.0 ** -24 * np.sqrt(len(own)) * 4 * len(own)
+    assert np.max(np.abs(after[keep] - before[keep])) <= bound
+    if where == "A":
+        assert np.max(np.abs(run.ws(ab.ABFT_WS_RC_PRED)[0][rest] - rc[rest])) <= 1e-5 * K
+    # max|.| takes Inf and passes over NaN
+    top = run.ws(ab.ABFT_WS_MAXABS)[0][0 if where == "A" else 1]
+    assert np.isinf(top) if np.isinf(value) else np.isfinite(top)
+
+
+@pytest.mark.parametrize("dtype,scale", [("bf16", 2.0 ** -100), ("bf16", 2.0 ** 100), ("f16", 2.0 ** -14), ("f16", 1.0), ("f16", 2.0 ** 9)])
+@pytest.mark.parametrize("value", [0.0, np.inf, 3.3995e38])
+def test_fast_kernel_row_predictions_over_the_range_of_b(ctx, dtype, scale, value):
+    """A b from the terms b is split into: B over the operand type's range (fp16: subnormal to near its largest); then with a
+    b (the encoding of another B) that holds an Inf, or a finite value near the end of fp32."""
+    M, N, K = 2050, 2060, 384
+    assert_fast(dtype, M, N, K)
+    rng = np.random.default_rng(57)
+    A, B = gen.gen_operands(dtype, M, N, K, 53, 54, trans_b=True, batch=1)
+    x = (scale * rng.standard_normal((1, N, K))).astype(np.float32)
+    B = x.astype(np.float16).view(np.uint16) if dtype == "f16" else ((x.view(np.uint32) + 0x8000) >> 16).astype(np.uint16)
+    k = 131
+    if np.isinf(value):
+        B[0, 7, k] = 0x7F80 if dtype == "bf16" else 0x7C00
+    elif value and dtype == "bf16":
+        B[0, :, k] = 0
+        B[0, 7, k], B[0, 9, k] = 0x7F7F, 0x7B40                       # 3.3895e38 + 1.0e36
+    run = Run(ctx, dtype, A, B, True)
+    run.tau = 1.0
+    run.gemm()
+    Ad, Bd = orc.decode(A[0], dtype).astype(np.float64), orc.decode(B[0], dtype).astype(np.float64)
+    with np.errstate(invalid="ignore", over="ignore"):
+        want = Ad @ Bd.sum(axis=0)
+        # b is a sum of N, A b one of K, in fp32
+        bound = 2.0 ** -24 * (np.sqrt(N) + np.sqrt(K)) * (np.abs(Ad) @ np.abs(Bd).sum(axis=0))
+    got = run.ws(ab.ABFT_WS_RC_PRED)[0]
+    fin = np.isfinite(want) & (np.abs(want) < 3e38)
+    assert fin.all() or value != 0.0
+    assert np.all(np.abs(got[fin] - want[fin]) <= bound[fin])
+    bad = ~np.isfinite(want)
+    assert not np.isfinite(got[bad]).any()
+    assert np.array_equal(got[bad], want[bad].astype(np.float32), equal_nan=True)
+
+
 # (M, N, K, batch, trans_b): one workgroup per item, where its kernels' blocks, rings and chunks end
 ITEM_EDGES = [
     (300, 128, 96, 64, True),       # the widest item whose waves own rows; two blocks of rows for some waves
