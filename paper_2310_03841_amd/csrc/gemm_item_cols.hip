@@ -24,7 +24,7 @@ struct ColsLds {
     __host__ __device__ ColsLds(const ItemArgs &g, int es, bool sto)
     {
         KP = g.steps * (es == 2 ? 16 : 32);
-        Mr = g.MB * 32; Nr = g.NB * 32; RC = g.rch * 32;
+        Mr = g.MB * 32; Nr = (g.NB + (g.NB < COLS_NW ? 1 : 0)) * 32; RC = g.rch * 32;      // (the sums of a shared block's second half behind the others)
         int o = 0;
         a = o; o += KP;
         b = o; o += KP;
@@ -61,6 +61,11 @@ __global__ __launch_bounds__(COLS_NT, TPW == 1 && !STO ? 4 : 2) void item_cols_k
              *my_a = vec + L.apart + wave * L.KP, *my_rs = vec + L.rspart + wave * L.RC;
     uint8_t *terms = reinterpret_cast<uint8_t *>(vec + L.terms);
     const int ract = g.MB < COLS_NW ? g.MB : COLS_NW;            // waves that have a share of the pass over A
+    // The last block of columns hangs over the edge of C and takes twice as long to store as another: where a wave has no block, it
+    // takes the second half of that block's rows.  (197 columns, seven blocks: the other waves waited 5900 of an item's 30000
+    // clocks for the seventh, 2700 so.  bf16 197 x 197 x 64, 128 items 17.0 -> 15.6 us, 384 items 21.6 -> 21.3, unprotected 13.2 -> 12.6.)
+    const bool shared = TPW == 1 && g.NB < COLS_NW && g.NB * 32 > N;
+    const int nb_first = shared && wave == g.NB ? g.NB - 1 : wave;
     unsigned nr_w = 0, nc_w = 0;
 
     for (int bz = blockIdx.x; bz < g.batch; bz += gridDim.x) {
@@ -150,6 +155,7 @@ __global__ __launch_bounds__(COLS_NT, TPW == 1 && !STO ? 4 : 2) void item_cols_k
             }
             // One block of columns per wave: two blocks of rows at a time, two independent chains of MFMAs and
             // of what follows them.
+            const int half = ((rb1 - rb0 + 1) / 2 + R - 1) / R * R;         // a shared block: rows of its owner
             for (int rb = rb0; rb < rb1; rb += R) {
                 const int lane = item_opaque(tid) & 63, l32 = lane & 31, lh = lane >> 5;
                 const Frag fb(smem, g.pb, lane);
@@ -164,8 +170,8 @@ __global__ __launch_bounds__(COLS_NT, TPW == 1 && !STO ? 4 : 2) void item_cols_k
                 float rs_s[2] = {0.f, 0.f};
                 static_for<0, TPW>([&](auto t_c) {
                     constexpr int t = decltype(t_c)::value;
-                    const int nb = wave + COLS_NW * t;
-                    if (nb < g.NB) {
+                    const int nb = nb_first + COLS_NW * t;
+                    if (nb < g.NB && !(shared && nb == g.NB - 1 && (rb - rb0 >= half) != (wave == g.NB))) {
                         accv_t acc[R];
                         auto piece = [&](auto first_c, int p) __attribute__((always_inline)) {
                             constexpr bool FIRST = decltype(first_c)::value;
@@ -257,7 +263,7 @@ __global__ __launch_bounds__(COLS_NT, TPW == 1 && !STO ? 4 : 2) void item_cols_k
             static_for<0, TPW>([&](auto t_c) {
                 constexpr int t = decltype(t_c)::value;
                 const int nb = wave + COLS_NW * t;
-                if (nb < g.NB) {
+                if (nb < g.NB + (shared ? 1 : 0)) {
                     const acc_t v = fold16<acc_t>(cs[t], lane);
                     if ((lane & 1) == 0) vec[L.ccobs + nb * 32 + fold16_column(lane)] = as_word(v);
                     if (STO) {
@@ -278,10 +284,12 @@ __global__ __launch_bounds__(COLS_NT, TPW == 1 && !STO ? 4 : 2) void item_cols_k
                 bool fl = false;
                 if (lane < 32 && n < N) {
                     const long o = (long)bz * N + n;
-                    const uint32_t obs = vec[L.ccobs + n];
+                    const bool two = shared && nb == g.NB - 1;
+                    uint32_t obs = vec[L.ccobs + n];
+                    if (two) obs = as_word(add_t(from_word<acc_t>(obs), from_word<acc_t>(vec[L.ccobs + n + 32])));
                     g.cc_pred[o] = as_word(d);
                     g.cc_obs[o] = obs;
-                    if (STO) g.cc_sto[o] = vec[L.ccsto + n];
+                    if (STO) g.cc_sto[o] = two ? __float_as_uint(__uint_as_float(vec[L.ccsto + n]) + __uint_as_float(vec[L.ccsto + n + 32])) : vec[L.ccsto + n];
                     fl = mismatch<T::IS_INT>(obs, as_word(d), tol_c);
                     g.col_flag[o] = fl ? 1 : 0;
                 }

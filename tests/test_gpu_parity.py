@@ -2046,6 +2046,37 @@ def test_item_kernels_at_their_edges(dtype, M, N, K, batch, trans_b):
         ab.abft_destroy(ctx)
 
 
+# A last block of columns that hangs over the edge and a wave without a block: two waves share its rows
+@pytest.mark.parametrize("dtype", ["i8", "bf16", "f16"])
+# (K of at least N / 4: a repair ends with a re-sum of the rounded C against tau, and the rounding of a row of N values, about
+# sqrt(N) 2^-9 of one, has to stay below tau, 1e-3 K of the largest)
+@pytest.mark.parametrize("M,N,K", [(1, 130, 64), (33, 161, 64), (65, 193, 96), (100, 223, 64), (290, 195, 104)])
+def test_item_kernel_last_block_of_columns_shared(ctx_items, dtype, M, N, K):
+    _clean_case(ctx_items, dtype, M, N, K, 64, True)
+    A, B = gen.gen_operands(dtype, M, N, K, 63, 64, trans_b=True, batch=64, b_kind="act")
+    run = Run(ctx_items, dtype, A, B, True)
+    run.gemm()
+    C0 = run.C().copy()
+    # flips in the first and the last row of that block: found, repaired
+    for (bi, i, j) in [(0, 0, N - 1), (63, M - 1, N - 1), (7, M // 2, N - 1)]:
+        run.inject(bi, i, j, 30, ab.ABFT_INJECT_ACCUMULATOR)
+        run.gemm(ab.ABFT_DETECT)
+        rf, cf = run.flags()
+        assert rf.sum() == 1 and cf.sum() == 1 and rf[bi, i] and cf[bi, j]
+        run.correct()
+        assert np.array_equal(run.C(), C0) and run.cnt()[2] == ab.ABFT_CLEAN
+    if dtype == "i8":
+        return
+    # the sums of the values as stored, whose two shares meet in the same place
+    run.gemm(ab.ABFT_DETECT | ab.ABFT_STORED_SUMS)
+    run.verify()
+    assert run.cnt()[2] == ab.ABFT_CLEAN
+    stored = orc.decode(run.C(), dtype).astype(np.float64)
+    got = run.ws(ab.ABFT_WS_CC_STO)
+    # fp32 sums of M values in any order
+    assert np.all(np.abs(got - stored.sum(axis=1)) <= 2.0 ** -24 * M * np.abs(stored).sum(axis=1) + 1e-30)
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 @pytest.mark.parametrize("value", [np.inf, np.nan])
 @pytest.mark.parametrize("M,N,K,trans_b", [(70, 60, 100, False), (70, 200, 64, True)])
