@@ -184,14 +184,14 @@ __device__ __forceinline__ void a_pass(const uint8_t *sA, const uint32_t *b_lds,
     }
 }
 
-// ---- The fast kernel's form of the pass: matrix instructions on the fragments the GEMM has in registers.
+// ---- The fast kernel's form of the pass: matrix instructions on the MFMA fragments of the slab.
 // A 16 x 16 MFMA takes lane l of a 32-row fragment for row l & 15 and piece l >> 4 along its own K, so rows r and r + 16 meet
 // in one sum.  Times the identity, positions along K come out in the lanes, to be added up over rows (four registers and two
 // exchanges per slab); times b, split into terms that the operand type holds exactly, the dots of the fragment's 32 rows do, a
 // term to a register.  (The item kernels do the same: gemm_item.h.)  The four waves that share rows of A take a step
 // of the slab each.  Per owned slab of a 256-row tile that is eight MFMAs of 16 clocks (int8 twelve) and some seventy-five
 // vector instructions of one wave in four, where element by element it was two hundred of every wave.  What an owned slab adds to
-// a tile: int8 36928 x 1024 x 4096 (eight to a tile) 3000 -> 2300 clocks, the launch 171.9 -> 161.4 us; f16 6304 x 768 x 3072 1700.
+// a tile: int8 36928 x 1024 x 4096 (eight to a tile) 3000 -> 1300 clocks, the launch 171.9 -> 155.8 us.
 // Products with one are exact, and so are those with b's terms before they are added.  But Inf and NaN reach through
 // products with zeros what they have no part in: sums and dots that are not finite are formed again, element by element, from
 // memory (fast_dot_again, fast_col_again).
@@ -247,59 +247,35 @@ __device__ __forceinline__ void b_scale(uint32_t bmax_bits, int N, float *scale,
     *back = __uint_as_float(ok ? (uint32_t)(127 - 15 + e) << 23 : 0x7FC00000u);
 }
 
-// d[mi] += b x[mi] and c = the sum over mi of x[mi] turned; operands and results in vector registers.  As instructions: the
+// d0 += b x[0], d1 += b x[1] and c = x[0], x[1] turned and added up; operands and results in vector registers.  As instructions: the
 // built-in's results would be given accumulation registers, which the tile fills.  The waits cover what the compiler does not
 // see in here: operands written by vector instructions just ahead, results read right behind.
 template <int DT> struct TurnSums { typename Acc4<DT>::type c[2]; };
 #define ABFT_M16(OP, D, A, B, C) OP " %" D ", %" A ", %" B ", " C "\n\t"
-template <int DT, int MI>
-__device__ __forceinline__ void pass_mfmas(typename Acc4<DT>::type (&d)[MI], TurnSums<DT> &ts, const i32x4 (&x)[MI], const i32x4 &b,
-                                           const i32x4 &id0, const i32x4 &id1)
+template <int DT>
+__device__ __forceinline__ void pass_mfmas(typename Acc4<DT>::type &d0, typename Acc4<DT>::type &d1, TurnSums<DT> &ts, const i32x4 (&x)[2],
+                                           const i32x4 &b, const i32x4 &id0, const i32x4 &id1)
 {
-    // operands: %0 %1 the turned sums, %2 .. the dots, then the fragments, b, id0, id1
     if constexpr (DT == DT_I8) {
-        if constexpr (MI == 4)
-            asm volatile("s_nop 4\n\t"
-                         ABFT_M16("v_mfma_i32_16x16x64_i8", "0", "6", "11", "0") ABFT_M16("v_mfma_i32_16x16x64_i8", "1", "6", "12", "0")
-                         ABFT_M16("v_mfma_i32_16x16x64_i8", "2", "10", "6", "%2")
-                         ABFT_M16("v_mfma_i32_16x16x64_i8", "3", "10", "7", "%3") "s_nop 7\n\t"
-                         ABFT_M16("v_mfma_i32_16x16x64_i8", "0", "7", "11", "%0") ABFT_M16("v_mfma_i32_16x16x64_i8", "1", "7", "12", "%1")
-                         ABFT_M16("v_mfma_i32_16x16x64_i8", "4", "10", "8", "%4") "s_nop 7\n\t"
-                         ABFT_M16("v_mfma_i32_16x16x64_i8", "0", "8", "11", "%0") ABFT_M16("v_mfma_i32_16x16x64_i8", "1", "8", "12", "%1")
-                         ABFT_M16("v_mfma_i32_16x16x64_i8", "5", "10", "9", "%5") "s_nop 7\n\t"
-                         ABFT_M16("v_mfma_i32_16x16x64_i8", "0", "9", "11", "%0") ABFT_M16("v_mfma_i32_16x16x64_i8", "1", "9", "12", "%1")
-                         "s_nop 15\n\ts_nop 7"
-                         : "=&v"(ts.c[0]), "=&v"(ts.c[1]), "+v"(d[0]), "+v"(d[1]), "+v"(d[2]), "+v"(d[3])
-                         : "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]), "v"(b), "v"(id0), "v"(id1));
-        else
-            asm volatile("s_nop 4\n\t"
-                         ABFT_M16("v_mfma_i32_16x16x64_i8", "0", "4", "7", "0") ABFT_M16("v_mfma_i32_16x16x64_i8", "1", "4", "8", "0")
-                         ABFT_M16("v_mfma_i32_16x16x64_i8", "2", "6", "4", "%2") ABFT_M16("v_mfma_i32_16x16x64_i8", "3", "6", "5", "%3") "s_nop 7\n\t"
-                         ABFT_M16("v_mfma_i32_16x16x64_i8", "0", "5", "7", "%0") ABFT_M16("v_mfma_i32_16x16x64_i8", "1", "5", "8", "%1")
-                         "s_nop 15\n\ts_nop 7"
-                         : "=&v"(ts.c[0]), "=&v"(ts.c[1]), "+v"(d[0]), "+v"(d[1])
-                         : "v"(x[0]), "v"(x[1]), "v"(b), "v"(id0), "v"(id1));
+        // c[0]: positions 0..15 of the step, c[1]: 16..31
+        asm volatile("s_nop 4\n\t"
+                     ABFT_M16("v_mfma_i32_16x16x64_i8", "0", "4", "7", "0") ABFT_M16("v_mfma_i32_16x16x64_i8", "1", "4", "8", "0")
+                     ABFT_M16("v_mfma_i32_16x16x64_i8", "2", "6", "4", "%2") ABFT_M16("v_mfma_i32_16x16x64_i8", "3", "6", "5", "%3") "s_nop 7\n\t"
+                     ABFT_M16("v_mfma_i32_16x16x64_i8", "0", "5", "7", "%0") ABFT_M16("v_mfma_i32_16x16x64_i8", "1", "5", "8", "%1")
+                     "s_nop 15\n\ts_nop 3"
+                     : "=&v"(ts.c[0]), "=&v"(ts.c[1]), "+v"(d0), "+v"(d1)
+                     : "v"(x[0]), "v"(x[1]), "v"(b), "v"(id0), "v"(id1));
     } else {
-        // (the two turned sums take every other fragment each; the caller adds them)
+        // c[0] of x[0], c[1] of x[1]; the caller adds them
 #define ABFT_PASS16(OP)                                                                                                             \
-        if constexpr (MI == 4)                                                                                                      \
-            asm volatile("s_nop 4\n\t"                                                                                              \
-                         ABFT_M16(OP, "0", "6", "11", "0") ABFT_M16(OP, "2", "10", "6", "%2")                                       \
-                         ABFT_M16(OP, "1", "7", "11", "0") ABFT_M16(OP, "3", "10", "7", "%3") "s_nop 3\n\t"                         \
-                         ABFT_M16(OP, "0", "8", "11", "%0") ABFT_M16(OP, "4", "10", "8", "%4") "s_nop 3\n\t"                        \
-                         ABFT_M16(OP, "1", "9", "11", "%1") ABFT_M16(OP, "5", "10", "9", "%5")                                      \
-                         "s_nop 15\n\ts_nop 7"                                                                                      \
-                         : "=&v"(ts.c[0]), "=&v"(ts.c[1]), "+v"(d[0]), "+v"(d[1]), "+v"(d[2]), "+v"(d[3])                           \
-                         : "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]), "v"(b), "v"(id0));                                           \
-        else                                                                                                                        \
-            asm volatile("s_nop 4\n\t"                                                                                              \
-                         ABFT_M16(OP, "0", "4", "7", "0") ABFT_M16(OP, "2", "6", "4", "%2")                                         \
-                         ABFT_M16(OP, "1", "5", "7", "0") ABFT_M16(OP, "3", "6", "5", "%3")                                         \
-                         "s_nop 15\n\ts_nop 7"                                                                                      \
-                         : "=&v"(ts.c[0]), "=&v"(ts.c[1]), "+v"(d[0]), "+v"(d[1])                                                   \
-                         : "v"(x[0]), "v"(x[1]), "v"(b), "v"(id0))
-        if constexpr (DT == DT_BF16) { ABFT_PASS16("v_mfma_f32_16x16x32_bf16"); }
-        else { ABFT_PASS16("v_mfma_f32_16x16x32_f16"); }
+        asm volatile("s_nop 4\n\t"                                                                                                  \
+                     ABFT_M16(OP, "0", "4", "7", "0") ABFT_M16(OP, "1", "5", "7", "0")                                              \
+                     ABFT_M16(OP, "2", "6", "4", "%2") ABFT_M16(OP, "3", "6", "5", "%3")                                            \
+                     "s_nop 15\n\ts_nop 3"                                                                                          \
+                     : "=&v"(ts.c[0]), "=&v"(ts.c[1]), "+v"(d0), "+v"(d1)                                                           \
+                     : "v"(x[0]), "v"(x[1]), "v"(b), "v"(id0))
+        if constexpr (DT == DT_BF16) ABFT_PASS16("v_mfma_f32_16x16x32_bf16");
+        else ABFT_PASS16("v_mfma_f32_16x16x32_f16");
 #undef ABFT_PASS16
     }
 }
