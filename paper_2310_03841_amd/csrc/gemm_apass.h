@@ -216,9 +216,13 @@ template <int DT> __device__ __forceinline__ i32x4 turn_operand(int lane, int u)
     return f;
 }
 
-// Term d = 0, 1, 2 of b, as bits of the operand type; what is left of it in v.  int8: signed bytes (|b| < 2^23).  bf16: three times
+// Term d = 0, 1, 2 of b, as bits of the operand type; what is left of it in v.  int8: signed bytes, which hold up to 0x7F7F7F
+// (N below 65536, see gemm_fast_eligible: b is 127 * 65535 = 0x7EFF81 at most, and -128 * 65535 at least).  bf16: three times
 // eight bits, cut off and not rounded (a value near the largest must not become Inf).  fp16: of b times a power of two that
-// brings N max|B| below 2^15: what the last term leaves off is 2^-40 of that.
+// brings N max|B| below 2^15, and each rest times 2^11, so that it does not sink below the type's range: what the last term leaves
+// off is 2^-62 of N max|B|.  (Rests as they are leave off 2^-40 of it: all of the b of a column whose elements are small next to
+// max|B|.)
+constexpr float F16_REST = 2048.f;
 template <int DT> __device__ __forceinline__ uint32_t b_term(typename Traits<DT>::acc_t &v)
 {
     if constexpr (DT == DT_I8) {
@@ -231,7 +235,7 @@ template <int DT> __device__ __forceinline__ uint32_t b_term(typename Traits<DT>
         return hi >> 16;
     } else {
         const uint32_t h = f32_to_f16_bits(v);
-        v -= f16_bits_to_f32(h);
+        v = (v - f16_bits_to_f32(h)) * F16_REST;
         return h;
     }
 }
@@ -290,7 +294,10 @@ template <int DT, int MI> struct FastPass {
     __device__ __forceinline__ acc_t total(int mi) const
     {
         if constexpr (DT == DT_I8) return (int)((uint32_t)dot[mi][0] + ((uint32_t)dot[mi][1] << 8) + ((uint32_t)dot[mi][2] << 16));
-        else return ((float)dot[mi][2] + (float)dot[mi][1]) + (float)dot[mi][0];
+        else {
+            constexpr float REST = DT == DT_F16 ? 1.f / F16_REST : 1.f;
+            return __builtin_fmaf(__builtin_fmaf((float)dot[mi][2], REST, (float)dot[mi][1]), REST, (float)dot[mi][0]);
+        }
     }
 };
 

@@ -1986,6 +1986,49 @@ def test_fast_kernel_keeps_non_finite_values_apart(ctx, dtype, value, where, M, 
     assert np.isinf(top) if np.isinf(value) else np.isfinite(top)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+# 2^low: the unit of b.  bf16: its smallest subnormal, ordinary, the largest whose sums over rows stay finite; fp16: the same
+@pytest.mark.parametrize("low", ["smallest", "ordinary", "largest"])
+@pytest.mark.parametrize("outlier", [False, True])
+@pytest.mark.parametrize("M,N,K", [(2050, 2060, 384), (4200, 1030, 640)])
+def test_fast_kernel_row_predictions_hold_every_bit_of_b(ctx, dtype, low, outlier, M, N, K):
+    """A row of A holds one element, a power of two, so that its prediction is one value of b, exactly; B is made so that every b
+    is a whole number of 24 bits, its sums exact in any order.  outlier: one column of B holds the type's largest value, next
+    to which the others are small."""
+    assert_fast(dtype, M, N, K)
+    rng = np.random.default_rng(59)
+    unit = {"smallest": (-133, -24), "ordinary": (-16, -16), "largest": (100, -8)}[low][dtype == "f16"]
+    m = rng.integers(1, 256, (K, 3)) | [0x80, 0, 1]                  # eight bits each, the highest and the lowest bit of b set
+    n = np.argsort(rng.random((K, N)), axis=1)[:, :3]
+    Bv = np.zeros((N, K))
+    for j, shift in enumerate((16, 8, 0)):
+        Bv[n[:, j], np.arange(K)] = np.ldexp(m[:, j] * rng.choice([-1.0, 1.0], K), unit + shift)
+    if outlier:
+        Bv[:, K // 3] = 0
+        Bv[17, K // 3] = 65504.0 if dtype == "f16" else float(orc.decode(np.array([0x7F7F], np.uint16), "bf16")[0])
+    e = rng.integers(-3, 4, M) if low != "smallest" else rng.integers(0, 7, M)
+    k = (np.arange(M) * 7) % K                                       # (7 is prime to K: every position of K)
+    Av = np.zeros((M, K))
+    Av[np.arange(M), k] = np.ldexp(1.0, e)
+    enc = (lambda v: v.astype(np.float16).view(np.uint16)) if dtype == "f16" else (lambda v: (v.astype(np.float32).view(np.uint32) >> 16).astype(np.uint16))
+    A, B = enc(Av)[None], enc(Bv)[None]
+    assert np.array_equal(orc.decode(A[0], dtype), Av) and np.array_equal(orc.decode(B[0], dtype), Bv)
+    b = Bv.sum(axis=0)
+    want = (Av[np.arange(M), k] * b[k]).astype(np.float32)
+    fin = k != K // 3 if outlier else np.ones(M, bool)
+    assert np.array_equal(b.astype(np.float32), b) and np.isfinite(want[fin]).all()
+    # what two terms hold is not b
+    two = b.astype(np.float32).view(np.uint32) & 0xFFFFFF00
+    assert (two.view(np.float32) != b).mean() > 0.9
+    run = Run(ctx, dtype, A, B, True)
+    run.gemm()
+    assert np.array_equal(run.ws(ab.ABFT_WS_B_SUM)[0], b.astype(np.float32))
+    got = run.ws(ab.ABFT_WS_RC_PRED)[0]
+    bad = np.flatnonzero((got != want) & fin)
+    assert bad.size == 0, (bad.size, bad[:5], got[bad[:5]], want[bad[:5]])
+    assert np.array_equal(run.ws(ab.ABFT_WS_A_SUM)[0], Av.sum(axis=0).astype(np.float32))
+
+
 @pytest.mark.parametrize("dtype,scale", [("bf16", 2.0 ** -100), ("bf16", 2.0 ** 100), ("f16", 2.0 ** -14), ("f16", 1.0), ("f16", 2.0 ** 9)])
 @pytest.mark.parametrize("value", [0.0, np.inf, 3.3995e38])
 def test_fast_kernel_row_predictions_over_the_range_of_b(ctx, dtype, scale, value):
