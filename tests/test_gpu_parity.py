@@ -2032,8 +2032,8 @@ def test_fast_kernel_row_predictions_hold_every_bit_of_b(ctx, dtype, low, outlie
 @pytest.mark.parametrize("dtype,scale", [("bf16", 2.0 ** -100), ("bf16", 2.0 ** 100), ("f16", 2.0 ** -14), ("f16", 1.0), ("f16", 2.0 ** 9)])
 @pytest.mark.parametrize("value", [0.0, np.inf, 3.3995e38])
 def test_fast_kernel_row_predictions_over_the_range_of_b(ctx, dtype, scale, value):
-    """A b from the terms b is split into: B over the operand type's range (fp16: subnormal to near its largest); then with a
-    b (the encoding of another B) that holds an Inf, or a finite value near the end of fp32."""
+    """A b over the operand type's range of B (fp16: subnormal to near its largest), to the rounding of fp32 sums; then with a
+    column of B that holds an Inf, or whose sum is the largest finite one: near the end of fp32, fp16 65504 N."""
     M, N, K = 2050, 2060, 384
     assert_fast(dtype, M, N, K)
     rng = np.random.default_rng(57)
@@ -2046,6 +2046,8 @@ def test_fast_kernel_row_predictions_over_the_range_of_b(ctx, dtype, scale, valu
     elif value and dtype == "bf16":
         B[0, :, k] = 0
         B[0, 7, k], B[0, 9, k] = 0x7F7F, 0x7B40                       # 3.3895e38 + 1.0e36
+    elif value:
+        B[0, :, k] = 0x7BFF
     run = Run(ctx, dtype, A, B, True)
     run.tau = 1.0
     run.gemm()
