@@ -219,9 +219,9 @@ template <int DT> __device__ __forceinline__ i32x4 turn_operand(int lane, int u)
 // Term d = 0, 1, 2 of b, as bits of the operand type; what is left of it in v.  int8: signed bytes, which hold up to 0x7F7F7F
 // (N below 65536, see gemm_fast_eligible: b is 127 * 65535 = 0x7EFF81 at most, and -128 * 65535 at least).  bf16: three times
 // eight bits, cut off and not rounded (a value near the largest must not become Inf).  fp16: of b times a power of two that
-// brings N max|B| below 2^15, and each rest times 2^11, so that it does not sink below the type's range: what the last term leaves
-// off is 2^-62 of N max|B|.  (Rests as they are leave off 2^-40 of it: all of the b of a column whose elements are small next to
-// max|B|.)
+// brings N values of the type below 2^15, and each rest times 2^11, so that it does not sink below the type's range: the last
+// bit of the last term is 2^-45 N (N as a power of two), below that of any sum of fp16 values.  (Rests as they are would leave off
+// 2^-40 of the largest b: all of the b of a column whose elements are small.)
 constexpr float F16_REST = 2048.f;
 template <int DT> __device__ __forceinline__ uint32_t b_term(typename Traits<DT>::acc_t &v)
 {
@@ -239,16 +239,12 @@ template <int DT> __device__ __forceinline__ uint32_t b_term(typename Traits<DT>
         return h;
     }
 }
-// fp16: the exponent of that power of two; N max|B| past 2^100 (or none): NaN for its inverse, and every dot is formed again
-__device__ __forceinline__ void b_scale(uint32_t bmax_bits, int N, float *scale, float *back)
+// fp16: that power of two, and what undoes it
+__device__ __forceinline__ void b_scale(int N, float *scale, float *back)
 {
-    // (in scalar registers)
-    const uint32_t bits = __builtin_amdgcn_readfirstlane(__float_as_uint(__uint_as_float(bmax_bits) * (float)N));
-    const int ex = (int)(bits >> 23) - 127 + 1;                            // the bound is below 2^ex (infinity, NaN: 129)
-    const bool ok = ex <= 100;
-    const int e = ok ? (ex < -80 ? -80 : ex) : 0;
+    const int e = 16 + 32 - __builtin_clz((unsigned)N - 1);     // N values below 2^16: b below 2^e
     *scale = __uint_as_float((uint32_t)(127 + 15 - e) << 23);
-    *back = __uint_as_float(ok ? (uint32_t)(127 - 15 + e) << 23 : 0x7FC00000u);
+    *back = __uint_as_float((uint32_t)(127 - 15 + e) << 23);
 }
 
 // d0 += b x[0], d1 += b x[1] and c = x[0], x[1] turned and added up; operands and results in vector registers.  As instructions: the

@@ -28,7 +28,7 @@ struct GemmArgs {
     int a_given;                                  // a = e^T A and max|A| come from the caller: the pass over A's
                                                   // slabs forms the row dots only, nothing is added to a_sum / a_max
     const uint32_t *bias;                         // layer bias [N] (float / int32 words) or null
-    const uint32_t *b_sum, *b_max;                // B e and max|B|, complete before the launch [batch][K], [batch]
+    const uint32_t *b_sum;                        // B e, complete before the launch [batch][K]
     uint32_t *counts;                             // fast kernel, protected: cleared for the check kernel
     BesideArgs beside;
 };

@@ -213,7 +213,7 @@ __device__ __forceinline__ void fast_tile(const GemmArgs &g, uint8_t *smem, int 
         };
         // b of the next slab to reduce in terms of the operand type, a slab ahead of it
         float scale = 1.f;
-        if constexpr (OWN && DT == DT_F16) b_scale(g.b_max[bz], N, &scale, &ep.back);
+        if constexpr (OWN && DT == DT_F16) b_scale(N, &scale, &ep.back);
         auto put_terms = [&]() __attribute__((always_inline)) {
             if (wave < KE / 64) {
                 typename T::acc_t v = from_word<typename T::acc_t>(words[(own_at & 1) * KE + 64 * wave + lane]);

@@ -852,7 +852,7 @@ hipError_t launch_gemm(int dt, bool protect, bool stored_sums, bool encode_b, co
     g.sA = s.sA; g.sB = s.sB; g.sC = s.sC;
     g.inj_b = arm.batch; g.inj_row = arm.row; g.inj_col = arm.col; g.inj_bit = arm.bit;
     g.cc_obs = w.cc_obs; g.rc_obs = w.rc_obs; g.rc_pred = w.rc_pred; g.cc_acc = w.cc_acc; g.rc_acc = w.rc_acc;
-    g.a_sum = w.a_sum; g.a_max = w.a_max; g.b_sum = w.b_sum; g.b_max = w.b_max;
+    g.a_sum = w.a_sum; g.a_max = w.a_max; g.b_sum = w.b_sum;
     g.bias = w.bias;
     g.cc_sto = (protect && stored_sums && dt != DT_I8) ? w.cc_sto : nullptr;
     g.rc_sto = g.cc_sto ? w.rc_sto : nullptr;
