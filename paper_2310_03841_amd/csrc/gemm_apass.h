@@ -193,8 +193,8 @@ __device__ __forceinline__ void a_pass(const uint8_t *sA, const uint32_t *b_lds,
 // vector instructions of one wave in four, where element by element it was two hundred of every wave.  What an owned slab adds to
 // a tile: int8 36928 x 1024 x 4096 (eight to a tile) 3000 -> 1300 clocks, the launch 171.9 -> 155.8 us.
 // Products with one are exact, and so are those with b's terms before they are added.  But Inf and NaN reach through
-// products with zeros what they have no part in: sums and dots that are not finite are formed again, element by element, from
-// memory (fast_dot_again, fast_col_again).
+// products with zeros what they have no part in, and a NaN hides the largest |element| of a lane: sums, dots and maxima that are not
+// finite are formed again, element by element, from memory (dots_again, columns_again, amax_again).
 //
 // LDS: the column sums of every owned slab; b in three terms, of two slabs in turn; 128 bytes of zeros; words of b, of two slabs in turn.
 __host__ __device__ inline size_t fast_aux_bytes(int dt, int nslab, int tiles_n)

@@ -91,27 +91,109 @@ template <int DT, int MI> struct EpiProt {
     float back;               // fp16: what undoes the scale of b's terms
 };
 
-// A dot of row `row` of A with b over the owned slabs, and a column sum of A over rows row0 .. + rows, formed again from memory:
-// where the sums along K by matrix instructions are not finite.  amax: of the row's elements, NaN left out.
+// Sums along K by matrix instructions that are not finite, formed again from memory.  A wave does it together, 16 bytes to a lane and
+// several loads on their way: with an Inf or NaN in an operand these are some of a tile's sums (its own row or column, and what
+// it reached through products with zeros) or, with one in B, the dots of all of a tile's rows.  A thread to a sum, a trip to memory for
+// every element, took bf16 4096 x 4096 x 4096 with an Inf in A from 133 to 196 us, with a NaN to 171, 8200 x 512 x 640 with an
+// Inf in B from 25 to 32; so 140, 140 and 28 (the element-wise pass over A in the tiles by four waves: 143, 143 and 28).
+
+// The dots of rows row0 + r, r < 32, with b over the owned slabs, where bit r of `which` is set: to lane r, v of the others.
+// Eight rows at a time, a chunk of the slab's eight to a lane.
 template <int DT, int MI>
-__device__ __forceinline__ float fast_dot_again(const GemmArgs &g, const EpiProt<DT, MI> &ep, int bz, int row, float *amax)
+__device__ __forceinline__ float dots_again(const GemmArgs &g, const EpiProt<DT, MI> &ep, int bz, int row0, uint32_t which, float v)
 {
-    constexpr int KE = SLAB_BYTES / Traits<DT>::ES;
-    float v = 0.f;
-    for (int j = 0; j < ep.owned; ++j)
-        for (int e = 0; e < KE; ++e) {
-            const int k = (ep.slab0 + j * ep.slab_step) * KE + e;
-            const float x = (float)Traits<DT>::load_c(g.A, (long)bz * g.sA + (long)row * g.lda + k);
-            v = __builtin_fmaf(x, __uint_as_float(g.b_sum[(long)bz * g.K + k]), v);
-            *amax = fmaxf(*amax, fabsf(x));
+    constexpr int KE = SLAB_BYTES / 2, UN = 4;
+    const int lane = tile_thread_index() & 63;
+#pragma unroll 1
+    for (int r8 = 0; r8 < 32; r8 += 8) {
+        if (!(which >> r8 & 0xFFu)) continue;
+        const int row = row0 + r8 + (lane >> 3), at = (lane & 7) * 8;
+        const uint8_t *src = g.A + ((long)bz * g.sA + (long)(row < g.M ? row : g.M - 1) * g.lda + at) * 2;
+        const uint32_t *bsrc = g.b_sum + (long)bz * g.K + at;
+        float dot = 0.f;
+#pragma unroll 1
+        for (int j0 = 0; j0 < ep.owned; j0 += UN) {
+            i32x4 x[UN], b[UN][2];
+#pragma unroll
+            for (int u = 0; u < UN; ++u) {
+                const int j = j0 + u < ep.owned ? j0 + u : ep.owned - 1, k = (ep.slab0 + j * ep.slab_step) * KE;
+                x[u] = *reinterpret_cast<const i32x4 *>(src + 2 * k);
+                b[u][0] = *reinterpret_cast<const i32x4 *>(bsrc + k);
+                b[u][1] = *reinterpret_cast<const i32x4 *>(bsrc + k + 4);
+            }
+#pragma unroll
+            for (int u = 0; u < UN; ++u)
+                if (j0 + u < ep.owned) {
+#pragma unroll
+                    for (int e = 0; e < 8; ++e)
+                        dot = __builtin_fmaf((float)Traits<DT>::elem(x[u], e), __uint_as_float((uint32_t)b[u][e >> 2][e & 3]), dot);
+                }
         }
+        dot = __shfl(row8_sum(dot), (lane & 7) * 8);
+        if ((lane >> 3) == (r8 >> 3) && (which >> lane & 1u)) v = dot;
+    }
     return v;
 }
-template <int DT> __device__ __forceinline__ float fast_col_again(const GemmArgs &g, int bz, int row0, int rows, int k)
+
+// The sums of columns k0 + l of A, l < 64, over rows row0 .. + rows (at most 256), where bit l of `which` is set: to lane l, v of the
+// others.  A row's chunk to a lane, all of a chunk's rows at a time.
+template <int DT> __device__ __forceinline__ float columns_again(const GemmArgs &g, int bz, int row0, int rows, int k0, uint64_t which, float v)
 {
-    float v = 0.f;
-    for (int r = row0; r < row0 + rows; ++r) v += (float)Traits<DT>::load_c(g.A, (long)bz * g.sA + (long)r * g.lda + k);
+    constexpr int UN = 4;
+    const int lane = tile_thread_index() & 63;
+#pragma unroll 1
+    for (int c = 0; c < 8; ++c) {
+        if (!(which >> (8 * c) & 0xFFu)) continue;
+        const uint8_t *src = g.A + ((long)bz * g.sA + (long)row0 * g.lda + k0 + 8 * c) * 2;
+        i32x4 x[UN];
+#pragma unroll
+        for (int u = 0; u < UN; ++u) {
+            const int r = lane + 64 * u;
+            x[u] = *reinterpret_cast<const i32x4 *>(src + (long)(r < rows ? r : rows - 1) * g.lda * 2);
+        }
+#pragma unroll
+        for (int u = 0; u < UN; ++u)
+            if (lane + 64 * u >= rows) x[u] = i32x4{0, 0, 0, 0};
+        float mine = 0.f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            float t = 0.f;
+#pragma unroll
+            for (int u = 0; u < UN; ++u) t += (float)Traits<DT>::elem(x[u], e);
+            t = wave_sum(t);
+            if ((lane & 7) == e) mine = t;
+        }
+        if ((lane >> 3) == c && (which >> lane & 1u)) v = mine;
+    }
     return v;
+}
+
+// The largest |element| (bits) of those a lane saw in its pass over the owned slabs, where a NaN hides it: NaN left out.
+template <int DT, int MI>
+__device__ __forceinline__ uint32_t amax_again(const GemmArgs &g, const EpiProt<DT, MI> &ep, int bz, int m0, int wm, int wn)
+{
+    constexpr uint32_t INF_BITS = DT == DT_BF16 ? 0x7F80u : 0x7C00u;
+    const int lane = tile_thread_index() & 63, row0 = m0 + wm * MI * 32 + (lane & 31);
+    const uint8_t *src = g.A + (long)bz * g.sA * 2 + wn * 32 + (lane >> 5) * 16;
+    uint32_t top = 0u;
+#pragma unroll 1
+    for (int j = 0; j < ep.owned; ++j) {
+        i32x4 x[MI];
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi) {
+            const int r = row0 + mi * 32;                       // (rows past the end: the last one's elements, as good as its own)
+            x[mi] = *reinterpret_cast<const i32x4 *>(src + (long)(r < g.M ? r : g.M - 1) * g.lda * 2 + (long)(ep.slab0 + j * ep.slab_step) * SLAB_BYTES);
+        }
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const uint32_t lo = (uint32_t)x[mi][e] & 0x7FFFu, hi = (uint32_t)x[mi][e] >> 16 & 0x7FFFu;
+                if (lo <= INF_BITS && lo > top) top = lo;
+                if (hi <= INF_BITS && hi > top) top = hi;
+            }
+    }
+    return top;
 }
 
 template <int DT, int BM, bool PROT, bool STO, bool BIAS>
@@ -141,6 +223,7 @@ __device__ __forceinline__ void gemm_epilogue_impl(const GemmArgs &g,
     acc_t *cs_part = rs_part + 4 * BM;                                     // [2][BN] by wave row: a place to a thread
     acc_t *rp_part = cs_part + 2 * BN;                                     // [4][BM] row dots of the A pass, by wave column
     uint32_t *amax_w = reinterpret_cast<uint32_t *>(rp_part + 4 * BM);     // largest |element| the pass saw (bits), by wave
+    constexpr uint32_t DOTS_BAD = 1u << 31;                                // beside it: a dot of this wave's is not finite
     uint8_t *Cb = g.C + (long)bz * g.sC * OS;
     // layer bias of this tile's columns, staged once (zero beyond N); added to every accumulator
     // value on its way out, before the sums and before rounding
@@ -153,16 +236,26 @@ __device__ __forceinline__ void gemm_epilogue_impl(const GemmArgs &g,
     if (PROT && ep.owned > 0) {
         // what the pass over A's slabs left in registers (nothing in a tile that reduced no slab: where K has fewer slabs than the
         // tile row has tiles, that is most tiles)
+        bool dots_bad = false;
 #pragma unroll
         for (int mi = 0; mi < MI; ++mi) {
             acc_t v = ep.pass.total(mi);
             if constexpr (DT == DT_F16) v *= ep.back;
             if (lane < 32) rp_part[wn * BM + wm * TM + mi * 32 + lane] = v;
+            // (finite, and so is the sum of four)
+            if constexpr (!T::IS_INT) dots_bad |= lane < 32 && !(fabsf(v) < 0x1p125f);
         }
         if constexpr (!T::IS_INT) {
-            const uint32_t m = ep.pass.amax, hi = m >> 16, lo = m & 0xFFFFu;
-            const uint32_t w = wave_max_u32(hi > lo ? hi : lo);
-            if (lane == 0) amax_w[wave] = w;
+            constexpr uint32_t INF_BITS = DT == DT_BF16 ? 0x7F80u : 0x7C00u;
+            const uint32_t hi = ep.pass.amax >> 16, lo = ep.pass.amax & 0xFFFFu;
+            uint32_t w = hi > lo ? hi : lo;
+            if (__any(w > INF_BITS)) {
+                const uint32_t again = amax_again<DT>(g, ep, bz, m0, wm, wn);
+                if (w > INF_BITS) w = again;
+            }
+            w = wave_max_u32(w);
+            dots_bad = __any(dots_bad);
+            if (lane == 0) amax_w[wave] = w | (dots_bad ? DOTS_BAD : 0u);
         }
     }
     const bool inj_here = g.inj_b == bz && g.inj_row >= m0 && g.inj_row < m0 + BM &&
@@ -427,14 +520,12 @@ __device__ __forceinline__ void gemm_epilogue_impl(const GemmArgs &g,
         // Barrier over LDS traffic only: the partial sums meet in LDS, and a full barrier would
         // also wait until every store of C issued above has been acknowledged.
         asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-        constexpr uint32_t INF_BITS = DT == DT_BF16 ? 0x7F80u : 0x7C00u;
         uint32_t amax = 0u;
         if (!T::IS_INT && ep.owned > 0) {
 #pragma unroll
             for (int w = 0; w < FAST_WAVES; ++w) amax = amax_w[w] > amax ? amax_w[w] : amax;
         }
-        const bool nan_seen = amax > INF_BITS;                  // a NaN hides the largest of the others
-        float amax_again = 0.f;
+        const bool dots_bad = __builtin_amdgcn_readfirstlane(amax) >= DOTS_BAD;
         for (int t = tid; t < BM + BN; t += THREADS) {
             if (t < BM) {
                 const int gr = m0 + t;
@@ -442,13 +533,8 @@ __device__ __forceinline__ void gemm_epilogue_impl(const GemmArgs &g,
                     if constexpr (STO)
                         unsafeAtomicAdd(reinterpret_cast<float *>(g.rc_sto) + (long)bz * M + gr, (rs_sto[t] + rs_sto[BM + t]) + (rs_sto[2 * BM + t] + rs_sto[3 * BM + t]));
                     atomic_add_word(g.rc_obs + (long)bz * M + gr, add_t(add_t(rs_part[t], rs_part[BM + t]), add_t(rs_part[2 * BM + t], rs_part[3 * BM + t])));
-                    if (ep.owned > 0) {
-                        acc_t v = add_t(add_t(rp_part[t], rp_part[BM + t]), add_t(rp_part[2 * BM + t], rp_part[3 * BM + t]));
-                        if constexpr (!T::IS_INT) {
-                            if (nan_seen || !(fabsf(v) < __builtin_inff())) v = fast_dot_again<DT>(g, ep, bz, gr, &amax_again);
-                        }
-                        atomic_add_word(g.rc_pred + (long)bz * M + gr, v);
-                    }
+                    if (ep.owned > 0 && !dots_bad)
+                        atomic_add_word(g.rc_pred + (long)bz * M + gr, add_t(add_t(rp_part[t], rp_part[BM + t]), add_t(rp_part[2 * BM + t], rp_part[3 * BM + t])));
                 }
             } else {
                 const int gc = n0 + (t - BM);
@@ -468,21 +554,35 @@ __device__ __forceinline__ void gemm_epilogue_impl(const GemmArgs &g,
                 if (m > 0.f) atomicMax(g.c_max + bz, __float_as_uint(m));
             }
         }
+        if (dots_bad) {
+            // BM / 8 rows to a wave
+            constexpr int RW = BM / FAST_WAVES;
+            const int ln = tile_thread_index() & 63, t = wave * RW + (ln & (RW - 1));
+            float v = (float)rp_part[t] + (float)rp_part[BM + t] + ((float)rp_part[2 * BM + t] + (float)rp_part[3 * BM + t]);
+            const bool mine = ln < RW && m0 + t < M;
+            const uint32_t which = (uint32_t)__ballot(mine && !(fabsf(v) < __builtin_inff()));
+            if constexpr (!T::IS_INT) v = dots_again<DT>(g, ep, bz, m0 + wave * RW, which, v);
+            if (mine) atomic_add_word(g.rc_pred + (long)bz * M + m0 + t, v);
+        }
         // column sums of A over this tile's rows, for the slabs this workgroup reduced
         for (int t = tid; t < ep.owned * KE && !g.a_given; t += THREADS) {
             const int k = (ep.slab0 + (t / KE) * ep.slab_step) * KE + (t % KE);
             acc_t v = from_word<acc_t>(ep.col_lds[t]);
             if constexpr (!T::IS_INT) {
-                if (!(fabsf(v) < __builtin_inff())) v = fast_col_again<DT>(g, bz, m0, M - m0 < BM ? M - m0 : BM, k);
+                // (a wave's 64 columns are one slab's)
+                const uint64_t which = __ballot(!(fabsf(v) < __builtin_inff()));
+                if (which) v = columns_again<DT>(g, bz, m0, M - m0 < BM ? M - m0 : BM, k - (t % KE), which, v);
             }
             atomic_add_word(g.a_sum + (long)bz * g.K + k, v);
         }
-        if (!T::IS_INT && !g.a_given && ep.owned > 0) {
-            if (nan_seen) {
-                if (amax_again > 0.f) atomicMax(g.a_max + bz, __float_as_uint(amax_again));
-            } else if (tid == 0 && amax > 0u) {
-                atomicMax(g.a_max + bz, __float_as_uint(DT == DT_BF16 ? bf16_bits_to_f32(amax) : f16_bits_to_f32(amax)));
+        if (!T::IS_INT && !g.a_given && tid == 0) {
+            uint32_t top = 0u;
+            if (dots_bad) {
+                for (int w = 0; w < FAST_WAVES; ++w) top = (amax_w[w] & ~DOTS_BAD) > top ? amax_w[w] & ~DOTS_BAD : top;
+            } else {
+                top = amax;
             }
+            if (top > 0u) atomicMax(g.a_max + bz, __float_as_uint(DT == DT_BF16 ? bf16_bits_to_f32(top) : f16_bits_to_f32(top)));
         }
     }
 }

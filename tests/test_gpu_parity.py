@@ -1987,6 +1987,40 @@ def test_fast_kernel_keeps_non_finite_values_apart(ctx, dtype, value, where, M, 
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("value", [np.inf, np.nan])
+# three tile columns with 7 and 6 of 19 slabs (the last tile row has 8 rows); twelve slabs of which a tile owns one or two
+@pytest.mark.parametrize("M,N,K", [(8200, 520, 1216), (2050, 2060, 768)])
+def test_fast_kernel_sums_formed_again(ctx, dtype, value, M, N, K):
+    """Infs or NaNs at the edges of tiles, waves, blocks of rows, slabs and chunks of A, then in B too (every dot of the tiles that
+    own its slab): sums, dots and max|A| against 64 bits."""
+    assert_fast(dtype, M, N, K)
+    A, B = gen.gen_operands(dtype, M, N, K, 61, 62, trans_b=True, batch=1)
+    rows = [0, 7, 8, 31, 32, 127, 128, 255, 256, 511, M - 9, M - 8, M - 1]
+    cols = [0, 7, 8, 63, 64, 65, K // 2, K - 64, K - 9, K - 1]
+    bits = {("bf16", False): 0x7F80, ("bf16", True): 0x7FC0, ("f16", False): 0x7C00, ("f16", True): 0x7E00}[dtype, bool(np.isnan(value))]
+    for n, i in enumerate(rows):
+        A[0, i, cols[n % len(cols)]] = bits
+    A[0, 40, :K // 2] = bits
+    A[0, 8, 70] = 0x4640 if dtype == "bf16" else 0x7A00              # the largest element (12288, 49152), of a lane that sees NaN of row 40
+    for in_b in (False, True):
+        if in_b:
+            B[0, 11, 70] = bits
+        run = Run(ctx, dtype, A, B, True)
+        run.tau = 1.0
+        run.gemm()
+        Ad, Bd = orc.decode(A[0], dtype).astype(np.float64), orc.decode(B[0], dtype).astype(np.float64)
+        with np.errstate(invalid="ignore"):
+            for got, want, mags in ((run.ws(ab.ABFT_WS_RC_PRED)[0], Ad @ Bd.sum(axis=0), np.abs(Ad) @ np.abs(Bd).sum(axis=0)),
+                                    (run.ws(ab.ABFT_WS_A_SUM)[0], Ad.sum(axis=0), np.abs(Ad).sum(axis=0))):
+                fin = np.isfinite(want)
+                assert fin.any() or in_b
+                # fp32 sums of at most M, N and K values in any order
+                assert np.all(np.abs(got[fin] - want[fin]) <= 2.0 ** -24 * (np.sqrt(N) + np.sqrt(K) + np.sqrt(M)) * mags[fin])
+                assert np.array_equal(got[~fin], want[~fin].astype(np.float32), equal_nan=True)
+        assert run.ws(ab.ABFT_WS_MAXABS)[0][0] == (np.inf if np.isinf(value) else np.nanmax(np.abs(Ad)))
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
 # 2^low: the unit of b.  bf16: its smallest subnormal, ordinary, the largest whose sums over rows stay finite; fp16: the same
 @pytest.mark.parametrize("low", ["smallest", "ordinary", "largest"])
 @pytest.mark.parametrize("outlier", [False, True])
