@@ -33,6 +33,9 @@
 
 namespace abft {
 
+// Sums of the values as stored beside those of the accumulators: none; in a kernel of 128-row tiles only; of both tile heights.
+enum { STO_NO, STO_128, STO_256 };
+
 // bytes of wave-private LDS the epilogue needs for a wave tile that is TN columns wide
 __host__ __device__ constexpr int epi_wave_bytes(int TN) { return 32 * (TN * 4 + 16); }
 __host__ __device__ constexpr int epi_total_bytes(int BM, int BN)
@@ -196,7 +199,19 @@ __device__ __forceinline__ uint32_t amax_again(const GemmArgs &g, const EpiProt<
     return top;
 }
 
-template <int DT, int BM, bool PROT, bool STO, bool BIAS>
+// c += x times `elem`, r += x times `rows`, in vector registers and with waits as in pass_mfmas: the built-in's results would be
+// given accumulation registers, and a block of a 256-row tile's, which fills them, would go to scratch memory instead, in the main loop too.
+template <int DT>
+__device__ __forceinline__ void stored_mfmas(typename Acc4<DT>::type &c, typename Acc4<DT>::type &r, const i32x4 &x, const i32x4 &elem, const i32x4 &rows)
+{
+#define ABFT_STORED16(OP) \
+    asm volatile("s_nop 4\n\t" OP " %0, %2, %3, %0\n\t" OP " %1, %2, %4, %1\n\ts_nop 15\n\ts_nop 3" : "+v"(c), "+v"(r) : "v"(x), "v"(elem), "v"(rows))
+    if constexpr (DT == DT_BF16) ABFT_STORED16("v_mfma_f32_16x16x32_bf16");
+    else ABFT_STORED16("v_mfma_f32_16x16x32_f16");
+#undef ABFT_STORED16
+}
+
+template <int DT, int BM, bool PROT, int STO, bool BIAS>
 __device__ __forceinline__ void gemm_epilogue_impl(const GemmArgs &g,
                                               typename Traits<DT>::accv_t (&acc)[BM / 64][2],
                                               uint8_t *smem, int m0, int n0, int bz, const EpiProt<DT, BM / 64> &ep)
@@ -289,6 +304,9 @@ __device__ __forceinline__ void gemm_epilogue_impl(const GemmArgs &g,
     // the rows' sums: two MFMAs for what took some nine vector instructions per value.  Products with one are exact and the
     // values themselves are the stored ones.  Inf and NaN would reach their neighbours through the
     // zeros: a group that holds one is summed element by element.
+    // FULL: a kernel of 256-row tiles, which has no register left: the pieces are read from LDS once more and the products stay out
+    // of the accumulation registers, 1.5 to 2.5 % of a launch where all tiles have 128 rows (bf16 2048 x 2048 x 2048 45.1 -> 46.5 us).
+    constexpr bool FULL = STO == STO_256;
     auto stored_sums = [&](int mi, const i32x4 *rowv) __attribute__((always_inline)) {
         if constexpr (STO) {
             typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
@@ -304,11 +322,16 @@ __device__ __forceinline__ void gemm_epilogue_impl(const GemmArgs &g,
             auto sums = dcol, drow = acc4_zero<DT>();
 #pragma unroll
             for (int it = 0; it < 4; ++it) {
+                const i32x4 x = FULL ? *reinterpret_cast<const i32x4 *>(wbuf + (8 * it + (ln >> 3)) * CROW + (ln & 7) * 16) : rowv[it];
                 const int w = j == 4 * it + k4 ? (int)(ONE | (ONE << 16)) : 0;
-                sums = mfma16<DT>(rowv[it], elem, sums);
-                drow = mfma16<DT>(rowv[it], i32x4{w, w, w, w}, drow);
+                if constexpr (FULL) {
+                    stored_mfmas<DT>(sums, drow, x, elem, i32x4{w, w, w, w});
+                } else {
+                    sums = mfma16<DT>(x, elem, sums);
+                    drow = mfma16<DT>(x, i32x4{w, w, w, w}, drow);
+                }
 #pragma unroll
-                for (int e = 0; e < 4; ++e) mx = __builtin_elementwise_max(mx, __builtin_bit_cast(u16x2, rowv[it][e] & 0x7FFF7FFF));
+                for (int e = 0; e < 4; ++e) mx = __builtin_elementwise_max(mx, __builtin_bit_cast(u16x2, x[e] & 0x7FFF7FFF));
             }
             // lane l: column j = 4 it + row / 2 of rows 4 (l >> 4) .. + 4 of the result: chunks of parity l >> 5
             const float row = add_xor16(((float)drow[0] + (float)drow[1]) + ((float)drow[2] + (float)drow[3]));
@@ -589,7 +612,7 @@ __device__ __forceinline__ void gemm_epilogue_impl(const GemmArgs &g,
 
 // With and without a layer bias: two copies of the epilogue behind one uniform branch (a test per
 // group of four values inside one copy costs a branch per group).
-template <int DT, int BM, bool PROT, bool STO>
+template <int DT, int BM, bool PROT, int STO>
 __device__ __forceinline__ void gemm_epilogue(const GemmArgs &g,
                                               typename Traits<DT>::accv_t (&acc)[BM / 64][2],
                                               uint8_t *smem, int m0, int n0, int bz, const EpiProt<DT, BM / 64> &ep)

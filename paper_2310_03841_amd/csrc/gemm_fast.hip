@@ -72,7 +72,7 @@ template <int MODE> constexpr int fast_lds_bytes()
 
 // One BM x 256 tile with origin (m0, n0) of batch item bz.
 // What the pass over A keeps lies behind the operand buffers.
-template <int DT, int BM, int MODE, bool STO>
+template <int DT, int BM, int MODE, int STO>
 __device__ __forceinline__ void fast_tile(const GemmArgs &g, uint8_t *smem, int m0, int n0, int bz, int tn)
 {
     using T = Traits<DT>;
@@ -397,7 +397,7 @@ __device__ __forceinline__ void fast_tile(const GemmArgs &g, uint8_t *smem, int 
 // big_rows rows, 128 x 256 tiles the rest; how many of each is chosen by playing the dispatch
 // through (choose_big_rows).  (600 big tiles on 256 CUs would be three rounds for 2.34 rounds
 // of work.)
-template <int DT, int MODE, bool STO>
+template <int DT, int MODE, int STO>
 __global__ __launch_bounds__(64 * FAST_WAVES) void gemm_fast_kernel(GemmArgs g)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
@@ -420,9 +420,9 @@ __global__ __launch_bounds__(64 * FAST_WAVES) void gemm_fast_kernel(GemmArgs g)
     for (int t = blockIdx.x; t < total; t += n_tile) {
         const int bz = t / per_item, bid = t - bz * per_item;
         int tm, tn;
-        if (!STO && bid >= g.n_small) {
+        if (STO != STO_128 && bid >= g.n_small) {
             map_tile(bid - g.n_small, g.n_big, g.tiles_m_big, g.tiles_n, &tm, &tn);
-            if constexpr (!STO) fast_tile<DT, 256, MODE, STO>(g, smem, tm * 256, tn * 256, bz, tn);
+            if constexpr (STO != STO_128) fast_tile<DT, 256, MODE, STO>(g, smem, tm * 256, tn * 256, bz, tn);
         } else {
             map_tile(bid, g.n_small, g.tiles_m_small, g.tiles_n, &tm, &tn);
             fast_tile<DT, 128, MODE, STO>(g, smem, g.tiles_m_big * 256 + tm * 128, tn * 256, bz, tn);
@@ -525,9 +525,7 @@ static hipError_t launch_fast_one(GemmArgs &g, int batch, hipStream_t st)
     const int num_cu = device_cu_count(&e);
     if (e != hipSuccess) return e;
     g.tiles_n = (g.N + 255) / 256;
-    // (The sums of the stored values need registers that only 128-row tiles leave: in 256-row tiles blocks of accumulators go to
-    // scratch memory.)
-    const int big_rows = STO ? 0 : choose_big_rows(g.M, g.tiles_n, batch, num_cu, PROT);
+    const int big_rows = choose_big_rows(g.M, g.tiles_n, batch, num_cu, PROT);
     g.tiles_m_big = big_rows;
     g.n_big = big_rows * g.tiles_n;
     const int rest = g.M - big_rows * 256;
@@ -544,12 +542,16 @@ static hipError_t launch_fast_one(GemmArgs &g, int batch, hipStream_t st)
         grid.x += g.beside.n;
     }
     size_t smem;
-    auto kern = gemm_fast_kernel<DT, PROT ? FAST_OWN : FAST_PLAIN, STO>;
+    // Stored sums: the mix of tiles of any other call, and a kernel of its own where all have 128 rows (gemm_epilogue.h).  us, protected and
+    // stored: all of 128 rows / mixed: bf16 12608 x 768 x 3072 103.4 / 81.7, 12608 x 3072 x 768 95.5 / 85.5, 6304 x 3072 x 768 62.0 / 55.0,
+    // fp16 12212 x 3712 x 3904 381 / 344.
+    constexpr int ALL = STO ? STO_256 : STO_NO, SMALL = STO ? STO_128 : STO_NO;
+    auto kern = STO && !big_rows ? gemm_fast_kernel<DT, PROT ? FAST_OWN : FAST_PLAIN, SMALL> : gemm_fast_kernel<DT, PROT ? FAST_OWN : FAST_PLAIN, ALL>;
     if constexpr (PROT) {
         const size_t aux = fast_aux_bytes(DT, slabs, g.tiles_n);
         smem = fast_lds_bytes<FAST_OWN>() + aux;
         if (g.beside.n) {
-            kern = gemm_fast_kernel<DT, FAST_BESIDE, STO>;
+            kern = STO && !big_rows ? gemm_fast_kernel<DT, FAST_BESIDE, SMALL> : gemm_fast_kernel<DT, FAST_BESIDE, ALL>;
             smem = fast_lds_bytes<FAST_BESIDE>();
         }
     } else {

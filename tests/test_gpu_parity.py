@@ -2191,8 +2191,48 @@ def test_item_kernels_keep_non_finite_values_apart(ctx_items, dtype, value, M, N
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("bias", [False, True])
+# tiles of 256 rows, then of 128, hanging over both edges or none; 256 rows only (whole rounds of them)
+# (M at most 8 K, N at most 4 K: verify sums rounded values against tau)
+@pytest.mark.parametrize("M,N,K", [(8300, 2058, 1088), (6272, 3072, 896), (8192, 2048, 1024)])
+def test_fast_kernel_stored_sums_of_both_tile_heights(ctx, dtype, bias, M, N, K):
+    """The sums of the stored values, and their largest, against those of C as read back; verify finds a small flip by them."""
+    assert_fast(dtype, M, N, K)
+    A, B = gen.gen_operands(dtype, M, N, K, 47, 48, trans_b=True, batch=1)
+    run = Run(ctx, dtype, A, B, True)
+    d_bias = torch.linspace(-0.5, 0.5, N, device="cuda") if bias else None
+    if bias:
+        run.gemm_bias(d_bias, ab.ABFT_DETECT | ab.ABFT_STORED_SUMS)
+    else:
+        run.gemm(ab.ABFT_DETECT | ab.ABFT_STORED_SUMS)
+    assert run.cnt()[2] == ab.ABFT_CLEAN
+    C = orc.decode(run.C()[0], dtype).astype(np.float64)
+    # fp32 sums in any order
+    for got, axis, n in ((run.ws(ab.ABFT_WS_CC_STO)[0], 0, M), (run.ws(ab.ABFT_WS_RC_STO)[0], 1, N)):
+        assert np.all(np.abs(got - C.sum(axis=axis)) <= 2.0 ** -24 * np.sqrt(n) * np.abs(C).sum(axis=axis) + 1e-30)
+    assert run.ws(ab.ABFT_WS_C_MAX)[0, 0] == np.float32(np.max(np.abs(C)))
+    run.verify()
+    assert run.cnt()[2] == ab.ABFT_CLEAN
+    tol = orc.STO_TOL_FACTOR * run.ws(ab.ABFT_WS_TAU)[0, 0]
+    for (i, j) in ((0, 0), (255, N - 1), (M - 1, 256), (M // 2, N // 2)):
+        old = run.dC[0, i, j].item()
+        for bit in range(14):                                        # the smallest bit that the check by these sums has to find
+            new = np.int16(old ^ (1 << bit))
+            if abs(float(orc.decode(np.array([new], np.int16).view(np.uint16), dtype)[0]) - C[i, j]) > 4 * tol:
+                break
+        run.inject(0, i, j, bit)
+        run.verify()
+        rf, cf = run.flags()
+        assert rf.sum() == 1 and cf.sum() == 1 and rf[0, i] and cf[0, j], (i, j, bit)
+        run.dC[0, i, j] = old
+    run.verify()
+    assert run.cnt()[2] == ab.ABFT_CLEAN
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
 @pytest.mark.parametrize("value", [np.inf, np.nan])
-@pytest.mark.parametrize("M,N,K", [(600, 520, 256), (2100, 2090, 256)])
+# (the last: tiles of 256 rows, then of 128)
+@pytest.mark.parametrize("M,N,K", [(600, 520, 256), (2100, 2090, 256), (8300, 2058, 192)])
 @pytest.mark.parametrize("row", [21, -3])
 def test_stored_sums_keep_non_finite_values_apart(ctx, dtype, value, M, N, K, row):
     """One Inf or NaN in A, on the general and on the fast kernel, in a whole and in the ragged last group of
@@ -2222,7 +2262,8 @@ def test_stored_sums_keep_non_finite_values_apart(ctx, dtype, value, M, N, K, ro
 
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 @pytest.mark.parametrize("value", [np.inf, np.nan])
-@pytest.mark.parametrize("M,N,K", [(600, 520, 256), (2100, 2090, 256)])
+# (the last: tiles of 256 rows, then of 128)
+@pytest.mark.parametrize("M,N,K", [(600, 520, 256), (2100, 2090, 256), (8300, 2058, 192)])
 @pytest.mark.parametrize("col", [150, -3])
 def test_stored_sums_of_other_columns_keep_a_column_apart(ctx, dtype, value, M, N, K, col):
     """The same with the value in B, in one column of C, in a whole and in the ragged last group of columns."""
