@@ -18,13 +18,27 @@ namespace abft {
 
 constexpr int COLS_NW = 8, COLS_NT = 64 * COLS_NW;
 
+// The last block of columns hangs over the edge of C and takes twice as long to store as another: where a wave has no block, it
+// takes the second half of that block's rows.  (197 columns, seven blocks: the other waves waited 5900 of an item's 30000
+// clocks for the seventh, 2700 so.  bf16 197 x 197 x 64, 128 items 17.0 -> 15.6 us, 384 items 21.6 -> 21.3, unprotected 13.2 -> 12.6.)
+static __host__ __device__ bool shares_last_block(int NB, int N) { return NB < COLS_NW && NB * 32 > N; }
+// The kernel that can share it.  The other one has 50 to 110 instructions and up to 16 bytes of spilled registers less, and takes the
+// items without such a block: 197 x 224 x 64, 384 items, fp16 21.6 -> 21.1 us, with stored sums (192 columns) 33.2 -> 31.1, int8 22.4 -> 22.1.
+// Not in bf16 with B stored K x N, nor with stored sums and B stored N x K: there the compiler spills more scalar registers in it (256 items 197 x
+// 224 x 64: 18.3 us against 17.4 by this one; 384 items 197 x 160 x 64 with stored sums 32.9 against 31.6).
+static constexpr bool always_sharing_kernel(int dt, bool transB, bool protect, bool sto) { return dt == DT_BF16 && protect && sto == transB; }
+static bool takes_sharing_kernel(int dt, bool transB, bool protect, bool sto, int NB, int N)
+{
+    return NB <= COLS_NW && (shares_last_block(NB, N) || always_sharing_kernel(dt, transB, protect, sto));
+}
+
 // Offsets (words) of the vectors behind B and A.
 struct ColsLds {
     int KP, Mr, Nr, RC, a, b, apart, terms, rcobs, rcpred, rspart, ccobs, misc, rcsto, rsspart, ccsto, total;
-    __host__ __device__ ColsLds(const ItemArgs &g, int es, bool sto)
+    __host__ __device__ ColsLds(const ItemArgs &g, int es, bool sto, bool shared)
     {
         KP = g.steps * (es == 2 ? 16 : 32);
-        Mr = g.MB * 32; Nr = (g.NB + (g.NB < COLS_NW ? 1 : 0)) * 32; RC = g.rch * 32;      // (the sums of a shared block's second half behind the others)
+        Mr = g.MB * 32; Nr = (g.NB + (shared && g.NB < COLS_NW ? 1 : 0)) * 32; RC = g.rch * 32;      // (the sums of a shared block's second half behind the others)
         int o = 0;
         a = o; o += KP;
         b = o; o += KP;
@@ -42,7 +56,8 @@ struct ColsLds {
     }
 };
 
-template <int DT, int TPW, bool PROT, bool TRANSB, bool STO>
+// SHARED: the last block of columns may be two waves' (TPW = 1).
+template <int DT, int TPW, bool PROT, bool TRANSB, bool STO, bool SHARED>
 __global__ __launch_bounds__(COLS_NT, TPW == 1 && !STO ? 4 : 2) void item_cols_kernel(ItemArgs g)
 {
     using T = Traits<DT>;
@@ -54,17 +69,14 @@ __global__ __launch_bounds__(COLS_NT, TPW == 1 && !STO ? 4 : 2) void item_cols_k
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int M = g.M, N = g.N, K = g.K, np = g.steps / 2;
-    const ColsLds L(g, ES, STO);
+    const ColsLds L(g, ES, STO, SHARED);
     uint8_t *sA = smem + g.lds_a;
     uint32_t *vec = reinterpret_cast<uint32_t *>(smem + g.lds_vec);
     uint32_t *a_lds = vec + L.a, *b_lds = vec + L.b, *rcobs = vec + L.rcobs, *rcpred = vec + L.rcpred, *misc = vec + L.misc,
              *my_a = vec + L.apart + wave * L.KP, *my_rs = vec + L.rspart + wave * L.RC;
     uint8_t *terms = reinterpret_cast<uint8_t *>(vec + L.terms);
     const int ract = g.MB < COLS_NW ? g.MB : COLS_NW;            // waves that have a share of the pass over A
-    // The last block of columns hangs over the edge of C and takes twice as long to store as another: where a wave has no block, it
-    // takes the second half of that block's rows.  (197 columns, seven blocks: the other waves waited 5900 of an item's 30000
-    // clocks for the seventh, 2700 so.  bf16 197 x 197 x 64, 128 items 17.0 -> 15.6 us, 384 items 21.6 -> 21.3, unprotected 13.2 -> 12.6.)
-    const bool shared = TPW == 1 && g.NB < COLS_NW && g.NB * 32 > N;
+    const bool shared = SHARED && shares_last_block(g.NB, N);
     const int nb_first = shared && wave == g.NB ? g.NB - 1 : wave;
     unsigned nr_w = 0, nc_w = 0;
 
@@ -308,8 +320,8 @@ __global__ __launch_bounds__(COLS_NT, TPW == 1 && !STO ? 4 : 2) void item_cols_k
 // ------------------------------------------------------------------------------------------
 size_t item_cols_lds(int dt, const Shape &s, bool protect, bool sto, ItemArgs *g)
 {
-    (void)s;
     const int es = elem_size(dt);
+    const bool shared = takes_sharing_kernel(dt, s.transB, protect, sto, g->NB, s.N);
     if (g->NB > 3 * COLS_NW || (sto && g->NB > COLS_NW)) return 0;
     // one batch of loads must hold a chunk of A
     const int most = ((COLS_NT >> g->a_lg) * ITEM_U) / 32;
@@ -320,7 +332,7 @@ size_t item_cols_lds(int dt, const Shape &s, bool protect, bool sto, ItemArgs *g
             g->nchunk = (g->MB + g->rch - 1) / g->rch;
             g->lds_a = (g->b_rows * g->pb + 15) / 16 * 16;
             g->lds_vec = g->lds_a + g->rch * 32 * g->pa;
-            const ColsLds L(*g, es, sto);
+            const ColsLds L(*g, es, sto, shared);
             const size_t bytes = (size_t)g->lds_vec + (protect ? (size_t)L.total * 4 : 0);
             if (bytes <= budget) return bytes;
             // smaller chunks cost more in barriers than a second workgroup gives (one block: see gemm_item_eligible)
@@ -332,7 +344,9 @@ size_t item_cols_lds(int dt, const Shape &s, bool protect, bool sto, ItemArgs *g
 template <int DT, int TPW, bool PROT, bool TRANSB, bool STO>
 static hipError_t cols_one(const ItemArgs &g, size_t smem, hipStream_t st)
 {
-    auto kern = item_cols_kernel<DT, TPW, PROT, TRANSB, STO>;
+    auto kern = item_cols_kernel<DT, TPW, PROT, TRANSB, STO, TPW == 1 && always_sharing_kernel(DT, TRANSB, PROT, STO)>;
+    if constexpr (TPW == 1)
+        if (takes_sharing_kernel(DT, TRANSB, PROT, STO, g.NB, g.N)) kern = item_cols_kernel<DT, TPW, PROT, TRANSB, STO, true>;
     hipError_t e = ensure_max_lds(reinterpret_cast<const void *>(kern), ITEM_LDS_LIMIT);
     if (e != hipSuccess) return e;
     const unsigned blocks = (unsigned)(g.batch < ITEM_MAX_BLOCKS ? g.batch : ITEM_MAX_BLOCKS);
