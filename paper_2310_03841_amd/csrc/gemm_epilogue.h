@@ -264,7 +264,7 @@ __device__ __forceinline__ void gemm_epilogue_impl(const GemmArgs &g,
             constexpr uint32_t INF_BITS = DT == DT_BF16 ? 0x7F80u : 0x7C00u;
             const uint32_t hi = ep.pass.amax >> 16, lo = ep.pass.amax & 0xFFFFu;
             uint32_t w = hi > lo ? hi : lo;
-            if (__any(w > INF_BITS)) {
+            if (__builtin_expect(__any(w > INF_BITS), 0)) {
                 const uint32_t again = amax_again<DT>(g, ep, bz, m0, wm, wn);
                 if (w > INF_BITS) w = again;
             }
@@ -556,7 +556,7 @@ __device__ __forceinline__ void gemm_epilogue_impl(const GemmArgs &g,
                     if constexpr (STO)
                         unsafeAtomicAdd(reinterpret_cast<float *>(g.rc_sto) + (long)bz * M + gr, (rs_sto[t] + rs_sto[BM + t]) + (rs_sto[2 * BM + t] + rs_sto[3 * BM + t]));
                     atomic_add_word(g.rc_obs + (long)bz * M + gr, add_t(add_t(rs_part[t], rs_part[BM + t]), add_t(rs_part[2 * BM + t], rs_part[3 * BM + t])));
-                    if (ep.owned > 0 && !dots_bad)
+                    if (ep.owned > 0 && __builtin_expect(!dots_bad, 1))
                         atomic_add_word(g.rc_pred + (long)bz * M + gr, add_t(add_t(rp_part[t], rp_part[BM + t]), add_t(rp_part[2 * BM + t], rp_part[3 * BM + t])));
                 }
             } else {
@@ -577,7 +577,7 @@ __device__ __forceinline__ void gemm_epilogue_impl(const GemmArgs &g,
                 if (m > 0.f) atomicMax(g.c_max + bz, __float_as_uint(m));
             }
         }
-        if (dots_bad) {
+        if (__builtin_expect(dots_bad, 0)) {
             // BM / 8 rows to a wave
             constexpr int RW = BM / FAST_WAVES;
             const int ln = tile_thread_index() & 63, t = wave * RW + (ln & (RW - 1));
@@ -594,13 +594,13 @@ __device__ __forceinline__ void gemm_epilogue_impl(const GemmArgs &g,
             if constexpr (!T::IS_INT) {
                 // (a wave's 64 columns are one slab's)
                 const uint64_t which = __ballot(!(fabsf(v) < __builtin_inff()));
-                if (which) v = columns_again<DT>(g, bz, m0, M - m0 < BM ? M - m0 : BM, k - (t % KE), which, v);
+                if (__builtin_expect(which != 0, 0)) v = columns_again<DT>(g, bz, m0, M - m0 < BM ? M - m0 : BM, k - (t % KE), which, v);
             }
             atomic_add_word(g.a_sum + (long)bz * g.K + k, v);
         }
         if (!T::IS_INT && !g.a_given && tid == 0) {
             uint32_t top = 0u;
-            if (dots_bad) {
+            if (__builtin_expect(dots_bad, 0)) {
                 for (int w = 0; w < FAST_WAVES; ++w) top = (amax_w[w] & ~DOTS_BAD) > top ? amax_w[w] & ~DOTS_BAD : top;
             } else {
                 top = amax;
