@@ -26,19 +26,18 @@ static __host__ __device__ bool shares_last_block(int NB, int N) { return NB < C
 // items without such a block: 197 x 224 x 64, 384 items, fp16 21.6 -> 21.1 us, with stored sums (192 columns) 33.2 -> 31.1, int8 22.4 -> 22.1.
 // Not in bf16 with B stored K x N, nor with stored sums and B stored N x K: there the compiler spills more scalar registers in it (256 items 197 x
 // 224 x 64: 18.3 us against 17.4 by this one; 384 items 197 x 160 x 64 with stored sums 32.9 against 31.6).
-static constexpr bool always_sharing_kernel(int dt, bool transB, bool protect, bool sto) { return dt == DT_BF16 && protect && sto == transB; }
 static bool takes_sharing_kernel(int dt, bool transB, bool protect, bool sto, int NB, int N)
 {
-    return NB <= COLS_NW && (shares_last_block(NB, N) || always_sharing_kernel(dt, transB, protect, sto));
+    return NB <= COLS_NW && (shares_last_block(NB, N) || (dt == DT_BF16 && protect && sto == transB));
 }
 
 // Offsets (words) of the vectors behind B and A.
 struct ColsLds {
     int KP, Mr, Nr, RC, a, b, apart, terms, rcobs, rcpred, rspart, ccobs, misc, rcsto, rsspart, ccsto, total;
-    __host__ __device__ ColsLds(const ItemArgs &g, int es, bool sto)
+    __host__ __device__ ColsLds(const ItemArgs &g, int es, bool sto, bool shared)
     {
         KP = g.steps * (es == 2 ? 16 : 32);
-        Mr = g.MB * 32; Nr = g.NB * 32; RC = g.rch * 32;
+        Mr = g.MB * 32; Nr = (g.NB + (shared && g.NB < COLS_NW ? 1 : 0)) * 32; RC = g.rch * 32;      // (the sums of a shared block's second half behind the others)
         int o = 0;
         a = o; o += KP;
         b = o; o += KP;
@@ -69,7 +68,7 @@ __global__ __launch_bounds__(COLS_NT, TPW == 1 && !STO ? 4 : 2) void item_cols_k
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int M = g.M, N = g.N, K = g.K, np = g.steps / 2;
-    const ColsLds L(g, ES, STO);
+    const ColsLds L(g, ES, STO, SHARED);
     uint8_t *sA = smem + g.lds_a;
     uint32_t *vec = reinterpret_cast<uint32_t *>(smem + g.lds_vec);
     uint32_t *a_lds = vec + L.a, *b_lds = vec + L.b, *rcobs = vec + L.rcobs, *rcpred = vec + L.rcpred, *misc = vec + L.misc,
@@ -272,18 +271,15 @@ __global__ __launch_bounds__(COLS_NT, TPW == 1 && !STO ? 4 : 2) void item_cols_k
                 if (lane == 0) misc[40 + wave] = __float_as_uint(m);
             }
             // column sums of C over the lanes
-            uint32_t *past_a = reinterpret_cast<uint32_t *>(sA);
             static_for<0, TPW>([&](auto t_c) {
                 constexpr int t = decltype(t_c)::value;
                 const int nb = wave + COLS_NW * t;
                 if (nb < g.NB + (shared ? 1 : 0)) {
-                    // (a shared block's second half: where the rows of A were, which nobody reads any more)
-                    const bool second = shared && nb == g.NB;
                     const acc_t v = fold16<acc_t>(cs[t], lane);
-                    if ((lane & 1) == 0) (second ? past_a : vec + L.ccobs + nb * 32)[fold16_column(lane)] = as_word(v);
+                    if ((lane & 1) == 0) vec[L.ccobs + nb * 32 + fold16_column(lane)] = as_word(v);
                     if (STO) {
                         const float x = fold16<float>(cs_s[STO ? t : 0], lane);
-                        if ((lane & 1) == 0) (second ? past_a + 32 : vec + L.ccsto + nb * 32)[fold16_column(lane)] = __float_as_uint(x);
+                        if ((lane & 1) == 0) vec[L.ccsto + nb * 32 + fold16_column(lane)] = __float_as_uint(x);
                     }
                 }
             });
@@ -301,10 +297,10 @@ __global__ __launch_bounds__(COLS_NT, TPW == 1 && !STO ? 4 : 2) void item_cols_k
                     const long o = (long)bz * N + n;
                     const bool two = shared && nb == g.NB - 1;
                     uint32_t obs = vec[L.ccobs + n];
-                    if (two) obs = as_word(add_t(from_word<acc_t>(obs), from_word<acc_t>(past_a[l32])));
+                    if (two) obs = as_word(add_t(from_word<acc_t>(obs), from_word<acc_t>(vec[L.ccobs + n + 32])));
                     g.cc_pred[o] = as_word(d);
                     g.cc_obs[o] = obs;
-                    if (STO) g.cc_sto[o] = two ? __float_as_uint(__uint_as_float(vec[L.ccsto + n]) + __uint_as_float(past_a[32 + l32])) : vec[L.ccsto + n];
+                    if (STO) g.cc_sto[o] = two ? __float_as_uint(__uint_as_float(vec[L.ccsto + n]) + __uint_as_float(vec[L.ccsto + n + 32])) : vec[L.ccsto + n];
                     fl = mismatch<T::IS_INT>(obs, as_word(d), tol_c);
                     g.col_flag[o] = fl ? 1 : 0;
                 }
@@ -321,10 +317,16 @@ __global__ __launch_bounds__(COLS_NT, TPW == 1 && !STO ? 4 : 2) void item_cols_k
 }
 
 // ------------------------------------------------------------------------------------------
+// The sums of a shared block's second half lie behind the others: a block is shared where they fit beside the chunk of rows and the number
+// of workgroups that the item has without.  (512 items of 367 x 161 x 128, bf16: 36.8 us, 46.7 with a chunk more.)
+static size_t cols_bytes(const ItemArgs &g, int es, bool protect, bool sto, bool shared)
+{
+    return (size_t)g.lds_vec + (protect ? (size_t)ColsLds(g, es, sto, shared).total * 4 : 0);
+}
+
 size_t item_cols_lds(int dt, const Shape &s, bool protect, bool sto, ItemArgs *g)
 {
     const int es = elem_size(dt);
-    (void)s;
     if (g->NB > 3 * COLS_NW || (sto && g->NB > COLS_NW)) return 0;
     // one batch of loads must hold a chunk of A
     const int most = ((COLS_NT >> g->a_lg) * ITEM_U) / 32;
@@ -335,9 +337,11 @@ size_t item_cols_lds(int dt, const Shape &s, bool protect, bool sto, ItemArgs *g
             g->nchunk = (g->MB + g->rch - 1) / g->rch;
             g->lds_a = (g->b_rows * g->pb + 15) / 16 * 16;
             g->lds_vec = g->lds_a + g->rch * 32 * g->pa;
-            const ColsLds L(*g, es, sto);
-            const size_t bytes = (size_t)g->lds_vec + (protect ? (size_t)L.total * 4 : 0);
-            if (bytes <= budget) return bytes;
+            const size_t bytes = cols_bytes(*g, es, protect, sto, false);
+            if (bytes <= budget) {
+                const size_t sharing = cols_bytes(*g, es, protect, sto, true);
+                return takes_sharing_kernel(dt, s.transB, protect, sto, g->NB, s.N) && sharing <= budget ? sharing : bytes;
+            }
             // smaller chunks cost more in barriers than a second workgroup gives (one block: see gemm_item_eligible)
             if (g->rch <= (budget < (size_t)ITEM_LDS_LIMIT ? 2 : 1)) break;
         }
@@ -347,9 +351,9 @@ size_t item_cols_lds(int dt, const Shape &s, bool protect, bool sto, ItemArgs *g
 template <int DT, int TPW, bool PROT, bool TRANSB, bool STO>
 static hipError_t cols_one(const ItemArgs &g, size_t smem, hipStream_t st)
 {
-    auto kern = item_cols_kernel<DT, TPW, PROT, TRANSB, STO, TPW == 1 && always_sharing_kernel(DT, TRANSB, PROT, STO)>;
+    auto kern = item_cols_kernel<DT, TPW, PROT, TRANSB, STO, false>;
     if constexpr (TPW == 1)
-        if (takes_sharing_kernel(DT, TRANSB, PROT, STO, g.NB, g.N)) kern = item_cols_kernel<DT, TPW, PROT, TRANSB, STO, true>;
+        if (takes_sharing_kernel(DT, TRANSB, PROT, STO, g.NB, g.N) && smem >= cols_bytes(g, Traits<DT>::ES, PROT, STO, true)) kern = item_cols_kernel<DT, TPW, PROT, TRANSB, STO, true>;
     hipError_t e = ensure_max_lds(reinterpret_cast<const void *>(kern), ITEM_LDS_LIMIT);
     if (e != hipSuccess) return e;
     const unsigned blocks = (unsigned)(g.batch < ITEM_MAX_BLOCKS ? g.batch : ITEM_MAX_BLOCKS);
