@@ -488,15 +488,16 @@ static int choose_big_rows(int M, int tiles_n, int batch, int ncu, bool protect)
 }
 
 // Workgroups that reduce A on the `idle` compute units the tiles of a single round leave (a_beside).  Windows of 8
-// to 64 chunks along K (least padding, then widest), the rows dealt to as many row blocks as fit.  The tiles
-// are then free of their owned slabs, but their first slabs queue behind this pass's loads: about 1 us lost, against 0.5 us
-// (int8 1 us) for each owned slab.  Measured against tiles that reduce A, us: f16 6304 x 768 x 3072 (16 owned of 48 slabs)
-// 54.4 -> 52.1, 10870 x 896 x 2688 bf16 81.9 -> 75.2, int8 5099 x 896 x 2176 37.1 -> 32.7, 6422 x 1536 x 2688 47.5 -> 42.6; where K is
-// short or shared by many tile columns it lost (tiles by four waves): f16 6783 x 704 x 832 37.8 -> 38.4, 2788 x 3648 x 2240 (2.3 owned) 87.0 ->
-// 88.4, int8 10144 x 1408 x 1024 32.2 -> 33.3.  A workgroup reads 64 KB at a time, some 20 GB/s; the pass must end before
-// the tiles do (0.75 us per slab and 128 rows).
-constexpr double BESIDE_FIXED_US = 4.0, BESIDE_BYTES_PER_US = 20e3, TILE_SLAB_US = 0.75;
-static BesideArgs plan_beside(int dt, int M, int K, int batch, int slabs, int tiles_n, int idle, double tiles_us)
+// to 64 chunks along K (least padding, then widest), the rows dealt to as few row blocks as end in 0.85 of the time that the
+// tiles take: whatever reads A at once takes from the tiles' loads, and on every idle compute unit the pass cost more than it saved
+// where those were many.  us, tiles that own slabs / a workgroup on every idle unit / so: bf16 3775 x 1280 x 1600 33.2 / 33.6 / 30.3, f16 1447 x
+// 2752 x 2304 41.2 / 42.2 / 36.0, 8014 x 512 x 1344 31.0 / 33.8 / 28.3, 6304 x 768 x 3072 50.5 / 48.4 / 44.7; bf16 5664 x 768 x 3904 58.3 / 49.6 /
+// 49.5, int8 4655 x 1664 x 2688 40.2 / 37.8 / 37.5.  210 random problems that the conditions below let in: 0.957 of the time with owned
+// slabs (the worst 1.02, as far as two runs differ), 16-bit types 0.964 and int8 0.993 of that with all idle units.
+// Times in us of a workgroup's pass (it reads 64 KB at a time) and of a tile beside one, with what the clock comes down to under load.
+static double beside_us(int dt, long bytes) { return 4.0 + (double)bytes / (dt == DT_I8 ? 15e3 : 20e3); }
+static double tile_us(bool big, int slabs) { return big ? 8.0 + 1.25 * slabs : 6.0 + 0.7 * slabs; }
+static BesideArgs plan_beside(int dt, int M, int K, int batch, int slabs, int tiles_n, int idle, bool big)
 {
     const BesideArgs none = {0, 0, 0, 0, 0};
     if (dt == DT_I8 ? slabs < 9 || slabs < tiles_n : slabs < 20 || slabs < 3 * tiles_n) return none;
@@ -506,14 +507,18 @@ static BesideArgs plan_beside(int dt, int M, int K, int batch, int slabs, int ti
     BesideArgs b;
     b.cw_log2 = w.cw_log2; b.nwin = w.nwin;
     const int rl = (64 * FAST_WAVES >> w.cw_log2) * 8;                      // rows a workgroup takes at a time
-    b.nrb = (int)(idle / per_row_block);
-    b.rpb = (M + b.nrb - 1) / b.nrb;
-    b.rpb = (b.rpb + 15) / 16 * 16;
-    if (b.rpb < rl) b.rpb = rl;
+    const double tiles_us = tile_us(big, slabs);
+    const int most = (int)(idle / per_row_block);
+    double us = 0.0;
+    for (int n = 1; n <= most; ++n) {
+        b.rpb = ((M + n - 1) / n + 15) / 16 * 16;
+        if (b.rpb < rl) b.rpb = rl;
+        us = beside_us(dt, (long)b.rpb * (16 << w.cw_log2));
+        if (us <= 0.85 * tiles_us || b.rpb == rl) break;
+    }
     b.nrb = (M + b.rpb - 1) / b.rpb;
     b.n = (int)(b.nrb * per_row_block);
-    const double us = BESIDE_FIXED_US + (double)b.rpb * (16 << w.cw_log2) / BESIDE_BYTES_PER_US;
-    return us <= tiles_us ? b : none;
+    return us <= 1.2 * tiles_us ? b : none;
 }
 
 template <int DT, bool PROT, bool STO>
@@ -538,7 +543,7 @@ static hipError_t launch_fast_one(GemmArgs &g, int batch, hipStream_t st)
     dim3 grid((unsigned)(total < num_cu ? total : num_cu), 1, 1);
     g.beside.n = 0;
     if (PROT && total < num_cu) {
-        g.beside = plan_beside(DT, g.M, g.K, batch, slabs, g.tiles_n, num_cu - (int)total, TILE_SLAB_US * (g.n_big ? 2 : 1) * slabs);
+        g.beside = plan_beside(DT, g.M, g.K, batch, slabs, g.tiles_n, num_cu - (int)total, g.n_big != 0);
         grid.x += g.beside.n;
     }
     size_t smem;
