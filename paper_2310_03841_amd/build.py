@@ -21,7 +21,7 @@ FLAGS = [
 ]
 
 
-# The fast GEMM kernels count their outstanding loads by hand and keep 256 accumulators per lane:
+# The fast GEMM kernels count their outstanding loads by hand and keep up to 128 accumulators per lane, two waves to a SIMD:
 # a register spilled to scratch memory inside them costs speed at best.  The build fails on one.
 NO_SPILL_SOURCES = ["gemm_fast.hip"]
 

@@ -10,7 +10,8 @@
 // checksums beside their tiles: encode_pass.h).
 //
 // LDS slab layout (both GEMM kernels): row r is 128 bytes = eight 16-byte chunks, chunk c stored
-// in slot c ^ ((r >> 1) & 7).  Thread t reduces chunk c = t & 7 of rows (t >> 3) + 32 p.
+// in slot c ^ ((r >> 1) & 7).  The general kernel reduces it element by element, thread t chunk c = t & 7 of rows
+// (t >> 3) + 32 p (a_pass); the fast kernel by matrix instructions on the fragments (FastPass below).
 #pragma once
 #include <type_traits>
 

@@ -40,7 +40,7 @@ enum { STO_NO, STO_128, STO_256 };
 __host__ __device__ constexpr int epi_wave_bytes(int TN) { return 32 * (TN * 4 + 16); }
 __host__ __device__ constexpr int epi_total_bytes(int BM, int BN)
 {
-    return FAST_WAVES * epi_wave_bytes(BN / 4) + (12 * BM + 5 * BN) * 4 + 8 * FAST_WAVES;
+    return FAST_WAVES * epi_wave_bytes(BN / 4) + (12 * BM + 5 * BN) * 4 + 8 * FAST_WAVES;      // (with stored sums: the most)
 }
 
 // Read one accumulator element where it lives (an AGPR) at the point of use.  Without this the

@@ -1,6 +1,6 @@
 // Fast path of the protected GEMM for gfx950: B stored N x K (both operands K-contiguous) and
 // K a whole number (at least three) of 128-byte slabs.  The data movement:
-//   * global -> LDS with direct-to-LDS loads (global_load_lds_dwordx4): no VGPR staging.  One
+//   * global -> LDS with buffer loads that go straight there (buffer_load_dwordx4 ... lds): no VGPR staging.  One
 //     wave instruction fills 8 LDS rows of 128 bytes; the XOR swizzle of the LDS layout is
 //     applied by choosing which global 16-byte chunk each lane fetches.
 //   * 256 x 256 tiles by eight waves of 128 x 64 (eight 32x32 MFMA blocks per wave), 128 x 256 tiles by eight of 64 x 64;
@@ -167,6 +167,7 @@ __device__ __forceinline__ void fast_tile(const GemmArgs &g, uint8_t *smem, int 
     // Protected tiles reduce the slabs of A they own (slab s belongs to tile column s mod
     // tiles_n) while those are resident: see gemm_apass.h.
     constexpr int AUX_OFF = fast_lds_bytes<MODE>();    // behind the buffers of the larger tile
+    static_assert(epi_total_bytes(BM, 256) <= AUX_OFF, "the epilogue reads the column sums there while it fills the LDS ahead of them");
     EpiProt<DT, MI> ep;
     ep.slab0 = tn; ep.slab_step = g.tiles_n; ep.owned = (OWN && tn < nslab) ? (nslab - tn + g.tiles_n - 1) / g.tiles_n : 0;
     ep.col_lds = reinterpret_cast<uint32_t *>(smem + AUX_OFF);
@@ -241,9 +242,9 @@ __device__ __forceinline__ void fast_tile(const GemmArgs &g, uint8_t *smem, int 
                 fetch_b(own_at + 1);
             }
         };
-        // The pass over a slab this tile owns: a wave takes the fragments of step wn once more, of its rows, two at a time.  Cut into pieces,
-        // of which a middle slab has one behind every MFMA: some ninety instructions of a wave beside thirty-two (128-row tiles
-        // sixteen) MFMAs, for each of which the SIMD's other wave holds the matrix pipe as long.  (In one block behind or ahead of a
+        // The pass over a slab this tile owns: a wave takes the fragments of step wn once more, of its rows, two at a time.  Cut into pieces
+        // (19 in a 256-row tile, 128 rows 11; int8 15 and 9), dealt out in a middle slab over the MFMAs of steps 0 to 2, 24 and 12 of
+        // them: some ninety instructions of a wave, and the SIMD's other wave holds the matrix pipe as long.  (In one block behind or ahead of a
         // step the pass was longer than the other wave's MFMAs of the whole slab, and an owned slab cost a
         // tile of 256 rows, int8, 2300 clocks, one of 128 rows, f16, 1700; 1300 and 1450 so.  int8 36928 x 1024 x 4096 158.6 -> 155.8 us, 36928 x 4096
         // x 1024 202.7 -> 200.8.)
@@ -436,7 +437,9 @@ __global__ __launch_bounds__(64 * FAST_WAVES) void gemm_fast_kernel(GemmArgs g)
 // How many tile rows get 256-row tiles (the rest of M gets 128-row tiles).  Workgroups are
 // dispatched in index order to whichever CU is free, one per CU; a 128 x 256 tile takes 0.57 of the time of a 256 x 256 tile
 // (19.6 k of 34.6 k clocks at 12 slabs), protected 0.66 (29.7 k of 45 k): its prologue is the same.  A few candidate splits are
-// played through with those two costs and the one that finishes first wins; the result is remembered per shape.
+// played through with those two costs and the one that finishes first wins; the result is remembered per shape.  (The ratio falls
+// with depth, to 0.54 and 0.57 at 60 slabs.  Costs by a problem's slabs and owned slabs were
+// no better: 1.001 of the time over 120 random problems, single ones within 4 % either way.)
 static double play_schedule(int big_rows, int M, int tiles_n, int batch, int ncu, double small)
 {
     const int rest = M - big_rows * 256;
@@ -578,7 +581,7 @@ bool gemm_fast_eligible(int dt, int M, int N, int K, bool transB, long lda, long
     return transB && (K % ke) == 0 && K >= 3 * ke && M >= 512 && N >= 512 && (dt != DT_I8 || N < 65536) &&
            lda * elem_size(dt) < (1L << 23) && ldb * elem_size(dt) < (1L << 23) &&
            // what the pass over A's slabs keeps per tile fits behind the operand buffers (protected or
-           // not: the tile shape of a problem does not depend on the mode)
+           // not: a problem takes the same kernel in every mode)
            fast_lds_bytes<FAST_OWN>() + fast_aux_bytes(dt, K / ke, (N + 255) / 256) <= 160 * 1024;
 }
 
