@@ -2192,9 +2192,10 @@ def test_item_kernels_keep_non_finite_values_apart(ctx_items, dtype, value, M, N
 
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 @pytest.mark.parametrize("bias", [False, True])
-# tiles of 256 rows, then of 128, hanging over both edges or none; 256 rows only (whole rounds of them)
+# tiles of 256 rows, then of 128, hanging over both edges or none; 256 rows only (whole rounds of them); A reduced beside tiles of 128
+# and of 256 rows
 # (M at most 8 K, N at most 4 K: verify sums rounded values against tau)
-@pytest.mark.parametrize("M,N,K", [(8300, 2058, 1088), (6272, 3072, 896), (8192, 2048, 1024)])
+@pytest.mark.parametrize("M,N,K", [(8300, 2058, 1088), (6272, 3072, 896), (8192, 2048, 1024), (4100, 1030, 1408), (8200, 1530, 1408)])
 def test_fast_kernel_stored_sums_of_both_tile_heights(ctx, dtype, bias, M, N, K):
     """The sums of the stored values, and their largest, against those of C as read back; verify finds a small flip by them."""
     assert_fast(dtype, M, N, K)
