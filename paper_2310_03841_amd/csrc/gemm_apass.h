@@ -191,8 +191,8 @@ __device__ __forceinline__ void a_pass(const uint8_t *sA, const uint32_t *b_lds,
 // exchanges per slab); times b, split into terms that the operand type holds exactly, the dots of the fragment's 32 rows do, a
 // term to a register.  (The item kernels do the same: gemm_item.h.)  The four waves that share rows of A take a step
 // of the slab each.  Per owned slab of a 256-row tile that is eight MFMAs of 16 clocks (int8 twelve) and some seventy-five
-// vector instructions of one wave in four, where element by element it was two hundred of every wave.  What an owned slab adds to
-// a tile: int8 36928 x 1024 x 4096 (eight to a tile) 3000 -> 1300 clocks, the launch 171.9 -> 155.8 us.
+// vector instructions of one wave in four, where element by element it was two hundred of every wave.  int8 36928 x 1024 x 4096
+// (eight to a tile): the launch 171.9 -> 156 us.
 // Products with one are exact, and so are those with b's terms before they are added.  But Inf and NaN reach through
 // products with zeros what they have no part in, and a NaN hides the largest |element| of a lane: sums, dots and maxima that are not
 // finite are formed again, element by element, from memory (dots_again, columns_again, amax_again).

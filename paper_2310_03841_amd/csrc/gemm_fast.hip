@@ -242,75 +242,58 @@ __device__ __forceinline__ void fast_tile(const GemmArgs &g, uint8_t *smem, int 
                 fetch_b(own_at + 1);
             }
         };
-        // The pass over a slab this tile owns: a wave takes the fragments of step wn once more, of its rows, two at a time.  Cut into pieces
-        // (19 in a 256-row tile, 128 rows 11; int8 15 and 9), dealt out in a middle slab over the MFMAs of steps 0 to 2, 24 and 12 of
-        // them: some ninety instructions of a wave, and the SIMD's other wave holds the matrix pipe as long.  (In one block behind or ahead of a
-        // step the pass was longer than the other wave's MFMAs of the whole slab, and an owned slab cost a
-        // tile of 256 rows, int8, 2300 clocks, one of 128 rows, f16, 1700; 1300 and 1450 so.  int8 36928 x 1024 x 4096 158.6 -> 155.8 us, 36928 x 4096
-        // x 1024 202.7 -> 200.8.)
-        struct {
-            i32x4 b, x[2];
-            TurnSums<DT> ts;
-            typename Acc4<DT>::type sums[T::IS_INT ? 2 : 1];
-        } rd;
-        constexpr int RD_HALF = T::IS_INT ? 6 : 8, RD_PIECES = 1 + MI / 2 * RD_HALF + 2;
-        auto piece = [&](auto n_c) __attribute__((always_inline)) {
-            constexpr int n = decltype(n_c)::value;
-            constexpr int NU = T::IS_INT ? 2 : 1;
-            auto fetch_x = [&](auto h_c) __attribute__((always_inline)) {
-                static_for<0, 2>([&](auto i_c) {
-                    constexpr int mi = 2 * decltype(h_c)::value + decltype(i_c)::value, q = L::load_of_a(mi);
-                    rd.x[mi & 1] = *(lds_frag)(lds + ((frag_at ^ (32 * wn)) + (L::ring3(q) ? f0 : r0)) + L::at(q));
-                });
-            };
-            if constexpr (n == 0) {
+        // The pass over a slab this tile owns, ahead of its MFMAs: a wave takes the fragments of step wn once more, of its rows, two at a
+        // time: some ninety instructions, beside which the SIMD's other wave multiplies.  (Dealt out in pieces behind the MFMAs of the slab's
+        // first three steps it is no faster: pieces / so, us, bf16 12608 x 768 x 3072 72.7 / 72.2, 20000 x 768 x 2048 66.8 / 65.8, f16 12608 x 768 x
+        // 768 30.5 / 30.0, int8 36928 x 1024 x 4096 163.5 / 163.0; 72 problems, 1.006 of the time in pieces.)
+        auto reduce = [&](int s) __attribute__((always_inline)) {
+            if constexpr (OWN) {
+                if (s != next_own) return;
+                constexpr int NU = T::IS_INT ? 2 : 1;
                 // lane: column c = lane & 15 of the product belongs to the rows of half c >> 2, and to term c & 3
-                const int c = lane & 15, term = (c >> 2) == ((lane >> 4) & 1) ? c & 3 : 3;
+                const int ln = tile_thread_index() & 63, c = ln & 15, term = (c >> 2) == ((ln >> 4) & 1) ? c & 3 : 3;  // (formed here, not kept across the tile)
                 const uint8_t *src = terms + (term < 3 ? (own_at & 1) * TERMS + term * TERM : 2 * TERMS);
-                rd.b = *reinterpret_cast<const i32x4 *>(src + wn * 32 + lh * 16);
-                fetch_x(std::integral_constant<int, 0>{});
-            } else if constexpr (n < 1 + MI / 2 * RD_HALF) {
-                constexpr int h = (n - 1) / RD_HALF, k = (n - 1) % RD_HALF;
-                if constexpr (k < 2) {
-                    // rows past the end hold the last one's elements
-                    if (wm * TM + (2 * h + k) * 32 + l32 >= a_rows) rd.x[k] = i32x4{0, 0, 0, 0};
-                } else if constexpr (k == 2) {
-                    const int ln = tile_thread_index() & 63;       // (formed here, not kept across the tile)
-                    const i32x4 id0 = turn_operand<DT>(ln, 0), id1 = T::IS_INT ? turn_operand<DT>(ln, 1) : id0;
-                    pass_mfmas<DT>(ep.pass.dot[2 * h], ep.pass.dot[2 * h + 1], rd.ts, rd.x, rd.b, id0, id1);
-                } else if constexpr (!T::IS_INT && k < 7) {
-                    typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
-                    u16x2 m = __builtin_bit_cast(u16x2, ep.pass.amax);
+                const i32x4 b = *reinterpret_cast<const i32x4 *>(src + wn * 32 + (ln >> 5) * 16);
+                const i32x4 id0 = turn_operand<DT>(ln, 0), id1 = T::IS_INT ? turn_operand<DT>(ln, 1) : id0;
+                typename Acc4<DT>::type sums[NU];
+                static_for<0, MI / 2>([&](auto h_c) {
+                    constexpr int h = decltype(h_c)::value;
+                    i32x4 x[2];
+                    TurnSums<DT> ts;
+                    static_for<0, 2>([&](auto i_c) {
+                        constexpr int i = decltype(i_c)::value, q = L::load_of_a(2 * h + i);
+                        x[i] = *(lds_frag)(lds + ((frag_at ^ (32 * wn)) + (L::ring3(q) ? f0 : r0)) + L::at(q));
+                        // rows past the end hold the last one's elements
+                        if (wm * TM + (2 * h + i) * 32 + l32 >= a_rows) x[i] = i32x4{0, 0, 0, 0};
+                    });
+                    pass_mfmas<DT>(ep.pass.dot[2 * h], ep.pass.dot[2 * h + 1], ts, x, b, id0, id1);
+                    if constexpr (!T::IS_INT) {
+                        typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+                        u16x2 m = __builtin_bit_cast(u16x2, ep.pass.amax);
 #pragma unroll
-                    for (int i = 0; i < 2; ++i) m = __builtin_elementwise_max(m, __builtin_bit_cast(u16x2, rd.x[i][k - 3] & 0x7FFF7FFF));
-                    ep.pass.amax = __builtin_bit_cast(uint32_t, m);
-                } else if constexpr (k == (T::IS_INT ? 3 : 7)) {
-                    if constexpr (!T::IS_INT) rd.ts.c[0] += rd.ts.c[1];
+                        for (int i = 0; i < 8; ++i) m = __builtin_elementwise_max(m, __builtin_bit_cast(u16x2, x[i >> 2][i & 3] & 0x7FFF7FFF));
+                        ep.pass.amax = __builtin_bit_cast(uint32_t, m);
+                        ts.c[0] += ts.c[1];
+                    }
 #pragma unroll
-                    for (int u = 0; u < NU; ++u) rd.sums[u] = h == 0 ? rd.ts.c[u] : rd.sums[u] + rd.ts.c[u];
-                    if constexpr (h + 1 < MI / 2) fetch_x(std::integral_constant<int, h + 1>{});
-                }
-            } else if constexpr (n < RD_PIECES) {
-                constexpr int u = n - (RD_PIECES - 2);
-                if constexpr (u < NU) {
-                    typename T::acc_t v = add_t(add_t((typename T::acc_t)rd.sums[u][0], (typename T::acc_t)rd.sums[u][1]),
-                                                add_t((typename T::acc_t)rd.sums[u][2], (typename T::acc_t)rd.sums[u][3]));
+                    for (int u = 0; u < NU; ++u) sums[u] = h == 0 ? ts.c[u] : sums[u] + ts.c[u];
+                });
+#pragma unroll
+                for (int u = 0; u < NU; ++u) {
+                    typename T::acc_t v = add_t(add_t((typename T::acc_t)sums[u][0], (typename T::acc_t)sums[u][1]),
+                                                add_t((typename T::acc_t)sums[u][2], (typename T::acc_t)sums[u][3]));
                     v = add_xor32(add_xor16(v));
-                    if (lane < 16) lds_add_word(const_cast<uint32_t *>(ep.col_lds) + own_at * KE + wn * (KE / 4) + 16 * u + lane, v);
+                    if (ln < 16) lds_add_word(const_cast<uint32_t *>(ep.col_lds) + own_at * KE + wn * (KE / 4) + 16 * u + ln, v);
                 }
             }
         };
-        // all of it at once: the first slab and the last three
-        auto reduce = [&](int s) __attribute__((always_inline)) {
-            if (OWN && s == next_own) static_for<0, RD_PIECES>([&](auto n_c) { piece(n_c); });
-        };
         // A slab with loads between its MFMAs, in explicit program order (one group per MFMA, fenced): left
         // alone, the compiler issues all loads in one burst and the matrix pipe waits for them.  first_c: the first slab; all
-        // of slab 1 has been requested ahead of it.  
-        auto slab = [&](auto first_c, auto own_c, int s) __attribute__((always_inline)) {
-            constexpr bool FIRST = decltype(first_c)::value, MINE = decltype(own_c)::value;
+        // of slab 1 has been requested ahead of it.
+        auto slab = [&](auto first_c, int s) __attribute__((always_inline)) {
+            constexpr bool FIRST = decltype(first_c)::value;
             if constexpr (FIRST) reduce(s);
-            if constexpr (!MINE) own_ahead(s);
+            own_ahead(s);
             static_for<0, 4>([&](auto t_c) {
                 constexpr int t = decltype(t_c)::value;
                 // this step's loads: step 3 begins with those into this slab's buffers, steps 0 to 2 go on with those into the last one's
@@ -330,11 +313,6 @@ __device__ __forceinline__ void fast_tile(const GemmArgs &g, uint8_t *smem, int 
                         if (FIRST && t == 3 && q >= NR) to = to < nslab ? to : nslab - 1;      // of three slabs: bytes nobody reads
                         load(q_c, to, t == 3 ? Buf{f0, r0} : Buf{f2, r1});
                     });
-                    // the slab's buffers are read up to its barrier, behind step 2: the pieces are dealt out over steps 0 to 2
-                    if constexpr (MINE && t < 3) {
-                        constexpr int m = t * NMF + j;
-                        static_for<m * RD_PIECES / (3 * NMF), (m + 1) * RD_PIECES / (3 * NMF)>([&](auto n_c) { piece(n_c); });
-                    }
                     __builtin_amdgcn_sched_barrier(0);
                 });
                 if constexpr (t == 2) slab_barrier(std::true_type{});
@@ -372,22 +350,19 @@ __device__ __forceinline__ void fast_tile(const GemmArgs &g, uint8_t *smem, int 
             own_done(s);
             next();
         };
-        typedef std::true_type yes;
-        typedef std::false_type no;
-        slab(yes{}, no{}, 0);
-        // the middle slabs: runs of slabs that are not this workgroup's, each followed by one that is
-        // (loops and straight-line code only: an if / else with MFMAs in both arms would move the
-        // accumulators out of the accumulation registers)
+        slab(std::true_type{}, 0);
         int s = 1;
+        // the middle slabs: runs of slabs that are not this workgroup's, each followed by one that is
         const int mid_end = nslab - 3;
         if constexpr (OWN) {
             while (next_own < mid_end) {                   // next_own >= s here
-                for (; s < next_own; ++s) slab(no{}, no{}, s);
-                slab(no{}, yes{}, s);
+                for (; s < next_own; ++s) slab(std::false_type{}, s);
+                reduce(s);
+                slab(std::false_type{}, s);
                 ++s;
             }
         }
-        for (; s < mid_end; ++s) slab(no{}, no{}, s);
+        for (; s < mid_end; ++s) slab(std::false_type{}, s);
         for (; s < nslab; ++s) tail_slab(s);
     }
     __syncthreads();
