@@ -43,17 +43,21 @@ __host__ __device__ constexpr int epi_total_bytes(int BM, int BN)
     return FAST_WAVES * epi_wave_bytes(BN / 4) + (12 * BM + 5 * BN) * 4 + 8 * FAST_WAVES;      // (with stored sums: the most)
 }
 
-// Read one accumulator element where it lives (an AGPR) at the point of use.  Without this the
-// register allocator moves the whole accumulator set into VGPRs at the top of the epilogue and
-// spills part of it.
-__device__ __forceinline__ float acc_read(float v)
+// One accumulator element, at the point of use.  A kernel of 512 threads has 256 registers a lane, and where nothing asks for
+// accumulation registers the compiler takes all of them as vector registers: the MFMAs write there, and the epilogue's instructions
+// read there.  AGPR: the kernels that have no register to spare (STO_256) keep the accumulators in 128 accumulation
+// registers and read them one by one (left alone, the register allocator moves all of them at the top of the epilogue and
+// spills).
+template <bool AGPR> __device__ __forceinline__ float acc_read(float v)
 {
+    if constexpr (!AGPR) return v;
     float r;
     asm("v_accvgpr_read_b32 %0, %1" : "=v"(r) : "a"(v));
     return r;
 }
-__device__ __forceinline__ int acc_read(int v)
+template <bool AGPR> __device__ __forceinline__ int acc_read(int v)
 {
+    if constexpr (!AGPR) return v;
     int r;
     asm("v_accvgpr_read_b32 %0, %1" : "=v"(r) : "a"(v));
     return r;
@@ -224,6 +228,7 @@ __device__ __forceinline__ void gemm_epilogue_impl(const GemmArgs &g,
     constexpr int OS = T::OS;
     constexpr int KE = SLAB_BYTES / T::ES;
     static_assert(TN == 64, "a lane to a column where a wave walks a row");
+    constexpr bool AGPR = STO == STO_256;
     constexpr int WAVE_BYTES = epi_wave_bytes(TN);
     constexpr int CROW = TN * OS + 16;              // staged C row (bytes), padded
     constexpr int SROW = TN * 4 + 16;               // staged 32-bit row (bytes), padded
@@ -380,8 +385,8 @@ __device__ __forceinline__ void gemm_epilogue_impl(const GemmArgs &g,
                 constexpr int ni = decltype(ni_c)::value;
                 static_for<0, 4>([&](auto q_c) {
                     constexpr int q = decltype(q_c)::value;
-                    acc_t v0 = acc_read(acc[mi][ni][4 * q]), v1 = acc_read(acc[mi][ni][4 * q + 1]),
-                          v2 = acc_read(acc[mi][ni][4 * q + 2]), v3 = acc_read(acc[mi][ni][4 * q + 3]);
+                    acc_t v0 = acc_read<AGPR>(acc[mi][ni][4 * q]), v1 = acc_read<AGPR>(acc[mi][ni][4 * q + 1]),
+                          v2 = acc_read<AGPR>(acc[mi][ni][4 * q + 2]), v3 = acc_read<AGPR>(acc[mi][ni][4 * q + 3]);
                     if (has_bias) {
                         const i32x4 bb = *reinterpret_cast<const i32x4 *>(bias_lds + wn * TN + ni * 32 + 8 * q + 4 * lh);
                         v0 = add_t(v0, from_word<acc_t>((uint32_t)bb[0])); v1 = add_t(v1, from_word<acc_t>((uint32_t)bb[1]));
@@ -438,8 +443,8 @@ __device__ __forceinline__ void gemm_epilogue_impl(const GemmArgs &g,
                     constexpr int q = decltype(q_c)::value;
                     uint8_t *d = wbuf + l32 * SROW + (ni * 32 + 8 * q + 4 * lh) * 4;
                     *reinterpret_cast<i32x4 *>(d) =
-                        i32x4{(int)as_word(acc_read(acc[mi][ni][4 * q])), (int)as_word(acc_read(acc[mi][ni][4 * q + 1])),
-                              (int)as_word(acc_read(acc[mi][ni][4 * q + 2])), (int)as_word(acc_read(acc[mi][ni][4 * q + 3]))};
+                        i32x4{(int)as_word(acc_read<AGPR>(acc[mi][ni][4 * q])), (int)as_word(acc_read<AGPR>(acc[mi][ni][4 * q + 1])),
+                              (int)as_word(acc_read<AGPR>(acc[mi][ni][4 * q + 2])), (int)as_word(acc_read<AGPR>(acc[mi][ni][4 * q + 3]))};
                 });
             });
             wave_sync();
