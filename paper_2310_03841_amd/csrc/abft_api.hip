@@ -952,6 +952,7 @@ extern "C" int abft_tile_shape(abft_dtype dtype, const abft_shape *s, int *tile_
     Shape sh;
     memset(&sh, 0, sizeof(sh));
     sh.M = (int)s->M; sh.N = (int)s->N; sh.K = (int)s->K; sh.batch = (int)s->batch; sh.transB = s->transB;
+    sh.lda = s->lda; sh.ldb = s->ldb; sh.ldc = s->ldc;
     gemm_tile_shape(dtype, sh, tile_m, tile_n);
     return ABFT_OK;
 }

@@ -53,6 +53,16 @@ struct ItemArgs {
     uint32_t *c_max;                              // max|C as stored| as float bits, with the stored-side sums
 };
 
+// The arguments, read from where the launch put them: each phase of an item takes its own.  Taken from the parameter, every argument and
+// every offset, pitch and condition that follows from them is formed ahead of the loop over items and held across it: 200 to 290
+// scalars too many, which go to lanes of vector registers and come back one by one (some 500 of a kernel's 3400 instructions).
+__device__ __forceinline__ const ItemArgs &item_args()
+{
+    const __attribute__((address_space(4))) ItemArgs *p = (const __attribute__((address_space(4))) ItemArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return *(const ItemArgs *)p;
+}
+
 // Workgroup barrier over LDS traffic only: a full barrier would also wait until every store of C
 // issued so far has been acknowledged.
 __device__ __forceinline__ void item_barrier()
@@ -109,32 +119,35 @@ __device__ __forceinline__ int fold16_column(int lane)
 // ------------------------------------------------------------------ operands into LDS
 // Rows [0, rows_total) of `chunks` 16-byte chunks each; what lies past `rows` or past rowbytes is zero.
 // 1 << lg threads share a row.  A batch is ITEM_U independent loads per thread.
+// Buffer loads: what lies outside comes as zeros without a branch, and a load costs one addition.  Offsets stay below 2^31 (item_plan).
 constexpr int ITEM_U = 4;
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+constexpr int ITEM_RSRC_FLAGS = 0x00027000;
 struct ItemStage {
-    const uint8_t *src;
-    long ldbytes;
-    int rows, rows_total, rowbytes, chunks, lg, pitch;
+    __amdgpu_buffer_rsrc_t src;
+    int ldbytes, rows_total, rowbytes, chunks, lg, pitch;
 };
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t stage_source(const uint8_t *base, int rows, int ldbytes, int rowbytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(base), 0, rows > 0 ? (rows - 1) * ldbytes + ((rowbytes + 15) & ~15) : 0, ITEM_RSRC_FLAGS);
+}
 __device__ __forceinline__ void stage_load(const ItemStage &t, int row0, int nt, int tid, i32x4 (&v)[ITEM_U])
 {
     const int c = tid & ((1 << t.lg) - 1), r0 = row0 + (tid >> t.lg), rp = nt >> t.lg;
+    const unsigned at = c * 16 < t.rowbytes ? (unsigned)(r0 * t.ldbytes + c * 16) : 0x80000000u;
 #pragma unroll
-    for (int u = 0; u < ITEM_U; ++u) {
-        const int r = r0 + u * rp;
-        v[u] = i32x4{0, 0, 0, 0};
-        if (r < t.rows && c * 16 < t.rowbytes) v[u] = *reinterpret_cast<const i32x4 *>(t.src + (long)r * t.ldbytes + c * 16);
-    }
+    for (int u = 0; u < ITEM_U; ++u) v[u] = __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(t.src, at + (unsigned)(u * rp * t.ldbytes), 0, 0));
 }
 __device__ __forceinline__ void stage_store(const ItemStage &t, int row0, int nt, int tid, uint8_t *dst, const i32x4 (&v)[ITEM_U])
 {
     const int c = tid & ((1 << t.lg) - 1), r0 = row0 + (tid >> t.lg), rp = nt >> t.lg;
-    const int keep = t.rowbytes - c * 16;
+    const bool cut = (t.rowbytes & 15) != 0;                   // a chunk holds what does not belong to the row
+    uint8_t *d = dst + r0 * t.pitch + c * 16;
 #pragma unroll
     for (int u = 0; u < ITEM_U; ++u) {
-        const int r = r0 + u * rp;
         i32x4 x = v[u];
-        if (keep < 16) x = mask_chunk(x, keep);
-        if (r < t.rows_total && c < t.chunks) *reinterpret_cast<i32x4 *>(dst + r * t.pitch + c * 16) = x;
+        if (cut) x = mask_chunk(x, t.rowbytes - c * 16);
+        if (r0 + u * rp < t.rows_total && c < t.chunks) *reinterpret_cast<i32x4 *>(d + u * rp * t.pitch) = x;
     }
 }
 __device__ __forceinline__ int stage_batch_rows(const ItemStage &t, int nt) { return (nt >> t.lg) * ITEM_U; }
@@ -151,10 +164,9 @@ template <int DT, bool TRANSB> __device__ __forceinline__ ItemStage b_stage(cons
 {
     constexpr int ES = Traits<DT>::ES;
     ItemStage t;
-    t.src = g.B + (long)bz * g.sB * ES;
-    t.ldbytes = g.ldb * ES;
-    t.rows = TRANSB ? g.N : g.K;
+    t.ldbytes = (int)g.ldb * ES;
     t.rowbytes = (TRANSB ? g.K : g.N) * ES;
+    t.src = stage_source(g.B + (long)bz * g.sB * ES, TRANSB ? g.N : g.K, t.ldbytes, t.rowbytes);
     t.rows_total = g.b_rows; t.chunks = g.b_chunks; t.lg = g.b_lg; t.pitch = g.pb;
     return t;
 }
@@ -512,14 +524,33 @@ template <int DT> __device__ __forceinline__ float unpack_hi(uint32_t w)
 // (lane & 15) + 16 pass, and the four lanes of a row its 64 bytes.  int32 C: one more exchange, between
 // lane and lane ^ 8, makes it eight rows of 128 bytes (segments of 64 bytes, off their 64-byte boundaries
 // as rows of C usually are, wrote 1024 x 577 x 577 in 584 us, unprotected).
+// Where an item's C goes: buffer stores, which leave out rows past M without a branch (they lie past the end: the descriptor ends
+// with the last row), and a lane's place in a block as an offset, so that a store costs an addition.  Offsets stay below 2^31 (item_plan).
+struct ItemOut {
+    __amdgpu_buffer_rsrc_t dst;
+    int N, ldbytes, lane;
+};
+template <int DT> __device__ __forceinline__ int out_col(int lane)
+{
+    if constexpr (Traits<DT>::OS == 4) return 16 * ((lane >> 3) & 1) + 8 * ((lane >> 4) & 1) + 4 * (lane >> 5);
+    else return 16 * ((lane >> 4) & 1) + 8 * (lane >> 5);
+}
+template <int DT> __device__ __forceinline__ ItemOut item_out(const ItemArgs &g, int bz, int lane)
+{
+    constexpr int OS = Traits<DT>::OS;
+    ItemOut o;
+    o.N = g.N;
+    o.ldbytes = (int)g.ldc * OS;
+    o.dst = __builtin_amdgcn_make_buffer_rsrc(g.C + (long)bz * g.sC * OS, 0, (g.M - 1) * o.ldbytes + g.N * OS, ITEM_RSRC_FLAGS);
+    o.lane = (lane & (OS == 4 ? 7 : 15)) * o.ldbytes + out_col<DT>(lane) * OS;
+    return o;
+}
 template <int DT>
-__device__ __forceinline__ void store_block(const ItemArgs &g, uint8_t *Cb, const uint32_t *w, int m0, int n0, int lane)
+__device__ __forceinline__ void store_block(const ItemOut &o, const uint32_t *w, int m0, int n0, int lane)
 {
     constexpr int OS = Traits<DT>::OS;
     constexpr int NP = OS == 4 ? 4 : 2, RPP = 32 / NP;         // passes, rows per pass
     i32x4 out[NP];
-    int row, col;
-    const int lh = lane >> 5, b4 = (lane >> 4) & 1;
     if constexpr (OS == 4) {
         i32x4 s[2][2];                           // [half of the columns][rows 0..15, 16..31]
 #pragma unroll
@@ -538,8 +569,6 @@ __device__ __forceinline__ void store_block(const ItemArgs &g, uint8_t *Cb, cons
                 out[2 * r][j] = __builtin_amdgcn_update_dpp(s[0][r][j], s[1][r][j], 0x128, 0xF, 0xC, false);
                 out[2 * r + 1][j] = __builtin_amdgcn_update_dpp(s[1][r][j], s[0][r][j], 0x128, 0xF, 0x3, false);
             }
-        row = m0 + (lane & 7);
-        col = n0 + 16 * ((lane >> 3) & 1) + 8 * b4 + 4 * lh;
     } else {
         uint32_t u[4], v[4];
 #pragma unroll
@@ -555,43 +584,36 @@ __device__ __forceinline__ void store_block(const ItemArgs &g, uint8_t *Cb, cons
             out[0][j] = (int)p[0];
             out[1][j] = (int)p[1];
         }
-        row = m0 + (lane & 15);
-        col = n0 + 16 * b4 + 8 * lh;
     }
-    uint8_t *dst = Cb + ((long)row * g.ldc + col) * OS;
-    const long step = RPP * g.ldc * OS;
-    if (m0 + 32 <= g.M && n0 + 32 <= g.N) {
+    const int at = o.lane + m0 * o.ldbytes + n0 * OS, step = RPP * o.ldbytes;
+    if (n0 + 32 <= o.N) {
 #pragma unroll
-        for (int p = 0; p < NP; ++p) *reinterpret_cast<i32x4 *>(dst + p * step) = out[p];
+        for (int p = 0; p < NP; ++p) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, out[p]), o.dst, at + p * step, 0, 0);
     } else {
-        // The edges.  What is left of a lane's 16 bytes at the right one is the same for every lane and leaves
+        // The right edge.  What is left of a lane's 16 bytes there is the same for every lane and leaves
         // in falling powers of two, all passes of a size together: few branches, they cost most here.
-        typedef int i32x2 __attribute__((ext_vector_type(2)));
-        const int left = (g.N * OS) & 15;
-        const int rows = g.M - row;              // valid rows from this lane's first on
-        if (col + 16 / OS <= g.N) {
+        typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+        const int left = (o.N * OS) & 15;
+        const int col = n0 + out_col<DT>(lane);
+        if (col + 16 / OS <= o.N) {
 #pragma unroll
-            for (int p = 0; p < NP; ++p)
-                if (p * RPP < rows) *reinterpret_cast<i32x4 *>(dst + p * step) = out[p];
-        } else if (col < g.N) {
+            for (int p = 0; p < NP; ++p) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, out[p]), o.dst, at + p * step, 0, 0);
+        } else if (col < o.N) {
             if (left & 8) {
 #pragma unroll
-                for (int p = 0; p < NP; ++p)
-                    if (p * RPP < rows) *reinterpret_cast<i32x2 *>(dst + p * step) = i32x2{out[p][0], out[p][1]};
+                for (int p = 0; p < NP; ++p) __builtin_amdgcn_raw_buffer_store_b64(u32x2{(unsigned)out[p][0], (unsigned)out[p][1]}, o.dst, at + p * step, 0, 0);
             }
             if (left & 4) {
-                const int at = left & 8;
+                const int from = left & 8;
 #pragma unroll
-                for (int p = 0; p < NP; ++p)
-                    if (p * RPP < rows) *reinterpret_cast<int *>(dst + p * step + at) = at ? out[p][2] : out[p][0];
+                for (int p = 0; p < NP; ++p) __builtin_amdgcn_raw_buffer_store_b32((unsigned)(from ? out[p][2] : out[p][0]), o.dst, at + p * step + from, 0, 0);
             }
             if (left & 2) {
-                const int at = left & 12;
+                const int from = left & 12;
 #pragma unroll
                 for (int p = 0; p < NP; ++p)
-                    if (p * RPP < rows)
-                        *reinterpret_cast<uint16_t *>(dst + p * step + at) =
-                            (uint16_t)(at & 8 ? (at & 4 ? out[p][3] : out[p][2]) : (at & 4 ? out[p][1] : out[p][0]));
+                    __builtin_amdgcn_raw_buffer_store_b16((unsigned short)(from & 8 ? (from & 4 ? out[p][3] : out[p][2]) : (from & 4 ? out[p][1] : out[p][0])),
+                                                          o.dst, at + p * step + from, 0, 0);
             }
         }
     }
@@ -682,14 +704,10 @@ __device__ __forceinline__ void item_scalars_out(const ItemArgs &g, int bz, cons
         if (!g.cached_b) g.b_max[bz] = __float_as_uint(t.mb);
     }
 }
-// Flagged rows / columns of this workgroup, then its ticket (in two levels: atomics on one word are
-// served one after the other); the last workgroup writes counts and status.  cnt: 2 nw words of LDS.
-__device__ __forceinline__ void item_ticket(const ItemArgs &g, uint32_t *cnt, int nw, unsigned nr_w, unsigned nc_w)
+// The ticket of a workgroup, by one thread (in two levels: atomics on one word are served one after the other); the last workgroup writes
+// counts and status.  cnt: the waves' flagged rows, then columns (2 nw words of LDS, put there ahead of a barrier).
+__device__ __forceinline__ void item_ticket(const ItemArgs &g, const uint32_t *cnt, int nw)
 {
-    const int tid = threadIdx.x;
-    if ((tid & 63) == 0) { cnt[tid >> 6] = nr_w; cnt[nw + (tid >> 6)] = nc_w; }
-    item_barrier();
-    if (tid != 0) return;
     unsigned nr = 0, nc = 0;
     for (int w = 0; w < nw; ++w) { nr += cnt[w]; nc += cnt[nw + w]; }
     if (nr | nc) {

@@ -17,6 +17,9 @@ static size_t item_plan(int dt, const Shape &s, bool protect, bool sto, ItemArgs
     // N <= 128: as deep as B fits in LDS (bf16 attn V of 577 tokens, 400 items: 111 us, on tiles 281; 400
     // tokens of head dimension 128, 300 items: 65 / 131).  Wider items hold whole rows of A beside B.
     if ((long)s.K * es > (s.N <= 128 ? 1600 : s.N <= 256 ? 384 : 256)) return 0;
+    // offsets inside an item as 32-bit numbers: rows this wide are for the tiles
+    constexpr long MAX_LD_BYTES = 1L << 19;
+    if (s.lda * es > MAX_LD_BYTES || s.ldb * es > MAX_LD_BYTES || s.ldc * out_size(dt) > MAX_LD_BYTES) return 0;
     g->M = s.M; g->N = s.N; g->K = s.K; g->batch = s.batch;
     g->nch = (s.K * es + 15) / 16;
     g->steps = ((s.K * es + 31) / 32 + 1) / 2 * 2;

@@ -57,7 +57,7 @@ struct ColsLds {
 
 // SHARED: the last block of columns may be two waves' (TPW = 1).
 template <int DT, int TPW, bool PROT, bool TRANSB, bool STO, bool SHARED>
-__global__ __launch_bounds__(COLS_NT, TPW == 1 && !STO ? 4 : 2) void item_cols_kernel(ItemArgs g)
+__global__ __launch_bounds__(COLS_NT, TPW == 1 && !STO ? 4 : 2) void item_cols_kernel(ItemArgs)
 {
     using T = Traits<DT>;
     typedef typename T::acc_t acc_t;
@@ -67,47 +67,48 @@ __global__ __launch_bounds__(COLS_NT, TPW == 1 && !STO ? 4 : 2) void item_cols_k
     constexpr int R = TPW == 1 ? 2 : 1;         // blocks of rows at a time
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int M = g.M, N = g.N, K = g.K, np = g.steps / 2;
-    const ColsLds L(g, ES, STO, SHARED);
-    uint8_t *sA = smem + g.lds_a;
-    uint32_t *vec = reinterpret_cast<uint32_t *>(smem + g.lds_vec);
-    uint32_t *a_lds = vec + L.a, *b_lds = vec + L.b, *rcobs = vec + L.rcobs, *rcpred = vec + L.rcpred, *misc = vec + L.misc,
-             *my_a = vec + L.apart + wave * L.KP, *my_rs = vec + L.rspart + wave * L.RC;
-    uint8_t *terms = reinterpret_cast<uint8_t *>(vec + L.terms);
-    const int ract = g.MB < COLS_NW ? g.MB : COLS_NW;            // waves that have a share of the pass over A
-    const bool shared = SHARED && shares_last_block(g.NB, N);
-    const int nb_first = shared && wave == g.NB ? g.NB - 1 : wave;
     unsigned nr_w = 0, nc_w = 0;
 
-    for (int bz = blockIdx.x; bz < g.batch; bz += gridDim.x) {
+    for (int bz = blockIdx.x;; bz += gridDim.x) {
         const int tid = item_opaque(threadIdx.x), lane = tid & 63, l32 = lane & 31, lh = lane >> 5;
-        const Frag fb(smem, g.pb, lane);
-        const Ident<DT> id(lane);
-        uint8_t *Cb = g.C + (long)bz * g.sC * OS;
-        ItemStage as;
-        as.src = g.A + (long)bz * g.sA * ES;
-        as.ldbytes = g.lda * ES; as.rows = M; as.rowbytes = K * ES;
-        as.rows_total = L.RC; as.chunks = 2 * g.steps; as.lg = g.a_lg; as.pitch = g.pa;
-        const ItemStage bs = b_stage<DT, TRANSB>(g, bz);
+        // rows of A, from row row0 of the item on
+        auto a_stage = [&](const ItemArgs &g, const ColsLds &L, int row0) __attribute__((always_inline)) {
+            ItemStage as;
+            as.ldbytes = (int)g.lda * ES; as.rowbytes = g.K * ES;
+            as.src = stage_source(g.A + ((long)bz * g.sA + (long)row0 * g.lda) * ES, g.M - row0, as.ldbytes, as.rowbytes);
+            as.rows_total = L.RC; as.chunks = 2 * g.steps; as.lg = g.a_lg; as.pitch = g.pa;
+            return as;
+        };
         i32x4 va[ITEM_U];                        // rows of A on their way: one batch holds a chunk (see item_cols_lds)
-        stage_load(as, 0, COLS_NT, tid, va);
         {
+            const ItemArgs &g = item_args();
+            const ColsLds L(g, ES, STO, SHARED);
+            uint32_t *vec = reinterpret_cast<uint32_t *>(smem + g.lds_vec);
+            const ItemStage as = a_stage(g, L, 0), bs = b_stage<DT, TRANSB>(g, bz);
             i32x4 vb[ITEM_U];
+            stage_load(as, 0, COLS_NT, tid, va);
             stage_load(bs, 0, COLS_NT, tid, vb);
             if (PROT)
                 for (int k = tid; k < COLS_NW * L.KP; k += COLS_NT) vec[L.apart + k] = 0u;
-            stage_store(as, 0, COLS_NT, tid, sA, va);
+            stage_store(as, 0, COLS_NT, tid, smem + g.lds_a, va);
             stage_store(bs, 0, COLS_NT, tid, smem, vb);
             stage_rest(bs, stage_batch_rows(bs, COLS_NT), COLS_NT, tid, smem);
         }
         item_barrier();
         if (PROT) {
+            const ItemArgs &g = item_args();
+            const ColsLds L(g, ES, STO, SHARED);
+            uint32_t *vec = reinterpret_cast<uint32_t *>(smem + g.lds_vec);
+            uint8_t *terms = reinterpret_cast<uint8_t *>(vec + L.terms);
             uint32_t bmax = 0;
             if (g.cached_b) {
-                b_cached<DT>(g, bz, b_lds, terms, L.KP, tid, COLS_NT);
+                b_cached<DT>(g, bz, vec + L.b, terms, L.KP, tid, COLS_NT);
             } else {
-                b_pass<DT>(g, fb, id, b_lds, terms, L.KP, bs.src, TRANSB ? ES : bs.ldbytes, TRANSB ? bs.ldbytes : ES, wave, COLS_NW, lane, &bmax);
-                item_max_out<DT>(bmax, bs.src, bs.ldbytes, bs.rows, bs.rowbytes / ES, lane, misc + 8 + wave);
+                const Frag fb(smem, g.pb, lane);
+                const uint8_t *Bb = g.B + (long)bz * g.sB * ES;
+                const long ldb_bytes = g.ldb * ES;
+                b_pass<DT>(g, fb, Ident<DT>(lane), vec + L.b, terms, L.KP, Bb, TRANSB ? ES : ldb_bytes, TRANSB ? ldb_bytes : ES, wave, COLS_NW, lane, &bmax);
+                item_max_out<DT>(bmax, Bb, ldb_bytes, TRANSB ? g.N : g.K, TRANSB ? g.K : g.N, lane, vec + L.misc + 8 + wave);
             }
             item_barrier();
         }
@@ -120,19 +121,25 @@ __global__ __launch_bounds__(COLS_NT, TPW == 1 && !STO ? 4 : 2) void item_cols_k
 #pragma unroll
             for (int i = 0; i < 16; ++i) { cs[t][i] = T::zero(); cs_s[STO ? t : 0][i] = 0.f; }
 
-        for (int c = 0; c < g.nchunk; ++c) {
-            const int rb0 = c * g.rch, rb1 = min(rb0 + g.rch, g.MB);
-            if (c + 1 < g.nchunk) {
+        for (int c = 0;; ++c) {
+            bool more;
+            {
+                const ItemArgs &g = item_args();
+                const ColsLds L(g, ES, STO, SHARED);
+                more = c + 1 < g.nchunk;
                 // (the last chunk may be shorter: rows past M are zero)
-                ItemStage nx = as;
-                nx.src += (long)rb1 * 32 * as.ldbytes;
-                nx.rows = M - rb1 * 32;
-                stage_load(nx, 0, COLS_NT, tid, va);
+                if (more) stage_load(a_stage(g, L, (c + 1) * g.rch * 32), 0, COLS_NT, tid, va);
             }
             if (PROT) {
                 // the pass over A: a wave takes every eighth block of rows
+                const ItemArgs &g = item_args();
+                const ColsLds L(g, ES, STO, SHARED);
+                uint32_t *vec = reinterpret_cast<uint32_t *>(smem + g.lds_vec), *my_a = vec + L.apart + wave * L.KP, *b_lds = vec + L.b;
+                uint8_t *terms = reinterpret_cast<uint8_t *>(vec + L.terms);
+                const int rb0 = c * g.rch, rb1 = min(rb0 + g.rch, g.MB), np = g.steps / 2, M = g.M;
+                const Ident<DT> id(lane);
                 for (int rb = rb0 + ((wave - rb0) & (COLS_NW - 1)); rb < rb1; rb += COLS_NW) {
-                    const uint8_t *pa = sA + ((rb - rb0) * 32 + l32) * g.pa + lh * 16;
+                    const uint8_t *pa = smem + g.lds_a + ((rb - rb0) * 32 + l32) * g.pa + lh * 16;
                     SplitDot<DT> sdot;
                     Dot<DT> vdot;
                     const uint8_t *my_terms = split_b_lane<DT>(terms, L.KP, lane);
@@ -160,18 +167,27 @@ __global__ __launch_bounds__(COLS_NT, TPW == 1 && !STO ? 4 : 2) void item_cols_k
                     acc_t dot;
                     if constexpr (split_b<DT>()) dot = sdot.dot();
                     else dot = vdot.sum();
-                    if (lane < 32 && rb * 32 + lane < M) dot = dot_or_again<DT>(dot, as.src + (long)(rb * 32 + lane) * as.ldbytes, b_lds, K);
-                    if (lane < 32) rcpred[rb * 32 + lane] = as_word(dot);
+                    if (lane < 32 && rb * 32 + lane < M) dot = dot_or_again<DT>(dot, g.A + ((long)bz * g.sA + (long)(rb * 32 + lane) * g.lda) * ES, b_lds, g.K);
+                    if (lane < 32) vec[L.rcpred + rb * 32 + lane] = as_word(dot);
                 }
             }
+            {
             // One block of columns per wave: two blocks of rows at a time, two independent chains of MFMAs and
             // of what follows them.
+            const ItemArgs &g = item_args();
+            const ColsLds L(g, ES, STO, SHARED);
+            uint32_t *vec = reinterpret_cast<uint32_t *>(smem + g.lds_vec), *my_rs = vec + L.rspart + wave * L.RC;
+            const int rb0 = c * g.rch, rb1 = min(rb0 + g.rch, g.MB), np = g.steps / 2;
+            const bool shared = SHARED && shares_last_block(g.NB, g.N);
+            const int nb_first = shared && wave == g.NB ? g.NB - 1 : wave;
             const int half = ((rb1 - rb0 + 1) / 2 + R - 1) / R * R;         // a shared block: rows of its owner
+            // a lane's place in a block of rows of A, in a fragment of B and in a block of C
+            const uint8_t *pa_lane = smem + g.lds_a + l32 * g.pa + lh * 16;
+            const ItemOut co = item_out<DT>(g, bz, lane);
             for (int rb = rb0; rb < rb1; rb += R) {
-                const int lane = item_opaque(tid) & 63, l32 = lane & 31, lh = lane >> 5;
-                const Frag fb(smem, g.pb, lane);
+                const Frag fb(smem, g.pb, TRANSB ? lane : item_opaque(lane));        // (B stored K x N: no registers to keep it in)
                 const bool two = R == 2 && rb + 1 < rb1;
-                const uint8_t *pa0 = sA + ((rb - rb0) * 32 + l32) * g.pa + lh * 16;
+                const uint8_t *pa0 = pa_lane + (rb - rb0) * 32 * g.pa;
                 const uint8_t *pa1 = two ? pa0 + 32 * g.pa : pa0;
                 // Wide rows of C: the waves stay within a block of rows of each other, and the lines of C
                 // that two of them share are completed while the L2 holds them (int8 1024 x 577 x 577 x 64,
@@ -216,7 +232,7 @@ __global__ __launch_bounds__(COLS_NT, TPW == 1 && !STO ? 4 : 2) void item_cols_k
                                     uint32_t w[16];
 #pragma unroll
                                     for (int i = 0; i < 16; ++i) w[i] = (uint32_t)acc[r][i];
-                                    store_block<DT>(g, Cb, w, m0, n0, lane);
+                                    store_block<DT>(co, w, m0, n0, lane);
                                 } else {
                                     uint32_t w[8];
                                     pack_block<DT>(acc[r], w);
@@ -230,7 +246,7 @@ __global__ __launch_bounds__(COLS_NT, TPW == 1 && !STO ? 4 : 2) void item_cols_k
                                             cmax = fmaxf(cmax, fmaxf(fabsf(y0), fabsf(y1)));
                                         }
                                     }
-                                    store_block<DT>(g, Cb, w, m0, n0, lane);
+                                    store_block<DT>(co, w, m0, n0, lane);
                                 }
                             }
                         });
@@ -247,47 +263,71 @@ __global__ __launch_bounds__(COLS_NT, TPW == 1 && !STO ? 4 : 2) void item_cols_k
                     }
                 }
             }
-            if (PROT && c + 1 == g.nchunk) item_max_out<DT>(amax, as.src, as.ldbytes, M, K, lane, misc + wave);
-            item_barrier();
-            if (PROT) {
-                for (int r = tid; r < (rb1 - rb0) * 32; r += COLS_NT) {
-                    rcobs[rb0 * 32 + r] = as_word(sum_copies<acc_t>(vec + L.rspart + r, L.RC, COLS_NW));
-                    if (STO) vec[L.rcsto + rb0 * 32 + r] = __float_as_uint(sum_copies<float>(vec + L.rsspart + r, L.RC, COLS_NW));
+            }
+            if (PROT && !more) {
+                // what the last waves are waited for anyway: the largest |element| of A, the column sums of C over the lanes
+                const ItemArgs &g = item_args();
+                const ColsLds L(g, ES, STO, SHARED);
+                uint32_t *vec = reinterpret_cast<uint32_t *>(smem + g.lds_vec);
+                item_max_out<DT>(amax, g.A + (long)bz * g.sA * ES, g.lda * ES, g.M, g.K, lane, vec + L.misc + wave);
+                if (STO) {
+                    const float m = wave_max(cmax);
+                    if (lane == 0) vec[L.misc + 40 + wave] = __float_as_uint(m);
                 }
-            }
-            if (c + 1 < g.nchunk) {
-                stage_store(as, 0, COLS_NT, tid, sA, va);
-                item_barrier();
-            }
-        }
-        if (PROT) {
-            for (int k = tid; k < L.KP; k += COLS_NT) {
-                acc_t v = sum_copies<acc_t>(vec + L.apart + k, L.KP, ract);
-                if (k < K) v = finite_or_again<DT>(v, as.src + (long)k * ES, g.lda * ES, M);
-                a_lds[k] = as_word(v);
-            }
-            if (STO) {
-                const float m = wave_max(cmax);
-                if (lane == 0) misc[40 + wave] = __float_as_uint(m);
-            }
-            // column sums of C over the lanes
-            static_for<0, TPW>([&](auto t_c) {
-                constexpr int t = decltype(t_c)::value;
-                const int nb = wave + COLS_NW * t;
-                if (nb < g.NB + (shared ? 1 : 0)) {
-                    const acc_t v = fold16<acc_t>(cs[t], lane);
-                    if ((lane & 1) == 0) vec[L.ccobs + nb * 32 + fold16_column(lane)] = as_word(v);
-                    if (STO) {
-                        const float x = fold16<float>(cs_s[STO ? t : 0], lane);
-                        if ((lane & 1) == 0) vec[L.ccsto + nb * 32 + fold16_column(lane)] = __float_as_uint(x);
+                const int blocks = g.NB + (SHARED && shares_last_block(g.NB, g.N) ? 1 : 0);
+                static_for<0, TPW>([&](auto t_c) {
+                    constexpr int t = decltype(t_c)::value;
+                    const int nb = wave + COLS_NW * t;
+                    if (nb < blocks) {
+                        const acc_t v = fold16<acc_t>(cs[t], lane);
+                        if ((lane & 1) == 0) vec[L.ccobs + nb * 32 + fold16_column(lane)] = as_word(v);
+                        if (STO) {
+                            const float x = fold16<float>(cs_s[STO ? t : 0], lane);
+                            if ((lane & 1) == 0) vec[L.ccsto + nb * 32 + fold16_column(lane)] = __float_as_uint(x);
+                        }
                     }
-                }
-            });
+                });
+            }
             item_barrier();
+            const ItemArgs &g = item_args();
+            const ColsLds L(g, ES, STO, SHARED);
+            if (PROT) {
+                uint32_t *vec = reinterpret_cast<uint32_t *>(smem + g.lds_vec);
+                const int r0 = c * g.rch * 32, rows = min(g.rch, g.MB - c * g.rch) * 32;
+                for (int r = tid; r < rows; r += COLS_NT) {
+                    vec[L.rcobs + r0 + r] = as_word(sum_copies<acc_t>(vec + L.rspart + r, L.RC, COLS_NW));
+                    if (STO) vec[L.rcsto + r0 + r] = __float_as_uint(sum_copies<float>(vec + L.rsspart + r, L.RC, COLS_NW));
+                }
+            }
+            if (!more) break;
+            stage_store(a_stage(g, L, 0), 0, COLS_NT, tid, smem + g.lds_a, va);
+            item_barrier();
+        }
+        const bool last = bz + (int)gridDim.x >= item_args().batch;
+        if (PROT) {
+            {
+                const ItemArgs &g = item_args();
+                const ColsLds L(g, ES, STO, SHARED);
+                uint32_t *vec = reinterpret_cast<uint32_t *>(smem + g.lds_vec);
+                const int ract = g.MB < COLS_NW ? g.MB : COLS_NW;            // waves that have a share of the pass over A
+                // (by the last waves: the first ones add up the rows' sums)
+                for (int k = COLS_NT - 1 - tid; k < L.KP; k += COLS_NT) {
+                    acc_t v = sum_copies<acc_t>(vec + L.apart + k, L.KP, ract);
+                    if (k < g.K) v = finite_or_again<DT>(v, g.A + ((long)bz * g.sA + k) * ES, g.lda * ES, g.M);
+                    vec[L.a + k] = as_word(v);
+                }
+            }
+            item_barrier();
+            const ItemArgs &g = item_args();
+            const ColsLds L(g, ES, STO, SHARED);
+            uint32_t *vec = reinterpret_cast<uint32_t *>(smem + g.lds_vec), *misc = vec + L.misc, *a_lds = vec + L.a;
+            const int N = g.N;
+            const bool shared = SHARED && shares_last_block(g.NB, N);
+            const Frag fb(smem, g.pb, lane);
             const ItemTol tt = item_tolerance<DT>(g, misc, COLS_NW, bz);
             const float tol_c = g.tau_override_cols > 0.f ? g.tau_override_cols : tt.tol;
-            // a B from the resident B
-            for (int nb = wave; nb < g.NB; nb += COLS_NW) {
+            // a B from the resident B (the last waves first: the first ones have the rows)
+            for (int nb = COLS_NW - 1 - wave; nb < g.NB; nb += COLS_NW) {
                 Dot<DT> vdot;
                 for (int s = 0; s < g.steps; ++s) vdot.add(fb.get(nb, fb.at(s)), a_lds + s * (32 / ES) + lh * (16 / ES));
                 const acc_t d = vdot.sum();
@@ -306,14 +346,17 @@ __global__ __launch_bounds__(COLS_NT, TPW == 1 && !STO ? 4 : 2) void item_cols_k
                 }
                 nc_w += __popcll(__ballot(fl));
             }
-            nr_w += item_rows_out<DT>(g, bz, COLS_NT, tid, rcobs, rcpred, STO ? vec + L.rcsto : nullptr, a_lds, b_lds, tt.tol,
+            nr_w += item_rows_out<DT>(g, bz, COLS_NT, tid, vec + L.rcobs, vec + L.rcpred, STO ? vec + L.rcsto : nullptr, a_lds, vec + L.b, tt.tol,
                                       misc + 16 + wave);
+            if (last && lane == 0) { misc[24 + wave] = nr_w; misc[24 + COLS_NW + wave] = nc_w; }
             item_barrier();
-            if (tid == 0) item_scalars_out<DT, STO>(g, bz, misc, COLS_NW, tt);
+            // (past this barrier only these scalars' words are read: the next item may begin)
+            if (tid == 64) item_scalars_out<DT, STO>(g, bz, misc, COLS_NW, tt);
+            if (last && tid == 0) item_ticket(g, misc + 24, COLS_NW);
         }
-        item_barrier();                          // LDS is reused by the next item
+        // (unprotected: the barrier behind the last chunk is the one before the next item's first store)
+        if (last) return;
     }
-    if (PROT) item_ticket(g, vec + L.misc + 24, COLS_NW, nr_w, nc_w);
 }
 
 // ------------------------------------------------------------------------------------------

@@ -47,7 +47,7 @@ struct RowsLds {
 };
 
 template <int DT, int TPW, bool PROT, bool TRANSB, bool STO>
-__global__ __launch_bounds__(512, TPW == 2 && !STO ? 4 : 2) void item_rows_kernel(ItemArgs g)
+__global__ __launch_bounds__(512, TPW == 2 && !STO ? 4 : 2) void item_rows_kernel(ItemArgs)
 {
     using T = Traits<DT>;
     typedef typename T::acc_t acc_t;
@@ -56,31 +56,21 @@ __global__ __launch_bounds__(512, TPW == 2 && !STO ? 4 : 2) void item_rows_kerne
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
     const int lane_id = threadIdx.x & 63, nt = blockDim.x, nw = nt >> 6;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int M = g.M, N = g.N, K = g.K, MB = g.MB, np = g.steps / 2;
-    const int kbytes = K * ES;
-    const RowsLds L(g, ES, nw, STO);
-    uint32_t *vec = reinterpret_cast<uint32_t *>(smem + g.lds_vec);
-    uint32_t *a_lds = vec + L.a, *b_lds = vec + L.b, *rcobs = vec + L.rcobs, *rcpred = vec + L.rcpred,
-             *ccpred = vec + L.ccpred, *misc = vec + L.misc, *my_a = vec + L.apart + wave * L.KP, *my_cs = vec + L.cspart + wave * L.Nr;
-    uint8_t *terms = reinterpret_cast<uint8_t *>(vec + L.terms);
     typedef FragB<DT, TRANSB, rows_kn_pitch(ES, TPW)> Frag;
-    const int wact = MB < nw ? MB : nw;          // waves that have rows
     unsigned nr_w = 0, nc_w = 0;
 
-    for (int bz = blockIdx.x; bz < g.batch; bz += gridDim.x) {
+    for (int bz = blockIdx.x;; bz += gridDim.x) {
         const int tid = item_opaque(threadIdx.x), lane = tid & 63, l32 = lane & 31, lh = lane >> 5;
-        const Frag fb(smem, g.pb, lane);
-        const Ident<DT> id(lane);
-        const uint8_t *Ab = g.A + (long)bz * g.sA * ES;
-        uint8_t *Cb = g.C + (long)bz * g.sC * OS;
+        const uint8_t *Ab;
+        long lda_bytes;
+        int M, MB, last_ch;
         i32x4 fa[ROWS_RING][2];
         // piece p of a row block: rows past M and chunks past K fetch the last valid ones, cleared below
-        const uint8_t *arow = Ab;
-        int last_ch = g.nch - 1;
+        const uint8_t *arow;
         auto row_of = [&](int rb) __attribute__((always_inline)) {
             int r = rb * 32 + l32;
             r = r < M ? r : M - 1;
-            arow = Ab + (long)r * g.lda * ES;
+            arow = Ab + (long)r * lda_bytes;
         };
         auto fetch = [&](int p, i32x4 (&f)[2]) __attribute__((always_inline)) {
 #pragma unroll
@@ -92,29 +82,43 @@ __global__ __launch_bounds__(512, TPW == 2 && !STO ? 4 : 2) void item_rows_kerne
                 f[u] = *reinterpret_cast<const i32x4 *>(arow + ch * 16);
             }
         };
-        if (wave < MB) {
-            row_of(wave);
-            static_for<0, ROWS_RING>([&](auto j_c) { fetch(decltype(j_c)::value, fa[decltype(j_c)::value]); });
-        }
-        const ItemStage bs = b_stage<DT, TRANSB>(g, bz);
         {
+            const ItemArgs &g = item_args();
+            Ab = g.A + (long)bz * g.sA * ES;
+            lda_bytes = g.lda * ES;
+            M = g.M; MB = g.MB; last_ch = g.nch - 1;
+            arow = Ab;
+            if (wave < MB) {
+                row_of(wave);
+                static_for<0, ROWS_RING>([&](auto j_c) { fetch(decltype(j_c)::value, fa[decltype(j_c)::value]); });
+            }
+            const RowsLds L(g, ES, nw, STO);
+            uint32_t *vec = reinterpret_cast<uint32_t *>(smem + g.lds_vec);
+            const ItemStage bs = b_stage<DT, TRANSB>(g, bz);
             i32x4 v[ITEM_U];
             stage_load(bs, 0, nt, tid, v);
             if (PROT) {
                 for (int k = tid; k < nw * L.KP; k += nt) vec[L.apart + k] = 0u;
-                for (int n = tid; n < L.Nr; n += nt) ccpred[n] = 0u;
+                for (int n = tid; n < L.Nr; n += nt) vec[L.ccpred + n] = 0u;
             }
             stage_store(bs, 0, nt, tid, smem, v);
             stage_rest(bs, stage_batch_rows(bs, nt), nt, tid, smem);
         }
         item_barrier();
         if (PROT) {
+            const ItemArgs &g = item_args();
+            const RowsLds L(g, ES, nw, STO);
+            uint32_t *vec = reinterpret_cast<uint32_t *>(smem + g.lds_vec);
+            uint8_t *terms = reinterpret_cast<uint8_t *>(vec + L.terms);
             uint32_t bmax = 0;
             if (g.cached_b) {
-                b_cached<DT>(g, bz, b_lds, terms, L.KP, tid, nt);
+                b_cached<DT>(g, bz, vec + L.b, terms, L.KP, tid, nt);
             } else {
-                b_pass<DT>(g, fb, id, b_lds, terms, L.KP, bs.src, TRANSB ? ES : bs.ldbytes, TRANSB ? bs.ldbytes : ES, wave, nw, lane, &bmax);
-                item_max_out<DT>(bmax, bs.src, bs.ldbytes, bs.rows, bs.rowbytes / ES, lane, misc + 8 + wave);
+                const Frag fb(smem, g.pb, lane);
+                const uint8_t *Bb = g.B + (long)bz * g.sB * ES;
+                const long ldb_bytes = g.ldb * ES;
+                b_pass<DT>(g, fb, Ident<DT>(lane), vec + L.b, terms, L.KP, Bb, TRANSB ? ES : ldb_bytes, TRANSB ? ldb_bytes : ES, wave, nw, lane, &bmax);
+                item_max_out<DT>(bmax, Bb, ldb_bytes, TRANSB ? g.N : g.K, TRANSB ? g.K : g.N, lane, vec + L.misc + 8 + wave);
             }
             item_barrier();
         }
@@ -124,7 +128,13 @@ __global__ __launch_bounds__(512, TPW == 2 && !STO ? 4 : 2) void item_rows_kerne
         float csum_s[STO ? TPW : 1], cmax = 0.f;
 #pragma unroll
         for (int t = 0; t < TPW; ++t) { csum[t] = T::zero(); csum_s[STO ? t : 0] = 0.f; }
+        const Ident<DT> id(lane);
         for (int rb = wave; rb < MB; rb += nw) {
+            const ItemArgs &g = item_args();
+            const RowsLds L(g, ES, nw, STO);
+            uint32_t *vec = reinterpret_cast<uint32_t *>(smem + g.lds_vec), *my_a = vec + L.apart + wave * L.KP, *b_lds = vec + L.b;
+            uint8_t *terms = reinterpret_cast<uint8_t *>(vec + L.terms);
+            const int np = g.steps / 2, kbytes = g.K * ES;
             const int lane = item_opaque(lane_id), l32 = lane & 31, lh = lane >> 5;
             const Frag fb(smem, g.pb, lane);
             const int m0 = rb * 32;
@@ -197,6 +207,7 @@ __global__ __launch_bounds__(512, TPW == 2 && !STO ? 4 : 2) void item_rows_kerne
                 }
             }
             // ---- the block row leaves
+            const ItemOut co = item_out<DT>(g, bz, lane);
             acc_t rs = T::zero();
             float rs_s = 0.f;
             static_for<0, TPW>([&](auto t_c) {
@@ -211,7 +222,7 @@ __global__ __launch_bounds__(512, TPW == 2 && !STO ? 4 : 2) void item_rows_kerne
                         uint32_t w[16];
 #pragma unroll
                         for (int i = 0; i < 16; ++i) w[i] = (uint32_t)acc[t][i];
-                        store_block<DT>(g, Cb, w, m0, t * 32, lane);
+                        store_block<DT>(co, w, m0, t * 32, lane);
                     } else {
                         uint32_t w[8];
                         pack_block<DT>(acc[t], w);
@@ -224,7 +235,7 @@ __global__ __launch_bounds__(512, TPW == 2 && !STO ? 4 : 2) void item_rows_kerne
                             rs_s += sum16<float>(sv);
                             csum_s[t] += fold16<float>(sv, lane);
                         }
-                        store_block<DT>(g, Cb, w, m0, t * 32, lane);
+                        store_block<DT>(co, w, m0, t * 32, lane);
                     }
                 }
             });
@@ -233,38 +244,56 @@ __global__ __launch_bounds__(512, TPW == 2 && !STO ? 4 : 2) void item_rows_kerne
                 acc_t dot;
                 if constexpr (split_b<DT>()) dot = sdot.dot();
                 else dot = vdot.sum();
-                if (lane < 32 && m0 + lane < M) dot = dot_or_again<DT>(dot, Ab + (long)(m0 + lane) * g.lda * ES, b_lds, K);
+                if (lane < 32 && m0 + lane < M) dot = dot_or_again<DT>(dot, Ab + (long)(m0 + lane) * lda_bytes, b_lds, g.K);
                 if (STO) rs_s = add_xor32(rs_s);
                 if (lane < 32) {
-                    rcobs[m0 + lane] = as_word(rsum);
-                    rcpred[m0 + lane] = as_word(dot);
+                    vec[L.rcobs + m0 + lane] = as_word(rsum);
+                    vec[L.rcpred + m0 + lane] = as_word(dot);
                     if (STO) vec[L.rcsto + m0 + lane] = __float_as_uint(rs_s);
                 }
             }
         }
+        const bool last = bz + (int)gridDim.x >= item_args().batch;
         if (PROT) {
-            if ((lane & 1) == 0) {
+            {
+                const ItemArgs &g = item_args();
+                const RowsLds L(g, ES, nw, STO);
+                uint32_t *vec = reinterpret_cast<uint32_t *>(smem + g.lds_vec), *misc = vec + L.misc, *my_cs = vec + L.cspart + wave * L.Nr;
+                if ((lane & 1) == 0) {
 #pragma unroll
-                for (int t = 0; t < TPW; ++t)
-                    if (t < g.NB) {
-                        my_cs[t * 32 + fold16_column(lane)] = as_word(csum[t]);
-                        if (STO) vec[L.csspart + wave * L.Nr + t * 32 + fold16_column(lane)] = __float_as_uint(csum_s[t]);
-                    }
-            }
-            item_max_out<DT>(amax, Ab, g.lda * ES, M, K, lane, misc + wave);
-            if (STO) {
-                const float m = wave_max(cmax);
-                if (lane == 0) misc[40 + wave] = __float_as_uint(m);
-            }
-            item_barrier();
-            for (int k = tid; k < L.KP; k += nt) {
-                acc_t v = sum_copies<acc_t>(vec + L.apart + k, L.KP, wact);
-                if (k < K) v = finite_or_again<DT>(v, Ab + (long)k * ES, g.lda * ES, M);
-                a_lds[k] = as_word(v);
+                    for (int t = 0; t < TPW; ++t)
+                        if (t < g.NB) {
+                            my_cs[t * 32 + fold16_column(lane)] = as_word(csum[t]);
+                            if (STO) vec[L.csspart + wave * L.Nr + t * 32 + fold16_column(lane)] = __float_as_uint(csum_s[t]);
+                        }
+                }
+                item_max_out<DT>(amax, Ab, lda_bytes, M, g.K, lane, misc + wave);
+                if (STO) {
+                    const float m = wave_max(cmax);
+                    if (lane == 0) misc[40 + wave] = __float_as_uint(m);
+                }
             }
             item_barrier();
+            const int wact = MB < nw ? MB : nw;  // waves that have rows
+            {
+                const ItemArgs &g = item_args();
+                const RowsLds L(g, ES, nw, STO);
+                uint32_t *vec = reinterpret_cast<uint32_t *>(smem + g.lds_vec);
+                const int K = g.K;
+                for (int k = tid; k < L.KP; k += nt) {
+                    acc_t v = sum_copies<acc_t>(vec + L.apart + k, L.KP, wact);
+                    if (k < K) v = finite_or_again<DT>(v, Ab + (long)k * ES, lda_bytes, M);
+                    vec[L.a + k] = as_word(v);
+                }
+            }
+            item_barrier();
+            const ItemArgs &g = item_args();
+            const RowsLds L(g, ES, nw, STO);
+            uint32_t *vec = reinterpret_cast<uint32_t *>(smem + g.lds_vec), *misc = vec + L.misc, *ccpred = vec + L.ccpred, *a_lds = vec + L.a;
+            const int N = g.N;
             // ---- a B from the resident B: a wave takes every nw-th step of K
             {
+                const Frag fb(smem, g.pb, lane);
                 Dot<DT> d[TPW];
                 for (int s = wave; s < g.steps; s += nw) {
                     const int at = fb.at(s);
@@ -281,7 +310,7 @@ __global__ __launch_bounds__(512, TPW == 2 && !STO ? 4 : 2) void item_rows_kerne
                 }
             }
             const ItemTol tt = item_tolerance<DT>(g, misc, nw, bz);
-            nr_w += item_rows_out<DT>(g, bz, nt, tid, rcobs, rcpred, STO ? vec + L.rcsto : nullptr, a_lds, b_lds, tt.tol, misc + 16 + wave);
+            nr_w += item_rows_out<DT>(g, bz, nt, tid, vec + L.rcobs, vec + L.rcpred, STO ? vec + L.rcsto : nullptr, a_lds, vec + L.b, tt.tol, misc + 16 + wave);
             item_barrier();
             if (tid < L.Nr) {
                 bool fl = false;
@@ -297,11 +326,16 @@ __global__ __launch_bounds__(512, TPW == 2 && !STO ? 4 : 2) void item_rows_kerne
                 }
                 nc_w += __popcll(__ballot(fl));
             }
-            if (tid == 0) item_scalars_out<DT, STO>(g, bz, misc, nw, tt);
+            if (last && lane == 0) { misc[24 + wave] = nr_w; misc[24 + nw + wave] = nc_w; }
+            item_barrier();
+            // (past this barrier only these scalars' words are read: the next item may begin)
+            if (tid == 64) item_scalars_out<DT, STO>(g, bz, misc, nw, tt);
+            if (last && tid == 0) item_ticket(g, misc + 24, nw);
+        } else {
+            item_barrier();                      // LDS is reused by the next item
         }
-        item_barrier();                          // LDS is reused by the next item
+        if (last) return;
     }
-    if (PROT) item_ticket(g, vec + L.misc + 24, nw, nr_w, nc_w);
 }
 
 // ------------------------------------------------------------------------------------------
