@@ -54,4 +54,14 @@ bool gemm_fast_eligible(int dt, int M, int N, int K, bool transB, long lda, long
 hipError_t launch_gemm_fast(int dt, bool protect, GemmArgs &g, int batch, hipStream_t st);
 void gemm_fast_tile(int *tm, int *tn);
 
+// A kernel's arguments (its first parameter), read from where the launch put them: each phase of a tile or item takes its own.  Taken from
+// the parameter, every argument and every offset, pitch and condition that follows from them is formed ahead of the loop over tiles
+// or items and held across it: too many scalars, which go to lanes of vector registers and come back one by one.
+template <typename ARGS> __device__ __forceinline__ const ARGS &kernel_args()
+{
+    const __attribute__((address_space(4))) ARGS *p = (const __attribute__((address_space(4))) ARGS *)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return *(const ARGS *)p;
+}
+
 }  // namespace abft

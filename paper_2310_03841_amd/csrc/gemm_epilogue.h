@@ -216,10 +216,10 @@ __device__ __forceinline__ void stored_mfmas(typename Acc4<DT>::type &c, typenam
 }
 
 template <int DT, int BM, bool PROT, int STO, bool BIAS>
-__device__ __forceinline__ void gemm_epilogue_impl(const GemmArgs &g,
-                                              typename Traits<DT>::accv_t (&acc)[BM / 64][2],
+__device__ __forceinline__ void gemm_epilogue_impl(const GemmArgs &tile, typename Traits<DT>::accv_t (&acc)[BM / 64][2],
                                               uint8_t *smem, int m0, int n0, int bz, const EpiProt<DT, BM / 64> &ep)
 {
+    const GemmArgs &g = PROT ? kernel_args<GemmArgs>() : tile;
     using T = Traits<DT>;
     typedef typename T::acc_t acc_t;
     constexpr int BN = 256, THREADS = 64 * FAST_WAVES;
@@ -548,6 +548,8 @@ __device__ __forceinline__ void gemm_epilogue_impl(const GemmArgs &g,
         // Barrier over LDS traffic only: the partial sums meet in LDS, and a full barrier would
         // also wait until every store of C issued above has been acknowledged.
         asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        const GemmArgs &g = kernel_args<GemmArgs>();
+        const int M = g.M, N = g.N;
         uint32_t amax = 0u;
         if (!T::IS_INT && ep.owned > 0) {
 #pragma unroll

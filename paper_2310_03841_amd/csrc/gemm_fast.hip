@@ -374,26 +374,27 @@ __device__ __forceinline__ void fast_tile(const GemmArgs &g, uint8_t *smem, int 
 // through (choose_big_rows).  (600 big tiles on 256 CUs would be three rounds for 2.34 rounds
 // of work.)
 template <int DT, int MODE, int STO>
-__global__ __launch_bounds__(64 * FAST_WAVES) void gemm_fast_kernel(GemmArgs g)
+__global__ __launch_bounds__(64 * FAST_WAVES) void gemm_fast_kernel(GemmArgs whole)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
     constexpr bool PROT = MODE != FAST_PLAIN;
-    if (PROT && blockIdx.x == 0 && threadIdx.x < 5) g.counts[threadIdx.x] = 0u;      // completed by the check kernel
     // Persistent workgroups: one per compute unit, each walks the tile list with the grid's stride.
     // The 128-row tiles come first in the list: the compute units that start with one are half a
     // tile ahead of the others from then on, so the two groups store their tiles of C at different
     // times (a round of the machine that stores in step asks for tens of MB at once) and draw on
     // the matrix pipes at different times.  Measured on 12608 x 3072 x 768 (tiles by four waves): 63 -> 60.5 us.
-    const int per_item = g.n_small + g.n_big;
-    const int total = per_item * g.batch;
-    const int n_tile = MODE == FAST_BESIDE ? (int)gridDim.x - g.beside.n : (int)gridDim.x;
-    if constexpr (MODE == FAST_BESIDE) {
-        if ((int)blockIdx.x >= n_tile) {
-            a_beside<DT>(g, (int)blockIdx.x - n_tile, smem);
-            return;
+    for (int t = blockIdx.x;;) {
+        // (unprotected, there are scalars enough for all of a launch, and one trip to them is less)
+        const GemmArgs &g = PROT ? kernel_args<GemmArgs>() : whole;
+        if (PROT && t == 0 && threadIdx.x < 5) g.counts[threadIdx.x] = 0u;               // completed by the check kernel
+        const int n_tile = MODE == FAST_BESIDE ? (int)gridDim.x - g.beside.n : (int)gridDim.x;
+        if constexpr (MODE == FAST_BESIDE) {
+            if ((int)blockIdx.x >= n_tile) {
+                a_beside<DT>(g, (int)blockIdx.x - n_tile, smem);
+                return;
+            }
         }
-    }
-    for (int t = blockIdx.x; t < total; t += n_tile) {
+        const int per_item = g.n_small + g.n_big;
         const int bz = t / per_item, bid = t - bz * per_item;
         int tm, tn;
         if (STO != STO_128 && bid >= g.n_small) {
@@ -403,6 +404,8 @@ __global__ __launch_bounds__(64 * FAST_WAVES) void gemm_fast_kernel(GemmArgs g)
             map_tile(bid, g.n_small, g.tiles_m_small, g.tiles_n, &tm, &tn);
             fast_tile<DT, 128, MODE, STO>(g, smem, g.tiles_m_big * 256 + tm * 128, tn * 256, bz, tn);
         }
+        t += n_tile;
+        if (t >= per_item * g.batch) break;
         // the epilogue's last reads of LDS precede the next tile's first writes
         asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
     }

@@ -53,15 +53,8 @@ struct ItemArgs {
     uint32_t *c_max;                              // max|C as stored| as float bits, with the stored-side sums
 };
 
-// The arguments, read from where the launch put them: each phase of an item takes its own.  Taken from the parameter, every argument and
-// every offset, pitch and condition that follows from them is formed ahead of the loop over items and held across it: 200 to 290
-// scalars too many, which go to lanes of vector registers and come back one by one (some 500 of a kernel's 3400 instructions).
-__device__ __forceinline__ const ItemArgs &item_args()
-{
-    const __attribute__((address_space(4))) ItemArgs *p = (const __attribute__((address_space(4))) ItemArgs *)__builtin_amdgcn_kernarg_segment_ptr();
-    asm volatile("" : "+s"(p));
-    return *(const ItemArgs *)p;
-}
+// (An item kernel with its arguments taken from the parameter had 200 to 290 scalars in vector registers and 500 of its 3400 instructions to move them.)
+__device__ __forceinline__ const ItemArgs &item_args() { return kernel_args<ItemArgs>(); }
 
 // Workgroup barrier over LDS traffic only: a full barrier would also wait until every store of C
 // issued so far has been acknowledged.
