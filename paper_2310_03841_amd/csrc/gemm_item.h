@@ -334,13 +334,18 @@ template <int DT> struct Turned {
 };
 // The share of a = e^T A of 32 positions from k0 on, added to the wave's copy.  (Read, add, write: the copy
 // is the wave's own, and an LDS atomic would hold its next reads back.  Both halves of the wave hold
-// the totals and write them.)
-template <int DT> __device__ __forceinline__ void a_sums(const Turned<DT> &t, uint32_t *copy, int k0, int lane)
+// the totals and write them.)  ATOMIC: a copy that several waves add to; integers only, so that their order does not show.
+template <int DT, bool ATOMIC = false> __device__ __forceinline__ void a_sums(const Turned<DT> &t, uint32_t *copy, int k0, int lane)
 {
     typedef typename Traits<DT>::acc_t acc_t;
     uint32_t *c = copy + k0 + (lane & 31);
-    const acc_t old = from_word<acc_t>(*c);
-    *c = as_word(add_t(old, t.sum()));
+    const acc_t v = t.sum();
+    if constexpr (ATOMIC) {
+        if (lane < 32) lds_add_word(c, v);
+    } else {
+        const acc_t old = from_word<acc_t>(*c);
+        *c = as_word(add_t(old, v));
+    }
 }
 
 template <int DT> __device__ __forceinline__ constexpr bool split_b() { return DT != DT_F16; }

@@ -21,6 +21,10 @@ namespace abft {
 // pitch of a B stored K x N: an odd number of 32-byte (int8: 16-byte) pieces
 __host__ __device__ constexpr int rows_kn_pitch(int es, int tpw) { return es == 2 ? tpw * 64 + 32 : tpw * 32 + 16; }
 
+// Copies of a = e^T A that the waves add to: one each, so that the order of additions is fixed; of integers two for all, which leaves
+// deep items the LDS for a second workgroup on the compute unit (577 x 64 x 577: 87 KB with eight copies, 71 so).
+__host__ __device__ constexpr int rows_a_copies(int es, int nw) { return es == 1 ? 2 : nw; }
+
 constexpr int ROWS_RING = 4;                     // pieces of two steps of A a wave keeps in flight
 
 // Offsets (words) of the vectors behind B.
@@ -34,7 +38,7 @@ struct RowsLds {
         a = o; o += KP;
         b = o; o += KP;
         terms = o; o += KP * es;                 // [4][KP] elements
-        apart = o; o += nw * KP;
+        apart = o; o += rows_a_copies(es, nw) * KP;
         rcobs = o; o += Mr;
         rcpred = o; o += Mr;
         cspart = o; o += nw * Nr;
@@ -98,7 +102,7 @@ __global__ __launch_bounds__(512, TPW == 2 && !STO ? 4 : 2) void item_rows_kerne
             i32x4 v[ITEM_U];
             stage_load(bs, 0, nt, tid, v);
             if (PROT) {
-                for (int k = tid; k < nw * L.KP; k += nt) vec[L.apart + k] = 0u;
+                for (int k = tid; k < rows_a_copies(ES, nw) * L.KP; k += nt) vec[L.apart + k] = 0u;
                 for (int n = tid; n < L.Nr; n += nt) vec[L.ccpred + n] = 0u;
             }
             stage_store(bs, 0, nt, tid, smem, v);
@@ -132,7 +136,7 @@ __global__ __launch_bounds__(512, TPW == 2 && !STO ? 4 : 2) void item_rows_kerne
         for (int rb = wave; rb < MB; rb += nw) {
             const ItemArgs &g = item_args();
             const RowsLds L(g, ES, nw, STO);
-            uint32_t *vec = reinterpret_cast<uint32_t *>(smem + g.lds_vec), *my_a = vec + L.apart + wave * L.KP, *b_lds = vec + L.b;
+            uint32_t *vec = reinterpret_cast<uint32_t *>(smem + g.lds_vec), *my_a = vec + L.apart + (T::IS_INT ? wave & 1 : wave) * L.KP, *b_lds = vec + L.b;
             uint8_t *terms = reinterpret_cast<uint8_t *>(vec + L.terms);
             const int np = g.steps / 2, kbytes = g.K * ES;
             const int lane = item_opaque(lane_id), l32 = lane & 31, lh = lane >> 5;
@@ -191,11 +195,11 @@ __global__ __launch_bounds__(512, TPW == 2 && !STO ? 4 : 2) void item_rows_kerne
 #pragma unroll
                             for (int t = 0; t < TPW; ++t) acc[t] = T::mfma(bf[u][t], x[u], acc[t]);
                         if (PROT) {
-                            a_sums<DT>(turned, my_a, T::IS_INT ? s * 32 : s * 16, lane);
+                            a_sums<DT, T::IS_INT>(turned, my_a, T::IS_INT ? s * 32 : s * 16, lane);
                             if constexpr (T::IS_INT) {
                                 Turned<DT> next;
                                 next.add(x[1], x[1], id);
-                                a_sums<DT>(next, my_a, s * 32 + 32, lane);
+                                a_sums<DT, T::IS_INT>(next, my_a, s * 32 + 32, lane);
                             }
                         }
                     }
@@ -281,7 +285,7 @@ __global__ __launch_bounds__(512, TPW == 2 && !STO ? 4 : 2) void item_rows_kerne
                 uint32_t *vec = reinterpret_cast<uint32_t *>(smem + g.lds_vec);
                 const int K = g.K;
                 for (int k = tid; k < L.KP; k += nt) {
-                    acc_t v = sum_copies<acc_t>(vec + L.apart + k, L.KP, wact);
+                    acc_t v = sum_copies<acc_t>(vec + L.apart + k, L.KP, T::IS_INT ? 2 : wact);
                     if (k < K) v = finite_or_again<DT>(v, Ab + (long)k * ES, lda_bytes, M);
                     vec[L.a + k] = as_word(v);
                 }
