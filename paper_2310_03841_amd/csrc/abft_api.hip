@@ -729,7 +729,7 @@ extern "C" int abft_correct(abft_ctx *ctx, const void *A, const void *B, void *C
         ctx->list_dirty = true;
         ctx->vobs_valid = false;
         HIP_TRY(launch_correct(dtype, A, B, C, sh, w, v, ctx->sto_valid, clear_list, true, 0, nullptr, 0, st));
-        ctx->list_dirty = false;
+        ctx->list_dirty = correct_finds(sh);
         ctx->vobs_valid = true;
         return ABFT_OK;
     }

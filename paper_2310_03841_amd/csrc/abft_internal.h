@@ -137,7 +137,7 @@ hipError_t launch_check(int dt, bool after_fast, bool rc_ready, const void *A, c
 // zero_ptr / zero_words: a region every block of the kernel helps to clear (may be null / 0)
 // gated: the kernel does nothing when the tile list of the correction before it is empty
 hipError_t launch_compare(int dt, const Shape &s, const Workspace &w, const Verdict &v, bool after_fix,
-                          bool with_sto, uint32_t *zero_ptr, size_t zero_words, hipStream_t st, bool gated = false);
+                          bool with_sto, uint32_t *zero_ptr, size_t zero_words, hipStream_t st, bool gated = false, bool counts_ready = false);
 // counts: cleared for the compare that follows (null: that of a correction, which writes them all itself)
 hipError_t launch_verify_sums(int dt, const void *C, const Shape &s, const Workspace &w, uint32_t *counts, hipStream_t st,
                               bool gated = false);
@@ -149,6 +149,8 @@ hipError_t launch_verify_sums(int dt, const void *C, const Shape &s, const Works
 // of stored C and the final compare do nothing: flags and counts stay as that check wrote them
 // clear_list: the tile list's counters may be non-zero (the final compare of a correction leaves
 // them at zero, so only after a call that failed half way)
+// Whether a correction leaves its list of tiles behind: whatever lists tiles next clears it first.
+bool correct_finds(const Shape &s);
 hipError_t launch_correct(int dt, const void *A, const void *B, void *C, const Shape &s,
                           const Workspace &w, const Verdict &v, bool with_sto, bool clear_list, bool targeted,
                           size_t stale_words, uint32_t *zero_ptr, size_t zero_words, hipStream_t st,

@@ -143,15 +143,17 @@ int protect_max_k(int dt) { (void)dt; return 4096; }
 // waves at least one sees both; "localised" goes in whatever is there, "suspect" only replaces "clean".
 // (With every wave looking and writing, a bf16 12608 x 3072 x 768 whose every row and column flags took 137 us;
 // so 84, and 78 clean: atomics on one line are served one after the other.)
-__device__ __forceinline__ void report_flags(uint32_t *counts, int side, unsigned n)
+// fix_count: after a correction (counts[4] is the status before it; counts[2] stays where the list was too long).
+__device__ __forceinline__ void report_flags(uint32_t *counts, int side, unsigned n, const uint32_t *fix_count = nullptr)
 {
     if (atomicAdd(counts + side, n) != 0u) return;
+    if (fix_count && fix_count[1]) return;
     if (atomicAdd(counts + (side ^ 1), 0u) != 0u) {
         atomicExch(counts + 2, 1u);
-        atomicExch(counts + 4, 1u);
+        if (!fix_count) atomicExch(counts + 4, 1u);
     } else {
         atomicCAS(counts + 2, 0u, 2u);
-        atomicCAS(counts + 4, 0u, 2u);
+        if (!fix_count) atomicCAS(counts + 4, 0u, 2u);
     }
 }
 
@@ -176,6 +178,7 @@ struct CmpArgs {
     int M, N, batch;
     const uint32_t *gate; // non-null: if *gate == 0 (no tile was listed for recomputation) the kernel
                           // leaves flags and counts as the check before it wrote them
+    int counts_ready;     // after a correction: resum_touched_kernel has written counts, the list is not cleared
 };
 
 template <bool IS_INT>
@@ -222,14 +225,14 @@ __global__ __launch_bounds__(256) void compare_kernel(CmpArgs a)
             fcol = fcol || mismatch<false>(a.cc_obs[(long)bz * N + j], a.cc_sto[(long)bz * N + j], STO_TOL_FACTOR * tol_c);
         a.col_flag[(long)bz * N + j] = fcol ? 1 : 0;
     }
-    if (!a.fix_count) {
+    if (!a.fix_count || a.counts_ready) {
         // the pass over stored C has cleared the counts: only waves that saw a mismatch touch them.  (A ticket per block and
         // a last block that publishes are two trips to memory more: int8 6304 x 768 x 3072, flip, verify and repair
         // 33.7 -> 32.8 us; bf16 6304 x 3072 x 768 with stored sums and verify 80.0 -> 77.1.)
         const unsigned wr = __popcll(__ballot(frow)), wc = __popcll(__ballot(fcol));
         if ((tid & 63) == 0) {
-            if (wr) report_flags(a.counts, 0, wr);
-            if (wc) report_flags(a.counts, 1, wc);
+            if (wr) report_flags(a.counts, 0, wr, a.fix_count);
+            if (wc) report_flags(a.counts, 1, wc, a.fix_count);
         }
         return;
     }
@@ -264,9 +267,10 @@ __global__ __launch_bounds__(256) void compare_kernel(CmpArgs a)
 }
 
 hipError_t launch_compare(int dt, const Shape &s, const Workspace &w, const Verdict &v, bool after_fix,
-                          bool with_sto, uint32_t *zero_ptr, size_t zero_words, hipStream_t st, bool gated)
+                          bool with_sto, uint32_t *zero_ptr, size_t zero_words, hipStream_t st, bool gated, bool counts_ready)
 {
     CmpArgs a;
+    a.counts_ready = counts_ready ? 1 : 0;
     a.gate = gated ? w.fix_count : nullptr;
     a.zero_ptr = zero_ptr; a.zero_words = zero_ptr ? zero_words : 0;
     a.cc_sto = (with_sto && dt != DT_I8) ? w.cc_sto : nullptr;
@@ -789,38 +793,43 @@ struct LocArgs {
 
 constexpr int LOC_THREADS = 1024;
 
-// Appends the CT-tile index of every non-zero byte of flag[0..n) to list (at most MAX_LIST kept;
-// *count keeps counting).  Sixteen flags per load where the address allows: flags are almost
+// note(i) for every non-zero byte i of flag[0..n), by NT threads.  Sixteen flags per load where the address allows: flags are almost
 // all zero, and the scan is bound by the latency of its loads.
-__device__ inline void list_flagged(const uint8_t *flag, int n, int *list, int *count, int tid)
+template <int NT, typename NOTE> __device__ __forceinline__ void scan_flags(const uint8_t *flag, int n, int tid, NOTE &&note)
 {
-    auto note = [&](int i) {
-        int p = atomicAdd(count, 1);
-        if (p < MAX_LIST) list[p] = i / CT;
-    };
     const int head = min(n, (int)((16u - (unsigned)((uintptr_t)flag & 15u)) & 15u));
     const int nchunk = (n - head) / 16;
     const int tail0 = head + nchunk * 16;
     if (tid < head && flag[tid]) note(tid);
     if (tid < n - tail0 && flag[tail0 + tid]) note(tail0 + tid);
     const i32x4 *body = reinterpret_cast<const i32x4 *>(flag + head);
-    for (int c0 = 0; c0 < nchunk; c0 += 4 * LOC_THREADS) {
+    for (int c0 = 0; c0 < nchunk; c0 += 4 * NT) {
         i32x4 v[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            const int c = c0 + u * LOC_THREADS + tid;
+            const int c = c0 + u * NT + tid;
             v[u] = i32x4{0, 0, 0, 0};
             if (c < nchunk) v[u] = body[c];
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             if ((v[u][0] | v[u][1] | v[u][2] | v[u][3]) == 0) continue;
-            const int c = c0 + u * LOC_THREADS + tid;
-#pragma unroll
-            for (int q = 0; q < 16; ++q)
-                if (((unsigned)v[u][q >> 2] >> (8 * (q & 3))) & 0xFFu) note(head + c * 16 + q);
+            const int c = c0 + u * NT + tid;
+#pragma unroll 1
+            for (int q = 0; q < 16; ++q) {
+                const unsigned w = (unsigned)(q < 8 ? q < 4 ? v[u][0] : v[u][1] : q < 12 ? v[u][2] : v[u][3]);
+                if ((w >> (8 * (q & 3))) & 0xFFu) note(head + c * 16 + q);
+            }
         }
     }
+}
+// Appends the CT-tile index of every flagged entry to list (at most MAX_LIST kept; *count keeps counting).
+__device__ inline void list_flagged(const uint8_t *flag, int n, int *list, int *count, int tid)
+{
+    scan_flags<LOC_THREADS>(flag, n, tid, [&](int i) {
+        int p = atomicAdd(count, 1);
+        if (p < MAX_LIST) list[p] = i / CT;
+    });
 }
 
 __global__ __launch_bounds__(LOC_THREADS) void locate_kernel(LocArgs a)
@@ -861,7 +870,7 @@ __global__ __launch_bounds__(LOC_THREADS) void locate_kernel(LocArgs a)
     if (overflow) atomicExch(a.fix_count + 1, 1u);
 }
 
-// Step 2: one workgroup recomputes one CT x CT tile of C over the whole K.  Its first wave issues
+// Step 2, many tiles: one workgroup recomputes one CT x CT tile of C over the whole K.  Its first wave issues
 // every MFMA, the same instruction in the same ascending-k order as the GEMM kernel, so a
 // floating-point tile comes back with the bits the GEMM produced.  What bounds the step is the
 // latency of the operand loads (a wave keeps 2 * FIX_UB 16-byte loads per lane in flight), so
@@ -877,14 +886,211 @@ struct FixArgs {
     uint8_t *C;
     int M, N, K, transB;
     long lda, ldb, ldc, sA, sB, sC;
-    const int32_t *fix_tiles;
-    const uint32_t *fix_count;
+    int32_t *fix_tiles;
+    uint32_t *fix_count;
     uint32_t *cc_vobs;      // non-null: the re-summed column sums of the tile's columns are cleared (they are
                             // accumulated again by resum_touched_kernel)
     const uint32_t *bias;   // layer bias [N] or null
+    const uint8_t *row_flag, *col_flag;      // FIND: where the tiles are found
 };
 
+// Few tiles: sixteen workgroups share a tile, 8 x 8 elements each.  A compute unit takes in some 27 GB/s of rows that are a few
+// whole lines each, and a tile's operands are 64 rows; a part's are sixteen, and eight lanes read 128 bytes of one, where a
+// fragment's lanes read 32.  The MFMAs are the same, in the same order, on rows and columns repeated four times over: an
+// element's bits depend on its own row and column only.  (Of integers the order does not matter: four waves take a quarter each.)
+// us a launch: int8 6304 x 768 x 3072 10.2 -> 5.9, f16 the same 18 -> 9.
+constexpr int FIX_PARTS = 16, FIX_PART = 8;     // parts of a tile, rows and columns of one
+constexpr int FIX_GROUP = FIX_WAVES * 8;        // slabs in LDS at a time: 512 bytes for each step of 32 bytes of K
+static_assert(FIX_GROUP * 4 * 512 == FIX_LDS_BYTES, "the parts' steps fill what a whole tile's run takes");
 template <int DT>
+__device__ __forceinline__ void recompute_part(const FixArgs &a, uint8_t *lds, int bz, int tr, int tc, int part)
+{
+    using T = Traits<DT>;
+    typedef typename T::acc_t acc_t;
+    constexpr int ES = T::ES, KE = SLAB_BYTES / ES;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l32 = lane & 31, lh = lane >> 5;
+    const int row0 = tr * CT + (part >> 2) * FIX_PART, col0 = tc * CT + (part & 3) * FIX_PART;
+    const int kbytes = a.K * ES, slabs = (kbytes + SLAB_BYTES - 1) / SLAB_BYTES, lw = wave - 1;
+    const uint8_t *Ab = a.A + (long)bz * a.sA * ES, *Bb = a.B + (long)bz * a.sB * ES;
+    if (a.cc_vobs && part < 4 && threadIdx.x < FIX_PART && col0 + (int)threadIdx.x < a.N) a.cc_vobs[(long)bz * a.N + col0 + threadIdx.x] = 0u;
+    // a lane's place in a slab: row lane >> 3 of the part, chunk lane & 7; in LDS step 4 slab + (chunk >> 1)
+    const int r8 = lane >> 3, ch = lane & 7, last_ch = (kbytes - 1) / 16 * 16;
+    const uint8_t *pa = Ab + (long)min(row0 + r8, a.M - 1) * a.lda * ES, *pb = Bb + (long)min(col0 + r8, a.N - 1) * a.ldb * ES;
+    const int at = (ch >> 1) * 512 + r8 * 32 + (ch & 1) * 16;
+    // columns of a B stored K x N: a chunk holds all of the part's (past the end: the last whole chunk)
+    const uint8_t *pk = Bb + min(col0, (a.N - 1) / FIX_PART * FIX_PART) * ES;
+    // slabs s0 + FIX_WAVES u, u < U; what lies past the end of K is cleared
+    auto stage = [&](auto u_c, int s0, int g0) __attribute__((always_inline)) {
+        constexpr int U = decltype(u_c)::value;
+        typedef int i32x2 __attribute__((ext_vector_type(2)));
+        i32x4 x[U], y[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int s = s0 + FIX_WAVES * u, kb = min(s * SLAB_BYTES + ch * 16, last_ch);
+            x[u] = *reinterpret_cast<const i32x4 *>(pa + kb);
+            if (a.transB) {
+                y[u] = *reinterpret_cast<const i32x4 *>(pb + kb);
+            } else if constexpr (ES == 2) {
+                y[u] = *reinterpret_cast<const i32x4 *>(pk + (long)min(s * KE + lane, a.K - 1) * a.ldb * ES);
+            } else {
+                const i32x2 lo = *reinterpret_cast<const i32x2 *>(pk + (long)min(s * KE + 2 * lane, a.K - 1) * a.ldb);
+                const i32x2 hi = *reinterpret_cast<const i32x2 *>(pk + (long)min(s * KE + 2 * lane + 1, a.K - 1) * a.ldb);
+                y[u] = i32x4{lo[0], lo[1], hi[0], hi[1]};
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int s = s0 + FIX_WAVES * u;
+            if (s >= slabs) break;
+            uint8_t *d = lds + (s - g0) * 4 * 512;
+            const int keep = kbytes - (s * SLAB_BYTES + ch * 16);
+            if ((s + 1) * SLAB_BYTES > kbytes) {
+                x[u] = mask_chunk(x[u], keep);
+                if (a.transB) y[u] = mask_chunk(y[u], keep);
+            }
+            *reinterpret_cast<i32x4 *>(d + at) = x[u];
+            if (a.transB) {
+                *reinterpret_cast<i32x4 *>(d + at + 256) = y[u];
+            } else {
+                // element (k, column c) goes to row c of the step that holds k
+#pragma unroll
+                for (int e = 0; e < 16 / ES; ++e) {
+                    const int k = ES == 2 ? lane : 2 * lane + (e >> 3), c = e & 7;
+                    const unsigned bits = (unsigned)y[u][e * ES / 4] >> (8 * ES * (e % (4 / ES)));
+                    uint8_t *to = d + (k * ES >> 5) * 512 + 256 + c * 32 + (k * ES & 31);
+                    const bool in = s * KE + k < a.K;
+                    if constexpr (ES == 2) *reinterpret_cast<uint16_t *>(to) = in ? (uint16_t)bits : 0;
+                    else *to = in ? (uint8_t)bits : 0;
+                }
+            }
+        }
+    };
+    typename T::accv_t acc;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[i] = T::zero();
+    for (int g0 = 0; g0 < slabs; g0 += FIX_GROUP) {
+        if (g0) __syncthreads();
+        if (lw >= 0) {
+            if (slabs - g0 <= 4 * FIX_WAVES) stage(std::integral_constant<int, 4>{}, g0 + lw, g0);
+            else stage(std::integral_constant<int, 8>{}, g0 + lw, g0);
+        }
+        __syncthreads();
+        // whole runs of eight steps (of those past the end of K, which hold nothing, only slabs that hold something are read)
+        const int steps = min(FIX_GROUP, slabs - g0) * 4;
+        const int share = T::IS_INT ? ((steps + 15) / 16) * 4 : steps, first = T::IS_INT ? wave * share : 0, end = min(steps, first + share);
+        if (wave < (T::IS_INT ? 4 : 1)) {
+            const uint8_t *src = lds + (l32 & 7) * 32 + lh * 16;
+            constexpr int RU = 4;
+            i32x4 x0[RU], y0[RU], x1[RU], y1[RU];
+            auto read = [&](int t, i32x4 (&x)[RU], i32x4 (&y)[RU]) __attribute__((always_inline)) {
+#pragma unroll
+                for (int u = 0; u < RU; ++u) {
+                    x[u] = *reinterpret_cast<const i32x4 *>(src + (t + u) * 512);
+                    y[u] = *reinterpret_cast<const i32x4 *>(src + (t + u) * 512 + 256);
+                }
+            };
+            if (first < end) read(first, x0, y0);
+            for (int t = first; t < end; t += 2 * RU) {
+                if (t + RU < end) read(t + RU, x1, y1);
+#pragma unroll
+                for (int u = 0; u < RU; ++u) acc = T::mfma(y0[u], x0[u], acc);   // B first: lane = row of C, registers = columns
+                if (t + RU < end) {
+                    if (t + 2 * RU < end) read(t + 2 * RU, x0, y0);
+#pragma unroll
+                    for (int u = 0; u < RU; ++u) acc = T::mfma(y1[u], x1[u], acc);
+                }
+            }
+        }
+    }
+    // rows 0..7 of the block are the part's rows, columns 0..7 its columns: register i < 4, column 4 (lane >> 5) + i
+    acc_t v[4] = {(acc_t)acc[0], (acc_t)acc[1], (acc_t)acc[2], (acc_t)acc[3]};
+    if constexpr (T::IS_INT) {
+        __syncthreads();                                        // every wave has read its steps
+        i32x4 *meet = reinterpret_cast<i32x4 *>(lds);
+        if (wave > 0 && wave < 4 && l32 < FIX_PART) meet[(wave * 2 + lh) * FIX_PART + l32] = i32x4{v[0], v[1], v[2], v[3]};
+        __syncthreads();
+        if (wave == 0 && l32 < FIX_PART) {
+#pragma unroll
+            for (int w = 1; w < 4; ++w) {
+                const i32x4 o = meet[(w * 2 + lh) * FIX_PART + l32];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] += o[e];
+            }
+        }
+    }
+    if (wave != 0 || l32 >= FIX_PART || row0 + l32 >= a.M) return;
+    uint8_t *Cb = a.C + (long)bz * a.sC * T::OS;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const int gc = col0 + 4 * lh + e;
+        if (gc < a.N) T::store_c(Cb, (long)(row0 + l32) * a.ldc + gc, a.bias ? add_t(v[e], from_word<acc_t>(a.bias[gc])) : v[e]);
+    }
+}
+
+// FIND: the tiles of a single problem, found by every workgroup for itself from the flags (at most FIND_FLAGS of them: a load or
+// four to a thread), which saves the launch that lists them: what that writes is read a trip to memory later.  The tile rows and tile columns with a
+// flag, in ascending order, so that all workgroups agree; the first one also leaves the list for the kernels behind.
+constexpr int FIND_FLAGS = 32768;
+struct FoundTiles {
+    int flagged[2], unique[2];                  // rows, columns; tile rows, tile columns
+    uint32_t bits[2][FIND_FLAGS / CT / 32];
+    int tile[2][MAX_LIST];
+};
+__device__ __forceinline__ unsigned find_tiles(const FixArgs &a, FoundTiles *f)
+{
+    constexpr int NT = 64 * (FIX_WAVES + 1);
+    const int tid = threadIdx.x;
+    for (int i = tid; i < (int)(offsetof(FoundTiles, tile) / 4); i += NT) reinterpret_cast<uint32_t *>(f)[i] = 0u;
+    __syncthreads();
+    auto note = [&](int side, int i) {
+        atomicAdd(&f->flagged[side], 1);
+        const int t = i / CT;
+        if (!(atomicOr(&f->bits[side][t >> 5], 1u << (t & 31)) >> (t & 31) & 1u)) {
+            const int p = atomicAdd(&f->unique[side], 1);
+            if (p < MAX_LIST) f->tile[side][p] = t;
+        }
+    };
+    scan_flags<NT>(a.row_flag, a.M, tid, [&](int i) { note(0, i); });
+    scan_flags<NT>(a.col_flag, a.N, tid, [&](int i) { note(1, i); });
+    __syncthreads();
+    const int nr = f->flagged[0], nc = f->flagged[1], ur = f->unique[0], uc = f->unique[1];
+    unsigned n = 0;
+    bool overflow = false;
+    if (nr && nc) {
+        // in ascending order; of more than are kept, the first ones
+        int mine = 0, rank = 0;
+        const int side = tid / MAX_LIST, i = tid % MAX_LIST, count = side == 0 ? ur : uc;
+        const bool sorts = side < 2 && count <= MAX_LIST && i < count;
+        if (sorts) {
+            mine = f->tile[side][i];
+            for (int q = 0; q < count; ++q) rank += f->tile[side][q] < mine ? 1 : 0;
+        }
+        __syncthreads();
+        if (sorts) f->tile[side][rank] = mine;
+        else if (side < 2 && i == 0 && count > MAX_LIST) {
+            int p = 0;
+            for (int t = 0; p < MAX_LIST; ++t)
+                if (f->bits[side][t >> 5] >> (t & 31) & 1u) f->tile[side][p++] = t;
+        }
+        __syncthreads();
+        const int kr = min(ur, MAX_LIST), kc = min(uc, MAX_LIST);
+        n = (unsigned)(kr * kc);
+        overflow = nr > MAX_LIST || nc > MAX_LIST || n > (unsigned)MAX_FIX_TILES;
+        f->unique[0] = kr; f->unique[1] = kc;           // (every thread writes the same, and reads them behind the next barrier or itself)
+    }
+    if (blockIdx.x == 0) {
+        if (tid == 0) { a.fix_count[0] = n; a.fix_count[1] = overflow ? 1u : 0u; }
+        const int kc = min(uc, MAX_LIST);
+        for (int t = tid; t < (int)min(n, (unsigned)MAX_FIX_TILES); t += NT) {
+            a.fix_tiles[3 * t] = 0;
+            a.fix_tiles[3 * t + 1] = f->tile[0][t / kc];
+            a.fix_tiles[3 * t + 2] = f->tile[1][t % kc];
+        }
+    }
+    return n;
+}
+
+template <int DT, bool FIND>
 __global__ __launch_bounds__(64 * (FIX_WAVES + 1)) void recompute_kernel(FixArgs a)
 {
     using T = Traits<DT>;
@@ -893,11 +1099,27 @@ __global__ __launch_bounds__(64 * (FIX_WAVES + 1)) void recompute_kernel(FixArgs
     constexpr int UB = FIX_UB;
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     i32x4 *stage = reinterpret_cast<i32x4 *>(lds);          // [FIX_WAVES * UB k-steps][A, B][64 lanes]
-    unsigned n = a.fix_count[0];
+    __shared__ FoundTiles found;
+    unsigned n;
+    if constexpr (FIND) n = find_tiles(a, &found);
+    else n = a.fix_count[0];
     if (n > (unsigned)MAX_FIX_TILES) n = MAX_FIX_TILES;
-    if (blockIdx.x >= n) return;                            // the whole workgroup leaves
-    const int bz = a.fix_tiles[3 * blockIdx.x], tr = a.fix_tiles[3 * blockIdx.x + 1],
-              tc = a.fix_tiles[3 * blockIdx.x + 2];
+    // the whole workgroup leaves, or takes a part of a tile, or a tile
+    const bool parts = n * FIX_PARTS <= (unsigned)MAX_FIX_TILES;
+    if (blockIdx.x >= (parts ? n * FIX_PARTS : n)) return;
+    const int tile = __builtin_amdgcn_readfirstlane(parts ? blockIdx.x / FIX_PARTS : blockIdx.x);
+    int bz = 0, tr, tc;
+    if constexpr (FIND) {
+        const int kc = found.unique[1];
+        tr = __builtin_amdgcn_readfirstlane(found.tile[0][tile / kc]);
+        tc = __builtin_amdgcn_readfirstlane(found.tile[1][tile % kc]);
+    } else {
+        bz = a.fix_tiles[3 * tile]; tr = a.fix_tiles[3 * tile + 1]; tc = a.fix_tiles[3 * tile + 2];
+    }
+    if (__builtin_expect(parts, 1)) {
+        recompute_part<DT>(a, lds, bz, tr, tc, blockIdx.x % FIX_PARTS);
+        return;
+    }
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l32 = lane & 31, lh = lane >> 5;
     const int row = tr * CT + l32, col = tc * CT + l32;
     const uint8_t *Ab = a.A + (long)bz * a.sA * ES, *Bb = a.B + (long)bz * a.sB * ES;
@@ -1053,6 +1275,7 @@ struct TouchArgs {
     const int32_t *fix_tiles;
     const uint32_t *fix_count;
     uint32_t *cc_vobs, *rc_vobs;
+    uint32_t *counts;       // non-null: made ready for a compare without a ticket
 };
 
 template <int DT>
@@ -1067,6 +1290,14 @@ __global__ __launch_bounds__(256) void resum_touched_kernel(TouchArgs a)
     unsigned n = a.fix_count[0];
     if (n > (unsigned)MAX_FIX_TILES) n = MAX_FIX_TILES;
     const int part = blockIdx.y, tid = threadIdx.x;
+    if (a.counts && blockIdx.x == 0 && part == TOUCH_PARTS - 1 && tid == 0) {
+        const uint32_t before = a.counts[2];
+        a.counts[0] = 0u;
+        a.counts[1] = 0u;
+        a.counts[2] = a.fix_count[1] ? 3u : 0u;
+        a.counts[3] = n;
+        a.counts[4] = before;
+    }
     // the grid has TOUCH_TILES workgroups per part; listed tiles beyond that many take further trips
     for (int t = blockIdx.x; t < (int)n; t += gridDim.x) {
         const int bz = a.fix_tiles[3 * t], tr = a.fix_tiles[3 * t + 1], tc = a.fix_tiles[3 * t + 2];
@@ -1141,26 +1372,33 @@ __global__ __launch_bounds__(256) void resum_touched_kernel(TouchArgs a)
 template <int DT>
 static hipError_t launch_recompute(const FixArgs &f, hipStream_t st)
 {
-    auto kern = recompute_kernel<DT>;
+    auto kern = f.row_flag ? recompute_kernel<DT, true> : recompute_kernel<DT, false>;
     hipError_t e = ensure_max_lds(reinterpret_cast<const void *>(kern), (int)FIX_LDS_BYTES);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3(MAX_FIX_TILES), dim3(64 * (FIX_WAVES + 1)), FIX_LDS_BYTES, st, f);
     return hipGetLastError();
 }
 
+// One problem of not too many flags: the recompute finds its tiles itself, and leaves their list behind.
+bool correct_finds(const Shape &s) { return s.batch == 1 && s.M + s.N <= FIND_FLAGS; }
+
 hipError_t launch_correct(int dt, const void *A, const void *B, void *C, const Shape &s,
                           const Workspace &w, const Verdict &v, bool with_sto, bool clear_list, bool targeted,
                           size_t stale_words, uint32_t *zero_ptr, size_t zero_words, hipStream_t st, bool skip_if_clean)
 {
     hipError_t e = hipSuccess;
-    if (clear_list && (e = launch_zero(w.fix_count, 2, st)) != hipSuccess) return e;
-    LocArgs l;
-    l.row_flag = v.row_flag; l.col_flag = v.col_flag; l.M = s.M; l.N = s.N;
-    l.fix_tiles = w.fix_tiles; l.fix_count = w.fix_count;
-    hipLaunchKernelGGL(locate_kernel, dim3((unsigned)s.batch), dim3(LOC_THREADS), 0, st, l);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+    const bool find = correct_finds(s);
+    if (!find) {
+        if (clear_list && (e = launch_zero(w.fix_count, 2, st)) != hipSuccess) return e;
+        LocArgs l;
+        l.row_flag = v.row_flag; l.col_flag = v.col_flag; l.M = s.M; l.N = s.N;
+        l.fix_tiles = w.fix_tiles; l.fix_count = w.fix_count;
+        hipLaunchKernelGGL(locate_kernel, dim3((unsigned)s.batch), dim3(LOC_THREADS), 0, st, l);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
 
     FixArgs f;
+    f.row_flag = find ? v.row_flag : nullptr; f.col_flag = find ? v.col_flag : nullptr;
     f.A = (const uint8_t *)A; f.B = (const uint8_t *)B; f.C = (uint8_t *)C;
     f.M = s.M; f.N = s.N; f.K = s.K; f.transB = s.transB;
     f.lda = s.lda; f.ldb = s.ldb; f.ldc = s.ldc; f.sA = s.sA; f.sB = s.sB; f.sC = s.sC;
@@ -1178,6 +1416,7 @@ hipError_t launch_correct(int dt, const void *A, const void *B, void *C, const S
         TouchArgs t;
         t.C = (const uint8_t *)C; t.ldc = s.ldc; t.sC = s.sC; t.M = s.M; t.N = s.N;
         t.fix_tiles = w.fix_tiles; t.fix_count = w.fix_count; t.cc_vobs = w.cc_vobs; t.rc_vobs = w.rc_vobs;
+        t.counts = find ? v.counts : nullptr;
         const dim3 grid(TOUCH_TILES, TOUCH_PARTS);
         switch (dt) {
         case DT_I8:   hipLaunchKernelGGL(resum_touched_kernel<DT_I8>, grid, dim3(256), 0, st, t); break;
@@ -1185,7 +1424,7 @@ hipError_t launch_correct(int dt, const void *A, const void *B, void *C, const S
         default:      hipLaunchKernelGGL(resum_touched_kernel<DT_F16>, grid, dim3(256), 0, st, t); break;
         }
         if ((e = hipGetLastError()) != hipSuccess) return e;
-        return launch_compare(dt, s, w, v, true, with_sto, nullptr, 0, st);
+        return launch_compare(dt, s, w, v, true, with_sto, nullptr, 0, st, false, find);
     }
     // re-check without earlier sums of this C: the stored C is re-summed as a whole (a streaming
     // pass at HBM speed) and compared with the predictions
