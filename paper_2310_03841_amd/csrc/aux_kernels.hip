@@ -101,6 +101,7 @@ struct EncBArgs {
 template <int DT>
 __global__ __launch_bounds__(256) void encode_b_kernel(EncBArgs a)
 {
+    fetch_args<EncBArgs>();
     __shared__ uint32_t red[256 * (16 / Traits<DT>::ES) + 4];
     const int tid = threadIdx.x, bz = blockIdx.z;
     {
@@ -184,6 +185,7 @@ struct CmpArgs {
 template <bool IS_INT>
 __global__ __launch_bounds__(256) void compare_kernel(CmpArgs a)
 {
+    fetch_args<CmpArgs>();
     __shared__ int is_last;
     const int bz = blockIdx.z, tid = threadIdx.x;
     const int idx = blockIdx.x * 256 + tid;
@@ -398,6 +400,7 @@ constexpr int CHK_KN_LANES = 4;        // chunk columns of a unit over a B store
 template <int DT, int RW>
 __global__ __launch_bounds__(256) void check_kernel(ChkArgs f)
 {
+    fetch_args<ChkArgs>();
     using T = Traits<DT>;
     typedef typename T::acc_t acc_t;
     constexpr int ES = T::ES, CE = 16 / ES;
@@ -696,6 +699,7 @@ template <int DT> __device__ __forceinline__ typename Traits<DT>::acc_t out_elem
 template <int DT>
 __global__ __launch_bounds__(256) void verify_kernel(VerArgs a)
 {
+    fetch_args<VerArgs>();
     using T = Traits<DT>;
     typedef typename T::acc_t acc_t;
     constexpr int OS = T::OS, CE = 16 / OS;
@@ -1093,6 +1097,7 @@ __device__ __forceinline__ unsigned find_tiles(const FixArgs &a, FoundTiles *f)
 template <int DT, bool FIND>
 __global__ __launch_bounds__(64 * (FIX_WAVES + 1)) void recompute_kernel(FixArgs a)
 {
+    fetch_args<FixArgs>();
     using T = Traits<DT>;
     typedef typename T::accv_t accv_t;
     constexpr int ES = T::ES, CE = 16 / ES;
@@ -1281,6 +1286,7 @@ struct TouchArgs {
 template <int DT>
 __global__ __launch_bounds__(256) void resum_touched_kernel(TouchArgs a)
 {
+    fetch_args<TouchArgs>();
     using T = Traits<DT>;
     typedef typename T::acc_t acc_t;
     constexpr int OS = T::OS, CE = 16 / OS;

@@ -378,6 +378,7 @@ __global__ __launch_bounds__(64 * FAST_WAVES) void gemm_fast_kernel(GemmArgs who
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
     constexpr bool PROT = MODE != FAST_PLAIN;
+    fetch_args<GemmArgs>();
     // Persistent workgroups: one per compute unit, each walks the tile list with the grid's stride.
     // The 128-row tiles come first in the list: the compute units that start with one are half a
     // tile ahead of the others from then on, so the two groups store their tiles of C at different

@@ -91,11 +91,11 @@ __global__ __launch_bounds__(256) void gemm_tile_kernel(typename KernelArgs<ONE>
     static_assert((NS - 2) * (GA + GB) < 64, "the wait count is an immediate");
 
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+    if constexpr (!ONE) fetch_args<TileArgs>();
     const GemmArgs &g = a.g;
     const int bz = blockIdx.y;
     if constexpr (ONE) {
-        // The arguments that the end of the call needs, a few lines of them, are asked for here: a scalar load that
-        // misses in the middle of the chain at the end costs half a microsecond.
+        // (Of its eleven lines of arguments the ones that the end of the call needs: all of them at once cost the start 1 to 2 % of a call.)
         asm volatile("" :: "s"(a.g.cc_acc), "s"(a.g.bias), "s"(a.p.rc_pacc), "s"(a.p.tickets), "s"(a.p.cc_acc), "s"(a.p.tau), "s"(a.p.counts));
         const size_t first = (size_t)bz * a.p.wgs + blockIdx.x, nw = (size_t)a.p.wgs * a.p.batch;
         for (size_t i = first * 256 + threadIdx.x; i < a.p.zero_words; i += nw * 256) a.p.zero_ptr[i] = 0u;
