@@ -11,7 +11,7 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libabft.so")
 SOURCES = ["gemm_tile.hip", "gemm_fast.hip", "gemm_item_rows.hip", "gemm_item_cols.hip", "gemm_item.hip", "aux_kernels.hip", "abft_api.hip"]
-HEADERS = ["abft_internal.h", "abft_device.h", "gemm_args.h", "gemm_epilogue.h", "gemm_apass.h", "gemm_item.h", "encode_pass.h", "predict_pass.h", os.path.join("..", "..", "include", "abft.h")]
+HEADERS = ["abft_internal.h", "abft_device.h", "gemm_args.h", "gemm_epilogue.h", "gemm_apass.h", "gemm_item.h", "block_out.h", "encode_pass.h", "predict_pass.h", os.path.join("..", "..", "include", "abft.h")]
 
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-fPIC", "-std=c++17", "-munsafe-fp-atomics",

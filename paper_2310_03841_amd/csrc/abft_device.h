@@ -23,6 +23,16 @@ __device__ __forceinline__ int tile_thread_index()
     return t;
 }
 
+// A kernel's arguments (its first parameter), read from where the launch put them: each phase of a tile or item takes its own.  Taken from
+// the parameter, every argument and every offset, pitch and condition that follows from them is formed ahead of the loop over tiles
+// or items and held across it: too many scalars, which go to lanes of vector registers and come back one by one.
+template <typename ARGS> __device__ __forceinline__ const ARGS &kernel_args()
+{
+    const __attribute__((address_space(4))) ARGS *p = (const __attribute__((address_space(4))) ARGS *)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return *(const ARGS *)p;
+}
+
 // Asks for every 64-byte line of a kernel's arguments at once, first thing.  A launch's arguments lie in memory, and a line that is touched for
 // the first time takes a compute unit some 500 clocks (0.22 us); left alone, the compiler loads each argument where it is used, and the
 // kernels of a small call went through three to five such trips one behind the other.

@@ -14,6 +14,7 @@ struct GemmArgs {
     int M, N, K;
     long lda, ldb, ldc, sA, sB, sC;               // elements
     int tiles_m, tiles_n;
+    uint32_t group_inv;                           // map_inverse(tiles_n)
     int n_big, tiles_m_big, tiles_m_small;        // fast path: 256-row tiles and 128-row tiles
     int n_small, batch;                           // fast path: 128-row tiles per batch item; batch items
     int inj_b, inj_row, inj_col, inj_bit;         // armed accumulator flip (inj_b < 0: none)
@@ -36,32 +37,27 @@ struct GemmArgs {
 // Workgroup -> tile inside a region of tiles_m x tiles_n tiles: consecutive ids of one XCD
 // (workgroups are dealt to the 8 XCDs round-robin) walk GROUP_M tile rows, then the next column,
 // so the workgroups that share an L2 work on a compact group of tiles.
-__device__ __forceinline__ void map_tile(int bid, int nb, int tiles_m, int tiles_n, int *tm, int *tn)
+// group_inv: 2^32 / (4 tiles_n) rounded down (map_inverse): a quotient by it is the true one or one less.  (Three divisions, of which a scalar unit
+// has none, took 830 of the 3200 clocks before a tile's first load.)
+constexpr int GROUP_M = 4;              // measured against 2, 3, 6, 8, 16: best or equal on every Linear shape
+inline uint32_t map_inverse(int tiles_n) { return (uint32_t)((1ull << 32) / ((uint64_t)GROUP_M * tiles_n)); }
+__device__ __forceinline__ void map_tile(int bid, int nb, int tiles_m, int tiles_n, uint32_t group_inv, int *tm, int *tn)
 {
-    constexpr int GROUP_M = 4;          // measured against 2, 3, 6, 8, 16: best or equal on every Linear shape
     const int q = nb >> 3, r = nb & 7, xcd = bid & 7;
     const int L = xcd * q + (xcd < r ? xcd : r) + (bid >> 3);
     const int per_group = GROUP_M * tiles_n;
-    const int grp = L / per_group, in_grp = L % per_group;
-    const int first_m = grp * GROUP_M;
-    const int gsz = (tiles_m - first_m) < GROUP_M ? (tiles_m - first_m) : GROUP_M;
-    *tm = first_m + in_grp % gsz;
-    *tn = in_grp / gsz;
+    int grp = (int)__umulhi((uint32_t)L, group_inv), in_grp = L - grp * per_group;
+    if (in_grp >= per_group) { ++grp; in_grp -= per_group; }
+    const int first_m = grp * GROUP_M, gsz = tiles_m - first_m;
+    // rows of a group: four, in the last one one to four
+    const int col = gsz >= 4 ? in_grp >> 2 : gsz == 3 ? (int)__umulhi((uint32_t)in_grp, 0x55555556u) : gsz == 2 ? in_grp >> 1 : in_grp;
+    *tm = first_m + in_grp - col * (gsz < GROUP_M ? gsz : GROUP_M);
+    *tn = col;
 }
 
 // Fast path (gemm_fast.hip): B stored N x K, K a whole number of 128-byte slabs.
 bool gemm_fast_eligible(int dt, int M, int N, int K, bool transB, long lda, long ldb);
 hipError_t launch_gemm_fast(int dt, bool protect, GemmArgs &g, int batch, hipStream_t st);
 void gemm_fast_tile(int *tm, int *tn);
-
-// A kernel's arguments (its first parameter), read from where the launch put them: each phase of a tile or item takes its own.  Taken from
-// the parameter, every argument and every offset, pitch and condition that follows from them is formed ahead of the loop over tiles
-// or items and held across it: too many scalars, which go to lanes of vector registers and come back one by one.
-template <typename ARGS> __device__ __forceinline__ const ARGS &kernel_args()
-{
-    const __attribute__((address_space(4))) ARGS *p = (const __attribute__((address_space(4))) ARGS *)__builtin_amdgcn_kernarg_segment_ptr();
-    asm volatile("" : "+s"(p));
-    return *(const ARGS *)p;
-}
 
 }  // namespace abft

@@ -396,13 +396,13 @@ __global__ __launch_bounds__(64 * FAST_WAVES) void gemm_fast_kernel(GemmArgs who
             }
         }
         const int per_item = g.n_small + g.n_big;
-        const int bz = t / per_item, bid = t - bz * per_item;
+        const int bz = t < per_item ? 0 : t / per_item, bid = t - bz * per_item;
         int tm, tn;
         if (STO != STO_128 && bid >= g.n_small) {
-            map_tile(bid - g.n_small, g.n_big, g.tiles_m_big, g.tiles_n, &tm, &tn);
+            map_tile(bid - g.n_small, g.n_big, g.tiles_m_big, g.tiles_n, g.group_inv, &tm, &tn);
             if constexpr (STO != STO_128) fast_tile<DT, 256, MODE, STO>(g, smem, tm * 256, tn * 256, bz, tn);
         } else {
-            map_tile(bid, g.n_small, g.tiles_m_small, g.tiles_n, &tm, &tn);
+            map_tile(bid, g.n_small, g.tiles_m_small, g.tiles_n, g.group_inv, &tm, &tn);
             fast_tile<DT, 128, MODE, STO>(g, smem, g.tiles_m_big * 256 + tm * 128, tn * 256, bz, tn);
         }
         t += n_tile;
@@ -512,6 +512,7 @@ static hipError_t launch_fast_one(GemmArgs &g, int batch, hipStream_t st)
     const int num_cu = device_cu_count(&e);
     if (e != hipSuccess) return e;
     g.tiles_n = (g.N + 255) / 256;
+    g.group_inv = map_inverse(g.tiles_n);
     const int big_rows = choose_big_rows(g.M, g.tiles_n, batch, num_cu, PROT);
     g.tiles_m_big = big_rows;
     g.n_big = big_rows * g.tiles_n;

@@ -19,6 +19,7 @@
 #include "gemm_args.h"
 #include "gemm_apass.h"
 #include "gemm_epilogue.h"
+#include "block_out.h"
 
 namespace abft {
 
@@ -69,44 +70,6 @@ __device__ __forceinline__ int item_opaque(int v)
 {
     asm volatile("" : "+v"(v));
     return v;
-}
-
-// ------------------------------------------------------------------ sums over 32 lanes
-__device__ __forceinline__ uint32_t item_bits(int v) { return (uint32_t)v; }
-__device__ __forceinline__ uint32_t item_bits(float v) { return __float_as_uint(v); }
-
-// lanes with bit 4 clear get a, the others b, each summed over lane and lane ^ 16
-template <typename V> __device__ __forceinline__ V fold_xor16(V a, V b)
-{
-    auto p = __builtin_amdgcn_permlane16_swap(item_bits(a), item_bits(b), false, false);
-    return add_t(from_word<V>(p[0]), from_word<V>(p[1]));
-}
-// lanes with up set get b, the others a, each summed with the lane that CTRL names (its `up` is the other one)
-template <int CTRL, typename V> __device__ __forceinline__ V fold_dpp(V a, V b, bool up)
-{
-    const V keep = up ? b : a, send = up ? a : b;
-    return add_t(keep, dpp_get<CTRL>(send));
-}
-// The sixteen values of an accumulator block, each summed over the 32 lanes of a half of the wave; the lane
-// gets the value of column fold16_column(lane)
-template <typename V, typename ACC> __device__ __forceinline__ V fold16(const ACC &v, int lane)
-{
-    V w[8], x[4], y[2];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) w[j] = fold_xor16<V>(v[2 * j], v[2 * j + 1]);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) x[j] = fold_dpp<0x128>(w[2 * j], w[2 * j + 1], (lane & 8) != 0);
-#pragma unroll
-    for (int j = 0; j < 2; ++j) y[j] = fold_dpp<0x141>(x[2 * j], x[2 * j + 1], (lane & 4) != 0);
-    V z = fold_dpp<0x4E>(y[0], y[1], (lane & 2) != 0);
-    return add_t(z, dpp_get<0xB1>(z));
-}
-// column inside a 32 x 32 block of the value fold16 leaves in this lane (register i of a block holds
-// column 8 (i >> 2) + 4 (lane >> 5) + (i & 3); i = 8 b1 + 4 b2 + 2 b3 + b4 in bits of the lane)
-__device__ __forceinline__ int fold16_column(int lane)
-{
-    const int i = ((lane & 2) << 2) + (lane & 4) + ((lane >> 2) & 2) + ((lane >> 4) & 1);
-    return 8 * (i >> 2) + 4 * (lane >> 5) + (i & 3);
 }
 
 // ------------------------------------------------------------------ operands into LDS
@@ -443,17 +406,6 @@ template <int DT> struct Dot {
     __device__ __forceinline__ acc_t sum() const { return add_xor32(add_t(total, chains())); }
 };
 
-// The sixteen values of a block, added up.
-template <typename V, typename ACC> __device__ __forceinline__ V sum16(const ACC &v)
-{
-    V a[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) a[i] = add_t((V)v[i], (V)v[i + 8]);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) a[i] = add_t(a[i], a[i + 4]);
-    return add_t(add_t(a[0], a[2]), add_t(a[1], a[3]));
-}
-
 // b = B e and max|B| from the resident B, b also as the terms of A b's operand.  X: B in memory, ks / ns: bytes from one k / one column to the next (finite_or_again).
 template <int DT, typename FRAG>
 __device__ __forceinline__ void b_pass(const ItemArgs &g, const FRAG &fb, const Ident<DT> &id, uint32_t *b_lds, uint8_t *terms, int KP,
@@ -503,36 +455,12 @@ __device__ __forceinline__ void item_flip(const ItemArgs &g, ACC &acc, int m0, i
             acc[i] = from_word<typename Traits<DT>::acc_t>(as_word((typename Traits<DT>::acc_t)acc[i]) ^ (1u << g.inj_bit));
 }
 
-// 16-bit types: the block rounded, as words of two columns: word 2 q + j = columns 8 q + 4 (lane >> 5) + 2 j + {0, 1}
-template <int DT, typename ACC> __device__ __forceinline__ void pack_block(const ACC &acc, uint32_t (&w)[8])
-{
-#pragma unroll
-    for (int j = 0; j < 8; ++j) w[j] = pack2<DT>((float)acc[2 * j], (float)acc[2 * j + 1]);
-}
-template <int DT> __device__ __forceinline__ float unpack_lo(uint32_t w)
-{
-    return DT == DT_BF16 ? __uint_as_float(w << 16) : f16_bits_to_f32(w & 0xFFFFu);
-}
-template <int DT> __device__ __forceinline__ float unpack_hi(uint32_t w)
-{
-    return DT == DT_BF16 ? __uint_as_float(w & 0xFFFF0000u) : f16_bits_to_f32(w >> 16);
-}
-
-// A 32 x 32 block at (m0, n0) as row segments.  16-bit C: after the swaps a lane holds 16 bytes of row
-// (lane & 15) + 16 pass, and the four lanes of a row its 64 bytes.  int32 C: one more exchange, between
-// lane and lane ^ 8, makes it eight rows of 128 bytes (segments of 64 bytes, off their 64-byte boundaries
-// as rows of C usually are, wrote 1024 x 577 x 577 in 584 us, unprotected).
 // Where an item's C goes: buffer stores, which leave out rows past M without a branch (they lie past the end: the descriptor ends
 // with the last row), and a lane's place in a block as an offset, so that a store costs an addition.  Offsets stay below 2^31 (item_plan).
 struct ItemOut {
     __amdgpu_buffer_rsrc_t dst;
     int N, ldbytes, lane;
 };
-template <int DT> __device__ __forceinline__ int out_col(int lane)
-{
-    if constexpr (Traits<DT>::OS == 4) return 16 * ((lane >> 3) & 1) + 8 * ((lane >> 4) & 1) + 4 * (lane >> 5);
-    else return 16 * ((lane >> 4) & 1) + 8 * (lane >> 5);
-}
 template <int DT> __device__ __forceinline__ ItemOut item_out(const ItemArgs &g, int bz, int lane)
 {
     constexpr int OS = Traits<DT>::OS;
@@ -540,49 +468,17 @@ template <int DT> __device__ __forceinline__ ItemOut item_out(const ItemArgs &g,
     o.N = g.N;
     o.ldbytes = (int)g.ldc * OS;
     o.dst = __builtin_amdgcn_make_buffer_rsrc(g.C + (long)bz * g.sC * OS, 0, (g.M - 1) * o.ldbytes + g.N * OS, ITEM_RSRC_FLAGS);
-    o.lane = (lane & (OS == 4 ? 7 : 15)) * o.ldbytes + out_col<DT>(lane) * OS;
+    o.lane = out_row<DT>(lane) * o.ldbytes + out_col<DT>(lane) * OS;
     return o;
 }
+// A block at (m0, n0), see turn_block.
 template <int DT>
 __device__ __forceinline__ void store_block(const ItemOut &o, const uint32_t *w, int m0, int n0, int lane)
 {
     constexpr int OS = Traits<DT>::OS;
-    constexpr int NP = OS == 4 ? 4 : 2, RPP = 32 / NP;         // passes, rows per pass
+    constexpr int NP = out_passes<DT>(), RPP = 32 / NP;        // passes, rows per pass
     i32x4 out[NP];
-    if constexpr (OS == 4) {
-        i32x4 s[2][2];                           // [half of the columns][rows 0..15, 16..31]
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                auto p = __builtin_amdgcn_permlane16_swap(w[8 * h + j], w[8 * h + 4 + j], false, false);
-                s[h][0][j] = (int)p[0];
-                s[h][1][j] = (int)p[1];
-            }
-        // lanes with bit 3 clear: the first half of row (lane & 7), of row (lane & 7) + 8; the others the second
-#pragma unroll
-        for (int r = 0; r < 2; ++r)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                out[2 * r][j] = __builtin_amdgcn_update_dpp(s[0][r][j], s[1][r][j], 0x128, 0xF, 0xC, false);
-                out[2 * r + 1][j] = __builtin_amdgcn_update_dpp(s[1][r][j], s[0][r][j], 0x128, 0xF, 0x3, false);
-            }
-    } else {
-        uint32_t u[4], v[4];
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            auto p = __builtin_amdgcn_permlane32_swap(w[j], w[2 + j], false, false);
-            u[j] = p[0]; u[2 + j] = p[1];
-            auto q = __builtin_amdgcn_permlane32_swap(w[4 + j], w[6 + j], false, false);
-            v[j] = q[0]; v[2 + j] = q[1];
-        }
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            auto p = __builtin_amdgcn_permlane16_swap(u[j], v[j], false, false);
-            out[0][j] = (int)p[0];
-            out[1][j] = (int)p[1];
-        }
-    }
+    turn_block<DT>(w, out);
     const int at = o.lane + m0 * o.ldbytes + n0 * OS, step = RPP * o.ldbytes;
     if (n0 + 32 <= o.N) {
 #pragma unroll

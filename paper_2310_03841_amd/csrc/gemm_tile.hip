@@ -31,6 +31,7 @@
 #include <algorithm>
 
 #include "abft_device.h"
+#include "block_out.h"
 #include "encode_pass.h"
 #include "gemm_apass.h"
 #include "gemm_args.h"
@@ -50,21 +51,31 @@ struct TileArgs {
     EncArgs ea, eb;
     uint32_t *counts;             // protected: cleared here, completed by the check kernel
     uint32_t *bias_sum;           // protected, with a bias: its sum, formed by one more workgroup
-    int fuse_bm;                  // host: rows of a tile of the instantiations with APASS, 0: the others
     int aux_off;                  // APASS: where the words of b and of a begin in LDS; ONE: the words of the predictions
+    int bias_off;                 // with a bias: where that of a tile's columns lies in LDS, behind all else
 };
-// ONE alone takes the arguments of the predictions: what a launch copies, every call pays for.
-struct OneArgs : TileArgs { PredArgs p; };
+// What the host fills in.
+struct HostArgs : TileArgs {
+    PredArgs p;
+    int fuse_bm;                  // rows of a tile of the instantiations with APASS, 0: the others
+};
+// ONE alone takes the arguments of the predictions, and none of the passes beside the tiles: what a launch copies, every call pays for, and
+// each line of 64 bytes costs the start of a kernel some 100 clocks.
+struct OneArgs {
+    GemmArgs g;
+    int n_extra, n_tiles, aux_off, bias_off;
+    PredArgs p;
+};
 template <bool ONE> struct KernelArgs { typedef TileArgs type; };
 template <> struct KernelArgs<true> { typedef OneArgs type; };
 
-constexpr int TILE_STAGE_ROW = 36;                               // words per staged row of a 32 x 32 block (32 + pad)
-constexpr int TILE_STAGE_WAVE = 32 * TILE_STAGE_ROW * 4;
+// The sums of a tile's rows and columns by wave column and wave row, of the accumulators and of the stored values, and eight words of maxima.
+constexpr int tile_epi_bytes(int BM, int BN) { return 4 * (BM + BN) * 4 + 8 * 4; }
 
 // ns: buffers in use, min(NS, slabs of the problem)
 __host__ __device__ constexpr int tile_lds_bytes(int BM, int BN, int ns)
 {
-    const int loop = ns * (BM + BN) * SLAB_BYTES, epi = 4 * TILE_STAGE_WAVE + 4 * (BM + BN) * 4;
+    const int loop = ns * (BM + BN) * SLAB_BYTES, epi = tile_epi_bytes(BM, BN);
     return loop > epi ? loop : epi;
 }
 
@@ -77,7 +88,7 @@ template <int ES, int ROWB> __device__ __forceinline__ int kn_swizzle(int k)
 
 // ONE: the whole protected call (predict_pass.h)
 template <int DT, int BM, int BN, int NS, bool PROT, bool TRANSB, bool APASS, bool ONE>
-__global__ __launch_bounds__(256) void gemm_tile_kernel(typename KernelArgs<ONE>::type a)
+__global__ __launch_bounds__(256) void gemm_tile_kernel(typename KernelArgs<ONE>::type whole)
 {
     using T = Traits<DT>;
     typedef typename T::acc_t acc_t;
@@ -91,12 +102,14 @@ __global__ __launch_bounds__(256) void gemm_tile_kernel(typename KernelArgs<ONE>
     static_assert((NS - 2) * (GA + GB) < 64, "the wait count is an immediate");
 
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
-    if constexpr (!ONE) fetch_args<TileArgs>();
+    fetch_args<typename KernelArgs<ONE>::type>();
+    // ONE: each argument where it is used (a few of those that the call's end needs and all of the tiles' do not fit the scalar registers; and, from the
+    // parameter, the compiler asks for some twenty of them ahead of the line above: int8 873 x 249 x 128 7.5 us, 6.9 so).  The others have scalars
+    // enough: 197 x 3072 x 768 and its check 10.5 us, 11.0 with each where it is used.
+    const auto &a = ONE ? kernel_args<typename KernelArgs<ONE>::type>() : whole;
     const GemmArgs &g = a.g;
     const int bz = blockIdx.y;
     if constexpr (ONE) {
-        // (Of its eleven lines of arguments the ones that the end of the call needs: all of them at once cost the start 1 to 2 % of a call.)
-        asm volatile("" :: "s"(a.g.cc_acc), "s"(a.g.bias), "s"(a.p.rc_pacc), "s"(a.p.tickets), "s"(a.p.cc_acc), "s"(a.p.tau), "s"(a.p.counts));
         const size_t first = (size_t)bz * a.p.wgs + blockIdx.x, nw = (size_t)a.p.wgs * a.p.batch;
         for (size_t i = first * 256 + threadIdx.x; i < a.p.zero_words; i += nw * 256) a.p.zero_ptr[i] = 0u;
         for (size_t i = first * 256 + threadIdx.x; i < a.p.zero2_words; i += nw * 256) a.p.zero2_ptr[i] = 0u;
@@ -122,7 +135,7 @@ __global__ __launch_bounds__(256) void gemm_tile_kernel(typename KernelArgs<ONE>
     const int wm = wave >> 1, wn = wave & 1;
     const int l32 = lane & 31, lh = lane >> 5;
     int tm, tn;
-    map_tile(PROT ? blockIdx.x - a.n_extra : blockIdx.x, a.n_tiles, g.tiles_m, g.tiles_n, &tm, &tn);
+    map_tile(PROT ? blockIdx.x - a.n_extra : blockIdx.x, a.n_tiles, g.tiles_m, g.tiles_n, g.group_inv, &tm, &tn);
     const int m0 = tm * BM, n0 = tn * BN;
     const int M = g.M, N = g.N, K = g.K;
     const int nslab = (K + KE - 1) / KE;
@@ -130,16 +143,6 @@ __global__ __launch_bounds__(256) void gemm_tile_kernel(typename KernelArgs<ONE>
 
     const uint8_t *Ab = g.A + (long)bz * g.sA * ES;
     const uint8_t *Bb = g.B + (long)bz * g.sB * ES;
-
-    // the bias of this lane's four columns of every block column, requested before everything else
-    acc_t bias4[NI][4];
-#pragma unroll
-    for (int ni = 0; ni < NI; ++ni)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int gc = n0 + wn * TN + ni * 32 + 4 * (lane & 7) + e;
-            bias4[ni][e] = (g.bias && gc < N) ? from_word<acc_t>(g.bias[gc]) : T::zero();
-        }
 
     // ---- sources of the direct loads.  K-contiguous operand: group p of this wave fills LDS rows
     // (4 p + wave) * 8 .. + 8, lane l row l >> 3, slot l & 7.
@@ -294,6 +297,13 @@ __global__ __launch_bounds__(256) void gemm_tile_kernel(typename KernelArgs<ONE>
             }
         for (int i = tid; i < owned * KE; i += 256) col_lds[i] = 0u;
     }
+    // the bias of the tile's columns (past the end of N the last one's), straight into LDS of its own, ahead of the slabs: a wait for a slab is
+    // one for everything before it
+    const uint32_t *bias_lds = reinterpret_cast<const uint32_t *>(smem + a.bias_off);
+    if (g.bias && wave < BN / 64) {
+        const int gc = n0 + 64 * wave + lane;
+        __builtin_amdgcn_global_load_lds((tile_gas_ptr)(g.bias + (gc < N ? gc : N - 1)), (tile_las_ptr)(smem + a.bias_off + 256 * wave), 4, 0, 0);
+    }
     for (int s = 0; s < NS - 1; ++s)
         if (s < nslab) issue(s);
     auto arrive = [&](int s) __attribute__((always_inline)) {
@@ -343,9 +353,10 @@ __global__ __launch_bounds__(256) void gemm_tile_kernel(typename KernelArgs<ONE>
         mfmas(set0{});
     }
 
-    // ---- epilogue: block by block through a stage of the wave's own.  Lane l holds row l & 31 of a
-    // block and in register i column 8 (i >> 2) + 4 (l >> 5) + (i & 3); read back, lane l has four
-    // consecutive columns 4 (l & 7) .. of rows 8 p + (l >> 3).
+    // ---- epilogue, from the registers (block_out.h): lane l holds row l & 31 of a block and in register i column
+    // 8 (i >> 2) + 4 (l >> 5) + (i & 3).  Row sums are in-lane adds, column sums fold lanes and values together, C leaves as segments of 64 bytes of
+    // sixteen rows (int32: 128 of eight).  (Each block through a stage in LDS, and from there four columns of four rows to a lane: 3200 of the 13700
+    // clocks of a bf16 197 x 3072 x 768.)
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");       // every wave is done with the operand buffers
     if constexpr (APASS) {
         if (!g.a_given) {
@@ -357,150 +368,152 @@ __global__ __launch_bounds__(256) void gemm_tile_kernel(typename KernelArgs<ONE>
         const int r = m0 + (tid >> 3) + 32 * (tid & 7);
         if (owned && (tid & 7) < BM / 32 && r < M) atomic_add_word(g.rc_pred + (long)bz * M + r, ast.rdot);
     }
-    uint8_t *stage = smem + wave * TILE_STAGE_WAVE;
-    acc_t *rs_part = reinterpret_cast<acc_t *>(smem + 4 * TILE_STAGE_WAVE);          // [2][BM] by wave column
+    acc_t *rs_part = reinterpret_cast<acc_t *>(smem);                                // [2][BM] by wave column
     acc_t *cs_part = rs_part + 2 * BM;                                               // [2][BN] by wave row
     float *rs_sto = reinterpret_cast<float *>(cs_part + 2 * BN);                     // the same of the values as stored
     float *cs_sto = rs_sto + 2 * BM;
-    uint8_t *Cb = g.C + (long)bz * g.sC * OS;
+    float *max_part = cs_sto + 2 * BN;                                               // max|C as stored| by wave, max|A|
     const bool sto = PROT && !T::IS_INT && g.cc_sto != nullptr;
     const bool inj_here = g.inj_b == bz && g.inj_row >= m0 && g.inj_row < m0 + BM && g.inj_col >= n0 && g.inj_col < n0 + BN;
+    const bool inside = m0 + BM <= M && n0 + BN <= N;
     float cmax_s = 0.f;
-    acc_t cs[NI][4];
-    float cs_s[NI][4];
+    constexpr int NP = out_passes<DT>(), RPP = 32 / NP;                  // passes of a block's stores, rows of one
+    // this lane's 16 bytes of pass 0 of the wave's first block
+    const int orow = m0 + wm * TM + out_row<DT>(lane), ocol = n0 + wn * TN + out_col<DT>(lane);
+    uint8_t *const dst0 = g.C + ((long)bz * g.sC + (long)orow * g.ldc + ocol) * OS;
+    const long pass_bytes = (long)RPP * g.ldc * OS;
+    // what is left of a lane's 16 bytes at the right edge is the same for all lanes there
+    const int left = (N * OS) & 15;
+    acc_t cs[NI][16];
+    float cs_s[NI][16];
+    if (PROT) {
 #pragma unroll
-    for (int ni = 0; ni < NI; ++ni)
+        for (int ni = 0; ni < NI; ++ni)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) { cs[ni][e] = T::zero(); cs_s[ni][e] = 0.f; }
-    auto wave_sync = [&]() __attribute__((always_inline)) {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    };
+            for (int i = 0; i < 16; ++i) { cs[ni][i] = T::zero(); cs_s[ni][i] = 0.f; }
+    }
     static_for<0, MI>([&](auto mi_c) {
         constexpr int mi = decltype(mi_c)::value;
-        const int row0 = m0 + wm * TM + mi * 32 + (lane >> 3);           // this lane's row of pass 0; pass p: + 8 p
-        acc_t rsum[4] = {T::zero(), T::zero(), T::zero(), T::zero()};
-        float rsum_s[4] = {0.f, 0.f, 0.f, 0.f};
+        const int row = m0 + wm * TM + mi * 32 + l32;
+        acc_t rsum = T::zero();
+        float rsum_s = 0.f;
         static_for<0, NI>([&](auto ni_c) {
             constexpr int ni = decltype(ni_c)::value;
+            const int c0 = n0 + wn * TN + ni * 32;
+            acc_t v[16];
 #pragma unroll
-            for (int q = 0; q < 4; ++q)
-                *reinterpret_cast<i32x4 *>(stage + (l32 * TILE_STAGE_ROW + 8 * q + 4 * lh) * 4) =
-                    i32x4{(int)as_word(acc[mi][ni][4 * q]), (int)as_word(acc[mi][ni][4 * q + 1]),
-                          (int)as_word(acc[mi][ni][4 * q + 2]), (int)as_word(acc[mi][ni][4 * q + 3])};
-            wave_sync();
-            i32x4 w4[4];
-#pragma unroll
-            for (int p = 0; p < 4; ++p)
-                w4[p] = *reinterpret_cast<const i32x4 *>(stage + ((8 * p + (lane >> 3)) * TILE_STAGE_ROW + 4 * (lane & 7)) * 4);
-            wave_sync();                                                 // the stage is free for the next block
-            const int gc = n0 + wn * TN + ni * 32 + 4 * (lane & 7);
-            const bool cfull = gc + 4 <= N;
-            if (inj_here) {
+            for (int i = 0; i < 16; ++i) v[i] = acc[mi][ni][i];
+            if (inj_here && row == g.inj_row) {
                 // the armed flip: one bit of one accumulator, before rounding and before the sums
 #pragma unroll
-                for (int p = 0; p < 4; ++p)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        if (row0 + 8 * p == g.inj_row && g.inj_col == gc + e) w4[p][e] ^= (int)(1u << g.inj_bit);
+                for (int i = 0; i < 16; ++i)
+                    if (c0 + 8 * (i >> 2) + 4 * lh + (i & 3) == g.inj_col) v[i] = from_word<acc_t>(as_word(v[i]) ^ (1u << g.inj_bit));
             }
+            if (g.bias) {
 #pragma unroll
-            for (int p = 0; p < 4; ++p) {
-                const bool rv = row0 + 8 * p < M;
-                acc_t v[4];
+                for (int q = 0; q < 4; ++q) {
+                    const i32x4 b4 = *reinterpret_cast<const i32x4 *>(bias_lds + wn * TN + ni * 32 + 8 * q + 4 * lh);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] = add_t(from_word<acc_t>((uint32_t)w4[p][e]), bias4[ni][e]);
-                if (PROT) {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const acc_t x = (rv && gc + e < N) ? v[e] : T::zero();
-                        cs[ni][e] = add_t(cs[ni][e], x);
-                        rsum[p] = add_t(rsum[p], x);
-                    }
+                    for (int e = 0; e < 4; ++e) v[4 * q + e] = add_t(v[4 * q + e], from_word<acc_t>((uint32_t)b4[e]));
                 }
-                uint8_t *dst = Cb + ((long)(row0 + 8 * p) * g.ldc + gc) * OS;
-                if constexpr (T::IS_INT) {
-                    if (rv && cfull) {
-                        *reinterpret_cast<i32x4 *>(dst) = i32x4{v[0], v[1], v[2], v[3]};
-                    } else if (rv) {
+            }
+            if (PROT && !inside) {
+                // past the edges: values of the last row and column again, in no sum
 #pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            if (gc + e < N) reinterpret_cast<int *>(dst)[e] = v[e];
-                    }
-                } else {
-                    const uint32_t lo = pack2<DT>(v[0], v[1]), hi = pack2<DT>(v[2], v[3]);
-                    if (sto) {
-                        float sv[4];
-                        if constexpr (DT == DT_BF16) {
-                            sv[0] = __uint_as_float(lo << 16); sv[1] = __uint_as_float(lo & 0xFFFF0000u);
-                            sv[2] = __uint_as_float(hi << 16); sv[3] = __uint_as_float(hi & 0xFFFF0000u);
-                        } else {
-                            sv[0] = f16_bits_to_f32(lo & 0xFFFFu); sv[1] = f16_bits_to_f32(lo >> 16);
-                            sv[2] = f16_bits_to_f32(hi & 0xFFFFu); sv[3] = f16_bits_to_f32(hi >> 16);
-                        }
+                for (int i = 0; i < 16; ++i) v[i] = row < M && c0 + 8 * (i >> 2) + 4 * lh + (i & 3) < N ? v[i] : T::zero();
+            }
+            if (PROT) {
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            const float x = (rv && gc + e < N) ? sv[e] : 0.f;
-                            cs_s[ni][e] += x;
-                            rsum_s[p] += x;
-                            cmax_s = fmaxf(cmax_s, fabsf(x));
-                        }
+                for (int i = 0; i < 16; ++i) cs[ni][i] = add_t(cs[ni][i], v[i]);
+                rsum = add_t(rsum, sum16<acc_t>(v));
+            }
+            i32x4 out[NP];
+            if constexpr (T::IS_INT) {
+                uint32_t w[16];
+#pragma unroll
+                for (int i = 0; i < 16; ++i) w[i] = (uint32_t)v[i];
+                turn_block<DT>(w, out);
+            } else {
+                uint32_t w[8];
+                pack_block<DT>(v, w);
+                if (sto) {
+                    float sv[16];
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) { sv[2 * j] = unpack_lo<DT>(w[j]); sv[2 * j + 1] = unpack_hi<DT>(w[j]); }
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) {
+                        cs_s[ni][i] += sv[i];
+                        cmax_s = fmaxf(cmax_s, fabsf(sv[i]));
                     }
-                    if (rv && cfull) {
-                        typedef __attribute__((ext_vector_type(2))) unsigned int u32x2;
-                        *reinterpret_cast<u32x2 *>(dst) = u32x2{lo, hi};
-                    } else if (rv) {
-                        uint16_t *d16 = reinterpret_cast<uint16_t *>(dst);
-                        if (gc + 0 < N) d16[0] = (uint16_t)(lo & 0xFFFFu);
-                        if (gc + 1 < N) d16[1] = (uint16_t)(lo >> 16);
-                        if (gc + 2 < N) d16[2] = (uint16_t)(hi & 0xFFFFu);
-                        if (gc + 3 < N) d16[3] = (uint16_t)(hi >> 16);
+                    rsum_s += sum16<float>(sv);
+                }
+                turn_block<DT>(w, out);
+            }
+            uint8_t *dst = dst0 + (long)(mi * 32) * g.ldc * OS + ni * 32 * OS;
+            if (inside) {
+#pragma unroll
+                for (int p = 0; p < NP; ++p) *reinterpret_cast<i32x4 *>(dst + p * pass_bytes) = out[p];
+            } else {
+                const int gc = ocol + ni * 32, rows = M - (orow + mi * 32);      // valid rows from this lane's first on
+                if (gc + 16 / OS <= N) {
+#pragma unroll
+                    for (int p = 0; p < NP; ++p)
+                        if (p * RPP < rows) *reinterpret_cast<i32x4 *>(dst + p * pass_bytes) = out[p];
+                } else if (gc < N) {
+                    // in falling powers of two, all passes of a size together: few branches
+                    if (left & 8) {
+#pragma unroll
+                        for (int p = 0; p < NP; ++p)
+                            if (p * RPP < rows) *reinterpret_cast<i32x2 *>(dst + p * pass_bytes) = i32x2{out[p][0], out[p][1]};
+                    }
+                    if (left & 4) {
+                        const int at = left & 8;
+#pragma unroll
+                        for (int p = 0; p < NP; ++p)
+                            if (p * RPP < rows) *reinterpret_cast<int *>(dst + p * pass_bytes + at) = at ? out[p][2] : out[p][0];
+                    }
+                    if (left & 2) {
+                        const int at = left & 12;
+#pragma unroll
+                        for (int p = 0; p < NP; ++p)
+                            if (p * RPP < rows)
+                                *reinterpret_cast<uint16_t *>(dst + p * pass_bytes + at) =
+                                    (uint16_t)(at & 8 ? (at & 4 ? out[p][3] : out[p][2]) : (at & 4 ? out[p][1] : out[p][0]));
                     }
                 }
             }
         });
         if (PROT) {
-#pragma unroll
-            for (int p = 0; p < 4; ++p) {
-                const acc_t r = row8_sum(rsum[p]);
-                if ((lane & 7) == 0) rs_part[wn * BM + wm * TM + mi * 32 + 8 * p + (lane >> 3)] = r;
-                if constexpr (!T::IS_INT) {
-                    if (sto) {
-                        const float rs = row8_sum(rsum_s[p]);
-                        if ((lane & 7) == 0) rs_sto[wn * BM + wm * TM + mi * 32 + 8 * p + (lane >> 3)] = rs;
-                    }
+            const acc_t r = add_xor32(rsum);
+            if (lane < 32) rs_part[wn * BM + wm * TM + mi * 32 + lane] = r;
+            if constexpr (!T::IS_INT) {
+                if (sto) {
+                    const float rs = add_xor32(rsum_s);
+                    if (lane < 32) rs_sto[wn * BM + wm * TM + mi * 32 + lane] = rs;
                 }
             }
         }
     });
     if (PROT) {
-        auto over_rows = [&](auto v) __attribute__((always_inline)) {
-            v = add_t(v, dpp_get<0x128>(v));                              // lane ^ 8
-            v = add_xor16(v);
-            return add_xor32(v);
-        };
 #pragma unroll
-        for (int ni = 0; ni < NI; ++ni)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const acc_t t = over_rows(cs[ni][e]);
-                if (lane < 8) cs_part[wm * BN + wn * TN + ni * 32 + 4 * lane + e] = t;
-                if constexpr (!T::IS_INT) {
-                    if (sto) {
-                        const float ts = over_rows(cs_s[ni][e]);
-                        if (lane < 8) cs_sto[wm * BN + wn * TN + ni * 32 + 4 * lane + e] = ts;
-                    }
+        for (int ni = 0; ni < NI; ++ni) {
+            const acc_t t = fold16<acc_t>(cs[ni], lane);
+            if ((lane & 1) == 0) cs_part[wm * BN + wn * TN + ni * 32 + fold16_column(lane)] = t;
+            if constexpr (!T::IS_INT) {
+                if (sto) {
+                    const float ts = fold16<float>(cs_s[ni], lane);
+                    if ((lane & 1) == 0) cs_sto[wm * BN + wn * TN + ni * 32 + fold16_column(lane)] = ts;
                 }
             }
+        }
         if constexpr (!T::IS_INT) {
             if (sto) {
                 cmax_s = wave_max(cmax_s);
-                if (lane == 0) *reinterpret_cast<float *>(stage) = cmax_s;       // (the wave is done with its stage)
+                if (lane == 0) max_part[wave] = cmax_s;
             }
             if (APASS && !g.a_given) {
                 const float m = wave_max(ast.amax);
-                if (lane == 0) *reinterpret_cast<float *>(stage + 4) = m;
+                if (lane == 0) max_part[4 + wave] = m;
             }
         }
         // over LDS traffic only: a full barrier would also wait for every store of C
@@ -531,7 +544,7 @@ __global__ __launch_bounds__(256) void gemm_tile_kernel(typename KernelArgs<ONE>
             auto publish = [&](uint32_t *word, int at) __attribute__((always_inline)) {
                 float m = 0.f;
 #pragma unroll
-                for (int w = 0; w < 4; ++w) m = fmaxf(m, *reinterpret_cast<const float *>(smem + w * TILE_STAGE_WAVE + at));
+                for (int w = 0; w < 4; ++w) m = fmaxf(m, max_part[at + w]);
                 if (m > 0.f) atomicMax(word + bz, __float_as_uint(m));
             };
             if (sto && tid == 0) publish(g.c_max, 0);
@@ -545,9 +558,9 @@ __global__ __launch_bounds__(256) void gemm_tile_kernel(typename KernelArgs<ONE>
 static int slabs_of(int dt, int K) { return (int)(((long)K * elem_size(dt) + SLAB_BYTES - 1) / SLAB_BYTES); }
 
 template <int DT, int BM, int BN, int NS, bool PROT, bool TRANSB, bool APASS = false, bool ONE = false>
-static hipError_t launch_one(OneArgs &a, int batch, hipStream_t st)
+static hipError_t launch_one(HostArgs &a, int batch, hipStream_t st)
 {
-    constexpr int smem_max = APASS || ONE ? 160 * 1024 : tile_lds_bytes(BM, BN, NS);
+    constexpr int smem_max = APASS || ONE ? 160 * 1024 : tile_lds_bytes(BM, BN, NS) + BN * 4;
     static_assert(tile_lds_bytes(BM, BN, 1) >= 256 * 16 * 4, "the passes over A and B use 16 KB");
     auto kern = gemm_tile_kernel<DT, BM, BN, NS, PROT, TRANSB, APASS, ONE>;
     if (smem_max > 48 * 1024) {
@@ -566,8 +579,15 @@ static hipError_t launch_one(OneArgs &a, int batch, hipStream_t st)
         a.p.wgs = a.n_extra + a.n_tiles;
         a.p.tiles_m = a.g.tiles_m; a.p.tiles_n = a.g.tiles_n; a.p.bm = BM; a.p.bn = BN;
     }
+    a.bias_off = smem = (smem + 15) & ~15;
+    if (a.g.bias) smem += BN * 4;
     dim3 grid((unsigned)(a.n_extra + a.n_tiles), (unsigned)batch, 1);
-    hipLaunchKernelGGL(kern, grid, dim3(256), smem, st, a);
+    if constexpr (ONE) {
+        const OneArgs k = {a.g, a.n_extra, a.n_tiles, a.aux_off, a.bias_off, a.p};
+        hipLaunchKernelGGL(kern, grid, dim3(256), smem, st, k);
+    } else {
+        hipLaunchKernelGGL(kern, grid, dim3(256), smem, st, (const TileArgs &)a);
+    }
     return hipGetLastError();
 }
 
@@ -607,7 +627,7 @@ static bool fuses_a(int dt, const Shape &s, int nslab, int *bm)
     const int tiles_n = (s.N + 127) / 128;
     const long tiles = tiles_of(s.M, s.N, s.batch, *bm, 128);
     return tiles >= 128 && tiles >= (s.transB ? 4 : 24) * apass_owned_slabs(nslab, tiles_n) && tiles / s.batch <= MAX_GRID_X &&
-           tile_lds_bytes(*bm, 128, 3) + apass_lds_bytes(dt, nslab, tiles_n) <= 160 * 1024;
+           tile_lds_bytes(*bm, 128, 3) + apass_lds_bytes(dt, nslab, tiles_n) + 128 * 4 <= 160 * 1024;       // (with the bias of a tile's columns)
 }
 
 // 64 x 64, 64 x 128 or 128 x 128 tiles.  Wider tiles cost less LDS traffic per product, but a problem of few
@@ -639,10 +659,11 @@ static void tile_size(int M, int N, int nslab, int batch, bool beside, int *bm, 
 }
 
 template <int DT, int BM, int BN, int NS>
-static hipError_t launch_cfg(bool protect, bool transB, OneArgs &a, int batch, hipStream_t st)
+static hipError_t launch_cfg(bool protect, bool transB, HostArgs &a, int batch, hipStream_t st)
 {
     a.g.tiles_m = (a.g.M + BM - 1) / BM;
     a.g.tiles_n = (a.g.N + BN - 1) / BN;
+    a.g.group_inv = map_inverse(a.g.tiles_n);
     const long tiles = (long)a.g.tiles_m * a.g.tiles_n;
     if (tiles + a.n_extra > MAX_GRID_X) return hipErrorInvalidValue;
     a.n_tiles = (int)tiles;
@@ -662,7 +683,7 @@ static hipError_t launch_cfg(bool protect, bool transB, OneArgs &a, int batch, h
 // 14.5 with three); otherwise three, for more workgroups on a compute unit (6304 x 768 x 768 on 64 x 64
 // tiles: 17.3 us against 20.2 with four).
 template <int DT>
-static hipError_t launch_tile(bool protect, bool transB, OneArgs &a, int batch, hipStream_t st)
+static hipError_t launch_tile(bool protect, bool transB, HostArgs &a, int batch, hipStream_t st)
 {
     int bm = a.fuse_bm, bn = 128;
     if (!bm) tile_size(a.g.M, a.g.N, slabs_of(DT, a.g.K), batch, protect, &bm, &bn);
@@ -842,7 +863,7 @@ hipError_t launch_gemm(int dt, bool protect, bool stored_sums, bool encode_b, co
     // 256 items 24.4 -> 25.0 us): such a call is tiled, C comes out bit for bit the same.
     if (!protect && !w.bias && arm.batch < 0 && gemm_item_eligible(dt, s, false, false))
         return launch_gemm_item(dt, false, false, false, A, B, C, s, w, nullptr, arm, st);
-    OneArgs a;
+    HostArgs a;
     GemmArgs &g = a.g;
     g.A = (const uint8_t *)A;
     g.B = (const uint8_t *)B;
