@@ -2511,3 +2511,106 @@ def test_tiles_that_reduce_a_with_every_option(ctx_large, dtype):
     assert np.max(np.abs(a1[~hit_a] - a0[~hit_a])) <= 2.0 ** -23 * M * big
     assert np.max(np.abs(r1[~want_r] - r0[~want_r])) <= 2.0 ** -23 * K * big * N * max(p.max_b for p in P)
     assert np.max(np.abs(s1[~want_r] - s0[~want_r])) <= 2.0 ** -23 * N * np.max(np.abs(s0))
+
+
+@pytest.mark.parametrize("dtype", ["i8", "bf16", "f16"])
+@pytest.mark.parametrize("M,N,K,trans_b", [(165, 163, 77, True), (161, 168, 1100, True), (190, 165, 115, False), (167, 161, 2049, False),
+                                           (163, 166, 4096, True)])
+@pytest.mark.parametrize("spots", [1, 4, 5])
+def test_repair_by_parts_and_by_whole_tiles(ctx, dtype, M, N, K, trans_b, spots):
+    """Flips on a diagonal: up to sixteen tiles (four rows by four columns) are recomputed in parts of 8 x 8, twenty-five whole.  Last
+    rows and columns, parts that hang over the edge, depths of no whole step, chunk or slab; C comes back bit for bit."""
+    A, B = gen.gen_operands(dtype, M, N, K, 901 + K, 902 + M, trans_b=trans_b)
+    run = Run(ctx, dtype, A, B, trans_b)
+    run.gemm(ab.ABFT_DETECT)
+    C = run.C().copy()
+    run.verify()
+    assert run.cnt()[2] == ab.ABFT_CLEAN
+    at = [(M - 1 - 33 * s, N - 1 - 33 * s) for s in range(spots)]                # each in a tile row and tile column of its own
+    for s, (i, j) in enumerate(at):
+        run.inject(0, i, j, 30 - s if dtype == "i8" else 14)
+    run.verify()
+    rf, cf = run.flags()
+    assert sorted(np.flatnonzero(rf[0])) == sorted(i for i, _ in at) and sorted(np.flatnonzero(cf[0])) == sorted(j for _, j in at)
+    run.correct()
+    cnt = run.cnt()
+    assert np.array_equal(run.C(), C) and cnt[0] == 0 and cnt[1] == 0 and cnt[2] == ab.ABFT_CLEAN and cnt[3] == spots * spots
+    assert cnt[4] == ab.ABFT_LOCALISED
+    run.verify()
+    assert run.cnt()[2] == ab.ABFT_CLEAN
+
+
+def test_repair_of_more_flags_than_are_listed(ctx):
+    """Seventy flagged rows in seventy tile rows: more than a correction lists.  It repairs the first 64 tile rows and says so."""
+    M, N, K = 70 * 32, 64, 64
+    A, B = gen.gen_operands("i8", M, N, K, 911, 912, trans_b=True)
+    run = Run(ctx, "i8", A, B, True)
+    run.gemm(ab.ABFT_DETECT)
+    C = run.C().copy()
+    for s in range(70):
+        run.inject(0, 32 * s + 5, 3, s % 24)
+    run.verify()
+    assert run.cnt()[0] == 70 and run.cnt()[1] == 1
+    run.correct()
+    cnt, got = run.cnt(), run.C()
+    assert cnt[2] == ab.ABFT_TOO_MANY and cnt[3] == 64 and cnt[0] == 6
+    assert np.array_equal(got[0, :64 * 32], C[0, :64 * 32]) and (got[0] != C[0]).sum() == 6
+    run.correct()                                           # six tiles are left
+    assert run.cnt()[2] == ab.ABFT_CLEAN and run.cnt()[3] == 6 and np.array_equal(run.C(), C)
+
+
+@pytest.mark.parametrize("M,batch", [(32704, 1), (32736, 1), (700, 3)])
+def test_repair_with_the_list_from_either_kernel(M, batch):
+    """Up to 32768 flags of one problem the recompute finds its tiles itself, beyond and for batches a kernel lists them; one after the
+    other in one context, so that each finds the list as the other leaves it."""
+    own = ab.abft_create(max_rows=32768, max_cols=256, max_depth=256, max_batch=4)
+    try:
+        for m, b in ((M, batch), (300, 1), (M, batch), (300, 2)):
+            N, K = 64, 64
+            A, B = gen.gen_operands("i8", m, N, K, 921, 922, trans_b=True, batch=b)
+            run = Run(own, "i8", A, B, True)
+            run.gemm(ab.ABFT_DETECT)
+            C = run.C().copy()
+            run.inject(b - 1, m - 1, N - 1, 7)
+            run.verify()
+            run.correct()
+            assert run.cnt()[2] == ab.ABFT_CLEAN and run.cnt()[3] == 1 and np.array_equal(run.C(), C)
+            run.gemm(ab.ABFT_DETECT_CORRECT)
+            assert run.cnt()[2] == ab.ABFT_CLEAN and np.array_equal(run.C(), C)
+    finally:
+        ab.abft_destroy(own)
+
+
+@pytest.mark.parametrize("ld", [1 << 19, (1 << 19) + 16])
+def test_items_with_wide_rows(ctx_items, ld):
+    """Items take rows of up to 512 KB (their offsets are 32-bit numbers), wider ones the tiles: the same C and flags."""
+    M, N, K, batch = 45, 37, 64, 64
+    A, B = gen.gen_operands("i8", M, N, K, 931, 932, trans_b=True, batch=batch)
+    P = oracle_items("i8", A, B, True)
+    dA = torch.full((M, ld), 0x55, dtype=torch.int8, device="cuda")                      # heads side by side in a row
+    dA[:, :batch * K] = torch.from_numpy(np.ascontiguousarray(A.transpose(1, 0, 2)).reshape(M, batch * K)).to("cuda")
+    dB = torch.from_numpy(np.ascontiguousarray(B)).to("cuda")
+    dC = torch.zeros((batch, M, 40), dtype=torch.int32, device="cuda")
+    shape = ab.make_shape(M, N, K, batch=batch, lda=ld, ldb=K, ldc=40, strideA=K, strideB=N * K, strideC=M * 40, transB=True)
+    rf, cf = (torch.full((batch * n,), 7, dtype=torch.uint8, device="cuda") for n in (M, N))
+    cnt = torch.full((8,), 99, dtype=torch.int32, device="cuda")
+    rc = ab.abft_gemm(ctx_items, dA, dB, dC, ab.ABFT_I8, ab.ABFT_DETECT, shape, ab.make_result(rf, cf, cnt, 0.0))
+    assert rc == ab.ABFT_OK, ab.abft_strerror(rc)
+    torch.cuda.synchronize()
+    assert cnt[2].item() == ab.ABFT_CLEAN and not rf.any() and not cf.any()
+    got = dC.cpu().numpy()
+    assert all(np.array_equal(got[b, :, :N], P[b].C_stored) for b in range(batch)) and not got[:, :, N:].any()
+
+
+@pytest.mark.parametrize("dtype", ["i8", "bf16", "f16"])
+@pytest.mark.parametrize("N", [65, 66, 67, 68, 69, 70, 71, 72, 129])
+@pytest.mark.parametrize("M,batch", [(65, 1), (100, 2), (33, 64)])
+def test_right_edges_of_c(ctx_items, dtype, N, M, batch):
+    """Every remainder of a row of C by sixteen bytes, tiles and items that hang over both edges: C, sums, flags, and nothing written past N."""
+    K = 80
+    A, B = gen.gen_operands(dtype, M, N, K, 941 + N, 942 + M, trans_b=True, batch=batch, b_kind="act")
+    run = Run(ctx_items, dtype, A, B, True)
+    run.gemm(ab.ABFT_DETECT)
+    check_clean(run, oracle_items(dtype, A, B, True))
+    pad = run.dC.cpu().numpy()[:, :, N:]
+    assert (pad == (0x5A5A5A5A if dtype == "i8" else 0x5A5A)).all()
