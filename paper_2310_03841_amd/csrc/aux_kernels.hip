@@ -902,7 +902,8 @@ struct FixArgs {
 // whole lines each, and a tile's operands are 64 rows; a part's are sixteen, and eight lanes read 128 bytes of one, where a
 // fragment's lanes read 32.  The MFMAs are the same, in the same order, on rows and columns repeated four times over: an
 // element's bits depend on its own row and column only.  (Of integers the order does not matter: four waves take a quarter each.)
-// us a launch: int8 6304 x 768 x 3072 10.2 -> 5.9, f16 the same 18 -> 9.
+// int8 6304 x 768 x 3072: a launch 10.2 us and 3.3 for the list ahead of it, 8.3 with the search in it; flip, verify and repair 30.4 -> 24.8, f16 37.6 ->
+// 27.7.
 constexpr int FIX_PARTS = 16, FIX_PART = 8;     // parts of a tile, rows and columns of one
 constexpr int FIX_GROUP = FIX_WAVES * 8;        // slabs in LDS at a time: 512 bytes for each step of 32 bytes of K
 static_assert(FIX_GROUP * 4 * 512 == FIX_LDS_BYTES, "the parts' steps fill what a whole tile's run takes");

@@ -249,7 +249,7 @@ __device__ __forceinline__ void b_scale(int N, float *scale, float *back)
 }
 
 // d0 += b x[0], d1 += b x[1] and c = x[0], x[1] turned and added up; operands and results in vector registers.  As instructions: the
-// built-in's results would be given accumulation registers, which the tile fills.  The waits cover what the compiler does not
+// built-in's results would be given accumulation registers in the kernels that keep their accumulators there, which the tile fills.  The waits cover what the compiler does not
 // see in here: operands written by vector instructions just ahead, results read right behind.
 template <int DT> struct TurnSums { typename Acc4<DT>::type c[2]; };
 #define ABFT_M16(OP, D, A, B, C) OP " %" D ", %" A ", %" B ", " C "\n\t"

@@ -125,7 +125,7 @@ __device__ __forceinline__ void fast_tile(const GemmArgs &g, uint8_t *smem, int 
 
     // The accumulators are never zero-filled: the first MFMA of every block takes a literal
     // zero as its addend.  Every block is always computed, also where the tile hangs over the
-    // edge of the problem: a conditional MFMA would force the accumulators out of the AGPRs.
+    // edge of the problem: a conditional MFMA would move the accumulators out of their registers.
     accv_t acc[MI][NI];
     accv_t zerov;
 #pragma unroll

@@ -8,7 +8,9 @@
 // waves by blocks of rows.
 //
 // Measured (384 items 197 x 197 x 64 bf16, Q K^T of 32 images; floor 9.8 us): 32.0 us with four waves per item, C
-// through an LDS stage and the sums along K in vector instructions, 21.5 so, 12.9 unprotected (before: 18.0).
+// through an LDS stage and the sums along K in vector instructions, 21.2 so, 18.5 since the phases read their own arguments (item_args), 12.9
+// unprotected (before: 18.0).  A compute unit with two items is bound by its vector instructions: reading the main loop's fragments a piece ahead, or
+// dealing the pass over B to all waves, which each cost some more of them, gained nothing (21.4, and 2 to 4 % slower elsewhere).
 // int8 1024 x 577 x 577 x 64 (1.44 GB, floor 285 us): 432 us, so 378 (on another
 // card 412 and 349); bound by the stores of C, whose rows
 // are 16-byte aligned only.

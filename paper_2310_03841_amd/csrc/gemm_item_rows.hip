@@ -10,10 +10,9 @@
 // sums and the row dot stay with the lane that owns the row.
 //
 // Measured (384 items 197 x 64 x 197 bf16, attn V of 32 images; floor 9.8 us): 45.8 us with one workgroup
-// of four computing waves and a loading wave per item and the sums along K in vector instructions, 21.9
-// so, 11.5 unprotected (before: 21.5).  What bounds it: an item is one chain of about 2500 instructions per wave
-// (load B, b, the row blocks, the checks) and the 384 items are 1.5 for each compute unit; with 768 items
-// it reaches 2.9 TB/s.
+// of four computing waves and a loading wave per item and the sums along K in vector instructions, 21.6
+// so, 19.8 since the phases read their own arguments (item_args), 11.5 unprotected (before: 21.5).  What bounds it: an item is one chain of some
+// 2000 instructions per wave (load B, b, the row blocks, the checks) and the 384 items are 1.5 for each compute unit.
 #include "gemm_item.h"
 
 namespace abft {

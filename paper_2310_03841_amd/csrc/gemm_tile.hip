@@ -5,7 +5,8 @@
 //
 // What bounds these problems is not arithmetic or bandwidth but the chain of latencies of a call.
 // A call of few tiles is therefore one launch (predict_pass.h): workgroups beside the tiles form both predictions, and who
-// is last compares.  Call after call, in us, two launches / one: int8 197 x 768 x 768 8.7 / 7.5, 3000 x 128 x 1024 14.2 / 9.3, bf16
+// is last compares.  Call after call, in us, two launches / one (both with the epilogue and the start of before; one now: int8 197 x 768 x 768
+// 7.2, bf16 197 x 768 x 3072 14.4): int8 197 x 768 x 768 8.7 / 7.5, 3000 x 128 x 1024 14.2 / 9.3, bf16
 // 197 x 768 x 3072 16.4 / 15.4, 64 x 500 x 3072 with B stored K x N 25.1 / 18.9.  (A call takes 3 us before its first and after its
 // last workgroup; a second kernel adds that gap, a trip to memory and a reduction.)
 // More tiles, or predictions that would take longer than they: the input-side vectors a = e^T A and b = B e, which depend
@@ -16,7 +17,9 @@
 // Tile: BM x BN by four waves of (BM/2) x (BN/2), 32 x 32 MFMA blocks.  K advances in slabs of 128
 // bytes per row of A.  Slabs go from global memory straight into LDS (global_load_lds_dwordx4),
 // NS buffers deep, so NS - 1 slabs are in flight while one is multiplied; one barrier per slab.
-// The fragments of slab s are read while the MFMAs of slab s - 1 run (two register sets).
+// The fragments of slab s are read while the MFMAs of slab s - 1 run (two register sets).  A slab of a 64 x 64 tile takes some 490 clocks, alone on a compute
+// unit; eight buffers instead of four do not change that (fc2 of one image 14.35 -> 14.7 us, 197 x 3072 x 768 10.6 -> 11.0), and loads dealt out between the MFMAs,
+// as the fast kernel has them, come too late (14.3 -> 17.0, 10.4 -> 11.0).
 //
 // LDS: rows of 128 bytes as eight 16-byte chunks, chunk c of row r in slot c ^ ((r >> 1) & 7)
 // (sixteen consecutive rows of a fragment read then fall on sixteen different 16-byte bank groups).
