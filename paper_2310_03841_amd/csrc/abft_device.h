@@ -291,6 +291,44 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v)
     return q[0] > q[1] ? q[0] : q[1];
 }
 
+// ---------------------------------------------------------------- sums over the 32 lanes of a half-wave
+__device__ __forceinline__ uint32_t item_bits(int v) { return (uint32_t)v; }
+__device__ __forceinline__ uint32_t item_bits(float v) { return __float_as_uint(v); }
+
+// lanes with bit 4 clear get a, the others b, each summed over lane and lane ^ 16
+template <typename V> __device__ __forceinline__ V fold_xor16(V a, V b)
+{
+    auto p = __builtin_amdgcn_permlane16_swap(item_bits(a), item_bits(b), false, false);
+    return add_t(from_word<V>(p[0]), from_word<V>(p[1]));
+}
+// lanes with up set get b, the others a, each summed with the lane that CTRL names (its `up` is the other one)
+template <int CTRL, typename V> __device__ __forceinline__ V fold_dpp(V a, V b, bool up)
+{
+    const V keep = up ? b : a, send = up ? a : b;
+    return add_t(keep, dpp_get<CTRL>(send));
+}
+// The sixteen values of an accumulator block, each summed over the 32 lanes of a half of the wave; the lane
+// gets the value of column fold16_column(lane)
+template <typename V, typename ACC> __device__ __forceinline__ V fold16(const ACC &v, int lane)
+{
+    V w[8], x[4], y[2];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) w[j] = fold_xor16<V>(v[2 * j], v[2 * j + 1]);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) x[j] = fold_dpp<0x128>(w[2 * j], w[2 * j + 1], (lane & 8) != 0);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) y[j] = fold_dpp<0x141>(x[2 * j], x[2 * j + 1], (lane & 4) != 0);
+    V z = fold_dpp<0x4E>(y[0], y[1], (lane & 2) != 0);
+    return add_t(z, dpp_get<0xB1>(z));
+}
+// column inside a 32 x 32 block of the value fold16 leaves in this lane (register i of a block holds
+// column 8 (i >> 2) + 4 (lane >> 5) + (i & 3); i = 8 b1 + 4 b2 + 2 b3 + b4 in bits of the lane)
+__device__ __forceinline__ int fold16_column(int lane)
+{
+    const int i = ((lane & 2) << 2) + (lane & 4) + ((lane >> 2) & 2) + ((lane >> 4) & 1);
+    return 8 * (i >> 2) + 4 * (lane >> 5) + (i & 3);
+}
+
 // Sum of the layer bias over its N entries, by the whole block (every thread gets the total).
 template <typename acc_t>
 __device__ __forceinline__ acc_t block_bias_sum(const uint32_t *bias, int N, acc_t *red4)
