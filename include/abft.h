@@ -267,8 +267,10 @@ int abft_verify(abft_ctx *ctx, const void *C, abft_dtype dtype, const abft_shape
  * when the context holds the sums of this stored C (the last call on it was abft_verify,
  * abft_correct or abft_correct_checksum, and C has not been written since), only the rows and the
  * columns of the recomputed tiles are summed again; otherwise the whole stored C is, as
- * abft_verify does.  At most 256 tiles per call; beyond that status = ABFT_TOO_MANY and the
- * caller replays the GEMM.  A and B must be unchanged since abft_gemm. */
+ * abft_verify does.  At most 256 tiles per call, of at most 64 rows and 64 columns of tiles; of a
+ * batch, or where M + N is above 32768, tiles of at most 64 flagged rows and 64 flagged columns of
+ * an item.  Beyond that status = ABFT_TOO_MANY and the caller replays the GEMM.  A and B must be
+ * unchanged since abft_gemm. */
 int abft_correct(abft_ctx *ctx, const void *A, const void *B, void *C, abft_dtype dtype,
                  const abft_shape *s, const abft_result *r, void *stream);
 

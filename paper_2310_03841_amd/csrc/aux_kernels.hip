@@ -1080,7 +1080,8 @@ __device__ __forceinline__ unsigned find_tiles(const FixArgs &a, FoundTiles *f)
         __syncthreads();
         const int kr = min(ur, MAX_LIST), kc = min(uc, MAX_LIST);
         n = (unsigned)(kr * kc);
-        overflow = nr > MAX_LIST || nc > MAX_LIST || n > (unsigned)MAX_FIX_TILES;
+        // (by tiles, not by flags: a hundred flagged columns of one row are four tiles or five, and all of them are recomputed)
+        overflow = ur > MAX_LIST || uc > MAX_LIST || n > (unsigned)MAX_FIX_TILES;
         f->unique[0] = kr; f->unique[1] = kc;           // (every thread writes the same, and reads them behind the next barrier or itself)
     }
     if (blockIdx.x == 0) {

@@ -2559,6 +2559,27 @@ def test_repair_of_more_flags_than_are_listed(ctx):
     assert run.cnt()[2] == ab.ABFT_CLEAN and run.cnt()[3] == 6 and np.array_equal(run.C(), C)
 
 
+@pytest.mark.parametrize("dtype", ["i8", "bf16"])
+@pytest.mark.parametrize("rows", [True, False])
+def test_repair_of_many_flags_in_few_tiles(ctx, dtype, rows):
+    """A hundred flagged rows (columns) of one column (row): more than 64 flags, but four tiles, all of which are recomputed.  The status
+    speaks of tiles."""
+    M, N, K = 330, 340, 96
+    A, B = gen.gen_operands(dtype, M, N, K, 951, 952, trans_b=True)
+    run = Run(ctx, dtype, A, B, True)
+    run.gemm(ab.ABFT_DETECT)
+    C = run.C().copy()
+    at = [(64 + s, 70) if rows else (70, 64 + s) for s in range(100)]
+    for s, (i, j) in enumerate(at):
+        run.inject(0, i, j, s % 24 if dtype == "i8" else 14)
+    run.verify()
+    assert run.cnt()[0 if rows else 1] == 100 and run.cnt()[1 if rows else 0] == 1
+    run.correct()
+    cnt = run.cnt()
+    assert np.array_equal(run.C(), C) and cnt[0] == 0 and cnt[1] == 0 and cnt[3] == 4
+    assert cnt[2] == ab.ABFT_CLEAN and cnt[4] == ab.ABFT_LOCALISED
+
+
 @pytest.mark.parametrize("M,batch", [(32704, 1), (32736, 1), (700, 3)])
 def test_repair_with_the_list_from_either_kernel(M, batch):
     """Up to 32768 flags of one problem the recompute finds its tiles itself, beyond and for batches a kernel lists them; one after the
