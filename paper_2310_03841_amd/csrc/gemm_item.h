@@ -75,7 +75,7 @@ __device__ __forceinline__ int item_opaque(int v)
 // ------------------------------------------------------------------ operands into LDS
 // Rows [0, rows_total) of `chunks` 16-byte chunks each; what lies past `rows` or past rowbytes is zero.
 // 1 << lg threads share a row.  A batch is ITEM_U independent loads per thread.
-// Buffer loads: what lies outside comes as zeros without a branch, and a load costs one addition.  Offsets stay below 2^31 (item_plan).
+// Buffer loads: what lies outside comes as zeros without a branch, and a load costs one addition.  Offsets stay below 2^31 (item_offsets_fit).
 constexpr int ITEM_U = 4;
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 constexpr int ITEM_RSRC_FLAGS = 0x00027000;
@@ -456,7 +456,7 @@ __device__ __forceinline__ void item_flip(const ItemArgs &g, ACC &acc, int m0, i
 }
 
 // Where an item's C goes: buffer stores, which leave out rows past M without a branch (they lie past the end: the descriptor ends
-// with the last row), and a lane's place in a block as an offset, so that a store costs an addition.  Offsets stay below 2^31 (item_plan).
+// with the last row), and a lane's place in a block as an offset, so that a store costs an addition.  Offsets stay below 2^31 (item_offsets_fit).
 struct ItemOut {
     __amdgpu_buffer_rsrc_t dst;
     int N, ldbytes, lane;

@@ -1,4 +1,6 @@
 // Which batches of small problems one workgroup per item takes, and how (gemm_item.h).
+#include <algorithm>
+
 #include "gemm_item.h"
 
 namespace abft {
@@ -7,7 +9,20 @@ namespace abft {
 // kernel's tiles and check: bf16 Q K^T 197 x 197 x 64, 24 items 15.2 / 12.4 us, 48 items 15.7 / 15.6, 384 items
 // 21.7 / 57.6; int8 attn V 577 x 64 x 577, 16 items 23.8 / 14.7, 48 items 24.4 / 28.9.
 constexpr int ITEM_MIN_BATCH = 64;
-constexpr int ITEM_MAX_N = 640, ITEM_MAX_M = 1024;
+constexpr int ITEM_MAX_N = 640, ITEM_MAX_M = 1024, ITEM_MAX_THREADS = 512;
+
+// Offsets inside an item are 32-bit numbers (ItemStage, ItemOut): the rows that batches of loads reach, past the last one too, and the row blocks of C
+// must end below 2^31 bytes, with a row to spare for what a lane adds along one.  That bounds rows times their distance: up to 1024 rows reached may be 2 MB
+// apart (heads side by side, q, k and v of 16 heads x 64 in bf16: 340 images; a limit of 512 KB sent 86 images to the tiles, at twice the time).
+// Wider ones are for the tiles.  The kernel by rows reads A by whole addresses.
+static bool item_offsets_fit(int dt, const Shape &s, const ItemArgs &g)
+{
+    const long es = elem_size(dt);
+    auto reach = [](int rows, int lg) { const long batch = (long)(ITEM_MAX_THREADS >> lg) * ITEM_U; return (rows + batch - 1) / batch * batch; };
+    auto fits = [](long rows, long ld_bytes) { return ld_bytes <= INT32_MAX / (rows + 1); };
+    if (!fits(reach(g.b_rows, g.b_lg), s.ldb * es) || !fits((long)g.MB * 32, s.ldc * out_size(dt))) return false;
+    return s.N <= 128 || fits(std::max(reach(g.rch * 32, g.a_lg), (long)s.M), s.lda * es);
+}
 
 // Fills in the geometry; returns the bytes of LDS, 0 if the item does not fit.
 static size_t item_plan(int dt, const Shape &s, bool protect, bool sto, ItemArgs *g)
@@ -17,9 +32,6 @@ static size_t item_plan(int dt, const Shape &s, bool protect, bool sto, ItemArgs
     // N <= 128: as deep as B fits in LDS (bf16 attn V of 577 tokens, 400 items: 111 us, on tiles 281; 400
     // tokens of head dimension 128, 300 items: 65 / 131).  Wider items hold whole rows of A beside B.
     if ((long)s.K * es > (s.N <= 128 ? 1600 : s.N <= 256 ? 384 : 256)) return 0;
-    // offsets inside an item as 32-bit numbers: rows this wide are for the tiles
-    constexpr long MAX_LD_BYTES = 1L << 19;
-    if (s.lda * es > MAX_LD_BYTES || s.ldb * es > MAX_LD_BYTES || s.ldc * out_size(dt) > MAX_LD_BYTES) return 0;
     g->M = s.M; g->N = s.N; g->K = s.K; g->batch = s.batch;
     g->nch = (s.K * es + 15) / 16;
     g->steps = ((s.K * es + 31) / 32 + 1) / 2 * 2;
@@ -39,7 +51,8 @@ static size_t item_plan(int dt, const Shape &s, bool protect, bool sto, ItemArgs
     g->a_lg = item_log2(2 * g->steps);
     g->rch = g->MB;
     g->nchunk = 1;
-    return s.N <= 128 ? item_rows_lds(dt, s, protect, sto, g) : item_cols_lds(dt, s, protect, sto, g);
+    const size_t smem = s.N <= 128 ? item_rows_lds(dt, s, protect, sto, g) : item_cols_lds(dt, s, protect, sto, g);
+    return smem && item_offsets_fit(dt, s, *g) ? smem : 0;
 }
 
 // Where B leaves room for one block of rows of A at a time only, an item has a barrier per block and the

@@ -2602,25 +2602,64 @@ def test_repair_with_the_list_from_either_kernel(M, batch):
         ab.abft_destroy(own)
 
 
-@pytest.mark.parametrize("ld", [1 << 19, (1 << 19) + 16])
-def test_items_with_wide_rows(ctx_items, ld):
-    """Items take rows of up to 512 KB (their offsets are 32-bit numbers), wider ones the tiles: the same C and flags."""
-    M, N, K, batch = 45, 37, 64, 64
-    A, B = gen.gen_operands("i8", M, N, K, 931, 932, trans_b=True, batch=batch)
-    P = oracle_items("i8", A, B, True)
-    dA = torch.full((M, ld), 0x55, dtype=torch.int8, device="cuda")                      # heads side by side in a row
-    dA[:, :batch * K] = torch.from_numpy(np.ascontiguousarray(A.transpose(1, 0, 2)).reshape(M, batch * K)).to("cuda")
-    dB = torch.from_numpy(np.ascontiguousarray(B)).to("cuda")
-    dC = torch.zeros((batch, M, 40), dtype=torch.int32, device="cuda")
-    shape = ab.make_shape(M, N, K, batch=batch, lda=ld, ldb=K, ldc=40, strideA=K, strideB=N * K, strideC=M * 40, transB=True)
-    rf, cf = (torch.full((batch * n,), 7, dtype=torch.uint8, device="cuda") for n in (M, N))
-    cnt = torch.full((8,), 99, dtype=torch.int32, device="cuda")
-    rc = ab.abft_gemm(ctx_items, dA, dB, dC, ab.ABFT_I8, ab.ABFT_DETECT, shape, ab.make_result(rf, cf, cnt, 0.0))
-    assert rc == ab.ABFT_OK, ab.abft_strerror(rc)
-    torch.cuda.synchronize()
-    assert cnt[2].item() == ab.ABFT_CLEAN and not rf.any() and not cf.any()
-    got = dC.cpu().numpy()
-    assert all(np.array_equal(got[b, :, :N], P[b].C_stored) for b in range(batch)) and not got[:, :, N:].any()
+@pytest.mark.parametrize("which,M,N,trans_b", [("A", 45, 37, True), ("A", 45, 140, True), ("B", 45, 37, True), ("B", 45, 140, True), ("B", 45, 140, False),
+                                               ("C", 1, 40, True), ("C", 1, 140, True)])
+def test_items_with_wide_rows(which, M, N, trans_b):
+    """Offsets inside an item are 32-bit numbers: items take rows up to where the last one reached begins below 2^31 bytes, wider ones the
+    tiles, with the same C and flags.  Both sides of the line, by operand; the kernel by rows (N <= 128) takes rows of A of any width."""
+    K, batch = 64, 64
+    A, B = gen.gen_operands("i8", M, N, K, 931, 932, trans_b=trans_b, batch=batch)
+    P = oracle_items("i8", A, B, trans_b)
+    own = ab.abft_create(max_rows=batch * M, max_cols=batch * N, max_depth=batch * 128, max_batch=batch)
+
+    def shape_at(ld):
+        wide = {"lda": ld, "strideA": K} if which == "A" else {"ldb": ld, "strideB": K if trans_b else 144} if which == "B" else {"ldc": ld, "strideC": M * ld}
+        kw = {"lda": K, "strideA": M * K, "ldb": K if trans_b else 144, "strideB": N * K if trans_b else 144 * K, "ldc": 144, "strideC": M * 144}
+        return ab.make_shape(M, N, K, batch=batch, transB=trans_b, **{**kw, **wide})
+
+    def item(ld):
+        return ab.abft_tile_shape(ab.ABFT_I8, shape_at(ld)) == (M, N)
+
+    def operand(X, ld, stride, wide):                       # items side by side in rows of ld, or one behind the other
+        if not wide:
+            out = torch.full((batch, X.shape[1], ld), 0x55, dtype=torch.int8, device="cuda")
+            out[:, :, :X.shape[2]] = torch.from_numpy(np.ascontiguousarray(X)).to("cuda")
+            return out
+        out = torch.full((X.shape[1], ld), 0x55, dtype=torch.int8, device="cuda")
+        side = np.full((X.shape[1], batch, stride), 0x55, dtype=np.int8)
+        side[:, :, :X.shape[2]] = X.transpose(1, 0, 2)
+        out[:, :batch * stride] = torch.from_numpy(side.reshape(X.shape[1], batch * stride)).to("cuda")
+        return out
+
+    step = 4 if which == "C" else 16
+    if which == "A" and N <= 128:
+        lds = [1 << 23]
+        assert item(1 << 23) and item(1 << 31)
+    else:
+        lo, hi = 1 << 14, 1 << 30
+        while hi - lo > step:
+            mid = (lo + hi) // 2 // step * step
+            lo, hi = (mid, hi) if item(mid) else (lo, mid)
+        assert lo * (4 if which == "C" else 1) > 1 << 20 and not item(hi)
+        lds = [lo, hi]
+    try:
+        for ld in lds:
+            s = shape_at(ld)
+            dA, dB = operand(A, s.lda, s.strideA, which == "A"), operand(B, s.ldb, s.strideB, which == "B")
+            dC = torch.zeros((batch, M, s.ldc), dtype=torch.int32, device="cuda")
+            rf, cf = (torch.full((batch * n,), 7, dtype=torch.uint8, device="cuda") for n in (M, N))
+            cnt = torch.full((8,), 99, dtype=torch.int32, device="cuda")
+            rc = ab.abft_gemm(own, dA, dB, dC, ab.ABFT_I8, ab.ABFT_DETECT, s, ab.make_result(rf, cf, cnt, 0.0))
+            assert rc == ab.ABFT_OK, ab.abft_strerror(rc)
+            torch.cuda.synchronize()
+            assert cnt[2].item() == ab.ABFT_CLEAN and not rf.any() and not cf.any(), ld
+            got = dC[:, :, :N].cpu().numpy()
+            assert all(np.array_equal(got[b], P[b].C_stored) for b in range(batch)), ld
+            dC[:, :, :N] = 0
+            assert not dC.any(), ld                          # nothing past a row
+            del dA, dB, dC
+    finally:
+        ab.abft_destroy(own)
 
 
 @pytest.mark.parametrize("dtype", ["i8", "bf16", "f16"])
