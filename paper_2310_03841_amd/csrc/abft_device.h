@@ -35,11 +35,11 @@ template <typename ARGS> __device__ __forceinline__ const ARGS &kernel_args()
 
 // Asks for every 64-byte line of a kernel's arguments at once, first thing.  A launch's arguments lie in memory, and a line that is touched for
 // the first time takes a compute unit some 500 clocks (0.22 us); left alone, the compiler loads each argument where it is used, and the
-// kernels of a small call went through three to five such trips one behind the other.
-template <typename ARGS> __device__ __forceinline__ void fetch_args()
+// kernels of a small call went through three to five such trips one behind the other.  BYTES: of which a kernel reads the first ones only.
+template <typename ARGS, int BYTES = (int)sizeof(ARGS)> __device__ __forceinline__ void fetch_args()
 {
     const __attribute__((address_space(4))) uint32_t *p = (const __attribute__((address_space(4))) uint32_t *)__builtin_amdgcn_kernarg_segment_ptr();
-    constexpr int LINES = ((int)sizeof(ARGS) + 63) / 64;
+    constexpr int LINES = (BYTES + 63) / 64;
     static_assert(LINES <= 16, "one wait for all");
     uint32_t v[16];
 #pragma unroll

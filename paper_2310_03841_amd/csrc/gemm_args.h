@@ -18,6 +18,7 @@ struct GemmArgs {
     int n_big, tiles_m_big, tiles_m_small;        // fast path: 256-row tiles and 128-row tiles
     int n_small, batch;                           // fast path: 128-row tiles per batch item; batch items
     int inj_b, inj_row, inj_col, inj_bit;         // armed accumulator flip (inj_b < 0: none)
+    const uint32_t *bias;                         // layer bias [N] (float / int32 words) or null
     // protected launches: all of these are accumulated with atomics and start at zero
     uint32_t *cc_obs, *rc_obs;                    // observed sums of C        [batch][N], [batch][M]
     double *cc_acc, *rc_acc;                      // general kernel, floating point: what its tiles add to instead
@@ -28,7 +29,6 @@ struct GemmArgs {
     uint32_t *c_max;                              // max|C as stored| as float bits [batch] (with cc_sto)
     int a_given;                                  // a = e^T A and max|A| come from the caller: the pass over A's
                                                   // slabs forms the row dots only, nothing is added to a_sum / a_max
-    const uint32_t *bias;                         // layer bias [N] (float / int32 words) or null
     const uint32_t *b_sum;                        // B e, complete before the launch [batch][K]
     uint32_t *counts;                             // fast kernel, protected: cleared for the check kernel
     BesideArgs beside;

@@ -69,8 +69,15 @@ struct OneArgs {
     int n_extra, n_tiles, aux_off, bias_off;
     PredArgs p;
 };
-template <bool ONE> struct KernelArgs { typedef TileArgs type; };
-template <> struct KernelArgs<true> { typedef OneArgs type; };
+// Unprotected tiles take none of the passes' either, and ask for the lines ahead of what only protected ones read: three of eight.
+struct PlainArgs {
+    int n_tiles, bias_off;
+    GemmArgs g;
+};
+template <bool PROT, bool ONE> struct KernelArgs { typedef TileArgs type; };
+template <> struct KernelArgs<true, true> { typedef OneArgs type; };
+template <> struct KernelArgs<false, false> { typedef PlainArgs type; };
+constexpr int PLAIN_ARGS_READ = offsetof(PlainArgs, g) + offsetof(GemmArgs, cc_obs);
 
 // The sums of a tile's rows and columns by wave column and wave row, of the accumulators and of the stored values, and eight words of maxima.
 constexpr int tile_epi_bytes(int BM, int BN) { return 4 * (BM + BN) * 4 + 8 * 4; }
@@ -91,7 +98,7 @@ template <int ES, int ROWB> __device__ __forceinline__ int kn_swizzle(int k)
 
 // ONE: the whole protected call (predict_pass.h)
 template <int DT, int BM, int BN, int NS, bool PROT, bool TRANSB, bool APASS, bool ONE>
-__global__ __launch_bounds__(256) void gemm_tile_kernel(typename KernelArgs<ONE>::type whole)
+__global__ __launch_bounds__(256) void gemm_tile_kernel(typename KernelArgs<PROT, ONE>::type whole)
 {
     using T = Traits<DT>;
     typedef typename T::acc_t acc_t;
@@ -105,11 +112,12 @@ __global__ __launch_bounds__(256) void gemm_tile_kernel(typename KernelArgs<ONE>
     static_assert((NS - 2) * (GA + GB) < 64, "the wait count is an immediate");
 
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
-    fetch_args<typename KernelArgs<ONE>::type>();
+    typedef typename KernelArgs<PROT, ONE>::type Args;
+    fetch_args<Args, PROT ? (int)sizeof(Args) : PLAIN_ARGS_READ>();
     // ONE: each argument where it is used (a few of those that the call's end needs and all of the tiles' do not fit the scalar registers; and, from the
     // parameter, the compiler asks for some twenty of them ahead of the line above: int8 873 x 249 x 128 7.5 us, 6.9 so).  The others have scalars
     // enough: 197 x 3072 x 768 and its check 10.5 us, 11.0 with each where it is used.
-    const auto &a = ONE ? kernel_args<typename KernelArgs<ONE>::type>() : whole;
+    const Args &a = ONE ? kernel_args<Args>() : whole;
     const GemmArgs &g = a.g;
     const int bz = blockIdx.y;
     if constexpr (ONE) {
@@ -121,7 +129,7 @@ __global__ __launch_bounds__(256) void gemm_tile_kernel(typename KernelArgs<ONE>
             end_predict<DT>(a.p, blockIdx.x, a.n_extra, bz, reinterpret_cast<uint32_t *>(smem));
             return;
         }
-    } else if (PROT) {
+    } else if constexpr (PROT) {
         if (blockIdx.x == 0 && bz == 0 && threadIdx.x < 5) a.counts[threadIdx.x] = 0u;
         const int e = blockIdx.x;
         if (e < a.n_extra) {
@@ -138,7 +146,9 @@ __global__ __launch_bounds__(256) void gemm_tile_kernel(typename KernelArgs<ONE>
     const int wm = wave >> 1, wn = wave & 1;
     const int l32 = lane & 31, lh = lane >> 5;
     int tm, tn;
-    map_tile(PROT ? blockIdx.x - a.n_extra : blockIdx.x, a.n_tiles, g.tiles_m, g.tiles_n, g.group_inv, &tm, &tn);
+    int bid = blockIdx.x;
+    if constexpr (PROT) bid -= a.n_extra;
+    map_tile(bid, a.n_tiles, g.tiles_m, g.tiles_n, g.group_inv, &tm, &tn);
     const int m0 = tm * BM, n0 = tn * BN;
     const int M = g.M, N = g.N, K = g.K;
     const int nslab = (K + KE - 1) / KE;
@@ -285,7 +295,9 @@ __global__ __launch_bounds__(256) void gemm_tile_kernel(typename KernelArgs<ONE>
     // APASS: of the tiles that share rows of A, the one in column s mod tiles_n reduces slab s while it is resident
     // (gemm_apass.h).  Its words of b go straight into LDS ahead of the slabs.
     const int owned = (APASS && tn < nslab) ? (nslab - tn + g.tiles_n - 1) / g.tiles_n : 0;
-    uint32_t *b_lds = reinterpret_cast<uint32_t *>(smem + a.aux_off), *col_lds = b_lds + owned * KE;
+    int aux_off = 0;
+    if constexpr (APASS) aux_off = a.aux_off;
+    uint32_t *b_lds = reinterpret_cast<uint32_t *>(smem + aux_off), *col_lds = b_lds + owned * KE;
     APassState<DT> ast;
     ast.rdot = T::zero(); ast.amax = 0.f;
     int next_own = tn, own_at = 0;
@@ -588,8 +600,11 @@ static hipError_t launch_one(HostArgs &a, int batch, hipStream_t st)
     if constexpr (ONE) {
         const OneArgs k = {a.g, a.n_extra, a.n_tiles, a.aux_off, a.bias_off, a.p};
         hipLaunchKernelGGL(kern, grid, dim3(256), smem, st, k);
-    } else {
+    } else if constexpr (PROT) {
         hipLaunchKernelGGL(kern, grid, dim3(256), smem, st, (const TileArgs &)a);
+    } else {
+        const PlainArgs k = {a.n_tiles, a.bias_off, a.g};
+        hipLaunchKernelGGL(kern, grid, dim3(256), smem, st, k);
     }
     return hipGetLastError();
 }
