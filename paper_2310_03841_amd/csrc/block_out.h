@@ -37,12 +37,46 @@ template <int DT> __device__ __forceinline__ float unpack_hi(uint32_t w)
 // lane and lane ^ 8, makes it eight rows of 128 bytes (segments of 64 bytes, off their 64-byte boundaries
 // as rows of C usually are, wrote 1024 x 577 x 577 in 584 us, unprotected).
 template <int DT> constexpr int out_passes() { return Traits<DT>::OS == 4 ? 4 : 2; }
-// a lane's row of pass 0 (pass p: 32 / passes rows on) and its first column
-template <int DT> __device__ __forceinline__ int out_row(int lane) { return lane & (Traits<DT>::OS == 4 ? 7 : 15); }
-template <int DT> __device__ __forceinline__ int out_col(int lane)
+// QUADS, int32 C of unprotected tiles: four neighbouring lanes hold 64 bytes of a row, which a store takes as one piece; in the other order
+// neighbours lie in different rows, and a store of 1 KB is 64 pieces.  Its exchanges between neighbours are 24 vector instructions more, which hide
+// behind the stores where there are no sums to form.  us, graph replays, other order / so: int8 197 x 768 x 768 4.09 / 3.81, 1576 x 768 x 768
+// 5.96 / 5.53, 64 x 64 x 64 3.09 / 2.86.  Protected tiles 0.98 to 1.03 and items 1.00 to 1.01 of their time, so they keep the other.
+// a lane's row of pass 0, the rows from one pass to the next, and its first column
+template <int DT, bool QUADS = false> __device__ __forceinline__ int out_row(int lane) { return lane & (QUADS ? 28 : Traits<DT>::OS == 4 ? 7 : 15); }
+template <int DT, bool QUADS = false> constexpr int out_step() { return QUADS ? 1 : 32 / out_passes<DT>(); }
+template <int DT, bool QUADS = false> __device__ __forceinline__ int out_col(int lane)
 {
-    if constexpr (Traits<DT>::OS == 4) return 16 * ((lane >> 3) & 1) + 8 * ((lane >> 4) & 1) + 4 * (lane >> 5);
+    if constexpr (QUADS) return 4 * (lane & 3) + 16 * (lane >> 5);
+    else if constexpr (Traits<DT>::OS == 4) return 16 * ((lane >> 3) & 1) + 8 * ((lane >> 4) & 1) + 4 * (lane >> 5);
     else return 16 * ((lane >> 4) & 1) + 8 * (lane >> 5);
+}
+// lo: x in lanes with `up` clear, in the others the y of the lane that CTRL pairs with theirs; hi: what is left of both
+template <int CTRL> __device__ __forceinline__ void swap_lanes(uint32_t x, uint32_t y, bool up, uint32_t *lo, uint32_t *hi)
+{
+    const uint32_t xs = (uint32_t)dpp_get<CTRL>((int)x), ys = (uint32_t)dpp_get<CTRL>((int)y);
+    *lo = up ? ys : x;
+    *hi = up ? y : xs;
+}
+// A lane's row is bits 0..4 of its number and its columns 16 q1 + 8 q0 + 4 (lane >> 5) + j (word 8 q1 + 4 q0 + j).  q1 changes place with bit 5, what was
+// bit 5 with bit 0, q0 with bit 1: the low two bits of the row number the passes.
+__device__ __forceinline__ void turn_quads(const uint32_t *w, i32x4 (&out)[4], int lane)
+{
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        uint32_t t[2][2], even[2], odd[2], r[4];             // t: [what was bit 5][q0]
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            auto p = __builtin_amdgcn_permlane32_swap(w[4 * q + j], w[8 + 4 * q + j], false, false);
+            t[0][q] = p[0];
+            t[1][q] = p[1];
+        }
+#pragma unroll
+        for (int q = 0; q < 2; ++q) swap_lanes<0xB1>(t[0][q], t[1][q], (lane & 1) != 0, &even[q], &odd[q]);
+        swap_lanes<0x4E>(even[0], even[1], (lane & 2) != 0, &r[0], &r[2]);
+        swap_lanes<0x4E>(odd[0], odd[1], (lane & 2) != 0, &r[1], &r[3]);
+#pragma unroll
+        for (int p = 0; p < 4; ++p) out[p][j] = (int)r[p];
+    }
 }
 template <int DT> __device__ __forceinline__ void turn_block(const uint32_t *w, i32x4 (&out)[out_passes<DT>()])
 {

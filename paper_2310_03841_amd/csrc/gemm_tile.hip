@@ -392,9 +392,10 @@ __global__ __launch_bounds__(256) void gemm_tile_kernel(typename KernelArgs<PROT
     const bool inj_here = g.inj_b == bz && g.inj_row >= m0 && g.inj_row < m0 + BM && g.inj_col >= n0 && g.inj_col < n0 + BN;
     const bool inside = m0 + BM <= M && n0 + BN <= N;
     float cmax_s = 0.f;
-    constexpr int NP = out_passes<DT>(), RPP = 32 / NP;                  // passes of a block's stores, rows of one
+    constexpr bool QUADS = T::IS_INT && !PROT;
+    constexpr int NP = out_passes<DT>(), RPP = out_step<DT, QUADS>();    // passes of a block's stores, rows from one to the next
     // this lane's 16 bytes of pass 0 of the wave's first block
-    const int orow = m0 + wm * TM + out_row<DT>(lane), ocol = n0 + wn * TN + out_col<DT>(lane);
+    const int orow = m0 + wm * TM + out_row<DT, QUADS>(lane), ocol = n0 + wn * TN + out_col<DT, QUADS>(lane);
     uint8_t *const dst0 = g.C + ((long)bz * g.sC + (long)orow * g.ldc + ocol) * OS;
     const long pass_bytes = (long)RPP * g.ldc * OS;
     // what is left of a lane's 16 bytes at the right edge is the same for all lanes there
@@ -447,7 +448,8 @@ __global__ __launch_bounds__(256) void gemm_tile_kernel(typename KernelArgs<PROT
                 uint32_t w[16];
 #pragma unroll
                 for (int i = 0; i < 16; ++i) w[i] = (uint32_t)v[i];
-                turn_block<DT>(w, out);
+                if constexpr (QUADS) turn_quads(w, out, lane);
+                else turn_block<DT>(w, out);
             } else {
                 uint32_t w[8];
                 pack_block<DT>(v, w);

@@ -2674,3 +2674,34 @@ def test_right_edges_of_c(ctx_items, dtype, N, M, batch):
     check_clean(run, oracle_items(dtype, A, B, True))
     pad = run.dC.cpu().numpy()[:, :, N:]
     assert (pad == (0x5A5A5A5A if dtype == "i8" else 0x5A5A)).all()
+
+
+@pytest.mark.parametrize("M,N,K,trans_b", [(1, 1, 16, True), (31, 65, 80, False), (65, 66, 80, True), (64, 128, 128, False), (97, 67, 200, True), (197, 768, 768, True),
+                                           (130, 130, 300, False), (1000, 1003, 500, True), (1025, 513, 300, False), (12600, 1399, 1030, True)])
+def test_unprotected_int8_tiles_store_what_protected_ones_do(ctx_big, M, N, K, trans_b):
+    """Unprotected tiles turn their int32 C into rows in an order of their own (tiles of 64 and 128, inside and over every edge): the same C, with
+    a bias and with an armed flip too, and nothing past the end of a row."""
+    A, B = gen.gen_operands("i8", M, N, K, 961, 962, trans_b=trans_b, b_kind="act")
+    run = Run(ctx_big, "i8", A, B, trans_b)
+    bias = torch.arange(N, dtype=torch.int32, device="cuda") * 77777 - 5
+
+    def three():
+        out = []
+        for kind in ("plain", "bias", "flip"):
+            run.dC.fill_(0x5A5A5A5A)
+            if kind == "flip":
+                run.inject(0, M - 1, N - 1, 30, ab.ABFT_INJECT_ACCUMULATOR)
+            if kind == "bias":
+                run.gemm_bias(bias, mode)
+            else:
+                run.gemm(mode)
+            out.append(run.dC.clone())
+        return out
+
+    mode = ab.ABFT_DETECT
+    want = three()
+    mode = ab.ABFT_OFF
+    got = three()
+    for w, g in zip(want, got):
+        assert torch.equal(w, g)
+    assert (got[0][:, :, N:] == 0x5A5A5A5A).all() and not torch.equal(got[0], got[2])
