@@ -2583,7 +2583,7 @@ def test_repair_of_many_flags_in_few_tiles(ctx, dtype, rows):
 @pytest.mark.parametrize("M,batch", [(32704, 1), (32736, 1), (700, 3)])
 def test_repair_with_the_list_from_either_kernel(M, batch):
     """Up to 32768 flags of one problem the recompute finds its tiles itself, beyond and for batches a kernel lists them; one after the
-    other in one context, so that each finds the list as the other leaves it."""
+    other in one context, each correction followed by one inside a GEMM."""
     own = ab.abft_create(max_rows=32768, max_cols=256, max_depth=256, max_batch=4)
     try:
         for m, b in ((M, batch), (300, 1), (M, batch), (300, 2)):
@@ -2598,6 +2598,143 @@ def test_repair_with_the_list_from_either_kernel(M, batch):
             assert run.cnt()[2] == ab.ABFT_CLEAN and run.cnt()[3] == 1 and np.array_equal(run.C(), C)
             run.gemm(ab.ABFT_DETECT_CORRECT)
             assert run.cnt()[2] == ab.ABFT_CLEAN and np.array_equal(run.C(), C)
+    finally:
+        ab.abft_destroy(own)
+
+
+def _spoil(run, at, bits):
+    for s, (b, i, j) in enumerate(at):
+        run.inject(b, i, j, bits[s % len(bits)])
+
+
+@pytest.mark.parametrize("M2,batch2", [(200, 2), (32740, 1)])
+def test_a_list_left_behind_is_cleared(M2, batch2):
+    """A correction that finds its tiles itself leaves its list, and whether it was too long, in the context; one whose tiles a kernel lists comes right
+    behind it, with no other correction in between, and finds neither."""
+    own = ab.abft_create(max_rows=40000, max_cols=1024, max_depth=1024, max_batch=4)
+    N, K = 64, 64
+
+    def problem(M, batch, seed):
+        A, B = gen.gen_operands("i8", M, N, K, seed, seed + 1, trans_b=True, batch=batch)
+        run = Run(own, "i8", A, B, True)
+        run.gemm(ab.ABFT_DETECT)
+        return run, run.C().copy()
+
+    try:
+        for long_list in (False, True, False):
+            for inside in (False, True):
+                run, C = problem(70 * 32, 1, 971)
+                _spoil(run, [(0, 32 * s + 5, 3) for s in range(70 if long_list else 9)], range(20))
+                run.verify()
+                run.correct()
+                cnt = run.cnt()
+                assert (cnt[2], cnt[3], cnt[0]) == ((ab.ABFT_TOO_MANY, 64, 6) if long_list else (ab.ABFT_CLEAN, 9, 0))
+                run, C = problem(M2, batch2, 973)
+                if inside:
+                    run.inject(batch2 - 1, M2 - 1, N - 1, 7, ab.ABFT_INJECT_ACCUMULATOR)
+                    run.gemm(ab.ABFT_DETECT_CORRECT)
+                else:
+                    run.inject(batch2 - 1, M2 - 1, N - 1, 7)
+                    run.verify()
+                    run.correct()
+                cnt = run.cnt()
+                assert (cnt[0], cnt[1], cnt[2], cnt[3], cnt[4]) == (0, 0, ab.ABFT_CLEAN, 1, ab.ABFT_LOCALISED) and np.array_equal(run.C(), C)
+    finally:
+        ab.abft_destroy(own)
+
+
+@pytest.mark.parametrize("dtype", ["i8", "bf16"])
+@pytest.mark.parametrize("rows,cols", [(1, 16), (1, 17), (16, 1), (17, 1), (4, 4)])
+def test_repair_where_parts_become_whole_tiles(ctx, dtype, rows, cols):
+    """Sixteen tiles are recomputed in parts, seventeen whole."""
+    M, N, K = 17 * 32 + 3, 17 * 32 + 5, 200
+    A, B = gen.gen_operands(dtype, M, N, K, 981, 982, trans_b=True)
+    run = Run(ctx, dtype, A, B, True)
+    run.gemm(ab.ABFT_DETECT)
+    C = run.C().copy()
+    _spoil(run, [(0, 33 * (s % rows), 33 * (s % cols)) for s in range(max(rows, cols))], [9] if dtype == "i8" else [14])
+    run.verify()
+    assert run.cnt()[0] == rows and run.cnt()[1] == cols
+    run.correct()
+    cnt = run.cnt()
+    assert (cnt[0], cnt[1], cnt[2], cnt[3]) == (0, 0, ab.ABFT_CLEAN, rows * cols) and np.array_equal(run.C(), C)
+
+
+@pytest.mark.parametrize("dtype", ["i8", "bf16"])
+def test_repair_of_more_tiles_than_are_recomputed(ctx, dtype):
+    """Flips on a diagonal of 17 x 17 tiles: 289 candidates, of which the first 256, row by row, are recomputed; the next correction does the rest."""
+    M, N, K = 17 * 32, 17 * 32, 72
+    A, B = gen.gen_operands(dtype, M, N, K, 991, 992, trans_b=True)
+    run = Run(ctx, dtype, A, B, True)
+    run.gemm(ab.ABFT_DETECT)
+    C = run.C().copy()
+    at = [(0, 32 * s + s, 32 * s + 31 - s) for s in range(17)]
+    _spoil(run, at, [11] if dtype == "i8" else [14])
+    run.verify()
+    assert run.cnt()[0] == 17 and run.cnt()[1] == 17
+    run.correct()
+    cnt, got = run.cnt(), run.C()
+    assert cnt[2] == ab.ABFT_TOO_MANY and cnt[3] == 256 and cnt[0] == 2 and cnt[1] == 2
+    assert sorted(map(tuple, np.argwhere(got != C))) == at[15:]
+    run.correct()
+    assert run.cnt()[2] == ab.ABFT_CLEAN and run.cnt()[3] == 4 and np.array_equal(run.C(), C)
+
+
+@pytest.mark.parametrize("dtype", ["i8", "bf16"])
+@pytest.mark.parametrize("captured,eager", [((300, 1), (130, 3)), ((130, 3), (300, 1)), ((300, 1), (450, 1))])
+def test_corrections_can_be_captured_in_a_graph(dtype, captured, eager):
+    """GEMM, a flip of stored C, verify and correct in one graph, replayed, with an eager correction of another problem in the same context between the
+    replays: either's list is the other's to clear."""
+    own = ab.abft_create(max_rows=1024, max_cols=1024, max_depth=1024, max_batch=4)
+    N, K, bit = 100, 96, 9 if dtype == "i8" else 14
+
+    def problem(M, batch):
+        A, B = gen.gen_operands(dtype, M, N, K, 995, 996, trans_b=True, batch=batch, b_kind="act")
+        return Run(own, dtype, A, B, True), batch
+
+    def all_of(run, b, i, j):
+        res = run.result()
+        return (ab.abft_gemm(own, run.dA, run.dB, run.dC, run.code, ab.ABFT_DETECT, run.shape, res),
+                ab.abft_inject(own, run.dC, run.code, run.shape, b, i, j, bit, ab.ABFT_INJECT_STORED_C),
+                ab.abft_verify(own, run.dC, run.code, run.shape, res),
+                ab.abft_correct(own, run.dA, run.dB, run.dC, run.code, run.shape, res))
+
+    def check(run, C, tag):
+        torch.cuda.synchronize()
+        cnt = run.cnt()
+        assert (cnt[0], cnt[1], cnt[2], cnt[3], cnt[4]) == (0, 0, ab.ABFT_CLEAN, 1, ab.ABFT_LOCALISED), (tag, cnt)
+        assert np.array_equal(run.C(), C), tag
+
+    try:
+        (run, batch), (other, batch_o) = problem(*captured), problem(*eager)
+        place = {}
+        for r, b in ((run, batch), (other, batch_o)):
+            r.gemm(ab.ABFT_DETECT)
+            C = r.C().copy()
+            i, j = (3, 4) if dtype == "i8" else map(int, np.argwhere(np.abs(orc.decode(C[b - 1], dtype)) < 1.0)[0])
+            place[r] = (b - 1, i, j), C
+        for r in (run, other):
+            assert all(rc == ab.ABFT_OK for rc in all_of(r, *place[r][0]))           # eager first: kernel attributes
+            check(r, place[r][1], "first")
+        graph, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+        side.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(side):
+            with torch.cuda.graph(graph, stream=side):
+                rcs = all_of(run, *place[run][0])
+        torch.cuda.current_stream().wait_stream(side)
+        assert all(rc == ab.ABFT_OK for rc in rcs)
+        for rep in range(4):
+            run.dC.fill_(0)
+            run.counts.fill_(99)
+            torch.cuda.synchronize()
+            graph.replay()
+            check(run, place[run][1], ("replay", rep))
+            assert all(rc == ab.ABFT_OK for rc in all_of(other, *place[other][0]))
+            check(other, place[other][1], ("eager", rep))
+            if rep == 1:
+                graph.replay()
+                check(run, place[run][1], ("replay again", rep))
+        del graph
     finally:
         ab.abft_destroy(own)
 
