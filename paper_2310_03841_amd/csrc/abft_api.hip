@@ -41,7 +41,7 @@ struct abft_ctx {
     bool vobs_captured;     // ... and they were formed by a call enqueued under capture
     const void *vobs_C;     // the stored C the re-summed vectors belong to (with its ldc and batch stride)
     int64_t vobs_ldc, vobs_strideC;
-    bool list_dirty;        // the tile list's counters may be non-zero (a correction failed half way)
+    bool list_dirty;        // the tile list's counters may be non-zero: a correction failed half way, or was one that leaves its list (correct_finds)
     int b_dt, pred_dt;
     const void *given_a, *given_amax;   // abft_supply_a: a = e^T A and max|A| for the next call with ABFT_A_CHECKSUM_GIVEN
     hipEvent_t done_event;              // abft_gemm_done_event: recorded behind every GEMM kernel (null: none)

@@ -147,14 +147,15 @@ hipError_t launch_verify_sums(int dt, const void *C, const Shape &s, const Works
 // the rows and columns of the recomputed tiles are summed again, in place (stale_words, zero_ptr unused)
 // skip_if_clean: when no tile was listed (the check before found nothing to recompute) the re-sum
 // of stored C and the final compare do nothing: flags and counts stay as that check wrote them
-// clear_list: the tile list's counters may be non-zero (the final compare of a correction leaves
-// them at zero, so only after a call that failed half way)
-// Whether a correction leaves its list of tiles behind: whatever lists tiles next clears it first.
-bool correct_finds(const Shape &s);
+// clear_list: the tile list's counters may be non-zero, after a call that failed half way or a targeted correction that found its tiles itself
+// (correct_finds): the final compare of any other leaves them at zero
 hipError_t launch_correct(int dt, const void *A, const void *B, void *C, const Shape &s,
                           const Workspace &w, const Verdict &v, bool with_sto, bool clear_list, bool targeted,
                           size_t stale_words, uint32_t *zero_ptr, size_t zero_words, hipStream_t st,
                           bool skip_if_clean = false);
+// Whether the recompute of a correction finds its tiles itself.  It writes the list anew whatever was there; a targeted one leaves it, and whatever
+// lists tiles next clears it first.
+bool correct_finds(const Shape &s);
 // integers: repairs a single flagged element per batch item from the checksums alone
 hipError_t launch_arith_fix(void *C, const Shape &s, const Workspace &w, const Verdict &v, hipStream_t st);
 // stored: the sums of the last re-sum of stored C instead of the epilogue's

@@ -171,7 +171,7 @@ struct CmpArgs {
     uint8_t *row_flag, *col_flag;
     uint32_t *counts;
     uint32_t *ticket;     // after a correction: [3]: ticket, flagged rows, flagged cols (self-cleaning)
-    uint32_t *fix_count;  // non-null after a correction: [0] tiles listed, [1] overflow (cleared after use)
+    uint32_t *fix_count;  // non-null after a correction: [0] tiles listed, [1] overflow (cleared after use, but with counts_ready)
     const int32_t *fix_tiles;          // after a correction: the tiles it recomputed
     uint32_t *cc_sto, *rc_sto;         // non-null: stored-side sums of the GEMM (floating point)
     uint32_t *zero_ptr;   // region every block helps to clear: the re-summing region not in use,

@@ -66,7 +66,7 @@ __global__ __launch_bounds__(COLS_NT, TPW == 1 && !STO ? 4 : 2) void item_cols_k
     typedef typename T::accv_t accv_t;
     typedef FragB<DT, TRANSB, 0> Frag;
     fetch_args<ItemArgs>();
-    constexpr int ES = T::ES, OS = T::OS;
+    constexpr int ES = T::ES;
     constexpr int R = TPW == 1 ? 2 : 1;         // blocks of rows at a time
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);

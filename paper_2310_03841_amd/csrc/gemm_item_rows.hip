@@ -56,7 +56,7 @@ __global__ __launch_bounds__(512, TPW == 2 && !STO ? 4 : 2) void item_rows_kerne
     typedef typename T::acc_t acc_t;
     typedef typename T::accv_t accv_t;
     fetch_args<ItemArgs>();
-    constexpr int ES = T::ES, OS = T::OS;
+    constexpr int ES = T::ES;
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
     const int lane_id = threadIdx.x & 63, nt = blockDim.x, nw = nt >> 6;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
