@@ -32,7 +32,7 @@ def kernels(tmp_path_factory):
                 notes = subprocess.run([READELF, "--notes", str(path)], capture_output=True, text=True, check=True).stdout
                 for text in re.split(r"\n  - (?=\.agpr_count)", notes)[1:]:
                     name = re.search(r"\.name:\s+(_Z\S+)", text).group(1)
-                    out[name] = {k: int(re.search(rf"\.{k}:\s+(\d+)", text).group(1)) for k in ("agpr_count", "kernarg_segment_size", "vgpr_spill_count")}
+                    out[name] = {k: int(re.search(rf"\.{k}:\s+(\d+)", text).group(1)) for k in ("agpr_count", "kernarg_segment_size", "sgpr_spill_count", "vgpr_spill_count")}
             p += length
         at += 24
     return out
@@ -56,3 +56,19 @@ def test_unprotected_tiles_take_few_arguments(kernels):
     for t, k in of(kernels, "gemm_tile_kernel"):
         sizes[bool(t[4])].add(k["kernarg_segment_size"])
     assert max(sizes[False]) <= 5 * 64, sizes
+
+
+def test_fast_tiles_keep_their_accumulators_in_vector_registers(kernels):
+    """The epilogue reads accumulators where they are; a built-in or an asm that asks for an accumulation register makes the compiler split a lane's
+    registers, and each accumulator is moved before it is used.  Only tiles of both heights with stored sums (STO 2) are built that way."""
+    for (dt, mode, sto), k in of(kernels, "gemm_fast_kernel"):
+        assert (k["agpr_count"] == 0) == (sto != 2), ((dt, mode, sto), k)
+        assert k["vgpr_spill_count"] == 0, ((dt, mode, sto), k)
+
+
+@pytest.mark.parametrize("kernel", ["gemm_fast_kernel", "item_rows_kernel", "item_cols_kernel"])
+def test_phases_read_their_own_arguments(kernels, kernel):
+    """Arguments taken from the parameter are held across the loop over tiles or items: 60 to 290 scalars more than there are, which live in lanes of vector
+    registers.  Read by phase, the most is 15."""
+    for t, k in of(kernels, kernel):
+        assert k["sgpr_spill_count"] <= 24 and k["vgpr_spill_count"] <= 1, (t, k)
