@@ -38,10 +38,10 @@ HBM_PEAK_GBS = 8000.0
 
 # HBM bytes per GEMM-kernel launch from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs, scaled by the
 # same counters on a plain copy kernel (see profiles/); None until measured for this kernel version.
-MEASURED_TRAFFIC_BYTES = int((58870.0 / 0.5 + 77740.0) * 1024)   # profiles/gemm_fast_bf16_fc1_b64_hbm_traffic.txt
+MEASURED_TRAFFIC_BYTES = int((59470.0 / 0.5 + 77770.0) * 1024)   # profiles/gemm_fast_bf16_fc1_b64_hbm_traffic.txt
 # average duration of the same kernel under rocprofv3 --kernel-trace --stats (dispatch to completion, without
 # the launch latency that HIP events around a kernel include); profiles/gemm_fast_bf16_fc1_b64_kernel_stats.txt
-PROFILED_KERNEL_US = 64.29
+PROFILED_KERNEL_US = 61.28
 
 
 def log(*a):
