@@ -9,7 +9,7 @@
 //
 // Measured (384 items 197 x 197 x 64 bf16, Q K^T of 32 images; floor 9.8 us): 32.0 us with four waves per item, C
 // through an LDS stage and the sums along K in vector instructions, 21.2 so, 18.5 since the phases read their own arguments (item_args), 12.9
-// unprotected (before: 18.0).  A compute unit with two items is bound by its vector instructions: reading the main loop's fragments a piece ahead, or
+// unprotected (before: 18.0).  An item takes what its waves' instructions take (a SIMD issues one in 0.44 of the cycles): reading the main loop's fragments a piece ahead, or
 // dealing the pass over B to all waves, which each cost some more of them, gained nothing (21.4, and 2 to 4 % slower elsewhere).
 // int8 1024 x 577 x 577 x 64 (1.44 GB, floor 285 us): 432 us, so 378 (on another
 // card 412 and 349); bound by the stores of C, whose rows
