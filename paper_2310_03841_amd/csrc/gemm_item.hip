@@ -13,8 +13,8 @@ constexpr int ITEM_MAX_N = 640, ITEM_MAX_M = 1024, ITEM_MAX_THREADS = 512;
 
 // Offsets inside an item are 32-bit numbers (ItemStage, ItemOut): the rows that batches of loads reach, past the last one too, and the row blocks of C
 // must end below 2^31 bytes, with a row to spare for what a lane adds along one.  That bounds rows times their distance: up to 1024 rows reached may be 2 MB
-// apart (heads side by side, q, k and v of 16 heads x 64 in bf16: 340 images; a limit of 512 KB sent 86 images to the tiles, at twice the time).
-// Wider ones are for the tiles.  The kernel by rows reads A by whole addresses.
+// apart (heads side by side, q, k and v of 16 heads x 64 in bf16: 340 images).  Wider ones are for the tiles; 86 images there / here, us: Q K^T 577 x 577 x 64
+// 1006 / 355, unprotected 643 / 332, attn V 646 / 340, unprotected 287 / 298.  The kernel by rows reads A by whole addresses.
 static bool item_offsets_fit(int dt, const Shape &s, const ItemArgs &g)
 {
     const long es = elem_size(dt);
