@@ -183,7 +183,8 @@ int abft_encode_b(abft_ctx *ctx, const void *B, abft_dtype dtype, const abft_sha
  * A and B must stay unchanged until the last of these kernels has run.
  * A batch of at least 64 small problems (per-head attention products: N <= 640, M <= 1024; a row
  * of K at most 1600 bytes for N <= 128, 384 for N <= 256, 256 beyond; operands and vectors of one item
- * fitting the local memory of a compute unit; with ABFT_STORED_SUMS only up to N = 256) is one kernel
+ * fitting the local memory of a compute unit; rows at most some 2 MB apart, more where an item has few;
+ * with ABFT_STORED_SUMS only up to N = 256) is one kernel
  * instead: one workgroup per batch item forms b, a, both predictions and both observed sums from on-chip
  * operands and compares them itself.  (Wide items that fill that memory need 104 and more of them.)
  * mode ABFT_OFF ignores `r` (may be NULL).  Flags and counts are overwritten. */
